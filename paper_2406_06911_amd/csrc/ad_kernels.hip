@@ -2268,43 +2268,56 @@ ad_status launch_attention_frames(int dtype, const void* q, const void* k, const
 }
 
 // =================================================================================================
-// GroupNorm (+SiLU), NHWC, two launches.  Pass 1: every workgroup reduces a run of pixels of one source to
-// per-channel (sum, sum of squares) with fully coalesced row reads and folds the channels of each group in a
-// fixed order: one (sum, sumsq) pair per (source, sample, pixel chunk, group).  Pass 2: every workgroup first
-// folds those pairs of its sample in double precision (a few KiB, L2-resident) into mean and 1/std per group,
-// then applies y = silu(x * scale + shift) to its run of pixels.  No atomics, no fences: the result does not
-// depend on scheduling.
+// GroupNorm (+SiLU), NHWC.  Maps whose groups fit a workgroup's registers take one launch (k_gn_group below), larger ones two.
+// Pass 1: every workgroup reduces a run of pixels of one source to per-channel (sum, sum of squares) with fully
+// coalesced row reads, eight rows in flight per thread, and folds the channels of each group in a fixed order: one
+// (sum, sumsq) pair per (source, sample, pixel chunk, group); both sources of a concatenation in one launch.  Pass 2:
+// every workgroup first folds those pairs of its sample in double precision (a few KiB, L2-resident) into mean and 1/std
+// per group, then applies y = silu(x * scale + shift) to its run of pixels.  No atomics, no fences: the result does not
+// depend on scheduling.  Both passes are bound by the latency of a launch (3.5 us for any map) and of the memory system
+// rather than by bandwidth at these sizes: 96x96x320, two samples, 17.3 us for 35 MB (18.9 with 64 chunks, four rows in
+// flight and a serial fold of the channels); 96x96x(640+320) 28.7 us (42.3 with a launch per source).
 // =================================================================================================
 constexpr int kGnMaxChunks = 64;
-constexpr int kGnMaxChannels = 4096;      // channels of one source (LDS staging of the per-channel sums)
 constexpr int kGnMaxGroups = 256;
 
-static int gn_chunks(int hw) {
-  int n = hw / 8;
-  return n < 1 ? 1 : (n > kGnMaxChunks ? kGnMaxChunks : n);
+// pixel chunks of the statistics pass: 64, or 128 (a workgroup on every CU with two samples) where the partial sums of both sources
+// still fit the library's own 512 KiB array and the caller's scratch (sized by channels, hence two channels a group)
+constexpr size_t kStaticGnBytes = 512 * 1024;
+static int gn_chunks(int batch, int hw, int groups, int c) {
+  const int most = c >= 2 * groups && (size_t)2 * batch * 128 * groups * 2 * sizeof(float) <= kStaticGnBytes ? 128 : 64;
+  const int n = hw / 8;
+  return n < 1 ? 1 : (n > most ? most : n);
 }
 
-// gpart layout: [source 0/1][sample][chunk][group][2]
+// gpart layout: [source 0/1][sample][chunk][group][2]; blockIdx.z = source
 template <typename T>
-__global__ __launch_bounds__(256) void k_gn_partial(const T* __restrict__ src, int cs, int hw, int nchunk, int groups, int cpg,
-                                                    int coff, float* __restrict__ gpart) {
+__global__ __launch_bounds__(256) void k_gn_partial(const T* __restrict__ src0, const T* __restrict__ src1, int c0, int c1, int hw,
+                                                    int nchunk, int groups, int cpg, size_t src_stride, float* __restrict__ gpart) {
   typedef typename Vec<T>::type V;
   constexpr int VN = Vec<T>::N;
-  __shared__ float red[256 * 2 * VN];
-  __shared__ float csum[kGnMaxChannels * 2];
+  __shared__ float2 red[256 * VN];
+  __shared__ float2 fold[256];
   const int chunk = blockIdx.x, b = blockIdx.y, tid = threadIdx.x;
+  const T* src = blockIdx.z ? src1 : src0;
+  const int cs = blockIdx.z ? c1 : c0, coff = blockIdx.z ? c0 : 0;
   const int p0 = (int)((long long)hw * chunk / nchunk), p1 = (int)((long long)hw * (chunk + 1) / nchunk);
   const int nv = cs / VN;
   const int cvb = nv < 256 ? nv : 256;      // column vectors handled per pass
   const int pl = 256 / cvb;                 // pixel lanes
   const int cv = tid % cvb, lanep = tid / cvb;
+  // channels -> groups: thread (group, part) adds every parts-th channel of its group, over the pixel lanes in order; a group may
+  // extend into the other source, which adds its own pair
+  const int parts = 256 / groups, g = tid / parts, part = tid - g * parts;
+  const int lo = max(g * cpg, coff) - coff, hi = g < groups ? min((g + 1) * cpg, coff + cs) - coff : 0;
+  float gs = 0.f, gq = 0.f;
   for (int cb = 0; cb < nv; cb += cvb) {
     float s[VN], q[VN];
 #pragma unroll
     for (int e = 0; e < VN; ++e) { s[e] = 0.f; q[e] = 0.f; }
     const bool on = lanep < pl && cb + cv < nv;
     if (on) {
-      constexpr int UN = 4;                     // rows in flight per thread; summed in row order
+      constexpr int UN = 8;                     // rows in flight per thread; summed in row order
       const T* sp = src + (size_t)b * hw * cs + (size_t)(cb + cv) * VN;
       for (int p = p0 + lanep; p < p1; p += pl * UN) {
         V v[UN];
@@ -2319,36 +2332,29 @@ __global__ __launch_bounds__(256) void k_gn_partial(const T* __restrict__ src, i
         }
       }
     }
-    __syncthreads();
+    if (cb > 0) __syncthreads();                // the previous block of channels has been folded
 #pragma unroll
-    for (int e = 0; e < VN; ++e) { red[(tid * VN + e) * 2] = s[e]; red[(tid * VN + e) * 2 + 1] = q[e]; }
+    for (int e = 0; e < VN; ++e) red[e * 256 + tid] = make_float2(s[e], q[e]);
     __syncthreads();
-    if (lanep == 0 && cb + cv < nv) {
-#pragma unroll
-      for (int e = 0; e < VN; ++e) {
-        float ts = 0.f, tq = 0.f;
-        for (int j = 0; j < pl; ++j) { ts += red[((j * cvb + cv) * VN + e) * 2]; tq += red[((j * cvb + cv) * VN + e) * 2 + 1]; }
-        const int c = (cb + cv) * VN + e;
-        csum[c * 2] = ts; csum[c * 2 + 1] = tq;
+    const int c_end = min(hi, min(nv, cb + cvb) * VN);
+    for (int j = 0; j < pl; ++j)
+      for (int c = max(lo, cb * VN) + part; c < c_end; c += parts) {
+        const float2 v = red[(c % VN) * 256 + j * cvb + c / VN - cb];
+        gs += v.x; gq += v.y;
       }
-    }
   }
+  fold[tid] = make_float2(gs, gq);
   __syncthreads();
-  // channels -> groups, in channel order; a group may extend into the other source, which adds its own pair
-  float* dst = gpart + ((size_t)b * nchunk + chunk) * groups * 2;
-  for (int g = tid; g < groups; g += 256) {
-    const int lo = max(g * cpg, coff) - coff, hi = min((g + 1) * cpg, coff + cs) - coff;
-    if (lo >= hi) continue;
-    float ts = 0.f, tq = 0.f;
-    for (int c = lo; c < hi; ++c) { ts += csum[c * 2]; tq += csum[c * 2 + 1]; }
-    dst[g * 2] = ts; dst[g * 2 + 1] = tq;
+  if (part == 0 && lo < hi) {
+    for (int j = 1; j < parts; ++j) { gs += fold[tid + j].x; gq += fold[tid + j].y; }
+    *(float2*)(gpart + blockIdx.z * src_stride + (((size_t)b * nchunk + chunk) * groups + g) * 2) = make_float2(gs, gq);
   }
 }
 
 template <typename T>
 __global__ __launch_bounds__(256) void k_gn_apply(const T* __restrict__ src0, const T* __restrict__ src1, int c0, int c1, int hw,
                                                   int rows_per_block, int nchunk, int groups, const float* __restrict__ gpart,
-                                                  size_t src_stride, const float* __restrict__ gamma,
+                                                  size_t src_stride, FastDiv div_cpg, const float* __restrict__ gamma,
                                                   const float* __restrict__ beta, float eps, int silu, T* __restrict__ out) {
   typedef typename Vec<T>::type V;
   constexpr int VN = Vec<T>::N;
@@ -2362,11 +2368,17 @@ __global__ __launch_bounds__(256) void k_gn_apply(const T* __restrict__ src0, co
     const int g = g0 + tid % (groups < 256 ? groups : 256), part = tid / (groups < 256 ? groups : 256);
     double s = 0.0, q = 0.0;
     if (g < groups && part < parts) {
-      const bool in0 = g * cpg < c0, in1 = (g + 1) * cpg > c0;
-      for (int ch = part; ch < nchunk; ch += parts) {
-        const size_t o = (((size_t)b * nchunk + ch) * groups + g) * 2;
-        if (in0) { s += gpart[o]; q += gpart[o + 1]; }
-        if (in1) { s += gpart[src_stride + o]; q += gpart[src_stride + o + 1]; }
+      // (both sources only where the group straddles them)
+      for (int z = g * cpg < c0 ? 0 : 1; z <= ((g + 1) * cpg > c0 ? 1 : 0); ++z) {
+        const float2* gp = (const float2*)(gpart + z * src_stride) + (size_t)b * nchunk * groups + g;
+        constexpr int UN = 8;
+        for (int ch = part; ch < nchunk; ch += parts * UN) {
+          float2 v[UN];
+#pragma unroll
+          for (int u = 0; u < UN; ++u) v[u] = ch + u * parts < nchunk ? gp[(size_t)(ch + u * parts) * groups] : make_float2(0.f, 0.f);
+#pragma unroll
+          for (int u = 0; u < UN; ++u) { s += v[u].x; q += v[u].y; }
+        }
       }
     }
     dred[tid * 2] = s; dred[tid * 2 + 1] = q;
@@ -2393,7 +2405,7 @@ __global__ __launch_bounds__(256) void k_gn_apply(const T* __restrict__ src0, co
     float sc[VN], sh[VN];
 #pragma unroll
     for (int e = 0; e < VN; ++e) {
-      const int g = (c + e) / cpg;
+      const int g = (int)fast_div((unsigned)(c + e), div_cpg);
       sc[e] = srstd[g] * gamma[c + e];
       sh[e] = beta[c + e] - smean[g] * sc[e];
     }
@@ -2421,58 +2433,66 @@ __global__ __launch_bounds__(256) void k_gn_apply(const T* __restrict__ src0, co
   }
 }
 
-// GroupNorm for small feature maps in one launch: a workgroup owns one (sample, group), keeps its
-// (C/G) x HW elements in registers, reduces them and writes the normalised result.
-constexpr int kGnSmallVecs = 8;    // 16-byte vectors a thread can hold (larger maps take the three-pass path)
-
-template <typename T>
-__global__ __launch_bounds__(256) void k_gn_small(const T* __restrict__ src0, const T* __restrict__ src1, int c0, int c1, int hw,
-                                                  int groups, const float* __restrict__ gamma, const float* __restrict__ beta,
-                                                  float eps, int silu, T* __restrict__ out) {
-  typedef typename Vec<T>::type V;
-  constexpr int VN = Vec<T>::N;
-  __shared__ float red[8];
-  const int g = blockIdx.x, b = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int ctot = c0 + c1, cpg = ctot / groups, vpp = cpg / VN;
-  const int ch0 = g * cpg;                               // first channel of the group in the concatenation
-  const bool second = ch0 >= c0;                         // the launcher guarantees a group does not straddle the sources
-  const T* src = second ? src1 : src0;
-  const int cs = second ? c1 : c0, coff = second ? ch0 - c0 : ch0;
-  const int nvec = hw * vpp;
-  V x[kGnSmallVecs];
+// GroupNorm in one launch: a workgroup owns one (sample, group), keeps its (C/G) x HW elements in registers, reduces them
+// and writes the normalised result, so the tensor is read once and nothing
+// goes through scratch memory.  G: channels per access (the widest that divides the channels of a group), NV: accesses a
+// thread can hold; thread (pixel lane, access of the pixel) walks the pixels in steps of `pl`, so its channels stay the same.
+// Neighbouring groups share cache lines: xcd_remap puts them on one XCD.  Bound by one round trip to memory and the launch.
+template <typename T, int G, int NT, int NV>
+__global__ __launch_bounds__(NT) void k_gn_group(const T* __restrict__ src0, const T* __restrict__ src1, int c0, int c1, int hw,
+                                                 int groups, int pl, const float* __restrict__ gamma, const float* __restrict__ beta,
+                                                 float eps, int silu, T* __restrict__ out) {
+  typedef T V __attribute__((ext_vector_type(G)));
+  __shared__ float red[2][NT / 64];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int vid = xcd_remap(blockIdx.x, gridDim.x);
+  const int b = vid / groups, g = vid - b * groups;
+  const int ctot = c0 + c1, cpg = ctot / groups, vpp = cpg / G;
+  const int lanep = tid / vpp, c = g * cpg + (tid - lanep * vpp) * G;
+  const bool second = c >= c0;                           // an access never straddles the sources: both widths are multiples of G
+  const int ld = second ? c1 : c0;
+  const T* src = (second ? src1 + (c - c0) : src0 + c) + (size_t)b * hw * ld;
+  const int p_end = lanep < pl ? hw : 0;
+  // sums of x - pivot and of its square in one pass: with the pivot inside the data nothing cancels
+  const int cg = g * cpg;
+  const float pivot = to_f(cg >= c0 ? src1[(size_t)b * hw * c1 + cg - c0] : src0[(size_t)b * hw * c0 + cg]);
+  V x[NV];
+#pragma unroll
+  for (int k = 0; k < NV; ++k) {
+    const int p = lanep + k * pl;
+    if (p < p_end) x[k] = *(const V*)(src + (size_t)p * ld);
+  }
+  float ga[G], be[G];
+#pragma unroll
+  for (int e = 0; e < G; ++e) { ga[e] = p_end ? gamma[c + e] : 0.f; be[e] = p_end ? beta[c + e] : 0.f; }
   float s = 0.f, q = 0.f;
 #pragma unroll
-  for (int k = 0; k < kGnSmallVecs; ++k) {
-    const int v = tid + 256 * k;
-    if (v < nvec) {
-      const int p = v / vpp, vi = v - p * vpp;
-      x[k] = *(const V*)(src + ((size_t)b * hw + p) * cs + coff + vi * VN);
+  for (int k = 0; k < NV; ++k)
+    if (lanep + k * pl < p_end)
 #pragma unroll
-      for (int e = 0; e < VN; ++e) { const float f = to_f(x[k][e]); s += f; q += f * f; }
-    }
-  }
+      for (int e = 0; e < G; ++e) { const float d = to_f(x[k][e]) - pivot; s += d; q += d * d; }
   s = wave_sum(s); q = wave_sum(q);
-  if (lane == 0) { red[wave * 2] = s; red[wave * 2 + 1] = q; }
+  if (lane == 0) { red[0][wave] = s; red[1][wave] = q; }
   __syncthreads();
-  const float n = (float)hw * cpg;
-  const float mean = (red[0] + red[2] + red[4] + red[6]) / n;
-  float var = (red[1] + red[3] + red[5] + red[7]) / n - mean * mean;
-  var = var < 0.f ? 0.f : var;
-  const float rstd = rsqrtf(var + eps);
+  s = 0.f; q = 0.f;
 #pragma unroll
-  for (int k = 0; k < kGnSmallVecs; ++k) {
-    const int v = tid + 256 * k;
-    if (v < nvec) {
-      const int p = v / vpp, vi = v - p * vpp;
+  for (int w = 0; w < NT / 64; ++w) { s += red[0][w]; q += red[1][w]; }
+  const float n = (float)hw * cpg, shift = s / n, mean = pivot + shift;
+  const float rstd = rsqrtf(fmaxf(q / n - shift * shift, 0.f) + eps);
+#pragma unroll
+  for (int e = 0; e < G; ++e) { ga[e] *= rstd; be[e] -= mean * ga[e]; }
+#pragma unroll
+  for (int k = 0; k < NV; ++k) {
+    const int p = lanep + k * pl;
+    if (p < p_end) {
       V o;
 #pragma unroll
-      for (int e = 0; e < VN; ++e) {
-        const int c = ch0 + vi * VN + e;
-        float y = (to_f(x[k][e]) - mean) * rstd * gamma[c] + beta[c];
+      for (int e = 0; e < G; ++e) {
+        float y = to_f(x[k][e]) * ga[e] + be[e];
         if (silu) y = silu_f(y);
         o[e] = from_f<T>(y);
       }
-      *(V*)(out + ((size_t)b * hw + p) * ctot + ch0 + vi * VN) = o;
+      *(V*)(out + ((size_t)b * hw + p) * ctot + c) = o;
     }
   }
 }
@@ -2486,31 +2506,53 @@ extern "C" size_t ad_groupnorm_scratch_bytes(int batch, int hw, int c) {
 
 namespace ad {
 
+template <typename T, int NT, int REGS>
+static ad_status launch_gn_group(const void* src0, const void* src1, int c0, int c1, int batch, int hw, int groups, int ga,
+                                 const float* gamma, const float* beta, float eps, int silu, void* out, hipStream_t s) {
+  const int ctot = c0 + c1, pl = NT / (ctot / groups / ga);
+  constexpr int VN = Vec<T>::N;
+  ProfLaunch prof("gn_group", 0, 2.0 * batch * hw * ctot * sizeof(T), s, batch * hw, ctot, 0);
+  const dim3 grid(groups * batch);
+#define AD_GN(G_) hipLaunchKernelGGL((k_gn_group<T, G_, NT, REGS * 4 / (G_ * (int)sizeof(T))>), grid, dim3(NT), 0, s, (const T*)src0, (const T*)src1, \
+                                     c0, c1, hw, groups, pl, gamma, beta, eps, silu, (T*)out)
+  if (ga == VN) AD_GN(VN);
+  else if (ga == VN / 2) AD_GN(VN / 2);
+  else AD_GN(VN / 4);
+#undef AD_GN
+  AD_HIP(hipGetLastError());
+  return AD_OK;
+}
+
 template <typename T>
 static ad_status run_groupnorm(const void* src0, const void* src1, int c0, int c1, int batch, int hw, int groups,
                                const float* gamma, const float* beta, float eps, int silu, void* out, void* scratch,
                                hipStream_t s) {
-  const int ctot = c0 + c1, nchunk = gn_chunks(hw);
+  const int ctot = c0 + c1, nchunk = gn_chunks(batch, hw, groups, ctot);
   const int cpg = ctot / groups;
-  if (cpg % Vec<T>::N == 0 && c0 % cpg == 0 && (long long)hw * (cpg / Vec<T>::N) <= 256LL * kGnSmallVecs) {
-    ProfLaunch pl("gn_small", 0, 2.0 * batch * hw * ctot * sizeof(T), s, batch * hw, ctot, 0);
-    hipLaunchKernelGGL(k_gn_small<T>, dim3(groups, batch), dim3(256), 0, s, (const T*)src0, (const T*)src1, c0, c1, hw, groups, gamma, beta, eps,
-                       silu, (T*)out);
-    AD_HIP(hipGetLastError());
-    return AD_OK;
+  // One launch where a workgroup can hold a group of a sample in registers and has at most 16384 accesses to make (16 a thread).
+  // Measured on both sides of the line (two samples, 32 groups, bf16, launches back to back): 24x24x1280 7.9 us against 11.4 of the
+  // two launches, 48x48x640 (11.5k accesses) 10.2 / 14.1, 72x40x320 (14.4k) 10.4 / 12.6, but 64x64x320 (20.5k accesses of 4
+  // bytes) 15.3 / 14.0 and 96x96x320 (46k) 29.9 / 17.3; small maps of narrow models 3.6 / 11.3.
+  int ga = Vec<T>::N;                                        // channels per access: the widest that divides a group
+  while (ga > 1 && cpg % ga) ga >>= 1;
+  if (ga * (int)sizeof(T) >= 4 && (long long)hw * (cpg / ga) <= 16384) {
+    const int words = ga * (int)sizeof(T) / 4, vpp = cpg / ga;     // 32-bit registers an access takes; accesses per pixel
+    auto fits = [&](int nt, int regs) { return vpp <= nt && (long long)(nt / vpp) * (regs / words) >= hw; };
+#define AD_GN_ONE(NT_, REGS_) if (fits(NT_, REGS_)) return launch_gn_group<T, NT_, REGS_>(src0, src1, c0, c1, batch, hw, groups, ga, gamma, beta, eps, silu, out, s)
+    AD_GN_ONE(256, 16);
+    AD_GN_ONE(512, 16);
+    AD_GN_ONE(1024, 16);
+    AD_GN_ONE(1024, 48);
+#undef AD_GN_ONE
   }
-  if (c0 > kGnMaxChannels || c1 > kGnMaxChannels || groups > kGnMaxGroups)
-    AD_FAIL(AD_ERR_INVALID, "groupnorm: at most %d channels per source and %d groups", kGnMaxChannels, kGnMaxGroups);
+  if (groups > kGnMaxGroups) AD_FAIL(AD_ERR_INVALID, "groupnorm: at most %d groups", kGnMaxGroups);
   float* gpart = (float*)scratch;
   const size_t src_stride = (size_t)batch * nchunk * groups * 2;
   const long long rows = (long long)batch * hw;
   {
-    ProfLaunch pl("gn_partial", 0, (double)rows * c0 * sizeof(T), s, (int)rows, c0, 0);
-    hipLaunchKernelGGL(k_gn_partial<T>, dim3(nchunk, batch), dim3(256), 0, s, (const T*)src0, c0, hw, nchunk, groups, cpg, 0, gpart);
-  }
-  if (c1) {
-    ProfLaunch pl("gn_partial", 0, (double)rows * c1 * sizeof(T), s, (int)rows, c1, 0);
-    hipLaunchKernelGGL(k_gn_partial<T>, dim3(nchunk, batch), dim3(256), 0, s, (const T*)src1, c1, hw, nchunk, groups, cpg, c0, gpart + src_stride);
+    ProfLaunch pl("gn_partial", 0, (double)rows * ctot * sizeof(T), s, (int)rows, ctot, 0);
+    hipLaunchKernelGGL(k_gn_partial<T>, dim3(nchunk, batch, c1 ? 2 : 1), dim3(256), 0, s, (const T*)src0, (const T*)src1, c0, c1, hw, nchunk, groups,
+                       cpg, src_stride, gpart);
   }
   // about 768 workgroups: each folds the statistics of its sample once and then streams its rows
   int rows_per_block = (hw * batch + 767) / 768;
@@ -2518,14 +2560,14 @@ static ad_status run_groupnorm(const void* src0, const void* src1, int c0, int c
   const int row_blocks = (hw + rows_per_block - 1) / rows_per_block;
   ProfLaunch pl("gn_apply", 0, 2.0 * rows * ctot * sizeof(T), s, (int)rows, ctot, 0);
   hipLaunchKernelGGL(k_gn_apply<T>, dim3(row_blocks, batch), dim3(256), 0, s, (const T*)src0, (const T*)src1, c0, c1, hw, rows_per_block, nchunk,
-                     groups, gpart, src_stride, gamma, beta, eps, silu, (T*)out);
+                     groups, gpart, src_stride, make_fastdiv((unsigned)cpg), gamma, beta, eps, silu, (T*)out);
   AD_HIP(hipGetLastError());
   return AD_OK;
 }
 
 // bytes of partial sums the two-pass path writes: [2 sources][batch][chunks][groups][sum, sum of squares]
-static size_t gn_partial_bytes(int batch, int hw, int groups) {
-  return (size_t)2 * batch * gn_chunks(hw) * groups * 2 * sizeof(float);
+static size_t gn_partial_bytes(int batch, int hw, int groups, int c) {
+  return (size_t)2 * batch * gn_chunks(batch, hw, groups, c) * groups * 2 * sizeof(float);
 }
 
 ad_status launch_groupnorm(int dtype, const void* src0, const void* src1, int c0, int c1, int batch, int hw, int groups,
@@ -2535,7 +2577,7 @@ ad_status launch_groupnorm(int dtype, const void* src0, const void* src1, int c0
   const int vn = dtype == AD_BF16 ? 8 : 4;
   if (batch < 1 || hw < 1 || c0 < vn || c0 % vn || c1 < 0 || c1 % vn || groups < 1 || (c0 + c1) % groups)
     AD_FAIL(AD_ERR_INVALID, "groupnorm: bad shape");
-  if (scratch_bytes < gn_partial_bytes(batch, hw, groups)) AD_FAIL(AD_ERR_NOMEM, "groupnorm: scratch too small");
+  if (scratch_bytes < gn_partial_bytes(batch, hw, groups, c0 + c1)) AD_FAIL(AD_ERR_NOMEM, "groupnorm: scratch too small");
   if (dtype == AD_BF16) return run_groupnorm<bf16>(src0, src1, c0, c1, batch, hw, groups, gamma, beta, eps, silu, out, scratch, s);
   if (dtype == AD_F32) return run_groupnorm<float>(src0, src1, c0, c1, batch, hw, groups, gamma, beta, eps, silu, out, scratch, s);
   AD_FAIL(AD_ERR_INVALID, "groupnorm: bad dtype");
@@ -2546,7 +2588,6 @@ ad_status launch_groupnorm(int dtype, const void* src0, const void* src1, int c0
 // instead of a caller-supplied scratch buffer.  Host code never uses the array's name as an address: the device
 // address is looked up once per device (hipGetSymbolAddress, with that device current) and kept.
 // -------------------------------------------------------------------------------------------------
-constexpr size_t kStaticGnBytes = 512 * 1024;      // e.g. batch 16, 64 pixel chunks, 32 groups, two sources
 constexpr int kMaxDevices = 64;
 static __device__ __align__(256) unsigned char scratch[kStaticGnBytes];
 static void* g_scratch_ptr[kMaxDevices] = {nullptr};
@@ -2570,10 +2611,10 @@ static ad_status static_scratch(void** out) {
 ad_status launch_groupnorm_static(int dtype, const void* src0, const void* src1, int c0, int c1, int batch, int hw, int groups,
                                   const float* gamma, const float* beta, float eps, int silu, void* out, hipStream_t s) {
   if (batch < 1 || hw < 1 || groups < 1) AD_FAIL(AD_ERR_INVALID, "groupnorm: bad shape");
-  const size_t need = gn_partial_bytes(batch, hw, groups);
+  const size_t need = gn_partial_bytes(batch, hw, groups, c0 + c1);
   if (need > kStaticGnBytes)
     AD_FAIL(AD_ERR_NOMEM, "groupnorm (static scratch): batch %d x %d chunks x %d groups needs %zu bytes, the fixed buffer holds %zu",
-            batch, gn_chunks(hw), groups, need, kStaticGnBytes);
+            batch, gn_chunks(batch, hw, groups, c0 + c1), groups, need, kStaticGnBytes);
   void* ptr = nullptr;
   ad_status st = static_scratch(&ptr);
   if (st != AD_OK) return st;
