@@ -850,6 +850,236 @@ static ad_status run_igemm_p3(const IgemmParams& p0, const char* name, hipStream
 }
 
 // =================================================================================================
+// GEMM for outputs of a few hundred small tiles (the deep levels, narrow models, single samples).
+//
+// Such a launch is bound by latency: its operands come from memory (weights) or the memory-side cache (activations the
+// previous launch has just written), a CU takes in only about 60 GB/s of those, and with 64x64 tiles there are fewer
+// workgroups than CUs, each walking the whole of K tile by tile behind a barrier.  So the tiles are small (16x16 to 32x64,
+// enough of them for the chip), the wavefronts of a workgroup share K (wavefront w takes k-tiles w, w + NW, ...) and load
+// their 16x16x32 MFMA fragments straight from memory into registers, two k-tiles ahead: no LDS, no barrier before the
+// partial tiles are added, in wavefront order, through LDS.  The weights are the A operand, so that a lane holds four
+// consecutive columns of a row.  What the epilogue adds is requested before the loop.
+// Measured, bf16, weights from memory, us (64x64 tiles in three stages -> this kernel): 1152x64x64 4.1 -> 3.1, 3x3 1152x64x576
+// 7.4 -> 4.4, 3x3 288x128x1152 10.8 -> 4.8, 72x256x1024 7.8 -> 4.7, 180x1280x1280 11.4 -> 7.9; 3x3 72x256x2304 with K split
+// over workgroups and a second launch 11.8 -> 6.8.
+// =================================================================================================
+template <typename T> struct Mma16;
+template <> struct Mma16<bf16> {
+  static __device__ __forceinline__ void run(const bf16x8& a, const bf16x8& b, f32x4& c) { c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0); }
+};
+template <> struct Mma16<float> {
+  static __device__ __forceinline__ void run(const f32x4& a, const f32x4& b, f32x4& c) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) c = __builtin_amdgcn_mfma_f32_16x16x4f32(a[e], b[e], c, 0, 0, 0);
+  }
+};
+
+template <typename T, int TM, int TN, int MODE>
+__global__ __launch_bounds__(512) void k_igemm_small(IgemmParams p) {
+  typedef typename Vec<T>::type V;
+  typedef typename Vec4<T>::type V4;
+  constexpr int BM = 16 * TM, BN = 16 * TN, NW = 8, PF = 2, PITCH = BN + 4;
+  constexpr int ES = (int)sizeof(T), BK = kRowBytes / ES, VN = Vec<T>::N;
+  constexpr bool TRANSPOSED = MODE == OUT_TRANSPOSED || MODE == OUT_TRANSPOSED_F32;
+  static_assert(MODE != OUT_GEGLU || BN == 64, "32 value columns and their 32 gates");
+  extern __shared__ __attribute__((aligned(16))) char lds[];
+  float* const part = (float*)lds;                       // [wavefront][BM][PITCH]
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int r16 = lane & 15, kg = lane >> 4;
+  const TileId t3 = tile_of(p);
+  const int m0 = t3.m_tile * BM, n0 = t3.n_tile * BN;
+
+  // byte offsets of this lane's rows; the activations' at tap (0, 0), from a base moved back by one row and one pixel, with
+  // a bit per tap that falls inside the image
+  const unsigned shift = p.pad ? (unsigned)(p.ws + 1) : 0u;
+  unsigned a_off0[TM], a_off1[TM], a_taps[TM], b_off[TN];
+  int a_par[TM];                                         // nearest-2x input: row and column parity of tap (0, 0)
+#pragma unroll
+  for (int j = 0; j < TN; ++j) b_off[j] = (unsigned)((n0 + 16 * j + r16) * p.Kp + kg * VN) * ES;
+#pragma unroll
+  for (int i = 0; i < TM; ++i) {
+    const int m = m0 + 16 * i + r16;
+    a_taps[i] = 0; a_off0[i] = 0; a_off1[i] = 0; a_par[i] = 0;
+    if (m < p.M) {
+      const int b = (int)fast_div((unsigned)m, p.div_hw), r = m - b * p.hw_out;
+      const int oy = (int)fast_div((unsigned)r, p.div_w), ox = r - oy * p.wout;
+      const int iy0 = oy * p.stride - p.pad, ix0 = ox * p.stride - p.pad;
+      const unsigned pix = (unsigned)((b * p.hs + (iy0 >> p.up)) * p.ws + (ix0 >> p.up) + (int)shift);
+      a_off0[i] = (pix * (unsigned)p.c0 + kg * VN) * ES;
+      a_off1[i] = (pix * (unsigned)p.c1 + kg * VN) * ES;
+      a_par[i] = (iy0 & 1) + 2 * (ix0 & 1);
+#pragma unroll
+      for (int u = 0; u < 3; ++u)
+#pragma unroll
+        for (int v = 0; v < 3; ++v)
+          if (u < p.ksize && v < p.ksize && iy0 + u >= 0 && iy0 + u < p.hin && ix0 + v >= 0 && ix0 + v < p.win) a_taps[i] |= 1u << (u * 3 + v);
+    }
+  }
+  const __amdgpu_buffer_rsrc_t rs0 = make_rsrc((const char*)p.src0 - (size_t)shift * p.c0 * ES, p.bytes0 + shift * p.c0 * ES);
+  const __amdgpu_buffer_rsrc_t rs1 = make_rsrc((const char*)p.src1 - (size_t)shift * p.c1 * ES, p.bytes1 + shift * p.c1 * ES);
+  const __amdgpu_buffer_rsrc_t rsw = make_rsrc(p.w, p.bytes_w);
+
+  const int mine = (p.ktiles - wave + NW - 1) / NW;      // k-tiles of this wavefront (0 when there are fewer k-tiles than wavefronts)
+  int f_k = wave * BK, f_tap = f_k / p.ctot, f_cc = f_k - f_tap * p.ctot;
+  V af[PF][TM][2], bf[PF][TN][2];
+  auto fetch = [&](int s) {
+    const int u = p.ksize == 3 ? f_tap / 3 : 0, v = p.ksize == 3 ? f_tap - 3 * u : 0;
+    const unsigned bit = 1u << (u * 3 + v), sb = (unsigned)f_k * ES;
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) bf[s][j][h] = buffer_load16<V>(rsw, b_off[j] + h * 64, sb);
+    const bool second = f_cc >= p.c0;
+    const unsigned cs = (unsigned)(second ? p.c1 : p.c0) * ES, sc = (unsigned)(second ? f_cc - p.c0 : f_cc) * ES;
+    const unsigned sa = p.up ? sc : sc + (unsigned)(u * p.ws + v) * cs;
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+      unsigned o = second ? a_off1[i] : a_off0[i];
+      if (p.up) o += (unsigned)((((a_par[i] & 1) + u) >> 1) * p.ws + (((a_par[i] >> 1) + v) >> 1)) * cs;
+      o = (a_taps[i] & bit) ? o : kOob;
+#pragma unroll
+      for (int h = 0; h < 2; ++h) af[s][i][h] = second ? buffer_load16<V>(rs1, o + h * 64, sa) : buffer_load16<V>(rs0, o + h * 64, sa);
+    }
+    f_k += BK * NW; f_cc += BK * NW;
+    while (f_cc >= p.ctot) { f_cc -= p.ctot; ++f_tap; }
+  };
+#pragma unroll
+  for (int s = 0; s < PF; ++s)
+    if (s < mine) fetch(s);
+
+  // what the epilogue adds.  A thread of it finishes four consecutive columns of a row, or, for transposed outputs, four
+  // consecutive rows of a column
+  int which = 0, c3 = p.N;
+  if constexpr (MODE == OUT_QKV) { c3 = p.N / 3; which = n0 / c3; }          // a tile never straddles two thirds
+  const bool by_column = TRANSPOSED || (MODE == OUT_QKV && which == 2 && p.ld_t > 0);
+  constexpr int BO = MODE == OUT_GEGLU ? BN / 2 : BN;    // output columns of the tile
+  constexpr int QUADS = BM * BO / 4;
+  static_assert(QUADS <= 64 * NW, "one item per thread");
+  const int rl = by_column ? (tid % (BM / 4)) * 4 : tid / (BO / 4), cl = by_column ? tid / (BM / 4) : (tid % (BO / 4)) * 4;
+  const int row = m0 + rl, col = n0 + cl;
+  const bool live = tid < QUADS && row < p.M && (MODE == OUT_GEGLU || col < p.N);
+  float add[4] = {0.f, 0.f, 0.f, 0.f}, gate[4] = {0.f, 0.f, 0.f, 0.f};
+  if (live) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int c = by_column ? col : col + e, r = min(by_column ? row + e : row, p.M - 1);
+      if (c >= p.N) continue;
+      if (p.bias) { add[e] = p.bias[c]; if constexpr (MODE == OUT_GEGLU) gate[e] = p.bias[c + 32]; }
+      if constexpr (MODE == OUT_ROWMAJOR || TRANSPOSED)
+        if (p.rowvec) add[e] += p.rowvec[(size_t)fast_div((unsigned)r, p.div_hw) * p.rowvec_ld + c];
+      if constexpr (MODE == OUT_ROWMAJOR)
+        if (p.residual) add[e] += to_f(((const T*)p.residual)[(size_t)row * p.N + c]);
+    }
+  }
+
+  f32x4 acc[TM][TN];
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int i0 = 0; i0 < mine; i0 += PF) {
+#pragma unroll
+    for (int s = 0; s < PF; ++s) {
+      if (i0 + s >= mine) break;
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+          for (int j = 0; j < TN; ++j) Mma16<T>::run(bf[s][j][h], af[s][i][h], acc[i][j]);
+      if (i0 + s + PF < mine) fetch(s);
+    }
+  }
+  // lane: row r16 of row tile i, columns 4 kg .. 4 kg + 3 of column tile j
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j) *(f32x4*)(part + wave * (BM * PITCH) + (16 * i + r16) * PITCH + 16 * j + 4 * kg) = acc[i][j];
+  __syncthreads();
+  if (!live) return;
+  auto total = [&](int r, int c) {                       // four columns of a row, over the wavefronts in order
+    f32x4 v = *(const f32x4*)(part + r * PITCH + c);
+#pragma unroll
+    for (int w = 1; w < NW; ++w) v += *(const f32x4*)(part + w * (BM * PITCH) + r * PITCH + c);
+    return v;
+  };
+  if (by_column) {
+    float v[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      v[e] = part[(rl + e) * PITCH + cl];
+#pragma unroll
+      for (int w = 1; w < NW; ++w) v[e] += part[w * (BM * PITCH) + (rl + e) * PITCH + cl];
+      v[e] += add[e];
+    }
+    const int ncols = MODE == OUT_QKV ? c3 : p.N, cc = MODE == OUT_QKV ? col - 2 * c3 : col;
+    void* const dst = MODE == OUT_QKV ? p.out3 : p.out;
+    const int b = (int)fast_div((unsigned)row, p.div_hw);
+    const size_t o = ((size_t)b * ncols + cc) * p.ld_t + (row - b * p.hw_out);
+    if ((p.hw_out & 3) == 0 && (p.ld_t & 3) == 0 && row + 3 < p.M) {
+      if constexpr (MODE == OUT_TRANSPOSED_F32) *(f32x4*)((float*)dst + o) = f32x4{v[0], v[1], v[2], v[3]};
+      else *(V4*)((T*)dst + o) = V4{from_f<T>(v[0]), from_f<T>(v[1]), from_f<T>(v[2]), from_f<T>(v[3])};
+      return;
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      if (row + e >= p.M) break;
+      const int be = (int)fast_div((unsigned)(row + e), p.div_hw);
+      const size_t oe = ((size_t)be * ncols + cc) * p.ld_t + (row + e - be * p.hw_out);
+      if constexpr (MODE == OUT_TRANSPOSED_F32) ((float*)dst)[oe] = v[e];
+      else ((T*)dst)[oe] = from_f<T>(v[e]);
+    }
+    return;
+  }
+  f32x4 v = total(rl, cl);
+  int ncols = p.N, c_out = col;
+  T* dst = (T*)p.out;
+  if constexpr (MODE == OUT_GEGLU) {
+    const f32x4 g = total(rl, cl + 32);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] = (v[e] + add[e]) * gelu_f(g[e] + gate[e]);
+    ncols = p.N >> 1; c_out = (n0 >> 1) + cl;
+  } else {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] += add[e];
+  }
+  if constexpr (MODE == OUT_QKV) {
+    dst = (T*)(which == 0 ? p.out : which == 1 ? p.out2 : p.out3);
+    ncols = c3; c_out = col - which * c3;
+  }
+  const size_t o = (size_t)row * ncols + c_out;
+  if ((ncols & 3) == 0) {
+    *(V4*)(dst + o) = V4{from_f<T>(v[0]), from_f<T>(v[1]), from_f<T>(v[2]), from_f<T>(v[3])};
+  } else {
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (c_out + e < ncols) dst[o + e] = from_f<T>(v[e]);
+  }
+}
+
+template <typename T, int TM, int TN, int MODE>
+static ad_status run_igemm_small(const IgemmParams& p0, const char* name, hipStream_t s) {
+  IgemmParams p = p0;
+  p.tiles_n = (p.N + 16 * TN - 1) / (16 * TN);
+  p.tiles_m = (p.M + 16 * TM - 1) / (16 * TM);
+  constexpr int lds_bytes = 8 * 16 * TM * (16 * TN + 4) * 4;
+  if constexpr (lds_bytes > 65536) {
+    static std::atomic<bool> attr_set{false};
+    if (!attr_set) {
+      AD_HIP(hipFuncSetAttribute((const void*)k_igemm_small<T, TM, TN, MODE>, hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes));
+      attr_set = true;
+    }
+  }
+  const double in_bytes = (double)p.M * p.ctot * sizeof(T) * (p.stride == 2 ? 4 : 1) / (p.up ? 4 : 1);
+  const double out_cols = p.out_mode == OUT_GEGLU ? p.N / 2 : p.N;
+  ProfLaunch pl(name, 2.0 * p.M * p.N * p.k_prof, in_bytes + (double)p.N * p.Kp * sizeof(T) + (double)p.M * out_cols * sizeof(T), s, p.M, p.N, p.Kp);
+  hipLaunchKernelGGL((k_igemm_small<T, TM, TN, MODE>), dim3(p.tiles_n * p.tiles_m), dim3(512), lds_bytes, s, p);
+  AD_HIP(hipGetLastError());
+  return AD_OK;
+}
+
+// =================================================================================================
 // 3x3 convolution (stride 1) with the input staged in LDS as a halo tile, bf16.
 //
 // The implicit-GEMM kernels above fetch the A tile (BM output positions x 64 channels) once per tap: nine times the
@@ -1112,8 +1342,19 @@ __global__ __launch_bounds__(256) void k_splitk_reduce(const float* __restrict__
   const long long total = (long long)M * n4;
   for (long long i = (long long)blockIdx.x * 256 + threadIdx.x; i < total; i += (long long)gridDim.x * 256) {
     const int row = (int)(i / n4), col = (int)(i - (long long)row * n4) * 4;
-    f32x4 v = *(const f32x4*)(partial + (size_t)row * N + col);
-    for (int z = 1; z < splits; ++z) v += *(const f32x4*)(partial + ((size_t)z * M + row) * N + col);
+    // added in order, eight loads in flight (one at a time, each split costs a round trip to memory: 6.6 us a launch)
+    const float* src = partial + (size_t)row * N + col;
+    const size_t step = (size_t)M * N;
+    f32x4 v = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int z = 0; z < splits; z += 8) {
+      f32x4 t[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+        if (z + u < splits) t[u] = *(const f32x4*)(src + (z + u) * step);
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+        if (z + u < splits) v += t[u];
+    }
     const int b = row / hw_out;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
@@ -1141,7 +1382,7 @@ __global__ __launch_bounds__(256) void k_splitk_reduce(const float* __restrict__
 // Tile shapes.  The register-staged kernels (64x64, 128x128) serve fp32 and the transposed epilogues; bf16
 // GEMMs with a row-major, GEGLU, fused q/k/v or split-K epilogue take the three-stage LDS-DMA kernel with a
 // 128x128 or a 256x128 tile.
-enum { TILE_128x128 = 1, TILE_64x64 = 3, TILE_DMA2_128 = 4, TILE_P3_128 = 5, TILE_P3_256 = 6, TILE_P3_64 = 7, TILE_HALO_128 = 8, TILE_HALO_256 = 9, TILE_P3_256_W4 = 10, TILE_P3_128_W4 = 11, TILE_P3_256_W16 = 12, TILE_AUTO = -1 };
+enum { TILE_128x128 = 1, TILE_64x64 = 3, TILE_DMA2_128 = 4, TILE_P3_128 = 5, TILE_P3_256 = 6, TILE_P3_64 = 7, TILE_HALO_128 = 8, TILE_HALO_256 = 9, TILE_P3_256_W4 = 10, TILE_P3_128_W4 = 11, TILE_P3_256_W16 = 12, TILE_SMALL = 13, TILE_AUTO = -1 };
 static int g_tile_override = TILE_AUTO;
 static int g_order_override = -1;
 
@@ -1179,6 +1420,20 @@ static double plan_cost(long long m, int n, int ktiles, int tile, int splits) {
   return cost;
 }
 
+// Tile of k_igemm_small (16-row and 16-column units), or {0, 0} where another kernel is the better choice: the smallest tile that
+// makes at most a workgroup per CU, as long as a workgroup takes in at most 200 KiB (beyond that the 60 GB/s a CU gets from memory
+// decide, and K split over workgroups wins: 3x3 72x192x5760 13 us against 11).  GEGLU pairs 32 value with 32 gate columns.
+struct SmallTile { int tm, tn; };
+static SmallTile small_tile(long long m, int n, int ktiles, int out_mode) {
+  const SmallTile plain[] = {{1, 1}, {1, 2}, {2, 2}}, geglu[] = {{1, 4}, {2, 4}};
+  for (int i = 0; i < (out_mode == OUT_GEGLU ? 2 : 3); ++i) {
+    const SmallTile t = out_mode == OUT_GEGLU ? geglu[i] : plain[i];
+    const long long wgs = ((m + 16 * t.tm - 1) / (16 * t.tm)) * ((n + 16 * t.tn - 1) / (16 * t.tn));
+    if (wgs <= 256 && (long long)(t.tm + t.tn) * 16 * kRowBytes * ktiles <= 200 * 1024) return t;
+  }
+  return SmallTile{0, 0};
+}
+
 static ConvPlan choose_plan(int dtype, long long m, int n, int ktiles, int out_mode) {
   const bool geglu = out_mode == OUT_GEGLU;   // needs a value and a gate tile in the same wavefront
   const bool dma = dma_capable(dtype, out_mode);
@@ -1193,6 +1448,7 @@ static ConvPlan choose_plan(int dtype, long long m, int n, int ktiles, int out_m
   else if (forced != TILE_AUTO && geglu) forced = TILE_AUTO;
   if (forced == TILE_128x128 || forced == TILE_64x64) return ConvPlan{forced, splits_by_tiles(m, n, ktiles, out_mode, forced == TILE_64x64 ? 64 : 128)};
   if (forced == TILE_DMA2_128) return ConvPlan{forced, splits_by_tiles(m, n, ktiles, out_mode, 128)};
+  if (forced == TILE_AUTO && small_tile(m, n, ktiles, out_mode).tm) return ConvPlan{TILE_SMALL, 1};
   if (!dma) {
     // measured on the GEMM shapes of the SD-sized models: 128x128 register-staged tiles pay off once there is
     // more than one of them per CU, or with very few rows and a long K (the weights are re-read less often)
@@ -1343,6 +1599,25 @@ ad_status launch_conv(const ConvArgs& a, hipStream_t s) {
       if (wm == 2) { AD_P3W(128, 2, "w4") } else { AD_P3W(128, 4, "") }
     }
 #undef AD_P3W
+  } else if (tile == TILE_SMALL) {
+    const SmallTile t = small_tile(m, a.n_out, p.ktiles, a.out_mode);
+    name = h16 ? "igemm_bf16_small" : "igemm_f32_small";
+#define AD_SMALL(TM_, TN_, MODE_) st = h16 ? run_igemm_small<bf16, TM_, TN_, MODE_>(p, name, s) : run_igemm_small<float, TM_, TN_, MODE_>(p, name, s)
+#define AD_SMALL_MODE(MODE_)                                  \
+  case MODE_:                                                 \
+    if (t.tm == 2) { AD_SMALL(2, 2, MODE_); }                 \
+    else if (t.tn == 2) { AD_SMALL(1, 2, MODE_); }            \
+    else { AD_SMALL(1, 1, MODE_); }                           \
+    break;
+    switch (a.out_mode) {
+      AD_SMALL_MODE(OUT_ROWMAJOR)
+      AD_SMALL_MODE(OUT_QKV)
+      AD_SMALL_MODE(OUT_TRANSPOSED)
+      AD_SMALL_MODE(OUT_TRANSPOSED_F32)
+      default: if (t.tm == 2) { AD_SMALL(2, 4, OUT_GEGLU); } else { AD_SMALL(1, 4, OUT_GEGLU); }
+    }
+#undef AD_SMALL_MODE
+#undef AD_SMALL
   } else if (tile == TILE_P3_64) {
     switch (mode) {
       case OUT_ROWMAJOR: st = run_igemm_p3<bf16, 64, 64, OUT_ROWMAJOR>(p, "igemm_bf16_64x64_p3", s); break;

@@ -191,6 +191,36 @@ def test_conv_split_k(dtype):
     assert_kernel_close(got[:, :, :ho * wo], P.conv2d(x, w, bias).reshape(n, n_out, ho * wo), dtype)
 
 
+SMALL_CASES = [
+    # edges of the small-tile kernel: one row, fewer k-tiles than wavefronts, 16x16 / 16x32 / 32x32 tiles with remainders, K that does
+    # not divide over the wavefronts, two sources, stride 2, nearest-2x input with odd sizes, few columns
+    ("one_row", 1, 64, 0, 1, 1, 64, 1, 1, 0), ("one_tile_k", 1, 64, 0, 5, 3, 20, 1, 1, 0), ("16x16_ragged", 2, 128, 0, 7, 9, 132, 3, 1, 0),
+    ("16x32_ragged", 2, 64, 0, 23, 24, 72, 3, 1, 0), ("32x32_ragged", 1, 320, 0, 13, 21, 520, 1, 1, 0), ("concat", 1, 64, 128, 11, 6, 96, 3, 1, 0),
+    ("stride2", 2, 64, 0, 14, 10, 64, 3, 2, 0), ("stride2_1x1", 1, 128, 0, 9, 9, 48, 1, 2, 0), ("up", 2, 64, 64, 5, 7, 64, 3, 1, 1),
+    ("few_columns", 2, 64, 0, 12, 12, 4, 3, 1, 0), ("odd_columns", 1, 64, 0, 6, 6, 7, 3, 1, 0),
+]
+
+
+@pytest.mark.parametrize("dtype", DT)
+@pytest.mark.parametrize("case", SMALL_CASES, ids=[c[0] for c in SMALL_CASES])
+def test_conv_small_tiles(dtype, case):
+    """Row-major (bias, per-sample vector, residual) and both transposed outputs of one shape."""
+    name, n, c0, c1, hs, ws, n_out, k, stride, up = case
+    x0 = quantize(SI.make_array((n, c0, hs, ws), 311), dtype)
+    x1 = quantize(SI.make_array((n, c1, hs, ws), 312), dtype) if c1 else None
+    w = quantize(SI.make_array((n_out, c0 + c1, k, k), 313, 0.05), dtype)
+    bias, rowvec = SI.make_array((n_out,), 314, 0.1), SI.make_array((n, n_out), 315)
+    xin = x0 if x1 is None else np.concatenate([x0, x1], 1)
+    ref = P.conv2d(P.upsample_nearest2x(xin) if up else xin, w, bias, stride=stride)
+    ho, wo = ref.shape[2:]
+    res = quantize(SI.make_array((n, ho, wo, n_out), 316), dtype)
+    got, _ = run_conv(dtype, x0, x1, w, bias, stride, up, rowvec=rowvec, residual=res)
+    assert_kernel_close(nhwc_to_nchw(got), ref + rowvec[:, :, None, None] + nhwc_to_nchw(res), dtype)
+    for mode in (B.OUT_TRANSPOSED, B.OUT_TRANSPOSED_F32):
+        got, _ = run_conv(dtype, x0, x1, w, bias, stride, up, mode=mode)
+        assert_kernel_close(got[:, :, :ho * wo], ref.reshape(n, n_out, ho * wo), dtype)
+
+
 @pytest.mark.parametrize("dtype", DT)
 def test_linear_and_geglu(dtype):
     rows, cin, cff = 200, 64, 256                      # GEGLU: 64 -> 2*256, value * gelu(gate)
