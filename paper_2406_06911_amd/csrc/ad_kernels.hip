@@ -3,7 +3,7 @@
 //   k_igemm        implicit-GEMM convolution (3x3 / 1x1, stride 1 / 2, optional nearest-2x input,
 //                  optional channel concatenation) and linear layers on MFMA, with fused epilogues
 //   k_attn_mfma    fused attention (online softmax, K and V^T tiles in LDS, MFMA for QK^T and PV)
-//   k_attn_simple  generic attention, one wavefront per query (fp32 mode, odd head sizes)
+//   k_attn_generic generic attention on fp32 MFMA, keys shared out over the wavefronts (fp32 mode, odd head sizes)
 //   k_attn_frames_mfma / k_attn_frames  attention over the frame axis of a video model (one wavefront per
 //                  position and head; MFMA without LDS for bf16, LDS-staged generic kernel otherwise)
 //   k_gn_*         GroupNorm (+SiLU) in two passes: per-group partial sums, then statistics + apply
@@ -2237,54 +2237,143 @@ finished:
   }
 }
 
-// Generic attention: one wavefront per query, keys in chunks of 64 (one per lane), online softmax.
-template <typename T>
-__global__ __launch_bounds__(256) void k_attn_simple(const T* __restrict__ Q, const T* __restrict__ K,
-                                                     const T* __restrict__ V, int v_t, T* __restrict__ O, int L, int Lk,
-                                                     int C, int d, int ldq, int ldk, int ldv, int ldo, float scale) {
-  __shared__ float qs[4][128];
-  __shared__ float ps[4][64];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int b = blockIdx.z, h = blockIdx.y;
-  const int query = blockIdx.x * 4 + wave;
-  const bool active = query < L;
-  if (active)
-    for (int t = lane; t < d; t += 64) qs[wave][t] = to_f(Q[((size_t)b * L + query) * ldq + h * d + t]) * scale;
-  __syncthreads();
-  float m_run = -INFINITY, l_run = 0.f, acc0 = 0.f, acc1 = 0.f;
-  for (int key0 = 0; key0 < Lk; key0 += 64) {
-    const int key = key0 + lane;
-    float s = -INFINITY;
-    if (active && key < Lk) {
-      const T* kr = K + ((size_t)b * Lk + key) * ldk + h * d;
-      s = 0.f;
-      for (int t = 0; t < d; ++t) s += qs[wave][t] * to_f(kr[t]);
+// Generic attention (fp32, other head widths, v in its own layout): fp32 arithmetic on the 16x16x4 MFMA whatever the storage type.
+// A workgroup owns 16 queries of one (sample, head); its eight wavefronts take every eighth block of 16 keys with an online softmax
+// of their own (these sequences are short, so the keys have to be shared out for the chip to see enough wavefronts) and are
+// merged through LDS at the end.  Scores are computed transposed, S^T = K Q^T: a lane holds four keys (4 g + r) of query
+// lane & 15, which is the B operand of O^T += V^T P^T as it stands.  No LDS before the merge.  DT: head width in units of 16;
+// VEC: four consecutive elements of a row can be loaded at once.  Bound by the latency of the loads of a key block and its
+// dependent softmax.
+// fp32, two samples, heads of 64: 576 x 576, one head, 14.7 us; 144 x 144, two heads, 7.6 us; 4096 x 4096, one head, 156 us = 55 TFLOP/s
+// (124, 31 and 1660 us with one wavefront per query, one key per lane).
+template <typename T, int DT, bool VEC>
+__global__ __launch_bounds__(512) void k_attn_generic(const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ V, int v_t,
+                                                      T* __restrict__ O, int L, int Lk, int C, int d, int ldq, int ldk, int ldv, int ldo,
+                                                      float scale_log2) {
+  constexpr int NW = 8, PITCH = 16 * DT + 4;
+  extern __shared__ __attribute__((aligned(16))) char lds[];
+  float* const part = (float*)lds;                       // [wavefront][query][PITCH]: O, then m and l behind the head width
+  typedef T V4 __attribute__((ext_vector_type(4)));
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, q16 = lane & 15, g = lane >> 4;
+  const int b = blockIdx.z, h = blockIdx.y, q0 = blockIdx.x * 16;
+  // elements 4 i .. 4 i + 3 of a row of the head, zero beyond the head width
+  auto load4 = [&](const T* row, int i) {
+    f32x4 v = {0.f, 0.f, 0.f, 0.f};
+    if (VEC) {
+      if (4 * i < d) {
+        const V4 t = *(const V4*)(row + 4 * i);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = to_f(t[e]);
+      }
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (4 * i + e < d) v[e] = to_f(row[4 * i + e]);
     }
-    const float m_new = fmaxf(m_run, wave_max(s));
-    const float alpha = active ? __expf(m_run - m_new) : 0.f;
-    const float pj = (active && key < Lk) ? __expf(s - m_new) : 0.f;
-    l_run = l_run * alpha + wave_sum(pj);
-    m_run = m_new;
-    ps[wave][lane] = pj;
-    __syncthreads();
-    acc0 *= alpha; acc1 *= alpha;
-    if (active) {
-      const int nk = min(64, Lk - key0);
-      for (int j = 0; j < nk; ++j) {
-        const float pv = ps[wave][j];
-        if (lane < d)
-          acc0 += pv * to_f(v_t ? V[((size_t)b * C + h * d + lane) * ldv + key0 + j] : V[((size_t)b * Lk + key0 + j) * ldv + h * d + lane]);
-        if (lane + 64 < d)
-          acc1 += pv * to_f(v_t ? V[((size_t)b * C + h * d + lane + 64) * ldv + key0 + j] : V[((size_t)b * Lk + key0 + j) * ldv + h * d + lane + 64]);
+    return v;
+  };
+  f32x4 qf[DT], o[DT];
+  {
+    const T* row = Q + ((size_t)b * L + min(q0 + q16, L - 1)) * ldq + h * d;
+#pragma unroll
+    for (int t = 0; t < DT; ++t) {
+      qf[t] = load4(row, 4 * t + g) * scale_log2;
+      o[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+  }
+  float m = -INFINITY, l = 0.f;
+  for (int key0 = wave * 16; key0 < Lk; key0 += NW * 16) {
+    const T* krow = K + ((size_t)b * Lk + min(key0 + q16, Lk - 1)) * ldk + h * d;
+    f32x4 kf[DT], vf[DT];
+#pragma unroll
+    for (int t = 0; t < DT; ++t) kf[t] = load4(krow, 4 * t + g);
+    // V^T rows (channels 16 t + q16) at keys 4 g + r; the probability of a key past the end is zero, its value is never read
+#pragma unroll
+    for (int t = 0; t < DT; ++t) {
+      const int c = 16 * t + q16;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int key = key0 + 4 * g + r;
+        vf[t][r] = c < d && key < Lk ? to_f(v_t ? V[((size_t)b * C + h * d + c) * ldv + key] : V[((size_t)b * Lk + key) * ldv + h * d + c]) : 0.f;
       }
     }
-    __syncthreads();
+    f32x4 s = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int t = 0; t < DT; ++t)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) s = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[t][e], qf[t][e], s, 0, 0, 0);
+    float mx = -INFINITY;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      if (key0 + 4 * g + r >= Lk) s[r] = -INFINITY;
+      mx = fmaxf(mx, s[r]);
+    }
+    mx = fmaxf(mx, __shfl_xor(mx, 16));
+    mx = fmaxf(mx, __shfl_xor(mx, 32));
+    const float m_new = fmaxf(m, mx), alpha = __builtin_amdgcn_exp2f(m - m_new);
+    m = m_new;
+    float sum = 0.f;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) { s[r] = __builtin_amdgcn_exp2f(s[r] - m); sum += s[r]; }
+    l = l * alpha + sum;                                 // of this lane's keys; the four groups are added at the end
+#pragma unroll
+    for (int t = 0; t < DT; ++t) {
+      o[t] *= alpha;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) o[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[t][r], s[r], o[t], 0, 0, 0);
+    }
   }
-  if (active) {
-    T* orow = O + ((size_t)b * L + query) * ldo + h * d;
-    if (lane < d) orow[lane] = from_f<T>(acc0 / l_run);
-    if (lane + 64 < d) orow[lane + 64] = from_f<T>(acc1 / l_run);
+  l += __shfl_xor(l, 16);
+  l += __shfl_xor(l, 32);
+  float* mine = part + (wave * 16 + q16) * PITCH;
+#pragma unroll
+  for (int t = 0; t < DT; ++t) *(f32x4*)(mine + 16 * t + 4 * g) = o[t];          // channels 16 t + 4 g + r of query q16
+  if (g == 0) { mine[16 * DT] = m; mine[16 * DT + 1] = l; }
+  __syncthreads();
+  for (int i = tid; i < 16 * d; i += 64 * NW) {
+    const int q = i / d, c = i - q * d;
+    if (q0 + q >= L) break;
+    float top = -INFINITY;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) top = fmaxf(top, part[(w * 16 + q) * PITCH + 16 * DT]);
+    float num = 0.f, den = 0.f;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+      const float* p = part + (w * 16 + q) * PITCH;
+      const float f = __builtin_amdgcn_exp2f(p[16 * DT] - top);
+      num += f * p[c];
+      den += f * p[16 * DT + 1];
+    }
+    O[((size_t)b * L + q0 + q) * ldo + h * d + c] = from_f<T>(num / den);
   }
+}
+
+template <typename T>
+static ad_status run_attn_generic(const void* q, const void* k, const void* v, int v_t, int batch, int l, int lk, int c, int d, int ldq,
+                                  int ldk, int ldv, int ldo, void* out, float scale_log2, hipStream_t s) {
+  const bool vec = d % 4 == 0 && (ldq | ldk) % 4 == 0 && (((uintptr_t)q | (uintptr_t)k) % (4 * sizeof(T))) == 0;
+  const dim3 grid((l + 15) / 16, c / d, batch);
+#define AD_ATTNG(DT_, VEC_)                                                                                                              \
+  do {                                                                                                                                   \
+    constexpr int lds_bytes = 8 * 16 * (16 * DT_ + 4) * 4;                                                                               \
+    static std::atomic<bool> attr_set{false};                                                                                            \
+    if (lds_bytes > 65536 && !attr_set) {                                                                                                \
+      AD_HIP(hipFuncSetAttribute((const void*)k_attn_generic<T, DT_, VEC_>, hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes));     \
+      attr_set = true;                                                                                                                   \
+    }                                                                                                                                    \
+    hipLaunchKernelGGL((k_attn_generic<T, DT_, VEC_>), grid, dim3(512), lds_bytes, s, (const T*)q, (const T*)k, (const T*)v, v_t,        \
+                       (T*)out, l, lk, c, d, ldq, ldk, ldv, ldo, scale_log2);                                                            \
+  } while (0)
+#define AD_ATTNG_D(VEC_)                 \
+  if (d <= 16) AD_ATTNG(1, VEC_);        \
+  else if (d <= 32) AD_ATTNG(2, VEC_);   \
+  else if (d <= 64) AD_ATTNG(4, VEC_);   \
+  else AD_ATTNG(8, VEC_)
+  if (vec) { AD_ATTNG_D(true); } else { AD_ATTNG_D(false); }
+#undef AD_ATTNG_D
+#undef AD_ATTNG
+  AD_HIP(hipGetLastError());
+  return AD_OK;
 }
 
 // which MFMA attention kernel: 0 = first generation (32 queries per wavefront, register-staged tiles), 1 / 2 = second
@@ -2345,13 +2434,11 @@ ad_status launch_attention(int dtype, const void* q, const void* k, const void* 
       hipLaunchKernelGGL(k_attn_mfma<false>, dim3(qblocks * heads * batch), dim3(256), 0, s, (const bf16*)q, (const bf16*)k,
                          (const bf16*)v, (bf16*)out, l, lk, c, ldq, ldk, ldv, ldo, scale * 1.44269504088896341f, qblocks);
   } else if (dtype == AD_BF16) {
-    ProfLaunch pl("attn_simple_bf16", 4.0 * batch * l * lk * c, 2.0 * batch * c * (2.0 * l + 2.0 * lk), s);
-    hipLaunchKernelGGL(k_attn_simple<bf16>, dim3((l + 3) / 4, heads, batch), dim3(256), 0, s, (const bf16*)q, (const bf16*)k,
-                       (const bf16*)v, v_t, (bf16*)out, l, lk, c, head_dim, ldq, ldk, ldv, ldo, scale);
+    ProfLaunch pl("attn_generic_bf16", 4.0 * batch * l * lk * c, 2.0 * batch * c * (2.0 * l + 2.0 * lk), s);
+    return run_attn_generic<bf16>(q, k, v, v_t, batch, l, lk, c, head_dim, ldq, ldk, ldv, ldo, out, scale * 1.44269504088896341f, s);
   } else if (dtype == AD_F32) {
-    ProfLaunch pl("attn_simple_f32", 4.0 * batch * l * lk * c, 4.0 * batch * c * (2.0 * l + 2.0 * lk), s);
-    hipLaunchKernelGGL(k_attn_simple<float>, dim3((l + 3) / 4, heads, batch), dim3(256), 0, s, (const float*)q, (const float*)k,
-                       (const float*)v, v_t, (float*)out, l, lk, c, head_dim, ldq, ldk, ldv, ldo, scale);
+    ProfLaunch pl("attn_generic_f32", 4.0 * batch * l * lk * c, 4.0 * batch * c * (2.0 * l + 2.0 * lk), s);
+    return run_attn_generic<float>(q, k, v, v_t, batch, l, lk, c, head_dim, ldq, ldk, ldv, ldo, out, scale * 1.44269504088896341f, s);
   } else {
     AD_FAIL(AD_ERR_INVALID, "attention: bad dtype");
   }

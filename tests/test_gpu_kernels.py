@@ -359,6 +359,20 @@ def test_attention(case, attn_variant):
     assert_kernel_close(got, P.attention(q, k, v, heads), dtype, c=4.0)
 
 
+GENERIC_CASES = [
+    # the generic kernel: head widths in every register class, not a multiple of four (element loads), one key, one more and one
+    # less than a 16-key block and than the 128 keys of a turn of the eight wavefronts, queries that do not fill a block, v transposed
+    (B.AD_F32, 1, 1, 1, 1, 16, False), (B.AD_F32, 2, 17, 15, 1, 8, False), (B.AD_F32, 1, 33, 127, 2, 32, False), (B.AD_F32, 1, 15, 129, 1, 64, False),
+    (B.AD_F32, 1, 40, 257, 1, 128, False), (B.AD_F32, 2, 19, 50, 3, 18, False), (B.AD_F32, 1, 21, 33, 5, 5, False), (B.AD_F32, 1, 48, 70, 1, 72, True),
+    (B.AD_BF16, 1, 31, 65, 2, 40, False), (B.AD_BF16, 1, 18, 144, 3, 6, False), (B.AD_BF16, 1, 50, 30, 2, 64, False),
+]
+
+
+@pytest.mark.parametrize("case", GENERIC_CASES, ids=[f"{'bf16' if c[0] else 'f32'}_l{c[2]}_lk{c[3]}_h{c[4]}_d{c[5]}_{'vt' if c[6] else 'v'}" for c in GENERIC_CASES])
+def test_attention_generic(case):
+    test_attention(case, -1)
+
+
 @pytest.mark.parametrize("dtype,tr", [(B.AD_F32, False), (B.AD_BF16, True)])
 def test_attention_peaky_softmax(dtype, tr, attn_variant):
     """Scores far from uniform (scaled q, k) so that a mistake in the running max / rescaling shows."""
