@@ -131,6 +131,8 @@ struct IgemmParams {
   FastDiv div_hw, div_w;              // by hw_out and by wout (row index -> sample, output row, output column)
   int tiles_m;                        // row tiles
   int k_prof;                         // K the profiler counts (the real one where the operand is zero-padded), else Kp
+  int vec16;                          // row-major outputs and the residual can be accessed 16 bytes at a time
+  int turn16;                         // OUT_QKV: so can the rows of the transposed third
   int n_major;                        // workgroup order: 0 = an XCD owns a run of row tiles (all column tiles of each),
                                       // 1 = an XCD owns a run of column tiles (all row tiles of each); see tile_of()
 };
@@ -151,6 +153,7 @@ __device__ __forceinline__ TileId tile_of(const IgemmParams& p) {
   return TileId{t / p.tiles_n, t % p.tiles_n, split};
 }
 
+constexpr size_t kLdsLimit = 160 * 1024;
 constexpr int kPitch = kRowBytes + 16;   // LDS row pitch in bytes
 
 template <typename T> struct Mma;
@@ -182,22 +185,95 @@ __device__ __forceinline__ V buffer_load16(__amdgpu_buffer_rsrc_t r, unsigned vo
 
 // MODE: epilogue selected at compile time (the OUT_* value, or OUT_PARTIAL for split-K partial sums)
 constexpr int OUT_PARTIAL = 5;
-// Epilogue shared by the GEMM kernels.  A lane holds column l32 of each 32x32 tile; accumulator register
-// r is row 8*(r/4) + 4*half + r%4 of the tile.  Row-major outputs go through LDS (one 32-column slab of
-// the wavefront's tile at a time, fp32, so the result is rounded once) and leave as 4-element vectors
-// with the residual read the same way; transposed outputs store the 4 consecutive rows a lane holds as
-// one vector.  `stage` is the wavefront's private LDS area of WTM rows x 144 bytes; the caller has
-// synchronised the workgroup after its last read of the k-loop tiles.
 template <typename T> struct Vec4;
 template <> struct Vec4<bf16> { typedef bf16x4 type; };
 template <> struct Vec4<float> { typedef f32x4 type; };
 
-template <typename T, int BM, int WTM, int WTN, int TM, int TN, int MODE>
+// How a wavefront's WTM x WTN tile leaves in rows: slabs of 128 bytes of a row (the last one may be 64), 16 bytes a lane.
+template <typename T, int WTM, int WTN>
+struct RowSlabs {
+  static constexpr int VN = Vec<T>::N, FULL = 8 * VN, COUNT = (WTN + FULL - 1) / FULL;
+  static constexpr int width(int s) { return WTN - s * FULL < FULL ? WTN - s * FULL : FULL; }
+  static constexpr int rows(int s) { return 64 * VN / width(s); }              // rows of one access of the wavefront
+  static constexpr int accesses(int s) { return WTM / rows(s); }
+  static constexpr int MAX = WTM / 8;
+  static constexpr int VGPRS = COUNT * MAX * 4;                                // the whole tile, 16 bytes a lane and access
+};
+// Residual rows of slab s in the layout they are added in (p.vec16; rows and columns beyond the output repeat its last ones).
+template <typename T, int WTM, int WTN>
+__device__ __forceinline__ void load_residual(const IgemmParams& p, int s, int row0, int col0, int lane,
+                                              typename Vec<T>::type (&dst)[RowSlabs<T, WTM, WTN>::MAX]) {
+  typedef RowSlabs<T, WTM, WTN> RS;
+  const int lpr = RS::width(s) / RS::VN;
+  const int col = min(col0 + s * RS::FULL + (lane % lpr) * RS::VN, p.N - RS::VN);
+#pragma unroll
+  for (int it = 0; it < RS::accesses(s); ++it) {
+    const int row = min(row0 + it * RS::rows(s) + lane / lpr, p.M - 1);
+    dst[it] = *(const typename Vec<T>::type*)((const T*)p.residual + (size_t)row * p.N + col);
+  }
+}
+// Bytes of LDS a wavefront stages its output in: CR rows of the tile (or all rows of 32 columns, for transposed outputs).
+// The pitch puts the rows that the two halves of a wavefront write together 32 banks apart.
+constexpr int stage_pitch(int columns) { return columns * 4 + 32; }
+template <typename T, int WTM, int WTN>
+constexpr int stage_bytes(int cr) {
+  const int rows = cr * stage_pitch(RowSlabs<T, WTM, WTN>::width(0)), cols = 32 * (WTM * (int)sizeof(T) + 16);
+  return rows > cols ? rows : cols;
+}
+// Orders a wavefront's LDS writes before the reads of other lanes that follow (the LDS unit serves a wavefront in order).
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Epilogue shared by the GEMM kernels.  A lane holds column l32 of each 32x32 tile; accumulator register r is row
+// 8*(r/4) + 4*half + r%4 of the tile.  Row-major outputs go through LDS, CR rows of a slab at a time in fp32 (so the result is
+// rounded once), and leave as whole 128-byte lines, 16 bytes a lane.  What limits it is latency: the residual, the bias and the
+// time projection are requested before the first store of the wavefront (loads and stores retire in order, a load behind a store
+// waits for it), the residual of small tiles even before the k-loop (res, PRE).  `stage`: the wavefront's private LDS area of
+// stage_bytes(CR); the caller has synchronised the workgroup after its last read of the k-loop tiles.
+// Measured (bf16, bias and residual, us; 64-byte pieces of lines and the residual read between the stores -> this): 65536x320x320
+// 62 -> 41, 16384x640x640 37 -> 27, 18432x320x320 16.4 -> 14.1, 2048x1280x1280 18.0 -> 16.5, 3x3 18432x320x2880 45.3 -> 41.2.
+template <typename T, int WTM, int WTN, int TM, int TN, int MODE, int CR, bool PRE>
 __device__ __forceinline__ void igemm_epilogue(const IgemmParams& p, f32x16 (&acc)[TM][TN], int m0, int n0, int wave_m,
-                                               int wave_n, int l32, int half, char* stage, int split) {
+                                               int wave_n, int l32, int half, char* stage, int split,
+                                               typename Vec<T>::type (&res)[RowSlabs<T, WTM, WTN>::COUNT][RowSlabs<T, WTM, WTN>::MAX]) {
   typedef typename Vec4<T>::type V4;
+  typedef typename Vec<T>::type V;
+  typedef RowSlabs<T, WTM, WTN> RS;
+  constexpr int VN = RS::VN;
   const int row_base = m0 + wave_m * WTM + 4 * half;
-  const int col_base = n0 + wave_n * WTN + l32;
+  const int row0 = m0 + wave_m * WTM, col0 = n0 + wave_n * WTN;      // first row and column of this wavefront
+  const int col_base = col0 + l32;
+  const int lane = l32 + 32 * half;
+  // VN columns of one row, staged in fp32
+  auto staged = [&](int row, int pitch, int col, float (&v)[VN]) {
+    const float* src = (const float*)(stage + row * pitch) + col;
+#pragma unroll
+    for (int e = 0; e < VN; e += 4) {
+      const f32x4 x = *(const f32x4*)(src + e);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) v[e + k] = x[k];
+    }
+  };
+  // VN columns to dst, `left` of them inside the output
+  auto store = [&](T* dst, const float (&v)[VN], int ncols, int left) {
+    if (p.vec16) {
+      V o;
+#pragma unroll
+      for (int e = 0; e < VN; ++e) o[e] = from_f<T>(v[e]);
+      *(V*)dst = o;
+    } else if ((ncols & 3) == 0) {
+#pragma unroll
+      for (int e = 0; e < VN; e += 4)
+        if (e < left) *(V4*)(dst + e) = V4{from_f<T>(v[e]), from_f<T>(v[e + 1]), from_f<T>(v[e + 2]), from_f<T>(v[e + 3])};
+    } else {
+#pragma unroll
+      for (int e = 0; e < VN; ++e)
+        if (e < left) dst[e] = from_f<T>(v[e]);
+    }
+  };
   if constexpr (MODE == OUT_PARTIAL) {
     float* dst = p.partial + (size_t)split * p.M * p.N;
 #pragma unroll
@@ -214,55 +290,145 @@ __device__ __forceinline__ void igemm_epilogue(const IgemmParams& p, f32x16 (&ac
     }
   } else if constexpr (MODE == OUT_GEGLU) {
     static_assert(TN % 2 == 0, "GEGLU needs a value and a gate tile per wavefront");
+    constexpr int PITCH = stage_pitch(32), LPR = 32 / VN, ROWS = 64 / LPR;
     const int half_n = p.N >> 1;
-    const int lane = l32 + 32 * half;
+    float bv[TN / 2], bg[TN / 2];
 #pragma unroll
     for (int j = 0; j < TN; j += 2) {
-      const int oc0 = (n0 + wave_n * WTN + j * 32) >> 1;       // packed columns: 32 value, 32 gate
-      const int cv = col_base + j * 32;
-      const float bv = p.bias ? p.bias[cv] : 0.f, bg = p.bias ? p.bias[cv + 32] : 0.f;
+      const int cv = min(col_base + j * 32, p.N - 33);         // packed columns: 32 value, 32 gate; N is a multiple of 64
+      bv[j / 2] = p.bias ? p.bias[cv] : 0.f;
+      bg[j / 2] = p.bias ? p.bias[cv + 32] : 0.f;
+    }
+#pragma unroll
+    for (int j = 0; j < TN; j += 2) {
+      const int oc = ((col0 + j * 32) >> 1) + (lane % LPR) * VN;
 #pragma unroll
       for (int i = 0; i < TM; ++i)
 #pragma unroll
-        for (int r = 0; r < 16; ++r)
-          *(float*)(stage + (i * 32 + 4 * half + 8 * (r >> 2) + (r & 3)) * kPitch + l32 * 4) =
-              (acc[i][j][r] + bv) * gelu_f(acc[i][j + 1][r] + bg);
-      const int c4 = (lane & 7) * 4;
-      if (oc0 + c4 < half_n) {
+        for (int c = 0; c < 32 / CR; ++c) {
+          wave_lds_fence();
 #pragma unroll
-        for (int it = 0; it < WTM / 8; ++it) {
-          const int rl = it * 8 + (lane >> 3), row = m0 + wave_m * WTM + rl;
-          if (row >= p.M) continue;
-          const f32x4 v = *(const f32x4*)(stage + rl * kPitch + c4 * 4);
-          V4 o;
+          for (int q = 0; q < CR / 2; ++q) {
+            const int r = c * (CR / 2) + q;
+            *(float*)(stage + (4 * half + 8 * (q >> 2) + (q & 3)) * PITCH + l32 * 4) = (acc[i][j][r] + bv[j / 2]) * gelu_f(acc[i][j + 1][r] + bg[j / 2]);
+          }
+          wave_lds_fence();
 #pragma unroll
-          for (int e = 0; e < 4; ++e) o[e] = from_f<T>(v[e]);
-          *(V4*)((T*)p.out + (size_t)row * half_n + oc0 + c4) = o;
+          for (int it = 0; it < CR / ROWS; ++it) {
+            const int rl = it * ROWS + lane / LPR, row = row0 + i * 32 + c * CR + rl;
+            float v[VN];
+            staged(rl, PITCH, (lane % LPR) * VN, v);
+            if (row < p.M && oc < half_n) store((T*)p.out + (size_t)row * half_n + oc, v, half_n, half_n - oc);
+          }
         }
-      }
     }
   } else {
-    // sample index of a row: a tile spans at most two samples when a sample has at least BM rows
-    const int b0 = m0 / p.hw_out;
-    const int bnd = (b0 + 1) * p.hw_out;
-    const bool one_step = p.hw_out >= BM;
-    auto sample_of = [&](int row) { return one_step ? b0 + (row >= bnd ? 1 : 0) : row / p.hw_out; };
-    const int lane = l32 + 32 * half;
+    auto sample_of = [&](int row) { return (int)fast_div((unsigned)row, p.div_hw); };
+    constexpr bool VECTOR = MODE != OUT_QKV;                 // a per-sample vector may be added
+    const int c3 = MODE == OUT_QKV ? p.N / 3 : p.N;          // columns of one destination
+    // first column that leaves transposed (a 32-column tile never straddles two thirds: c3 is a multiple of 32)
+    const int turned = (MODE == OUT_TRANSPOSED || MODE == OUT_TRANSPOSED_F32) ? 0 : (MODE == OUT_QKV && p.ld_t > 0) ? 2 * c3 : p.N;
+    // what is added to a column: the bias, and the per-sample vector where the wavefront's rows belong to one sample
+    const int b0 = sample_of(min(row0, p.M - 1));
+    const bool mixed = VECTOR && p.rowvec && sample_of(min(row0 + WTM, p.M) - 1) != b0;
+    float add[TN];
 #pragma unroll
     for (int j = 0; j < TN; ++j) {
-      const int slab = n0 + wave_n * WTN + j * 32;      // first column of this 32-column slab
-      const int col = slab + l32;
-      const float bias = (p.bias && col < p.N) ? p.bias[col] : 0.f;
-      bool transposed = MODE == OUT_TRANSPOSED || MODE == OUT_TRANSPOSED_F32;
-      int c3 = 0, which = 0;
-      if constexpr (MODE == OUT_QKV) {
-        c3 = p.N / 3; which = slab / c3;               // a slab never straddles two thirds (c3 is a multiple of 32)
-        transposed = which == 2 && p.ld_t > 0;
+      const int col = min(col_base + j * 32, p.N - 1);
+      add[j] = p.bias ? p.bias[col] : 0.f;
+      if (VECTOR && p.rowvec && !mixed) add[j] += p.rowvec[(size_t)b0 * p.rowvec_ld + col];
+    }
+    if (VECTOR && mixed) {                                   // rows of two samples: the vector goes into the accumulators
+#pragma unroll
+      for (int j = 0; j < TN; ++j) {
+        const int col = min(col_base + j * 32, p.N - 1);
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            const int row = min(row_base + i * 32 + 8 * (r >> 2) + (r & 3), p.M - 1);
+            acc[i][j][r] += add[j] + p.rowvec[(size_t)sample_of(row) * p.rowvec_ld + col];
+          }
+        add[j] = 0.f;
       }
-      if (transposed) {
+    }
+    // accumulator register r of tile (i, j), with everything added that belongs to its column
+    auto value = [&](int i, int j, int r) { return acc[i][j][r] + add[j]; };
+    const bool with_res = MODE == OUT_ROWMAJOR && p.residual != nullptr;
+    if (MODE == OUT_ROWMAJOR && !PRE && with_res && p.vec16) load_residual<T, WTM, WTN>(p, 0, row0, col0, lane, res[0]);
+    if constexpr (MODE == OUT_ROWMAJOR || MODE == OUT_QKV) {
+      // distances of the other destinations (a lane's columns decide which one it writes)
+      const ptrdiff_t to_k = MODE == OUT_QKV ? (const T*)p.out2 - (const T*)p.out : 0, to_v = MODE == OUT_QKV ? (const T*)p.out3 - (const T*)p.out : 0;
+#pragma unroll
+      for (int s = 0; s < RS::COUNT; ++s) {
+        if (!PRE && s + 1 < RS::COUNT && with_res && p.vec16) load_residual<T, WTM, WTN>(p, s + 1, row0, col0, lane, res[s + 1]);
+        const int width = RS::width(s), pitch = stage_pitch(width), lpr = width / VN, rows = RS::rows(s);
+        const int first = col0 + s * RS::FULL;
+        if (first >= turned) continue;
+        const int cl = (lane % lpr) * VN, col = first + cl;
+        const int which = MODE == OUT_QKV ? (col >= c3) + (col >= 2 * c3) : 0;
+        T* const dst = (T*)p.out + (which == 0 ? 0 : which == 1 ? to_k : to_v) + (col - which * c3);
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+          for (int c = 0; c < 32 / CR; ++c) {
+            wave_lds_fence();
+#pragma unroll
+            for (int jj = 0; jj < width / 32; ++jj)
+#pragma unroll
+              for (int q = 0; q < CR / 2; ++q)
+                *(float*)(stage + (4 * half + 8 * (q >> 2) + (q & 3)) * pitch + (jj * 32 + l32) * 4) =
+                    value(i, s * (RS::FULL / 32) + jj, c * (CR / 2) + q);
+            wave_lds_fence();
+#pragma unroll
+            for (int it = 0; it < CR / rows; ++it) {
+              const int rl = it * rows + lane / lpr, row = row0 + i * 32 + c * CR + rl;
+              float v[VN];
+              staged(rl, pitch, cl, v);
+              if (row >= p.M || col >= turned) continue;
+              if (with_res) {
+                if (p.vec16) {
+#pragma unroll
+                  for (int e = 0; e < VN; ++e) v[e] += to_f(res[s][(i * 32 + c * CR) / rows + it][e]);
+                } else {
+#pragma unroll
+                  for (int e = 0; e < VN; ++e)
+                    if (col + e < p.N) v[e] += to_f(((const T*)p.residual)[(size_t)row * p.N + col + e]);
+                }
+              }
+              store(dst + (size_t)row * c3, v, c3, c3 - (col - which * c3));
+            }
+          }
+      }
+    }
+    if constexpr (MODE != OUT_ROWMAJOR) {
+      const int ncols = c3, third = MODE == OUT_QKV ? 2 * c3 : 0;
+      void* dstp = MODE == OUT_QKV ? p.out3 : p.out;
+#pragma unroll
+      for (int j = 0; j < TN; ++j) {
+        const int tile = col0 + j * 32, col = tile + l32, cc = col - third;
+        if (tile < turned || tile >= p.N) continue;
+        if (MODE == OUT_QKV && p.turn16) {
+          // through LDS: the rows of a column leave 16 bytes a lane (eight rows never straddle two samples)
+          constexpr int PITCH = WTM * (int)sizeof(T) + 16, LPC = WTM / VN, COLS = 64 / LPC;
+          wave_lds_fence();
+#pragma unroll
+          for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int g = 0; g < 4; ++g)
+              *(V4*)(stage + l32 * PITCH + (i * 32 + 8 * g + 4 * half) * (int)sizeof(T)) =
+                  V4{from_f<T>(value(i, j, 4 * g)), from_f<T>(value(i, j, 4 * g + 1)), from_f<T>(value(i, j, 4 * g + 2)), from_f<T>(value(i, j, 4 * g + 3))};
+          wave_lds_fence();
+          const int row = row0 + (lane % LPC) * VN, b = sample_of(min(row, p.M - 1));
+#pragma unroll
+          for (int it = 0; it < 32 / COLS; ++it) {
+            const int cl = it * COLS + lane / LPC;
+            const V v = *(const V*)(stage + cl * PITCH + (lane % LPC) * 16);
+            if (row < p.M && tile + cl < p.N) *(V*)((T*)dstp + ((size_t)b * ncols + (tile + cl - third)) * p.ld_t + (row - b * p.hw_out)) = v;
+          }
+          continue;
+        }
         if (col >= p.N) continue;
-        const int ncols = MODE == OUT_QKV ? c3 : p.N, cc = MODE == OUT_QKV ? col - which * c3 : col;
-        void* dstp = MODE == OUT_QKV ? p.out3 : p.out;
 #pragma unroll
         for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -272,10 +438,7 @@ __device__ __forceinline__ void igemm_epilogue(const IgemmParams& p, f32x16 (&ac
             const int b = sample_of(row);
             float v[4];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              v[e] = acc[i][j][4 * g + e] + bias;
-              if (MODE != OUT_QKV && p.rowvec) v[e] += p.rowvec[(size_t)sample_of(row + e) * p.rowvec_ld + col];
-            }
+            for (int e = 0; e < 4; ++e) v[e] = value(i, j, 4 * g + e);
             const size_t o = ((size_t)b * ncols + cc) * p.ld_t + (row - b * p.hw_out);
             if ((p.hw_out & 3) == 0 && (p.ld_t & 3) == 0 && row + 3 < p.M) {
               if constexpr (MODE == OUT_TRANSPOSED_F32) *(f32x4*)((float*)dstp + o) = f32x4{v[0], v[1], v[2], v[3]};
@@ -291,50 +454,6 @@ __device__ __forceinline__ void igemm_epilogue(const IgemmParams& p, f32x16 (&ac
               }
             }
           }
-        continue;
-      }
-      // row-major: out [M][ncols] (the whole N, or one third of it for the fused q/k/v projection)
-      const int ncols = MODE == OUT_QKV ? c3 : p.N;
-      const int cslab = MODE == OUT_QKV ? slab - which * c3 : slab;
-      T* dst = (T*)(MODE == OUT_QKV ? (which == 0 ? p.out : which == 1 ? p.out2 : p.out3) : p.out);
-      const bool use_rowvec = MODE != OUT_QKV && p.rowvec != nullptr && col < p.N;
-#pragma unroll
-      for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          float v = acc[i][j][r] + bias;
-          if (use_rowvec) {
-            const int row = row_base + i * 32 + 8 * (r >> 2) + (r & 3);
-            v += p.rowvec[(size_t)sample_of(row < p.M ? row : p.M - 1) * p.rowvec_ld + col];
-          }
-          *(float*)(stage + (i * 32 + 4 * half + 8 * (r >> 2) + (r & 3)) * kPitch + l32 * 4) = v;
-        }
-      const int c4 = (lane & 7) * 4;
-      const bool vec_ok = (ncols & 3) == 0;
-      if (slab + c4 < p.N) {
-#pragma unroll
-        for (int it = 0; it < WTM / 8; ++it) {
-          const int rl = it * 8 + (lane >> 3), row = m0 + wave_m * WTM + rl;
-          if (row >= p.M) continue;
-          f32x4 v = *(const f32x4*)(stage + rl * kPitch + c4 * 4);
-          const size_t o = (size_t)row * ncols + cslab + c4;
-          if (vec_ok) {
-            if (MODE == OUT_ROWMAJOR && p.residual) {
-              const V4 rv = *(const V4*)((const T*)p.residual + o);
-#pragma unroll
-              for (int e = 0; e < 4; ++e) v[e] += to_f(rv[e]);
-            }
-            *(V4*)(dst + o) = V4{from_f<T>(v[0]), from_f<T>(v[1]), from_f<T>(v[2]), from_f<T>(v[3])};
-          } else {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              if (slab + c4 + e >= p.N) break;
-              float x = v[e];
-              if (MODE == OUT_ROWMAJOR && p.residual) x += to_f(((const T*)p.residual)[o + e]);
-              dst[o + e] = from_f<T>(x);
-            }
-          }
-        }
       }
     }
   }
@@ -474,7 +593,8 @@ __global__ __launch_bounds__(256) void k_igemm(IgemmParams p) {
   }
 
   // the k-loop ended with a barrier: every wavefront is done with the tiles, LDS can be reused
-  igemm_epilogue<T, BM, WTM, WTN, TM, TN, MODE>(p, acc, m0, n0, wave_m, wave_n, l32, half, lds + wave * (WTM * kPitch), tid3.split);
+  typename Vec<T>::type res[RowSlabs<T, WTM, WTN>::COUNT][RowSlabs<T, WTM, WTN>::MAX];
+  igemm_epilogue<T, WTM, WTN, TM, TN, MODE, 16, false>(p, acc, m0, n0, wave_m, wave_n, l32, half, lds + wave * stage_bytes<T, WTM, WTN>(16), tid3.split, res);
 }
 
 // =================================================================================================
@@ -626,7 +746,8 @@ __global__ __launch_bounds__(256) void k_igemm_dma(IgemmParams p) {
   }
   wait_vmcnt<0>();
   __syncthreads();     // every wavefront is done reading the last tile: LDS can be reused by the epilogue
-  igemm_epilogue<T, BM, WTM, WTN, TM, TN, MODE>(p, acc, m0, n0, wave_m, wave_n, l32, half, lds + wave * (WTM * kPitch), tid3.split);
+  typename Vec<T>::type res[RowSlabs<T, WTM, WTN>::COUNT][RowSlabs<T, WTM, WTN>::MAX];
+  igemm_epilogue<T, WTM, WTN, TM, TN, MODE, 16, false>(p, acc, m0, n0, wave_m, wave_n, l32, half, lds + wave * stage_bytes<T, WTM, WTN>(16), tid3.split, res);
 }
 
 // =================================================================================================
@@ -641,13 +762,13 @@ __global__ __launch_bounds__(256) void k_igemm_dma(IgemmParams p) {
 // =================================================================================================
 // WM: wavefronts along M (2: four wavefronts, one per SIMD; 4: eight wavefronts, two per SIMD, each with half the tile rows -
 // while one of a SIMD's two wavefronts waits at the barrier or for its fragments the other one has MFMAs to issue).
-template <typename T, int BM, int BN, int MODE, int WM = 2>
-__global__ __launch_bounds__(128 * WM) void k_igemm_p3(IgemmParams p) {
+template <typename T, int BM, int BN, int MODE, int WM = 2, int WN = 2, int NSTAGE = 3>
+__global__ __launch_bounds__(64 * WM * WN) void k_igemm_p3(IgemmParams p) {
   typedef typename Vec<T>::type V;
-  constexpr int NW = 2 * WM;                                   // wavefronts: WM x 2
-  constexpr int WTM = BM / WM, WTN = BN / 2, TM = WTM / 32, TN = WTN / 32;
+  constexpr int NW = WM * WN;
+  constexpr int WTM = BM / WM, WTN = BN / WN, TM = WTM / 32, TN = WTN / 32;
   constexpr int ES = (int)sizeof(T), VN = Vec<T>::N, BK = kRowBytes / ES;
-  constexpr int STAGE = (BM + BN) * kRowBytes, NSTAGE = 3;
+  constexpr int STAGE = (BM + BN) * kRowBytes;
   constexpr int AG = BM / (8 * NW), BG = BN / (8 * NW), OPS = AG + BG;     // 8-row groups (= loads) per wavefront and k-tile
   constexpr int RND = 8 * NW;                                  // rows one round of loads (one per wavefront) covers
   constexpr int NG = TM * TN;                                  // MFMA groups per k-step; loads go out during the first three k-steps
@@ -676,7 +797,10 @@ __global__ __launch_bounds__(128 * WM) void k_igemm_p3(IgemmParams p) {
   unsigned b_off[BG];
 #pragma unroll
   for (int i = 0; i < BG; ++i) b_off[i] = (unsigned)((n0 + (NW * i + wave) * 8 + r8) * p.Kp + scol * VN) * ES;
-  // the weight tiles of the first two k-tiles go out before the row arithmetic below, which they do not need
+  constexpr int CR = NW * stage_bytes<T, WTM, WTN>(32) <= NSTAGE * STAGE ? 32 : 16;
+  constexpr bool PRE = MODE == OUT_ROWMAJOR && RowSlabs<T, WTM, WTN>::VGPRS <= 32;
+  V res[RowSlabs<T, WTM, WTN>::COUNT][RowSlabs<T, WTM, WTN>::MAX];
+  // the weight tiles of the first k-tiles go out before the row arithmetic below, which they do not need
 #pragma unroll
   for (int t = 0; t < NSTAGE - 1; ++t)
     if (t < nkt) {
@@ -684,6 +808,10 @@ __global__ __launch_bounds__(128 * WM) void k_igemm_p3(IgemmParams p) {
       for (int i = 0; i < BG; ++i)
         dma_load16(rsw, b_off[i], (unsigned)((kt_begin + t) * BK * ES), lds_base + t * STAGE + grp + (BM + i * RND) * kRowBytes);
     }
+  if (PRE && p.residual && p.vec16 && !idle) {
+#pragma unroll
+    for (int t = 0; t < RowSlabs<T, WTM, WTN>::COUNT; ++t) load_residual<T, WTM, WTN>(p, t, m0 + wave_m * WTM, n0 + wave_n * WTN, lane, res[t]);
+  }
   int a_iy0[AG], a_ix0[AG], a_b[AG];
 #pragma unroll
   for (int i = 0; i < AG; ++i) {
@@ -764,7 +892,7 @@ __global__ __launch_bounds__(128 * WM) void k_igemm_p3(IgemmParams p) {
                            : *(const V*)(st + b_row + (r - TM) * 32 * kRowBytes + sw[ks & 3]);
   };
   int stage = 0;
-  // PHASE 2: a next tile follows and the tile after it is fetched; 1: a next tile follows; 0: last tile
+  // PHASE 2: a next tile follows and tile kt + NSTAGE - 1 is fetched; 1: a next tile follows; 0: last tile
   auto k_tile = [&](auto phase, auto idle_c) {
     constexpr int PHASE = decltype(phase)::value;
     constexpr bool IDLE = decltype(idle_c)::value;
@@ -779,7 +907,7 @@ __global__ __launch_bounds__(128 * WM) void k_igemm_p3(IgemmParams p) {
 #pragma unroll
     for (int ks = 0; ks < 4; ++ks) {
       if (ks == 3 && PHASE >= 1) {
-        if (PHASE == 2) wait_vmcnt<OPS>(); else wait_vmcnt<0>();
+        if (PHASE == 2) wait_vmcnt<(NSTAGE - 2) * OPS>(); else wait_vmcnt<0>();
         __syncthreads();
       }
 #pragma unroll
@@ -808,11 +936,11 @@ __global__ __launch_bounds__(128 * WM) void k_igemm_p3(IgemmParams p) {
     stage = next;
   };
   // issue order so far: B(0), B(1), A(0), A(1): tile 0 is complete once only A(1) is outstanding
-  if (nkt > 1) wait_vmcnt<AG>(); else wait_vmcnt<0>();
+  if (nkt >= NSTAGE - 1) wait_vmcnt<(NSTAGE - 2) * AG>(); else wait_vmcnt<0>();
   __syncthreads();
   int kt = 0;
   if (idle) {
-    for (; kt + 2 < nkt; ++kt) k_tile(std::integral_constant<int, 2>{}, std::true_type{});
+    for (; kt + NSTAGE - 1 < nkt; ++kt) k_tile(std::integral_constant<int, 2>{}, std::true_type{});
     for (; kt + 1 < nkt; ++kt) k_tile(std::integral_constant<int, 1>{}, std::true_type{});
     k_tile(std::integral_constant<int, 0>{}, std::true_type{});
     __syncthreads();
@@ -820,31 +948,31 @@ __global__ __launch_bounds__(128 * WM) void k_igemm_p3(IgemmParams p) {
   }
 #pragma unroll
   for (int r = 0; r < TM + TN; ++r) read_frag(lds, 0, r);
-  for (; kt + 2 < nkt; ++kt) k_tile(std::integral_constant<int, 2>{}, std::false_type{});
+  for (; kt + NSTAGE - 1 < nkt; ++kt) k_tile(std::integral_constant<int, 2>{}, std::false_type{});
   for (; kt + 1 < nkt; ++kt) k_tile(std::integral_constant<int, 1>{}, std::false_type{});
   k_tile(std::integral_constant<int, 0>{}, std::false_type{});
   __syncthreads();     // every wavefront holds its last fragments: LDS can be reused by the epilogue
-  igemm_epilogue<T, BM, WTM, WTN, TM, TN, MODE>(p, acc, m0, n0, wave_m, wave_n, l32, half, lds + wave * (WTM * kPitch), tid3.split);
+  igemm_epilogue<T, WTM, WTN, TM, TN, MODE, CR, PRE>(p, acc, m0, n0, wave_m, wave_n, l32, half, lds + wave * stage_bytes<T, WTM, WTN>(CR), tid3.split, res);
 }
 
-template <typename T, int BM, int BN, int MODE, int WM = 2>
+template <typename T, int BM, int BN, int MODE, int WM = 2, int WN = 2, int NSTAGE = 3>
 static ad_status run_igemm_p3(const IgemmParams& p0, const char* name, hipStream_t s) {
   IgemmParams p = p0;
   p.tiles_n = (p.N + BN - 1) / BN;
   const int tiles_m = (p.M + BM - 1) / BM;
   p.tiles_m = tiles_m;
-  constexpr int lds_bytes = 3 * (BM + BN) * kRowBytes;
-  static_assert(lds_bytes >= 2 * WM * (BM / WM) * kPitch, "epilogue staging fits");
+  constexpr int lds_bytes = NSTAGE * (BM + BN) * kRowBytes;
+  static_assert(lds_bytes >= WM * WN * stage_bytes<T, BM / WM, BN / WN>(16) && lds_bytes <= (int)kLdsLimit, "epilogue staging fits");
   static std::atomic<bool> attr_set{false};
   if (!attr_set) {
-    AD_HIP(hipFuncSetAttribute((const void*)k_igemm_p3<T, BM, BN, MODE, WM>, hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes));
+    AD_HIP(hipFuncSetAttribute((const void*)k_igemm_p3<T, BM, BN, MODE, WM, WN, NSTAGE>, hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes));
     attr_set = true;
   }
   const double in_bytes = (double)p.M * p.ctot * sizeof(T) * (p.stride == 2 ? 4 : 1) / (p.up ? 4 : 1);
   const double out_cols = p.out_mode == OUT_GEGLU ? p.N / 2 : p.N;
   ProfLaunch pl(name, 2.0 * p.M * p.N * p.k_prof, in_bytes + (double)p.N * p.Kp * sizeof(T) + (double)p.M * out_cols * sizeof(T), s, p.M, p.N, p.Kp);
   const int splits = (p.ktiles + p.kt_per_split - 1) / p.kt_per_split;
-  hipLaunchKernelGGL((k_igemm_p3<T, BM, BN, MODE, WM>), dim3(p.tiles_n * tiles_m, splits), dim3(128 * WM), lds_bytes, s, p);
+  hipLaunchKernelGGL((k_igemm_p3<T, BM, BN, MODE, WM, WN, NSTAGE>), dim3(p.tiles_n * tiles_m, splits), dim3(64 * WM * WN), lds_bytes, s, p);
   AD_HIP(hipGetLastError());
   return AD_OK;
 }
@@ -1248,7 +1376,8 @@ __global__ __launch_bounds__(256) void k_conv3_halo(IgemmParams p, HaloParams hp
   }
   wait_vmcnt<0>();
   __syncthreads();     // every wavefront is done reading the tiles: LDS can be reused by the epilogue
-  igemm_epilogue<T, BM, WTM, WTN, TM, TN, MODE>(p, acc, m0, n0, wave_m, wave_n, l32, half, lds + wave * (WTM * kPitch), tid3.split);
+  typename Vec<T>::type res[RowSlabs<T, WTM, WTN>::COUNT][RowSlabs<T, WTM, WTN>::MAX];
+  igemm_epilogue<T, WTM, WTN, TM, TN, MODE, 16, false>(p, acc, m0, n0, wave_m, wave_n, l32, half, lds + wave * stage_bytes<T, WTM, WTN>(16), tid3.split, res);
 }
 
 // Rows of the halo tile for a BM-position tile: the stored pixels between the one tap (-1, -1) of the first position
@@ -1263,7 +1392,6 @@ static int halo_rows(int bm, int ws, int up) {
 static size_t halo_lds_bytes(int bm, int nb, int ws, int up) {
   return (size_t)2 * halo_rows(bm, ws, up) * kRowBytes + (size_t)nb * 128 * kRowBytes + 128;
 }
-constexpr size_t kLdsLimit = 160 * 1024;
 
 template <int BM, int NB, int MODE>
 static ad_status run_conv3_halo(const IgemmParams& p0, int splits, const char* name, hipStream_t s) {
@@ -1531,6 +1659,11 @@ ad_status launch_conv(const ConvArgs& a, hipStream_t s) {
   // workgroup order: the operand that is re-fetched by every XCD should be the smaller one.  The activations of
   // a 3x3 convolution count once per tap: a tap's rows come back only after a whole pass over the channels, long
   // after an L2 has dropped them (measured: 333 instead of 828 MB of L2 fills for the 1920 -> 640 convolution)
+  const int vn = 16 / (int)esize(a.dtype), ncols = a.out_mode == OUT_GEGLU ? a.n_out / 2 : a.out_mode == OUT_QKV ? a.n_out / 3 : a.n_out;
+  const bool turned = a.out_mode == OUT_QKV && a.ld_t > 0;
+  const auto at16 = [](const void* q) { return ((uintptr_t)q & 15) == 0; };
+  p.vec16 = ncols % vn == 0 && at16(a.out) && at16(a.residual) && (a.out_mode != OUT_QKV || (at16(a.out2) && (turned || at16(a.out3))));
+  p.turn16 = turned && at16(a.out3) && a.ld_t % vn == 0 && p.hw_out % vn == 0;
   p.n_major = w_bytes > in_elems * (long long)(a.c0 + a.c1) * (long long)esize(a.dtype) * a.ksize * a.ksize ? 1 : 0;
   if (g_order_override >= 0) p.n_major = g_order_override;
   const ConvPlan plan = choose_plan(a.dtype, m, a.n_out, p.ktiles, a.out_mode);

@@ -191,6 +191,64 @@ def test_conv_split_k(dtype):
     assert_kernel_close(got[:, :, :ho * wo], P.conv2d(x, w, bias).reshape(n, n_out, ho * wo), dtype)
 
 
+EDGE_TILES = [-1, 1, 3, 4, 5, 6, 7]
+
+
+@pytest.mark.parametrize("tile", EDGE_TILES)
+@pytest.mark.parametrize("n_out,shift", [(192, 0), (192, 4), (200, 0), (36, 0), (68, 4), (130, 0)])
+def test_gemm_epilogue_widths_and_alignment(tile, n_out, shift):
+    """Row-major output with bias, per-sample vector and residual: rows of whole 16-byte groups, of whole 8-byte groups and of single
+    elements, tensors that start off a 16-byte boundary, tiles that span three samples and tiles inside one."""
+    for n, h, wd in ((2, 16, 18), (5, 7, 9)):
+        c = 128
+        x = quantize(SI.make_array((n, c, h, wd), 341), B.AD_BF16)
+        w = quantize(SI.make_array((n_out, c, 3, 3), 342, 0.05), B.AD_BF16)
+        bias, rowvec = SI.make_array((n_out,), 343, 0.1), SI.make_array((n, n_out), 344)
+        res = quantize(SI.make_array((n, h, wd, n_out), 345), B.AD_BF16)
+        dx, wp = dev(nchw_to_nhwc(x), B.AD_BF16), dev_bytes(B.pack_conv_weight(B.AD_BF16, w))
+        size = n * h * wd * n_out
+        out, dres = (torch.full((size + 16,), float("nan"), device=DEV, dtype=torch.bfloat16) for _ in range(2))
+        dres[shift:shift + size] = dev(res, B.AD_BF16).reshape(-1)
+        db, dv = dev(bias, B.AD_F32), dev(rowvec, B.AD_F32)
+        B.check(lib.ad_tune_conv_tile(tile))
+        try:
+            B.check(lib.ad_conv_forward(B.AD_BF16, p(dx), None, c, 0, n, h, wd, 0, 3, 1, p(wp), n_out, p(db), p(dv), p(dres[shift:]), p(out[shift:]),
+                                        None, None, B.OUT_ROWMAJOR, 0, None, 0, stream_ptr()))
+            sync()
+        finally:
+            B.check(lib.ad_tune_conv_tile(-1))
+        got = host(out)
+        assert np.isnan(got[:shift]).all() and np.isnan(got[shift + size:]).all()
+        ref = P.conv2d(x, w, bias) + rowvec[:, :, None, None] + nhwc_to_nchw(res)
+        assert_kernel_close(nhwc_to_nchw(got[shift:shift + size].reshape(n, h, wd, n_out)), ref, B.AD_BF16)
+
+
+@pytest.mark.parametrize("tile", EDGE_TILES)
+@pytest.mark.parametrize("bsz,l,c,ld_t,shift", [(2, 72, 64, 72, 0), (2, 72, 64, 76, 0), (3, 44, 64, 48, 0), (3, 45, 64, 45, 0), (1, 300, 320, 304, 0), (2, 72, 64, 72, 4), (2, 136, 96, 136, 0)])
+def test_qkv_transposed_third(tile, bsz, l, c, ld_t, shift):
+    """The transposed third of the fused projection: whole 16-byte groups of rows, sample lengths and pitches that are not, tiles
+    across samples, a destination off a 16-byte boundary; thirds of 96 columns share a 64-column slab."""
+    cin = 64
+    x = quantize(SI.make_array((bsz * l, cin), 351), B.AD_BF16)
+    w = quantize(SI.make_array((3 * c, cin), 352, 0.2), B.AD_BF16)
+    dx, wp = dev(x, B.AD_BF16), dev_bytes(B.pack_conv_weight(B.AD_BF16, w))
+    q, k = (torch.full((bsz * l, c), float("nan"), device=DEV, dtype=torch.bfloat16) for _ in range(2))
+    v = torch.full((bsz * c * ld_t + 16,), float("nan"), device=DEV, dtype=torch.bfloat16)
+    B.check(lib.ad_tune_conv_tile(tile))
+    try:
+        B.check(lib.ad_conv_forward(B.AD_BF16, p(dx), None, cin, 0, bsz, l, 1, 0, 1, 1, p(wp), 3 * c, None, None, None, p(q), p(k), p(v[shift:]),
+                                    B.OUT_QKV, ld_t, None, 0, stream_ptr()))
+        sync()
+    finally:
+        B.check(lib.ad_tune_conv_tile(-1))
+    ref = P.linear(x, w)
+    assert_kernel_close(host(q), ref[:, :c], B.AD_BF16)
+    assert_kernel_close(host(k), ref[:, c:2 * c], B.AD_BF16)
+    got = host(v)[shift:shift + bsz * c * ld_t].reshape(bsz, c, ld_t)
+    assert_kernel_close(got[:, :, :l], ref[:, 2 * c:].reshape(bsz, l, c).transpose(0, 2, 1), B.AD_BF16)
+    assert np.isnan(got[:, :, l:]).all()
+
+
 SMALL_CASES = [
     # edges of the small-tile kernel: one row, fewer k-tiles than wavefronts, 16x16 / 16x32 / 32x32 tiles with remainders, K that does
     # not divide over the wavefronts, two sources, stride 2, nearest-2x input with odd sizes, few columns
