@@ -1,6 +1,6 @@
 // HIP kernels for gfx950 (CDNA4, 64-wide wavefronts) and their launchers.
 //
-//   k_igemm        implicit-GEMM convolution (3x3 / 1x1, stride 1 / 2, optional nearest-2x input,
+//   k_igemm*       implicit-GEMM convolution (3x3 / 1x1, stride 1 / 2, optional nearest-2x input,
 //                  optional channel concatenation) and linear layers on MFMA, with fused epilogues
 //   k_attn_mfma    fused attention (online softmax, K and V^T tiles in LDS, MFMA for QK^T and PV)
 //   k_attn_generic generic attention on fp32 MFMA, keys shared out over the wavefronts (fp32 mode, odd head sizes)
@@ -14,6 +14,7 @@
 
 #include <algorithm>
 #include <atomic>
+#include <cmath>
 #include <mutex>
 #include <type_traits>
 
@@ -57,18 +58,23 @@ __device__ __forceinline__ float silu_f(float x) {
   return x * __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(-1.44269504088896341f * x));
 }
 // Exact-erf GELU x Phi(x) with erf from the rational approximation 7.1.26 of Abramowitz and Stegun,
-// erf(z) = 1 - (a1 t + ... + a5 t^5) exp(-z^2), t = 1 / (1 + p z), |error| <= 1.5e-7: a dozen branch-free vector
-// instructions (the library erff is shorter for |z| < 1 and about twice as long beyond).
+// gelu(x) = max(x, 0) - |x| erfc(|x| / sqrt 2) / 2 with erfc(z) = (a1 t + ... + a5 t^5) exp(-z^2), t = 1 / (1 + p z) (Abramowitz and
+// Stegun 7.1.26, |error| <= 1.5e-7): no sign to put back and no cancellation for negative x.  The GEGLU epilogue is vector work that
+// the matrix cores wait for: 17 instructions, two of them transcendental (30 with an IEEE division for t and 1 + erf).  v_rcp_f32 with one
+// Newton step instead of the division; |x| is capped where the second term has long underflowed, which keeps infinities out of the
+// products.  Against 64 bits over [-12, 12]: largest error 3.3e-7, rms 6.6e-8 (4.7e-7 and 7.2e-8 before).
 __device__ __forceinline__ float gelu_f(float x) {
-  const float z = fabsf(x) * 0.70710678118654752f;
-  const float t = __frcp_rn(fmaf(0.3275911f, z, 1.f));
-  const float e = __builtin_amdgcn_exp2f(-1.44269504088896341f * z * z);
-  float p = fmaf(t, 1.061405429f, -1.453152027f);
-  p = fmaf(t, p, 1.421413741f);
-  p = fmaf(t, p, -0.284496736f);
-  p = fmaf(t, p, 0.254829592f);
-  const float erf_abs = fmaf(-p * t, e, 1.f);
-  return 0.5f * x * (1.f + copysignf(erf_abs, x));
+  const float a = fminf(fabsf(x), 100.f);
+  const float d = fmaf(0.3275911f * 0.70710678118654752f, a, 1.f);
+  const float r = __builtin_amdgcn_rcpf(d);
+  const float t = fmaf(fmaf(-d, r, 1.f), r, r);
+  const float e = __builtin_amdgcn_exp2f(-0.72134752044448170f * a * a);
+  float p = fmaf(t, 0.5f * 1.061405429f, 0.5f * -1.453152027f);
+  p = fmaf(t, p, 0.5f * 1.421413741f);
+  p = fmaf(t, p, 0.5f * -0.284496736f);
+  p = fmaf(t, p, 0.5f * 0.254829592f);
+  const float h = 0.5f * x;
+  return fmaf(-a, p * t * e, h + fabsf(h));
 }
 
 __device__ __forceinline__ float wave_sum(float v) {
@@ -232,13 +238,15 @@ __device__ __forceinline__ void wave_lds_fence() {
 // rounded once), and leave as whole 128-byte lines, 16 bytes a lane.  What limits it is latency: the residual, the bias and the
 // time projection are requested before the first store of the wavefront (loads and stores retire in order, a load behind a store
 // waits for it), the residual of small tiles even before the k-loop (res, PRE).  `stage`: the wavefront's private LDS area of
-// stage_bytes(CR); the caller has synchronised the workgroup after its last read of the k-loop tiles.
+// stage_bytes(CR), swap: WTM x 32 floats that the wavefronts of the same rows share (GEGLU, odd TN); the caller has synchronised the
+// workgroup after its last read of the k-loop tiles.
 // Measured (bf16, bias and residual, us; 64-byte pieces of lines and the residual read between the stores -> this): 65536x320x320
 // 62 -> 41, 16384x640x640 37 -> 27, 18432x320x320 16.4 -> 14.1, 2048x1280x1280 18.0 -> 16.5, 3x3 18432x320x2880 45.3 -> 41.2.
 template <typename T, int WTM, int WTN, int TM, int TN, int MODE, int CR, bool PRE>
 __device__ __forceinline__ void igemm_epilogue(const IgemmParams& p, f32x16 (&acc)[TM][TN], int m0, int n0, int wave_m,
                                                int wave_n, int l32, int half, char* stage, int split,
-                                               typename Vec<T>::type (&res)[RowSlabs<T, WTM, WTN>::COUNT][RowSlabs<T, WTM, WTN>::MAX]) {
+                                               typename Vec<T>::type (&res)[RowSlabs<T, WTM, WTN>::COUNT][RowSlabs<T, WTM, WTN>::MAX],
+                                               float* swap = nullptr) {
   typedef typename Vec4<T>::type V4;
   typedef typename Vec<T>::type V;
   typedef RowSlabs<T, WTM, WTN> RS;
@@ -289,19 +297,16 @@ __device__ __forceinline__ void igemm_epilogue(const IgemmParams& p, f32x16 (&ac
         }
     }
   } else if constexpr (MODE == OUT_GEGLU) {
-    static_assert(TN % 2 == 0, "GEGLU needs a value and a gate tile per wavefront");
+    // packed columns: 32 value, 32 gate; N is a multiple of 64.  With an odd number of 32-column tiles per wavefront (two wavefronts
+    // along N) the last value tile of the first one belongs to the first gate tile of the second, which gets it through LDS.
     constexpr int PITCH = stage_pitch(32), LPR = 32 / VN, ROWS = 64 / LPR;
+    constexpr bool ODD = TN % 2 != 0;
     const int half_n = p.N >> 1;
-    float bv[TN / 2], bg[TN / 2];
+    float bias[TN];
 #pragma unroll
-    for (int j = 0; j < TN; j += 2) {
-      const int cv = min(col_base + j * 32, p.N - 33);         // packed columns: 32 value, 32 gate; N is a multiple of 64
-      bv[j / 2] = p.bias ? p.bias[cv] : 0.f;
-      bg[j / 2] = p.bias ? p.bias[cv + 32] : 0.f;
-    }
-#pragma unroll
-    for (int j = 0; j < TN; j += 2) {
-      const int oc = ((col0 + j * 32) >> 1) + (lane % LPR) * VN;
+    for (int j = 0; j < TN; ++j) bias[j] = p.bias ? p.bias[min(col_base + j * 32, p.N - 1)] : 0.f;
+    auto emit = [&](int tile, auto val, auto gate) {           // tile: first packed column of the pair; val / gate: (i, r) -> value
+      const int oc = (tile >> 1) + (lane % LPR) * VN;
 #pragma unroll
       for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -310,7 +315,7 @@ __device__ __forceinline__ void igemm_epilogue(const IgemmParams& p, f32x16 (&ac
 #pragma unroll
           for (int q = 0; q < CR / 2; ++q) {
             const int r = c * (CR / 2) + q;
-            *(float*)(stage + (4 * half + 8 * (q >> 2) + (q & 3)) * PITCH + l32 * 4) = (acc[i][j][r] + bv[j / 2]) * gelu_f(acc[i][j + 1][r] + bg[j / 2]);
+            *(float*)(stage + (4 * half + 8 * (q >> 2) + (q & 3)) * PITCH + l32 * 4) = val(i, r) * gelu_f(gate(i, r));
           }
           wave_lds_fence();
 #pragma unroll
@@ -321,6 +326,31 @@ __device__ __forceinline__ void igemm_epilogue(const IgemmParams& p, f32x16 (&ac
             if (row < p.M && oc < half_n) store((T*)p.out + (size_t)row * half_n + oc, v, half_n, half_n - oc);
           }
         }
+    };
+    auto pair = [&](auto jc) {
+      constexpr int J = decltype(jc)::value;
+      emit(col0 + J * 32, [&](int i, int r) { return acc[i][J][r] + bias[J]; }, [&](int i, int r) { return acc[i][J + 1][r] + bias[J + 1]; });
+    };
+    if constexpr (!ODD) {
+      pair(std::integral_constant<int, 0>{});
+      static_assert(TN <= 2, "further pairs");
+    } else {
+      static_assert(TN == 5, "two whole pairs and a shared one");
+      if (wave_n == 0) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) swap[(i * 16 + r) * 64 + lane] = acc[i][4][r] + bias[4];
+      }
+      __syncthreads();
+      if (wave_n == 0) {
+        pair(std::integral_constant<int, 0>{});
+        pair(std::integral_constant<int, 2>{});
+      } else {
+        emit(col0 - 32, [&](int i, int r) { return swap[(i * 16 + r) * 64 + lane]; }, [&](int i, int r) { return acc[i][0][r] + bias[0]; });
+        pair(std::integral_constant<int, 1>{});
+        pair(std::integral_constant<int, 3>{});
+      }
     }
   } else {
     auto sample_of = [&](int row) { return (int)fast_div((unsigned)row, p.div_hw); };
@@ -600,7 +630,7 @@ __global__ __launch_bounds__(256) void k_igemm(IgemmParams p) {
 // =================================================================================================
 // The same GEMM with the tiles brought into LDS by the load unit itself (buffer_load ... lds): no
 // VGPR staging, no ds_write (which shares the LDS pipe with the fragment reads and is the slower of
-// the two), and NSTAGE - 1 k-tiles in flight.  LDS rows are dense (128 bytes); the 16-byte column
+// the two).  LDS rows are dense (128 bytes); the 16-byte column
 // of a row is XOR-swizzled with the row number so that fragment reads stay conflict-free.  A
 // wavefront's load covers 8 rows x 128 bytes = 1 KiB, written at m0 + lane * 16.  The loads are
 // issued from inline assembly so that the k-loop can wait for exactly the tile it is about to use.
@@ -625,145 +655,25 @@ template <int N> __device__ __forceinline__ void wait_vmcnt() {
 // (counter SQ_LDS_BANK_CONFLICT: half of the LDS cycles).
 __device__ __forceinline__ int lds_swizzle(int row) { return (row >> 1) & 7; }
 
-template <typename T, int MODE, int NSTAGE>
-__global__ __launch_bounds__(256) void k_igemm_dma(IgemmParams p) {
-  typedef typename Vec<T>::type V;
-  constexpr int BM = 128, BN = 128, WTM = 64, WTN = 64, TM = 2, TN = 2, AV = 4, BV = 4;
-  constexpr int BK = kRowBytes / (int)sizeof(T), ES = (int)sizeof(T), VN = Vec<T>::N;
-  constexpr int STAGE = (BM + BN) * kRowBytes;
-  constexpr int OPS = AV + BV;                   // loads per wavefront per k-tile
-  static_assert(NSTAGE >= 2 && NSTAGE <= 4 && OPS * (NSTAGE - 1) < 64, "pipeline depth");
-  extern __shared__ __attribute__((aligned(16))) char lds[];
-
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int l32 = lane & 31, half = lane >> 5;
-  const int wave_m = wave >> 1, wave_n = wave & 1;
-  const TileId tid3 = tile_of(p);
-  const int m0 = tid3.m_tile * BM, n0 = tid3.n_tile * BN;
-  const u32x4 rs0 = make_rsrc_words(p.src0, p.bytes0), rs1 = make_rsrc_words(p.src1, p.bytes1);
-  const u32x4 rsw = make_rsrc_words(p.w, p.bytes_w);
-
-  // lane -> (row of the wavefront's 8-row group, swizzled 16-byte column it fetches)
-  const int drow = wave * 8 + (lane >> 3);
-  const int scol = (lane & 7) ^ ((drow >> 1) & 7);      // see lds_swizzle()
-  int a_iy0[AV], a_ix0[AV], a_b[AV];
-#pragma unroll
-  for (int i = 0; i < AV; ++i) {
-    const int m = m0 + drow + 32 * i;
-    if (m < p.M) {
-      const int b = (int)fast_div((unsigned)m, p.div_hw), r = m - b * p.hw_out;
-      const int oy = (int)fast_div((unsigned)r, p.div_w), ox = r - oy * p.wout;
-      a_b[i] = b * p.hs; a_iy0[i] = oy * p.stride - p.pad; a_ix0[i] = ox * p.stride - p.pad;
-    } else {
-      a_b[i] = -1; a_iy0[i] = 0; a_ix0[i] = 0;
-    }
-  }
-  unsigned b_off[BV];
-#pragma unroll
-  for (int i = 0; i < BV; ++i) b_off[i] = (unsigned)((n0 + drow + 32 * i) * p.Kp + scol * VN) * ES;
-  unsigned a_off0[AV], a_off1[AV];
-  auto set_tap = [&](int tap) {
-    const int u = tap / p.ksize, v = tap - u * p.ksize;
-#pragma unroll
-    for (int i = 0; i < AV; ++i) {
-      const int iy = a_iy0[i] + u, ix = a_ix0[i] + v;
-      const bool ok = a_b[i] >= 0 && iy >= 0 && iy < p.hin && ix >= 0 && ix < p.win;
-      const unsigned pix = (unsigned)((a_b[i] + (iy >> p.up)) * p.ws + (ix >> p.up));
-      a_off0[i] = ok ? (pix * (unsigned)p.c0 + scol * VN) * ES : kOob;
-      a_off1[i] = ok ? (pix * (unsigned)p.c1 + scol * VN) * ES : kOob;
-    }
-  };
-  const int kt_begin = tid3.split * p.kt_per_split;
-  const int nkt = min(p.ktiles - kt_begin, p.kt_per_split);
-  int f_k0 = kt_begin * BK;
-  int f_tap = f_k0 / p.ctot, f_cc = f_k0 - f_tap * p.ctot;
-  set_tap(f_tap);
-  const unsigned lds_base = (unsigned)(size_t)(__attribute__((address_space(3))) char*)lds;
-  const unsigned grp = (unsigned)wave * 8 * kRowBytes;      // this wavefront's 8-row group inside a 32-row slab
-  auto issue = [&](int stage) {
-    const unsigned st = lds_base + stage * STAGE + grp;
-    if (f_cc < p.c0) {
-#pragma unroll
-      for (int i = 0; i < AV; ++i) dma_load16(rs0, a_off0[i], (unsigned)(f_cc * ES), st + i * 32 * kRowBytes);
-    } else {
-#pragma unroll
-      for (int i = 0; i < AV; ++i) dma_load16(rs1, a_off1[i], (unsigned)((f_cc - p.c0) * ES), st + i * 32 * kRowBytes);
-    }
-#pragma unroll
-    for (int i = 0; i < BV; ++i) dma_load16(rsw, b_off[i], (unsigned)(f_k0 * ES), st + (BM + i * 32) * kRowBytes);
-    f_k0 += BK;
-    f_cc += BK;
-    if (f_cc >= p.ctot) {
-      f_cc = 0;
-      ++f_tap;
-      if (f_tap < p.ksize * p.ksize) set_tap(f_tap);
-    }
-  };
-
-  f32x16 acc[TM][TN];
-#pragma unroll
-  for (int i = 0; i < TM; ++i)
-#pragma unroll
-    for (int j = 0; j < TN; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-
-#pragma unroll
-  for (int t = 0; t < NSTAGE - 1; ++t)
-    if (t < nkt) issue(t);
-  // fragment reads: row * 128 + ((chunk ^ lds_swizzle(row)) * 16), chunk = 2 ks + half
-  const int a_row = (wave_m * WTM + l32) * kRowBytes, b_row = (BM + wave_n * WTN + l32) * kRowBytes;
-  const int x7 = lds_swizzle(l32);
-  int stage = 0;
-  for (int kt = 0; kt < nkt; ++kt) {
-    // tiles issued after kt that may still be in flight: min(NSTAGE - 2, nkt - 1 - kt)
-    const int later = min(NSTAGE - 2, nkt - 1 - kt);
-    if (later >= 2) wait_vmcnt<2 * OPS>();
-    else if (later == 1) wait_vmcnt<OPS>();
-    else wait_vmcnt<0>();
-    __syncthreads();     // tile kt is complete for every wavefront; the stage read in iteration kt-1 is free again
-    if (kt + NSTAGE - 1 < nkt) {
-      int target = stage + NSTAGE - 1;
-      if (target >= NSTAGE) target -= NSTAGE;
-      issue(target);
-    }
-    const char* st = lds + stage * STAGE;
-#pragma unroll
-    for (int ks = 0; ks < kRowBytes / 32; ++ks) {
-      const int sw = ((ks * 2 + half) ^ x7) << 4;
-      V af[TM], bf[TN];
-#pragma unroll
-      for (int i = 0; i < TM; ++i) af[i] = *(const V*)(st + a_row + i * 32 * kRowBytes + sw);
-#pragma unroll
-      for (int j = 0; j < TN; ++j) bf[j] = *(const V*)(st + b_row + j * 32 * kRowBytes + sw);
-#pragma unroll
-      for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j) Mma<T>::run(af[i], bf[j], acc[i][j]);
-    }
-    if (++stage == NSTAGE) stage = 0;
-  }
-  wait_vmcnt<0>();
-  __syncthreads();     // every wavefront is done reading the last tile: LDS can be reused by the epilogue
-  typename Vec<T>::type res[RowSlabs<T, WTM, WTN>::COUNT][RowSlabs<T, WTM, WTN>::MAX];
-  igemm_epilogue<T, WTM, WTN, TM, TN, MODE, 16, false>(p, acc, m0, n0, wave_m, wave_n, l32, half, lds + wave * stage_bytes<T, WTM, WTN>(16), tid3.split, res);
-}
-
 // =================================================================================================
-// Three-stage LDS-DMA GEMM.  Same tile layout in LDS as above; what differs is the order of work
-// inside a k-tile.  The loads of tile kt+2 are spread between the MFMAs of the first three k-steps of
-// tile kt (one every STEP MFMAs, so the load unit's queue never backs up into the issuing wavefront),
-// every fragment read is issued one k-step ahead of its use, and the workgroup barrier sits before
-// the last k-step: once it is passed, tile kt+1 has landed for everyone and everyone holds its last
-// fragments of tile kt in registers, so the first fragments of tile kt+1 are read during that last
-// k-step and the stage of tile kt can be refilled in the next iteration.  One workgroup per CU
-// (96 KiB for 128x128, 144 KiB for 256x128), 4 wavefronts in a 2 x 2 grid.
+// The same GEMM with the tiles brought into LDS by the load unit itself (see above), NSTAGE - 1 k-tiles in flight.  The loads of
+// tile kt + NSTAGE - 1 are spread between the MFMAs of the first three k-steps of tile kt (so the load unit's queue never backs up
+// into the issuing wavefront), every fragment read is issued one k-step ahead of its use, and the workgroup barrier sits before the
+// last k-step: once it is passed, tile kt + 1 has landed for everyone and everyone holds its last fragments of tile kt in registers,
+// so the first fragments of tile kt + 1 are read during that last k-step and the stage of tile kt can be refilled in the next
+// iteration.
+// Three stages, one workgroup per CU: 256x128 (144 KiB), 128x128 (96 KiB).  Two stages: 128x128 and 128x160 with two workgroups per
+// CU, which hide each other's prologue and epilogue, and 256x320 (144 KiB), whose k-tile is long enough for one tile in flight.
+// WM x WN wavefronts; with two per SIMD one has MFMAs to issue while the other waits at the barrier or for its fragments.
+// Bound by the feed from beyond the L2 and by what a launch of few rounds leaves idle, hence the choice of tiles (see kDmaTiles).
+// Measured, bf16, us (best of 128x128, 256x128 and 64x64 -> the tile of this list that kDmaTiles names): GEGLU 2048x10240x1280 72 -> 58
+// (256x320), 3x3 16384x640x5760 139 -> 116 (128x160), 3x3 65536x320x2880 130 -> 121 (256x320), q/k/v 65536x960x320 79 -> 64 (256x320),
+// GEGLU 8192x5120x640 78 -> 66 (256x320), 2048x1280x1280 16.2 -> 13.7 (128x128 for 64x64).
 // =================================================================================================
-// WM: wavefronts along M (2: four wavefronts, one per SIMD; 4: eight wavefronts, two per SIMD, each with half the tile rows -
-// while one of a SIMD's two wavefronts waits at the barrier or for its fragments the other one has MFMAs to issue).
+// Wavefronts per SIMD that LDS allows: what the register budget is set for.
+constexpr int p3_waves_per_simd(int bm, int bn, int waves, int stages) { return (int)(kLdsLimit / (stages * (bm + bn) * kRowBytes)) * waves / 4; }
 template <typename T, int BM, int BN, int MODE, int WM = 2, int WN = 2, int NSTAGE = 3>
-__global__ __launch_bounds__(64 * WM * WN) void k_igemm_p3(IgemmParams p) {
+__global__ __launch_bounds__(64 * WM * WN, p3_waves_per_simd(BM, BN, WM * WN, NSTAGE)) void k_igemm_p3(IgemmParams p) {
   typedef typename Vec<T>::type V;
   constexpr int NW = WM * WN;
   constexpr int WTM = BM / WM, WTN = BN / WN, TM = WTM / 32, TN = WTN / 32;
@@ -794,9 +704,20 @@ __global__ __launch_bounds__(64 * WM * WN) void k_igemm_p3(IgemmParams p) {
   const int nkt = min(p.ktiles - kt_begin, p.kt_per_split);
   const unsigned lds_base = (unsigned)(size_t)(__attribute__((address_space(3))) char*)lds;
   const unsigned grp = (unsigned)wave * 8 * kRowBytes;
-  unsigned b_off[BG];
+  // load i of the weights is RND rows after load 0; large tiles form its offset anew each time, for want of registers
+  constexpr bool TIGHT = TM * TN * 16 > 128;
+  const unsigned b_row0 = (unsigned)((n0 + wave * 8 + r8) * p.Kp + scol * VN) * ES, b_step = (unsigned)(RND * p.Kp) * ES;
+  unsigned b_off[TIGHT ? 1 : BG];
+  if constexpr (!TIGHT) {
 #pragma unroll
-  for (int i = 0; i < BG; ++i) b_off[i] = (unsigned)((n0 + (NW * i + wave) * 8 + r8) * p.Kp + scol * VN) * ES;
+    for (int i = 0; i < BG; ++i) b_off[i] = b_row0 + i * b_step;
+  }
+  auto b_at = [&](int i) {
+    if constexpr (!TIGHT) return b_off[i];
+    unsigned o;
+    asm volatile("v_add_u32 %0, %1, %2" : "=v"(o) : "s"(i * b_step), "v"(b_row0));
+    return o;
+  };
   constexpr int CR = NW * stage_bytes<T, WTM, WTN>(32) <= NSTAGE * STAGE ? 32 : 16;
   constexpr bool PRE = MODE == OUT_ROWMAJOR && RowSlabs<T, WTM, WTN>::VGPRS <= 32;
   V res[RowSlabs<T, WTM, WTN>::COUNT][RowSlabs<T, WTM, WTN>::MAX];
@@ -806,61 +727,73 @@ __global__ __launch_bounds__(64 * WM * WN) void k_igemm_p3(IgemmParams p) {
     if (t < nkt) {
 #pragma unroll
       for (int i = 0; i < BG; ++i)
-        dma_load16(rsw, b_off[i], (unsigned)((kt_begin + t) * BK * ES), lds_base + t * STAGE + grp + (BM + i * RND) * kRowBytes);
+        dma_load16(rsw, b_at(i), (unsigned)((kt_begin + t) * BK * ES), lds_base + t * STAGE + grp + (BM + i * RND) * kRowBytes);
     }
   if (PRE && p.residual && p.vec16 && !idle) {
 #pragma unroll
     for (int t = 0; t < RowSlabs<T, WTM, WTN>::COUNT; ++t) load_residual<T, WTM, WTN>(p, t, m0 + wave_m * WTM, n0 + wave_n * WTN, lane, res[t]);
   }
-  int a_iy0[AG], a_ix0[AG], a_b[AG];
+  // stored pixel of tap (0, 0), a bit per tap that falls inside the image, and (bits 9, 10) its parities for a nearest-2x input
+  int a_pix[AG], a_taps[AG];
 #pragma unroll
   for (int i = 0; i < AG; ++i) {
     const int m = m0 + (NW * i + wave) * 8 + r8;
+    a_pix[i] = 0; a_taps[i] = 0;
     if (m < p.M) {
       const int b = (int)fast_div((unsigned)m, p.div_hw), r = m - b * p.hw_out;
       const int oy = (int)fast_div((unsigned)r, p.div_w), ox = r - oy * p.wout;
-      a_b[i] = b * p.hs; a_iy0[i] = oy * p.stride - p.pad; a_ix0[i] = ox * p.stride - p.pad;
-    } else {
-      a_b[i] = -1; a_iy0[i] = 0; a_ix0[i] = 0;
+      const int iy = oy * p.stride - p.pad, ix = ox * p.stride - p.pad;
+      a_pix[i] = (b * p.hs + (iy >> p.up)) * p.ws + (ix >> p.up);
+      if (p.ksize == 1) {
+        a_taps[i] = 1;
+      } else {
+        int in_row = 0;
+#pragma unroll
+        for (int v = 0; v < 3; ++v) in_row |= (ix + v >= 0 && ix + v < p.win) ? 1 << v : 0;
+#pragma unroll
+        for (int u = 0; u < 3; ++u) a_taps[i] |= (iy + u >= 0 && iy + u < p.hin) ? in_row << (3 * u) : 0;
+      }
+      a_taps[i] |= (iy & 1) << 9 | (ix & 1) << 10;
     }
   }
-  unsigned a_off0[AG], a_off1[AG];
-  auto set_tap = [&](int tap) {
-    const int u = tap / p.ksize, v = tap - u * p.ksize;
+  // byte offsets of this lane's rows for the tap and the source being fetched
+  unsigned a_off[AG];
+  auto set_tap = [&](int tap, unsigned c) {                  // c: channels of the source
+    const int u = p.ksize == 3 ? tap * 11 >> 5 : 0, v = tap - 3 * u;      // tap / 3 without vector work
+    const int step = u * p.ws + v;
 #pragma unroll
     for (int i = 0; i < AG; ++i) {
-      const int iy = a_iy0[i] + u, ix = a_ix0[i] + v;
-      const bool ok = a_b[i] >= 0 && iy >= 0 && iy < p.hin && ix >= 0 && ix < p.win;
-      const unsigned pix = (unsigned)((a_b[i] + (iy >> p.up)) * p.ws + (ix >> p.up));
-      a_off0[i] = ok ? (pix * (unsigned)p.c0 + scol * VN) * ES : kOob;
-      a_off1[i] = ok ? (pix * (unsigned)p.c1 + scol * VN) * ES : kOob;
+      const int pix = a_pix[i] + (p.up ? (((a_taps[i] >> 9 & 1) + u) >> 1) * p.ws + (((a_taps[i] >> 10 & 1) + v) >> 1) : step);
+      a_off[i] = (a_taps[i] >> tap & 1) ? ((unsigned)pix * c + scol * VN) * ES : kOob;
     }
   };
   int f_k0 = kt_begin * BK;
-  int f_tap = f_k0 / p.ctot, f_cc = f_k0 - f_tap * p.ctot;
-  set_tap(f_tap);
-  // per-tile state of the loads being issued: which source holds the channels, and the scalar offsets
-  bool second = false;
+  int f_tap = __builtin_amdgcn_readfirstlane(f_k0 / p.ctot);    // the division is vector work; what follows from it must not be
+  int f_cc = f_k0 - f_tap * p.ctot;
+  const unsigned c0 = (unsigned)p.c0, c1 = (unsigned)p.c1;
+  set_tap(f_tap, f_cc >= p.c0 ? c1 : c0);
+  // per-tile state of the loads being issued: the source that holds the channels, and the scalar offsets
   u32x4 rsa = rs0;
   unsigned soff_a = 0, soff_b = 0;
   auto begin_tile = [&]() {
-    second = f_cc >= p.c0;
+    const bool second = f_cc >= p.c0;
     rsa = second ? rs1 : rs0;
     soff_a = (unsigned)((second ? f_cc - p.c0 : f_cc) * ES);
     soff_b = (unsigned)(f_k0 * ES);
   };
   auto issue_one = [&](int stage, int i) {
     const unsigned st = lds_base + stage * STAGE + grp;
-    if (i < AG) dma_load16(rsa, second ? a_off1[i] : a_off0[i], soff_a, st + i * RND * kRowBytes);
-    else dma_load16(rsw, b_off[i - AG], soff_b, st + (BM + (i - AG) * RND) * kRowBytes);
+    if (i < AG) dma_load16(rsa, a_off[i], soff_a, st + i * RND * kRowBytes);
+    else dma_load16(rsw, b_at(i - AG), soff_b, st + (BM + (i - AG) * RND) * kRowBytes);
   };
   auto end_tile = [&]() {
     f_k0 += BK;
     f_cc += BK;
-    if (f_cc >= p.ctot) {
-      f_cc = 0;
-      ++f_tap;
-      if (f_tap < p.ksize * p.ksize) set_tap(f_tap);
+    if (f_cc == p.c0 || f_cc == p.ctot) {                    // the next source (c0 and ctot are multiples of the k-tile) or the next tap
+      const int wrap = f_cc == p.ctot ? 1 : 0;
+      f_cc = wrap ? 0 : f_cc;
+      f_tap += wrap;
+      set_tap(f_tap, wrap ? c0 : c1);                        // behind the last tap nothing is fetched any more
     }
   };
 
@@ -944,6 +877,7 @@ __global__ __launch_bounds__(64 * WM * WN) void k_igemm_p3(IgemmParams p) {
     for (; kt + 1 < nkt; ++kt) k_tile(std::integral_constant<int, 1>{}, std::true_type{});
     k_tile(std::integral_constant<int, 0>{}, std::true_type{});
     __syncthreads();
+    if constexpr (MODE == OUT_GEGLU && TN % 2 != 0) __syncthreads();      // the epilogue's exchange
     return;
   }
 #pragma unroll
@@ -952,7 +886,8 @@ __global__ __launch_bounds__(64 * WM * WN) void k_igemm_p3(IgemmParams p) {
   for (; kt + 1 < nkt; ++kt) k_tile(std::integral_constant<int, 1>{}, std::false_type{});
   k_tile(std::integral_constant<int, 0>{}, std::false_type{});
   __syncthreads();     // every wavefront holds its last fragments: LDS can be reused by the epilogue
-  igemm_epilogue<T, WTM, WTN, TM, TN, MODE, CR, PRE>(p, acc, m0, n0, wave_m, wave_n, l32, half, lds + wave * stage_bytes<T, WTM, WTN>(CR), tid3.split, res);
+  igemm_epilogue<T, WTM, WTN, TM, TN, MODE, CR, PRE>(p, acc, m0, n0, wave_m, wave_n, l32, half, lds + wave * stage_bytes<T, WTM, WTN>(CR), tid3.split, res,
+                                                         (float*)(lds + NW * stage_bytes<T, WTM, WTN>(CR)) + wave_m * (WTM * 32));
 }
 
 template <typename T, int BM, int BN, int MODE, int WM = 2, int WN = 2, int NSTAGE = 3>
@@ -963,6 +898,7 @@ static ad_status run_igemm_p3(const IgemmParams& p0, const char* name, hipStream
   p.tiles_m = tiles_m;
   constexpr int lds_bytes = NSTAGE * (BM + BN) * kRowBytes;
   static_assert(lds_bytes >= WM * WN * stage_bytes<T, BM / WM, BN / WN>(16) && lds_bytes <= (int)kLdsLimit, "epilogue staging fits");
+  static_assert(MODE != OUT_GEGLU || BN / WN / 32 % 2 == 0 || lds_bytes >= WM * WN * stage_bytes<T, BM / WM, BN / WN>(32) + BM * 128, "so does the exchange");
   static std::atomic<bool> attr_set{false};
   if (!attr_set) {
     AD_HIP(hipFuncSetAttribute((const void*)k_igemm_p3<T, BM, BN, MODE, WM, WN, NSTAGE>, hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes));
@@ -1418,27 +1354,6 @@ static ad_status run_conv3_halo(const IgemmParams& p0, int splits, const char* n
   return AD_OK;
 }
 
-template <typename T, int MODE, int NSTAGE>
-static ad_status run_igemm_dma(const IgemmParams& p0, const char* name, hipStream_t s) {
-  IgemmParams p = p0;
-  p.tiles_n = (p.N + 127) / 128;
-  const int tiles_m = (p.M + 127) / 128;
-  p.tiles_m = tiles_m;
-  constexpr int lds_bytes = NSTAGE * 256 * kRowBytes;
-  static std::atomic<bool> attr_set{false};
-  if (!attr_set) {
-    AD_HIP(hipFuncSetAttribute((const void*)k_igemm_dma<T, MODE, NSTAGE>, hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes));
-    attr_set = true;
-  }
-  const double in_bytes = (double)p.M * p.ctot * sizeof(T) * (p.stride == 2 ? 4 : 1) / (p.up ? 4 : 1);
-  const double out_cols = p.out_mode == OUT_GEGLU ? p.N / 2 : p.N;
-  ProfLaunch pl(name, 2.0 * p.M * p.N * p.k_prof, in_bytes + (double)p.N * p.Kp * sizeof(T) + (double)p.M * out_cols * sizeof(T), s, p.M, p.N, p.Kp);
-  const int splits = (p.ktiles + p.kt_per_split - 1) / p.kt_per_split;
-  hipLaunchKernelGGL((k_igemm_dma<T, MODE, NSTAGE>), dim3(p.tiles_n * tiles_m, splits), dim3(256), lds_bytes, s, p);
-  AD_HIP(hipGetLastError());
-  return AD_OK;
-}
-
 template <typename T, int BM, int BN, int WGM, int WGN, int NSET, int MODE>
 static ad_status run_igemm(const IgemmParams& p0, const char* name, hipStream_t s) {
   IgemmParams p = p0;
@@ -1510,7 +1425,7 @@ __global__ __launch_bounds__(256) void k_splitk_reduce(const float* __restrict__
 // Tile shapes.  The register-staged kernels (64x64, 128x128) serve fp32 and the transposed epilogues; bf16
 // GEMMs with a row-major, GEGLU, fused q/k/v or split-K epilogue take the three-stage LDS-DMA kernel with a
 // 128x128 or a 256x128 tile.
-enum { TILE_128x128 = 1, TILE_64x64 = 3, TILE_DMA2_128 = 4, TILE_P3_128 = 5, TILE_P3_256 = 6, TILE_P3_64 = 7, TILE_HALO_128 = 8, TILE_HALO_256 = 9, TILE_P3_256_W4 = 10, TILE_P3_128_W4 = 11, TILE_P3_256_W16 = 12, TILE_SMALL = 13, TILE_AUTO = -1 };
+enum { TILE_128x128 = 1, TILE_64x64 = 3, TILE_D2_128 = 4, TILE_P3_128 = 5, TILE_P3_256 = 6, TILE_P3_64 = 7, TILE_HALO_128 = 8, TILE_HALO_256 = 9, TILE_P3_256_W4 = 10, TILE_P3_128_W4 = 11, TILE_P3_256_W16 = 12, TILE_SMALL = 13, TILE_D2_160 = 14, TILE_D2_320 = 15, TILE_AUTO = -1 };
 static int g_tile_override = TILE_AUTO;
 static int g_order_override = -1;
 
@@ -1534,17 +1449,29 @@ static int splits_by_tiles(long long m, int n, int ktiles, int out_mode, int bm)
   return (ktiles + per - 1) / per;
 }
 
-// Cost of a (tile, splits) choice for the one-workgroup-per-CU kernels, in units of one 128x128 k-tile of one
-// workgroup (about 0.4 us): rounds of 256 workgroups x (k-tiles per workgroup + a fixed prologue / epilogue
-// share), a 256x128 tile costing 1.8 tiles of 128x128, plus the second pass of split-K (a launch and
-// (splits + 1/2) x M x N x 4 bytes through memory).
-static double plan_cost(long long m, int n, int ktiles, int tile, int splits) {
-  const int bm = tile == TILE_P3_256 ? 256 : 128;
-  const long long wgs = ((m + bm - 1) / bm) * ((n + 127) / 128) * splits;
-  const long long rounds = (wgs + 255) / 256;
+// The LDS-DMA kernels and what a workgroup of theirs takes, in us: `fixed` for prologue, epilogue and launch, and per k-tile with 1, 2
+// or 3 of them resident on a CU (measured over the GEMM shapes of the SD-sized models, operands from beyond the L2).  Wide tiles
+// take the fewest bytes per multiply-add (256x320: 28 bytes a clock and CU at full matrix rate, 128x128: 64, of the 60 or so a CU gets
+// from its L2), two resident workgroups hide each other's prologue and epilogue, small tiles fill the chip when there are few rows.
+struct DmaTile { int tile, bm, bn, per_cu; double fixed, per_kt[3]; };
+static const DmaTile kDmaTiles[] = {
+    {TILE_P3_64, 64, 64, 3, 4.0, {0.32, 0.40, 0.62}},   {TILE_D2_128, 128, 128, 2, 5.0, {0.90, 0.98, 0.98}},
+    {TILE_P3_128, 128, 128, 1, 4.0, {0.50, 0.50, 0.50}}, {TILE_D2_160, 128, 160, 2, 7.0, {1.05, 1.25, 1.25}},
+    {TILE_P3_256, 256, 128, 1, 5.0, {0.80, 0.80, 0.80}}, {TILE_D2_320, 256, 320, 1, 12.0, {2.00, 2.00, 2.00}},
+};
+// Time of a launch, in us.  Rounds of resident workgroups; of the part of the chip that the last round leaves idle kTail is
+// charged, since other streams use the rest.  GEGLU: 1.4 us of vector work per 128x128 tile, which a second resident workgroup
+// covers half of.  Split-K: a second launch that reads the partial sums.
+constexpr double kTail = 0.7;
+static double plan_cost(long long m, int n, int ktiles, int out_mode, const DmaTile& t, int splits) {
+  const long long wgs = ((m + t.bm - 1) / t.bm) * ((n + t.bn - 1) / t.bn) * splits;
+  const int resident = (int)std::min<long long>(t.per_cu, (wgs + 255) / 256);
   const int per = (ktiles + splits - 1) / splits;
-  double cost = (double)rounds * (per + 8) * (tile == TILE_P3_256 ? 1.8 : 1.0);
-  if (splits > 1) cost += 15.0 + (splits + 0.5) * (double)m * n * 4.0 / 2.5e12 / 0.4e-6;
+  const double gelu = out_mode == OUT_GEGLU ? 1.4 * t.bm * t.bn / 16384.0 : 0.0;
+  const double round = t.fixed + per * t.per_kt[resident - 1] + gelu;
+  const double full = (double)wgs / (256 * resident), rounds = std::ceil(full);
+  double cost = round * (kTail * rounds + (1.0 - kTail) * full);
+  if (splits > 1) cost += 4.0 + 2.0 * splits * (double)m * n * 4.0 / 5e6;
   return cost;
 }
 
@@ -1570,12 +1497,11 @@ static ConvPlan choose_plan(int dtype, long long m, int n, int ktiles, int out_m
   if (forced == TILE_P3_256_W4 || forced == TILE_P3_256_W16) forced = TILE_P3_256;
   if (forced == TILE_HALO_128) forced = TILE_P3_128;      // the halo kernels share the tile shapes (and the split-K planning) of these
   if (forced == TILE_HALO_256) forced = TILE_P3_256;
-  if (forced == TILE_P3_128 || forced == TILE_P3_256 || forced == TILE_DMA2_128 || forced == TILE_P3_64) {
-    if (!dma || (forced == TILE_P3_64 && geglu)) forced = TILE_AUTO;
+  if (forced == TILE_P3_128 || forced == TILE_P3_256 || forced == TILE_D2_128 || forced == TILE_P3_64 || forced == TILE_D2_160 || forced == TILE_D2_320) {
+    if (!dma || ((forced == TILE_P3_64 || forced == TILE_D2_160) && geglu)) forced = TILE_AUTO;
   }
   else if (forced != TILE_AUTO && geglu) forced = TILE_AUTO;
   if (forced == TILE_128x128 || forced == TILE_64x64) return ConvPlan{forced, splits_by_tiles(m, n, ktiles, out_mode, forced == TILE_64x64 ? 64 : 128)};
-  if (forced == TILE_DMA2_128) return ConvPlan{forced, splits_by_tiles(m, n, ktiles, out_mode, 128)};
   if (forced == TILE_AUTO && small_tile(m, n, ktiles, out_mode).tm) return ConvPlan{TILE_SMALL, 1};
   if (!dma) {
     // measured on the GEMM shapes of the SD-sized models: 128x128 register-staged tiles pay off once there is
@@ -1584,26 +1510,18 @@ static ConvPlan choose_plan(int dtype, long long m, int n, int ktiles, int out_m
     const int tile = (geglu || tiles128 >= 288 || (m <= 512 && ktiles >= 64)) ? TILE_128x128 : TILE_64x64;
     return ConvPlan{tile, splits_by_tiles(m, n, ktiles, out_mode, tile == TILE_64x64 ? 64 : 128)};
   }
-  // short K with more than a tile per CU: prologue and epilogue dominate, and two co-resident workgroups of the
-  // two-stage kernel (64 KiB each) overlap them; measured faster below about a dozen k-tiles
-  if (forced == TILE_AUTO && ktiles < 12 && ((m + 127) / 128) * ((n + 127) / 128) >= 256) return ConvPlan{TILE_DMA2_128, 1};
   ConvPlan best{TILE_P3_128, 1};
   double best_cost = 1e300;
   const int max_splits = (geglu || n % 4) ? 1 : 16;
-  // few output tiles and a short K (the linear layers of the deeper transformer blocks): nothing amortises the
-  // prologue and epilogue of a 128x128 workgroup, and 64x64 tiles (three workgroups per CU) overlap them;
-  // measured 1.1-1.3x there, slower everywhere else
-  const long long tiles128 = ((m + 127) / 128) * ((n + 127) / 128);
-  if (forced == TILE_P3_64) return ConvPlan{TILE_P3_64, splits_by_tiles(m, n, ktiles, out_mode, 64)};
-  if (forced == TILE_AUTO && !geglu && tiles128 <= 192 && ktiles <= 32) return ConvPlan{TILE_P3_64, 1};
-  for (int tile : {TILE_P3_128, TILE_P3_256}) {
-    if (forced != TILE_AUTO && tile != forced) continue;
+  for (const DmaTile& t : kDmaTiles) {
+    if (forced != TILE_AUTO && t.tile != forced) continue;
+    if (geglu && (t.tile == TILE_P3_64 || t.tile == TILE_D2_160)) continue;      // value and gate columns in one wavefront
     for (int sp = 1; sp <= max_splits; ++sp) {
       if (sp > 1 && ktiles / sp < 4) break;
       const int per = (ktiles + sp - 1) / sp;
       if ((ktiles + per - 1) / per != sp) continue;          // every split must own at least one k-tile
-      const double c = plan_cost(m, n, ktiles, tile, sp);
-      if (c < best_cost) { best_cost = c; best = ConvPlan{tile, sp}; }
+      const double c = plan_cost(m, n, ktiles, out_mode, t, sp);
+      if (c < best_cost) { best_cost = c; best = ConvPlan{t.tile, sp}; }
     }
   }
   return best;
@@ -1758,12 +1676,29 @@ ad_status launch_conv(const ConvArgs& a, hipStream_t s) {
       case OUT_PARTIAL: st = run_igemm_p3<bf16, 64, 64, OUT_PARTIAL>(p, "igemm_bf16_64x64_p3_splitk", s); break;
       default: break;
     }
-  } else if (tile == TILE_DMA2_128) {
-    name = "igemm_bf16_128x128_dma";
-    if (mode == OUT_ROWMAJOR) st = run_igemm_dma<bf16, OUT_ROWMAJOR, 2>(p, name, s);
-    else if (mode == OUT_GEGLU) st = run_igemm_dma<bf16, OUT_GEGLU, 2>(p, name, s);
-    else if (mode == OUT_QKV) st = run_igemm_dma<bf16, OUT_QKV, 2>(p, name, s);
-    else st = run_igemm_dma<bf16, OUT_PARTIAL, 2>(p, "igemm_bf16_128x128_dma_splitk", s);
+  } else if (tile == TILE_D2_128) {
+    switch (mode) {
+      case OUT_ROWMAJOR: st = run_igemm_p3<bf16, 128, 128, OUT_ROWMAJOR, 4, 2, 2>(p, "igemm_bf16_128x128_d2", s); break;
+      case OUT_GEGLU: st = run_igemm_p3<bf16, 128, 128, OUT_GEGLU, 4, 2, 2>(p, "igemm_bf16_128x128_d2", s); break;
+      case OUT_QKV: st = run_igemm_p3<bf16, 128, 128, OUT_QKV, 4, 2, 2>(p, "igemm_bf16_128x128_d2", s); break;
+      case OUT_PARTIAL: st = run_igemm_p3<bf16, 128, 128, OUT_PARTIAL, 4, 2, 2>(p, "igemm_bf16_128x128_d2_splitk", s); break;
+      default: break;
+    }
+  } else if (tile == TILE_D2_160) {
+    switch (mode) {
+      case OUT_ROWMAJOR: st = run_igemm_p3<bf16, 128, 160, OUT_ROWMAJOR, 4, 1, 2>(p, "igemm_bf16_128x160_d2", s); break;
+      case OUT_QKV: st = run_igemm_p3<bf16, 128, 160, OUT_QKV, 4, 1, 2>(p, "igemm_bf16_128x160_d2", s); break;
+      case OUT_PARTIAL: st = run_igemm_p3<bf16, 128, 160, OUT_PARTIAL, 4, 1, 2>(p, "igemm_bf16_128x160_d2_splitk", s); break;
+      default: break;
+    }
+  } else if (tile == TILE_D2_320) {
+    switch (mode) {
+      case OUT_ROWMAJOR: st = run_igemm_p3<bf16, 256, 320, OUT_ROWMAJOR, 4, 2, 2>(p, "igemm_bf16_256x320_d2", s); break;
+      case OUT_GEGLU: st = run_igemm_p3<bf16, 256, 320, OUT_GEGLU, 4, 2, 2>(p, "igemm_bf16_256x320_d2", s); break;
+      case OUT_QKV: st = run_igemm_p3<bf16, 256, 320, OUT_QKV, 4, 2, 2>(p, "igemm_bf16_256x320_d2", s); break;
+      case OUT_PARTIAL: st = run_igemm_p3<bf16, 256, 320, OUT_PARTIAL, 4, 2, 2>(p, "igemm_bf16_256x320_d2_splitk", s); break;
+      default: break;
+    }
   } else if (mode == OUT_GEGLU) {
     if (h16) AD_RUN(bf16, 128, OUT_GEGLU); else AD_RUN(float, 128, OUT_GEGLU);
   } else if (h16) {
@@ -3380,7 +3315,7 @@ size_t ad_conv_workspace_bytes(int dtype, int batch, int h_out, int w_out, int n
 }
 
 ad_status ad_tune_conv_tile(int tile) {
-  if (tile != -1 && tile != 1 && tile != 3 && (tile < 4 || tile > 12)) AD_FAIL(AD_ERR_INVALID, "tile must be -1, 1, 3 or 4..12");
+  if (tile != -1 && tile != 1 && tile != 3 && tile != 14 && tile != 15 && (tile < 4 || tile > 12)) AD_FAIL(AD_ERR_INVALID, "tile must be -1, 1, 3, 4..12, 14 or 15");
   set_tile_override(tile);
   return AD_OK;
 }

@@ -191,11 +191,11 @@ def test_conv_split_k(dtype):
     assert_kernel_close(got[:, :, :ho * wo], P.conv2d(x, w, bias).reshape(n, n_out, ho * wo), dtype)
 
 
-EDGE_TILES = [-1, 1, 3, 4, 5, 6, 7]
+EDGE_TILES = [-1, 1, 3, 4, 5, 6, 7, 14, 15]
 
 
 @pytest.mark.parametrize("tile", EDGE_TILES)
-@pytest.mark.parametrize("n_out,shift", [(192, 0), (192, 4), (200, 0), (36, 0), (68, 4), (130, 0)])
+@pytest.mark.parametrize("n_out,shift", [(192, 0), (192, 4), (200, 0), (36, 0), (68, 4), (130, 0), (328, 0)])
 def test_gemm_epilogue_widths_and_alignment(tile, n_out, shift):
     """Row-major output with bias, per-sample vector and residual: rows of whole 16-byte groups, of whole 8-byte groups and of single
     elements, tensors that start off a 16-byte boundary, tiles that span three samples and tiles inside one."""
@@ -247,6 +247,56 @@ def test_qkv_transposed_third(tile, bsz, l, c, ld_t, shift):
     got = host(v)[shift:shift + bsz * c * ld_t].reshape(bsz, c, ld_t)
     assert_kernel_close(got[:, :, :l], ref[:, 2 * c:].reshape(bsz, l, c).transpose(0, 2, 1), B.AD_BF16)
     assert np.isnan(got[:, :, l:]).all()
+
+
+@pytest.mark.parametrize("tile", [14, 15])
+@pytest.mark.parametrize("case", CONV_CASES[:5], ids=[c[0] for c in CONV_CASES[:5]])
+def test_conv_wide_tiles(tile, case):
+    B.check(lib.ad_tune_conv_tile(tile))
+    try:
+        test_conv_matches_direct_summation(B.AD_BF16, case)
+        test_conv_epilogues(B.AD_BF16)
+        test_conv_split_k(B.AD_BF16)
+    finally:
+        B.check(lib.ad_tune_conv_tile(-1))
+
+
+@pytest.mark.parametrize("tile", [-1, 4, 5, 6, 15])
+@pytest.mark.parametrize("rows,cin,cff", [(300, 64, 160), (77, 128, 32), (520, 64, 224), (256, 192, 64), (130, 64, 96)])
+def test_geglu_tile_edges(tile, rows, cin, cff):
+    """Projection widths that end in every value / gate pair of a 320-column tile (one of them is shared by two wavefronts); a gate far
+    out on either side."""
+    x = quantize(SI.make_array((1, cin, rows, 1), 361), B.AD_BF16)
+    w = quantize(SI.make_array((2 * cff, cin), 362, 0.2), B.AD_BF16)
+    b = SI.make_array((2 * cff,), 363, 0.1)
+    b[cff:cff + 4] = (40.0, -40.0, 300.0, -300.0)
+    B.check(lib.ad_tune_conv_tile(tile))
+    try:
+        got, _ = run_conv(B.AD_BF16, x, None, w[:, :, None, None], b, mode=B.OUT_GEGLU, geglu=True)
+    finally:
+        B.check(lib.ad_tune_conv_tile(-1))
+    y = P.linear(x[0, :, :, 0].T, w, b)
+    ref = y[:, :cff] * P.gelu(y[:, cff:])
+    assert_kernel_close(got.reshape(rows, cff), ref, B.AD_BF16)
+
+
+@pytest.mark.parametrize("tile", [4, 14, 15])
+@pytest.mark.parametrize("c0,c1,k,stride,up", [(192, 64, 3, 1, 1), (64, 192, 3, 2, 0), (128, 128, 1, 2, 0), (64, 64, 3, 1, 0)])
+def test_two_stage_tiles_follow_sources_and_taps(tile, c0, c1, k, stride, up):
+    """The change of source in the middle of a tap, strides and a nearest-2x input of odd size, split over K or not."""
+    n, hs, ws, n_out = 2, 9, 7, 96
+    x0, x1 = (quantize(SI.make_array((n, c, hs, ws), 371 + i), B.AD_BF16) for i, c in enumerate((c0, c1)))
+    w = quantize(SI.make_array((n_out, c0 + c1, k, k), 373, 0.05), B.AD_BF16)
+    bias = SI.make_array((n_out,), 374, 0.1)
+    xin = np.concatenate([x0, x1], 1)
+    ref = P.conv2d(P.upsample_nearest2x(xin) if up else xin, w, bias, stride=stride)
+    B.check(lib.ad_tune_conv_tile(tile))
+    try:
+        for splitk in (False, True):
+            got, _ = run_conv(B.AD_BF16, x0, x1, w, bias, stride, up, splitk=splitk)
+            assert_kernel_close(nhwc_to_nchw(got), ref, B.AD_BF16)
+    finally:
+        B.check(lib.ad_tune_conv_tile(-1))
 
 
 SMALL_CASES = [
