@@ -393,6 +393,15 @@ def test_layernorm(dtype, rows, c):
     assert_kernel_close(host(out), P.layer_norm(x, gam, bet, 1e-5), dtype, rel=1e-5 if dtype == B.AD_F32 else 5e-3)
 
 
+@pytest.mark.parametrize("dtype", DT)
+@pytest.mark.parametrize("rows,c", [(1, 8), (5, 16), (3, 24), (9000, 320), (8193, 640), (2050, 1280), (700, 1304), (66, 2560), (2, 4096), (20000, 88), (70000, 8)])
+def test_layernorm_lane_groups(dtype, rows, c):
+    """Every number of lanes per row, rows that do not fill the last wavefront, widths that do not fill the lanes."""
+    if c > 2048 and dtype == B.AD_F32:
+        c //= 2
+    test_layernorm(dtype, rows, c)
+
+
 # ---------------------------------------------------------------------------------------------------
 LOG2E_F32 = np.float32(1.4426950408889634)
 
