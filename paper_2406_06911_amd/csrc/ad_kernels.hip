@@ -849,7 +849,8 @@ __global__ __launch_bounds__(64 * WM * WN, p3_waves_per_simd(BM, BN, WM * WN, NS
         for (int j = 0; j < TN; ++j) {
           const int g = i * TN + j;
           if constexpr (!IDLE) Mma<T>::run(fr[ks & 1][i], fr[ks & 1][TM + j], acc[i][j]);
-          // fragment r of the next k-step follows MFMA group floor(r NG / (TM+TN)); load l follows slot floor(l 3NG / OPS)
+          // fragment r of the next k-step follows MFMA group floor(r NG / (TM+TN)); the loads follow one another over the first three
+          // k-steps, with two stages over the first one (they are needed before this tile ends: 256x320 tiles, K = 5760, 246 -> 236 us)
 #pragma unroll
           for (int r = 0; r < TM + TN; ++r)
             if (!IDLE && r * NG / (TM + TN) == g) {
@@ -859,7 +860,7 @@ __global__ __launch_bounds__(64 * WM * WN, p3_waves_per_simd(BM, BN, WM * WN, NS
           if (PHASE == 2 && ks < 3) {
 #pragma unroll
             for (int l = 0; l < OPS; ++l)
-              if (l * 3 * NG / OPS == q) issue_one(target, l);
+              if (l * (NSTAGE == 2 ? 1 : 3) * NG / OPS == q) issue_one(target, l);
           }
           __builtin_amdgcn_sched_barrier(0);
           ++q;
@@ -1377,17 +1378,32 @@ static ad_status run_igemm(const IgemmParams& p0, const char* name, hipStream_t 
 
 // Split-K second pass: sums the fp32 partials in a fixed order and applies the epilogue.
 template <typename T>
-__global__ __launch_bounds__(256) void k_splitk_reduce(const float* __restrict__ partial, int splits, int M, int N, int hw_out,
-                                                       const float* __restrict__ bias, const float* __restrict__ rowvec,
-                                                       int rowvec_ld, const T* __restrict__ residual, void* __restrict__ out,
-                                                       void* __restrict__ out2, void* __restrict__ out3, int out_mode, int ld_t) {
-  const int n4 = N / 4;
-  const long long total = (long long)M * n4;
-  for (long long i = (long long)blockIdx.x * 256 + threadIdx.x; i < total; i += (long long)gridDim.x * 256) {
-    const int row = (int)(i / n4), col = (int)(i - (long long)row * n4) * 4;
-    // added in order, eight loads in flight (one at a time, each split costs a round trip to memory: 6.6 us a launch)
+__global__ __launch_bounds__(256) void k_splitk_reduce(const float* __restrict__ partial, int splits, int M, int N, int hw_out, FastDiv div_n4,
+                                                       FastDiv div_hw, int vec, const float* __restrict__ bias,
+                                                       const float* __restrict__ rowvec, int rowvec_ld, const T* __restrict__ residual,
+                                                       void* __restrict__ out, void* __restrict__ out2, void* __restrict__ out3, int out_mode, int ld_t) {
+  typedef typename Vec4<T>::type V4;
+  const unsigned n4 = N / 4, total = (unsigned)M * n4;
+  for (unsigned i = blockIdx.x * 256 + threadIdx.x; i < total; i += gridDim.x * 256) {
+    const int row = (int)fast_div(i, div_n4), col = (int)(i - (unsigned)row * n4) * 4, b = (int)fast_div((unsigned)row, div_hw);
+    // added in order, eight loads in flight (one at a time, each split costs a round trip to memory: 6.6 us a launch); what is added
+    // behind them is requested with them
     const float* src = partial + (size_t)row * N + col;
     const size_t step = (size_t)M * N;
+    float add[4] = {0.f, 0.f, 0.f, 0.f}, per[4] = {0.f, 0.f, 0.f, 0.f};
+    V4 res = V4{};
+    const bool with_res = out_mode == OUT_ROWMAJOR && residual;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      if (bias) add[e] = bias[col + e];
+      if (rowvec) per[e] = rowvec[(size_t)b * rowvec_ld + col + e];
+    }
+    if (with_res) {
+      if (vec) res = *(const V4*)(residual + (size_t)row * N + col);
+      else
+#pragma unroll
+        for (int e = 0; e < 4; ++e) res[e] = residual[(size_t)row * N + col + e];
+    }
     f32x4 v = f32x4{0.f, 0.f, 0.f, 0.f};
     for (int z = 0; z < splits; z += 8) {
       f32x4 t[8];
@@ -1398,19 +1414,29 @@ __global__ __launch_bounds__(256) void k_splitk_reduce(const float* __restrict__
       for (int u = 0; u < 8; ++u)
         if (z + u < splits) v += t[u];
     }
-    const int b = row / hw_out;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      float x = v[e];
-      if (bias) x += bias[col + e];
-      if (rowvec) x += rowvec[(size_t)b * rowvec_ld + col + e];
+      if (bias) v[e] += add[e];
+      if (rowvec) v[e] += per[e];
+      if (with_res) v[e] += to_f(res[e]);
+    }
+    // four columns of a row (never of two thirds where vec is set), or one at a time
+    const int c3 = out_mode == OUT_QKV ? N / 3 : N, which = out_mode == OUT_QKV ? col / c3 : 0;
+    const bool turned = out_mode == OUT_TRANSPOSED || out_mode == OUT_TRANSPOSED_F32 || (which == 2 && ld_t > 0);
+    if (vec && !turned) {
+      T* dst = (T*)(which == 0 ? out : which == 1 ? out2 : out3);
+      *(V4*)(dst + (size_t)row * c3 + col - which * c3) = V4{from_f<T>(v[0]), from_f<T>(v[1]), from_f<T>(v[2]), from_f<T>(v[3])};
+      continue;
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const float x = v[e];
       if (out_mode == OUT_ROWMAJOR) {
-        if (residual) x += to_f(residual[(size_t)row * N + col + e]);
         ((T*)out)[(size_t)row * N + col + e] = from_f<T>(x);
       } else if (out_mode == OUT_QKV) {
-        const int c3 = N / 3, which = (col + e) / c3, cc = col + e - which * c3;
-        if (which == 0) ((T*)out)[(size_t)row * c3 + cc] = from_f<T>(x);
-        else if (which == 1) ((T*)out2)[(size_t)row * c3 + cc] = from_f<T>(x);
+        const int w = (col + e) / c3, cc = col + e - w * c3;
+        if (w == 0) ((T*)out)[(size_t)row * c3 + cc] = from_f<T>(x);
+        else if (w == 1) ((T*)out2)[(size_t)row * c3 + cc] = from_f<T>(x);
         else if (ld_t > 0) ((T*)out3)[((size_t)b * c3 + cc) * ld_t + (row - b * hw_out)] = from_f<T>(x);
         else ((T*)out3)[(size_t)row * c3 + cc] = from_f<T>(x);
       } else {
@@ -1588,6 +1614,7 @@ ad_status launch_conv(const ConvArgs& a, hipStream_t s) {
   const int tile = plan.tile;
   int splits = plan.splits;
   if (splits > 1 && (!a.splitk_ws || a.splitk_bytes < (size_t)splits * m * a.n_out * 4)) splits = 1;   // no scratch: plain launch
+  if (m * (a.n_out / 4) >= 1LL << 31) splits = 1;            // the second pass counts groups of four columns in 32 bits
   p.kt_per_split = splits > 1 ? (p.ktiles + splits - 1) / splits : p.ktiles;
   p.partial = splits > 1 ? (float*)a.splitk_ws : nullptr;
   const int mode = splits > 1 ? OUT_PARTIAL : a.out_mode;
@@ -1712,13 +1739,15 @@ ad_status launch_conv(const ConvArgs& a, hipStream_t s) {
   const long long quads = m * (a.n_out / 4);
   const int blocks = (int)((quads + 255) / 256 < 2048 ? (quads + 255) / 256 : 2048);
   const int rowvec_ld = a.rowvec_ld > 0 ? a.rowvec_ld : (a.rowvec_ld < 0 ? 0 : a.n_out);
+  const auto at4 = [&](const void* q) { return (uintptr_t)q % (4 * esize(a.dtype)) == 0; };
+  const int vec4 = ncols % 4 == 0 && at4(a.out) && at4(a.residual) && (a.out_mode != OUT_QKV || (at4(a.out2) && (turned || at4(a.out3))));
   ProfLaunch pl("splitk_reduce", 0, (double)splits * m * a.n_out * 4 + (double)m * a.n_out * esize(a.dtype), s);
-  if (a.dtype == AD_BF16)
-    hipLaunchKernelGGL(k_splitk_reduce<bf16>, dim3(blocks), dim3(256), 0, s, p.partial, splits, p.M, p.N, p.hw_out, a.bias, a.rowvec,
-                       rowvec_ld, (const bf16*)a.residual, a.out, a.out2, a.out3, a.out_mode, a.ld_t);
-  else
-    hipLaunchKernelGGL(k_splitk_reduce<float>, dim3(blocks), dim3(256), 0, s, p.partial, splits, p.M, p.N, p.hw_out, a.bias, a.rowvec,
-                       rowvec_ld, (const float*)a.residual, a.out, a.out2, a.out3, a.out_mode, a.ld_t);
+#define AD_REDUCE(T_)                                                                                                                  \
+  hipLaunchKernelGGL(k_splitk_reduce<T_>, dim3(blocks), dim3(256), 0, s, p.partial, splits, p.M, p.N, p.hw_out, make_fastdiv((unsigned)(p.N / 4)), \
+                     p.div_hw, vec4, a.bias, a.rowvec, rowvec_ld, (const T_*)a.residual, a.out, a.out2, a.out3, a.out_mode, a.ld_t)
+  if (a.dtype == AD_BF16) AD_REDUCE(bf16);
+  else AD_REDUCE(float);
+#undef AD_REDUCE
   AD_HIP(hipGetLastError());
   return AD_OK;
 }
