@@ -57,7 +57,7 @@ template <> __device__ __forceinline__ float from_f<float>(float v) { return v; 
 __device__ __forceinline__ float silu_f(float x) {
   return x * __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(-1.44269504088896341f * x));
 }
-// Exact-erf GELU x Phi(x) with erf from the rational approximation 7.1.26 of Abramowitz and Stegun,
+// Exact-erf GELU x Phi(x):
 // gelu(x) = max(x, 0) - |x| erfc(|x| / sqrt 2) / 2 with erfc(z) = (a1 t + ... + a5 t^5) exp(-z^2), t = 1 / (1 + p z) (Abramowitz and
 // Stegun 7.1.26, |error| <= 1.5e-7): no sign to put back and no cancellation for negative x.  The GEGLU epilogue is vector work that
 // the matrix cores wait for: 17 instructions, two of them transcendental (30 with an IEEE division for t and 1 + erf).  v_rcp_f32 with one
@@ -1448,9 +1448,8 @@ __global__ __launch_bounds__(256) void k_splitk_reduce(const float* __restrict__
   }
 }
 
-// Tile shapes.  The register-staged kernels (64x64, 128x128) serve fp32 and the transposed epilogues; bf16
-// GEMMs with a row-major, GEGLU, fused q/k/v or split-K epilogue take the three-stage LDS-DMA kernel with a
-// 128x128 or a 256x128 tile.
+// Tile shapes.  The register-staged kernels (64x64, 128x128) serve fp32 and the transposed epilogues; bf16 GEMMs with a row-major,
+// GEGLU, fused q/k/v or split-K epilogue take the LDS-DMA kernel with a tile of kDmaTiles; launches of few small tiles k_igemm_small.
 enum { TILE_128x128 = 1, TILE_64x64 = 3, TILE_D2_128 = 4, TILE_P3_128 = 5, TILE_P3_256 = 6, TILE_P3_64 = 7, TILE_HALO_128 = 8, TILE_HALO_256 = 9, TILE_P3_256_W4 = 10, TILE_P3_128_W4 = 11, TILE_P3_256_W16 = 12, TILE_SMALL = 13, TILE_D2_160 = 14, TILE_D2_320 = 15, TILE_AUTO = -1 };
 static int g_tile_override = TILE_AUTO;
 static int g_order_override = -1;
