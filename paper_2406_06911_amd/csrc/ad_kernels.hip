@@ -955,9 +955,8 @@ __global__ __launch_bounds__(512) void k_igemm_small(IgemmParams p) {
   const TileId t3 = tile_of(p);
   const int m0 = t3.m_tile * BM, n0 = t3.n_tile * BN;
 
-  // byte offsets of this lane's rows; the activations' at tap (0, 0), from a base moved back by one row and one pixel, with
-  // a bit per tap that falls inside the image
-  const unsigned shift = p.pad ? (unsigned)(p.ws + 1) : 0u;
+  // byte offsets of this lane's rows; the activations' at tap (0, 0) (modulo 2^32 where that tap lies before the tensor), with a bit per
+  // tap that falls inside the image
   unsigned a_off0[TM], a_off1[TM], a_taps[TM], b_off[TN];
   int a_par[TM];                                         // nearest-2x input: row and column parity of tap (0, 0)
 #pragma unroll
@@ -970,7 +969,7 @@ __global__ __launch_bounds__(512) void k_igemm_small(IgemmParams p) {
       const int b = (int)fast_div((unsigned)m, p.div_hw), r = m - b * p.hw_out;
       const int oy = (int)fast_div((unsigned)r, p.div_w), ox = r - oy * p.wout;
       const int iy0 = oy * p.stride - p.pad, ix0 = ox * p.stride - p.pad;
-      const unsigned pix = (unsigned)((b * p.hs + (iy0 >> p.up)) * p.ws + (ix0 >> p.up) + (int)shift);
+      const unsigned pix = (unsigned)((b * p.hs + (iy0 >> p.up)) * p.ws + (ix0 >> p.up));
       a_off0[i] = (pix * (unsigned)p.c0 + kg * VN) * ES;
       a_off1[i] = (pix * (unsigned)p.c1 + kg * VN) * ES;
       a_par[i] = (iy0 & 1) + 2 * (ix0 & 1);
@@ -981,8 +980,8 @@ __global__ __launch_bounds__(512) void k_igemm_small(IgemmParams p) {
           if (u < p.ksize && v < p.ksize && iy0 + u >= 0 && iy0 + u < p.hin && ix0 + v >= 0 && ix0 + v < p.win) a_taps[i] |= 1u << (u * 3 + v);
     }
   }
-  const __amdgpu_buffer_rsrc_t rs0 = make_rsrc((const char*)p.src0 - (size_t)shift * p.c0 * ES, p.bytes0 + shift * p.c0 * ES);
-  const __amdgpu_buffer_rsrc_t rs1 = make_rsrc((const char*)p.src1 - (size_t)shift * p.c1 * ES, p.bytes1 + shift * p.c1 * ES);
+  const __amdgpu_buffer_rsrc_t rs0 = make_rsrc(p.src0, p.bytes0);
+  const __amdgpu_buffer_rsrc_t rs1 = make_rsrc(p.src1, p.bytes1);
   const __amdgpu_buffer_rsrc_t rsw = make_rsrc(p.w, p.bytes_w);
 
   const int mine = (p.ktiles - wave + NW - 1) / NW;      // k-tiles of this wavefront (0 when there are fewer k-tiles than wavefronts)
@@ -997,14 +996,16 @@ __global__ __launch_bounds__(512) void k_igemm_small(IgemmParams p) {
       for (int h = 0; h < 2; ++h) bf[s][j][h] = buffer_load16<V>(rsw, b_off[j] + h * 64, sb);
     const bool second = f_cc >= p.c0;
     const unsigned cs = (unsigned)(second ? p.c1 : p.c0) * ES, sc = (unsigned)(second ? f_cc - p.c0 : f_cc) * ES;
-    const unsigned sa = p.up ? sc : sc + (unsigned)(u * p.ws + v) * cs;
+    // the tap goes into the lane's offset: the range check compares that offset with the tensor's size less the scalar one, which
+    // therefore has to stay below the size (it does: a channel, never a row, of the tensor)
+    const unsigned tap = (unsigned)(u * p.ws + v) * cs;
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
       unsigned o = second ? a_off1[i] : a_off0[i];
-      if (p.up) o += (unsigned)((((a_par[i] & 1) + u) >> 1) * p.ws + (((a_par[i] >> 1) + v) >> 1)) * cs;
+      o += p.up ? (unsigned)((((a_par[i] & 1) + u) >> 1) * p.ws + (((a_par[i] >> 1) + v) >> 1)) * cs : tap;
       o = (a_taps[i] & bit) ? o : kOob;
 #pragma unroll
-      for (int h = 0; h < 2; ++h) af[s][i][h] = second ? buffer_load16<V>(rs1, o + h * 64, sa) : buffer_load16<V>(rs0, o + h * 64, sa);
+      for (int h = 0; h < 2; ++h) af[s][i][h] = second ? buffer_load16<V>(rs1, o + h * 64, sc) : buffer_load16<V>(rs0, o + h * 64, sc);
     }
     f_k += BK * NW; f_cc += BK * NW;
     while (f_cc >= p.ctot) { f_cc -= p.ctot; ++f_tap; }

@@ -306,6 +306,10 @@ SMALL_CASES = [
     ("16x32_ragged", 2, 64, 0, 23, 24, 72, 3, 1, 0), ("32x32_ragged", 1, 320, 0, 13, 21, 520, 1, 1, 0), ("concat", 1, 64, 128, 11, 6, 96, 3, 1, 0),
     ("stride2", 2, 64, 0, 14, 10, 64, 3, 2, 0), ("stride2_1x1", 1, 128, 0, 9, 9, 48, 1, 2, 0), ("up", 2, 64, 64, 5, 7, 64, 3, 1, 1),
     ("few_columns", 2, 64, 0, 12, 12, 4, 3, 1, 0), ("odd_columns", 1, 64, 0, 6, 6, 7, 3, 1, 0),
+    # maps smaller than the distance between the first and the last tap: one pixel, one row, one column, of one sample and of two
+    ("one_pixel", 1, 256, 0, 1, 1, 256, 3, 1, 0), ("one_pixel_x2", 2, 256, 0, 1, 1, 256, 3, 1, 0), ("one_pixel_concat", 2, 64, 128, 1, 1, 64, 3, 1, 0),
+    ("one_row_3x3", 1, 128, 0, 1, 6, 96, 3, 1, 0), ("one_row_concat", 1, 64, 64, 1, 5, 64, 3, 1, 0), ("one_column", 1, 128, 0, 2, 1, 64, 3, 1, 0),
+    ("one_row_stride2", 1, 64, 0, 1, 9, 64, 3, 2, 0), ("one_pixel_up", 1, 128, 0, 1, 1, 64, 3, 1, 1),
 ]
 
 
