@@ -2920,16 +2920,16 @@ __global__ __launch_bounds__(NT) void k_gn_apply(const T* __restrict__ src0, con
 }
 
 // GroupNorm in one launch: a workgroup owns one (sample, group), keeps its (C/G) x HW elements in registers, reduces them
-// and writes the normalised result, so the tensor is read once and nothing
-// goes through scratch memory.  G: channels per access (the widest that divides the channels of a group), NV: accesses a
-// thread can hold; thread (pixel lane, access of the pixel) walks the pixels in steps of `pl`, so its channels stay the same.
+// and writes the normalised result, so the tensor is read once and nothing goes through scratch memory.  G: channels per
+// access (the widest that divides the channels of a group), NV: accesses a thread can hold; thread (pixel lane, access of the pixel)
+// walks the pixels in steps of `pl`, so its channels stay the same.
 // Neighbouring groups share cache lines: xcd_remap puts them on one XCD.  Bound by one round trip to memory and the launch.
 template <typename T, int G, int NT, int NV>
 __global__ __launch_bounds__(NT) void k_gn_group(const T* __restrict__ src0, const T* __restrict__ src1, int c0, int c1, int hw,
-                                                 int groups, int pl, const float* __restrict__ gamma, const float* __restrict__ beta,
-                                                 float eps, int silu, T* __restrict__ out) {
+                                                 int groups, int pl, double inv_n, const float* __restrict__ gamma,
+                                                 const float* __restrict__ beta, float eps, int silu, T* __restrict__ out) {
   typedef T V __attribute__((ext_vector_type(G)));
-  __shared__ float red[2][NT / 64];
+  __shared__ float red[3][NT / 64];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int vid = xcd_remap(blockIdx.x, gridDim.x);
   const int b = vid / groups, g = vid - b * groups;
@@ -2939,9 +2939,6 @@ __global__ __launch_bounds__(NT) void k_gn_group(const T* __restrict__ src0, con
   const int ld = second ? c1 : c0;
   const T* src = (second ? src1 + (c - c0) : src0 + c) + (size_t)b * hw * ld;
   const int p_end = lanep < pl ? hw : 0;
-  // sums of x - pivot and of its square in one pass: with the pivot inside the data nothing cancels
-  const int cg = g * cpg;
-  const float pivot = to_f(cg >= c0 ? src1[(size_t)b * hw * c1 + cg - c0] : src0[(size_t)b * hw * c0 + cg]);
   V x[NV];
 #pragma unroll
   for (int k = 0; k < NV; ++k) {
@@ -2951,22 +2948,43 @@ __global__ __launch_bounds__(NT) void k_gn_group(const T* __restrict__ src0, con
   float ga[G], be[G];
 #pragma unroll
   for (int e = 0; e < G; ++e) { ga[e] = p_end ? gamma[c + e] : 0.f; be[e] = p_end ? beta[c + e] : 0.f; }
+  // The mean first, to the 12 leading bits (x less it is then exact but for a few elements), then the sums of the deviations from it and of
+  // their squares: nothing cancels whatever the offset and the outliers.  The wavefronts' sums are folded in double, as in the two
+  // launches.
   float s = 0.f, q = 0.f;
 #pragma unroll
   for (int k = 0; k < NV; ++k)
     if (lanep + k * pl < p_end)
 #pragma unroll
-      for (int e = 0; e < G; ++e) { const float d = to_f(x[k][e]) - pivot; s += d; q += d * d; }
-  s = wave_sum(s); q = wave_sum(q);
-  if (lane == 0) { red[0][wave] = s; red[1][wave] = q; }
+      for (int e = 0; e < G; ++e) s += to_f(x[k][e]);
+  s = wave_sum(s);
+  if (lane == 0) red[0][wave] = s;
   __syncthreads();
-  s = 0.f; q = 0.f;
+  s = 0.f;
 #pragma unroll
-  for (int w = 0; w < NT / 64; ++w) { s += red[0][w]; q += red[1][w]; }
-  const float n = (float)hw * cpg, shift = s / n, mean = pivot + shift;
-  const float rstd = rsqrtf(fmaxf(q / n - shift * shift, 0.f) + eps);
+  for (int w = 0; w < NT / 64; ++w) s += red[0][w];
+  float about = __uint_as_float(__float_as_uint(s * (float)inv_n) & 0xfffff000u);
+  s = 0.f;
 #pragma unroll
-  for (int e = 0; e < G; ++e) { ga[e] *= rstd; be[e] -= mean * ga[e]; }
+  for (int k = 0; k < NV; ++k)
+    if (lanep + k * pl < p_end)
+#pragma unroll
+      for (int e = 0; e < G; ++e) { const float d = to_f(x[k][e]) - about; s += d; q += d * d; }
+  s = wave_sum(s); q = wave_sum(q);
+  if (lane == 0) { red[1][wave] = s; red[2][wave] = q; }
+  __syncthreads();
+  double ds = 0.0, dq = 0.0;
+#pragma unroll 4
+  for (int w = 0; w < NT / 64; ++w) { ds += red[1][w]; dq += red[2][w]; }
+  const double rest = ds * inv_n;                        // mean - about
+  double var = dq * inv_n - rest * rest;
+  var = (var < 0.0 ? 0.0 : var) + (double)eps;
+  // 1 / sqrt(var): one Newton step on the fp32 value, a fifth of the instructions of the double division and root
+  const float r0 = rsqrtf((float)var);
+  const float rstd = (float)(var > 1e-30 && var < 1e30 ? r0 * (1.5 - 0.5 * var * r0 * r0) : 1.0 / sqrt(var)), shift = (float)rest;
+#pragma unroll
+  for (int e = 0; e < G; ++e) { ga[e] *= rstd; be[e] -= shift * ga[e]; }
+  asm volatile("" : "+v"(about));                        // x - about is formed anew: kept from the sums on, 48 elements would not fit
 #pragma unroll
   for (int k = 0; k < NV; ++k) {
     const int p = lanep + k * pl;
@@ -2974,7 +2992,7 @@ __global__ __launch_bounds__(NT) void k_gn_group(const T* __restrict__ src0, con
       V o;
 #pragma unroll
       for (int e = 0; e < G; ++e) {
-        float y = to_f(x[k][e]) * ga[e] + be[e];
+        float y = (to_f(x[k][e]) - about) * ga[e] + be[e];
         if (silu) y = silu_f(y);
         o[e] = from_f<T>(y);
       }
@@ -2999,8 +3017,9 @@ static ad_status launch_gn_group(const void* src0, const void* src1, int c0, int
   constexpr int VN = Vec<T>::N;
   ProfLaunch prof("gn_group", 0, 2.0 * batch * hw * ctot * sizeof(T), s, batch * hw, ctot, 0);
   const dim3 grid(groups * batch);
+  const double inv_n = 1.0 / ((double)hw * (ctot / groups));
 #define AD_GN(G_) hipLaunchKernelGGL((k_gn_group<T, G_, NT, REGS * 4 / (G_ * (int)sizeof(T))>), grid, dim3(NT), 0, s, (const T*)src0, (const T*)src1, \
-                                     c0, c1, hw, groups, pl, gamma, beta, eps, silu, (T*)out)
+                                     c0, c1, hw, groups, pl, inv_n, gamma, beta, eps, silu, (T*)out)
   if (ga == VN) AD_GN(VN);
   else if (ga == VN / 2) AD_GN(VN / 2);
   else AD_GN(VN / 4);

@@ -386,6 +386,30 @@ def test_groupnorm_every_path(dtype, shape):
 
 
 @pytest.mark.parametrize("dtype", DT)
+@pytest.mark.parametrize("shape", [(2, 256, 0, 6, 7, 32), (1, 640, 320, 24, 21, 32), (2, 1280, 0, 24, 24, 32), (2, 320, 0, 61, 59, 32), (1, 4608, 0, 9, 7, 32)],
+                         ids=["one_launch_256", "one_launch_straddling", "one_launch_1024", "two_launches", "4608_channels"])
+@pytest.mark.parametrize("outlier,offset", [(30.0, 0.0), (-100.0, 0.0), (0.0, 10.0), (0.0, -100.0)])
+def test_groupnorm_outliers_and_offsets(dtype, shape, outlier, offset):
+    """Statistics that must not cancel: the first element of every group of every sample far out, all elements far from zero."""
+    n, c0, c1, h, w, groups = shape
+    if h * w > 3000 and abs(offset) > 10:
+        offset = math.copysign(10.0, offset)       # two launches: fp32 sums of squares about zero, 2^-24 (1 + offset^2) at most
+    c = c0 + c1
+    x = SI.make_array((n, c, h, w), 45) + offset
+    if outlier:
+        x[:, ::c // groups, 0, 0] = outlier
+    x = quantize(x, dtype)
+    gam, bet = 1 + SI.make_array((c,), 46, 0.3), SI.make_array((c,), 47, 0.3)
+    d0, d1 = dev(nchw_to_nhwc(x[:, :c0]), dtype), dev(nchw_to_nhwc(x[:, c0:]), dtype) if c1 else None
+    out = torch.full((n, h, w, c), float("nan"), device=DEV, dtype=tdtype(dtype))
+    scratch = torch.zeros(lib.ad_groupnorm_scratch_bytes(n, h * w, c), dtype=torch.uint8, device=DEV)
+    dg, dbt = dev_f32(gam), dev_f32(bet)
+    B.check(lib.ad_groupnorm_forward(dtype, p(d0), p(d1), c0, c1, n, h * w, groups, p(dg), p(dbt), 1e-5, 0, p(out), p(scratch), stream_ptr()))
+    sync()
+    assert_kernel_close(nhwc_to_nchw(host(out)), P.group_norm(x, groups, gam, bet, 1e-5), dtype, rel=1e-5 if dtype == B.AD_F32 else 5e-3)
+
+
+@pytest.mark.parametrize("dtype", DT)
 @pytest.mark.parametrize("rows,c", [(7, 64), (300, 320), (33, 1280)])
 def test_layernorm(dtype, rows, c):
     x = quantize(SI.make_array((rows, c), 51) * 3 + 1, dtype)
