@@ -3064,7 +3064,8 @@ static ad_status run_groupnorm(const void* src0, const void* src1, int c0, int c
   // workgroups of 256 threads, each folding the same 32 KiB in two dependent steps, 18.0, 28.3 and 23.0.
   constexpr int NT = 1024;
   const int nv = ctot / Vec<T>::N, pl = NT / std::min(nv, NT);
-  const int rows_per_block = std::max(pl, (int)((rows * NT + 256 * 1024 - 1) / (256 * 1024)));
+  const int per_sample = std::max(1, 256 / batch);            // a 257th workgroup would wait for a CU
+  const int rows_per_block = std::max(pl, (hw + per_sample - 1) / per_sample);
   const int row_blocks = (hw + rows_per_block - 1) / rows_per_block;
   ProfLaunch pl_("gn_apply", 0, 2.0 * rows * ctot * sizeof(T), s, (int)rows, ctot, 0);
   hipLaunchKernelGGL((k_gn_apply<T, NT>), dim3(row_blocks, batch), dim3(NT), 0, s, (const T*)src0, (const T*)src1, c0, c1, hw, rows_per_block, nchunk,
