@@ -3034,13 +3034,22 @@ static ad_status run_groupnorm(const void* src0, const void* src1, int c0, int c
                                hipStream_t s) {
   const int ctot = c0 + c1, nchunk = gn_chunks(batch, hw, groups, ctot);
   const int cpg = ctot / groups;
-  // One launch where a workgroup can hold a group of a sample in registers and has at most 16384 accesses to make (16 a thread).
-  // Measured on both sides of the line (two samples, 32 groups, bf16, launches back to back): 24x24x1280 7.9 us against 11.4 of the
-  // two launches, 48x48x640 (11.5k accesses) 10.2 / 14.1, 72x40x320 (14.4k) 10.4 / 12.6, but 64x64x320 (20.5k accesses of 4
-  // bytes) 15.3 / 14.0 and 96x96x320 (46k) 29.9 / 17.3; small maps of narrow models 3.6 / 11.3.
+  // One launch where a workgroup can hold a group of a sample in registers and has few enough accesses and elements to get through; two
+  // launches spread a large group over more CUs.  Up to 96 workgroups most CUs have nothing to do and the limits are low, up to 256 they
+  // are wide (the chip is busy with one launch as well), beyond that workgroups wait for or share a CU.  More groups than the two
+  // launches take always go this way.
+  // Measured on both sides of the line (32 groups, launches back to back, us, one launch / two): two samples, bf16: 24x24x1280 9.1 / 10.6,
+  // 48x48x320 10.2 / 11.3, 32x32x1280 (40960 elements) 11.9 / 11.6, 72x40x320 (14400 accesses) 12.0 / 11.4, 48x48x640 12.6 / 11.9,
+  // 48x48x1280 21.4 / 15.0, narrow models 5.5 / 12; fp32: 32x32x1280 12.4 / 13.7, 48x48x640 15.0 / 13.5; eight samples: 48x48x640 15.6 / 19.9,
+  // 64x64x320 (20480 accesses) 21.1 / 19.2; sixteen: 32x32x640 16.1 / 18.8, 48x48x320 22.0 / 19.8, 64x64x128 22.0 / 17.6.
   int ga = Vec<T>::N;                                        // channels per access: the widest that divides a group
   while (ga > 1 && cpg % ga) ga >>= 1;
-  if (ga * (int)sizeof(T) >= 4 && (long long)hw * (cpg / ga) <= 16384) {
+  const int wgs = batch * groups;
+  const long long accesses = (long long)hw * (cpg / ga), elements = (long long)hw * cpg;
+  const bool few = wgs <= 96    ? hw <= 4096 && accesses <= 12288 && elements <= 40960
+                   : wgs <= 256 ? hw <= 4096 && accesses <= 16384 && elements <= 65536
+                                : hw <= 3072 && accesses <= 10240 && elements <= 40960;
+  if (ga * (int)sizeof(T) >= 4 && (few || groups > kGnMaxGroups)) {
     const int words = ga * (int)sizeof(T) / 4, vpp = cpg / ga;     // 32-bit registers an access takes; accesses per pixel
     auto fits = [&](int nt, int regs) { return vpp <= nt && (long long)(nt / vpp) * (regs / words) >= hw; };
 #define AD_GN_ONE(NT_, REGS_) if (fits(NT_, REGS_)) return launch_gn_group<T, NT_, REGS_>(src0, src1, c0, c1, batch, hw, groups, ga, gamma, beta, eps, silu, out, s)

@@ -377,10 +377,12 @@ def test_groupnorm_silu(dtype, shape):
     # one launch: 8 / 4 / 2 channels per access (4 / 2 / 1 in fp32), 256 / 512 / 1024 threads, few and many registers, one pixel,
     # a group that straddles the two sources
     (2, 256, 0, 1, 1, 32, 1), (1, 64, 0, 45, 23, 32, 1), (2, 128, 64, 24, 24, 32, 0), (1, 640, 0, 24, 21, 32, 1), (1, 1280, 640, 15, 17, 32, 1),
-    (1, 1280, 0, 37, 23, 32, 1), (1, 320, 0, 40, 39, 32, 1), (2, 96, 64, 19, 19, 16, 1), (1, 2560, 0, 27, 29, 32, 1),
-    # two launches: beyond 16384 accesses, an odd number of channels per group, several sources and samples, more than 256
-    # channel vectors, few chunks
-    (2, 320, 0, 43, 41, 32, 1), (1, 640, 320, 48, 39, 32, 1), (2, 64, 96, 11, 5, 32, 0), (3, 64, 32, 9, 7, 32, 1), (1, 2560, 0, 83, 61, 128, 1)])
+    (1, 1280, 0, 37, 23, 32, 1), (1, 320, 0, 40, 39, 32, 1), (2, 96, 64, 19, 19, 16, 1), (2, 320, 0, 43, 41, 32, 1), (4, 2560, 0, 27, 23, 32, 1),
+    (9, 128, 0, 40, 39, 32, 1), (1, 1280, 0, 7, 5, 320, 1),
+    # two launches: each limit of the choice exceeded, an odd number of channels per group (bf16), several sources and samples, more
+    # than 256 channel vectors, few chunks, samples that do not divide the workgroups
+    (2, 320, 0, 61, 59, 32, 1), (1, 2560, 0, 27, 29, 32, 1), (1, 640, 320, 48, 39, 32, 1), (2, 64, 96, 11, 5, 32, 0), (3, 64, 32, 9, 7, 32, 1),
+    (1, 2560, 0, 83, 61, 128, 1), (1, 64, 0, 83, 61, 32, 1), (5, 320, 0, 61, 59, 32, 1), (9, 128, 64, 57, 55, 32, 1)])
 def test_groupnorm_every_path(dtype, shape):
     test_groupnorm_silu(dtype, shape)
 
