@@ -2407,11 +2407,12 @@ __global__ __launch_bounds__(512) void k_attn_generic(const T* __restrict__ Q, c
     }
     mx = fmaxf(mx, __shfl_xor(mx, 16));
     mx = fmaxf(mx, __shfl_xor(mx, 32));
-    const float m_new = fmaxf(m, mx), alpha = __builtin_amdgcn_exp2f(m - m_new);
+    // (as long as every score has been minus infinity there is no maximum to subtract: all terms are zero)
+    const float m_new = fmaxf(m, mx), ref = m_new == -INFINITY ? 0.f : m_new, alpha = __builtin_amdgcn_exp2f(m - ref);
     m = m_new;
     float sum = 0.f;
 #pragma unroll
-    for (int r = 0; r < 4; ++r) { s[r] = __builtin_amdgcn_exp2f(s[r] - m); sum += s[r]; }
+    for (int r = 0; r < 4; ++r) { s[r] = __builtin_amdgcn_exp2f(s[r] - ref); sum += s[r]; }
     l = l * alpha + sum;                                 // of this lane's keys; the four groups are added at the end
 #pragma unroll
     for (int t = 0; t < DT; ++t) {

@@ -520,6 +520,21 @@ def test_attention_generic(case):
     test_attention(case, -1)
 
 
+@pytest.mark.parametrize("dtype", DT)
+@pytest.mark.parametrize("masked", [[(0, 16)], [(0, 48), (112, 144)], [(32, 300)], [(0, 299)]], ids=str)
+def test_attention_generic_scores_of_minus_infinity(dtype, masked):
+    """Keys whose score overflows to minus infinity have no weight, also where they are all that one wavefront sees for a while."""
+    l, lk, d = 20, 300, 16
+    q, k, v = (quantize(SI.make_array((1, n, d), 76 + i), dtype) for i, n in enumerate((l, lk, lk)))
+    q[..., 0], k[..., 0] = quantize(1e20, dtype), 0.0
+    keep = np.ones(lk, bool)
+    for a, b in masked:
+        keep[a:b] = False
+    k[:, ~keep, 0] = quantize(-1e20, dtype)
+    got = run_attention(dtype, q, k, v, 1, False)
+    assert_kernel_close(got, P.attention(q, k[:, keep], v[:, keep], 1), dtype, c=4.0)
+
+
 @pytest.mark.parametrize("dtype,tr", [(B.AD_F32, False), (B.AD_BF16, True)])
 def test_attention_peaky_softmax(dtype, tr, attn_variant):
     """Scores far from uniform (scaled q, k) so that a mistake in the running max / rescaling shows."""
