@@ -2026,16 +2026,17 @@ __global__ __attribute__((amdgpu_waves_per_eu(OCC, OCC))) __launch_bounds__(256)
   auto issue = [&](int t, int stage) {
     const unsigned st = lds_base + stage * kAttn2Stage + (unsigned)wave * 1024u;
     const bool last = RAGGED && t == ntiles - 1;
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      // keys past the end read zeros (their scores are masked, but the pad must not hold NaNs)
-      const unsigned ko = (last && t * 64 + krow + 32 * i >= Lk) ? kOob : koff;
-      dma_load16(rsk, ko, (unsigned)t * kstep + i * khalf, st + i * 4096);
-    }
     if (!last) {
+#pragma unroll
+      for (int i = 0; i < 2; ++i) dma_load16(rsk, koff, (unsigned)t * kstep + i * khalf, st + i * 4096);
 #pragma unroll
       for (int i = 0; i < 2; ++i) dma_load16(rsv, voff, (unsigned)t * 128u + i * vhalf, st + 8192 + i * 4096);
     } else {
+      // keys past the end read zeros (their scores are masked, but the pad must not hold NaNs).  The row goes into the lane's offset:
+      // the range check compares that with the size less the scalar offset, and 32 rows on may lie beyond the size.
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+        dma_load16(rsk, t * 64 + krow + 32 * i >= Lk ? kOob : koff + (unsigned)t * kstep + i * khalf, 0u, st + i * 4096);
       // the last, partial tile of V^T goes through registers: values of keys past the end are cleared, whatever the pad holds
 #pragma unroll
       for (int i = 0; i < 2; ++i) {
