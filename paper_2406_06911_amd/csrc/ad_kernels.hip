@@ -3228,7 +3228,9 @@ static void run_layernorm(const void* src, int rows, int c, const float* gamma, 
     return;                                                                                                                            \
   }
   AD_LN(1)
+  AD_LN(2)
   AD_LN(3)
+  AD_LN(4)
   AD_LN(5)
   AD_LN(8)
 #undef AD_LN

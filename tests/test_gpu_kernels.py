@@ -424,7 +424,7 @@ def test_layernorm(dtype, rows, c):
 
 
 @pytest.mark.parametrize("dtype", DT)
-@pytest.mark.parametrize("rows,c", [(1, 8), (5, 16), (3, 24), (9000, 320), (8193, 640), (2050, 1280), (700, 1304), (66, 2560), (2, 4096), (20000, 88), (70000, 8)])
+@pytest.mark.parametrize("rows,c", [(1, 8), (5, 16), (3, 24), (9000, 320), (8193, 640), (2050, 1280), (700, 1304), (66, 2560), (2, 4096), (20000, 88), (70000, 8), (300, 640), (64, 1024), (2880, 1000), (1152, 2048)])
 def test_layernorm_lane_groups(dtype, rows, c):
     """Every number of lanes per row, rows that do not fill the last wavefront, widths that do not fill the lanes."""
     if c > 2048 and dtype == B.AD_F32:
