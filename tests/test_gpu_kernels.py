@@ -250,13 +250,15 @@ def test_qkv_transposed_third(tile, bsz, l, c, ld_t, shift):
 
 
 @pytest.mark.parametrize("tile", [14, 15])
-@pytest.mark.parametrize("case", CONV_CASES[:5], ids=[c[0] for c in CONV_CASES[:5]])
+@pytest.mark.parametrize("case", CONV_CASES[:5] + [None], ids=[c[0] for c in CONV_CASES[:5]] + ["epilogues"])
 def test_conv_wide_tiles(tile, case):
     B.check(lib.ad_tune_conv_tile(tile))
     try:
-        test_conv_matches_direct_summation(B.AD_BF16, case)
-        test_conv_epilogues(B.AD_BF16)
-        test_conv_split_k(B.AD_BF16)
+        if case:
+            test_conv_matches_direct_summation(B.AD_BF16, case)
+        else:
+            test_conv_epilogues(B.AD_BF16)
+            test_conv_split_k(B.AD_BF16)
     finally:
         B.check(lib.ad_tune_conv_tile(-1))
 
@@ -297,6 +299,81 @@ def test_two_stage_tiles_follow_sources_and_taps(tile, c0, c1, k, stride, up):
             assert_kernel_close(nhwc_to_nchw(got), ref, B.AD_BF16)
     finally:
         B.check(lib.ad_tune_conv_tile(-1))
+
+
+@pytest.mark.parametrize("dtype", DT)
+@pytest.mark.parametrize("tile", [-1, 5, 14])
+@pytest.mark.parametrize("bsz,l,c,ld_t,shift", [(2, 36, 64, 0, 0), (2, 36, 64, 0, 1), (2, 36, 64, 36, 0), (3, 21, 96, 21, 2), (1, 70, 32, 96, 4)])
+def test_split_k_second_pass_of_the_fused_projection(dtype, tile, bsz, l, c, ld_t, shift):
+    """The thirds of q/k/v out of partial sums: row-major and transposed, whole vectors and single elements, destinations off a vector."""
+    cin = 5120
+    x = quantize(SI.make_array((bsz * l, cin), 381), dtype)
+    w = quantize(SI.make_array((3 * c, cin), 382, 0.02), dtype)
+    dx, wp = dev(x, dtype), dev_bytes(B.pack_conv_weight(dtype, w))
+    q, k = (torch.full((bsz * l * c + 8,), float("nan"), device=DEV, dtype=tdtype(dtype)) for _ in range(2))
+    size = bsz * c * ld_t if ld_t else bsz * l * c
+    v = torch.full((size + 8,), float("nan"), device=DEV, dtype=tdtype(dtype))
+    B.check(lib.ad_tune_conv_tile(tile))
+    try:
+        ws_bytes = lib.ad_conv_workspace_bytes(dtype, bsz, l, 1, 3 * c, cin, 1, B.OUT_QKV)
+        assert ws_bytes > 0, "shape was expected to split"
+        wsb = torch.zeros(ws_bytes, dtype=torch.uint8, device=DEV)
+        B.check(lib.ad_conv_forward(dtype, p(dx), None, cin, 0, bsz, l, 1, 0, 1, 1, p(wp), 3 * c, None, None, None, p(q[shift:]), p(k[shift:]),
+                                    p(v[shift:]), B.OUT_QKV, ld_t, p(wsb), ws_bytes, stream_ptr()))
+        sync()
+    finally:
+        B.check(lib.ad_tune_conv_tile(-1))
+    ref = P.linear(x, w)
+    for t, r in ((q, ref[:, :c]), (k, ref[:, c:2 * c])):
+        got = host(t)
+        assert np.isnan(got[:shift]).all() and np.isnan(got[shift + r.size:]).all()
+        assert_kernel_close(got[shift:shift + r.size].reshape(r.shape), r, dtype)
+    got = host(v)
+    assert np.isnan(got[:shift]).all() and np.isnan(got[shift + size:]).all()
+    got = got[shift:shift + size]
+    if ld_t:
+        got = got.reshape(bsz, c, ld_t)
+        assert np.isnan(got[:, :, l:]).all()
+        assert_kernel_close(got[:, :, :l], ref[:, 2 * c:].reshape(bsz, l, c).transpose(0, 2, 1), dtype)
+    else:
+        assert_kernel_close(got.reshape(bsz * l, c), ref[:, 2 * c:], dtype)
+
+
+@pytest.mark.parametrize("dtype", DT)
+@pytest.mark.parametrize("mode", [B.OUT_ROWMAJOR, B.OUT_TRANSPOSED, B.OUT_TRANSPOSED_F32], ids=["rows", "turned", "turned_f32"])
+@pytest.mark.parametrize("n_out,shift", [(192, 0), (36, 0), (200, 1), (68, 2), (192, 4)])
+def test_split_k_second_pass_alignment(dtype, mode, n_out, shift):
+    """Bias, per-sample vector and (row-major) residual added to partial sums, tensors on and off a boundary of four elements."""
+    n, c, h, wd = 2, 640, 5, 7
+    x = quantize(SI.make_array((n, c, h, wd), 391), dtype)
+    w = quantize(SI.make_array((n_out, c, 3, 3), 392, 0.02), dtype)
+    bias, rowvec = SI.make_array((n_out,), 393, 0.1), SI.make_array((n, n_out), 394)
+    ref = P.conv2d(x, w, bias) + rowvec[:, :, None, None]
+    ld_t, size = (0, n * h * wd * n_out) if mode == B.OUT_ROWMAJOR else (h * wd + 2, n * n_out * (h * wd + 2))
+    dres = None
+    if mode == B.OUT_ROWMAJOR:
+        res = quantize(SI.make_array((n, h, wd, n_out), 395), dtype)
+        ref = ref + nhwc_to_nchw(res)
+        dres = torch.full((size + 8,), float("nan"), device=DEV, dtype=tdtype(dtype))
+        dres[shift:shift + size] = dev(res, dtype).reshape(-1)
+        dres = dres[shift:]
+    out = torch.full((size + 8,), float("nan"), device=DEV, dtype=torch.float32 if mode == B.OUT_TRANSPOSED_F32 else tdtype(dtype))
+    dx, wp, db, dv = dev(nchw_to_nhwc(x), dtype), dev_bytes(B.pack_conv_weight(dtype, w)), dev_f32(bias), dev_f32(rowvec)
+    ws_bytes = lib.ad_conv_workspace_bytes(dtype, n, h, wd, n_out, c, 3, mode)
+    assert ws_bytes > 0, "shape was expected to split"
+    wsb = torch.zeros(ws_bytes, dtype=torch.uint8, device=DEV)
+    B.check(lib.ad_conv_forward(dtype, p(dx), None, c, 0, n, h, wd, 0, 3, 1, p(wp), n_out, p(db), p(dv), p(dres), p(out[shift:]), None, None,
+                                mode, ld_t, p(wsb), ws_bytes, stream_ptr()))
+    sync()
+    got = host(out)
+    assert np.isnan(got[:shift]).all() and np.isnan(got[shift + size:]).all()
+    got = got[shift:shift + size]
+    if mode == B.OUT_ROWMAJOR:
+        assert_kernel_close(nhwc_to_nchw(got.reshape(n, h, wd, n_out)), ref, dtype)
+    else:
+        got = got.reshape(n, n_out, ld_t)
+        assert np.isnan(got[:, :, h * wd:]).all()
+        assert_kernel_close(got[:, :, :h * wd], ref.reshape(n, n_out, h * wd), dtype)
 
 
 SMALL_CASES = [
