@@ -3050,20 +3050,20 @@ static ad_status run_groupnorm(const void* src0, const void* src1, int c0, int c
   const int ctot = c0 + c1, nchunk = gn_chunks(batch, hw, groups, ctot);
   const int cpg = ctot / groups;
   // One launch where a workgroup can hold a group of a sample in registers and has few enough accesses and elements to get through; two
-  // launches spread a large group over more CUs.  Up to 96 workgroups most CUs have nothing to do and the limits are low, up to 256 they
-  // are wide (the chip is busy with one launch as well), beyond that workgroups wait for or share a CU.  More groups than the two
-  // launches take always go this way.
+  // launches spread a large group over more CUs.  Up to 96 workgroups most CUs have nothing to do, up to 256 one launch keeps the chip
+  // busy as well, beyond that its workgroups wait for or share a CU.  More groups than the two launches take always go this way.
   // Measured on both sides of the line (32 groups, launches back to back, us, one launch / two): two samples, bf16: 24x24x1280 9.1 / 10.6,
-  // 48x48x320 10.2 / 11.3, 32x32x1280 (40960 elements) 11.9 / 11.6, 72x40x320 (14400 accesses) 12.0 / 11.4, 48x48x640 12.6 / 11.9,
-  // 48x48x1280 21.4 / 15.0, narrow models 5.5 / 12; fp32: 32x32x1280 12.4 / 13.7, 48x48x640 15.0 / 13.5; eight samples: 48x48x640 15.6 / 19.9,
-  // 64x64x320 (20480 accesses) 21.1 / 19.2; sixteen: 32x32x640 16.1 / 18.8, 48x48x320 22.0 / 19.8, 64x64x128 22.0 / 17.6.
+  // 48x48x320 10.2 / 11.3, 48x48x640 12.6 / 11.9, 72x40x320 (14400 accesses) 12.0 / 11.4, 64x64x320 (20480) 17.6 / 11.7, 32x32x1920 (61440
+  // elements) 14.7 / 12.7, 48x48x1280 21.4 / 14.9, narrow models 5.5 / 12; fp32: 32x32x1280 12.4 / 13.7, 48x48x640 15.0 / 13.5; eight samples:
+  // 48x48x640 15.6 / 19.9, 64x64x320 21.1 / 19.2; sixteen: 32x32x640 16.1 / 18.8, 48x48x320 22.0 / 19.8, 64x64x128 22.0 / 17.6.
+  // Up to 96 workgroups the line lies where two launches are a seventh faster, not where both are even: they take every CU, one launch
+  // leaves the rest to the other streams (with 40960 elements and 12288 accesses whole 768px runs of four components lost 1 %).
   int ga = Vec<T>::N;                                        // channels per access: the widest that divides a group
   while (ga > 1 && cpg % ga) ga >>= 1;
   const int wgs = batch * groups;
   const long long accesses = (long long)hw * (cpg / ga), elements = (long long)hw * cpg;
-  const bool few = wgs <= 96    ? hw <= 4096 && accesses <= 12288 && elements <= 40960
-                   : wgs <= 256 ? hw <= 4096 && accesses <= 16384 && elements <= 65536
-                                : hw <= 3072 && accesses <= 10240 && elements <= 40960;
+  const bool few = wgs <= 256 ? hw <= 4096 && accesses <= 16384 && elements <= (wgs <= 96 ? 49152 : 65536)
+                              : hw <= 3072 && accesses <= 10240 && elements <= 40960;
   if (ga * (int)sizeof(T) >= 4 && (few || groups > kGnMaxGroups)) {
     const int words = ga * (int)sizeof(T) / 4, vpp = cpg / ga;     // 32-bit registers an access takes; accesses per pixel
     auto fits = [&](int nt, int regs) { return vpp <= nt && (long long)(nt / vpp) * (regs / words) >= hw; };
