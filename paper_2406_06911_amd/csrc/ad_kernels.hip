@@ -6,7 +6,7 @@
 //   k_attn_generic generic attention on fp32 MFMA, keys shared out over the wavefronts (fp32 mode, odd head sizes)
 //   k_attn_frames_mfma / k_attn_frames  attention over the frame axis of a video model (one wavefront per
 //                  position and head; MFMA without LDS for bf16, LDS-staged generic kernel otherwise)
-//   k_gn_*         GroupNorm (+SiLU) in two passes: per-group partial sums, then statistics + apply
+//   k_gn_*         GroupNorm (+SiLU): one launch where a group fits a workgroup's registers, else partial sums, then statistics + apply
 //   k_layernorm    several rows per wavefront
 //   k_linear_rows  skinny linear layer for the time-embedding path
 //   k_sampler      guidance combination + DDIM / Euler latent update
@@ -2749,17 +2749,18 @@ ad_status launch_attention_frames(int dtype, const void* q, const void* k, const
 // every workgroup first folds those pairs of its sample in double precision (a few KiB, L2-resident) into mean and 1/std
 // per group, then applies y = silu(x * scale + shift) to its run of pixels.  No atomics, no fences: the result does not
 // depend on scheduling.  Both passes are bound by the latency of a launch (3.5 us for any map) and of the memory system
-// rather than by bandwidth at these sizes: 96x96x320, two samples, 17.3 us for 35 MB (18.9 with 64 chunks, four rows in
-// flight and a serial fold of the channels); 96x96x(640+320) 28.7 us (42.3 with a launch per source).
+// rather than by bandwidth at these sizes: 96x96x320, two samples, 15.3 us for 35 MB (19.4 with 64 chunks, four rows in
+// flight and a serial fold of the channels); 96x96x(320+320) 19.5 us (34.5 with a launch per source).
 // =================================================================================================
-constexpr int kGnMaxChunks = 64;
 constexpr int kGnMaxGroups = 256;
 
 // pixel chunks of the statistics pass: 64, or 128 (a workgroup on every CU with two samples) where the partial sums of both sources
-// still fit the library's own 512 KiB array and the caller's scratch (sized by channels, hence two channels a group)
+// still fit the library's own 512 KiB array and the caller's scratch (64 chunks of as many groups as there are channels, so two
+// channels a group)
+constexpr int kGnScratchChunks = 64;
 constexpr size_t kStaticGnBytes = 512 * 1024;
 static int gn_chunks(int batch, int hw, int groups, int c) {
-  const int most = c >= 2 * groups && (size_t)2 * batch * 128 * groups * 2 * sizeof(float) <= kStaticGnBytes ? 128 : 64;
+  const int most = c >= 2 * groups && (size_t)2 * batch * 2 * kGnScratchChunks * groups * 2 * sizeof(float) <= kStaticGnBytes ? 2 * kGnScratchChunks : kGnScratchChunks;
   const int n = hw / 8;
   return n < 1 ? 1 : (n > most ? most : n);
 }
@@ -3020,7 +3021,8 @@ __global__ __launch_bounds__(NT) void k_gn_group(const T* __restrict__ src0, con
 
 extern "C" size_t ad_groupnorm_scratch_bytes(int batch, int hw, int c) {
   (void)hw;
-  return (size_t)batch * ad::kGnMaxChunks * c * 4 * sizeof(float);     // two sources x (sum, sumsq) per chunk and group (groups <= c)
+  // two sources x (sum, sum of squares) per chunk and group: 64 chunks of up to c groups, or 128 of up to c / 2 (gn_chunks)
+  return (size_t)batch * ad::kGnScratchChunks * c * 4 * sizeof(float);
 }
 
 namespace ad {
@@ -3159,7 +3161,8 @@ ad_status launch_groupnorm_static(int dtype, const void* src0, const void* src1,
 // the two statistics passes.  Bound by the round trip to memory, so a wavefront has several rows in flight, every lane has work (a
 // row of 320 channels is 40 accesses) and gain and offset are requested with the rows.  FULL: lanes * K accesses are the whole row.
 // Measured, bf16, us (one row per wavefront, gain and offset read behind the statistics -> this): 65536x320 33.6 -> 14.6 (5.7 TB/s),
-// 16384x640 14.4 -> 9.0, 18432x320 12.3 -> 6.9, 8192x640 8.6 -> 6.0, 2048x1280 4.9 -> 4.3.
+// 16384x640 14.4 -> 9.0, 18432x320 12.3 -> 6.9, 8192x640 8.6 -> 6.0, 2048x1280 4.9 -> 4.3.  An instance per number of accesses up to five:
+// two and four in those of three and five cost a fifth (1152x2048 5.6 us against 4.5).
 template <typename T, int K, bool FULL>
 __global__ __launch_bounds__(256) void k_layernorm(const T* __restrict__ src, int rows, int c, int log_lanes, const float* __restrict__ gamma,
                                                    const float* __restrict__ beta, float eps, T* __restrict__ out) {
