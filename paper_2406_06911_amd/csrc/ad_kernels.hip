@@ -82,6 +82,22 @@ __device__ __forceinline__ float wave_sum(float v) {
   for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
   return v;
 }
+// The same on the vector unit alone (all lanes active): rows of 16 lanes by DPP, the four rows through scalar registers.  A shuffle is a round
+// trip to the LDS unit, six of them one after the other are a third of a microsecond.
+template <int CTRL>
+__device__ __forceinline__ float dpp_f(float v) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xf, 0xf, true));
+}
+__device__ __forceinline__ float lane_f(float v, int lane) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), lane));
+}
+__device__ __forceinline__ float wave_sum_rows(float v) {
+  v += dpp_f<0xB1>(v);      // quad_perm 1 0 3 2
+  v += dpp_f<0x4E>(v);      // quad_perm 2 3 0 1
+  v += dpp_f<0x141>(v);     // row_half_mirror
+  v += dpp_f<0x140>(v);     // row_mirror
+  return (lane_f(v, 0) + lane_f(v, 16)) + (lane_f(v, 32) + lane_f(v, 48));
+}
 __device__ __forceinline__ double wave_sum_d(double v) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
@@ -2973,7 +2989,7 @@ __global__ __launch_bounds__(NT) void k_gn_group(const T* __restrict__ src0, con
     if (lanep + k * pl < p_end)
 #pragma unroll
       for (int e = 0; e < G; ++e) s += to_f(x[k][e]);
-  s = wave_sum(s);
+  s = wave_sum_rows(s);
   if (lane == 0) red[0][wave] = s;
   __syncthreads();
   s = 0.f;
@@ -2986,7 +3002,7 @@ __global__ __launch_bounds__(NT) void k_gn_group(const T* __restrict__ src0, con
     if (lanep + k * pl < p_end)
 #pragma unroll
       for (int e = 0; e < G; ++e) { const float d = to_f(x[k][e]) - about; s += d; q += d * d; }
-  s = wave_sum(s); q = wave_sum(q);
+  s = wave_sum_rows(s); q = wave_sum_rows(q);
   if (lane == 0) { red[1][wave] = s; red[2][wave] = q; }
   __syncthreads();
   double ds = 0.0, dq = 0.0;
@@ -3054,10 +3070,10 @@ static ad_status run_groupnorm(const void* src0, const void* src1, int c0, int c
   // One launch where a workgroup can hold a group of a sample in registers and has few enough accesses and elements to get through; two
   // launches spread a large group over more CUs.  Up to 96 workgroups most CUs have nothing to do, up to 256 one launch keeps the chip
   // busy as well, beyond that its workgroups wait for or share a CU.  More groups than the two launches take always go this way.
-  // Measured on both sides of the line (32 groups, launches back to back, us, one launch / two): two samples, bf16: 24x24x1280 9.1 / 10.6,
-  // 48x48x320 10.2 / 11.3, 48x48x640 12.6 / 11.9, 72x40x320 (14400 accesses) 12.0 / 11.4, 64x64x320 (20480) 17.6 / 11.7, 32x32x1920 (61440
-  // elements) 14.7 / 12.7, 48x48x1280 21.4 / 14.9, narrow models 5.5 / 12; fp32: 32x32x1280 12.4 / 13.7, 48x48x640 15.0 / 13.5; eight samples:
-  // 48x48x640 15.6 / 19.9, 64x64x320 21.1 / 19.2; sixteen: 32x32x640 16.1 / 18.8, 48x48x320 22.0 / 19.8, 64x64x128 22.0 / 17.6.
+  // Measured on both sides of the line (32 groups, launches back to back, us, one launch / two): two samples, bf16: 24x24x1280 8.8 / 10.6,
+  // 48x48x320 9.9 / 11.3, 48x48x640 12.2 / 11.9, 72x40x320 (14400 accesses) 11.8 / 11.4, 64x64x320 (20480) 17.7 / 11.7, 32x32x1920 (61440
+  // elements) 14.3 / 12.7, 48x48x1280 21.1 / 14.9, narrow models 5.5 / 12; fp32: 32x32x1280 12.2 / 13.7, 48x48x640 14.7 / 13.5; eight samples:
+  // 48x48x640 16.0 / 19.9, 64x64x320 21.3 / 19.2; sixteen: 32x32x640 15.2 / 18.8, 48x48x320 21.3 / 19.8, 64x64x128 21.5 / 17.6.
   // Up to 96 workgroups the line lies where two launches are a seventh faster, not where both are even: they take every CU, one launch
   // leaves the rest to the other streams (with 40960 elements and 12288 accesses whole 768px runs of four components lost 1 %).
   int ga = Vec<T>::N;                                        // channels per access: the widest that divides a group
