@@ -1,5 +1,6 @@
 """C-ABI library: it loads, exports every declared symbol, and its integer host logic (unit list,
 partition, schedule table, timesteps) is bit-exact against the oracle.  No GPU needed."""
+import concurrent.futures
 import ctypes
 import os
 import re
@@ -218,3 +219,25 @@ def test_kernel_entry_points_reject_bad_shapes_before_touching_the_gpu():
     ]
     assert all(st == B.AD_ERR_INVALID for st in bad), bad
     assert b"frame attention" in L.ad_last_error() or b"attention" in L.ad_last_error()
+
+
+def test_split_k_scratch_does_not_depend_on_earlier_queries():
+    """The plan of a GEMM follows from its shape and the tile override alone: many shapes, other overrides and other threads in between."""
+    shapes = [(dt, b, h, h, n, c, k, mode) for dt in (B.AD_F32, B.AD_BF16) for b in (1, 2, 7) for h in (1, 3, 6, 12, 24) for n in (192, 960, 3840)
+              for c, k in ((640, 3), (5120, 1)) for mode in (B.OUT_ROWMAJOR, B.OUT_QKV, B.OUT_GEGLU)]
+
+    def query(tile):
+        B.check(B.lib.ad_tune_conv_tile(tile))
+        return {s: B.lib.ad_conv_workspace_bytes(*s) for s in shapes}
+
+    try:
+        first = {tile: query(tile) for tile in (-1, 5, 14)}
+        assert any(first[-1].values()) and first[-1] != first[5]
+        for tile in (14, -1, 5, -1):
+            assert query(tile) == first[tile]
+        B.check(B.lib.ad_tune_conv_tile(-1))
+        with concurrent.futures.ThreadPoolExecutor(4) as pool:
+            for got in pool.map(lambda s: (s, B.lib.ad_conv_workspace_bytes(*s)), shapes[::-1]):
+                assert got[1] == first[-1][got[0]]
+    finally:
+        B.check(B.lib.ad_tune_conv_tile(-1))
