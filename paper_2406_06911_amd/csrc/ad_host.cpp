@@ -285,6 +285,7 @@ static void build_manifest(Ctx& c) {
       }
       case AD_UNIT_TFM: {
         const int C = f.c_in;
+        const size_t first = c.weights.size();
         add_w(c, n + ".gn.g", W_VEC_F32, {C}); add_w(c, n + ".gn.b", W_VEC_F32, {C});
         add_w(c, n + ".proj_in.w", W_CONV1, {C, C}); add_w(c, n + ".proj_in.b", W_VEC_F32, {C});
         for (int k = 0; k < f.depth; ++k) {
@@ -308,6 +309,14 @@ static void build_manifest(Ctx& c) {
           add_w(c, p + ".q.w", W_QKV_Q, {C, C}); add_w(c, p + ".k.w", W_QKV_KV, {C, C}); add_w(c, p + ".v.w", W_QKV_KV, {C, C});
           add_w(c, p + ".o.w", W_CONV1, {C, C}); add_w(c, p + ".o.b", W_VEC_F32, {C});
         }
+        // what the row-local kernel takes in: all but the text's keys and values and the temporal layer's output projection
+        if (tfm_rows_fits(g.dtype, C, g.head_dim, g.ctx_len))
+          for (size_t i = first; i < c.weights.size(); ++i) {
+            Weight& w = c.weights[i];
+            const std::string nm = w.info.name;
+            auto ends = [&](const char* t) { const size_t l = std::strlen(t); return nm.size() >= l && nm.compare(nm.size() - l, l, t) == 0; };
+            w.fragments = (w.role == W_CONV1 || w.role == W_GEGLU || w.role == W_QKV_Q) && !ends(".attn2.k.w") && !ends(".attn2.v.w") && !ends(".temp.o.w");
+          }
         break;
       }
     }
@@ -349,6 +358,19 @@ void pack_conv(int dtype, const float* w, int n_out, int c_in, int ksize, bool g
     const float* ws = w + (size_t)src * c_in * taps;
     for (int t = 0; t < taps; ++t)
       for (int i = 0; i < c_in; ++i) put(dtype, out, (size_t)r * kp + (size_t)t * c_in + i, ws[(size_t)i * taps + t]);
+  }
+}
+
+void pack_fragments(void* packed, int rows, int row_bytes) {
+  std::vector<char> t((size_t)16 * row_bytes);
+  for (int r0 = 0; r0 < rows; r0 += 16) {
+    char* tile = (char*)packed + (size_t)r0 * row_bytes;
+    for (int r = 0; r < 16; ++r)
+      for (int k = 0; k < row_bytes; k += 16) {              // 64 bytes of K of the 16 rows are one load of a wavefront, lane (k / 16) % 4 * 16 + r
+        const int lane = k / 16 % 4 * 16 + r;
+        std::memcpy(t.data() + (size_t)(k / 64) * 1024 + lane * 16, tile + (size_t)r * row_bytes + k, 16);
+      }
+    std::memcpy(tile, t.data(), t.size());
   }
 }
 

@@ -65,6 +65,7 @@ struct Weight {
   size_t dev_off = 0;     // offset in the weight arena
   size_t dev_bytes = 0;
   int n_pad = 0, k_pad = 0;
+  bool fragments = false; // packed operand in fragment order (pack_fragments) instead of rows
 };
 
 struct Component {
@@ -168,6 +169,12 @@ size_t tensor_bytes(const Ctx& c, int unit);
 size_t packed_conv_bytes(int dtype, int n_out, int c_in, int ksize);
 void pack_conv(int dtype, const float* w, int n_out, int c_in, int ksize, bool geglu, void* out);
 void pack_rows(int dtype, const float* w, size_t n, void* out);   // plain conversion
+// packed rows (a multiple of 16) into the order in which k_tfm_rows loads them: 16-row tiles, 64 bytes of K of a tile after the other, each
+// laid out by lane; in place
+void pack_fragments(void* packed, int rows, int row_bytes);
+
+// whether a transformer block of this width runs in the row-local kernel (its weights are packed for that)
+bool tfm_rows_fits(int dtype, int c, int head_dim, int ctx_len);
 uint16_t f32_to_bf16(float f);
 
 }  // namespace ad

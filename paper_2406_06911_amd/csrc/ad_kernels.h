@@ -64,6 +64,27 @@ ad_status launch_layernorm(int dtype, const void* src, int rows, int c, const fl
                            void* out, hipStream_t s);
 ad_status launch_attention(int dtype, const void* q, const void* k, const void* v, int v_t, int batch, int l, int lk, int c,
                            int head_dim, int ldq, int ldk, int ldv, int ldo, void* out, hipStream_t s);
+// The row-local part of a transformer block (see k_tfm_rows): the input projection (w_in) or what follows an attention over the image
+// (w_o .. b_ff2), then, where asked for, the block's output projection with its residual x (w_out, into z), then LayerNorm and q/k/v
+// (w_qkv).  Without w_out the rows go to h.  text_k [text samples][lk][c]; text_v the same, or, in bf16, [text samples][c][text_ldv].
+struct TfmRows {
+  int dtype, batch, l, c, head_dim;
+  float eps;
+  const void* in; void* h;
+  const void* w_in = nullptr; const float* b_in = nullptr;
+  const void* w_o = nullptr; const float* b_o = nullptr;
+  const float *ln2_g = nullptr, *ln2_b = nullptr;
+  const void* w_q2 = nullptr;
+  const void *text_k = nullptr, *text_v = nullptr; int lk = 0, text_ldv = 0, text_shared = 0;
+  const void* w_o2 = nullptr; const float* b_o2 = nullptr;
+  const float *ln3_g = nullptr, *ln3_b = nullptr;
+  const void* w_ff1 = nullptr; const float* b_ff1 = nullptr;
+  const void* w_ff2 = nullptr; const float* b_ff2 = nullptr;
+  const void* w_out = nullptr; const float* b_out = nullptr; const void* x = nullptr; void* z = nullptr;
+  const float *ln_g = nullptr, *ln_b = nullptr; const void* w_qkv = nullptr;
+  void *q = nullptr, *k = nullptr, *v = nullptr; int ld_t = 0;
+};
+ad_status launch_tfm_rows(const TfmRows& a, hipStream_t s);
 // attention over the frame axis: row (f, p) = f * positions + p of q / k / v / out; heads = c / head width
 ad_status launch_attention_frames(int dtype, const void* q, const void* k, const void* v, int frames, int positions, int c,
                                   int heads, int ldq, int ldk, int ldv, int ldo, void* out, hipStream_t s);

@@ -111,6 +111,53 @@ struct Eval {
     return linear(text, B * Lk, c.cfg.ctx_dim, w + 11, -1, nullptr, vdst);
   }
 
+  // narrow models: between the GroupNorm (done) and the attentions over the image a block is row-local and runs in one launch each
+  ad_status tfm_by_rows(const ad_unit_info& f, int w, const void* x, void* z, int ui) const {
+    WView wv{c};
+    const int B = c.cfg.batch, L = f.h_in * f.w_in, Cc = f.c_in, d = c.cfg.head_dim, Lk = c.cfg.ctx_len, lp = round_up(L, 64);
+    const bool vt = dt == AD_BF16;
+    const int w_out = w + 4 + 20 * f.depth, w_temp = w_out + 2;
+    auto with_qkv = [&](TfmRows& a, int at, int ld_t) {      // at: ln.g ln.b q k v
+      a.ln_g = wv.f32(at); a.ln_b = wv.f32(at + 1);
+      a.w_qkv = wv.at(at + 2);
+      a.q = temp(2); a.k = temp(3); a.v = temp(4); a.ld_t = ld_t;
+    };
+    TfmRows first{dt, B, L, Cc, d, c.cfg.ln_eps, temp(0), temp(1)};
+    first.w_in = wv.at(w + 2); first.b_in = wv.f32(w + 3);
+    if (f.depth > 0) with_qkv(first, w + 4, vt ? lp : 0);
+    AD_TRY(launch_tfm_rows(first, s));
+    w += 4;
+    for (int k = 0; k < f.depth; ++k, w += 20) {
+      AD_TRY(launch_attention(dt, temp(2), temp(3), temp(4), vt, B, L, L, Cc, d, Cc, Cc, vt ? lp : Cc, Cc, temp(5), s));
+      TfmRows a{dt, B, L, Cc, d, c.cfg.ln_eps, temp(5), temp(1)};
+      if (c.text_cached == text) {
+        a.text_k = work(c.text_k_off[ui][k]); a.text_v = work(c.text_v_off[ui][k]);
+      } else {
+        AD_TRY(text_kv(w, temp(7), temp(8)));
+        a.text_k = temp(7); a.text_v = temp(8);
+      }
+      a.lk = Lk; a.text_ldv = round_up(Lk, 64); a.text_shared = c.cfg.frames > 0;
+      a.w_o = wv.at(w + 5); a.b_o = wv.f32(w + 6);
+      a.ln2_g = wv.f32(w + 7); a.ln2_b = wv.f32(w + 8);
+      a.w_q2 = wv.at(w + 9);
+      a.w_o2 = wv.at(w + 12); a.b_o2 = wv.f32(w + 13);
+      a.ln3_g = wv.f32(w + 14); a.ln3_b = wv.f32(w + 15);
+      a.w_ff1 = wv.at(w + 16); a.b_ff1 = wv.f32(w + 17);
+      a.w_ff2 = wv.at(w + 18); a.b_ff2 = wv.f32(w + 19);
+      if (k + 1 < f.depth) {
+        with_qkv(a, w + 20, vt ? lp : 0);
+      } else {
+        a.w_out = wv.at(w_out); a.b_out = wv.f32(w_out + 1); a.x = x; a.z = z;
+        if (c.cfg.temporal_heads > 0) with_qkv(a, w_temp, 0);
+      }
+      AD_TRY(launch_tfm_rows(a, s));
+    }
+    if (c.cfg.temporal_heads == 0) return AD_OK;
+    // temporal layer: temp.ln.g temp.ln.b temp.q temp.k temp.v temp.o.w temp.o.b; tokens = the frames of one position
+    AD_TRY(launch_attention_frames(dt, temp(2), temp(3), temp(4), c.cfg.frames, L, Cc, c.cfg.temporal_heads, Cc, Cc, Cc, Cc, temp(5), s));
+    return linear(temp(5), B * L, Cc, w_temp + 5, w_temp + 6, z, z);
+  }
+
   ad_status tfm(const Unit& u, int ui) const {
     const ad_unit_info& f = u.info;
     const int B = c.cfg.batch, L = f.h_in * f.w_in, Cc = f.c_in, M = B * L, d = c.cfg.head_dim;
@@ -121,6 +168,7 @@ struct Eval {
     int w = u.w_first;
     // gn.g gn.b proj_in.w proj_in.b | per layer 20 entries | proj_out.w proj_out.b
     AD_TRY(gn(x, nullptr, Cc, 0, L, w + 0, 0, temp(0)));
+    if (tfm_rows_fits(dt, Cc, d, Lk)) return tfm_by_rows(f, w, x, tensor_out(ui), ui);
     AD_TRY(linear(temp(0), M, Cc, w + 2, w + 3, nullptr, temp(1)));
     w += 4;
     void* h = temp(1);
@@ -373,6 +421,7 @@ ad_status ad_load_weights(ad_ctx* ctx, const float* const* host_ptrs, int n) {
       for (int j = 0; j < 3; ++j) std::memcpy(cat.data() + j * each, host_ptrs[i + j], each * 4);
       stage.assign(w.dev_bytes, 0);
       pack_conv(dt, cat.data(), 3 * sh[0], sh[1], 1, false, stage.data());
+      if (w.fragments) pack_fragments(stage.data(), w.n_pad, w.k_pad * (int)esize(dt));
       AD_HIP(hipMemcpy(c.weights_dev + w.dev_off, stage.data(), w.dev_bytes, hipMemcpyHostToDevice));
       continue;
     }
@@ -408,6 +457,7 @@ ad_status ad_load_weights(ad_ctx* ctx, const float* const* host_ptrs, int n) {
       }
       default: break;
     }
+    if (w.fragments) pack_fragments(stage.data(), w.n_pad, w.k_pad * (int)esize(dt));
     AD_HIP(hipMemcpy(c.weights_dev + w.dev_off, stage.data(), w.dev_bytes, hipMemcpyHostToDevice));
   }
   if (c.temb_rows_total > 0) {

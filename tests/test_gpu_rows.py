@@ -1,0 +1,42 @@
+"""The row-local transformer kernel of narrow models (k_tfm_rows) against the oracle's transformer block, at the sizes where it can go
+wrong: token counts around its tiles of 16 and 32, key counts around its blocks, one and several layers, shared text, every head width."""
+import numpy as np
+import pytest
+import torch
+
+from configs import CONFIGS
+from gpu_util import dev, host, nchw_to_nhwc, nhwc_to_nchw, rel_l2
+from paper_2406_06911_amd import binding as B
+from test_gpu_pipeline import Case
+
+pytestmark = pytest.mark.gpu
+
+BF, F32 = B.AD_BF16, B.AD_F32
+
+
+@pytest.mark.parametrize("dtype,c,head_dim,depth,height,width,batch,ctx_len,frames", [
+    (BF, 64, 64, 1, 4, 4, 1, 77, 0), (BF, 64, 64, 1, 5, 5, 2, 32, 0), (BF, 64, 64, 3, 17, 1, 2, 33, 0), (BF, 64, 64, 1, 65, 65, 2, 77, 0),
+    (BF, 128, 64, 1, 3, 3, 1, 1, 0), (BF, 128, 64, 2, 13, 5, 2, 154, 0), (BF, 128, 64, 1, 8, 4, 5, 64, 5), (BF, 64, 64, 2, 3, 5, 3, 96, 3),
+    (F32, 32, 16, 1, 4, 4, 1, 8, 0), (F32, 32, 32, 2, 5, 7, 2, 17, 0), (F32, 64, 16, 1, 1, 1, 1, 16, 0), (F32, 64, 32, 1, 11, 3, 3, 77, 3),
+    (F32, 64, 64, 2, 9, 7, 2, 77, 0), (F32, 64, 16, 1, 91, 91, 1, 5, 0)])
+def test_transformer_of_a_narrow_model_matches_oracle(monkeypatch, dtype, c, head_dim, depth, height, width, batch, ctx_len, frames):
+    d = dict(latent_channels=4, height=height, width=width, batch=batch, channels=[c], layers_per_block=1, transformer_depth=[depth], mid_depth=0,
+             head_dim=head_dim, gn_groups=8, ctx_len=ctx_len, ctx_dim=64, pooled_dim=0, frames=frames, temporal_heads=4 if frames else 0)
+    monkeypatch.setitem(CONFIGS, "rows", d)
+    # weights of about 1 / sqrt(width): the block adds as much as it is given
+    case = Case("rows", dtype, 3, 1, 1, 1, std=c ** -0.5, cuts=[2, 3])
+    assert [u.name.decode() for u in case.m.units()][2] == "d0.0.tfm"
+    trace = []
+    case.oracle.run(case.noise, case.text, case.pooled, trace=trace)
+    before, after = trace[0][1][1], trace[1][1][2]
+    x = dev(nchw_to_nhwc(before), dtype)
+    out = [case.alloc_unit(u) for u in case.m.component_io(2)[1]]
+    for _ in range(2):                       # the text's keys and values computed on the way, then from the cache
+        case.m.component_forward(2, [x if u == 1 else None for u in case.m.component_io(2)[0]], 0, case.d_text, out, torch.cuda.current_stream())
+        torch.cuda.synchronize()
+        got = nhwc_to_nchw(host(out[case.m.component_io(2)[1].index(2)]) - host(x))
+        # what the block adds.  bf16: some ten roundings of 1.1e-3 on the way (input, hidden rows, q, probabilities, inner rows, result) and
+        # the sums behind them, 4-8e-3 in all; fp32: sums of a few hundred terms, 1e-6
+        err = rel_l2(got, after - before)
+        assert np.isfinite(got).all() and err < (2e-2 if dtype == BF else 1e-5), err
+        case.m.precompute_text(case.d_text, torch.cuda.current_stream())
