@@ -80,7 +80,7 @@ struct Workspace {
   std::vector<size_t> unit_off;        // per unit of the component (index unit - first); SIZE_MAX = external output
   size_t temp_off[kNumTemps] = {0};
   size_t temp_bytes[kNumTemps] = {0};
-  size_t f32_off = 0;                  // small fp32 area: sinusoid, time MLP, projections
+  size_t f32_off = 0;                  // small fp32 area: time MLP, projections
   size_t gn_off = 0;                   // GroupNorm scratch
 };
 

@@ -100,8 +100,21 @@ struct StepRef {
   const int* counter = nullptr;
   int offset = 0;
 };
-ad_status launch_sinusoid(float tau, StepRef ref, int dim, float* out, hipStream_t s);
-ad_status launch_advance(int* counter, int by, hipStream_t s);
+// first layer of the time embedding on the sinusoid of tau: out[n] = SiLU(bias[n] + w[n] . [cos | sin])
+ad_status launch_time_first(int dtype, float tau, StepRef ref, int dim, const void* w, const float* bias, int n, float* out, hipStream_t s);
+// the whole time embedding in one launch where time_fused_fits(): w1 [td][c0], w2 [td][td], pooled branch w3 [td][pooled_dim], w4 [td][td] (pooled
+// may be null), projections wp [rows][td] of SiLU(embedding); out [batch][rows]
+struct TimeArgs {
+  int dtype, c0, td, batch, rows;
+  float tau; StepRef ref;
+  const void* w1; const float* b1; const void* w2; const float* b2; const void* wp; const float* bp;
+  float* out;
+  const float* pooled = nullptr; int pooled_dim = 0;
+  const void* w3 = nullptr; const float* b3 = nullptr; const void* w4 = nullptr; const float* b4 = nullptr;
+};
+bool time_fused_fits(const TimeArgs& a);
+ad_status launch_time_fused(const TimeArgs& a, hipStream_t s);
+ad_status launch_advance(int* counter, int by, hipStream_t s, int* other = nullptr);
 // im2col of the fp32 latent (times scale) for the first 3x3 convolution: out [batch*h*w][kConvInK]; the latent is
 // [cl][h][w] shared by all batch rows, or [batch][cl][h][w] when per_sample is set
 ad_status launch_pack_latent(int dtype, const float* latent, int per_sample, float scale, StepRef ref, int cl, int h, int w, int batch,

@@ -226,29 +226,31 @@ static ad_status time_projection(Eval& e, int tau, StepRef tau_ref, const void* 
   // without the pooled branch every batch row has the same embedding: one row is computed and shared
   const int B = c.cfg.pooled_dim > 0 ? c.cfg.batch : 1;
   const int td = c.temb_dim, c0 = c.cfg.channels[0], dt = e.dt;
-  float* sinus = e.f32area();
-  float* t1 = sinus + c0;
+  float* t1 = e.f32area();
   float* temb = t1 + (size_t)B * td;
   float* pool1 = temb + (size_t)B * td;
   float* proj = pool1 + 2 * (size_t)B * td;
   WView wv{c};
-  AD_TRY(launch_sinusoid((float)tau, tau_ref, c0, sinus, e.s));
+  const char* wmat = c.weights_dev + c.temb_w_off + (size_t)e.cp.temb_row0 * td * esize(dt);
+  const float* bvec = (const float*)(c.weights_dev + c.temb_b_off) + e.cp.temb_row0;
+  e.proj = proj;
+  e.proj_ld = c.cfg.pooled_dim > 0 ? e.cp.temb_rows : -1;
+  if (c.cfg.pooled_dim > 0 && !pooled) AD_FAIL(AD_ERR_INVALID, "pooled embedding required by this configuration");
+  if (e.cp.temb_rows == 0) return AD_OK;                     // no ResBlock, nobody to tell
+  TimeArgs all{dt, c0, td, B, e.cp.temb_rows, (float)tau, tau_ref, wv.at(0), wv.f32(1), wv.at(2), wv.f32(3), wmat, bvec, proj};
+  if (c.cfg.pooled_dim > 0) {
+    all.pooled = (const float*)pooled; all.pooled_dim = c.cfg.pooled_dim;
+    all.w3 = wv.at(4); all.b3 = wv.f32(5); all.w4 = wv.at(6); all.b4 = wv.f32(7);
+  }
+  if (time_fused_fits(all)) return launch_time_fused(all, e.s);
   // the sinusoid is the same for every batch row: evaluate the MLP on one row, broadcast below
-  AD_TRY(launch_linear_rows(dt, sinus, 0, 1, c0, wv.at(0), wv.f32(1), td, 0, 1, 0, t1, e.s));
+  AD_TRY(launch_time_first(dt, (float)tau, tau_ref, c0, wv.at(0), wv.f32(1), td, t1, e.s));
   AD_TRY(launch_linear_rows(dt, t1, 0, B, td, wv.at(2), wv.f32(3), td, 0, 0, 0, temb, e.s));
   if (c.cfg.pooled_dim > 0) {
-    if (!pooled) AD_FAIL(AD_ERR_INVALID, "pooled embedding required by this configuration");
     AD_TRY(launch_linear_rows(dt, (const float*)pooled, c.cfg.pooled_dim, B, c.cfg.pooled_dim, wv.at(4), wv.f32(5), td, 0, 1, 0, pool1, e.s));
     AD_TRY(launch_linear_rows(dt, pool1, td, B, td, wv.at(6), wv.f32(7), td, 0, 0, 1, temb, e.s));
   }
-  e.proj = proj;
-  e.proj_ld = c.cfg.pooled_dim > 0 ? e.cp.temb_rows : -1;
-  if (e.cp.temb_rows > 0) {
-    const char* wmat = c.weights_dev + c.temb_w_off + (size_t)e.cp.temb_row0 * td * esize(dt);
-    const float* bvec = (const float*)(c.weights_dev + c.temb_b_off) + e.cp.temb_row0;
-    AD_TRY(launch_linear_rows(dt, temb, td, B, td, wmat, bvec, e.cp.temb_rows, 1, 0, 0, proj, e.s));
-  }
-  return AD_OK;
+  return launch_linear_rows(dt, temb, td, B, td, wmat, bvec, e.cp.temb_rows, 1, 0, 0, proj, e.s);
 }
 
 static ad_status run_component(Ctx& c, int comp, int lane, const void* const* in, int tau, float latent_scale,
@@ -664,8 +666,7 @@ static ad_status enqueue_round_edges(Ctx& c, size_t r0, size_t r1, void* latent,
                           StepRef{table, counter, lane_eps_off[j]}, c.cfg_scale, ss));
     if (steps_out) steps_out->push_back(lane_step[j]);
   }
-  AD_TRY(launch_advance(counter, (int)lane_stream.size(), ss));
-  AD_TRY(launch_advance(counters, (int)lane_stream.size(), ss));          // the counter of the barrier rounds moves along
+  AD_TRY(launch_advance(counter, (int)lane_stream.size(), ss, counters));          // (the counter of the barrier rounds moves along)
   AD_HIP(hipEventRecord(c.ev_sampler[g & 3], ss));
   AD_HIP(hipEventRecord(ev_done_of(c, c.N, g), ss));
   return AD_OK;

@@ -7,7 +7,7 @@ import torch
 from configs import CONFIGS
 from gpu_util import dev, host, nchw_to_nhwc, nhwc_to_nchw, rel_l2
 from paper_2406_06911_amd import binding as B
-from test_gpu_pipeline import Case
+from test_gpu_pipeline import Case, run_components_isolated
 
 pytestmark = pytest.mark.gpu
 
@@ -40,3 +40,16 @@ def test_transformer_of_a_narrow_model_matches_oracle(monkeypatch, dtype, c, hea
         err = rel_l2(got, after - before)
         assert np.isfinite(got).all() and err < (2e-2 if dtype == BF else 1e-5), err
         case.m.precompute_text(case.d_text, torch.cuda.current_stream())
+
+
+@pytest.mark.parametrize("dtype,c,batch,pooled,frames", [(F32, 32, 1, 0, 0), (F32, 64, 2, 8, 0), (BF, 64, 2, 128, 0), (BF, 64, 5, 0, 5), (BF, 128, 2, 16, 0),
+                                                         (F32, 96, 1, 0, 0), (BF, 192, 2, 0, 0)])
+def test_time_embedding_reaches_the_residual_blocks(monkeypatch, dtype, c, batch, pooled, frames):
+    """Both ways of the time embedding: in one launch (up to 256 features in fp32, 362 in bf16) and layer by layer, with and without the pooled
+    branch, at several timesteps (the ResBlock's output depends on them through the projection, whose weights are large here)."""
+    d = dict(latent_channels=4, height=4, width=4, batch=batch, channels=[c], layers_per_block=1, transformer_depth=[0], mid_depth=0, head_dim=32,
+             gn_groups=8, ctx_len=8, ctx_dim=64, pooled_dim=pooled, frames=frames, temporal_heads=4 if frames else 0)
+    monkeypatch.setitem(CONFIGS, "temb", d)
+    case = Case("temb", dtype, 2, 1, 1, 4, std=2 * c ** -0.5, cuts=[1])
+    # 1e-4 / 2e-2: the budget of a component, asserted inside
+    run_components_isolated(case)
