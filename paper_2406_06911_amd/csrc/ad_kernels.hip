@@ -1895,22 +1895,29 @@ constexpr float kAttnBig = 1.2676506e30f;         // 2^100: a 32-key row sum at 
 // one of the first 32 - the workgroup repeats its work with the checked block-by-block loop below.  The K fragments of a
 // step are fetched from LDS one step ahead, so a tile is opened (waited for, barrier) one block before its first scores:
 // three tiles are in use across that barrier plus one in flight, hence four stages (64 KiB, two workgroups per CU).
-template <int QSETS, bool RAGGED, int NSTG = 3, int OCC = (QSETS == 1 ? 3 : 2), int PIPE = 0>
-__global__ __attribute__((amdgpu_waves_per_eu(OCC, OCC))) __launch_bounds__(256) void k_attn_mfma2(
+//
+// KS > 1: the keys are shared out over KS groups of NWQ wavefronts, each with tiles and stages of its own, and merged at the end (launch
+// rule in attn_split()).
+template <int QSETS, bool RAGGED, int NSTG = 3, int OCC = (QSETS == 1 ? 3 : 2), int PIPE = 0, int NWQ = 4, int KS = 1>
+__global__ __attribute__((amdgpu_waves_per_eu(OCC, OCC))) __launch_bounds__(64 * NWQ * KS) void k_attn_mfma2(
     const bf16* __restrict__ Q, const bf16* __restrict__ K, const bf16* __restrict__ Vt, bf16* __restrict__ O, int L, int Lk, int C,
     int ldq, int ldk, int ldv, int ldo, float scale_log2, int qblocks) {
-  __shared__ __attribute__((aligned(128))) char lds[NSTG * kAttn2Stage];
+  extern __shared__ __attribute__((aligned(128))) char lds_all[];
+  static_assert(KS == 1 || (PIPE == 0 && QSETS == 1), "shared keys: the plain loop");
   constexpr int QW = 32 * QSETS;                  // queries per wavefront
   const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, half = lane >> 5;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wave_all = __builtin_amdgcn_readfirstlane(tid >> 6), wave = wave_all % NWQ, group = wave_all / NWQ;
+  char* const lds = lds_all + group * (NSTG * kAttn2Stage);
   const bool low = half == 0;
   const int vid = xcd_remap(blockIdx.x, gridDim.x);
   const int bh = vid / qblocks, heads = C / 64;
   const int b = bh / heads, h = bh - b * heads;
-  const int q0 = (vid - bh * qblocks) * (4 * QW) + wave * QW + l32;
+  const int q0 = (vid - bh * qblocks) * (NWQ * QW) + wave * QW + l32;
   const int ntiles = (Lk + 63) / 64;
+  // this group's tiles (never none): t_first .. t_last - 1
+  const int t_each = (ntiles + KS - 1) / KS, t_first = KS == 1 ? 0 : group * t_each, t_last = KS == 1 ? ntiles : min(ntiles, t_first + t_each);
 
-  // ---- tile loads: per 64-key tile a wavefront issues two 8-row groups of K and two of V^T
+  // ---- tile loads: per 64-key tile a wavefront issues LPT 8-row groups of K and LPT of V^T
   const bf16* kbase = K + (size_t)b * Lk * ldk + h * 64;
   const bf16* vbase = Vt + ((size_t)b * C + h * 64) * ldv;
   const u32x4 rsk = make_rsrc_words(kbase, (unsigned)(((size_t)(Lk - 1) * ldk + 64) * 2));
@@ -1918,34 +1925,35 @@ __global__ __attribute__((amdgpu_waves_per_eu(OCC, OCC))) __launch_bounds__(256)
   // LDS row r keeps its 16-byte chunk c at position c ^ ((r >> 1) & 7): the 16 rows that one quarter of a wavefront
   // reads in a cycle (same chunk, consecutive rows) then fall on 16 different 16-byte bank groups of the 256-byte
   // bank window (rows r and r + 8 collide with the plain r & 7 swizzle)
-  // A wavefront fills the 8-row groups g = wave and wave + 4 of the K tile and of the V^T tile: both have the same swizzle
-  // column, and their rows are 32 keys (32 rows of V^T) apart, so one lane offset serves both (the distance goes into the
+  // A wavefront fills the 8-row groups g = wave, wave + NWQ, ... of the K tile and of the V^T tile: they have the same swizzle
+  // column, and their rows are 8 NWQ keys (rows of V^T) apart, so one lane offset serves all (the distance goes into the
   // scalar offset of the load)
+  constexpr int LPT = 8 / NWQ;
   const int r8 = lane >> 3;
   const int scol = (lane & 7) ^ (((wave * 8 + r8) >> 1) & 7);                // chunk this lane fetches for its row
-  const int krow = 16 * (wave >> 1) + 8 * (r8 >> 2) + 4 * (wave & 1) + (r8 & 3);   // key held by LDS row 8 wave + r8 (+ 32: row + 32)
+  const int krow = 16 * (wave >> 1) + 8 * (r8 >> 2) + 4 * (wave & 1) + (r8 & 3);   // key held by LDS row 8 wave + r8 (+ 8 NWQ: row + 8 NWQ)
   const unsigned koff = (unsigned)(krow * ldk + scol * 8) * 2;
   const unsigned voff = (unsigned)((wave * 8 + r8) * ldv + scol * 8) * 2;
   const unsigned lds_base = (unsigned)(size_t)(__attribute__((address_space(3))) char*)lds;
-  const unsigned kstep = 64u * (unsigned)ldk * 2u, khalf = 32u * (unsigned)ldk * 2u, vhalf = 32u * (unsigned)ldv * 2u;
+  const unsigned kstep = 64u * (unsigned)ldk * 2u, khalf = 8u * NWQ * (unsigned)ldk * 2u, vhalf = 8u * NWQ * (unsigned)ldv * 2u;
   auto issue = [&](int t, int stage) {
     const unsigned st = lds_base + stage * kAttn2Stage + (unsigned)wave * 1024u;
     const bool last = RAGGED && t == ntiles - 1;
     if (!last) {
 #pragma unroll
-      for (int i = 0; i < 2; ++i) dma_load16(rsk, koff, (unsigned)t * kstep + i * khalf, st + i * 4096);
+      for (int i = 0; i < LPT; ++i) dma_load16(rsk, koff, (unsigned)t * kstep + i * khalf, st + i * NWQ * 1024);
 #pragma unroll
-      for (int i = 0; i < 2; ++i) dma_load16(rsv, voff, (unsigned)t * 128u + i * vhalf, st + 8192 + i * 4096);
+      for (int i = 0; i < LPT; ++i) dma_load16(rsv, voff, (unsigned)t * 128u + i * vhalf, st + 8192 + i * NWQ * 1024);
     } else {
       // keys past the end read zeros (their scores are masked, but the pad must not hold NaNs).  The row goes into the lane's offset:
-      // the range check compares that with the size less the scalar offset, and 32 rows on may lie beyond the size.
+      // the range check compares that with the size less the scalar offset, and some rows on may lie beyond the size.
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
-        dma_load16(rsk, t * 64 + krow + 32 * i >= Lk ? kOob : koff + (unsigned)t * kstep + i * khalf, 0u, st + i * 4096);
+      for (int i = 0; i < LPT; ++i)
+        dma_load16(rsk, t * 64 + krow + 8 * NWQ * i >= Lk ? kOob : koff + (unsigned)t * kstep + i * khalf, 0u, st + i * NWQ * 1024);
       // the last, partial tile of V^T goes through registers: values of keys past the end are cleared, whatever the pad holds
 #pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        const int g = wave + 4 * i;
+      for (int i = 0; i < LPT; ++i) {
+        const int g = wave + NWQ * i;
         bf16x8 v = *(const bf16x8*)(vbase + (size_t)(g * 8 + r8) * ldv + t * 64 + scol * 8);
 #pragma unroll
         for (int e = 0; e < 8; ++e)
@@ -1954,8 +1962,8 @@ __global__ __attribute__((amdgpu_waves_per_eu(OCC, OCC))) __launch_bounds__(256)
       }
     }
   };
-  issue(0, 0);
-  if (NSTG > 2 && ntiles > 1) issue(1, 1);
+  issue(t_first, 0);
+  if (NSTG > 2 && t_first + 1 < t_last) issue(t_first + 1, 1);
 
   // ---- queries: B operand of the score product, pre-multiplied by log2(e) / sqrt(d)
   bf16x8 qf[QSETS][4];
@@ -2036,7 +2044,7 @@ __global__ __attribute__((amdgpu_waves_per_eu(OCC, OCC))) __launch_bounds__(256)
     probs(sc, pb, psum);
     bool redo = first;
 #pragma unroll
-    for (int s = 0; s < QSETS; ++s) redo |= !(psum[s] < kAttnBig);
+    for (int s = 0; s < QSETS; ++s) redo |= !(psum[s] < kAttnBig) || (KS > 1 && m_ref[s] == -INFINITY);
     // the score MFMAs keep their program order: each chain of four runs back to back
 #pragma unroll
     for (int i = 0; i < 4 * QSETS; ++i) __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
@@ -2062,14 +2070,16 @@ __global__ __attribute__((amdgpu_waves_per_eu(OCC, OCC))) __launch_bounds__(256)
         a = fmaxf(a, sc[s][15]);
         a = fmaxf(a, other_half(a, low));
         const float m_new = first ? a : fmaxf(m_ref[s], a);
-        const float alpha = first ? 1.f : __builtin_amdgcn_exp2f(m_ref[s] - m_new);
+        // a group that starts in the middle of the keys may see nothing but minus infinity at first: no reference yet, nothing to rescale
+        const bool none = KS > 1 && m_ref[s] == -INFINITY;
+        const float alpha = first || none ? 1.f : __builtin_amdgcn_exp2f(m_ref[s] - m_new), sub = KS > 1 && m_new == -INFINITY ? 0.f : m_new;
         m_ref[s] = m_new;
         l_run[s] *= alpha;
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
           o[s][0][r] *= alpha; o[s][1][r] *= alpha;
-          sc[s][r] -= m_new;
-          negm[s][r] = -m_new;
+          sc[s][r] -= sub;
+          negm[s][r] = -sub;
         }
       }
       probs(sc, pb, psum);
@@ -2091,10 +2101,10 @@ __global__ __attribute__((amdgpu_waves_per_eu(OCC, OCC))) __launch_bounds__(256)
   // (a partial last tile waits by itself); after the barrier tile t is complete for every wavefront and everybody is done with
   // tile t - 1 (the pipelined path, which opens a tile one block early, is then done with tile t - 2: hence its fourth stage).
   auto open_tile = [&](int t, int stage) {
-    if (NSTG > 2 && t + 1 < ntiles && !(RAGGED && t + 2 == ntiles)) wait_vmcnt<4>(); else wait_vmcnt<0>();
+    if (NSTG > 2 && t + 1 < t_last && !(RAGGED && t + 2 == ntiles)) wait_vmcnt<2 * LPT>(); else wait_vmcnt<0>();
     __syncthreads();
     constexpr int AHEAD = NSTG > 2 ? 2 : 1;      // tiles requested ahead (a fourth stage is slack for the pipelined path)
-    if (t + AHEAD < ntiles) {
+    if (t + AHEAD < t_last) {
       int target = stage + AHEAD;
       if (target >= NSTG) target -= NSTG;
       issue(t + AHEAD, target);
@@ -2211,15 +2221,45 @@ __global__ __attribute__((amdgpu_waves_per_eu(OCC, OCC))) __launch_bounds__(256)
   }
   {
   int stage = 0;
-  for (int t = 0; t < ntiles; ++t) {
+  for (int t = t_first; t < t_first + t_each; ++t) {         // every group passes the same barriers
     open_tile(t, stage);
-    const char* Ks = lds + stage * kAttn2Stage;
-    block(Ks, t, 0, t == 0);
-    block(Ks, t, 1, false);
+    if (KS == 1 || t < t_last) {
+      const char* Ks = lds + stage * kAttn2Stage;
+      block(Ks, t, 0, t == t_first);
+      block(Ks, t, 1, false);
+    }
     if (++stage == NSTG) stage = 0;
   }
   }
 finished:
+  if constexpr (KS > 1) {
+    // the other groups hand their sums, references and denominators to the first one, a register of all lanes at a time
+    __syncthreads();
+    float* const hand = (float*)lds_all;
+    auto at = [&](int g, int r) { return hand + (((g - 1) * NWQ + wave) * 34 + r) * 64 + lane; };
+    if (group > 0) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r) { *at(group, r) = o[0][0][r]; *at(group, 16 + r) = o[0][1][r]; }
+      *at(group, 32) = m_ref[0];
+      *at(group, 33) = l_run[0];
+    }
+    __syncthreads();
+    if (group > 0) return;
+    float top = m_ref[0];
+#pragma unroll
+    for (int g = 1; g < KS; ++g) top = fmaxf(top, *at(g, 32));
+    const float f0 = __builtin_amdgcn_exp2f(m_ref[0] - top);
+    l_run[0] *= f0;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) { o[0][0][r] *= f0; o[0][1][r] *= f0; }
+#pragma unroll
+    for (int g = 1; g < KS; ++g) {
+      const float f = __builtin_amdgcn_exp2f(*at(g, 32) - top);
+      l_run[0] += f * *at(g, 33);
+#pragma unroll
+      for (int r = 0; r < 16; ++r) { o[0][0][r] += f * *at(g, r); o[0][1][r] += f * *at(g, 16 + r); }
+    }
+  }
 #pragma unroll
   for (int s = 0; s < QSETS; ++s) {
     const float l_tot = l_run[s] + other_half(l_run[s], low);
@@ -2394,6 +2434,13 @@ static int attn_auto_variant(int bh, int l, int lk) {
   return lk > 256 ? 1 : 0;
 }
 
+// Where 64-query workgroups fit the chip once, the plain launch (128 queries) leaves half of it idle: 64 queries and two key halves a
+// workgroup instead, which halves the chain of key tiles as well.  One sample, us (128 queries -> this): 2880 x 2880, 5 heads, 36.6 -> 25.0;
+// 1536, 10 heads, 21.6 -> 14.4; 720, 10 heads, 14.2 -> 10.0; 640, 20 heads, 11.2 -> 8.2.  Beyond that they are level (320 workgroups 15.8 / 14.9,
+// 360 10.8 / 11.0) and then fall behind (9216, 2 x 5 heads: 230 / 268, keys and values are fetched twice as often).  Four key shares with 128 KiB of
+// LDS gain another tenth from 1500 keys on, but leave the other streams' workgroups no room.
+static bool attn_split(int bh, int l) { return (long long)bh * ((l + 63) / 64) <= 256; }
+
 ad_status launch_attention(int dtype, const void* q, const void* k, const void* v, int v_t, int batch, int l, int lk, int c,
                            int head_dim, int ldq, int ldk, int ldv, int ldo, void* out, hipStream_t s) {
   if (!q || !k || !v || !out) AD_FAIL(AD_ERR_INVALID, "attention: null pointer");
@@ -2416,17 +2463,21 @@ ad_status launch_attention(int dtype, const void* q, const void* k, const void* 
       if (((long long)(lk + 64) * ldk + 64) * 2 >= (1LL << 31) || (64LL * ldv + lk + 64) * 2 >= (1LL << 31))
         AD_FAIL(AD_ERR_INVALID, "attention: key tensor too large");
       if ((((uintptr_t)q | (uintptr_t)k | (uintptr_t)v | (uintptr_t)out) & 15) != 0) AD_FAIL(AD_ERR_INVALID, "attention: pointers must be 16-byte aligned");
-      const int qw = variant == 2 ? 256 : 128, qb = (l + qw - 1) / qw;
-      const dim3 grid(qb * heads * batch);
       const float sl2 = scale * 1.44269504088896341f;
-#define AD_ATTN2(QS, RG) hipLaunchKernelGGL((k_attn_mfma2<QS, RG>), grid, dim3(256), 0, s, (const bf16*)q, (const bf16*)k, (const bf16*)v, \
-                                            (bf16*)out, l, lk, c, ldq, ldk, ldv, ldo, sl2, qb)
-      if (variant == 3) {
-        if (lk & 63) hipLaunchKernelGGL((k_attn_mfma2<1, true, 4, 2, 1>), grid, dim3(256), 0, s, (const bf16*)q, (const bf16*)k, (const bf16*)v, (bf16*)out, l, lk, c, ldq, ldk, ldv, ldo, sl2, qb);
-        else hipLaunchKernelGGL((k_attn_mfma2<1, false, 4, 2, 1>), grid, dim3(256), 0, s, (const bf16*)q, (const bf16*)k, (const bf16*)v, (bf16*)out, l, lk, c, ldq, ldk, ldv, ldo, sl2, qb);
-      } else if (variant == 2) { if (lk & 63) AD_ATTN2(2, true); else AD_ATTN2(2, false); }
-      else { if (lk & 63) AD_ATTN2(1, true); else AD_ATTN2(1, false); }
-#undef AD_ATTN2
+      auto run = [&](auto kern, int queries, int waves, int stages) -> ad_status {
+        const int qb = (l + queries - 1) / queries, lds_bytes = stages * kAttn2Stage;
+        if (lds_bytes > 65536) AD_HIP(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes));
+        hipLaunchKernelGGL(kern, dim3(qb * heads * batch), dim3(64 * waves), lds_bytes, s, (const bf16*)q, (const bf16*)k, (const bf16*)v, (bf16*)out, l, lk, c,
+                           ldq, ldk, ldv, ldo, sl2, qb);
+        return AD_OK;
+      };
+      const bool ragged = (lk & 63) != 0;
+      ad_status st = AD_OK;
+      if (variant == 3) st = ragged ? run(k_attn_mfma2<1, true, 4, 2, 1>, 128, 4, 4) : run(k_attn_mfma2<1, false, 4, 2, 1>, 128, 4, 4);
+      else if (variant == 2) st = ragged ? run(k_attn_mfma2<2, true>, 256, 4, 3) : run(k_attn_mfma2<2, false>, 256, 4, 3);
+      else if (g_attn_variant < 0 && attn_split(batch * heads, l)) st = ragged ? run(k_attn_mfma2<1, true, 2, 2, 0, 2, 2>, 64, 4, 4) : run(k_attn_mfma2<1, false, 2, 2, 0, 2, 2>, 64, 4, 4);
+      else st = ragged ? run(k_attn_mfma2<1, true>, 128, 4, 3) : run(k_attn_mfma2<1, false>, 128, 4, 3);
+      if (st != AD_OK) return st;
       AD_HIP(hipGetLastError());
       return AD_OK;
     }

@@ -653,6 +653,36 @@ def test_attention_rising_and_falling_maximum(lk, attn_variant):
     assert (jumps > 8).any() and ((jumps > 0) & (jumps < 8)).any()          # both kinds of moves occur
 
 
+@pytest.mark.parametrize("bsz,l,lk,heads", [(1, 1, 257, 1), (2, 63, 320, 1), (1, 64, 321, 3), (1, 65, 383, 2), (2, 129, 384, 1), (1, 200, 1025, 1), (1, 70, 2111, 1)])
+@pytest.mark.parametrize("ramp", [0.0, 6.0, -6.0])
+def test_attention_keys_shared_out(bsz, l, lk, heads, ramp):
+    """Launches of few queries share the keys out over two groups of wavefronts: query and key counts around the tiles, even and odd
+    numbers of tiles, and scores that differ by hundreds between the halves."""
+    d, dtype = 64, B.AD_BF16
+    q, v = (quantize(SI.make_array(s, sd), dtype) for s, sd in (((bsz, l, heads * d), 81), ((bsz, lk, heads * d), 83)))
+    k = SI.make_array((bsz, lk, heads * d), 82)
+    k[..., ::d] += ramp * np.linspace(-8.0, 8.0, lk)[None, :, None]
+    q[..., ::d] = quantize(np.abs(q[..., ::d]) * 4, dtype)
+    k = quantize(k, dtype)
+    got = run_attention(dtype, q, k, v, heads, True)
+    assert_kernel_close(got, P.attention(mfma2_contract(q, d, -1, dtype, True, lk), k, v, heads), dtype, c=4.0)
+
+
+@pytest.mark.parametrize("masked", [[(160, 300)], [(192, 299)], [(100, 224)], [(32, 200), (230, 290)]], ids=str)
+def test_attention_keys_shared_out_scores_of_minus_infinity(masked):
+    """The second group may have no finite score at first, or at all."""
+    l, lk, d, dtype = 40, 300, 64, B.AD_BF16
+    q, k, v = (quantize(SI.make_array((1, n, d), 86 + i), dtype) for i, n in enumerate((l, lk, lk)))
+    q[..., 0], k[..., 0] = quantize(1e20, dtype), 0.0
+    keep = np.ones(lk, bool)
+    for a, b in masked:
+        keep[a:b] = False
+    k[:, ~keep, 0] = quantize(-1e20, dtype)
+    got = run_attention(dtype, q, k, v, 1, True)
+    qr = mfma2_contract(q, d, -1, dtype, True, lk)
+    assert_kernel_close(got, P.attention(qr, k[:, keep], v[:, keep], 1), dtype, c=4.0)
+
+
 # ---------------------------------------------------------------------------------------------------
 @pytest.mark.parametrize("batch", [1, 2])
 def test_sampler_update(batch):
