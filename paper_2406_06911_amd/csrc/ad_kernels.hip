@@ -2,7 +2,7 @@
 //
 //   k_igemm*       implicit-GEMM convolution (3x3 / 1x1, stride 1 / 2, optional nearest-2x input,
 //                  optional channel concatenation) and linear layers on MFMA, with fused epilogues
-//   k_attn_mfma    fused attention (online softmax, K and V^T tiles in LDS, MFMA for QK^T and PV)
+//   k_attn_mfma*   fused attention (online softmax, K and V^T tiles in LDS, MFMA for QK^T and PV)
 //   k_attn_generic generic attention on fp32 MFMA, keys shared out over the wavefronts (fp32 mode, odd head sizes)
 //   k_attn_frames_mfma / k_attn_frames  attention over the frame axis of a video model (one wavefront per
 //                  position and head; MFMA without LDS for bf16, LDS-staged generic kernel otherwise)
@@ -568,15 +568,20 @@ __device__ __forceinline__ int lds_swizzle(int row) { return (row >> 1) & 7; }
 // Three stages, one workgroup per CU: 256x128 (144 KiB), 128x128 (96 KiB).  Two stages: 128x128 and 128x160 with two workgroups per
 // CU, which hide each other's prologue and epilogue, and 256x320 (144 KiB), whose k-tile is long enough for one tile in flight.
 // WM x WN wavefronts; with two per SIMD one has MFMAs to issue while the other waits at the barrier or for its fragments.
-// Bound by the feed from beyond the L2 and by what a launch of few rounds leaves idle, hence the choice of tiles (see kDmaTiles).
+// KG > 1: the k-tiles are shared out over KG groups of WM x WN wavefronts, each with stages of its own; the sums meet in LDS.  For launches of
+// at most a 64x64 workgroup per CU, whose four wavefronts would wait for two tiles of 16 KiB at a time: 2880x320x2880 16.0 -> 12.4 us,
+// 720x640x2560 14.4 -> 12.0, 180x3840x1280 11.2 -> 9.7, 288x1280x1280 8.3 -> 7.2 (two stages, four groups or 128-row tiles: slower).
+// Bound by the feed from beyond the L2 and by what a launch of few rounds leaves idle, hence the choice of tiles (see kDmaTiles): with the
+// MFMAs taken out 2048x1280x5120 still takes 49 of its 50 us (weights from memory), with the loads taken out 29.  More stages do not help
+// (four and five: 49), nor does a wavefront that asks for the lines ahead (53).
 // Measured, bf16, us (best of 128x128, 256x128 and 64x64 -> the tile of this list that kDmaTiles names): GEGLU 2048x10240x1280 72 -> 58
 // (256x320), 3x3 16384x640x5760 139 -> 116 (128x160), 3x3 65536x320x2880 130 -> 121 (256x320), q/k/v 65536x960x320 79 -> 64 (256x320),
 // GEGLU 8192x5120x640 78 -> 66 (256x320), 2048x1280x1280 16.2 -> 13.7 (128x128 for 64x64).
 // =================================================================================================
 // Wavefronts per SIMD that LDS allows: what the register budget is set for.
 constexpr int p3_waves_per_simd(int bm, int bn, int waves, int stages) { return (int)(kLdsLimit / (stages * (bm + bn) * kRowBytes)) * waves / 4; }
-template <typename T, int BM, int BN, int MODE, int WM = 2, int WN = 2, int NSTAGE = 3>
-__global__ __launch_bounds__(64 * WM * WN, p3_waves_per_simd(BM, BN, WM * WN, NSTAGE)) void k_igemm_p3(IgemmParams p) {
+template <typename T, int BM, int BN, int MODE, int WM = 2, int WN = 2, int NSTAGE = 3, int KG = 1>
+__global__ __launch_bounds__(64 * WM * WN * KG, p3_waves_per_simd(BM, BN, WM * WN, NSTAGE)) void k_igemm_p3(IgemmParams p) {
   typedef typename Vec<T>::type V;
   constexpr int NW = WM * WN;
   constexpr int WTM = BM / WM, WTN = BN / WN, TM = WTM / 32, TN = WTN / 32;
@@ -586,10 +591,11 @@ __global__ __launch_bounds__(64 * WM * WN, p3_waves_per_simd(BM, BN, WM * WN, NS
   constexpr int RND = 8 * NW;                                  // rows one round of loads (one per wavefront) covers
   constexpr int NG = TM * TN;                                  // MFMA groups per k-step; loads go out during the first three k-steps
   static_assert(OPS < 32, "vmcnt range");
-  extern __shared__ __attribute__((aligned(16))) char lds[];
+  extern __shared__ __attribute__((aligned(16))) char lds_all[];
 
   const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wave_all = __builtin_amdgcn_readfirstlane(tid >> 6), wave = wave_all % NW, group = KG > 1 ? wave_all / NW : 0;
+  char* const lds = lds_all + group * (NSTAGE * STAGE);
   const int l32 = lane & 31, half = lane >> 5;
   // wavefronts w and w + 4 share a SIMD: with wave_n = w / WM they hold different column halves whenever a SIMD has two,
   // so when the tile's second half lies beyond N (N = 320: 2.5 tiles of 128) every SIMD keeps one working wavefront
@@ -603,8 +609,9 @@ __global__ __launch_bounds__(64 * WM * WN, p3_waves_per_simd(BM, BN, WM * WN, NS
 
   // load i of a k-tile covers rows (NW i + wave) * 8 .. + 7 of the A tile (i < AG) or of the B tile
   const int r8 = lane >> 3, scol = (lane & 7) ^ (((wave * 8 + r8) >> 1) & 7);      // see lds_swizzle(); rows (NW i + wave) * 8 + r8
-  const int kt_begin = tid3.split * p.kt_per_split;
-  const int nkt = min(p.ktiles - kt_begin, p.kt_per_split);
+  const int kt_first = tid3.split * p.kt_per_split, kt_all = min(p.ktiles - kt_first, p.kt_per_split);
+  // this group's share of them (never none, see the launcher)
+  const int kt_each = (kt_all + KG - 1) / KG, kt_begin = kt_first + group * kt_each, nkt = KG == 1 ? kt_all : min(kt_all - group * kt_each, kt_each);
   const unsigned lds_base = (unsigned)(size_t)(__attribute__((address_space(3))) char*)lds;
   const unsigned grp = (unsigned)wave * 8 * kRowBytes;
   // load i of the weights is RND rows after load 0; large tiles form its offset anew each time, for want of registers
@@ -632,7 +639,7 @@ __global__ __launch_bounds__(64 * WM * WN, p3_waves_per_simd(BM, BN, WM * WN, NS
       for (int i = 0; i < BG; ++i)
         dma_load16(rsw, b_at(i), (unsigned)((kt_begin + t) * BK * ES), lds_base + t * STAGE + grp + (BM + i * RND) * kRowBytes);
     }
-  if (PRE && p.residual && p.vec16 && !idle) {
+  if (PRE && p.residual && p.vec16 && !idle && group == 0) {
 #pragma unroll
     for (int t = 0; t < RowSlabs<T, WTM, WTN>::COUNT; ++t) load_residual<T, WTM, WTN>(p, t, m0 + wave_m * WTM, n0 + wave_n * WTN, lane, res[t]);
   }
@@ -780,7 +787,9 @@ __global__ __launch_bounds__(64 * WM * WN, p3_waves_per_simd(BM, BN, WM * WN, NS
     for (; kt + NSTAGE - 1 < nkt; ++kt) k_tile(std::integral_constant<int, 2>{}, std::true_type{});
     for (; kt + 1 < nkt; ++kt) k_tile(std::integral_constant<int, 1>{}, std::true_type{});
     k_tile(std::integral_constant<int, 0>{}, std::true_type{});
+    for (int i = nkt; i < kt_each; ++i) __syncthreads();
     __syncthreads();
+    if constexpr (KG > 1) __syncthreads();
     if constexpr (MODE == OUT_GEGLU && TN % 2 != 0) __syncthreads();      // the epilogue's exchange
     return;
   }
@@ -789,30 +798,55 @@ __global__ __launch_bounds__(64 * WM * WN, p3_waves_per_simd(BM, BN, WM * WN, NS
   for (; kt + NSTAGE - 1 < nkt; ++kt) k_tile(std::integral_constant<int, 2>{}, std::false_type{});
   for (; kt + 1 < nkt; ++kt) k_tile(std::integral_constant<int, 1>{}, std::false_type{});
   k_tile(std::integral_constant<int, 0>{}, std::false_type{});
+  for (int i = nkt; i < kt_each; ++i) __syncthreads();       // every group passes the same barriers
   __syncthreads();     // every wavefront holds its last fragments: LDS can be reused by the epilogue
+  if constexpr (KG > 1) {
+    // the other groups hand over their sums, a register of all lanes at a time, behind what the epilogue stages in; added in order
+    float* const hand = (float*)(lds_all + NSTAGE * STAGE);
+    auto at = [&](int g, int i, int j, int r) { return hand + ((((g - 1) * NW + wave) * TM + i) * TN + j) * 1024 + r * 64 + lane; };
+    static_assert((KG - 1) * NW * TM * TN * 4096 <= (KG - 1) * NSTAGE * STAGE, "hand-over area");
+    if (group > 0) {
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) *at(group, i, j, r) = acc[i][j][r];
+    }
+    __syncthreads();
+    if (group > 0) return;
+#pragma unroll
+    for (int g = 1; g < KG; ++g)
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) acc[i][j][r] += *at(g, i, j, r);
+  }
   igemm_epilogue<T, WTM, WTN, TM, TN, MODE, CR, PRE>(p, acc, m0, n0, wave_m, wave_n, l32, half, lds + wave * stage_bytes<T, WTM, WTN>(CR), tid3.split, res,
                                                          (float*)(lds + NW * stage_bytes<T, WTM, WTN>(CR)) + wave_m * (WTM * 32));
 }
 
-template <typename T, int BM, int BN, int MODE, int WM = 2, int WN = 2, int NSTAGE = 3>
+template <typename T, int BM, int BN, int MODE, int WM = 2, int WN = 2, int NSTAGE = 3, int KG = 1>
 static ad_status run_igemm_p3(const IgemmParams& p0, const char* name, hipStream_t s) {
   IgemmParams p = p0;
   p.tiles_n = (p.N + BN - 1) / BN;
   const int tiles_m = (p.M + BM - 1) / BM;
   p.tiles_m = tiles_m;
-  constexpr int lds_bytes = NSTAGE * (BM + BN) * kRowBytes;
-  static_assert(lds_bytes >= WM * WN * stage_bytes<T, BM / WM, BN / WN>(16) && lds_bytes <= (int)kLdsLimit, "epilogue staging fits");
+  constexpr int lds_bytes = KG * NSTAGE * (BM + BN) * kRowBytes;
+  static_assert(lds_bytes / KG >= WM * WN * stage_bytes<T, BM / WM, BN / WN>(16) && lds_bytes <= (int)kLdsLimit, "epilogue staging fits");
   static_assert(MODE != OUT_GEGLU || BN / WN / 32 % 2 == 0 || lds_bytes >= WM * WN * stage_bytes<T, BM / WM, BN / WN>(32) + BM * 128, "so does the exchange");
   static std::atomic<bool> attr_set{false};
   if (!attr_set) {
-    AD_HIP(hipFuncSetAttribute((const void*)k_igemm_p3<T, BM, BN, MODE, WM, WN, NSTAGE>, hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes));
+    AD_HIP(hipFuncSetAttribute((const void*)k_igemm_p3<T, BM, BN, MODE, WM, WN, NSTAGE, KG>, hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes));
     attr_set = true;
   }
   const double in_bytes = (double)p.M * p.ctot * sizeof(T) * (p.stride == 2 ? 4 : 1) / (p.up ? 4 : 1);
   const double out_cols = p.out_mode == OUT_GEGLU ? p.N / 2 : p.N;
   ProfLaunch pl(name, 2.0 * p.M * p.N * p.k_prof, in_bytes + (double)p.N * p.Kp * sizeof(T) + (double)p.M * out_cols * sizeof(T), s, p.M, p.N, p.Kp);
   const int splits = (p.ktiles + p.kt_per_split - 1) / p.kt_per_split;
-  hipLaunchKernelGGL((k_igemm_p3<T, BM, BN, MODE, WM, WN, NSTAGE>), dim3(p.tiles_n * tiles_m, splits), dim3(64 * WM * WN), lds_bytes, s, p);
+  hipLaunchKernelGGL((k_igemm_p3<T, BM, BN, MODE, WM, WN, NSTAGE, KG>), dim3(p.tiles_n * tiles_m, splits), dim3(64 * WM * WN * KG), lds_bytes, s, p);
   AD_HIP(hipGetLastError());
   return AD_OK;
 }
@@ -1343,7 +1377,7 @@ __global__ __launch_bounds__(256) void k_splitk_reduce(const float* __restrict__
 
 // Tile shapes.  The register-staged kernels (64x64, 128x128) serve fp32 and the transposed epilogues; bf16 GEMMs with a row-major,
 // GEGLU, fused q/k/v or split-K epilogue take the LDS-DMA kernel with a tile of kDmaTiles; launches of few small tiles k_igemm_small.
-enum { TILE_128x128 = 1, TILE_64x64 = 3, TILE_D2_128 = 4, TILE_P3_128 = 5, TILE_P3_256 = 6, TILE_P3_64 = 7, TILE_HALO_128 = 8, TILE_HALO_256 = 9, TILE_P3_256_W4 = 10, TILE_P3_128_W4 = 11, TILE_P3_256_W16 = 12, TILE_SMALL = 13, TILE_D2_160 = 14, TILE_D2_320 = 15, TILE_AUTO = -1 };
+enum { TILE_128x128 = 1, TILE_64x64 = 3, TILE_D2_128 = 4, TILE_P3_128 = 5, TILE_P3_256 = 6, TILE_P3_64 = 7, TILE_HALO_128 = 8, TILE_HALO_256 = 9, TILE_P3_256_W4 = 10, TILE_P3_128_W4 = 11, TILE_P3_256_W16 = 12, TILE_SMALL = 13, TILE_D2_160 = 14, TILE_D2_320 = 15, TILE_K2_64 = 16, TILE_AUTO = -1 };
 static int g_tile_override = TILE_AUTO;
 static int g_order_override = -1;
 
@@ -1373,7 +1407,7 @@ static int splits_by_tiles(long long m, int n, int ktiles, int out_mode, int bm)
 // from its L2), two resident workgroups hide each other's prologue and epilogue, small tiles fill the chip when there are few rows.
 struct DmaTile { int tile, bm, bn, per_cu; double fixed, per_kt[3]; };
 static const DmaTile kDmaTiles[] = {
-    {TILE_P3_64, 64, 64, 3, 4.0, {0.32, 0.40, 0.62}},   {TILE_D2_128, 128, 128, 2, 5.0, {0.90, 0.98, 0.98}},
+    {TILE_P3_64, 64, 64, 3, 4.0, {0.32, 0.40, 0.62}},   {TILE_K2_64, 64, 64, 1, 4.6, {0.22, 0.22, 0.22}},   {TILE_D2_128, 128, 128, 2, 5.0, {0.90, 0.98, 0.98}},
     {TILE_P3_128, 128, 128, 1, 4.0, {0.50, 0.50, 0.50}}, {TILE_D2_160, 128, 160, 2, 7.0, {1.05, 1.25, 1.25}},
     {TILE_P3_256, 256, 128, 1, 5.0, {0.80, 0.80, 0.80}}, {TILE_D2_320, 256, 320, 1, 12.0, {2.00, 2.00, 2.00}},
 };
@@ -1433,11 +1467,12 @@ static ConvPlan compute_plan(int dtype, long long m, int n, int ktiles, int out_
   const int max_splits = (geglu || n % 4) ? 1 : 16;
   for (const DmaTile& t : kDmaTiles) {
     if (forced != TILE_AUTO && t.tile != forced) continue;
-    if (geglu && (t.tile == TILE_P3_64 || t.tile == TILE_D2_160)) continue;      // value and gate columns in one wavefront
+    if (geglu && (t.tile == TILE_P3_64 || t.tile == TILE_K2_64 || t.tile == TILE_D2_160)) continue;      // value and gate columns in one wavefront
     for (int sp = 1; sp <= max_splits; ++sp) {
       if (sp > 1 && ktiles / sp < 4) break;
       const int per = (ktiles + sp - 1) / sp;
       if ((ktiles + per - 1) / per != sp) continue;          // every split must own at least one k-tile
+      if (t.tile == TILE_K2_64 && ktiles - (sp - 1) * per < 2) continue;         // so must both groups of wavefronts
       const double c = plan_cost(m, n, ktiles, out_mode, t, sp);
       if (c < best_cost) { best_cost = c; best = ConvPlan{t.tile, sp}; }
     }
@@ -1606,6 +1641,13 @@ ad_status launch_conv(const ConvArgs& a, hipStream_t s) {
       case OUT_ROWMAJOR: st = run_igemm_p3<bf16, 64, 64, OUT_ROWMAJOR>(p, "igemm_bf16_64x64_p3", s); break;
       case OUT_QKV: st = run_igemm_p3<bf16, 64, 64, OUT_QKV>(p, "igemm_bf16_64x64_p3", s); break;
       case OUT_PARTIAL: st = run_igemm_p3<bf16, 64, 64, OUT_PARTIAL>(p, "igemm_bf16_64x64_p3_splitk", s); break;
+      default: break;
+    }
+  } else if (tile == TILE_K2_64) {
+    switch (mode) {
+      case OUT_ROWMAJOR: st = run_igemm_p3<bf16, 64, 64, OUT_ROWMAJOR, 2, 2, 3, 2>(p, "igemm_bf16_64x64_k2", s); break;
+      case OUT_QKV: st = run_igemm_p3<bf16, 64, 64, OUT_QKV, 2, 2, 3, 2>(p, "igemm_bf16_64x64_k2", s); break;
+      case OUT_PARTIAL: st = run_igemm_p3<bf16, 64, 64, OUT_PARTIAL, 2, 2, 3, 2>(p, "igemm_bf16_64x64_k2_splitk", s); break;
       default: break;
     }
   } else if (tile == TILE_D2_128) {

@@ -301,6 +301,39 @@ def test_two_stage_tiles_follow_sources_and_taps(tile, c0, c1, k, stride, up):
         B.check(lib.ad_tune_conv_tile(-1))
 
 
+@pytest.mark.parametrize("c0,c1,k,stride,up,n_out", [(448, 0, 1, 1, 0, 640), (64, 0, 3, 1, 0, 640), (128, 64, 3, 1, 0, 600), (640, 640, 1, 1, 0, 642),
+                                                     (192, 0, 3, 2, 0, 1280), (64, 128, 3, 1, 1, 320), (2496, 0, 1, 1, 0, 640)])
+def test_k_shared_by_two_groups(c0, c1, k, stride, up, n_out):
+    """64x64 tiles whose k-tiles are shared out over two groups of wavefronts (the automatic choice for these shapes): odd and even numbers of
+    k-tiles, changes of tap and source at and beside the middle, ragged rows and columns, everything the epilogue adds, split over workgroups."""
+    n, hs, ws = (2, 25, 20) if not up else (2, 12, 11)
+    x0, x1 = (quantize(SI.make_array((n, c, hs, ws), 391 + i), B.AD_BF16) if c else None for i, c in enumerate((c0, c1)))
+    w = quantize(SI.make_array((n_out, c0 + c1, k, k), 393, 0.05), B.AD_BF16)
+    bias, rowvec = SI.make_array((n_out,), 394, 0.1), SI.make_array((n, n_out), 395)
+    xin = x0 if x1 is None else np.concatenate([x0, x1], 1)
+    ref = P.conv2d(P.upsample_nearest2x(xin) if up else xin, w, bias, stride=stride) + rowvec[:, :, None, None]
+    res = quantize(SI.make_array((n, ref.shape[2], ref.shape[3], n_out), 396), B.AD_BF16)
+    for splitk in (False, True):
+        got, _ = run_conv(B.AD_BF16, x0, x1, w, bias, stride, up, rowvec=rowvec, residual=res, splitk=splitk)
+        assert_kernel_close(nhwc_to_nchw(got), ref + nhwc_to_nchw(res), B.AD_BF16)
+
+
+@pytest.mark.parametrize("l,c,cin,ld_t", [(500, 320, 640, 512), (333, 192, 704, 0), (257, 320, 1344, 260)])
+def test_k_shared_by_two_groups_fused_projection(l, c, cin, ld_t):
+    x, w = quantize(SI.make_array((2 * l, cin), 397), B.AD_BF16), quantize(SI.make_array((3 * c, cin), 398, 0.05), B.AD_BF16)
+    dx, wp = dev(x, B.AD_BF16), dev_bytes(B.pack_conv_weight(B.AD_BF16, w))
+    q, k = (torch.full((2 * l, c), float("nan"), device=DEV, dtype=torch.bfloat16) for _ in range(2))
+    v = torch.full((2 * c * ld_t if ld_t else 2 * l * c,), float("nan"), device=DEV, dtype=torch.bfloat16)
+    B.check(lib.ad_conv_forward(B.AD_BF16, p(dx), None, cin, 0, 2, l, 1, 0, 1, 1, p(wp), 3 * c, None, None, None, p(q), p(k), p(v), B.OUT_QKV, ld_t, None, 0,
+                                stream_ptr()))
+    sync()
+    ref = P.linear(x, w)
+    assert_kernel_close(host(q), ref[:, :c], B.AD_BF16)
+    assert_kernel_close(host(k), ref[:, c:2 * c], B.AD_BF16)
+    got = host(v).reshape(2, c, ld_t)[:, :, :l] if ld_t else host(v).reshape(2, l, c).transpose(0, 2, 1)
+    assert_kernel_close(got, ref[:, 2 * c:].reshape(2, l, c).transpose(0, 2, 1), B.AD_BF16)
+
+
 @pytest.mark.parametrize("dtype", DT)
 @pytest.mark.parametrize("tile", [-1, 5, 14])
 @pytest.mark.parametrize("bsz,l,c,ld_t,shift", [(2, 36, 64, 0, 0), (2, 36, 64, 0, 1), (2, 36, 64, 36, 0), (3, 21, 96, 21, 2), (1, 70, 32, 96, 4)])
