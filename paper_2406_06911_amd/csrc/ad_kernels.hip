@@ -59,24 +59,35 @@ struct IgemmParams {
   int k_prof;                         // K the profiler counts (the real one where the operand is zero-padded), else Kp
   int vec16;                          // row-major outputs and the residual can be accessed 16 bytes at a time
   int turn16;                         // OUT_QKV: so can the rows of the transposed third
-  int n_major;                        // workgroup order: 0 = an XCD owns a run of row tiles (all column tiles of each),
-                                      // 1 = an XCD owns a run of column tiles (all row tiles of each); see tile_of()
+  int band;                           // workgroup order: row tiles per band, see tile_of(); 0 = all of them
+  FastDiv div_tiles, div_band, div_rows, div_last;      // by tiles, tiles of a band, row tiles of a band and of the last band
 };
 
 // Which (row tile, column tile, split) a workgroup computes.  Workgroups go to the 8 XCDs round-robin in
-// launch order (x fastest, then y); xcd_remap turns that into 8 contiguous runs of a virtual index, and the
-// virtual index is laid out [split][row tile][column tile] or [split][column tile][row tile].  With the first
-// order an XCD's L2 sees a slice of the activations and every weight it needs once per slice; with the second it
-// sees a slice of the weights and all activations.  The launcher picks the order that re-fetches the smaller
-// operand (deep levels: few rows, tens of MB of weights -> column-major).
+// launch order (x fastest, then y); xcd_remap turns that into 8 contiguous runs of a virtual index.  The virtual index
+// is laid out [split][band of row tiles][column tile][row tile of the band]: an XCD's run is a block of row and column
+// tiles, and what its L2 takes in per k-tile is the rows of that block plus its columns.  Bands of one row tile: a slice
+// of the activations and every weight; one band: a slice of the weights and every activation; between them (see
+// best_band()) the blocks are about square.
 struct TileId { int m_tile, n_tile, split; };
 __device__ __forceinline__ TileId tile_of(const IgemmParams& p) {
   const int tiles = p.tiles_m * p.tiles_n;
   const int lid = blockIdx.y * gridDim.x + blockIdx.x;
   const int vid = xcd_remap(lid, gridDim.x * gridDim.y);
-  const int split = vid / tiles, t = vid - split * tiles;
-  if (p.n_major) return TileId{t % p.tiles_m, t / p.tiles_m, split};
-  return TileId{t / p.tiles_n, t % p.tiles_n, split};
+  const int split = (int)fast_div((unsigned)vid, p.div_tiles), t = vid - split * tiles;
+  const int b = (int)fast_div((unsigned)t, p.div_band), r = t - b * p.band * p.tiles_n;
+  const int rows = min(p.band, p.tiles_m - b * p.band);
+  const int n_tile = (int)(rows == p.band ? fast_div((unsigned)r, p.div_rows) : fast_div((unsigned)r, p.div_last));
+  return TileId{b * p.band + r - n_tile * rows, n_tile, split};
+}
+static void set_tiles(IgemmParams& p, int bm, int bn) {
+  p.tiles_m = (p.M + bm - 1) / bm;
+  p.tiles_n = (p.N + bn - 1) / bn;
+  if (p.band < 1 || p.band > p.tiles_m) p.band = p.tiles_m;
+  p.div_tiles = make_fastdiv((unsigned)(p.tiles_m * p.tiles_n));
+  p.div_band = make_fastdiv((unsigned)(p.band * p.tiles_n));
+  p.div_rows = make_fastdiv((unsigned)p.band);
+  p.div_last = make_fastdiv((unsigned)(p.tiles_m % p.band ? p.tiles_m % p.band : p.band));
 }
 
 constexpr size_t kLdsLimit = 160 * 1024;
@@ -831,9 +842,7 @@ __global__ __launch_bounds__(64 * WM * WN * KG, p3_waves_per_simd(BM, BN, WM * W
 template <typename T, int BM, int BN, int MODE, int WM = 2, int WN = 2, int NSTAGE = 3, int KG = 1>
 static ad_status run_igemm_p3(const IgemmParams& p0, const char* name, hipStream_t s) {
   IgemmParams p = p0;
-  p.tiles_n = (p.N + BN - 1) / BN;
-  const int tiles_m = (p.M + BM - 1) / BM;
-  p.tiles_m = tiles_m;
+  set_tiles(p, BM, BN);
   constexpr int lds_bytes = KG * NSTAGE * (BM + BN) * kRowBytes;
   static_assert(lds_bytes / KG >= WM * WN * stage_bytes<T, BM / WM, BN / WN>(16) && lds_bytes <= (int)kLdsLimit, "epilogue staging fits");
   static_assert(MODE != OUT_GEGLU || BN / WN / 32 % 2 == 0 || lds_bytes >= WM * WN * stage_bytes<T, BM / WM, BN / WN>(32) + BM * 128, "so does the exchange");
@@ -846,7 +855,7 @@ static ad_status run_igemm_p3(const IgemmParams& p0, const char* name, hipStream
   const double out_cols = p.out_mode == OUT_GEGLU ? p.N / 2 : p.N;
   ProfLaunch pl(name, 2.0 * p.M * p.N * p.k_prof, in_bytes + (double)p.N * p.Kp * sizeof(T) + (double)p.M * out_cols * sizeof(T), s, p.M, p.N, p.Kp);
   const int splits = (p.ktiles + p.kt_per_split - 1) / p.kt_per_split;
-  hipLaunchKernelGGL((k_igemm_p3<T, BM, BN, MODE, WM, WN, NSTAGE, KG>), dim3(p.tiles_n * tiles_m, splits), dim3(64 * WM * WN * KG), lds_bytes, s, p);
+  hipLaunchKernelGGL((k_igemm_p3<T, BM, BN, MODE, WM, WN, NSTAGE, KG>), dim3(p.tiles_n * p.tiles_m, splits), dim3(64 * WM * WN * KG), lds_bytes, s, p);
   AD_HIP(hipGetLastError());
   return AD_OK;
 }
@@ -1053,8 +1062,7 @@ __global__ __launch_bounds__(512) void k_igemm_small(IgemmParams p) {
 template <typename T, int TM, int TN, int MODE>
 static ad_status run_igemm_small(const IgemmParams& p0, const char* name, hipStream_t s) {
   IgemmParams p = p0;
-  p.tiles_n = (p.N + 16 * TN - 1) / (16 * TN);
-  p.tiles_m = (p.M + 16 * TM - 1) / (16 * TM);
+  set_tiles(p, 16 * TM, 16 * TN);
   constexpr int lds_bytes = 8 * 16 * TM * (16 * TN + 4) * 4;
   if constexpr (lds_bytes > 65536) {
     static std::atomic<bool> attr_set{false};
@@ -1260,8 +1268,7 @@ static size_t halo_lds_bytes(int bm, int nb, int ws, int up) {
 template <int BM, int NB, int MODE>
 static ad_status run_conv3_halo(const IgemmParams& p0, int splits, const char* name, hipStream_t s) {
   IgemmParams p = p0;
-  p.tiles_n = (p.N + 127) / 128;
-  p.tiles_m = (p.M + BM - 1) / BM;
+  set_tiles(p, BM, 128);
   HaloParams hp;
   hp.hr = halo_rows(BM, p.ws, p.up);
   const int nchunks = p.ctot / 64;
@@ -1285,9 +1292,7 @@ static ad_status run_conv3_halo(const IgemmParams& p0, int splits, const char* n
 template <typename T, int BM, int BN, int WGM, int WGN, int NSET, int MODE>
 static ad_status run_igemm(const IgemmParams& p0, const char* name, hipStream_t s) {
   IgemmParams p = p0;
-  p.tiles_n = (p.N + BN - 1) / BN;
-  const int tiles_m = (p.M + BM - 1) / BM;
-  p.tiles_m = tiles_m;
+  set_tiles(p, BM, BN);
   constexpr int lds_bytes = 2 * (BM + BN) * kPitch;
   static std::atomic<bool> attr_set{false};     // LDS above 64 KiB has to be requested once per kernel
   if (!attr_set) {
@@ -1298,7 +1303,7 @@ static ad_status run_igemm(const IgemmParams& p0, const char* name, hipStream_t 
   const double out_cols = p.out_mode == OUT_GEGLU ? p.N / 2 : p.N;
   ProfLaunch pl(name, 2.0 * p.M * p.N * p.k_prof, in_bytes + (double)p.N * p.Kp * sizeof(T) + (double)p.M * out_cols * sizeof(T), s, p.M, p.N, p.Kp);
   const int splits = (p.ktiles + p.kt_per_split - 1) / p.kt_per_split;
-  hipLaunchKernelGGL((k_igemm<T, BM, BN, WGM, WGN, NSET, MODE>), dim3(p.tiles_n * tiles_m, splits), dim3(256), lds_bytes, s, p);
+  hipLaunchKernelGGL((k_igemm<T, BM, BN, WGM, WGN, NSET, MODE>), dim3(p.tiles_n * p.tiles_m, splits), dim3(256), lds_bytes, s, p);
   AD_HIP(hipGetLastError());
   return AD_OK;
 }
@@ -1381,7 +1386,7 @@ enum { TILE_128x128 = 1, TILE_64x64 = 3, TILE_D2_128 = 4, TILE_P3_128 = 5, TILE_
 static int g_tile_override = TILE_AUTO;
 static int g_order_override = -1;
 
-struct ConvPlan { int tile; int splits; };
+struct ConvPlan { int tile, splits, band; };      // band: of tile_of(), -1 = the launcher decides between one row tile and all
 
 static bool dma_capable(int dtype, int out_mode) {
   return dtype == AD_BF16 && (out_mode == OUT_ROWMAJOR || out_mode == OUT_GEGLU || out_mode == OUT_QKV);
@@ -1427,6 +1432,24 @@ static double plan_cost(long long m, int n, int ktiles, int out_mode, const DmaT
   return cost;
 }
 
+// Row tiles per band (tile_of): the workgroups of an XCD that run side by side, at most 32 CUs full, should take in the fewest rows
+// and columns per k-tile.  Weights from memory, us (bands of one row tile / one band / this): 2048x1280x5120 50.6 / 49.3 / 47.8, 8192x640x2560
+// 33.1 / 38.1 / 30.4, 4608x5120x640 45.8 / 48.6 / 42.4, 4608x640x2560 24.1 / 24.3 / 21.5, 2048x10240x1280 58.7 / 54.3 / 53.3, 3x3 18432x320x2880
+// 39.5 / 41.7 / 37.9; of 29 shapes one is slower than the better of the two by more than 3 % (2048x640x2560: 17.4 / 20.4 / 18.1).
+static int best_band(long long m, int n, const DmaTile& t, int splits) {
+  const long long tm = (m + t.bm - 1) / t.bm, tn = (n + t.bn - 1) / t.bn, wgs = tm * tn * splits;
+  const long long resident = std::min<long long>(t.per_cu, (wgs + 255) / 256);
+  const long long run = std::min({(wgs + 7) / 8, 32 * resident, tm * tn});
+  long long best = 1, best_rows = -1;
+  for (long long band = 1; band <= std::min(tm, run); ++band) {
+    const long long tiles = band * tn;                       // of a band; a run is part of one or several whole ones
+    const long long rows = tiles >= run ? band : std::min(tm, band * ((run + tiles - 1) / tiles)), cols = tiles >= run ? (run + band - 1) / band : tn;
+    const long long taken = rows * t.bm + cols * t.bn;
+    if (best_rows < 0 || taken < best_rows) { best_rows = taken; best = band; }
+  }
+  return (int)best;
+}
+
 // Tile of k_igemm_small (16-row and 16-column units), or {0, 0} where another kernel is the better choice: the smallest tile that
 // makes at most a workgroup per CU, as long as a workgroup takes in at most 200 KiB (beyond that the 60 GB/s a CU gets from memory
 // decide, and K split over workgroups wins: 3x3 72x192x5760 13 us against 11).  GEGLU pairs 32 value with 32 gate columns.
@@ -1453,16 +1476,17 @@ static ConvPlan compute_plan(int dtype, long long m, int n, int ktiles, int out_
     if (!dma || ((forced == TILE_P3_64 || forced == TILE_D2_160) && geglu)) forced = TILE_AUTO;
   }
   else if (forced != TILE_AUTO && geglu) forced = TILE_AUTO;
-  if (forced == TILE_128x128 || forced == TILE_64x64) return ConvPlan{forced, splits_by_tiles(m, n, ktiles, out_mode, forced == TILE_64x64 ? 64 : 128)};
-  if (forced == TILE_AUTO && small_tile(m, n, ktiles, out_mode).tm) return ConvPlan{TILE_SMALL, 1};
+  if (forced == TILE_128x128 || forced == TILE_64x64) return ConvPlan{forced, splits_by_tiles(m, n, ktiles, out_mode, forced == TILE_64x64 ? 64 : 128), -1};
+  if (forced == TILE_AUTO && small_tile(m, n, ktiles, out_mode).tm) return ConvPlan{TILE_SMALL, 1, -1};
   if (!dma) {
     // measured on the GEMM shapes of the SD-sized models: 128x128 register-staged tiles pay off once there is
     // more than one of them per CU, or with very few rows and a long K (the weights are re-read less often)
     const long long tiles128 = ((m + 127) / 128) * ((n + 127) / 128);
     const int tile = (geglu || tiles128 >= 288 || (m <= 512 && ktiles >= 64)) ? TILE_128x128 : TILE_64x64;
-    return ConvPlan{tile, splits_by_tiles(m, n, ktiles, out_mode, tile == TILE_64x64 ? 64 : 128)};
+    return ConvPlan{tile, splits_by_tiles(m, n, ktiles, out_mode, tile == TILE_64x64 ? 64 : 128), -1};
   }
-  ConvPlan best{TILE_P3_128, 1};
+  ConvPlan best{TILE_P3_128, 1, -1};
+  const DmaTile* chosen = nullptr;
   double best_cost = 1e300;
   const int max_splits = (geglu || n % 4) ? 1 : 16;
   for (const DmaTile& t : kDmaTiles) {
@@ -1474,9 +1498,10 @@ static ConvPlan compute_plan(int dtype, long long m, int n, int ktiles, int out_
       if ((ktiles + per - 1) / per != sp) continue;          // every split must own at least one k-tile
       if (t.tile == TILE_K2_64 && ktiles - (sp - 1) * per < 2) continue;         // so must both groups of wavefronts
       const double c = plan_cost(m, n, ktiles, out_mode, t, sp);
-      if (c < best_cost) { best_cost = c; best = ConvPlan{t.tile, sp}; }
+      if (c < best_cost) { best_cost = c; best = ConvPlan{t.tile, sp, -1}; chosen = &t; }
     }
   }
+  if (chosen) best.band = best_band(m, n, *chosen, best.splits);
   return best;
 }
 
@@ -1540,7 +1565,7 @@ ad_status launch_conv(const ConvArgs& a, hipStream_t s) {
   p.bytes0 = (unsigned)(in_elems * a.c0 * esize(a.dtype));
   p.bytes1 = a.c1 ? (unsigned)(in_elems * a.c1 * esize(a.dtype)) : p.bytes0;
   p.bytes_w = (unsigned)w_bytes;
-  // workgroup order: the operand that is re-fetched by every XCD should be the smaller one.  The activations of
+  // workgroup order where the plan has none: the operand that is re-fetched by every XCD should be the smaller one.  The activations of
   // a 3x3 convolution count once per tap: a tap's rows come back only after a whole pass over the channels, long
   // after an L2 has dropped them (measured: 333 instead of 828 MB of L2 fills for the 1920 -> 640 convolution)
   const int vn = 16 / (int)esize(a.dtype), ncols = a.out_mode == OUT_GEGLU ? a.n_out / 2 : a.out_mode == OUT_QKV ? a.n_out / 3 : a.n_out;
@@ -1548,9 +1573,9 @@ ad_status launch_conv(const ConvArgs& a, hipStream_t s) {
   const auto at16 = [](const void* q) { return ((uintptr_t)q & 15) == 0; };
   p.vec16 = ncols % vn == 0 && at16(a.out) && at16(a.residual) && (a.out_mode != OUT_QKV || (at16(a.out2) && (turned || at16(a.out3))));
   p.turn16 = turned && at16(a.out3) && a.ld_t % vn == 0 && p.hw_out % vn == 0;
-  p.n_major = w_bytes > in_elems * (long long)(a.c0 + a.c1) * (long long)esize(a.dtype) * a.ksize * a.ksize ? 1 : 0;
-  if (g_order_override >= 0) p.n_major = g_order_override;
   const ConvPlan plan = choose_plan(a.dtype, m, a.n_out, p.ktiles, a.out_mode);
+  p.band = plan.band >= 0 ? plan.band : w_bytes > in_elems * (long long)(a.c0 + a.c1) * (long long)esize(a.dtype) * a.ksize * a.ksize ? 0 : 1;
+  if (g_order_override >= 0) p.band = g_order_override == 1 ? 0 : 1;
   const int tile = plan.tile;
   int splits = plan.splits;
   if (splits > 1 && (!a.splitk_ws || a.splitk_bytes < (size_t)splits * m * a.n_out * 4)) splits = 1;   // no scratch: plain launch

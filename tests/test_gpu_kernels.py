@@ -301,6 +301,25 @@ def test_two_stage_tiles_follow_sources_and_taps(tile, c0, c1, k, stride, up):
         B.check(lib.ad_tune_conv_tile(-1))
 
 
+@pytest.mark.parametrize("rows,cin,n_out,tile", [(2048, 128, 1280, 5), (1800, 128, 1100, 5), (4500, 64, 640, 6), (1100, 448, 448, 7), (1100, 448, 448, -1), (2900, 64, 800, 14),
+                                                 (3000, 64, 1600, 15), (900, 1024, 640, 4)])
+def test_workgroup_order_in_bands(rows, cin, n_out, tile):
+    """Every output tile once, whatever the order: bands of several row tiles with a shorter last one, runs of an XCD that end inside a band, K-splits.
+    The order changes no sum, so all three are equal bit for bit."""
+    x, w = quantize(SI.make_array((rows, cin), 71), B.AD_BF16), quantize(SI.make_array((n_out, cin), 72, 0.1), B.AD_BF16)
+    got = []
+    B.check(lib.ad_tune_conv_tile(tile))
+    try:
+        for order in (-1, 0, 1):
+            B.check(lib.ad_tune_conv_order(order))
+            got.append(run_conv(B.AD_BF16, x.T.reshape(1, cin, rows, 1), None, w.reshape(n_out, cin, 1, 1), None, splitk=True)[0].reshape(rows, n_out))
+    finally:
+        B.check(lib.ad_tune_conv_tile(-1))
+        B.check(lib.ad_tune_conv_order(-1))
+    assert_kernel_close(got[0], P.linear(x, w), B.AD_BF16)
+    assert np.array_equal(got[0], got[1]) and np.array_equal(got[0], got[2])
+
+
 @pytest.mark.parametrize("c0,c1,k,stride,up,n_out", [(448, 0, 1, 1, 0, 640), (64, 0, 3, 1, 0, 640), (128, 64, 3, 1, 0, 600), (640, 640, 1, 1, 0, 642),
                                                      (192, 0, 3, 2, 0, 1280), (64, 128, 3, 1, 1, 320), (2496, 0, 1, 1, 0, 640)])
 def test_k_shared_by_two_groups(c0, c1, k, stride, up, n_out):
