@@ -475,6 +475,7 @@ static void plan_work(Ctx& c) {
           gemm(m_out, u.c_out, 9 * (u.c_in + u.c_skip));
           gemm(m_out, u.c_out, 9 * u.c_out);
           gemm(m_out, u.c_out, u.c_in + u.c_skip);
+          want(9, conv_workspace_bytes(g.dtype, (long long)m_out, u.c_out, 9 * u.c_out + u.c_in + u.c_skip, OUT_ROWMAJOR));      // both in one launch
           break;
         case AD_UNIT_TFM: {
           const size_t L = (size_t)u.h_in * u.w_in, C = u.c_in;

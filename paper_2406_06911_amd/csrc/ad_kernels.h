@@ -43,6 +43,11 @@ struct ConvArgs {
   size_t splitk_bytes = 0;
   void* out2 = nullptr; void* out3 = nullptr;   // OUT_QKV: columns [n/3, 2n/3) and [2n/3, n)
   int k_real = 0;                       // > 0: K without zero padding, for the profiler's FLOP count (the im2col'ed first convolution)
+  // a 1x1 convolution of x0 (and x1, concatenated on channels) added to a 3x3 one at stride 1, as further k-tiles of the same launch; only
+  // where conv_takes_shortcut() says so
+  const void* x0 = nullptr; const void* x1 = nullptr;
+  int xc0 = 0, xc1 = 0;
+  const void* xw = nullptr;             // packed [n_pad][xc0 + xc1]
 };
 // OUT_QKV: n_out = 3c; thirds go to out [m][c], out2 [m][c] and out3 ([batch][c][ld_t] when ld_t > 0, else [m][c])
 enum { OUT_ROWMAJOR = 0, OUT_GEGLU = 1, OUT_TRANSPOSED = 2, OUT_TRANSPOSED_F32 = 3, OUT_QKV = 4 };
@@ -53,6 +58,7 @@ void set_attn_variant(int variant);   // -1 automatic, 0 first-generation kernel
 void set_order_override(int order);   // -1 automatic, 0 row-tile-major, 1 column-tile-major workgroup order
 // scratch a convolution of this shape wants for split-K (0 = it will not split); k = taps * channels
 size_t conv_workspace_bytes(int dtype, long long m, int n, int k, int out_mode);
+bool conv_takes_shortcut(int dtype, long long m, int n, int c, int xc);      // c, xc: channels of the 3x3 and of the 1x1 convolution
 
 ad_status launch_groupnorm(int dtype, const void* src0, const void* src1, int c0, int c1, int batch, int hw, int groups,
                            const float* gamma, const float* beta, float eps, int silu, void* out, void* scratch,

@@ -61,6 +61,9 @@ struct IgemmParams {
   int turn16;                         // OUT_QKV: so can the rows of the transposed third
   int band;                           // workgroup order: row tiles per band, see tile_of(); 0 = all of them
   FastDiv div_tiles, div_band, div_rows, div_last;      // by tiles, tiles of a band, row tiles of a band and of the last band
+  const void* x0; const void* x1; const void* xw;       // XTRA (k_igemm_p3): sources and weights of the 1x1 convolution behind the taps
+  int xc0, xc1, kt_main;                                // its channels; k-tiles of the taps
+  unsigned xbytes0, xbytes1, xbytes_w;
 };
 
 // Which (row tile, column tile, split) a workgroup computes.  Workgroups go to the 8 XCDs round-robin in
@@ -591,7 +594,7 @@ __device__ __forceinline__ int lds_swizzle(int row) { return (row >> 1) & 7; }
 // =================================================================================================
 // Wavefronts per SIMD that LDS allows: what the register budget is set for.
 constexpr int p3_waves_per_simd(int bm, int bn, int waves, int stages) { return (int)(kLdsLimit / (stages * (bm + bn) * kRowBytes)) * waves / 4; }
-template <typename T, int BM, int BN, int MODE, int WM = 2, int WN = 2, int NSTAGE = 3, int KG = 1>
+template <typename T, int BM, int BN, int MODE, int WM = 2, int WN = 2, int NSTAGE = 3, int KG = 1, bool XTRA = false>
 __global__ __launch_bounds__(64 * WM * WN * KG, p3_waves_per_simd(BM, BN, WM * WN, NSTAGE)) void k_igemm_p3(IgemmParams p) {
   typedef typename Vec<T>::type V;
   constexpr int NW = WM * WN;
@@ -615,8 +618,8 @@ __global__ __launch_bounds__(64 * WM * WN * KG, p3_waves_per_simd(BM, BN, WM * W
   const int m0 = tid3.m_tile * BM, n0 = tid3.n_tile * BN;
   // all 64 columns of this wavefront are padding: it takes part in the tile loads and the barriers and skips the rest
   const bool idle = n0 + wave_n * WTN >= p.N;
-  const u32x4 rs0 = make_rsrc_words(p.src0, p.bytes0), rs1 = make_rsrc_words(p.src1, p.bytes1);
-  const u32x4 rsw = make_rsrc_words(p.w, p.bytes_w);
+  u32x4 rs0 = make_rsrc_words(p.src0, p.bytes0), rs1 = make_rsrc_words(p.src1, p.bytes1);
+  u32x4 rsw = make_rsrc_words(p.w, p.bytes_w);
 
   // load i of a k-tile covers rows (NW i + wave) * 8 .. + 7 of the A tile (i < AG) or of the B tile
   const int r8 = lane >> 3, scol = (lane & 7) ^ (((wave * 8 + r8) >> 1) & 7);      // see lds_swizzle(); rows (NW i + wave) * 8 + r8
@@ -627,7 +630,7 @@ __global__ __launch_bounds__(64 * WM * WN * KG, p3_waves_per_simd(BM, BN, WM * W
   const unsigned grp = (unsigned)wave * 8 * kRowBytes;
   // load i of the weights is RND rows after load 0; large tiles form its offset anew each time, for want of registers
   constexpr bool TIGHT = TM * TN * 16 > 128;
-  const unsigned b_row0 = (unsigned)((n0 + wave * 8 + r8) * p.Kp + scol * VN) * ES, b_step = (unsigned)(RND * p.Kp) * ES;
+  unsigned b_row0 = (unsigned)((n0 + wave * 8 + r8) * p.Kp + scol * VN) * ES, b_step = (unsigned)(RND * p.Kp) * ES;
   unsigned b_off[TIGHT ? 1 : BG];
   if constexpr (!TIGHT) {
 #pragma unroll
@@ -647,8 +650,15 @@ __global__ __launch_bounds__(64 * WM * WN * KG, p3_waves_per_simd(BM, BN, WM * W
   for (int t = 0; t < NSTAGE - 1; ++t)
     if (t < nkt) {
 #pragma unroll
-      for (int i = 0; i < BG; ++i)
-        dma_load16(rsw, b_at(i), (unsigned)((kt_begin + t) * BK * ES), lds_base + t * STAGE + grp + (BM + i * RND) * kRowBytes);
+      for (int i = 0; i < BG; ++i) {
+        if (XTRA && kt_begin + t >= p.kt_main) {
+          const int xk = p.xc0 + p.xc1;
+          dma_load16(make_rsrc_words(p.xw, p.xbytes_w), (unsigned)((n0 + wave * 8 + r8 + i * RND) * xk + scol * VN) * ES,
+                     (unsigned)((kt_begin + t - p.kt_main) * BK * ES), lds_base + t * STAGE + grp + (BM + i * RND) * kRowBytes);
+        } else {
+          dma_load16(rsw, b_at(i), (unsigned)((kt_begin + t) * BK * ES), lds_base + t * STAGE + grp + (BM + i * RND) * kRowBytes);
+        }
+      }
     }
   if (PRE && p.residual && p.vec16 && !idle && group == 0) {
 #pragma unroll
@@ -691,15 +701,34 @@ __global__ __launch_bounds__(64 * WM * WN * KG, p3_waves_per_simd(BM, BN, WM * W
   int f_k0 = kt_begin * BK;
   int f_tap = __builtin_amdgcn_readfirstlane(f_k0 / p.ctot);    // the division is vector work; what follows from it must not be
   int f_cc = f_k0 - f_tap * p.ctot;
-  const unsigned c0 = (unsigned)p.c0, c1 = (unsigned)p.c1;
-  set_tap(f_tap, f_cc >= p.c0 ? c1 : c0);
+  unsigned c0 = (unsigned)p.c0, c1 = (unsigned)p.c1;
+  int s_c0 = p.c0, s_ctot = p.ctot;                          // channels of the first source and of both
+  // XTRA: behind the nine taps other sources and weights take over, k counted anew; their pixel is the one of the middle tap
+  auto begin_extra = [&]() {
+    rs0 = make_rsrc_words(p.x0, p.xbytes0); rs1 = make_rsrc_words(p.x1, p.xbytes1); rsw = make_rsrc_words(p.xw, p.xbytes_w);
+    c0 = (unsigned)p.xc0; c1 = (unsigned)p.xc1;
+    s_c0 = p.xc0; s_ctot = p.xc0 + p.xc1;
+    b_row0 = (unsigned)((n0 + wave * 8 + r8) * s_ctot + scol * VN) * ES;
+    b_step = (unsigned)(RND * s_ctot) * ES;
+    if constexpr (!TIGHT) {
+#pragma unroll
+      for (int i = 0; i < BG; ++i) b_off[i] = b_row0 + i * b_step;
+    }
+  };
+  auto pixel_tap = [&](int tap) { return XTRA && tap >= 9 ? 4 : tap; };
+  if (XTRA && kt_begin >= p.kt_main) {
+    begin_extra();
+    f_k0 = f_cc = (kt_begin - p.kt_main) * BK;
+    f_tap = 9;
+  }
+  set_tap(pixel_tap(f_tap), f_cc >= s_c0 ? c1 : c0);
   // per-tile state of the loads being issued: the source that holds the channels, and the scalar offsets
   u32x4 rsa = rs0;
   unsigned soff_a = 0, soff_b = 0;
   auto begin_tile = [&]() {
-    const bool second = f_cc >= p.c0;
+    const bool second = f_cc >= s_c0;
     rsa = second ? rs1 : rs0;
-    soff_a = (unsigned)((second ? f_cc - p.c0 : f_cc) * ES);
+    soff_a = (unsigned)((second ? f_cc - s_c0 : f_cc) * ES);
     soff_b = (unsigned)(f_k0 * ES);
   };
   auto issue_one = [&](int stage, int i) {
@@ -710,11 +739,12 @@ __global__ __launch_bounds__(64 * WM * WN * KG, p3_waves_per_simd(BM, BN, WM * W
   auto end_tile = [&]() {
     f_k0 += BK;
     f_cc += BK;
-    if (f_cc == p.c0 || f_cc == p.ctot) {                    // the next source (c0 and ctot are multiples of the k-tile) or the next tap
-      const int wrap = f_cc == p.ctot ? 1 : 0;
+    if (f_cc == s_c0 || f_cc == s_ctot) {                    // the next source (c0 and ctot are multiples of the k-tile) or the next tap
+      const int wrap = f_cc == s_ctot ? 1 : 0;
       f_cc = wrap ? 0 : f_cc;
       f_tap += wrap;
-      set_tap(f_tap, wrap ? c0 : c1);                        // behind the last tap nothing is fetched any more
+      if (XTRA && wrap && f_tap == 9) { begin_extra(); f_k0 = 0; }
+      set_tap(pixel_tap(f_tap), wrap ? c0 : c1);             // behind the last tap nothing is fetched any more
     }
   };
 
@@ -839,8 +869,11 @@ __global__ __launch_bounds__(64 * WM * WN * KG, p3_waves_per_simd(BM, BN, WM * W
                                                          (float*)(lds + NW * stage_bytes<T, WTM, WTN>(CR)) + wave_m * (WTM * 32));
 }
 
-template <typename T, int BM, int BN, int MODE, int WM = 2, int WN = 2, int NSTAGE = 3, int KG = 1>
+template <typename T, int BM, int BN, int MODE, int WM = 2, int WN = 2, int NSTAGE = 3, int KG = 1, bool XTRA = false>
 static ad_status run_igemm_p3(const IgemmParams& p0, const char* name, hipStream_t s) {
+  if constexpr (!XTRA && (MODE == OUT_ROWMAJOR || MODE == OUT_PARTIAL) && !(BM <= 256 && BN == 128 && NSTAGE == 3 && WM * WN != 8))
+    if (p0.xw) return run_igemm_p3<T, BM, BN, MODE, WM, WN, NSTAGE, KG, true>(p0, name, s);
+  if (!XTRA && p0.xw) AD_FAIL(AD_ERR_INVALID, "conv: this tile does not take a shortcut");
   IgemmParams p = p0;
   set_tiles(p, BM, BN);
   constexpr int lds_bytes = KG * NSTAGE * (BM + BN) * kRowBytes;
@@ -848,14 +881,15 @@ static ad_status run_igemm_p3(const IgemmParams& p0, const char* name, hipStream
   static_assert(MODE != OUT_GEGLU || BN / WN / 32 % 2 == 0 || lds_bytes >= WM * WN * stage_bytes<T, BM / WM, BN / WN>(32) + BM * 128, "so does the exchange");
   static std::atomic<bool> attr_set{false};
   if (!attr_set) {
-    AD_HIP(hipFuncSetAttribute((const void*)k_igemm_p3<T, BM, BN, MODE, WM, WN, NSTAGE, KG>, hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes));
+    AD_HIP(hipFuncSetAttribute((const void*)k_igemm_p3<T, BM, BN, MODE, WM, WN, NSTAGE, KG, XTRA>, hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes));
     attr_set = true;
   }
-  const double in_bytes = (double)p.M * p.ctot * sizeof(T) * (p.stride == 2 ? 4 : 1) / (p.up ? 4 : 1);
+  const int xk = p.xc0 + p.xc1;
+  const double in_bytes = (double)p.M * (p.ctot + xk) * sizeof(T) * (p.stride == 2 ? 4 : 1) / (p.up ? 4 : 1);
   const double out_cols = p.out_mode == OUT_GEGLU ? p.N / 2 : p.N;
-  ProfLaunch pl(name, 2.0 * p.M * p.N * p.k_prof, in_bytes + (double)p.N * p.Kp * sizeof(T) + (double)p.M * out_cols * sizeof(T), s, p.M, p.N, p.Kp);
+  ProfLaunch pl(name, 2.0 * p.M * p.N * (p.k_prof + xk), in_bytes + (double)p.N * (p.Kp + xk) * sizeof(T) + (double)p.M * out_cols * sizeof(T), s, p.M, p.N, p.Kp + xk);
   const int splits = (p.ktiles + p.kt_per_split - 1) / p.kt_per_split;
-  hipLaunchKernelGGL((k_igemm_p3<T, BM, BN, MODE, WM, WN, NSTAGE, KG>), dim3(p.tiles_n * p.tiles_m, splits), dim3(64 * WM * WN * KG), lds_bytes, s, p);
+  hipLaunchKernelGGL((k_igemm_p3<T, BM, BN, MODE, WM, WN, NSTAGE, KG, XTRA>), dim3(p.tiles_n * p.tiles_m, splits), dim3(64 * WM * WN * KG), lds_bytes, s, p);
   AD_HIP(hipGetLastError());
   return AD_OK;
 }
@@ -1524,6 +1558,19 @@ size_t conv_workspace_bytes(int dtype, long long m, int n, int k, int out_mode) 
   return splits > 1 ? (size_t)splits * m * n * 4 : 0;
 }
 
+// A 1x1 convolution of the block's input (the shortcut) added to the 3x3 one: as further k-tiles of the same launch on the LDS-DMA kernels, a
+// launch of its own, whose sum goes through memory as the residual, on the others.  Saves a launch of 7 to 25 us per such block (14 of 22
+// blocks of the SD-sized models) for as many k-tiles at the rate of a long launch: whole runs at 576x320 px 67.5 -> 66.2 ms, 512px 191.4 -> 188.3,
+// 768px 299.1 -> 297.5, 1024px level.
+bool conv_takes_shortcut(int dtype, long long m, int n, int c, int xc) {
+  if (dtype != AD_BF16 || c % bk_elems(dtype) || xc % bk_elems(dtype)) return false;
+  switch (choose_plan(dtype, m, n, (9 * c + xc) / bk_elems(dtype), OUT_ROWMAJOR).tile) {
+    case TILE_P3_64: case TILE_K2_64: case TILE_D2_128: case TILE_D2_160: case TILE_D2_320: return true;
+    case TILE_P3_128: case TILE_P3_256: return g_tile_override == TILE_AUTO || g_tile_override == TILE_P3_128 || g_tile_override == TILE_P3_256;
+    default: return false;
+  }
+}
+
 ad_status launch_conv(const ConvArgs& a, hipStream_t s) {
   if (a.dtype != AD_F32 && a.dtype != AD_BF16) AD_FAIL(AD_ERR_INVALID, "conv: bad dtype");
   const int bk = bk_elems(a.dtype);
@@ -1547,7 +1594,20 @@ ad_status launch_conv(const ConvArgs& a, hipStream_t s) {
   if (m > 0x7fffffffLL / 4) AD_FAIL(AD_ERR_INVALID, "conv: too many output positions");
   p.M = (int)m; p.N = a.n_out;
   p.Kp = a.ksize * a.ksize * p.ctot;      // a multiple of the k-tile because ctot is
-  p.ktiles = p.Kp / bk;
+  p.kt_main = p.Kp / bk;
+  p.xw = a.xw; p.x0 = a.x0; p.x1 = a.xc1 ? a.x1 : a.x0; p.xc0 = a.xw ? a.xc0 : 0; p.xc1 = a.xw ? a.xc1 : 0;
+  p.xbytes0 = p.xbytes1 = p.xbytes_w = 0;
+  if (a.xw) {
+    if (a.ksize != 3 || a.stride != 1 || a.up || a.c1 || a.residual || a.out_mode != OUT_ROWMAJOR || !a.x0 || a.xc0 < bk || a.xc0 % bk || a.xc1 < 0 ||
+        a.xc1 % bk || (a.xc1 > 0 && !a.x1) || !conv_takes_shortcut(a.dtype, m, a.n_out, a.c0, a.xc0 + a.xc1))
+      AD_FAIL(AD_ERR_INVALID, "conv: bad shortcut");
+    const long long pixels = (long long)a.batch * a.hs * a.ws, es = (long long)esize(a.dtype), wb = (long long)round_up(a.n_out, kNPad) * (a.xc0 + a.xc1) * es;
+    if (pixels * std::max(a.xc0, a.xc1) * es >= 0x7fffffffLL || wb >= 0x7fffffffLL) AD_FAIL(AD_ERR_INVALID, "conv: operands of 2 GiB or more are not supported");
+    p.xbytes0 = (unsigned)(pixels * a.xc0 * es);
+    p.xbytes1 = a.xc1 ? (unsigned)(pixels * a.xc1 * es) : p.xbytes0;
+    p.xbytes_w = (unsigned)wb;
+  }
+  p.ktiles = p.kt_main + (p.xc0 + p.xc1) / bk;
   p.k_prof = a.k_real > 0 ? a.k_real : p.Kp;
   p.w = a.w; p.bias = a.bias; p.rowvec = a.rowvec; p.residual = a.residual;
   p.out = a.out; p.out_mode = a.out_mode; p.ld_t = a.ld_t; p.rowvec_ld = a.rowvec_ld > 0 ? a.rowvec_ld : (a.rowvec_ld < 0 ? 0 : a.n_out);

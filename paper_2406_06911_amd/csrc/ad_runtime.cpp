@@ -95,6 +95,13 @@ struct Eval {
     AD_TRY(conv(temp(0), nullptr, ci, 0, f.h_in, f.w_in, 0, 3, 1, w0 + 2, w0 + 3, rowvec, nullptr, temp(1)));
     AD_TRY(gn(temp(1), nullptr, f.c_out, 0, hw, w0 + 6, 1, temp(0)));
     const void* shortcut = x0;
+    if (ci != f.c_out && conv_takes_shortcut(dt, (long long)c.cfg.batch * hw, f.c_out, f.c_out, ci)) {
+      WView wv{c};                      // the shortcut's bias goes in as a row vector that all samples share
+      ConvArgs a{dt, temp(0), nullptr, f.c_out, 0, c.cfg.batch, f.h_in, f.w_in, 0, 3, 1, wv.at(w0 + 8), f.c_out, wv.f32(w0 + 9), wv.f32(w0 + 11), -1,
+                 nullptr, tensor_out(ui), OUT_ROWMAJOR, 0, temp(9), ws.temp_bytes[9]};
+      a.x0 = x0; a.x1 = x1; a.xc0 = f.c_in; a.xc1 = f.c_skip; a.xw = wv.at(w0 + 10);
+      return launch_conv(a, s);
+    }
     if (ci != f.c_out) {
       AD_TRY(conv(x0, x1, f.c_in, f.c_skip, f.h_in, f.w_in, 0, 1, 1, w0 + 10, w0 + 11, nullptr, nullptr, temp(2)));
       shortcut = temp(2);
