@@ -2557,6 +2557,8 @@ static int attn_auto_variant(int bh, int l, int lk) {
   // the deepest level) its longer prologue loses, and 64 queries per wavefront (two wavefronts per SIMD) never won.
   // The pipelined variant (3) is 4-10 % faster launched alone and 1 % slower inside the concurrent schedule (its 64 KiB of
   // LDS and two wavefronts per SIMD leave less room for the other streams' workgroups), so it stays a selectable variant.
+  // Up to 512 workgroups, where no CU gets a third one anyway, it is 6-12 % faster alone (two samples, 4096 tokens, 5 heads 70.6 -> 62.8 us,
+  // 2304, 10 heads 45.3 -> 41.3) and whole runs of two and four components are level.
   (void)bh; (void)l;
   return lk > 256 ? 1 : 0;
 }
@@ -3012,12 +3014,12 @@ __global__ __launch_bounds__(NT) void k_gn_apply(const T* __restrict__ src0, con
 // Neighbouring groups share cache lines: xcd_remap puts them on one XCD.  Bound by one round trip to memory and the launch.
 template <typename T, int G, int NT, int NV>
 __global__ __launch_bounds__(NT) void k_gn_group(const T* __restrict__ src0, const T* __restrict__ src1, int c0, int c1, int hw,
-                                                 int groups, int pl, double inv_n, const float* __restrict__ gamma,
+                                                 int groups, int pl, int log_parts, double inv_n, const float* __restrict__ gamma,
                                                  const float* __restrict__ beta, float eps, int silu, T* __restrict__ out) {
   typedef T V __attribute__((ext_vector_type(G)));
   __shared__ float red[3][NT / 64];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int vid = xcd_remap(blockIdx.x, gridDim.x);
+  const int wg = xcd_remap(blockIdx.x, gridDim.x), vid = wg >> log_parts, mask = (1 << log_parts) - 1, part = wg & mask;
   const int b = vid / groups, g = vid - b * groups;
   const int ctot = c0 + c1, cpg = ctot / groups, vpp = cpg / G;
   const int lanep = tid / vpp, c = g * cpg + (tid - lanep * vpp) * G;
@@ -3074,7 +3076,7 @@ __global__ __launch_bounds__(NT) void k_gn_group(const T* __restrict__ src0, con
 #pragma unroll
   for (int k = 0; k < NV; ++k) {
     const int p = lanep + k * pl;
-    if (p < p_end) {
+    if ((k & mask) == part && p < p_end) {
       V o;
 #pragma unroll
       for (int e = 0; e < G; ++e) {
@@ -3097,16 +3099,30 @@ extern "C" size_t ad_groupnorm_scratch_bytes(int batch, int hw, int c) {
 
 namespace ad {
 
+constexpr long long kGnPartElements = 2048;
 template <typename T, int NT, int REGS>
 static ad_status launch_gn_group(const void* src0, const void* src1, int c0, int c1, int batch, int hw, int groups, int ga,
                                  const float* gamma, const float* beta, float eps, int silu, void* out, hipStream_t s) {
   const int ctot = c0 + c1, pl = NT / (ctot / groups / ga);
   constexpr int VN = Vec<T>::N;
   ProfLaunch prof("gn_group", 0, 2.0 * batch * hw * ctot * sizeof(T), s, batch * hw, ctot, 0);
-  const dim3 grid(groups * batch);
+  // The groups of a single sample are 32 workgroups that spend half their time on the result, 14 vector instructions an element against 6 of the
+  // sums: up to four take all of a group in and write a part of it each, as long as that is a few thousand elements.  One sample, us: 2880 pixels
+  // of 320 channels 15.7 -> 12.6, 720 of 640 6.2 -> 5.6, 720 of 1280 10.8 -> 9.2; the 576x320 px run 66.1 -> 64.9 ms.  Two samples' groups gain
+  // 5-10 % alone as well (2304 of 640 13.8 -> 12.7), but take the CUs that other streams use: 768px runs 0.7 % slower.  In place, a group belongs to
+  // one workgroup.
+  const long long elements = (long long)hw * (ctot / groups), rows = (long long)batch * hw;
+  auto apart = [&](const void* src, int c) {
+    const char *a = (const char*)src, *o = (const char*)out;
+    return c == 0 || a + rows * c * sizeof(T) <= o || o + rows * ctot * sizeof(T) <= a;
+  };
+  const bool shared = groups * batch <= 32 && apart(src0, c0) && apart(src1, c1);
+  int log_parts = 0;
+  while (shared && log_parts < 2 && elements >> (log_parts + 1) >= kGnPartElements) ++log_parts;
+  const dim3 grid((groups * batch) << log_parts);
   const double inv_n = 1.0 / ((double)hw * (ctot / groups));
 #define AD_GN(G_) hipLaunchKernelGGL((k_gn_group<T, G_, NT, REGS * 4 / (G_ * (int)sizeof(T))>), grid, dim3(NT), 0, s, (const T*)src0, (const T*)src1, \
-                                     c0, c1, hw, groups, pl, inv_n, gamma, beta, eps, silu, (T*)out)
+                                     c0, c1, hw, groups, pl, log_parts, inv_n, gamma, beta, eps, silu, (T*)out)
   if (ga == VN) AD_GN(VN);
   else if (ga == VN / 2) AD_GN(VN / 2);
   else AD_GN(VN / 4);
