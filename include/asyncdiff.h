@@ -305,8 +305,9 @@ ad_status ad_conv_forward(int dtype, const void* src0, const void* src1, int c0,
 ad_status ad_tune_conv_tile(int tile);
 /* Tuning knob for measurements: order in which the workgroups of a GEMM walk its output tiles.  0: an XCD owns a
  * run of row tiles and every column tile of them (the weights are fetched into every L2); 1: an XCD owns a run of
- * column tiles (the activations are fetched into every L2); -1: automatic, the default (the smaller operand is
- * the one fetched everywhere).  Results are bit-identical. */
+ * column tiles (the activations are fetched into every L2); -1: automatic, the default (blocks of row and column
+ * tiles that take in the fewest rows and columns; kernels without such a plan fetch the smaller operand everywhere).
+ * Results are bit-identical. */
 ad_status ad_tune_conv_order(int order);
 /* Tuning knob for measurements and tests (process-global, not thread-safe): which MFMA attention kernel serves bf16,
  * head_dim 64, transposed v.  0: 32 queries per wavefront, register-staged tiles; 1 / 2: tiles filled by the load
