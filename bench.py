@@ -32,7 +32,7 @@ MEASURED_TRAFFIC = {"sd21_768": {
     "igemm_bf16_64x64_p3_splitk": 28573696, "igemm_bf16_small": 4582716}}
 
 
-TRAFFIC_SOURCE = "not measured in this run: FETCH_SIZE + WRITE_SIZE of two rocprofv3 --pmc runs of this file, profiles/bench_sd21_768_all_kernels.md"
+TRAFFIC_SOURCE = "not measured in this run: FETCH_SIZE + WRITE_SIZE of two rocprofv3 --pmc runs of this file, profiles/bench_sd21_768_all_kernels.md (kernels of commit 6fb9f3c, whose workgroups did not yet walk blocks of tiles)"
 
 
 def log(*a):
