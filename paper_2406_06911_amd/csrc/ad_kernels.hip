@@ -3426,10 +3426,10 @@ __global__ __launch_bounds__(256) void k_time_first(float tau, StepRef ref, int 
 }
 
 // The whole time embedding of a component in one launch: sinusoid, two layers, pooled branch, projections of its ResBlocks.  Every workgroup
-// computes the embedding for itself and a share of the projections, which pays as long as the second layer (td x td) is at most
-// kTimeFusedBytes; a launch of the four or six it replaces takes 3.7 us inside a replayed graph.  Two threads a feature in the layers, eight in the
-// projections; rows of weights are read 16 bytes at a time, all loads of a row in flight.
-constexpr int kTimeFusedBytes = 256 * 1024, kTimeRows = 64;
+// computes the embedding for itself and a share of the projections: it takes in the weights of all layers, those of the pooled branch once a
+// sample (see time_fused_fits()); a launch of the four or six it replaces takes 3.7 us inside a replayed graph.  Two threads a feature in the
+// layers, eight in the projections; rows of weights are read 16 bytes at a time, four loads of a thread in flight.  Bound by that chain.
+constexpr int kTimeFusedLayer = 256 * 1024, kTimeRows = 64;
 struct TimeParams {
   const void *w1, *w2, *w3, *w4, *wp; const float *b1, *b2, *b3, *b4, *bp;
   const float* pooled;                  // [batch][pooled_dim], or null
@@ -3520,8 +3520,15 @@ ad_status launch_time_first(int dtype, float tau, StepRef ref, int dim, const vo
 static size_t time_fused_lds(const TimeArgs& a) {
   return ((size_t)std::max(a.c0, a.batch * a.td) + a.td + (a.pooled ? (size_t)a.batch * a.td : 0)) * 4;
 }
+// One launch as long as the second layer (td x td) is at most kTimeFusedLayer and what a workgroup takes in costs less than the launches.  A
+// ResBlock of 4x4 positions behind it, us, layer by layer / one launch: bf16, no pooled branch (160 KiB) 21.9 / 19.8, with it, one sample 352 KiB
+// 27.5 / 23.9, 480 KiB 27.4 / 27.4, 640 KiB 28.1 / 31.8, 1.2 MiB 28.5 / 39.7, two samples 544 KiB 31.0 / 29.1, 640 KiB 30.9 / 30.5, 672 KiB 30.8 / 32.5,
+// 3.2 MiB 34.7 / 101; fp32, half the arithmetic a byte: 320 KiB 23.8 / 23.7, one sample 584 KiB 29.6 / 27.8, 704 KiB 29.8 / 30.5, two samples 464 KiB
+// 30.3 / 25.9, 720 KiB 30.9 / 31.3, 1088 KiB 32.6 / 37.9.
 bool time_fused_fits(const TimeArgs& a) {
-  return (size_t)a.td * a.td * esize(a.dtype) <= (size_t)kTimeFusedBytes && a.rows > 0 && time_fused_lds(a) <= 64 * 1024;
+  const size_t es = esize(a.dtype), td = (size_t)a.td, pooled = a.pooled ? (size_t)a.batch * (a.pooled_dim + td) : 0;
+  const size_t limit = (320 + 160 * (size_t)a.batch) * (a.dtype == AD_F32 ? 1280 : 1024);
+  return td * td * es <= (size_t)kTimeFusedLayer && td * (a.c0 + td + pooled) * es <= limit && a.rows > 0 && time_fused_lds(a) <= 64 * 1024;
 }
 
 ad_status launch_time_fused(const TimeArgs& a, hipStream_t s) {

@@ -45,11 +45,26 @@ def test_transformer_of_a_narrow_model_matches_oracle(monkeypatch, dtype, c, hea
 @pytest.mark.parametrize("dtype,c,batch,pooled,frames", [(F32, 32, 1, 0, 0), (F32, 64, 2, 8, 0), (BF, 64, 2, 128, 0), (BF, 64, 5, 0, 5), (BF, 128, 2, 16, 0),
                                                          (F32, 96, 1, 0, 0), (BF, 192, 2, 0, 0)])
 def test_time_embedding_reaches_the_residual_blocks(monkeypatch, dtype, c, batch, pooled, frames):
-    """Both ways of the time embedding: in one launch (up to 256 features in fp32, 362 in bf16) and layer by layer, with and without the pooled
-    branch, at several timesteps (the ResBlock's output depends on them through the projection, whose weights are large here)."""
+    """Both ways of the time embedding: in one launch (up to 256 features in fp32, 362 in bf16, and few pooled ones) and layer by layer, with and without the
+    pooled branch, at several timesteps (the ResBlock's output depends on them through the projection, whose weights are large here)."""
     d = dict(latent_channels=4, height=4, width=4, batch=batch, channels=[c], layers_per_block=1, transformer_depth=[0], mid_depth=0, head_dim=32,
              gn_groups=8, ctx_len=8, ctx_dim=64, pooled_dim=pooled, frames=frames, temporal_heads=4 if frames else 0)
     monkeypatch.setitem(CONFIGS, "temb", d)
     case = Case("temb", dtype, 2, 1, 1, 4, std=2 * c ** -0.5, cuts=[1])
     # 1e-4 / 2e-2: the budget of a component, asserted inside
     run_components_isolated(case)
+
+
+@pytest.mark.parametrize("dtype,c,batch,pooled,fused", [(BF, 64, 1, 0, True), (BF, 64, 1, 384, True), (BF, 64, 1, 392, False), (BF, 64, 2, 224, True), (BF, 64, 2, 232, False),
+                                                        (F32, 64, 1, 24, True), (F32, 64, 1, 32, False), (F32, 64, 2, 8, False), (F32, 32, 2, 592, True), (F32, 32, 2, 600, False)])
+def test_time_embedding_in_one_launch_up_to_the_weights_a_workgroup_takes_in(monkeypatch, dtype, c, batch, pooled, fused):
+    """The one launch reads the pooled branch's weights once a sample in every workgroup: around the line, which way is taken, and the result."""
+    d = dict(latent_channels=4, height=4, width=4, batch=batch, channels=[c], layers_per_block=1, transformer_depth=[0], mid_depth=0, head_dim=32,
+             gn_groups=8, ctx_len=8, ctx_dim=64, pooled_dim=pooled)
+    monkeypatch.setitem(CONFIGS, "temb", d)
+    # (the pooled branch's inputs grow with pooled_dim; weights that keep the embedding of unit size)
+    case = Case("temb", dtype, 2, 1, 1, 2, std=(c + 4 * c + pooled) ** -0.5, cuts=[1])
+    case.m.profile(True)
+    run_components_isolated(case)
+    names = {r[0] for r in case.m.profile_records()}
+    assert ("time_fused" in names) == fused and ("linear_rows" in names) == (not fused), names
