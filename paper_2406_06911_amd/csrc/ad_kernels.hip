@@ -3390,37 +3390,44 @@ ad_status launch_linear_rows(int dtype, const float* in, int in_ld, int rows, in
   return AD_OK;
 }
 
-// Sinusoidal timestep embedding [cos | sin], evaluated in double because tau * f reaches ~1e3 rad; by the threads of a workgroup.
-__device__ __forceinline__ void sinusoid(float tau, int dim, float* out) {
+// Sinusoidal timestep embedding [cos | sin], evaluated in double because tau * f reaches ~1e3 rad; by the threads of a workgroup.  Frequencies
+// from .. from + count - 1 of dim / 2: out is the cosines, then the sines.
+__device__ __forceinline__ void sinusoid(float tau, int dim, int from, int count, float* out) {
   const int half = dim / 2;
-  for (int k = threadIdx.x; k < half; k += blockDim.x) {
-    const double a = (double)tau * exp(-9.210340371976184 * (double)k / (double)half);   // ln(10^4)
+  for (int k = threadIdx.x; k < count; k += blockDim.x) {
+    const double a = (double)tau * exp(-9.210340371976184 * (double)(from + k) / (double)half);   // ln(10^4)
     double s, c;
     sincos(a, &s, &c);
     out[k] = (float)c;
-    out[half + k] = (float)s;
+    out[count + k] = (float)s;
   }
 }
 
 // First layer of the time embedding: out[n] = SiLU(bias[n] + w[n] . sinusoid), one wavefront per feature; every workgroup evaluates the
-// sinusoid for itself (1.5 us more than the layer alone; a launch for it 3.4).
+// sinusoid for itself (1.5 us more than the layer alone; a launch for it 3.4), kTimePiece frequencies at a time.
+constexpr int kTimePiece = 512;
 template <typename T>
 __global__ __launch_bounds__(256) void k_time_first(float tau, StepRef ref, int dim, const T* __restrict__ w, const float* __restrict__ bias, int n,
                                                     float* __restrict__ out) {
   typedef typename Vec<T>::type V;
   constexpr int VN = Vec<T>::N;
-  extern __shared__ __attribute__((aligned(16))) float s[];
-  const int lane = threadIdx.x & 63, col = blockIdx.x * 4 + (threadIdx.x >> 6);
+  __shared__ __attribute__((aligned(16))) float s[2 * kTimePiece];
+  const int lane = threadIdx.x & 63, col = blockIdx.x * 4 + (threadIdx.x >> 6), half = dim / 2;
   if (ref.table) tau = ref.table[*ref.counter + ref.offset].tau;
-  sinusoid(tau, dim, s);
-  __syncthreads();
-  if (col >= n) return;
+  const T* const row = w + (size_t)min(col, n - 1) * dim;
   float acc = 0.f;
-  for (int v = lane; v < dim / VN; v += 64) {
-    const V wv = *(const V*)(w + (size_t)col * dim + v * VN);
+  for (int from = 0; from < half; from += kTimePiece) {
+    const int count = min(kTimePiece, half - from);
+    if (from > 0) __syncthreads();                           // the last piece has been read
+    sinusoid(tau, dim, from, count, s);
+    __syncthreads();
+    for (int i = lane * VN; i < 2 * count; i += 64 * VN) {   // (VN divides count: no access spans cosines and sines)
+      const V wv = *(const V*)(row + from + (i < count ? i : half - count + i));
 #pragma unroll
-    for (int e = 0; e < VN; ++e) acc += s[v * VN + e] * to_f(wv[e]);
+      for (int e = 0; e < VN; ++e) acc += s[i + e] * to_f(wv[e]);
+    }
   }
+  if (col >= n) return;
   const float t = wave_sum_rows(acc) + bias[col];
   if (lane == 0) out[col] = silu_f(t);
 }
@@ -3460,7 +3467,7 @@ __global__ __launch_bounds__(512) void k_time_fused(TimeParams p) {
   };
   float tau = p.tau;
   if (p.ref.table) tau = p.ref.table[*p.ref.counter + p.ref.offset].tau;
-  sinusoid(tau, p.c0, s);
+  sinusoid(tau, p.c0, 0, p.c0 / 2, s);
   __syncthreads();
   const int part = tid & 1;
   for (int n = tid >> 1; n < p.td; n += 256) {
@@ -3508,10 +3515,10 @@ ad_status launch_advance(int* counter, int by, hipStream_t s, int* other) {
 
 ad_status launch_time_first(int dtype, float tau, StepRef ref, int dim, const void* w, const float* bias, int n, float* out, hipStream_t s) {
   const int vn = dtype == AD_BF16 ? 8 : 4;
-  if (!w || !bias || !out || dim < 2 || dim % vn || dim > 16384 || n < 1) AD_FAIL(AD_ERR_INVALID, "time_first: bad argument");
+  if (!w || !bias || !out || dim < 2 || dim % (2 * vn) || n < 1) AD_FAIL(AD_ERR_INVALID, "time_first: bad argument");
   ProfLaunch pl("linear_rows", 2.0 * n * dim, (double)n * dim * (dtype == AD_BF16 ? 2 : 4), s);
-  if (dtype == AD_BF16) hipLaunchKernelGGL(k_time_first<bf16>, dim3((n + 3) / 4), dim3(256), dim * 4, s, tau, ref, dim, (const bf16*)w, bias, n, out);
-  else if (dtype == AD_F32) hipLaunchKernelGGL(k_time_first<float>, dim3((n + 3) / 4), dim3(256), dim * 4, s, tau, ref, dim, (const float*)w, bias, n, out);
+  if (dtype == AD_BF16) hipLaunchKernelGGL(k_time_first<bf16>, dim3((n + 3) / 4), dim3(256), 0, s, tau, ref, dim, (const bf16*)w, bias, n, out);
+  else if (dtype == AD_F32) hipLaunchKernelGGL(k_time_first<float>, dim3((n + 3) / 4), dim3(256), 0, s, tau, ref, dim, (const float*)w, bias, n, out);
   else AD_FAIL(AD_ERR_INVALID, "time_first: bad dtype");
   AD_HIP(hipGetLastError());
   return AD_OK;

@@ -1,11 +1,15 @@
 """The row-local transformer kernel of narrow models (k_tfm_rows) against the oracle's transformer block, at the sizes where it can go
 wrong: token counts around its tiles of 16 and 32, key counts around its blocks, one and several layers, shared text, every head width."""
+import ctypes as C
+
 import numpy as np
 import pytest
 import torch
 
+import synthetic_inputs as SI
 from configs import CONFIGS
-from gpu_util import dev, host, nchw_to_nhwc, nhwc_to_nchw, rel_l2
+from gpu_util import DEV, assert_kernel_close, dev, dev_f32, host, nchw_to_nhwc, nhwc_to_nchw, p, quantize, rel_l2, stream_ptr
+from oracle import primitives as P
 from paper_2406_06911_amd import binding as B
 from test_gpu_pipeline import Case, run_components_isolated
 
@@ -68,3 +72,20 @@ def test_time_embedding_in_one_launch_up_to_the_weights_a_workgroup_takes_in(mon
     run_components_isolated(case)
     names = {r[0] for r in case.m.profile_records()}
     assert ("time_fused" in names) == fused and ("linear_rows" in names) == (not fused), names
+
+
+class StepRef(C.Structure):
+    _fields_ = [("table", C.c_void_p), ("counter", C.c_void_p), ("offset", C.c_int)]
+
+
+@pytest.mark.parametrize("dtype,dim,n", [(BF, 64, 1), (BF, 1024, 7), (BF, 1088, 6), (BF, 16384, 5), (BF, 16448, 5), (F32, 32, 3), (F32, 1056, 4), (F32, 33056, 9)])
+def test_first_layer_of_the_time_embedding_at_any_width(dtype, dim, n):
+    """The layer by itself (a whole model of the widest of these has gigabytes of weights): one and several pieces of the sinusoid, a short last one."""
+    launch = getattr(B.lib, "_ZN2ad17launch_time_firstEifNS_7StepRefEiPKvPKfiPfP12ihipStream_t")       # ad::launch_time_first
+    launch.argtypes = [C.c_int, C.c_float, StepRef, C.c_int, C.c_void_p, C.c_void_p, C.c_int, C.c_void_p, C.c_void_p]
+    w, bias = quantize(SI.make_array((n, dim), 401, dim ** -0.5), dtype), SI.make_array((n,), 402)
+    dw, db, out = dev(w, dtype), dev_f32(bias), torch.full((n,), float("nan"), device=DEV)
+    for tau in (0, 999):
+        B.check(launch(dtype, float(tau), StepRef(None, None, 0), dim, p(dw), p(db), n, p(out), stream_ptr()))
+        torch.cuda.synchronize()
+        assert_kernel_close(host(out), P.silu(P.linear(P.timestep_embedding(tau, dim), w, bias)), F32)
