@@ -310,7 +310,7 @@ static void build_manifest(Ctx& c) {
           add_w(c, p + ".o.w", W_CONV1, {C, C}); add_w(c, p + ".o.b", W_VEC_F32, {C});
         }
         // what the row-local kernel takes in: all but the text's keys and values and the temporal layer's output projection
-        if (tfm_rows_fits(g.dtype, C, g.head_dim, g.ctx_len))
+        if (tfm_rows_fits(g.dtype, C, g.head_dim, g.ctx_len, (long long)g.batch * f.h_in * f.w_in))
           for (size_t i = first; i < c.weights.size(); ++i) {
             Weight& w = c.weights[i];
             const std::string nm = w.info.name;

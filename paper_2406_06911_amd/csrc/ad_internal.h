@@ -173,8 +173,8 @@ void pack_rows(int dtype, const float* w, size_t n, void* out);   // plain conve
 // laid out by lane; in place
 void pack_fragments(void* packed, int rows, int row_bytes);
 
-// whether a transformer block of this width runs in the row-local kernel (its weights are packed for that)
-bool tfm_rows_fits(int dtype, int c, int head_dim, int ctx_len);
+// whether a transformer block of this width and number of tokens (of all samples) runs in the row-local kernel (its weights are packed for that)
+bool tfm_rows_fits(int dtype, int c, int head_dim, int ctx_len, long long tokens);
 uint16_t f32_to_bf16(float f);
 
 }  // namespace ad

@@ -490,10 +490,17 @@ static RowPlan plan_rows(int dtype, int c, int head_dim, int batch, int l, int l
   return plan(1);
 }
 
-bool tfm_rows_fits(int dtype, int c, int head_dim, int lk) {
+// Up to kRowsMaxBytes a row, and beyond kRowsManyTokens only where C x C weights are at most 16 KiB: with that many tokens the separate launches
+// fill the chip, and a workgroup that takes in 15 C^2 weights for its 32 tokens falls behind.  Whole block, us (separate launches -> this): bf16, 128
+// channels 4608 tokens 106 -> 64, 10368 158 -> 148, 16384 (16 frames) 143 -> 123, but 18432 254 -> 267, 20480 (frames, as the next) 209 -> 220, 25600
+// 184 -> 208, 36864 245 -> 278, 65536 415 -> 485; 64 channels 18432 191 -> 177, 36864 180 -> 157, 65536 247 -> 242; fp32, 64 channels 36864 657 -> 579,
+// 65536 1448 -> 1406.
+constexpr long long kRowsManyTokens = 16384;
+bool tfm_rows_fits(int dtype, int c, int head_dim, int lk, long long tokens) {
   if (dtype != AD_BF16 && dtype != AD_F32) return false;
   if ((long long)(lk + 64) * c * (int)esize(dtype) >= 1LL << 31) return false;       // 32-bit offsets into a text sample
   if (c * (int)esize(dtype) > kRowsMaxBytes || c % bk_elems(dtype) || c % head_dim) return false;
+  if (tokens > kRowsManyTokens && c * c * (int)esize(dtype) > 16384) return false;
   return dtype == AD_BF16 ? head_dim == 64 : (head_dim == 16 || head_dim == 32 || head_dim == 64);
 }
 
@@ -510,7 +517,7 @@ static ad_status run_tfm_rows(const RowParams& p, int grid, int lds_bytes, hipSt
 }
 
 ad_status launch_tfm_rows(const TfmRows& a, hipStream_t s) {
-  if (a.batch < 1 || a.l < 1 || !a.in || !tfm_rows_fits(a.dtype, a.c, a.head_dim, a.lk)) AD_FAIL(AD_ERR_INVALID, "tfm_rows: unsupported shape");
+  if (a.batch < 1 || a.l < 1 || !a.in || !tfm_rows_fits(a.dtype, a.c, a.head_dim, a.lk, (long long)a.batch * a.l)) AD_FAIL(AD_ERR_INVALID, "tfm_rows: unsupported shape");
   if ((a.w_in != nullptr) == (a.w_o != nullptr)) AD_FAIL(AD_ERR_INVALID, "tfm_rows: either the input projection or the layer behind an attention");
   const int c = a.c, es = (int)esize(a.dtype);
   const RowPlan plan = plan_rows(a.dtype, c, a.head_dim, a.batch, a.l, a.w_o ? a.lk : 1);

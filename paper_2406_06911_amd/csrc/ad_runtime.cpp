@@ -175,7 +175,7 @@ struct Eval {
     int w = u.w_first;
     // gn.g gn.b proj_in.w proj_in.b | per layer 20 entries | proj_out.w proj_out.b
     AD_TRY(gn(x, nullptr, Cc, 0, L, w + 0, 0, temp(0)));
-    if (tfm_rows_fits(dt, Cc, d, Lk)) return tfm_by_rows(f, w, x, tensor_out(ui), ui);
+    if (tfm_rows_fits(dt, Cc, d, Lk, (long long)B * L)) return tfm_by_rows(f, w, x, tensor_out(ui), ui);
     AD_TRY(linear(temp(0), M, Cc, w + 2, w + 3, nullptr, temp(1)));
     w += 4;
     void* h = temp(1);

@@ -46,6 +46,22 @@ def test_transformer_of_a_narrow_model_matches_oracle(monkeypatch, dtype, c, hea
         case.m.precompute_text(case.d_text, torch.cuda.current_stream())
 
 
+@pytest.mark.parametrize("dtype,c,frames,height,width,by_rows", [(BF, 128, 16, 32, 32, True), (BF, 128, 15, 33, 34, False), (BF, 64, 15, 33, 34, True), (F32, 64, 15, 33, 34, True)])
+def test_transformer_of_many_tokens(monkeypatch, dtype, c, frames, height, width, by_rows):
+    """Beyond 16384 tokens 128 bf16 channels go through the separate launches (their weights are packed for those): which way is taken, and the result."""
+    names = []
+    forward = B.AsyncDiff.component_forward
+
+    def profiled(self, *args, **more):
+        self.profile(True)
+        forward(self, *args, **more)
+        names.extend(r[0] for r in self.profile_records())
+
+    monkeypatch.setattr(B.AsyncDiff, "component_forward", profiled)
+    test_transformer_of_a_narrow_model_matches_oracle(monkeypatch, dtype, c, 64, 1, height, width, frames, 77, frames)
+    assert any("tfm_rows" in n for n in names) == by_rows, set(names)
+
+
 @pytest.mark.parametrize("dtype,c,batch,pooled,frames", [(F32, 32, 1, 0, 0), (F32, 64, 2, 8, 0), (BF, 64, 2, 128, 0), (BF, 64, 5, 0, 5), (BF, 128, 2, 16, 0),
                                                          (F32, 96, 1, 0, 0), (BF, 192, 2, 0, 0)])
 def test_time_embedding_reaches_the_residual_blocks(monkeypatch, dtype, c, batch, pooled, frames):
