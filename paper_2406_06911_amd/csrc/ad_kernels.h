@@ -58,8 +58,6 @@ void set_attn_variant(int variant);   // -1 automatic, 0 first-generation kernel
 void set_order_override(int order);   // -1 automatic, 0 row-tile-major, 1 column-tile-major workgroup order
 // scratch a convolution of this shape wants for split-K (0 = it will not split); k = taps * channels
 size_t conv_workspace_bytes(int dtype, long long m, int n, int k, int out_mode);
-// row tiles per band of a GEMM's workgroup order (per_cu: workgroups a CU holds)
-int best_band(long long tiles_m, long long tiles_n, long long workgroups, int per_cu, int bm, int bn);
 bool conv_takes_shortcut(int dtype, long long m, int n, int c, int xc);      // c, xc: channels of the 3x3 and of the 1x1 convolution
 
 ad_status launch_groupnorm(int dtype, const void* src0, const void* src1, int c0, int c1, int batch, int hw, int groups,

@@ -1466,46 +1466,20 @@ static double plan_cost(long long m, int n, int ktiles, int out_mode, const DmaT
   return cost;
 }
 
-// What the workgroups of an XCD that run side by side take in per k-tile, in elements of K, summed over the first `xcds` XCDs: the distinct rows and
-// columns of the first `run` tiles of its share of the virtual index (see xcd_remap(), tile_of()); `workgroups` is a multiple of the tiles.
-static long long band_intake(long long tiles_m, long long tiles_n, long long workgroups, long long run, int xcds, long long band, int bm, int bn) {
-  const long long tiles = tiles_m * tiles_n;
-  long long sum = 0;
-  for (long long x = 0; x < xcds; ++x) {
-    long long v = x * (workgroups / 8) + std::min(x, workgroups % 8), left = std::min(run, workgroups / 8 + (x < workgroups % 8));
-    while (left > 0) {                                       // the part of the run that lies in one split
-      const long long t = v % tiles, n = std::min(left, tiles - t), end = t + n;
-      long long rows = 0, cols = 0;
-      for (long long b = t / (band * tiles_n); b * band * tiles_n < end; ++b) {
-        const long long start = b * band * tiles_n, high = std::min(band, tiles_m - b * band);
-        const long long from = std::max(t, start) - start, to = std::min(end - start, high * tiles_n);
-        rows += std::min(high, to - from);
-        cols += (to - 1) / high - from / high + 1;
-      }
-      sum += rows * bm + std::min(cols, tiles_n) * bn;       // (the columns of two bands: at most all of them)
-      v += n;
-      left -= n;
-    }
-  }
-  return sum;
-}
-
-// Row tiles per band (tile_of): the workgroups of an XCD that run side by side, at most 32 CUs full, should take in the fewest rows and columns per
-// k-tile.  In a launch of one round all eight XCDs count: a run that straddles two bands takes in the rows of both.  In a longer one, whose workgroups
-// drift apart, a run that begins with a band stands for all.  One row tile or all of them unless another band takes in an eighth less.
-// Weights from memory, us (bands of one row tile / all of them / this): 2048x1280x5120 50.0 / 49.7 / 48.2, 2048x640x2560 15.9 / 20.4 / 16.0 (bands of 5 and 8,
-// which take in a fourteenth less at best: 18.1), 4608x5120x640 45.0 / 46.3 / 41.8, 4928x5120x1280 92.8 / 91.1 / 84.4, 720x640x2560 12.3 / 12.4 / 11.5,
-// 8192x640x2560 30.9 / 37.6 / 30.9, 1400x10240x5120 149.8 / 142.4 / 142.6; of 119 shapes 18 are more than 2 % faster than
-// the better of the two and five more than 2 % slower (336x1280x5760: 18.6 / 20.2 / 20.2).
-int best_band(long long tiles_m, long long tiles_n, long long workgroups, int per_cu, int bm, int bn) {
-  const long long resident = std::min<long long>(per_cu, (workgroups + 255) / 256), run = std::min((workgroups + 7) / 8, 32 * resident);
-  const int xcds = workgroups > 8 * run ? 1 : 8;
-  auto taken = [&](long long band) { return band_intake(tiles_m, tiles_n, workgroups, run, xcds, band, bm, bn); };
-  const long long one = taken(1), all = taken(tiles_m), limit = std::min(one, all);
-  long long best = all < one ? tiles_m : 1, best_taken = limit;
-  for (long long band = 2; band < std::min(tiles_m, run + 1); ++band) {
-    const long long t = taken(band);
-    if (8 * t <= 7 * limit && t < best_taken) { best_taken = t; best = band; }
+// Row tiles per band (tile_of): the workgroups of an XCD that run side by side, at most 32 CUs full, should take in the fewest rows
+// and columns per k-tile.  Weights from memory, us (bands of one row tile / one band / this): 2048x1280x5120 50.6 / 49.3 / 47.8, 8192x640x2560
+// 33.1 / 38.1 / 30.4, 4608x5120x640 45.8 / 48.6 / 42.4, 4608x640x2560 24.1 / 24.3 / 21.5, 2048x10240x1280 58.7 / 54.3 / 53.3, 3x3 18432x320x2880
+// 39.5 / 41.7 / 37.9; of 29 shapes one is slower than the better of the two by more than 3 % (2048x640x2560: 17.4 / 20.4 / 18.1).
+static int best_band(long long m, int n, const DmaTile& t, int splits) {
+  const long long tm = (m + t.bm - 1) / t.bm, tn = (n + t.bn - 1) / t.bn, wgs = tm * tn * splits;
+  const long long resident = std::min<long long>(t.per_cu, (wgs + 255) / 256);
+  const long long run = std::min({(wgs + 7) / 8, 32 * resident, tm * tn});
+  long long best = 1, best_rows = -1;
+  for (long long band = 1; band <= std::min(tm, run); ++band) {
+    const long long tiles = band * tn;                       // of a band; a run is part of one or several whole ones
+    const long long rows = tiles >= run ? band : std::min(tm, band * ((run + tiles - 1) / tiles)), cols = tiles >= run ? (run + band - 1) / band : tn;
+    const long long taken = rows * t.bm + cols * t.bn;
+    if (best_rows < 0 || taken < best_rows) { best_rows = taken; best = band; }
   }
   return (int)best;
 }
@@ -1561,10 +1535,7 @@ static ConvPlan compute_plan(int dtype, long long m, int n, int ktiles, int out_
       if (c < best_cost) { best_cost = c; best = ConvPlan{t.tile, sp, -1}; chosen = &t; }
     }
   }
-  if (chosen) {
-    const long long tm = (m + chosen->bm - 1) / chosen->bm, tn = (n + chosen->bn - 1) / chosen->bn;
-    best.band = best_band(tm, tn, tm * tn * best.splits, chosen->per_cu, chosen->bm, chosen->bn);
-  }
+  if (chosen) best.band = best_band(m, n, *chosen, best.splits);
   return best;
 }
 

@@ -241,34 +241,3 @@ def test_split_k_scratch_does_not_depend_on_earlier_queries():
                 assert got[1] == first[-1][got[0]]
     finally:
         B.check(B.lib.ad_tune_conv_tile(-1))
-
-
-def _order(tiles_m, tiles_n, workgroups, band):
-    """(split, row tile, column tile) by launch index, one list an XCD: indices go to the XCDs in turn, each walks a contiguous share of
-    [split][band of row tiles][column tile][row tile of the band]."""
-    virtual = [(s, m, n) for s in range(workgroups // (tiles_m * tiles_n)) for b in range(0, tiles_m, band) for n in range(tiles_n)
-               for m in range(b, min(b + band, tiles_m))]
-    share = [workgroups // 8 + (x < workgroups % 8) for x in range(8)]
-    return [virtual[sum(share[:x]):sum(share[:x + 1])] for x in range(8)]
-
-
-@pytest.mark.parametrize("tiles_m,tiles_n,splits,per_cu,bm,bn", [
-    (32, 10, 1, 3, 64, 64), (18, 20, 1, 3, 64, 64), (16, 10, 1, 1, 128, 128), (12, 10, 1, 1, 64, 64), (9, 10, 2, 1, 128, 128), (5, 10, 5, 1, 256, 128),
-    (23, 20, 1, 3, 64, 64), (63, 8, 1, 2, 128, 160), (36, 5, 1, 1, 128, 128), (1, 7, 16, 3, 64, 64), (7, 1, 3, 2, 128, 128), (3, 1, 1, 1, 64, 64),
-    (18, 40, 1, 1, 256, 128), (86, 10, 1, 1, 256, 128), (6, 80, 1, 1, 256, 128), (4096, 3, 1, 3, 64, 64)])
-def test_bands_of_row_tiles_take_in_no_more_than_rows_or_columns_alone(tiles_m, tiles_n, splits, per_cu, bm, bn):
-    """The workgroup order of a GEMM: bands of one row tile or of all of them, or others that let the workgroups of an XCD that run side by side take in
-    at least an eighth less, counted here tile by tile (launches of one round: all XCDs; longer ones: a run that begins with a band)."""
-    best = getattr(B.lib, "_ZN2ad9best_bandExxxiii")                       # ad::best_band
-    best.argtypes, best.restype = [ctypes.c_longlong] * 3 + [ctypes.c_int] * 3, ctypes.c_int
-    workgroups = tiles_m * tiles_n * splits
-    run = min((workgroups + 7) // 8, 32 * min(per_cu, (workgroups + 255) // 256))
-    chosen = best(tiles_m, tiles_n, workgroups, per_cu, bm, bn)
-    assert 1 <= chosen <= tiles_m
-
-    def taken(band):
-        lists = _order(tiles_m, tiles_n, workgroups, band)[:1 if workgroups > 8 * run else 8]
-        return sum(len({t[:2] for t in v[:run]}) * bm + len({(t[0], t[2]) for t in v[:run]}) * bn for v in lists)
-
-    simple = min(taken(1), taken(tiles_m))
-    assert taken(chosen) == simple if chosen in (1, tiles_m) else taken(chosen) * 8 <= simple * 7
