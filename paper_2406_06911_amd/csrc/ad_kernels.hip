@@ -1498,6 +1498,17 @@ static SmallTile small_tile(long long m, int n, int ktiles, int out_mode) {
   return SmallTile{0, 0};
 }
 
+// Where the tiles whose K two groups of wavefronts share are left out: a group without a k-tile; 40 k-tiles and more a workgroup in a launch of at most
+// 48 workgroups, where K split over more of them is faster; 80 and more with weights of 8 MiB and more (0.25 to 0.27 us a k-tile, 0.15 to 0.2 elsewhere) or
+// fewer than 200 workgroups.  Weights from memory, us (these tiles / the next best plan), left out: 128x640x2560 11.4 / 8.8, 397x320x2560 11.5 / 9.4,
+// 512x1280x5120 26.4 / 21.4, 947x960x5120 25.9 / 23.2, 1026x640x5120 20.5 / 18.7; kept: 720x1280x2560 12.3 / 14.7, 995x320x2560 11.8 / 12.3, 104x960x2304
+// 10.1 / 10.9, 1168x512x4608 17.7 / 20.1, 2880x320x5760 20.3 / 23.4.
+static bool k2_suits(long long m, int n, int ktiles, int splits, int per) {
+  const long long wgs = ((m + 63) / 64) * ((n + 63) / 64) * splits;
+  if (ktiles - (splits - 1) * per < 2 || (per >= 40 && wgs <= 48)) return false;
+  return per < 80 || (wgs >= 200 && (long long)n * ktiles * kRowBytes < (8 << 20));
+}
+
 static ConvPlan compute_plan(int dtype, long long m, int n, int ktiles, int out_mode) {
   const bool geglu = out_mode == OUT_GEGLU;   // needs a value and a gate tile in the same wavefront
   const bool dma = dma_capable(dtype, out_mode);
@@ -1530,7 +1541,7 @@ static ConvPlan compute_plan(int dtype, long long m, int n, int ktiles, int out_
       if (sp > 1 && ktiles / sp < 4) break;
       const int per = (ktiles + sp - 1) / sp;
       if ((ktiles + per - 1) / per != sp) continue;          // every split must own at least one k-tile
-      if (t.tile == TILE_K2_64 && ktiles - (sp - 1) * per < 2) continue;         // so must both groups of wavefronts
+      if (t.tile == TILE_K2_64 && !k2_suits(m, n, ktiles, sp, per)) continue;
       const double c = plan_cost(m, n, ktiles, out_mode, t, sp);
       if (c < best_cost) { best_cost = c; best = ConvPlan{t.tile, sp, -1}; chosen = &t; }
     }

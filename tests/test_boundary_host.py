@@ -241,3 +241,12 @@ def test_split_k_scratch_does_not_depend_on_earlier_queries():
                 assert got[1] == first[-1][got[0]]
     finally:
         B.check(B.lib.ad_tune_conv_tile(-1))
+
+
+@pytest.mark.parametrize("rows,n_out,k,splits", [(512, 1280, 5120, True), (431, 1280, 5120, True), (1026, 640, 5120, True), (947, 960, 5120, True),
+                                                 (128, 640, 2560, True), (397, 320, 2560, True), (2880, 320, 5760, False), (720, 1280, 2560, False),
+                                                 (995, 320, 2560, False), (104, 960, 2304, False), (1168, 512, 4608, False)])
+def test_long_and_small_gemms_split_k_over_workgroups(rows, n_out, k, splits):
+    """Launches of few workgroups with a long K, and those whose workgroups would walk 80 k-tiles and more of large weights or leave much of the chip idle,
+    share K out over workgroups (they ask for scratch memory); the others leave it to the wavefront groups of a workgroup."""
+    assert (B.lib.ad_conv_workspace_bytes(B.AD_BF16, 1, rows, 1, n_out, k, 1, B.OUT_ROWMAJOR) > 0) == splits
