@@ -298,9 +298,9 @@ ad_status ad_conv_forward(int dtype, const void* src0, const void* src1, int c0,
  * LDS-DMA, 5: 128x128 three-stage LDS-DMA, 6: 256x128 three-stage LDS-DMA, 7: 64x64 three-stage LDS-DMA,
  * 8 / 9: as 5 / 6, with 3x3 stride-1 convolutions on the halo-staged kernel (128 / 256 output positions per workgroup),
  * 10 / 11: as 6 / 5 with four wavefronts per workgroup instead of eight, 12: as 6 with sixteen, 14 / 15: 128x160 / 256x320
- * two-stage LDS-DMA (14 leaves GEGLU to the automatic choice),
+ * two-stage LDS-DMA, 16: as 7 with the k-tiles shared by two groups of wavefronts (7, 14 and 16 leave GEGLU to the automatic choice),
  * -1: automatic choice, the default (3x3 convolutions on the per-tap kernels 5 / 6: measured faster than 8 / 9 on the SD-sized models)).
- * 4 to 12, 14 and 15 apply to bf16 GEMMs with a row-major, GEGLU or fused q/k/v output; other calls keep the automatic
+ * 4 to 12 and 14 to 16 apply to bf16 GEMMs with a row-major, GEGLU or fused q/k/v output; other calls keep the automatic
  * choice.  Results are the same up to rounding order.  Process-global, not thread-safe: for tests and measurements. */
 ad_status ad_tune_conv_tile(int tile);
 /* Tuning knob for measurements: order in which the workgroups of a GEMM walk its output tiles.  0: an XCD owns a

@@ -1498,14 +1498,14 @@ static SmallTile small_tile(long long m, int n, int ktiles, int out_mode) {
   return SmallTile{0, 0};
 }
 
-// Where the tiles whose K two groups of wavefronts share are left out: a group without a k-tile; 40 k-tiles and more a workgroup in a launch of at most
+// Where the tiles whose K two groups of wavefronts share are left out: 40 k-tiles and more a workgroup in a launch of at most
 // 48 workgroups, where K split over more of them is faster; 80 and more with weights of 8 MiB and more (0.25 to 0.27 us a k-tile, 0.15 to 0.2 elsewhere) or
 // fewer than 200 workgroups.  Weights from memory, us (these tiles / the next best plan), left out: 128x640x2560 11.4 / 8.8, 397x320x2560 11.5 / 9.4,
 // 512x1280x5120 26.4 / 21.4, 947x960x5120 25.9 / 23.2, 1026x640x5120 20.5 / 18.7; kept: 720x1280x2560 12.3 / 14.7, 995x320x2560 11.8 / 12.3, 104x960x2304
 // 10.1 / 10.9, 1168x512x4608 17.7 / 20.1, 2880x320x5760 20.3 / 23.4.
 static bool k2_suits(long long m, int n, int ktiles, int splits, int per) {
   const long long wgs = ((m + 63) / 64) * ((n + 63) / 64) * splits;
-  if (ktiles - (splits - 1) * per < 2 || (per >= 40 && wgs <= 48)) return false;
+  if (per >= 40 && wgs <= 48) return false;
   return per < 80 || (wgs >= 200 && (long long)n * ktiles * kRowBytes < (8 << 20));
 }
 
@@ -1517,8 +1517,8 @@ static ConvPlan compute_plan(int dtype, long long m, int n, int ktiles, int out_
   if (forced == TILE_P3_256_W4 || forced == TILE_P3_256_W16) forced = TILE_P3_256;
   if (forced == TILE_HALO_128) forced = TILE_P3_128;      // the halo kernels share the tile shapes (and the split-K planning) of these
   if (forced == TILE_HALO_256) forced = TILE_P3_256;
-  if (forced == TILE_P3_128 || forced == TILE_P3_256 || forced == TILE_D2_128 || forced == TILE_P3_64 || forced == TILE_D2_160 || forced == TILE_D2_320) {
-    if (!dma || ((forced == TILE_P3_64 || forced == TILE_D2_160) && geglu)) forced = TILE_AUTO;
+  if (forced == TILE_P3_128 || forced == TILE_P3_256 || forced == TILE_D2_128 || forced == TILE_P3_64 || forced == TILE_K2_64 || forced == TILE_D2_160 || forced == TILE_D2_320) {
+    if (!dma || ((forced == TILE_P3_64 || forced == TILE_K2_64 || forced == TILE_D2_160) && geglu)) forced = TILE_AUTO;
   }
   else if (forced != TILE_AUTO && geglu) forced = TILE_AUTO;
   if (forced == TILE_128x128 || forced == TILE_64x64) return ConvPlan{forced, splits_by_tiles(m, n, ktiles, out_mode, forced == TILE_64x64 ? 64 : 128), -1};
@@ -1541,7 +1541,8 @@ static ConvPlan compute_plan(int dtype, long long m, int n, int ktiles, int out_
       if (sp > 1 && ktiles / sp < 4) break;
       const int per = (ktiles + sp - 1) / sp;
       if ((ktiles + per - 1) / per != sp) continue;          // every split must own at least one k-tile
-      if (t.tile == TILE_K2_64 && !k2_suits(m, n, ktiles, sp, per)) continue;
+      if (t.tile == TILE_K2_64 && ktiles - (sp - 1) * per < 2) continue;         // so must both groups of wavefronts
+      if (t.tile == TILE_K2_64 && forced == TILE_AUTO && !k2_suits(m, n, ktiles, sp, per)) continue;
       const double c = plan_cost(m, n, ktiles, out_mode, t, sp);
       if (c < best_cost) { best_cost = c; best = ConvPlan{t.tile, sp, -1}; chosen = &t; }
     }
@@ -3689,7 +3690,7 @@ size_t ad_conv_workspace_bytes(int dtype, int batch, int h_out, int w_out, int n
 }
 
 ad_status ad_tune_conv_tile(int tile) {
-  if (tile != -1 && tile != 1 && tile != 3 && tile != 14 && tile != 15 && (tile < 4 || tile > 12)) AD_FAIL(AD_ERR_INVALID, "tile must be -1, 1, 3, 4..12, 14 or 15");
+  if (tile != -1 && tile != 1 && (tile < 3 || tile > 16 || tile == 13)) AD_FAIL(AD_ERR_INVALID, "tile must be -1, 1, 3..12 or 14..16");
   set_tile_override(tile);
   return AD_OK;
 }

@@ -323,8 +323,8 @@ def test_workgroup_order_in_bands(rows, cin, n_out, tile):
 @pytest.mark.parametrize("c0,c1,k,stride,up,n_out", [(448, 0, 1, 1, 0, 640), (64, 0, 3, 1, 0, 640), (128, 64, 3, 1, 0, 600), (640, 640, 1, 1, 0, 642),
                                                      (192, 0, 3, 2, 0, 1280), (64, 128, 3, 1, 1, 320), (2496, 0, 1, 1, 0, 640)])
 def test_k_shared_by_two_groups(c0, c1, k, stride, up, n_out):
-    """64x64 tiles whose k-tiles are shared out over two groups of wavefronts (the automatic choice for these shapes): odd and even numbers of
-    k-tiles, changes of tap and source at and beside the middle, ragged rows and columns, everything the epilogue adds, split over workgroups."""
+    """64x64 tiles whose k-tiles are shared out over two groups of wavefronts: odd and even numbers of k-tiles, changes of tap and source at and beside
+    the middle, ragged rows and columns, everything the epilogue adds."""
     n, hs, ws = (2, 25, 20) if not up else (2, 12, 11)
     x0, x1 = (quantize(SI.make_array((n, c, hs, ws), 391 + i), B.AD_BF16) if c else None for i, c in enumerate((c0, c1)))
     w = quantize(SI.make_array((n_out, c0 + c1, k, k), 393, 0.05), B.AD_BF16)
@@ -332,9 +332,29 @@ def test_k_shared_by_two_groups(c0, c1, k, stride, up, n_out):
     xin = x0 if x1 is None else np.concatenate([x0, x1], 1)
     ref = P.conv2d(P.upsample_nearest2x(xin) if up else xin, w, bias, stride=stride) + rowvec[:, :, None, None]
     res = quantize(SI.make_array((n, ref.shape[2], ref.shape[3], n_out), 396), B.AD_BF16)
-    for splitk in (False, True):
-        got, _ = run_conv(B.AD_BF16, x0, x1, w, bias, stride, up, rowvec=rowvec, residual=res, splitk=splitk)
+    for tile, splitk in ((16, False), (-1, False), (-1, True)):
+        B.check(lib.ad_tune_conv_tile(tile))
+        try:
+            got, _ = run_conv(B.AD_BF16, x0, x1, w, bias, stride, up, rowvec=rowvec, residual=res, splitk=splitk)
+        finally:
+            B.check(lib.ad_tune_conv_tile(-1))
         assert_kernel_close(nhwc_to_nchw(got), ref + nhwc_to_nchw(res), B.AD_BF16)
+
+
+@pytest.mark.parametrize("hs,ws,c0,c1,k,n_out,last", [(8, 4, 2368, 0, 1, 64, 2), (8, 4, 2112, 0, 1, 52, 3), (8, 4, 256, 256, 3, 64, 2), (7, 4, 320, 128, 3, 64, 3),
+                                                      (8, 4, 704, 0, 3, 36, 3)])
+def test_k_shared_by_workgroups_and_two_groups_each(hs, ws, c0, c1, k, n_out, last):
+    """The same with K shared out over workgroups first: the last of them has two or three k-tiles, one for each group of wavefronts or one more."""
+    x0, x1 = (quantize(SI.make_array((2, c, hs, ws), 411 + i), B.AD_BF16) if c else None for i, c in enumerate((c0, c1)))
+    w, bias = quantize(SI.make_array((n_out, c0 + c1, k, k), 413, 0.05), B.AD_BF16), SI.make_array((n_out,), 414, 0.1)
+    B.check(lib.ad_tune_conv_tile(16))
+    try:
+        got, _ = run_conv(B.AD_BF16, x0, x1, w, bias, splitk=True)
+    finally:
+        B.check(lib.ad_tune_conv_tile(-1))
+    ktiles, splits = k * k * (c0 + c1) // 64, run_conv.last_ws_bytes // (2 * hs * ws * n_out * 4)
+    assert splits > 1 and ktiles - (splits - 1) * -(-ktiles // splits) == last, (ktiles, splits)
+    assert_kernel_close(nhwc_to_nchw(got), P.conv2d(x0 if x1 is None else np.concatenate([x0, x1], 1), w, bias), B.AD_BF16)
 
 
 @pytest.mark.parametrize("l,c,cin,ld_t", [(500, 320, 640, 512), (333, 192, 704, 0), (257, 320, 1344, 260)])
@@ -343,9 +363,13 @@ def test_k_shared_by_two_groups_fused_projection(l, c, cin, ld_t):
     dx, wp = dev(x, B.AD_BF16), dev_bytes(B.pack_conv_weight(B.AD_BF16, w))
     q, k = (torch.full((2 * l, c), float("nan"), device=DEV, dtype=torch.bfloat16) for _ in range(2))
     v = torch.full((2 * c * ld_t if ld_t else 2 * l * c,), float("nan"), device=DEV, dtype=torch.bfloat16)
-    B.check(lib.ad_conv_forward(B.AD_BF16, p(dx), None, cin, 0, 2, l, 1, 0, 1, 1, p(wp), 3 * c, None, None, None, p(q), p(k), p(v), B.OUT_QKV, ld_t, None, 0,
-                                stream_ptr()))
-    sync()
+    B.check(lib.ad_tune_conv_tile(16))
+    try:
+        B.check(lib.ad_conv_forward(B.AD_BF16, p(dx), None, cin, 0, 2, l, 1, 0, 1, 1, p(wp), 3 * c, None, None, None, p(q), p(k), p(v), B.OUT_QKV, ld_t, None, 0,
+                                    stream_ptr()))
+        sync()
+    finally:
+        B.check(lib.ad_tune_conv_tile(-1))
     ref = P.linear(x, w)
     assert_kernel_close(host(q), ref[:, :c], B.AD_BF16)
     assert_kernel_close(host(k), ref[:, c:2 * c], B.AD_BF16)

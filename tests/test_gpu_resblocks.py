@@ -43,7 +43,7 @@ def check_blocks(monkeypatch, dtype, tile, channels, height, width, batch, wante
 
 
 @pytest.mark.parametrize("tile,channels,height,width,batch", [
-    (4, [128, 192], 22, 14, 2), (5, [128, 192], 22, 14, 2), (6, [128, 192], 22, 14, 2), (7, [128, 192], 22, 14, 2), (14, [128, 192], 22, 14, 2),
+    (4, [128, 192], 22, 14, 2), (5, [128, 192], 22, 14, 2), (6, [128, 192], 22, 14, 2), (7, [128, 192], 22, 14, 2), (14, [128, 192], 22, 14, 2), (16, [128, 192], 22, 14, 2), (16, [64, 320], 34, 18, 2), (16, [128, 192], 6, 4, 1),
     (15, [128, 192], 22, 14, 2), (5, [64, 64], 2, 2, 1), (7, [64, 320], 34, 18, 2), (-1, [320, 640], 20, 18, 1), (-1, [64, 320], 72, 40, 1),
     (-1, [320, 320], 48, 46, 2)])
 def test_shortcut_inside_the_second_convolution(monkeypatch, tile, channels, height, width, batch):
