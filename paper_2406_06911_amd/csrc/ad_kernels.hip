@@ -3019,8 +3019,9 @@ __global__ __launch_bounds__(NT) void k_gn_apply(const T* __restrict__ src0, con
   }
 }
 
-// GroupNorm in one launch: a workgroup owns one (sample, group), keeps its (C/G) x HW elements in registers, reduces them
-// and writes the normalised result, so the tensor is read once and nothing goes through scratch memory.  G: channels per
+// GroupNorm in one launch: a workgroup keeps the (C/G) x HW elements of one (sample, group) in registers, reduces them and writes the
+// normalised result, so nothing goes through scratch memory.  2^log_parts workgroups take in the same group (see launch_gn_group()), each
+// writes every 2^log_parts-th of a thread's accesses: with log_parts > 0 out must not overlap a source, which another one may still read.  G: channels per
 // access (the widest that divides the channels of a group), NV: accesses a thread can hold; thread (pixel lane, access of the pixel)
 // walks the pixels in steps of `pl`, so its channels stay the same.
 // Neighbouring groups share cache lines: xcd_remap puts them on one XCD.  Bound by one round trip to memory and the launch.
@@ -3121,8 +3122,9 @@ static ad_status launch_gn_group(const void* src0, const void* src1, int c0, int
   // The groups of a single sample are 32 workgroups that spend half their time on the result, 14 vector instructions an element against 6 of the
   // sums: up to four take all of a group in and write a part of it each, as long as that is a few thousand elements.  One sample, us: 2880 pixels
   // of 320 channels 15.7 -> 12.6, 720 of 640 6.2 -> 5.6, 720 of 1280 10.8 -> 9.2; the 576x320 px run 66.1 -> 64.9 ms.  Two samples' groups gain
-  // 5-10 % alone as well (2304 of 640 13.8 -> 12.7), but take the CUs that other streams use: 768px runs 0.7 % slower.  In place, a group belongs to
-  // one workgroup.
+  // 5-10 % alone as well (2304 of 640 13.8 -> 12.7), but take the CUs that other streams use: 768px runs 0.7 % slower.  One sample beside other
+  // streams, whole runs (one workgroup a group / this): 576x320 px on two streams 62.5 / 61.4 ms, on four 52.5 / 52.6, 320px 45.4 / 44.8, 512px 60.4 / 60.0,
+  // 768px 99.8 / 100.1.  In place, a group belongs to one workgroup.
   const long long elements = (long long)hw * (ctot / groups), rows = (long long)batch * hw;
   auto apart = [&](const void* src, int c) {
     const char *a = (const char*)src, *o = (const char*)out;

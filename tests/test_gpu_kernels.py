@@ -545,16 +545,19 @@ def test_groupnorm_every_path(dtype, shape):
                                                (2, 64, 259, 1), (1, 1280, 3, 1), (4, 256, 1111, 32)])
 def test_groupnorm_shared_by_workgroups_and_in_place(dtype, batch, c, hw, groups):
     """Groups of one launch whose result several workgroups write: around the lines between one, two and four of them, ragged last rounds, fewer rounds
-    than workgroups; and the same call with its input as output, which leaves a group to one workgroup."""
+    than workgroups; and the same call with its input as output, which leaves a group to one workgroup: the same bits."""
     x = quantize(SI.make_array((batch, hw, c), 48) * 2 + 0.5, dtype)
     gam, bet = 1 + SI.make_array((c,), 49, 0.3), SI.make_array((c,), 50, 0.3)
     ref = P.silu(P.group_norm(x.transpose(0, 2, 1)[..., None], groups, gam, bet, 1e-5))[..., 0].transpose(0, 2, 1)
     d, dg, dbt = dev(x, dtype), dev_f32(gam), dev_f32(bet)
     scratch = torch.zeros(lib.ad_groupnorm_scratch_bytes(batch, hw, c), dtype=torch.uint8, device=DEV)
+    got = []
     for out in (torch.full_like(d, float("nan")), d):
         B.check(lib.ad_groupnorm_forward(dtype, p(d), None, c, 0, batch, hw, groups, p(dg), p(dbt), 1e-5, 1, p(out), p(scratch), stream_ptr()))
         sync()
-        assert_kernel_close(host(out), ref, dtype, rel=1e-5 if dtype == B.AD_F32 else 5e-3)
+        got.append(host(out))
+        assert_kernel_close(got[-1], ref, dtype, rel=1e-5 if dtype == B.AD_F32 else 5e-3)
+    assert np.array_equal(got[0], got[1])
 
 
 @pytest.mark.parametrize("dtype", DT)
