@@ -68,16 +68,6 @@ __device__ __forceinline__ float wave_sum_rows(float v) {
   v += dpp_f<0x140>(v);     // row_mirror
   return (lane_f(v, 0) + lane_f(v, 16)) + (lane_f(v, 32) + lane_f(v, 48));
 }
-__device__ __forceinline__ double wave_sum_d(double v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
-}
-__device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
-  return v;
-}
 
 // Blocks are handed to the 8 XCDs round-robin; renumber them so that consecutive tile ids run on
 // the same XCD and share its L2.

@@ -447,7 +447,7 @@ static void plan_work(Ctx& c) {
   // per (component, lane) activation workspaces
   int cmax = 0;
   for (const Unit& u : c.units) cmax = std::max(cmax, std::max(u.info.c_in + u.info.c_skip, u.info.c_out));
-  c.f32_bytes = ((size_t)g.channels[0] + 4ull * g.batch * c.temb_dim + (size_t)g.batch * c.temb_rows_total) * 4;
+  c.f32_bytes = (4ull * g.batch * c.temb_dim + (size_t)g.batch * c.temb_rows_total) * 4;
   c.gn_bytes = ad_groupnorm_scratch_bytes(g.batch, g.height * g.width, cmax);
   c.ws.assign(c.N, {});
   for (int n = 0; n < c.N; ++n) {

@@ -869,9 +869,13 @@ __global__ __launch_bounds__(64 * WM * WN * KG, p3_waves_per_simd(BM, BN, WM * W
                                                          (float*)(lds + NW * stage_bytes<T, WTM, WTN>(CR)) + wave_m * (WTM * 32));
 }
 
+// the instances that conv_takes_shortcut() counts on: 64x64, the two-stage tiles, and 128x128 and 256x128 on eight wavefronts
+constexpr bool p3_takes_shortcut(int mode, int bn, int waves, int stages) {
+  return (mode == OUT_ROWMAJOR || mode == OUT_PARTIAL) && (bn == 64 || stages == 2 || waves == 8);
+}
 template <typename T, int BM, int BN, int MODE, int WM = 2, int WN = 2, int NSTAGE = 3, int KG = 1, bool XTRA = false>
 static ad_status run_igemm_p3(const IgemmParams& p0, const char* name, hipStream_t s) {
-  if constexpr (!XTRA && (MODE == OUT_ROWMAJOR || MODE == OUT_PARTIAL) && !(BM <= 256 && BN == 128 && NSTAGE == 3 && WM * WN != 8))
+  if constexpr (!XTRA && p3_takes_shortcut(MODE, BN, WM * WN, NSTAGE))
     if (p0.xw) return run_igemm_p3<T, BM, BN, MODE, WM, WN, NSTAGE, KG, true>(p0, name, s);
   if (!XTRA && p0.xw) AD_FAIL(AD_ERR_INVALID, "conv: this tile does not take a shortcut");
   IgemmParams p = p0;
@@ -2605,20 +2609,17 @@ ad_status launch_attention(int dtype, const void* q, const void* k, const void* 
         AD_FAIL(AD_ERR_INVALID, "attention: key tensor too large");
       if ((((uintptr_t)q | (uintptr_t)k | (uintptr_t)v | (uintptr_t)out) & 15) != 0) AD_FAIL(AD_ERR_INVALID, "attention: pointers must be 16-byte aligned");
       const float sl2 = scale * 1.44269504088896341f;
-      auto run = [&](auto kern, int queries, int waves, int stages) -> ad_status {
-        const int qb = (l + queries - 1) / queries, lds_bytes = stages * kAttn2Stage;
-        if (lds_bytes > 65536) AD_HIP(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes));
-        hipLaunchKernelGGL(kern, dim3(qb * heads * batch), dim3(64 * waves), lds_bytes, s, (const bf16*)q, (const bf16*)k, (const bf16*)v, (bf16*)out, l, lk, c,
+      auto run = [&](auto kern, int queries, int waves, int stages) {
+        static_assert(4 * kAttn2Stage <= 65536, "what a launch gets without asking");
+        const int qb = (l + queries - 1) / queries;
+        hipLaunchKernelGGL(kern, dim3(qb * heads * batch), dim3(64 * waves), stages * kAttn2Stage, s, (const bf16*)q, (const bf16*)k, (const bf16*)v, (bf16*)out, l, lk, c,
                            ldq, ldk, ldv, ldo, sl2, qb);
-        return AD_OK;
       };
       const bool ragged = (lk & 63) != 0;
-      ad_status st = AD_OK;
-      if (variant == 3) st = ragged ? run(k_attn_mfma2<1, true, 4, 2, 1>, 128, 4, 4) : run(k_attn_mfma2<1, false, 4, 2, 1>, 128, 4, 4);
-      else if (variant == 2) st = ragged ? run(k_attn_mfma2<2, true>, 256, 4, 3) : run(k_attn_mfma2<2, false>, 256, 4, 3);
-      else if (g_attn_variant < 0 && attn_split(batch * heads, l)) st = ragged ? run(k_attn_mfma2<1, true, 2, 2, 0, 2, 2>, 64, 4, 4) : run(k_attn_mfma2<1, false, 2, 2, 0, 2, 2>, 64, 4, 4);
-      else st = ragged ? run(k_attn_mfma2<1, true>, 128, 4, 3) : run(k_attn_mfma2<1, false>, 128, 4, 3);
-      if (st != AD_OK) return st;
+      if (variant == 3) ragged ? run(k_attn_mfma2<1, true, 4, 2, 1>, 128, 4, 4) : run(k_attn_mfma2<1, false, 4, 2, 1>, 128, 4, 4);
+      else if (variant == 2) ragged ? run(k_attn_mfma2<2, true>, 256, 4, 3) : run(k_attn_mfma2<2, false>, 256, 4, 3);
+      else if (g_attn_variant < 0 && attn_split(batch * heads, l)) ragged ? run(k_attn_mfma2<1, true, 2, 2, 0, 2, 2>, 64, 4, 4) : run(k_attn_mfma2<1, false, 2, 2, 0, 2, 2>, 64, 4, 4);
+      else ragged ? run(k_attn_mfma2<1, true>, 128, 4, 3) : run(k_attn_mfma2<1, false>, 128, 4, 3);
       AD_HIP(hipGetLastError());
       return AD_OK;
     }

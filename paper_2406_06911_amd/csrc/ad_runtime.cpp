@@ -131,7 +131,7 @@ struct Eval {
     };
     TfmRows first{dt, B, L, Cc, d, c.cfg.ln_eps, temp(0), temp(1)};
     first.w_in = wv.at(w + 2); first.b_in = wv.f32(w + 3);
-    if (f.depth > 0) with_qkv(first, w + 4, vt ? lp : 0);
+    with_qkv(first, w + 4, vt ? lp : 0);                     // (a transformer has at least one layer)
     AD_TRY(launch_tfm_rows(first, s));
     w += 4;
     for (int k = 0; k < f.depth; ++k, w += 20) {
