@@ -17,6 +17,7 @@
 #include <atomic>
 #include <cmath>
 #include <mutex>
+#include <numeric>
 #include <type_traits>
 
 namespace ad {
@@ -1471,9 +1472,13 @@ static double plan_cost(long long m, int n, int ktiles, int out_mode, const DmaT
 }
 
 // Row tiles per band (tile_of): the workgroups of an XCD that run side by side, at most 32 CUs full, should take in the fewest rows
-// and columns per k-tile.  Weights from memory, us (bands of one row tile / one band / this): 2048x1280x5120 50.6 / 49.3 / 47.8, 8192x640x2560
-// 33.1 / 38.1 / 30.4, 4608x5120x640 45.8 / 48.6 / 42.4, 4608x640x2560 24.1 / 24.3 / 21.5, 2048x10240x1280 58.7 / 54.3 / 53.3, 3x3 18432x320x2880
-// 39.5 / 41.7 / 37.9; of 29 shapes one is slower than the better of the two by more than 3 % (2048x640x2560: 17.4 / 20.4 / 18.1).
+// and columns per k-tile.  Weights from memory, launches back to back, us (bands of one row tile / one band / this): 2048x1280x5120 50.0 / 49.7 / 48.3,
+// 4608x5120x640 45.0 / 46.3 / 41.8, 4928x5120x1280 92.8 / 91.1 / 84.4, 720x640x2560 12.3 / 12.4 / 11.5, 8192x640x2560 30.9 / 37.6 / 30.9; slower than one of the
+// two: 2048x640x2560 15.9 / 20.3 / 18.1, 880x1280x1280 9.9 / 10.0 / 10.8 (their runs straddle two bands).  Inside the models, behind a kernel that leaves its rows
+// in the L2 of the XCD that owns them, those two are level (22.7 against 23.1) and bands of many rows lose: 1152x1280x1280 15.4 / 16.8 / 15.3.
+// A launch of several rounds without K-splits: no bands that leave fewer than four places where the XCDs begin in them, since XCDs that walk the same
+// columns at the same time wait for the same memory: 16384x5120x640 113.3 / 125.0 / 110.8 (bands of eight, all XCDs at the first column: 123.1),
+// 8192x5120x640 58.8 / 66.0 / 57.4 (eight, two places: 61.1), 4096x3840x1280 45.4 / 47.9 / 42.4 (46.7), 65536x2560x320 179 / 189 / 173 (175).
 static int best_band(long long m, int n, const DmaTile& t, int splits) {
   const long long tm = (m + t.bm - 1) / t.bm, tn = (n + t.bn - 1) / t.bn, wgs = tm * tn * splits;
   const long long resident = std::min<long long>(t.per_cu, (wgs + 255) / 256);
@@ -1481,6 +1486,7 @@ static int best_band(long long m, int n, const DmaTile& t, int splits) {
   long long best = 1, best_rows = -1;
   for (long long band = 1; band <= std::min(tm, run); ++band) {
     const long long tiles = band * tn;                       // of a band; a run is part of one or several whole ones
+    if (band > 1 && splits == 1 && wgs / 8 > run && tiles / std::gcd(wgs / 8, tiles) < 4) continue;
     const long long rows = tiles >= run ? band : std::min(tm, band * ((run + tiles - 1) / tiles)), cols = tiles >= run ? (run + band - 1) / band : tn;
     const long long taken = rows * t.bm + cols * t.bn;
     if (best_rows < 0 || taken < best_rows) { best_rows = taken; best = band; }
