@@ -302,9 +302,10 @@ def test_two_stage_tiles_follow_sources_and_taps(tile, c0, c1, k, stride, up):
 
 
 @pytest.mark.parametrize("rows,cin,n_out,tile", [(2048, 128, 1280, 5), (1800, 128, 1100, 5), (4500, 64, 640, 6), (1100, 448, 448, 7), (1100, 448, 448, -1), (2900, 64, 800, 14),
-                                                 (3000, 64, 1600, 15), (900, 1024, 640, 4)])
+                                                 (3000, 64, 1600, 15), (900, 1024, 640, 4), (4096, 64, 1280, 5), (2100, 64, 3840, 6)])
 def test_workgroup_order_in_bands(rows, cin, n_out, tile):
-    """Every output tile once, whatever the order: bands of several row tiles with a shorter last one, runs of an XCD that end inside a band, K-splits.
+    """Every output tile once, whatever the order: bands of several row tiles with a shorter last one, runs of an XCD that end inside a band, K-splits,
+    several rounds of which the bands are not to begin at the same column everywhere.
     The order changes no sum, so all three are equal bit for bit."""
     x, w = quantize(SI.make_array((rows, cin), 71), B.AD_BF16), quantize(SI.make_array((n_out, cin), 72, 0.1), B.AD_BF16)
     got = []
