@@ -587,8 +587,8 @@ __device__ __forceinline__ int lds_swizzle(int row) { return (row >> 1) & 7; }
 // at most a 64x64 workgroup per CU, whose four wavefronts would wait for two tiles of 16 KiB at a time: 2880x320x2880 16.0 -> 12.4 us,
 // 720x640x2560 14.4 -> 12.0, 180x3840x1280 11.2 -> 9.7, 288x1280x1280 8.3 -> 7.2 (two stages, four groups or 128-row tiles: slower).
 // Bound by the feed from beyond the L2 and by what a launch of few rounds leaves idle, hence the choice of tiles (see kDmaTiles): with the
-// MFMAs taken out 2048x1280x5120 still takes 49 of its 50 us (weights from memory), with the loads taken out 29.  More stages do not help
-// (four and five: 49), nor does a wavefront that asks for the lines ahead (53).
+// MFMAs taken out 2048x1280x5120 still took 49 of the 50 us that it took in the order of rows (weights from memory; 48 in that of best_band()), with the
+// loads taken out 29.  More stages do not help (four and five: 49), nor does a wavefront that asks for the lines ahead (53).
 // Measured, bf16, us (best of 128x128, 256x128 and 64x64 -> the tile of this list that kDmaTiles names): GEGLU 2048x10240x1280 72 -> 58
 // (256x320), 3x3 16384x640x5760 139 -> 116 (128x160), 3x3 65536x320x2880 130 -> 121 (256x320), q/k/v 65536x960x320 79 -> 64 (256x320),
 // GEGLU 8192x5120x640 78 -> 66 (256x320), 2048x1280x1280 16.2 -> 13.7 (128x128 for 64x64).
