@@ -2587,9 +2587,11 @@ static int attn_auto_variant(int bh, int l, int lk) {
 
 // Where 64-query workgroups fit the chip once, the plain launch (128 queries) leaves half of it idle: 64 queries and two key halves a
 // workgroup instead, which halves the chain of key tiles as well.  One sample, us (128 queries -> this): 2880 x 2880, 5 heads, 36.6 -> 25.0;
-// 1536, 10 heads, 21.6 -> 14.4; 720, 10 heads, 14.2 -> 10.0; 640, 20 heads, 11.2 -> 8.2.  Beyond that they are level (320 workgroups 15.8 / 14.9,
-// 360 10.8 / 11.0) and then fall behind (9216, 2 x 5 heads: 230 / 268, keys and values are fetched twice as often).  Four key shares with 128 KiB of
-// LDS gain another tenth from 1500 keys on, but leave the other streams' workgroups no room.
+// 1536, 10 heads, 21.6 -> 14.4; 720, 10 heads, 14.2 -> 10.0; 640, 20 heads, 11.2 -> 8.2.  Up to 400 workgroups, where some CUs get two, it is still faster
+// alone, by less: 1024, 20 heads 15.2 / 14.1, 2304, 10 heads 29.0 / 25.9, 5120, 5 heads 59.2 / 51.4, 576, 2 x 20 heads 10.4 / 10.2; but whole runs with the
+// line there are level (512px 0.3 % faster, 768px and 576x320 px 0.0, 768px wrapped 0.6 faster with runs of one side 0.8 apart), so it stays where no CU holds
+// more than one.  Far beyond it falls behind (9216, 2 x 5 heads: 230 / 268, keys and values are fetched twice as often).  Four key shares with 128 KiB of LDS
+// gain another tenth from 1500 keys on, but leave the other streams' workgroups no room.
 static bool attn_split(int bh, int l) { return (long long)bh * ((l + 63) / 64) <= 256; }
 
 ad_status launch_attention(int dtype, const void* q, const void* k, const void* v, int v_t, int batch, int l, int lk, int c,
