@@ -374,6 +374,16 @@ void pack_fragments(void* packed, int rows, int row_bytes) {
   }
 }
 
+void pack_blocks(void* packed, int rows, int row_bytes) {
+  std::vector<char> t((size_t)kWBlock * row_bytes);
+  for (int r0 = 0; r0 < rows; r0 += kWBlock) {
+    char* block = (char*)packed + (size_t)r0 * row_bytes;
+    for (int r = 0; r < kWBlock; ++r)
+      for (int k = 0; k < row_bytes; k += kRowBytes) std::memcpy(t.data() + (size_t)k * kWBlock + r * kRowBytes, block + (size_t)r * row_bytes + k, kRowBytes);
+    std::memcpy(block, t.data(), t.size());
+  }
+}
+
 void pack_rows(int dtype, const float* w, size_t n, void* out) {
   for (size_t i = 0; i < n; ++i) put(dtype, out, i, w[i]);
 }

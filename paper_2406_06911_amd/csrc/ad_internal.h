@@ -35,6 +35,7 @@ inline size_t esize(int dtype) { return dtype == AD_BF16 ? 2 : 4; }
 constexpr int kRowBytes = 128;                      // bytes of K per LDS row per k-tile
 inline int bk_elems(int dtype) { return kRowBytes / (int)esize(dtype); }   // 64 (bf16) / 32 (fp32)
 constexpr int kNPad = 128;                          // packed weight rows are padded to this multiple
+constexpr int kWBlock = 32;                         // rows of a block of a packed operand in blocks
 constexpr int kConvInK = 64;                        // padded K of the im2col'ed first convolution
 
 struct Unit {
@@ -172,6 +173,10 @@ void pack_rows(int dtype, const float* w, size_t n, void* out);   // plain conve
 // packed rows (a multiple of 16) into the order in which k_tfm_rows loads them: 16-row tiles, 64 bytes of K of a tile after the other, each
 // laid out by lane; in place
 void pack_fragments(void* packed, int rows, int row_bytes);
+
+// packed rows (a multiple of 32, of a multiple of 128 bytes) into blocks of 32 rows: the 128 bytes of a k-tile of the 32 rows side by side, k-tile after
+// k-tile; in place
+void pack_blocks(void* packed, int rows, int row_bytes);
 
 // whether a transformer block of this width and number of tokens (of all samples) runs in the row-local kernel (its weights are packed for that)
 bool tfm_rows_fits(int dtype, int c, int head_dim, int ctx_len, long long tokens);

@@ -48,6 +48,7 @@ struct ConvArgs {
   const void* x0 = nullptr; const void* x1 = nullptr;
   int xc0 = 0, xc1 = 0;
   const void* xw = nullptr;             // packed [n_pad][xc0 + xc1]
+  int w_blocks = 0;                     // w and xw are in blocks (pack_blocks()) instead of rows
 };
 // OUT_QKV: n_out = 3c; thirds go to out [m][c], out2 [m][c] and out3 ([batch][c][ld_t] when ld_t > 0, else [m][c])
 enum { OUT_ROWMAJOR = 0, OUT_GEGLU = 1, OUT_TRANSPOSED = 2, OUT_TRANSPOSED_F32 = 3, OUT_QKV = 4 };

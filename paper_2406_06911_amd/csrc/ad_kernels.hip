@@ -49,6 +49,7 @@ struct IgemmParams {
   int hs, ws, up, hin, win;
   int hout, wout, hw_out, stride, ksize, pad;
   int M, N, Kp, tiles_n, ktiles;
+  unsigned w_row, xw_row, w_kt;       // weights: bytes between the rows of a block of 32 (of w, of xw) and between k-tiles, see weight_at()
   const void* w; const float* bias; const float* rowvec; const void* residual;
   void* out; int out_mode; int ld_t; int rowvec_ld;
   unsigned bytes0, bytes1, bytes_w;   // sizes of the two sources and of the packed weights
@@ -73,6 +74,16 @@ struct IgemmParams {
 // tiles, and what its L2 takes in per k-tile is the rows of that block plus its columns.  Bands of one row tile: a slice
 // of the activations and every weight; one band: a slice of the weights and every activation; between them (see
 // best_band()) the blocks are about square.
+// Byte offset of a row of a packed operand within a k-tile (k-tile kt is kt * p.w_kt further).  Two layouts: rows of k_bytes one after the other
+// (ad_pack_conv_weight), or blocks of 32 rows with the 128 bytes of a k-tile of the rows side by side, k-tile after k-tile (pack_blocks(), what a
+// loaded model holds).  The workgroups of a launch walk K side by side, so at any time they ask for one k-tile of all rows: in rows these are pieces of
+// 128 bytes at a pitch of k_bytes, which for K = 1280, 2560, 5120 fall on half, a quarter, an eighth of the channels of an L2 and of memory; in blocks
+// they are runs of 4 KiB.  Weights from memory, us (rows -> blocks): 2048x1280x5120 46.8 -> 43.2, 2048x1280x1280 15.3 -> 14.3, 8192x640x2560 35.4 -> 33.3,
+// 1152x1280x5120 33.0 -> 30.7, 720x640x2560 13.2 -> 12.3, 3x3 4608x640x11520 82.5 -> 78.5; K = 320 and 640, whose pitch falls on all channels, level.
+// Blocks of all rows (one run per k-tile): as fast for long K, 2-4 % slower for K = 320 and 640.
+__device__ __forceinline__ unsigned weight_at(int row, unsigned k_bytes, unsigned row_bytes) {
+  return (unsigned)(row >> 5) * (32u * k_bytes) + (unsigned)(row & 31) * row_bytes;
+}
 struct TileId { int m_tile, n_tile, split; };
 __device__ __forceinline__ TileId tile_of(const IgemmParams& p) {
   const int tiles = p.tiles_m * p.tiles_n;
@@ -444,7 +455,7 @@ __global__ __launch_bounds__(256) void k_igemm(IgemmParams p) {
   }
   unsigned b_off[BV];
 #pragma unroll
-  for (int i = 0; i < BV; ++i) b_off[i] = (unsigned)((n0 + vrow + 32 * i) * p.Kp + vcol * (16 / ES)) * ES;
+  for (int i = 0; i < BV; ++i) b_off[i] = weight_at(n0 + vrow + 32 * i, (unsigned)p.Kp * ES, p.w_row) + vcol * 16;
 
   // byte offsets of this thread's A vectors for the tap being fetched (kOob = reads zeros)
   unsigned a_off0[AV], a_off1[AV];
@@ -467,8 +478,9 @@ __global__ __launch_bounds__(256) void k_igemm(IgemmParams p) {
   // this workgroup's range of k-tiles (all of them unless the launch splits K along grid.y)
   const int kt_begin = tid3.split * p.kt_per_split;
   const int nkt = min(p.ktiles - kt_begin, p.kt_per_split);
-  int f_k0 = kt_begin * BK;              // position of the next k-tile to fetch
+  const int f_k0 = kt_begin * BK;        // position of the next k-tile to fetch
   int f_tap = f_k0 / p.ctot, f_cc = f_k0 - f_tap * p.ctot;
+  unsigned f_w = kt_begin * p.w_kt;      // and of its weights
   set_tap(f_tap);
   auto fetch = [&](V (&ar)[AV], V (&br)[BV]) {
     if (f_cc < p.c0) {
@@ -479,8 +491,8 @@ __global__ __launch_bounds__(256) void k_igemm(IgemmParams p) {
       for (int i = 0; i < AV; ++i) ar[i] = buffer_load16<V>(rs1, a_off1[i], (unsigned)((f_cc - p.c0) * ES));
     }
 #pragma unroll
-    for (int i = 0; i < BV; ++i) br[i] = buffer_load16<V>(rsw, b_off[i], (unsigned)(f_k0 * ES));
-    f_k0 += BK;
+    for (int i = 0; i < BV; ++i) br[i] = buffer_load16<V>(rsw, b_off[i], f_w);
+    f_w += p.w_kt;
     f_cc += BK;
     if (f_cc >= p.ctot) {
       f_cc = 0;
@@ -631,7 +643,7 @@ __global__ __launch_bounds__(64 * WM * WN * KG, p3_waves_per_simd(BM, BN, WM * W
   const unsigned grp = (unsigned)wave * 8 * kRowBytes;
   // load i of the weights is RND rows after load 0; large tiles form its offset anew each time, for want of registers
   constexpr bool TIGHT = TM * TN * 16 > 128;
-  unsigned b_row0 = (unsigned)((n0 + wave * 8 + r8) * p.Kp + scol * VN) * ES, b_step = (unsigned)(RND * p.Kp) * ES;
+  unsigned b_row0 = weight_at(n0 + wave * 8 + r8, (unsigned)p.Kp * ES, p.w_row) + scol * 16, b_step = (unsigned)(RND * p.Kp) * ES;
   unsigned b_off[TIGHT ? 1 : BG];
   if constexpr (!TIGHT) {
 #pragma unroll
@@ -654,10 +666,10 @@ __global__ __launch_bounds__(64 * WM * WN * KG, p3_waves_per_simd(BM, BN, WM * W
       for (int i = 0; i < BG; ++i) {
         if (XTRA && kt_begin + t >= p.kt_main) {
           const int xk = p.xc0 + p.xc1;
-          dma_load16(make_rsrc_words(p.xw, p.xbytes_w), (unsigned)((n0 + wave * 8 + r8 + i * RND) * xk + scol * VN) * ES,
-                     (unsigned)((kt_begin + t - p.kt_main) * BK * ES), lds_base + t * STAGE + grp + (BM + i * RND) * kRowBytes);
+          dma_load16(make_rsrc_words(p.xw, p.xbytes_w), weight_at(n0 + wave * 8 + r8 + i * RND, (unsigned)xk * ES, p.xw_row) + scol * 16,
+                     (unsigned)(kt_begin + t - p.kt_main) * p.w_kt, lds_base + t * STAGE + grp + (BM + i * RND) * kRowBytes);
         } else {
-          dma_load16(rsw, b_at(i), (unsigned)((kt_begin + t) * BK * ES), lds_base + t * STAGE + grp + (BM + i * RND) * kRowBytes);
+          dma_load16(rsw, b_at(i), (unsigned)(kt_begin + t) * p.w_kt, lds_base + t * STAGE + grp + (BM + i * RND) * kRowBytes);
         }
       }
     }
@@ -699,7 +711,8 @@ __global__ __launch_bounds__(64 * WM * WN * KG, p3_waves_per_simd(BM, BN, WM * W
       a_off[i] = (a_taps[i] >> tap & 1) ? ((unsigned)pix * c + scol * VN) * ES : kOob;
     }
   };
-  int f_k0 = kt_begin * BK;
+  const int f_k0 = kt_begin * BK;
+  unsigned f_w = (unsigned)kt_begin * p.w_kt;
   int f_tap = __builtin_amdgcn_readfirstlane(f_k0 / p.ctot);    // the division is vector work; what follows from it must not be
   int f_cc = f_k0 - f_tap * p.ctot;
   unsigned c0 = (unsigned)p.c0, c1 = (unsigned)p.c1;
@@ -709,7 +722,7 @@ __global__ __launch_bounds__(64 * WM * WN * KG, p3_waves_per_simd(BM, BN, WM * W
     rs0 = make_rsrc_words(p.x0, p.xbytes0); rs1 = make_rsrc_words(p.x1, p.xbytes1); rsw = make_rsrc_words(p.xw, p.xbytes_w);
     c0 = (unsigned)p.xc0; c1 = (unsigned)p.xc1;
     s_c0 = p.xc0; s_ctot = p.xc0 + p.xc1;
-    b_row0 = (unsigned)((n0 + wave * 8 + r8) * s_ctot + scol * VN) * ES;
+    b_row0 = weight_at(n0 + wave * 8 + r8, (unsigned)s_ctot * ES, p.xw_row) + scol * 16;
     b_step = (unsigned)(RND * s_ctot) * ES;
     if constexpr (!TIGHT) {
 #pragma unroll
@@ -719,7 +732,8 @@ __global__ __launch_bounds__(64 * WM * WN * KG, p3_waves_per_simd(BM, BN, WM * W
   auto pixel_tap = [&](int tap) { return XTRA && tap >= 9 ? 4 : tap; };
   if (XTRA && kt_begin >= p.kt_main) {
     begin_extra();
-    f_k0 = f_cc = (kt_begin - p.kt_main) * BK;
+    f_cc = (kt_begin - p.kt_main) * BK;
+    f_w = (unsigned)(kt_begin - p.kt_main) * p.w_kt;
     f_tap = 9;
   }
   set_tap(pixel_tap(f_tap), f_cc >= s_c0 ? c1 : c0);
@@ -730,7 +744,7 @@ __global__ __launch_bounds__(64 * WM * WN * KG, p3_waves_per_simd(BM, BN, WM * W
     const bool second = f_cc >= s_c0;
     rsa = second ? rs1 : rs0;
     soff_a = (unsigned)((second ? f_cc - s_c0 : f_cc) * ES);
-    soff_b = (unsigned)(f_k0 * ES);
+    soff_b = f_w;
   };
   auto issue_one = [&](int stage, int i) {
     const unsigned st = lds_base + stage * STAGE + grp;
@@ -738,13 +752,13 @@ __global__ __launch_bounds__(64 * WM * WN * KG, p3_waves_per_simd(BM, BN, WM * W
     else dma_load16(rsw, b_at(i - AG), soff_b, st + (BM + (i - AG) * RND) * kRowBytes);
   };
   auto end_tile = [&]() {
-    f_k0 += BK;
+    f_w += p.w_kt;
     f_cc += BK;
     if (f_cc == s_c0 || f_cc == s_ctot) {                    // the next source (c0 and ctot are multiples of the k-tile) or the next tap
       const int wrap = f_cc == s_ctot ? 1 : 0;
       f_cc = wrap ? 0 : f_cc;
       f_tap += wrap;
-      if (XTRA && wrap && f_tap == 9) { begin_extra(); f_k0 = 0; }
+      if (XTRA && wrap && f_tap == 9) { begin_extra(); f_w = 0; }
       set_tap(pixel_tap(f_tap), wrap ? c0 : c1);             // behind the last tap nothing is fetched any more
     }
   };
@@ -934,7 +948,7 @@ __global__ __launch_bounds__(512) void k_igemm_small(IgemmParams p) {
   unsigned a_off0[TM], a_off1[TM], a_taps[TM], b_off[TN];
   int a_par[TM];                                         // nearest-2x input: row and column parity of tap (0, 0)
 #pragma unroll
-  for (int j = 0; j < TN; ++j) b_off[j] = (unsigned)((n0 + 16 * j + r16) * p.Kp + kg * VN) * ES;
+  for (int j = 0; j < TN; ++j) b_off[j] = weight_at(n0 + 16 * j + r16, (unsigned)p.Kp * ES, p.w_row) + kg * 16;
 #pragma unroll
   for (int i = 0; i < TM; ++i) {
     const int m = m0 + 16 * i + r16;
@@ -959,11 +973,12 @@ __global__ __launch_bounds__(512) void k_igemm_small(IgemmParams p) {
   const __amdgpu_buffer_rsrc_t rsw = make_rsrc(p.w, p.bytes_w);
 
   const int mine = (p.ktiles - wave + NW - 1) / NW;      // k-tiles of this wavefront (0 when there are fewer k-tiles than wavefronts)
-  int f_k = wave * BK, f_tap = f_k / p.ctot, f_cc = f_k - f_tap * p.ctot;
+  int f_tap = wave * BK / p.ctot, f_cc = wave * BK - f_tap * p.ctot;
+  unsigned f_w = (unsigned)wave * p.w_kt;
   V af[PF][TM][2], bf[PF][TN][2];
   auto fetch = [&](int s) {
     const int u = p.ksize == 3 ? f_tap / 3 : 0, v = p.ksize == 3 ? f_tap - 3 * u : 0;
-    const unsigned bit = 1u << (u * 3 + v), sb = (unsigned)f_k * ES;
+    const unsigned bit = 1u << (u * 3 + v), sb = f_w;
 #pragma unroll
     for (int j = 0; j < TN; ++j)
 #pragma unroll
@@ -981,7 +996,7 @@ __global__ __launch_bounds__(512) void k_igemm_small(IgemmParams p) {
 #pragma unroll
       for (int h = 0; h < 2; ++h) af[s][i][h] = second ? buffer_load16<V>(rs1, o + h * 64, sc) : buffer_load16<V>(rs0, o + h * 64, sc);
     }
-    f_k += BK * NW; f_cc += BK * NW;
+    f_w += NW * p.w_kt; f_cc += BK * NW;
     while (f_cc >= p.ctot) { f_cc -= p.ctot; ++f_tap; }
   };
 #pragma unroll
@@ -1201,9 +1216,9 @@ __global__ __launch_bounds__(256) void k_conv3_halo(IgemmParams p, HaloParams hp
   };
   unsigned b_off[BG];
 #pragma unroll
-  for (int i = 0; i < BG; ++i) b_off[i] = (unsigned)((n0 + (4 * i + wave) * 8 + r8) * p.Kp + scol * 8) * 2;
+  for (int i = 0; i < BG; ++i) b_off[i] = weight_at(n0 + (4 * i + wave) * 8 + r8, (unsigned)p.Kp * 2, p.w_row) + scol * 16;
   auto issue_b = [&](int chunk, int tap, int stage) {
-    const unsigned soff = __builtin_amdgcn_readfirstlane((unsigned)((tap * p.ctot + chunk * 64) * 2));
+    const unsigned soff = __builtin_amdgcn_readfirstlane((unsigned)(tap * nchunks + chunk) * p.w_kt);
 #pragma unroll
     for (int i = 0; i < BG; ++i)
       dma_load16(rsw, b_off[i], soff, __builtin_amdgcn_readfirstlane(lds_base + 2 * abytes + stage * BSTAGE + (4 * i + wave) * 1024));
@@ -1629,6 +1644,9 @@ ad_status launch_conv(const ConvArgs& a, hipStream_t s) {
     p.xbytes1 = a.xc1 ? (unsigned)(pixels * a.xc1 * es) : p.xbytes0;
     p.xbytes_w = (unsigned)wb;
   }
+  p.w_row = a.w_blocks ? kRowBytes : (unsigned)p.Kp * (unsigned)esize(a.dtype);
+  p.xw_row = a.w_blocks ? kRowBytes : (unsigned)(p.xc0 + p.xc1) * (unsigned)esize(a.dtype);
+  p.w_kt = a.w_blocks ? kWBlock * kRowBytes : kRowBytes;
   p.ktiles = p.kt_main + (p.xc0 + p.xc1) / bk;
   p.k_prof = a.k_real > 0 ? a.k_real : p.Kp;
   p.w = a.w; p.bias = a.bias; p.rowvec = a.rowvec; p.residual = a.residual;

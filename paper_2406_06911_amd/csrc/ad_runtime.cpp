@@ -62,6 +62,7 @@ struct Eval {
     WView wv{c};
     ConvArgs a{dt, src0, src1, c0, c1, c.cfg.batch, hs, wsz, up, ksize, stride, wv.at(w_idx), c.weights[w_idx].info.shape[0],
                b_idx >= 0 ? wv.f32(b_idx) : nullptr, rowvec, proj_ld, residual, dst, mode, ld_t, temp(9), ws.temp_bytes[9]};
+    a.w_blocks = 1;
     return launch_conv(a, s);
   }
   // linear layer on a [rows][cin] matrix
@@ -70,6 +71,7 @@ struct Eval {
     WView wv{c};
     ConvArgs a{dt, src, nullptr, cin, 0, batch, rows / batch, 1, 0, 1, 1, wv.at(w_idx), c.weights[w_idx].info.shape[0],
                b_idx >= 0 ? wv.f32(b_idx) : nullptr, nullptr, 0, residual, dst, mode, ld_t, temp(9), ws.temp_bytes[9]};
+    a.w_blocks = 1;
     return launch_conv(a, s);
   }
   ad_status gn(const void* src0, const void* src1, int c0, int c1, int hw, int g_idx, int silu, void* dst) const {
@@ -100,6 +102,7 @@ struct Eval {
       ConvArgs a{dt, temp(0), nullptr, f.c_out, 0, c.cfg.batch, f.h_in, f.w_in, 0, 3, 1, wv.at(w0 + 8), f.c_out, wv.f32(w0 + 9), wv.f32(w0 + 11), -1,
                  nullptr, tensor_out(ui), OUT_ROWMAJOR, 0, temp(9), ws.temp_bytes[9]};
       a.x0 = x0; a.x1 = x1; a.xc0 = f.c_in; a.xc1 = f.c_skip; a.xw = wv.at(w0 + 10);
+      a.w_blocks = 1;
       return launch_conv(a, s);
     }
     if (ci != f.c_out) {
@@ -186,6 +189,7 @@ struct Eval {
         WView wv{c};
         ConvArgs a{dt, temp(0), nullptr, Cc, 0, B, L, 1, 0, 1, 1, wv.at(w + 2), 3 * Cc, nullptr, nullptr, 0, nullptr, temp(2), OUT_QKV,
                    vt ? lp : 0, temp(9), ws.temp_bytes[9], temp(3), temp(4)};
+        a.w_blocks = 1;
         AD_TRY(launch_conv(a, s));
       }
       AD_TRY(launch_attention(dt, temp(2), temp(3), temp(4), vt, B, L, L, Cc, d, Cc, Cc, vt ? lp : Cc, Cc, temp(5), s));
@@ -219,6 +223,7 @@ struct Eval {
       WView wv{c};
       ConvArgs a{dt, temp(0), nullptr, Cc, 0, B, L, 1, 0, 1, 1, wv.at(w + 2), 3 * Cc, nullptr, nullptr, 0, nullptr, temp(2), OUT_QKV,
                  0, temp(9), ws.temp_bytes[9], temp(3), temp(4)};
+      a.w_blocks = 1;
       AD_TRY(launch_conv(a, s));
     }
     AD_TRY(launch_attention_frames(dt, temp(2), temp(3), temp(4), c.cfg.frames, L, Cc, c.cfg.temporal_heads, Cc, Cc, Cc, Cc, temp(5), s));
@@ -281,6 +286,7 @@ static ad_status run_component(Ctx& c, int comp, int lane, const void* const* in
           ConvArgs a{e.dt, e.temp(0), nullptr, kConvInK, 0, g.batch, g.height, g.width, 0, 1, 1, wv.at(u.w_first), c.weights[u.w_first].info.shape[0],
                      wv.f32(u.w_first + 1), nullptr, 0, nullptr, e.tensor_out(ui), OUT_ROWMAJOR, 0, e.temp(9), e.ws.temp_bytes[9]};
           a.k_real = 9 * g.latent_channels;
+          a.w_blocks = 1;
           AD_TRY(launch_conv(a, s));
         }
         break;
@@ -411,6 +417,12 @@ ad_status ad_load_weights(ad_ctx* ctx, const float* const* host_ptrs, int n) {
   std::vector<char> stage;
   for (int i = 0; i < n; ++i)
     if (!host_ptrs[i]) AD_FAIL(AD_ERR_INVALID, "weight %d (%s) is null", i, c.weights[i].info.name);
+  // a packed operand leaves the rows it was packed in for the order its kernel reads
+  auto arrange = [&](const Weight& w) {
+    if (w.n_pad == 0) return;
+    if (w.fragments) pack_fragments(stage.data(), w.n_pad, w.k_pad * (int)esize(dt));
+    else pack_blocks(stage.data(), w.n_pad, w.k_pad * (int)esize(dt));
+  };
   // the fused time-projection matrix is assembled from the ResBlocks' rows
   std::vector<char> temb_w((size_t)c.temb_rows_total * c.temb_dim * esize(dt));
   std::vector<float> temb_b((size_t)c.temb_rows_total);
@@ -430,7 +442,7 @@ ad_status ad_load_weights(ad_ctx* ctx, const float* const* host_ptrs, int n) {
       for (int j = 0; j < 3; ++j) std::memcpy(cat.data() + j * each, host_ptrs[i + j], each * 4);
       stage.assign(w.dev_bytes, 0);
       pack_conv(dt, cat.data(), 3 * sh[0], sh[1], 1, false, stage.data());
-      if (w.fragments) pack_fragments(stage.data(), w.n_pad, w.k_pad * (int)esize(dt));
+      arrange(w);
       AD_HIP(hipMemcpy(c.weights_dev + w.dev_off, stage.data(), w.dev_bytes, hipMemcpyHostToDevice));
       continue;
     }
@@ -466,7 +478,7 @@ ad_status ad_load_weights(ad_ctx* ctx, const float* const* host_ptrs, int n) {
       }
       default: break;
     }
-    if (w.fragments) pack_fragments(stage.data(), w.n_pad, w.k_pad * (int)esize(dt));
+    arrange(w);
     AD_HIP(hipMemcpy(c.weights_dev + w.dev_off, stage.data(), w.dev_bytes, hipMemcpyHostToDevice));
   }
   if (c.temb_rows_total > 0) {

@@ -48,3 +48,12 @@ def check_blocks(monkeypatch, dtype, tile, channels, height, width, batch, wante
     (-1, [320, 320], 48, 46, 2)])
 def test_shortcut_inside_the_second_convolution(monkeypatch, tile, channels, height, width, batch):
     check_blocks(monkeypatch, B.AD_BF16, tile, channels, height, width, batch, lambda u: u.c_in + u.c_skip != u.c_out)
+
+
+@pytest.mark.parametrize("dtype,tile,channels,height,width,batch", [
+    (B.AD_BF16, t, [128, 192], 22, 14, 2) for t in (1, 3, 8, 9, 10, 11, 12)] + [
+    (B.AD_F32, t, [64, 96], 22, 14, 1) for t in (1, 3, -1)] + [
+    (B.AD_BF16, -1, [64, 128], 8, 6, 1), (B.AD_BF16, 15, [64, 448], 12, 10, 1), (B.AD_F32, -1, [32, 64], 6, 4, 1)])
+def test_weights_in_blocks_in_every_kernel(monkeypatch, dtype, tile, channels, height, width, batch):
+    """The kernel families that the test above leaves out read a model's weights in blocks of 32 rows; tiles that end beyond the padded rows."""
+    check_blocks(monkeypatch, dtype, tile, channels, height, width, batch, lambda u: True)
