@@ -397,10 +397,10 @@ void fold_layernorm(const float* w, int rows, int cols, const float* gain, const
   }
 }
 
-float bf16_row_sum(const uint16_t* row, int n) {
+float packed_row_sum(int dtype, const void* row, int n) {
   double s = 0.0;
   for (int k = 0; k < n; ++k) {
-    const uint32_t u = (uint32_t)row[k] << 16;
+    const uint32_t u = dtype == AD_BF16 ? (uint32_t)((const uint16_t*)row)[k] << 16 : ((const uint32_t*)row)[k];
     float f;
     std::memcpy(&f, &u, 4);
     s += f;
@@ -530,7 +530,7 @@ static void plan_work(Ctx& c) {
           want(6, m_in * 4 * C * es);
           want(7, B * g.ctx_len * C * es);
           want(8, B * C * lkp * es);
-          if (g.dtype == AD_BF16 && !tfm_rows_fits(g.dtype, (int)C, g.head_dim, g.ctx_len, (long long)m_in)) want(10, m_in * C / 16 * 8);      // sums of the rows for a LayerNorm
+          if (!tfm_rows_fits(g.dtype, (int)C, g.head_dim, g.ctx_len, (long long)m_in)) want(10, m_in * C / 16 * 8);      // sums of the rows for a LayerNorm
           gemm(m_in, (int)C, (int)C);
           gemm(m_in, (int)(3 * C), (int)C, OUT_QKV);
           gemm(m_in, (int)C, (int)(4 * C));

@@ -176,7 +176,7 @@ void pack_rows(int dtype, const float* w, size_t n, void* out);   // plain conve
 inline int geglu_row(int r, int n) { return r % 64 < 32 ? r / 64 * 32 + r % 64 : n / 2 + r / 64 * 32 + r % 64 - 32; }   // row behind packed row r: 32 value, 32 gate
 // a LayerNorm's gain into the columns of w [rows][cols], its offset into the bias (null: none)
 void fold_layernorm(const float* w, int rows, int cols, const float* gain, const float* offset, const float* bias, float* out_w, float* out_b);
-float bf16_row_sum(const uint16_t* row, int n);
+float packed_row_sum(int dtype, const void* row, int n);
 // packed rows (a multiple of 16) into the order in which k_tfm_rows loads them: 16-row tiles, 64 bytes of K of a tile after the other, each
 // laid out by lane; in place
 void pack_fragments(void* packed, int rows, int row_bytes);

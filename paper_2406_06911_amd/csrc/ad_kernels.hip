@@ -180,11 +180,18 @@ __device__ __forceinline__ void ln_add(const bf16x2 v, float& sum, float& sq) {
 }
 // Sums of what LANES neighbouring lanes (4 or 8) hold of a row; the first of them writes the pair.
 template <int LANES>
-__device__ __forceinline__ void ln_emit(const LnOut& o, float sum, float sq, int row, int col, int lane) {
-  sum += dpp_f<0xB1>(sum); sq += dpp_f<0xB1>(sq);            // quad_perm 1 0 3 2
-  sum += dpp_f<0x4E>(sum); sq += dpp_f<0x4E>(sq);            // quad_perm 2 3 0 1
-  if (LANES == 8) { sum += dpp_f<0x141>(sum); sq += dpp_f<0x141>(sq); }        // row_half_mirror
+__device__ __forceinline__ float ln_lanes(float v) {
+  v += dpp_f<0xB1>(v);                                       // quad_perm 1 0 3 2
+  v += dpp_f<0x4E>(v);                                       // quad_perm 2 3 0 1
+  return LANES == 8 ? v + dpp_f<0x141>(v) : v;               // row_half_mirror
+}
+template <int LANES>
+__device__ __forceinline__ void ln_store(const LnOut& o, float sum, float sq, int row, int col, int lane) {
   if (lane % LANES == 0) *(f32x2*)(o.pairs + 2 * ((size_t)row * o.slabs + (col >> o.shift))) = f32x2{sum, sq};
+}
+template <int LANES>
+__device__ __forceinline__ void ln_emit(const LnOut& o, float sum, float sq, int row, int col, int lane) {
+  ln_store<LANES>(o, ln_lanes<LANES>(sum), ln_lanes<LANES>(sq), row, col, lane);
 }
 // A thread's pairs of a row (two at a time, TPR threads a row), L loads at once, and their fold: scale and shift of the row.
 template <int TPR, int L>
@@ -196,22 +203,40 @@ __device__ __forceinline__ void ln_load(const IgemmParams& p, int row, int sub, 
     v[i] = 2 * at < p.ln_slabs ? src[at] : f32x4{0.f, 0.f, 0.f, 0.f};
   }
 }
-template <int TPR, int L>
+template <int TPR>
+__device__ __forceinline__ float ln_threads(float v) {
+  if (TPR >= 2) v += dpp_f<0xB1>(v);
+  if (TPR >= 4) v += dpp_f<0x4E>(v);
+  if (TPR >= 8) v += dpp_f<0x141>(v);
+  if (TPR >= 16) v += dpp_f<0x140>(v);                       // row_mirror
+  if (TPR >= 32) v += __shfl_xor(v, 16, 64);
+  return v;
+}
+// CENTRED (fp32): the pairs are (sum, squared deviations from their own mean), so that an offset of the row does not cancel; all of a thread's pairs
+// are in v (the host checks that).  bf16: (sum, sum of squares), whose cancellation stays below the rounding of the values themselves.
+template <int TPR, bool CENTRED, int L>
 __device__ __forceinline__ void ln_fold(const IgemmParams& p, int row, int sub, f32x4 (&v)[L], float* out, int pitch) {
   float sum = 0.f, sq = 0.f;
   for (int from = 0;;) {
 #pragma unroll
     for (int i = 0; i < L; ++i) { sum += v[i][0] + v[i][2]; sq += v[i][1] + v[i][3]; }
     from += L * TPR;
-    if (2 * from >= p.ln_slabs) break;
+    if (CENTRED || 2 * from >= p.ln_slabs) break;
     ln_load<TPR>(p, row, sub, from, v);
   }
-  if (TPR >= 2) { sum += dpp_f<0xB1>(sum); sq += dpp_f<0xB1>(sq); }
-  if (TPR >= 4) { sum += dpp_f<0x4E>(sum); sq += dpp_f<0x4E>(sq); }
-  if (TPR >= 8) { sum += dpp_f<0x141>(sum); sq += dpp_f<0x141>(sq); }
-  if (TPR >= 16) { sum += dpp_f<0x140>(sum); sq += dpp_f<0x140>(sq); }           // row_mirror
-  if (TPR >= 32) { sum += __shfl_xor(sum, 16, 64); sq += __shfl_xor(sq, 16, 64); }
-  const float mean = sum * p.ln_inv, var = fmaf(sq, p.ln_inv, -mean * mean), scale = rsqrtf((var < 0.f ? 0.f : var) + p.ln_eps);      // NaN stays NaN
+  sum = ln_threads<TPR>(sum);
+  const float mean = sum * p.ln_inv;
+  if (CENTRED) {
+    const float width = 1.f / (p.ln_inv * p.ln_slabs), per = p.ln_inv * p.ln_slabs;       // columns of a pair (16 or 32) and its reciprocal
+#pragma unroll
+    for (int i = 0; i < L; ++i)
+      if (2 * (sub + i * TPR) < p.ln_slabs) {
+        const float d0 = v[i][0] * per - mean, d1 = v[i][2] * per - mean;
+        sq = fmaf(width * d0, d0, fmaf(width * d1, d1, sq));
+      }
+  }
+  sq = ln_threads<TPR>(sq);
+  const float var = CENTRED ? sq * p.ln_inv : fmaf(sq, p.ln_inv, -mean * mean), scale = rsqrtf((var < 0.f ? 0.f : var) + p.ln_eps);      // NaN stays NaN
   if (sub == 0) { out[0] = scale; out[pitch] = -mean * scale; }
 }
 
@@ -904,7 +929,7 @@ __global__ __launch_bounds__(64 * WM * WN * KG, p3_waves_per_simd(BM, BN, WM * W
     if (PHASE == 2) end_tile();
     stage = next;
   };
-  if constexpr (LN && TIGHT) ln_fold<TPR>(p, m0 + tid / TPR, tid % TPR, ln_in, ln_rows + tid / TPR, BM);
+  if constexpr (LN && TIGHT) ln_fold<TPR, !std::is_same<T, bf16>::value>(p, m0 + tid / TPR, tid % TPR, ln_in, ln_rows + tid / TPR, BM);
   // issue order so far: B(0), B(1), A(0), A(1): tile 0 is complete once only A(1) is outstanding
   if (nkt >= NSTAGE - 1) wait_vmcnt<(NSTAGE - 2) * AG>(); else wait_vmcnt<0>();
   __syncthreads();
@@ -914,7 +939,7 @@ __global__ __launch_bounds__(64 * WM * WN * KG, p3_waves_per_simd(BM, BN, WM * W
     for (; kt + 1 < nkt; ++kt) k_tile(std::integral_constant<int, 1>{}, std::true_type{});
     k_tile(std::integral_constant<int, 0>{}, std::true_type{});
     for (int i = nkt; i < kt_each; ++i) __syncthreads();
-    if constexpr (LN && !TIGHT) ln_fold<TPR>(p, m0 + tid / TPR, tid % TPR, ln_in, ln_rows + tid / TPR, BM);
+    if constexpr (LN && !TIGHT) ln_fold<TPR, !std::is_same<T, bf16>::value>(p, m0 + tid / TPR, tid % TPR, ln_in, ln_rows + tid / TPR, BM);
     __syncthreads();
     if constexpr (KG > 1) __syncthreads();
     if constexpr (MODE == OUT_GEGLU && TN % 2 != 0) __syncthreads();      // the epilogue's exchange
@@ -926,7 +951,7 @@ __global__ __launch_bounds__(64 * WM * WN * KG, p3_waves_per_simd(BM, BN, WM * W
   for (; kt + 1 < nkt; ++kt) k_tile(std::integral_constant<int, 1>{}, std::false_type{});
   k_tile(std::integral_constant<int, 0>{}, std::false_type{});
   for (int i = nkt; i < kt_each; ++i) __syncthreads();       // every group passes the same barriers
-  if constexpr (LN && !TIGHT) ln_fold<TPR>(p, m0 + tid / TPR, tid % TPR, ln_in, ln_rows + tid / TPR, BM);
+  if constexpr (LN && !TIGHT) ln_fold<TPR, !std::is_same<T, bf16>::value>(p, m0 + tid / TPR, tid % TPR, ln_in, ln_rows + tid / TPR, BM);
   __syncthreads();     // every wavefront holds its last fragments: LDS can be reused by the epilogue
   if constexpr (KG > 1) {
     // the other groups hand over their sums, a register of all lanes at a time, behind what the epilogue stages in; added in order
@@ -1158,7 +1183,7 @@ __global__ __launch_bounds__(512) void k_igemm_small(IgemmParams p) {
   for (int i = 0; i < TM; ++i)
 #pragma unroll
     for (int j = 0; j < TN; ++j) *(f32x4*)(part + wave * (BM * PITCH) + (16 * i + r16) * PITCH + 16 * j + 4 * kg) = acc[i][j];
-  if constexpr (LN) ln_fold<TPR>(p, m0 + tid / TPR, tid % TPR, ln_in, ln_rows + tid / TPR, BM);
+  if constexpr (LN) ln_fold<TPR, !std::is_same<T, bf16>::value>(p, m0 + tid / TPR, tid % TPR, ln_in, ln_rows + tid / TPR, BM);
   __syncthreads();
   if (!live) return;
   // v[e] becomes what the norm makes of it, without the bias; row r of the tile
@@ -1217,12 +1242,19 @@ __global__ __launch_bounds__(512) void k_igemm_small(IgemmParams p) {
     ncols = c3; c_out = col - which * c3;
   }
   const size_t o = (size_t)row * ncols + c_out;
-  if constexpr (MODE == OUT_ROWMAJOR && !LN && std::is_same<T, bf16>::value)
+  if constexpr (MODE == OUT_ROWMAJOR && !LN)
     if (p.ln_out.pairs) {                                        // (whole tiles: BO / 4 lanes a row)
       float sum = 0.f, sq = 0.f;
+      if constexpr (std::is_same<T, bf16>::value) {
 #pragma unroll
-      for (int e = 0; e < 4; e += 2) ln_add(bf16x2{from_f<T>(v[e]), from_f<T>(v[e + 1])}, sum, sq);
-      ln_emit<BO / 4>(p.ln_out, sum, sq, row, col, lane);
+        for (int e = 0; e < 4; e += 2) ln_add(bf16x2{from_f<T>(v[e]), from_f<T>(v[e + 1])}, sum, sq);
+        ln_emit<BO / 4>(p.ln_out, sum, sq, row, col, lane);
+      } else {
+        sum = ln_lanes<BO / 4>((v[0] + v[1]) + (v[2] + v[3]));
+#pragma unroll
+        for (int e = 0; e < 4; ++e) { const float d = v[e] - sum * (1.f / BO); sq = fmaf(d, d, sq); }
+        ln_store<BO / 4>(p.ln_out, sum, ln_lanes<BO / 4>(sq), row, col, lane);
+      }
     }
   if ((ncols & 3) == 0) {
     *(V4*)(dst + o) = V4{from_f<T>(v[0]), from_f<T>(v[1]), from_f<T>(v[2]), from_f<T>(v[3])};
@@ -1235,7 +1267,7 @@ __global__ __launch_bounds__(512) void k_igemm_small(IgemmParams p) {
 
 template <typename T, int TM, int TN, int MODE, bool LN = false>
 static ad_status run_igemm_small(const IgemmParams& p0, const char* name, hipStream_t s) {
-  if constexpr (!LN && std::is_same<T, bf16>::value && (MODE == OUT_ROWMAJOR || MODE == OUT_QKV || MODE == OUT_GEGLU))
+  if constexpr (!LN && (MODE == OUT_ROWMAJOR || MODE == OUT_QKV || MODE == OUT_GEGLU))
     if (p0.ln_in) return run_igemm_small<T, TM, TN, MODE, true>(p0, name, s);
   if (!LN && p0.ln_in) AD_FAIL(AD_ERR_INVALID, "conv: this tile does not take a LayerNorm");
   IgemmParams p = p0;
@@ -1738,7 +1770,7 @@ bool conv_takes_shortcut(int dtype, long long m, int n, int c, int xc) {
 }
 
 // A LayerNorm over the c channels in front of a linear layer: inside the layer's launch on the LDS-DMA and small-tile kernels without K-splits, which
-// is all bf16 launches behind a LayerNorm in the SD-sized models.
+// is all bf16 launches behind a LayerNorm in the SD-sized models; fp32: on the small-tile kernels (narrow models).
 static bool ln_tile(const ConvPlan& plan, int override) {
   if (plan.splits != 1) return false;
   switch (plan.tile) {
@@ -1747,15 +1779,16 @@ static bool ln_tile(const ConvPlan& plan, int override) {
     default: return false;
   }
 }
+constexpr int kLnMostF32 = 2560;      // pairs of 16 columns: 160, all in the registers of 16 threads a row (ln_fold)
 bool ln_folds(int dtype, long long m, int n, int c, int out_mode) {
-  return dtype == AD_BF16 && c % bk_elems(dtype) == 0 && ln_tile(compute_plan(dtype, m, n, c / bk_elems(dtype), out_mode, TILE_AUTO), TILE_AUTO);
+  return c % 64 == 0 && (dtype == AD_BF16 || c <= kLnMostF32) && ln_tile(compute_plan(dtype, m, n, c / bk_elems(dtype), out_mode, TILE_AUTO), TILE_AUTO);
 }
 bool conv_takes_ln(int dtype, long long m, int n, int c, int out_mode) {
-  return dtype == AD_BF16 && c % bk_elems(dtype) == 0 && ln_tile(choose_plan(dtype, m, n, c / bk_elems(dtype), out_mode), g_tile_override);
+  return c % 64 == 0 && (dtype == AD_BF16 || c <= kLnMostF32) && ln_tile(choose_plan(dtype, m, n, c / bk_elems(dtype), out_mode), g_tile_override);
 }
 
 int conv_ln_width(int dtype, long long m, int n, int k) {
-  if (dtype != AD_BF16 || n % 64 || k % bk_elems(dtype)) return 0;
+  if (n % 64 || k % bk_elems(dtype)) return 0;
   const int ktiles = k / bk_elems(dtype), tile = choose_plan(dtype, m, n, ktiles, OUT_ROWMAJOR).tile;
   if (tile == TILE_SMALL) return small_tile(m, n, ktiles, OUT_ROWMAJOR).tn == 1 ? 16 : 32;
   return tile == TILE_128x128 || tile == TILE_64x64 ? 0 : 32;

@@ -441,7 +441,7 @@ ad_status ad_load_weights(ad_ctx* ctx, const float* const* host_ptrs, int n) {
   auto load_ln = [&](const Weight& w, const std::vector<float>& bias) -> ad_status {
     std::vector<float> v(2 * (size_t)w.n_pad, 0.f);
     for (int r = 0; r < w.n_pad; ++r) {
-      v[r] = bf16_row_sum((const uint16_t*)stage.data() + (size_t)r * w.k_pad, w.k_pad);
+      v[r] = packed_row_sum(dt, stage.data() + (size_t)r * w.k_pad * esize(dt), w.k_pad);
       const int n = w.info.shape[0];
       v[w.n_pad + r] = bias[w.role == W_GEGLU && r < n ? geglu_row(r, n) : r];
     }
