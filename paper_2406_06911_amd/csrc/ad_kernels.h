@@ -70,7 +70,7 @@ bool conv_takes_shortcut(int dtype, long long m, int n, int c, int xc);      // 
 // the weights are packed
 bool ln_folds(int dtype, long long m, int n, int c, int out_mode);
 bool conv_takes_ln(int dtype, long long m, int n, int c, int out_mode);
-// columns a pair of row sums covers when a row-major launch of this shape leaves them (16 or 32; 0: it cannot)
+// columns a pair of row sums covers when a row-major launch of this shape leaves them (16, 32 or 64; 0: it cannot)
 int conv_ln_width(int dtype, long long m, int n, int k);
 
 ad_status launch_groupnorm(int dtype, const void* src0, const void* src1, int c0, int c1, int batch, int hw, int groups,

@@ -178,12 +178,13 @@ __device__ __forceinline__ void ln_add(const bf16x2 v, float& sum, float& sq) {
   sum = __builtin_amdgcn_fdot2_f32_bf16(v, bf16x2{(bf16)1.f, (bf16)1.f}, sum, false);
   sq = __builtin_amdgcn_fdot2_f32_bf16(v, v, sq, false);
 }
-// Sums of what LANES neighbouring lanes (4 or 8) hold of a row; the first of them writes the pair.
+// Sums of what LANES neighbouring lanes (4, 8 or 16) hold of a row; the first of them writes the pair.
 template <int LANES>
 __device__ __forceinline__ float ln_lanes(float v) {
   v += dpp_f<0xB1>(v);                                       // quad_perm 1 0 3 2
   v += dpp_f<0x4E>(v);                                       // quad_perm 2 3 0 1
-  return LANES == 8 ? v + dpp_f<0x141>(v) : v;               // row_half_mirror
+  if (LANES >= 8) v += dpp_f<0x141>(v);                      // row_half_mirror
+  return LANES == 16 ? v + dpp_f<0x140>(v) : v;              // row_mirror
 }
 template <int LANES>
 __device__ __forceinline__ void ln_store(const LnOut& o, float sum, float sq, int row, int col, int lane) {
@@ -436,11 +437,12 @@ __device__ __forceinline__ void igemm_epilogue(const IgemmParams& p, f32x16 (&ac
               }
               store(dst + (size_t)row * c3, v, c3, c3 - (col - which * c3));
               if constexpr (MODE == OUT_ROWMAJOR && !LN && std::is_same<T, bf16>::value)
-                if (p.ln_out.pairs) {                              // (whole 32-column tiles, four lanes each)
+                if (p.ln_out.pairs) {                              // (whole 32- or 64-column tiles, four or eight lanes each)
                   float sum = 0.f, sq = 0.f;
 #pragma unroll
                   for (int e = 0; e < VN; e += 2) ln_add(bf16x2{from_f<T>(v[e]), from_f<T>(v[e + 1])}, sum, sq);
-                  ln_emit<4>(p.ln_out, sum, sq, row, col, lane);
+                  if (WTN == 64 && p.ln_out.shift == 6) ln_emit<8>(p.ln_out, sum, sq, row, col, lane);
+                  else ln_emit<4>(p.ln_out, sum, sq, row, col, lane);
                 }
             }
           }
@@ -1569,10 +1571,11 @@ __global__ __launch_bounds__(256) void k_splitk_reduce(const float* __restrict__
       const V4 o = V4{from_f<T>(v[0]), from_f<T>(v[1]), from_f<T>(v[2]), from_f<T>(v[3])};
       *(V4*)(dst + (size_t)row * c3 + col - which * c3) = o;
       if constexpr (std::is_same<T, bf16>::value)
-        if (ln.pairs) {                                      // (N is a multiple of 32, so eight lanes hold 32 columns of a row)
+        if (ln.pairs) {                                      // (N is a multiple of the pair's 32 or 64 columns, which eight or sixteen lanes hold)
           float sum = 0.f, sq = 0.f;
           ln_add(bf16x2{o[0], o[1]}, sum, sq); ln_add(bf16x2{o[2], o[3]}, sum, sq);
-          ln_emit<8>(ln, sum, sq, row, col, threadIdx.x);
+          if (ln.shift == 6) ln_emit<16>(ln, sum, sq, row, col, threadIdx.x);
+          else ln_emit<8>(ln, sum, sq, row, col, threadIdx.x);
         }
       continue;
     }
@@ -1791,6 +1794,9 @@ int conv_ln_width(int dtype, long long m, int n, int k) {
   if (n % 64 || k % bk_elems(dtype)) return 0;
   const int ktiles = k / bk_elems(dtype), tile = choose_plan(dtype, m, n, ktiles, OUT_ROWMAJOR).tile;
   if (tile == TILE_SMALL) return small_tile(m, n, ktiles, OUT_ROWMAJOR).tn == 1 ? 16 : 32;
+  // where a wavefront holds 64 columns: half as many pairs for the GEMM to take in (a row tile's 40 instead of 80 KiB at 1280 channels, beside 640 KiB of
+  // rows; 1024px runs 0.6 % faster, 768px and 512px 0.1 to 0.2, video level).  An even number of pairs a row, since they are loaded in twos.
+  if (n % 128 == 0 && (tile == TILE_P3_128 || tile == TILE_P3_256 || tile == TILE_D2_128)) return 64;
   return tile == TILE_128x128 || tile == TILE_64x64 ? 0 : 32;
 }
 
@@ -1840,8 +1846,8 @@ ad_status launch_conv(const ConvArgs& a, hipStream_t s) {
   p.out2 = a.out2; p.out3 = a.out3;
   p.ln_in = a.ln_in; p.ln_sum = a.ln_sum; p.ln_eps = a.ln_eps; p.ln_inv = 1.f / (float)p.Kp;
   p.ln_slabs = a.ln_in ? p.Kp / a.ln_width : 0;
-  p.ln_out = LnOut{a.ln_out, a.ln_out ? a.n_out / a.ln_width : 0, a.ln_width == 16 ? 4 : 5};
-  if ((a.ln_in || a.ln_out) && a.ln_width != 16 && a.ln_width != 32) AD_FAIL(AD_ERR_INVALID, "conv: bad LayerNorm");
+  p.ln_out = LnOut{a.ln_out, a.ln_out ? a.n_out / a.ln_width : 0, a.ln_width == 16 ? 4 : a.ln_width == 32 ? 5 : 6};
+  if ((a.ln_in || a.ln_out) && a.ln_width != 16 && a.ln_width != 32 && a.ln_width != 64) AD_FAIL(AD_ERR_INVALID, "conv: bad LayerNorm");
   if (a.ln_in && (a.ksize != 1 || a.stride != 1 || a.up || a.c1 || a.residual || a.rowvec || !a.bias || !a.ln_sum || a.xw || a.ln_out || ((uintptr_t)a.ln_in & 15) ||
                   !conv_takes_ln(a.dtype, m, a.n_out, a.c0, a.out_mode)))
     AD_FAIL(AD_ERR_INVALID, "conv: bad LayerNorm");
