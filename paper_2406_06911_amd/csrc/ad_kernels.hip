@@ -71,12 +71,6 @@ struct IgemmParams {
   LnOut ln_out;
 };
 
-// Which (row tile, column tile, split) a workgroup computes.  Workgroups go to the 8 XCDs round-robin in
-// launch order (x fastest, then y); xcd_remap turns that into 8 contiguous runs of a virtual index.  The virtual index
-// is laid out [split][band of row tiles][column tile][row tile of the band]: an XCD's run is a block of row and column
-// tiles, and what its L2 takes in per k-tile is the rows of that block plus its columns.  Bands of one row tile: a slice
-// of the activations and every weight; one band: a slice of the weights and every activation; between them (see
-// best_band()) the blocks are about square.
 // Byte offset of a row of a packed operand within a k-tile (k-tile kt is kt * p.w_kt further).  Two layouts: rows of k_bytes one after the other
 // (ad_pack_conv_weight), or blocks of 32 rows with the 128 bytes of a k-tile of the rows side by side, k-tile after k-tile (pack_blocks(), what a
 // loaded model holds).  The workgroups of a launch walk K side by side, so at any time they ask for one k-tile of all rows: in rows these are pieces of
@@ -87,6 +81,13 @@ struct IgemmParams {
 __device__ __forceinline__ unsigned weight_at(int row, unsigned k_bytes, unsigned row_bytes) {
   return (unsigned)(row >> 5) * (32u * k_bytes) + (unsigned)(row & 31) * row_bytes;
 }
+
+// Which (row tile, column tile, split) a workgroup computes.  Workgroups go to the 8 XCDs round-robin in
+// launch order (x fastest, then y); xcd_remap turns that into 8 contiguous runs of a virtual index.  The virtual index
+// is laid out [split][band of row tiles][column tile][row tile of the band]: an XCD's run is a block of row and column
+// tiles, and what its L2 takes in per k-tile is the rows of that block plus its columns.  Bands of one row tile: a slice
+// of the activations and every weight; one band: a slice of the weights and every activation; between them (see
+// best_band()) the blocks are about square.
 struct TileId { int m_tile, n_tile, split; };
 __device__ __forceinline__ TileId tile_of(const IgemmParams& p) {
   const int tiles = p.tiles_m * p.tiles_n;
