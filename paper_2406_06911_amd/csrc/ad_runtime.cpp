@@ -74,7 +74,7 @@ struct Eval {
     a.w_blocks = 1;
     if (width) {
       *width = 0;
-      if (c.weights[next].ln >= 0 && (((uintptr_t)dst | (uintptr_t)residual) & 15) == 0) *width = conv_ln_width(dt, rows, a.n_out, cin);
+      if ((dt == AD_F32 || c.weights[next].ln >= 0) && (((uintptr_t)dst | (uintptr_t)residual) & 15) == 0) *width = conv_ln_width(dt, rows, a.n_out, cin);
       if (*width) { a.ln_out = (float*)temp(10); a.ln_width = *width; }
     }
     return launch_conv(a, s);
@@ -89,7 +89,7 @@ struct Eval {
     return launch_layernorm(dt, src, rows, ch, wv.f32(g_idx), wv.f32(g_idx + 1), c.cfg.ln_eps, dst, s);
   }
 
-  // the linear layer w_idx behind a LayerNorm of h, in one launch where the norm is in its weights, the launch's tile takes it and the launch that
+  // the linear layer w_idx behind a LayerNorm of h, in one launch where the norm is in its weights (fp32: its gain need not be), the launch's tile takes it and the launch that
   // wrote h has left the sums of its rows (width: columns a pair of them covers, else 0); a.bias is the layer's own bias
   ad_status ln_linear(const void* h, int rows, int ch, int g_idx, int w_idx, int width, ConvArgs a) const {
     WView wv{c};
@@ -98,8 +98,9 @@ struct Eval {
     a.w = wv.at(w_idx);
     a.w_blocks = 1;
     if (folded) a.bias = folded + w.n_pad;
-    if (folded && width && conv_takes_ln(dt, rows, a.n_out, ch, a.out_mode)) {
+    if ((folded || dt == AD_F32) && width && conv_takes_ln(dt, rows, a.n_out, ch, a.out_mode)) {
       a.src0 = h; a.ln_in = (const float*)temp(10); a.ln_width = width; a.ln_sum = folded; a.ln_eps = c.cfg.ln_eps;
+      if (!folded) { a.ln_gain = wv.f32(g_idx); a.ln_offset = wv.f32(g_idx + 1); }
       return launch_conv(a, s);
     }
     AD_TRY(ln(h, rows, ch, g_idx, temp(0)));
