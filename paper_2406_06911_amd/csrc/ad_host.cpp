@@ -317,21 +317,6 @@ static void build_manifest(Ctx& c) {
             auto ends = [&](const char* t) { const size_t l = std::strlen(t); return nm.size() >= l && nm.compare(nm.size() - l, l, t) == 0; };
             w.fragments = (w.role == W_CONV1 || w.role == W_GEGLU || w.role == W_QKV_Q) && !ends(".attn2.k.w") && !ends(".attn2.v.w") && !ends(".temp.o.w");
           }
-        else {
-          // LayerNorms that go into the linear layer behind them: gain and offset at `ln`, the layer at `w`
-          auto fold = [&](size_t ln, size_t w, int n, int mode) {
-            if (!ln_folds(g.dtype, (long long)g.batch * f.h_in * f.w_in, n, C, mode)) return;
-            c.weights[w].ln = (int)ln;
-            c.weights[ln].absorbed = c.weights[ln + 1].absorbed = true;
-          };
-          size_t w = first + 4;
-          for (int k = 0; k < f.depth; ++k, w += 20) {
-            fold(w + 0, w + 2, 3 * C, OUT_QKV);
-            fold(w + 7, w + 9, C, OUT_ROWMAJOR);
-            fold(w + 14, w + 16, 8 * C, OUT_GEGLU);
-          }
-          if (g.temporal_heads > 0) fold(w + 2, w + 4, 3 * C, OUT_QKV);
-        }
         break;
       }
     }
@@ -363,9 +348,13 @@ void pack_conv(int dtype, const float* w, int n_out, int c_in, int ksize, bool g
   const int taps = ksize * ksize;
   const int kp = round_up(taps * c_in, bk_elems(dtype));
   std::memset(out, 0, packed_conv_bytes(dtype, n_out, c_in, ksize));
+  const int half = n_out / 2;
   for (int r = 0; r < n_out; ++r) {
     int src = r;
-    if (geglu) src = geglu_row(r, n_out);
+    if (geglu) {   // packed rows alternate 32 value rows, 32 gate rows
+      const int blk = r / 64, in = r % 64;
+      src = in < 32 ? blk * 32 + in : half + blk * 32 + in - 32;
+    }
     const float* ws = w + (size_t)src * c_in * taps;
     for (int t = 0; t < taps; ++t)
       for (int i = 0; i < c_in; ++i) put(dtype, out, (size_t)r * kp + (size_t)t * c_in + i, ws[(size_t)i * taps + t]);
@@ -383,29 +372,6 @@ void pack_fragments(void* packed, int rows, int row_bytes) {
       }
     std::memcpy(tile, t.data(), t.size());
   }
-}
-
-void fold_layernorm(const float* w, int rows, int cols, const float* gain, const float* offset, const float* bias, float* out_w, float* out_b) {
-  for (int r = 0; r < rows; ++r) {
-    const float* src = w + (size_t)r * cols;
-    double b = bias ? bias[r] : 0.0;
-    for (int k = 0; k < cols; ++k) {
-      out_w[(size_t)r * cols + k] = src[k] * gain[k];
-      b += (double)src[k] * offset[k];
-    }
-    out_b[r] = (float)b;
-  }
-}
-
-float packed_row_sum(int dtype, const void* row, int n) {
-  double s = 0.0;
-  for (int k = 0; k < n; ++k) {
-    const uint32_t u = dtype == AD_BF16 ? (uint32_t)((const uint16_t*)row)[k] << 16 : ((const uint32_t*)row)[k];
-    float f;
-    std::memcpy(&f, &u, 4);
-    s += f;
-  }
-  return (float)s;
 }
 
 void pack_blocks(void* packed, int rows, int row_bytes) {
@@ -452,7 +418,6 @@ static void plan_weights(Ctx& c) {
     w.dev_off = off;
     w.dev_bytes = bytes;
     off += align_up(bytes);
-    if (w.ln >= 0) { w.ln_off = off; off += align_up((size_t)2 * w.n_pad * 4); }
   }
   c.temb_w_off = off;
   off += align_up((size_t)c.temb_rows_total * c.temb_dim * esize(dt));
@@ -530,7 +495,9 @@ static void plan_work(Ctx& c) {
           want(6, m_in * 4 * C * es);
           want(7, B * g.ctx_len * C * es);
           want(8, B * C * lkp * es);
-          if (!tfm_rows_fits(g.dtype, (int)C, g.head_dim, g.ctx_len, (long long)m_in)) want(10, m_in * C / 16 * 8);      // sums of the rows for a LayerNorm
+          // sums of the rows for a LayerNorm inside the layer behind it: two floats for 16 columns at the least
+          for (const auto& [n, md] : {std::pair<int, int>{3 * (int)C, OUT_QKV}, {(int)C, OUT_ROWMAJOR}, {8 * (int)C, OUT_GEGLU}})
+            if (!tfm_rows_fits(g.dtype, (int)C, g.head_dim, g.ctx_len, (long long)m_in) && conv_takes_ln(g.dtype, (long long)m_in, n, (int)C, md, true)) want(10, m_in * C / 16 * 8);
           gemm(m_in, (int)C, (int)C);
           gemm(m_in, (int)(3 * C), (int)C, OUT_QKV);
           gemm(m_in, (int)C, (int)(4 * C));

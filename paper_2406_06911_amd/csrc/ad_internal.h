@@ -67,9 +67,6 @@ struct Weight {
   size_t dev_bytes = 0;
   int n_pad = 0, k_pad = 0;
   bool fragments = false; // packed operand in fragment order (pack_fragments) instead of rows
-  int ln = -1;            // LayerNorm in front (index of its gain; the offset follows) whose gain is multiplied into this operand: fp32 [n_pad] sums
-  size_t ln_off = 0;      // of the packed rows and [n_pad] bias with the offset in it, in the weight arena
-  bool absorbed = false;  // such a gain or offset: held as ones or zeros
 };
 
 struct Component {
@@ -173,10 +170,6 @@ size_t tensor_bytes(const Ctx& c, int unit);
 size_t packed_conv_bytes(int dtype, int n_out, int c_in, int ksize);
 void pack_conv(int dtype, const float* w, int n_out, int c_in, int ksize, bool geglu, void* out);
 void pack_rows(int dtype, const float* w, size_t n, void* out);   // plain conversion
-inline int geglu_row(int r, int n) { return r % 64 < 32 ? r / 64 * 32 + r % 64 : n / 2 + r / 64 * 32 + r % 64 - 32; }   // row behind packed row r: 32 value, 32 gate
-// a LayerNorm's gain into the columns of w [rows][cols], its offset into the bias (null: none)
-void fold_layernorm(const float* w, int rows, int cols, const float* gain, const float* offset, const float* bias, float* out_w, float* out_b);
-float packed_row_sum(int dtype, const void* row, int n);
 // packed rows (a multiple of 16) into the order in which k_tfm_rows loads them: 16-row tiles, 64 bytes of K of a tile after the other, each
 // laid out by lane; in place
 void pack_fragments(void* packed, int rows, int row_bytes);

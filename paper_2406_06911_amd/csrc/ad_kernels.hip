@@ -67,8 +67,7 @@ struct IgemmParams {
   const void* x0; const void* x1; const void* xw;       // XTRA (k_igemm_p3): sources and weights of the 1x1 convolution behind the taps
   int xc0, xc1, kt_main;                                // its channels; k-tiles of the taps
   unsigned xbytes0, xbytes1, xbytes_w;
-  const float* ln_in; const float* ln_sum; int ln_slabs; float ln_eps, ln_inv;      // LN: pairs of the operand's rows, sums of the weights by column
-  const float* ln_gain; const float* ln_offset;       // fp32: of the channels
+  const float* ln_in; const float* ln_gain; const float* ln_offset; int ln_slabs; float ln_eps;      // LN (k_igemm_small): pairs of the operand's rows
   LnOut ln_out;
 };
 
@@ -167,99 +166,16 @@ __device__ __forceinline__ void wave_lds_fence() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// LayerNorm in front of a GEMM (LN): the operand is the tensor before the norm, the gain is in the weights and the offset in the bias, and
-//   out[m][n] = rstd[m] (sum_k x[m][k] w[n][k] - mean[m] ln_sum[n]) + bias[n],  ln_sum[n] = sum_k w[n][k]  (of the rounded weights, so the mean cancels).
-// The launch that writes the tensor leaves the sum and the sum of squares of every ln_width columns of a row, [row][ln_slabs] pairs, which the GEMM
-// folds in its prologue.  The launch of the norm, its pass through memory and the rounding of its result are gone.
-// Measured inside the models, bf16, us (norm + GEMM -> GEMM; the launches in front take 0.1 to 0.3 longer): q/k/v 1152x3840x1280 5.5 + 19.9 -> 20.9, query
-// 1152x1280x1280 5.5 + 12.4 -> 11.7 and 18432x320x320 8.4 + 10.9 -> 10.7, q/k/v 18432x960x320 8.4 + 21.4 -> 24.1, GEGLU 18432x2560x320 8.4 + 50 -> 52.7
-// and 2048x10240x1280 5.3 + 51.4 -> 53.4.  What is left of the norm is two multiply-adds an element of the output.
-// Tried: the sums taken from the fragments on their way into the matrix cores, by every column tile: 4 to 9 us a launch with 256x128 tiles, as much
-// as the norm.
-__device__ __forceinline__ void ln_add(const bf16x2 v, float& sum, float& sq) {
-  sum = __builtin_amdgcn_fdot2_f32_bf16(v, bf16x2{(bf16)1.f, (bf16)1.f}, sum, false);
-  sq = __builtin_amdgcn_fdot2_f32_bf16(v, v, sq, false);
-}
-// Sums of what LANES neighbouring lanes (4, 8 or 16) hold of a row; the first of them writes the pair.
-template <int LANES>
-__device__ __forceinline__ float ln_lanes(float v) {
-  v += dpp_f<0xB1>(v);                                       // quad_perm 1 0 3 2
-  v += dpp_f<0x4E>(v);                                       // quad_perm 2 3 0 1
-  if (LANES >= 8) v += dpp_f<0x141>(v);                      // row_half_mirror
-  return LANES == 16 ? v + dpp_f<0x140>(v) : v;              // row_mirror
-}
-template <int LANES>
-__device__ __forceinline__ void ln_store(const LnOut& o, float sum, float sq, int row, int col, int lane) {
-  if (lane % LANES == 0) *(f32x2*)(o.pairs + 2 * ((size_t)row * o.slabs + (col >> o.shift))) = f32x2{sum, sq};
-}
-template <int LANES>
-__device__ __forceinline__ void ln_emit(const LnOut& o, float sum, float sq, int row, int col, int lane) {
-  ln_store<LANES>(o, ln_lanes<LANES>(sum), ln_lanes<LANES>(sq), row, col, lane);
-}
-// A thread's pairs of a row (two at a time, TPR threads a row), L loads at once, and their fold: scale and shift of the row.
-template <int TPR, int L>
-__device__ __forceinline__ void ln_load(const IgemmParams& p, int row, int sub, int from, f32x4 (&v)[L]) {
-  const f32x4* src = (const f32x4*)(p.ln_in + (size_t)2 * p.ln_slabs * min(row, p.M - 1));
-#pragma unroll
-  for (int i = 0; i < L; ++i) {
-    const int at = from + sub + i * TPR;
-    v[i] = 2 * at < p.ln_slabs ? src[at] : f32x4{0.f, 0.f, 0.f, 0.f};
-  }
-}
-template <int TPR>
-__device__ __forceinline__ float ln_threads(float v) {
-  if (TPR >= 2) v += dpp_f<0xB1>(v);
-  if (TPR >= 4) v += dpp_f<0x4E>(v);
-  if (TPR >= 8) v += dpp_f<0x141>(v);
-  if (TPR >= 16) v += dpp_f<0x140>(v);                       // row_mirror
-  if (TPR >= 32) v += __shfl_xor(v, 16, 64);
-  return v;
-}
-template <int TPR, int L>
-__device__ __forceinline__ void ln_fold(const IgemmParams& p, int row, int sub, f32x4 (&v)[L], float* out, int pitch) {
-  float sum = 0.f, sq = 0.f;
-  for (int from = 0;;) {
-#pragma unroll
-    for (int i = 0; i < L; ++i) { sum += v[i][0] + v[i][2]; sq += v[i][1] + v[i][3]; }
-    from += L * TPR;
-    if (2 * from >= p.ln_slabs) break;
-    ln_load<TPR>(p, row, sub, from, v);
-  }
-  sum = ln_threads<TPR>(sum);
-  const float mean = sum * p.ln_inv;
-  sq = ln_threads<TPR>(sq);
-  const float var = fmaf(sq, p.ln_inv, -mean * mean), scale = rsqrtf((var < 0.f ? 0.f : var) + p.ln_eps);      // NaN stays NaN
-  if (sub == 0) { out[0] = scale; out[pitch] = -mean * scale; }
-}
-// fp32 (k_igemm_small): mean and 1 / standard deviation of the row, from pairs (sum, squared deviations from their own mean), which all are in v.  The row is
-// normalised in front of the product, so that nothing of its offset is left to cancel behind the sum over K: relative error of norm and layer (rows with a
-// mean of 100 standard deviations, 256 channels) 1.1e-5 behind the product, 3.6e-6 in front of it, 3.5e-6 with a launch for the norm.
-template <int TPR, int L>
-__device__ __forceinline__ void ln_moments(const IgemmParams& p, int sub, const f32x4 (&v)[L], float* mean_out, float* rstd_out) {
-  float sum = 0.f, sq = 0.f;
-#pragma unroll
-  for (int i = 0; i < L; ++i) sum += v[i][0] + v[i][2];
-  const float mean = ln_threads<TPR>(sum) / p.ctot, width = (float)(p.ctot / p.ln_slabs), per = 1.f / width;       // (a power of two)
-#pragma unroll
-  for (int i = 0; i < L; ++i)
-    if (2 * (sub + i * TPR) < p.ln_slabs) {
-      const float d0 = v[i][0] * per - mean, d1 = v[i][2] * per - mean;
-      sq += (v[i][1] + v[i][3]) + width * (d0 * d0 + d1 * d1);
-    }
-  sq = ln_threads<TPR>(sq);
-  if (sub == 0) { *mean_out = mean; *rstd_out = rsqrtf(sq / p.ctot + p.ln_eps); }
-}
-
 // Epilogue shared by the GEMM kernels.  A lane holds column l32 of each 32x32 tile; accumulator register r is row
 // 8*(r/4) + 4*half + r%4 of the tile.  Row-major outputs go through LDS, CR rows of a slab at a time in fp32 (so the result is
 // rounded once), and leave as whole 128-byte lines, 16 bytes a lane.  What limits it is latency: the residual, the bias and the
 // time projection are requested before the first store of the wavefront (loads and stores retire in order, a load behind a store
 // waits for it), the residual of small tiles even before the k-loop (res, PRE).  `stage`: the wavefront's private LDS area of
-// stage_bytes(CR), swap: WTM x 32 floats that the wavefronts of the same rows share (GEGLU, odd TN), LN: the bias is in the sums already; the caller has synchronised the
+// stage_bytes(CR), swap: WTM x 32 floats that the wavefronts of the same rows share (GEGLU, odd TN); the caller has synchronised the
 // workgroup after its last read of the k-loop tiles.
 // Measured (bf16, bias and residual, us; 64-byte pieces of lines and the residual read between the stores -> this): 65536x320x320
 // 62 -> 41, 16384x640x640 37 -> 27, 18432x320x320 16.4 -> 14.1, 2048x1280x1280 18.0 -> 16.5, 3x3 18432x320x2880 45.3 -> 41.2.
-template <typename T, int WTM, int WTN, int TM, int TN, int MODE, int CR, bool PRE, bool LN = false>
+template <typename T, int WTM, int WTN, int TM, int TN, int MODE, int CR, bool PRE>
 __device__ __forceinline__ void igemm_epilogue(const IgemmParams& p, f32x16 (&acc)[TM][TN], int m0, int n0, int wave_m,
                                                int wave_n, int l32, int half, char* stage, int split,
                                                typename Vec<T>::type (&res)[RowSlabs<T, WTM, WTN>::COUNT][RowSlabs<T, WTM, WTN>::MAX],
@@ -321,8 +237,7 @@ __device__ __forceinline__ void igemm_epilogue(const IgemmParams& p, f32x16 (&ac
     const int half_n = p.N >> 1;
     float bias[TN];
 #pragma unroll
-    for (int j = 0; j < TN; ++j) bias[j] = !LN && p.bias ? p.bias[min(col_base + j * 32, p.N - 1)] : 0.f;
-    auto value = [&](int i, int j, int r) { return LN ? acc[i][j][r] : acc[i][j][r] + bias[j]; };
+    for (int j = 0; j < TN; ++j) bias[j] = p.bias ? p.bias[min(col_base + j * 32, p.N - 1)] : 0.f;
     auto emit = [&](int tile, auto val, auto gate) {           // tile: first packed column of the pair; val / gate: (i, r) -> value
       const int oc = (tile >> 1) + (lane % LPR) * VN;
 #pragma unroll
@@ -347,7 +262,7 @@ __device__ __forceinline__ void igemm_epilogue(const IgemmParams& p, f32x16 (&ac
     };
     auto pair = [&](auto jc) {
       constexpr int J = decltype(jc)::value;
-      emit(col0 + J * 32, [&](int i, int r) { return value(i, J, r); }, [&](int i, int r) { return value(i, J + 1, r); });
+      emit(col0 + J * 32, [&](int i, int r) { return acc[i][J][r] + bias[J]; }, [&](int i, int r) { return acc[i][J + 1][r] + bias[J + 1]; });
     };
     if constexpr (!ODD) {
       pair(std::integral_constant<int, 0>{});
@@ -358,21 +273,21 @@ __device__ __forceinline__ void igemm_epilogue(const IgemmParams& p, f32x16 (&ac
 #pragma unroll
         for (int i = 0; i < TM; ++i)
 #pragma unroll
-          for (int r = 0; r < 16; ++r) swap[(i * 16 + r) * 64 + lane] = value(i, 4, r);
+          for (int r = 0; r < 16; ++r) swap[(i * 16 + r) * 64 + lane] = acc[i][4][r] + bias[4];
       }
       __syncthreads();
       if (wave_n == 0) {
         pair(std::integral_constant<int, 0>{});
         pair(std::integral_constant<int, 2>{});
       } else {
-        emit(col0 - 32, [&](int i, int r) { return swap[(i * 16 + r) * 64 + lane]; }, [&](int i, int r) { return value(i, 0, r); });
+        emit(col0 - 32, [&](int i, int r) { return swap[(i * 16 + r) * 64 + lane]; }, [&](int i, int r) { return acc[i][0][r] + bias[0]; });
         pair(std::integral_constant<int, 1>{});
         pair(std::integral_constant<int, 3>{});
       }
     }
   } else {
     auto sample_of = [&](int row) { return (int)fast_div((unsigned)row, p.div_hw); };
-    constexpr bool VECTOR = MODE != OUT_QKV && !LN;          // a per-sample vector may be added
+    constexpr bool VECTOR = MODE != OUT_QKV;                 // a per-sample vector may be added
     const int c3 = MODE == OUT_QKV ? p.N / 3 : p.N;          // columns of one destination
     // first column that leaves transposed (a 32-column tile never straddles two thirds: c3 is a multiple of 32)
     const int turned = (MODE == OUT_TRANSPOSED || MODE == OUT_TRANSPOSED_F32) ? 0 : (MODE == OUT_QKV && p.ld_t > 0) ? 2 * c3 : p.N;
@@ -383,7 +298,7 @@ __device__ __forceinline__ void igemm_epilogue(const IgemmParams& p, f32x16 (&ac
 #pragma unroll
     for (int j = 0; j < TN; ++j) {
       const int col = min(col_base + j * 32, p.N - 1);
-      add[j] = !LN && p.bias ? p.bias[col] : 0.f;
+      add[j] = p.bias ? p.bias[col] : 0.f;
       if (VECTOR && p.rowvec && !mixed) add[j] += p.rowvec[(size_t)b0 * p.rowvec_ld + col];
     }
     if (VECTOR && mixed) {                                   // rows of two samples: the vector goes into the accumulators
@@ -401,8 +316,8 @@ __device__ __forceinline__ void igemm_epilogue(const IgemmParams& p, f32x16 (&ac
       }
     }
     // accumulator register r of tile (i, j), with everything added that belongs to its column
-    auto value = [&](int i, int j, int r) { return LN ? acc[i][j][r] : acc[i][j][r] + add[j]; };
-    const bool with_res = MODE == OUT_ROWMAJOR && !LN && p.residual != nullptr;
+    auto value = [&](int i, int j, int r) { return acc[i][j][r] + add[j]; };
+    const bool with_res = MODE == OUT_ROWMAJOR && p.residual != nullptr;
     if (MODE == OUT_ROWMAJOR && !PRE && with_res && p.vec16) load_residual<T, WTM, WTN>(p, 0, row0, col0, lane, res[0]);
     if constexpr (MODE == OUT_ROWMAJOR || MODE == OUT_QKV) {
       // distances of the other destinations (a lane's columns decide which one it writes)
@@ -445,14 +360,6 @@ __device__ __forceinline__ void igemm_epilogue(const IgemmParams& p, f32x16 (&ac
                 }
               }
               store(dst + (size_t)row * c3, v, c3, c3 - (col - which * c3));
-              if constexpr (MODE == OUT_ROWMAJOR && !LN && std::is_same<T, bf16>::value)
-                if (p.ln_out.pairs) {                              // (whole 32- or 64-column tiles, four or eight lanes each)
-                  float sum = 0.f, sq = 0.f;
-#pragma unroll
-                  for (int e = 0; e < VN; e += 2) ln_add(bf16x2{from_f<T>(v[e]), from_f<T>(v[e + 1])}, sum, sq);
-                  if (WTN == 64 && p.ln_out.shift == 6) ln_emit<8>(p.ln_out, sum, sq, row, col, lane);
-                  else ln_emit<4>(p.ln_out, sum, sq, row, col, lane);
-                }
             }
           }
       }
@@ -704,7 +611,7 @@ __device__ __forceinline__ int lds_swizzle(int row) { return (row >> 1) & 7; }
 // =================================================================================================
 // Wavefronts per SIMD that LDS allows: what the register budget is set for.
 constexpr int p3_waves_per_simd(int bm, int bn, int waves, int stages) { return (int)(kLdsLimit / (stages * (bm + bn) * kRowBytes)) * waves / 4; }
-template <typename T, int BM, int BN, int MODE, int WM = 2, int WN = 2, int NSTAGE = 3, int KG = 1, bool XTRA = false, bool LN = false>
+template <typename T, int BM, int BN, int MODE, int WM = 2, int WN = 2, int NSTAGE = 3, int KG = 1, bool XTRA = false>
 __global__ __launch_bounds__(64 * WM * WN * KG, p3_waves_per_simd(BM, BN, WM * WN, NSTAGE)) void k_igemm_p3(IgemmParams p) {
   typedef typename Vec<T>::type V;
   constexpr int NW = WM * WN;
@@ -753,14 +660,8 @@ __global__ __launch_bounds__(64 * WM * WN * KG, p3_waves_per_simd(BM, BN, WM * W
     return o;
   };
   constexpr int CR = NW * stage_bytes<T, WTM, WTN>(32) <= NSTAGE * STAGE ? 32 : 16;
-  constexpr bool PRE = MODE == OUT_ROWMAJOR && RowSlabs<T, WTM, WTN>::VGPRS <= 32 && !LN;
+  constexpr bool PRE = MODE == OUT_ROWMAJOR && RowSlabs<T, WTM, WTN>::VGPRS <= 32;
   V res[RowSlabs<T, WTM, WTN>::COUNT][RowSlabs<T, WTM, WTN>::MAX];
-  // LN: the sums of this workgroup's rows, several threads a row; asked for ahead of the tiles, folded behind the k-loop (where the registers last: a
-  // fold in front of it waits for them and for the tiles in flight, 1 to 2 us)
-  constexpr int TPR = 64 * NW * KG / BM;
-  float* const ln_rows = (float*)(lds_all + KG * NSTAGE * STAGE);            // [BM] scale, [BM] shift
-  f32x4 ln_in[LN ? (TPR == 2 ? 10 : 5) : 1];                 // 1280 channels in one go
-  if constexpr (LN) ln_load<TPR>(p, m0 + tid / TPR, tid % TPR, 0, ln_in);
   // the weight tiles of the first k-tiles go out before the row arithmetic below, which they do not need
 #pragma unroll
   for (int t = 0; t < NSTAGE - 1; ++t)
@@ -786,9 +687,7 @@ __global__ __launch_bounds__(64 * WM * WN * KG, p3_waves_per_simd(BM, BN, WM * W
   for (int i = 0; i < AG; ++i) {
     const int m = m0 + (NW * i + wave) * 8 + r8;
     a_pix[i] = 0; a_taps[i] = 0;
-    if constexpr (LN) {                                      // a linear layer: the row is the pixel
-      a_pix[i] = m; a_taps[i] = m < p.M;
-    } else if (m < p.M) {
+    if (m < p.M) {
       const int b = (int)fast_div((unsigned)m, p.div_hw), r = m - b * p.hw_out;
       const int oy = (int)fast_div((unsigned)r, p.div_w), ox = r - oy * p.wout;
       const int iy = oy * p.stride - p.pad, ix = ox * p.stride - p.pad;
@@ -812,7 +711,7 @@ __global__ __launch_bounds__(64 * WM * WN * KG, p3_waves_per_simd(BM, BN, WM * W
     const int step = u * p.ws + v;
 #pragma unroll
     for (int i = 0; i < AG; ++i) {
-      const int pix = a_pix[i] + (LN ? 0 : p.up ? (((a_taps[i] >> 9 & 1) + u) >> 1) * p.ws + (((a_taps[i] >> 10 & 1) + v) >> 1) : step);
+      const int pix = a_pix[i] + (p.up ? (((a_taps[i] >> 9 & 1) + u) >> 1) * p.ws + (((a_taps[i] >> 10 & 1) + v) >> 1) : step);
       a_off[i] = (a_taps[i] >> tap & 1) ? ((unsigned)pix * c + scol * VN) * ES : kOob;
     }
   };
@@ -846,7 +745,7 @@ __global__ __launch_bounds__(64 * WM * WN * KG, p3_waves_per_simd(BM, BN, WM * W
   u32x4 rsa = rs0;
   unsigned soff_a = 0, soff_b = 0;
   auto begin_tile = [&]() {
-    const bool second = !LN && f_cc >= s_c0;
+    const bool second = f_cc >= s_c0;
     rsa = second ? rs1 : rs0;
     soff_a = (unsigned)((second ? f_cc - s_c0 : f_cc) * ES);
     soff_b = f_w;
@@ -859,7 +758,7 @@ __global__ __launch_bounds__(64 * WM * WN * KG, p3_waves_per_simd(BM, BN, WM * W
   auto end_tile = [&]() {
     f_w += p.w_kt;
     f_cc += BK;
-    if (!LN && (f_cc == s_c0 || f_cc == s_ctot)) {                   // the next source (c0 and ctot are multiples of the k-tile) or the next tap; LN: one of each
+    if (f_cc == s_c0 || f_cc == s_ctot) {                    // the next source (c0 and ctot are multiples of the k-tile) or the next tap
       const int wrap = f_cc == s_ctot ? 1 : 0;
       f_cc = wrap ? 0 : f_cc;
       f_tap += wrap;
@@ -940,7 +839,6 @@ __global__ __launch_bounds__(64 * WM * WN * KG, p3_waves_per_simd(BM, BN, WM * W
     if (PHASE == 2) end_tile();
     stage = next;
   };
-  if constexpr (LN && TIGHT) ln_fold<TPR>(p, m0 + tid / TPR, tid % TPR, ln_in, ln_rows + tid / TPR, BM);
   // issue order so far: B(0), B(1), A(0), A(1): tile 0 is complete once only A(1) is outstanding
   if (nkt >= NSTAGE - 1) wait_vmcnt<(NSTAGE - 2) * AG>(); else wait_vmcnt<0>();
   __syncthreads();
@@ -950,7 +848,6 @@ __global__ __launch_bounds__(64 * WM * WN * KG, p3_waves_per_simd(BM, BN, WM * W
     for (; kt + 1 < nkt; ++kt) k_tile(std::integral_constant<int, 1>{}, std::true_type{});
     k_tile(std::integral_constant<int, 0>{}, std::true_type{});
     for (int i = nkt; i < kt_each; ++i) __syncthreads();
-    if constexpr (LN && !TIGHT) ln_fold<TPR>(p, m0 + tid / TPR, tid % TPR, ln_in, ln_rows + tid / TPR, BM);
     __syncthreads();
     if constexpr (KG > 1) __syncthreads();
     if constexpr (MODE == OUT_GEGLU && TN % 2 != 0) __syncthreads();      // the epilogue's exchange
@@ -962,7 +859,6 @@ __global__ __launch_bounds__(64 * WM * WN * KG, p3_waves_per_simd(BM, BN, WM * W
   for (; kt + 1 < nkt; ++kt) k_tile(std::integral_constant<int, 1>{}, std::false_type{});
   k_tile(std::integral_constant<int, 0>{}, std::false_type{});
   for (int i = nkt; i < kt_each; ++i) __syncthreads();       // every group passes the same barriers
-  if constexpr (LN && !TIGHT) ln_fold<TPR>(p, m0 + tid / TPR, tid % TPR, ln_in, ln_rows + tid / TPR, BM);
   __syncthreads();     // every wavefront holds its last fragments: LDS can be reused by the epilogue
   if constexpr (KG > 1) {
     // the other groups hand over their sums, a register of all lanes at a time, behind what the epilogue stages in; added in order
@@ -988,28 +884,7 @@ __global__ __launch_bounds__(64 * WM * WN * KG, p3_waves_per_simd(BM, BN, WM * W
 #pragma unroll
           for (int r = 0; r < 16; ++r) acc[i][j][r] += *at(g, i, j, r);
   }
-  if constexpr (LN) {
-    float col_sum[TN], col_bias[TN];
-#pragma unroll
-    for (int j = 0; j < TN; ++j) {
-      const unsigned col = (unsigned)min(n0 + wave_n * WTN + j * 32 + l32, p.N - 1);
-      col_sum[j] = p.ln_sum[col]; col_bias[j] = p.bias[col];
-    }
-    if constexpr (TIGHT) __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const f32x4 scale = *(const f32x4*)(ln_rows + wave_m * WTM + i * 32 + 8 * g + 4 * half),
-                    shift = *(const f32x4*)(ln_rows + BM + wave_m * WTM + i * 32 + 8 * g + 4 * half);
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-#pragma unroll
-          for (int e = 0; e < 4; ++e) acc[i][j][4 * g + e] = fmaf(acc[i][j][4 * g + e], scale[e], fmaf(shift[e], col_sum[j], col_bias[j]));
-        if constexpr (TIGHT) __builtin_amdgcn_sched_barrier(0);      // no registers to read ahead with
-      }
-  }
-  igemm_epilogue<T, WTM, WTN, TM, TN, MODE, CR, PRE, LN>(p, acc, m0, n0, wave_m, wave_n, l32, half, lds + wave * stage_bytes<T, WTM, WTN>(CR), tid3.split, res,
+  igemm_epilogue<T, WTM, WTN, TM, TN, MODE, CR, PRE>(p, acc, m0, n0, wave_m, wave_n, l32, half, lds + wave * stage_bytes<T, WTM, WTN>(CR), tid3.split, res,
                                                          (float*)(lds + NW * stage_bytes<T, WTM, WTN>(CR)) + wave_m * (WTM * 32));
 }
 
@@ -1017,26 +892,19 @@ __global__ __launch_bounds__(64 * WM * WN * KG, p3_waves_per_simd(BM, BN, WM * W
 constexpr bool p3_takes_shortcut(int mode, int bn, int waves, int stages) {
   return (mode == OUT_ROWMAJOR || mode == OUT_PARTIAL) && (bn == 64 || stages == 2 || waves == 8);
 }
-// the instances that ln_tile() counts on: all but those with other numbers of wavefronts
-constexpr bool p3_takes_ln(int mode, int bm, int bn, int waves, int stages) {
-  return (mode == OUT_ROWMAJOR || mode == OUT_GEGLU || mode == OUT_QKV) && (bn == 64 || stages == 2 || waves == 8);
-}
-template <typename T, int BM, int BN, int MODE, int WM = 2, int WN = 2, int NSTAGE = 3, int KG = 1, bool XTRA = false, bool LN = false>
+template <typename T, int BM, int BN, int MODE, int WM = 2, int WN = 2, int NSTAGE = 3, int KG = 1, bool XTRA = false>
 static ad_status run_igemm_p3(const IgemmParams& p0, const char* name, hipStream_t s) {
   if constexpr (!XTRA && p3_takes_shortcut(MODE, BN, WM * WN, NSTAGE))
     if (p0.xw) return run_igemm_p3<T, BM, BN, MODE, WM, WN, NSTAGE, KG, true>(p0, name, s);
   if (!XTRA && p0.xw) AD_FAIL(AD_ERR_INVALID, "conv: this tile does not take a shortcut");
-  if constexpr (!LN && !XTRA && p3_takes_ln(MODE, BM, BN, WM * WN, NSTAGE))
-    if (p0.ln_in) return run_igemm_p3<T, BM, BN, MODE, WM, WN, NSTAGE, KG, false, true>(p0, name, s);
-  if (!LN && p0.ln_in) AD_FAIL(AD_ERR_INVALID, "conv: this tile does not take a LayerNorm");
   IgemmParams p = p0;
   set_tiles(p, BM, BN);
-  constexpr int lds_bytes = KG * NSTAGE * (BM + BN) * kRowBytes + (LN ? 2 * BM * 4 : 0);
+  constexpr int lds_bytes = KG * NSTAGE * (BM + BN) * kRowBytes;
   static_assert(lds_bytes / KG >= WM * WN * stage_bytes<T, BM / WM, BN / WN>(16) && lds_bytes <= (int)kLdsLimit, "epilogue staging fits");
   static_assert(MODE != OUT_GEGLU || BN / WN / 32 % 2 == 0 || lds_bytes >= WM * WN * stage_bytes<T, BM / WM, BN / WN>(32) + BM * 128, "so does the exchange");
   static std::atomic<bool> attr_set{false};
   if (!attr_set) {
-    AD_HIP(hipFuncSetAttribute((const void*)k_igemm_p3<T, BM, BN, MODE, WM, WN, NSTAGE, KG, XTRA, LN>, hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes));
+    AD_HIP(hipFuncSetAttribute((const void*)k_igemm_p3<T, BM, BN, MODE, WM, WN, NSTAGE, KG, XTRA>, hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes));
     attr_set = true;
   }
   const int xk = p.xc0 + p.xc1;
@@ -1044,7 +912,7 @@ static ad_status run_igemm_p3(const IgemmParams& p0, const char* name, hipStream
   const double out_cols = p.out_mode == OUT_GEGLU ? p.N / 2 : p.N;
   ProfLaunch pl(name, 2.0 * p.M * p.N * (p.k_prof + xk), in_bytes + (double)p.N * (p.Kp + xk) * sizeof(T) + (double)p.M * out_cols * sizeof(T), s, p.M, p.N, p.Kp + xk);
   const int splits = (p.ktiles + p.kt_per_split - 1) / p.kt_per_split;
-  hipLaunchKernelGGL((k_igemm_p3<T, BM, BN, MODE, WM, WN, NSTAGE, KG, XTRA, LN>), dim3(p.tiles_n * p.tiles_m, splits), dim3(64 * WM * WN * KG), lds_bytes, s, p);
+  hipLaunchKernelGGL((k_igemm_p3<T, BM, BN, MODE, WM, WN, NSTAGE, KG, XTRA>), dim3(p.tiles_n * p.tiles_m, splits), dim3(64 * WM * WN * KG), lds_bytes, s, p);
   AD_HIP(hipGetLastError());
   return AD_OK;
 }
@@ -1062,7 +930,56 @@ static ad_status run_igemm_p3(const IgemmParams& p0, const char* name, hipStream
 // Measured, bf16, weights from memory, us (64x64 tiles in three stages -> this kernel): 1152x64x64 4.1 -> 3.1, 3x3 1152x64x576
 // 7.4 -> 4.4, 3x3 288x128x1152 10.8 -> 4.8, 72x256x1024 7.8 -> 4.7, 180x1280x1280 11.4 -> 7.9; 3x3 72x256x2304 with K split
 // over workgroups and a second launch 11.8 -> 6.8.
+//
+// LN: a LayerNorm in front of the (linear) layer, without a launch and a pass through memory of its own: the fragments of the rows are normalised in
+// registers on their way into the matrix cores, with the arithmetic of k_layernorm (fp32 statistics, gain and offset, the result rounded to T).  Neither
+// the row's mean nor the gain goes through the product: taken off the sum over K the mean costs relative precision by its ratio to the row's spread
+// (fp32, 256 channels, 100 standard deviations: 1.1e-5 instead of 3.6e-6; rows of one value 1e-2 instead of 1.8e-7), and a gain that is rounded into bf16
+// weights shows where the products cancel (3e-2 instead of 2e-3).  The statistics are combined in front of the k-loop from what the launch that wrote the
+// rows leaves beside them: for every 16 or 32 columns (its tile's) the sum and, fp32, the squared deviations from their own mean, bf16, the sum of squares.
+// Whole runs, ms (a launch for the norm -> this): narrow model 37.7 -> 36.8, fp32 17.3 -> 17.0, with stride 2 27.1 -> 26.1, 576x320 px 64.1 -> 63.8, 512px
+// level.  The vector work is that of a k-tile or two a wavefront; the larger tiles, whose LDS is filled by the load unit and whose fragments every column
+// tile would normalise again, leave the norm to k_layernorm.
 // =================================================================================================
+constexpr int kLnLoads = 5;                              // pairs (two at a time) a thread takes in; 16 threads a row and pairs of 16 columns: 2560 columns
+constexpr int kLnMost = kLnLoads * 16 * 2 * 16;
+template <int LANES>                                     // sum over 4 or 8 neighbouring lanes
+__device__ __forceinline__ float ln_lanes(float v) {
+  v += dpp_f<0xB1>(v);                                   // quad_perm 1 0 3 2
+  v += dpp_f<0x4E>(v);                                   // quad_perm 2 3 0 1
+  return LANES == 8 ? v + dpp_f<0x141>(v) : v;           // row_half_mirror
+}
+template <int TPR>                                       // over the 16 or 32 threads of a row
+__device__ __forceinline__ float ln_threads(float v) {
+  v = ln_lanes<8>(v);
+  v += dpp_f<0x140>(v);                                  // row_mirror
+  return TPR == 32 ? v + __shfl_xor(v, 16, 64) : v;
+}
+template <int TPR>
+__device__ __forceinline__ void ln_load(const IgemmParams& p, int row, int sub, f32x4 (&v)[kLnLoads]) {
+  const f32x4* src = (const f32x4*)(p.ln_in + (size_t)2 * p.ln_slabs * min(row, p.M - 1));
+#pragma unroll
+  for (int i = 0; i < kLnLoads; ++i) v[i] = 2 * (sub + i * TPR) < p.ln_slabs ? src[sub + i * TPR] : f32x4{0.f, 0.f, 0.f, 0.f};
+}
+template <typename T, int TPR>
+__device__ __forceinline__ void ln_fold(const IgemmParams& p, int sub, const f32x4 (&v)[kLnLoads], float* mean_out, float* rstd_out) {
+  float sum = 0.f, sq = 0.f;
+#pragma unroll
+  for (int i = 0; i < kLnLoads; ++i) sum += v[i][0] + v[i][2];
+  const float mean = ln_threads<TPR>(sum) / p.ctot, width = (float)(p.ctot / p.ln_slabs), per = 1.f / width;       // (a power of two)
+#pragma unroll
+  for (int i = 0; i < kLnLoads; ++i)
+    if (2 * (sub + i * TPR) < p.ln_slabs) {
+      const float d0 = v[i][0] * per - mean, d1 = v[i][2] * per - mean;
+      sq += v[i][1] + v[i][3];
+      if constexpr (!std::is_same<T, bf16>::value) sq += width * (d0 * d0 + d1 * d1);
+    }
+  sq = ln_threads<TPR>(sq);
+  float var = sq / p.ctot;
+  if constexpr (std::is_same<T, bf16>::value) { var = fmaf(-mean, mean, var); var = var < 0.f ? 0.f : var; }
+  if (sub == 0) { *mean_out = mean; *rstd_out = rsqrtf(var + p.ln_eps); }
+}
+
 template <typename T, int TM, int TN, int MODE, bool LN = false>
 __global__ __launch_bounds__(512) void k_igemm_small(IgemmParams p) {
   typedef typename Vec<T>::type V;
@@ -1112,11 +1029,10 @@ __global__ __launch_bounds__(512) void k_igemm_small(IgemmParams p) {
   int f_tap = wave * BK / p.ctot, f_cc = wave * BK - f_tap * p.ctot;
   unsigned f_w = (unsigned)wave * p.w_kt;
   V af[PF][TM][2], bf[PF][TN][2];
-  constexpr bool FRONT = LN && !std::is_same<T, bf16>::value;       // the norm in front of the product, else behind it
   constexpr int GQ = VN / 4;                             // gains and offsets of a fragment, four at a time
-  f32x4 gain[FRONT ? PF : 1][2][GQ], offset[FRONT ? PF : 1][2][GQ];
+  f32x4 gain[LN ? PF : 1][2][GQ], offset[LN ? PF : 1][2][GQ];
   auto fetch = [&](int s) {
-    if constexpr (FRONT) {
+    if constexpr (LN) {
 #pragma unroll
       for (int h = 0; h < 2; ++h)
 #pragma unroll
@@ -1146,12 +1062,13 @@ __global__ __launch_bounds__(512) void k_igemm_small(IgemmParams p) {
       for (int h = 0; h < 2; ++h) af[s][i][h] = second ? buffer_load16<V>(rs1, o + h * 64, sc) : buffer_load16<V>(rs0, o + h * 64, sc);
     }
     f_w += NW * p.w_kt; f_cc += BK * NW;
+    if constexpr (LN) return;                            // one tap, one source
     while (f_cc >= p.ctot) { f_cc -= p.ctot; ++f_tap; }
   };
-  constexpr int TPR = 64 * NW / BM;
-  float* const ln_rows = part + NW * BM * PITCH;         // LN: [BM] scale, [BM] shift; FRONT: [BM] mean, [BM] 1 / standard deviation
-  f32x4 ln_in[LN ? 5 : 1];
-  if constexpr (FRONT) ln_load<TPR>(p, m0 + tid / TPR, tid % TPR, 0, ln_in);      // ahead of the fragments: the fold waits for these alone
+  constexpr int TPR = 64 * NW / BM;                      // LN: threads a row
+  float* const ln_rows = part + NW * BM * PITCH;         // [BM] mean, [BM] 1 / standard deviation
+  f32x4 ln_in[kLnLoads];
+  if constexpr (LN) ln_load<TPR>(p, m0 + tid / TPR, tid % TPR, ln_in);      // ahead of the fragments: the fold waits for these alone
 #pragma unroll
   for (int s = 0; s < PF; ++s)
     if (s < mine) fetch(s);
@@ -1168,14 +1085,12 @@ __global__ __launch_bounds__(512) void k_igemm_small(IgemmParams p) {
   const int row = m0 + rl, col = n0 + cl;
   const bool live = tid < QUADS && row < p.M && (MODE == OUT_GEGLU || col < p.N);
   float add[4] = {0.f, 0.f, 0.f, 0.f}, gate[4] = {0.f, 0.f, 0.f, 0.f};
-  float col_sum[4] = {0.f, 0.f, 0.f, 0.f}, gate_sum[4] = {0.f, 0.f, 0.f, 0.f};      // LN
   if (live) {
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       const int c = by_column ? col : col + e, r = min(by_column ? row + e : row, p.M - 1);
       if (c >= p.N) continue;
       if (p.bias) { add[e] = p.bias[c]; if constexpr (MODE == OUT_GEGLU) gate[e] = p.bias[c + 32]; }
-      if constexpr (LN && !FRONT) { col_sum[e] = p.ln_sum[c]; if constexpr (MODE == OUT_GEGLU) gate_sum[e] = p.ln_sum[c + 32]; }
       if constexpr (MODE == OUT_ROWMAJOR || TRANSPOSED)
         if (p.rowvec) add[e] += p.rowvec[(size_t)fast_div((unsigned)r, p.div_hw) * p.rowvec_ld + c];
       if constexpr (MODE == OUT_ROWMAJOR)
@@ -1183,15 +1098,13 @@ __global__ __launch_bounds__(512) void k_igemm_small(IgemmParams p) {
     }
   }
 
-  if constexpr (LN && !FRONT) ln_load<TPR>(p, m0 + tid / TPR, tid % TPR, 0, ln_in);
   float mean[TM], rstd[TM];
-  if constexpr (FRONT) {
-    ln_moments<TPR>(p, tid % TPR, ln_in, ln_rows + tid / TPR, ln_rows + BM + tid / TPR);
+  if constexpr (LN) {
+    ln_fold<T, TPR>(p, tid % TPR, ln_in, ln_rows + tid / TPR, ln_rows + BM + tid / TPR);
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < TM; ++i) { mean[i] = ln_rows[16 * i + r16]; rstd[i] = ln_rows[BM + 16 * i + r16]; }
   }
-
   f32x4 acc[TM][TN];
 #pragma unroll
   for (int i = 0; i < TM; ++i)
@@ -1206,7 +1119,7 @@ __global__ __launch_bounds__(512) void k_igemm_small(IgemmParams p) {
 #pragma unroll
         for (int i = 0; i < TM; ++i) {
           V a = af[s][i][h];
-          if constexpr (FRONT) {                         // as k_layernorm does it
+          if constexpr (LN) {
 #pragma unroll
             for (int e = 0; e < VN; ++e) a[e] = from_f<T>((to_f(a[e]) - mean[i]) * rstd[i] * gain[s][h][e / 4][e % 4] + offset[s][h][e / 4][e % 4]);
           }
@@ -1221,14 +1134,8 @@ __global__ __launch_bounds__(512) void k_igemm_small(IgemmParams p) {
   for (int i = 0; i < TM; ++i)
 #pragma unroll
     for (int j = 0; j < TN; ++j) *(f32x4*)(part + wave * (BM * PITCH) + (16 * i + r16) * PITCH + 16 * j + 4 * kg) = acc[i][j];
-  if constexpr (LN && !FRONT) ln_fold<TPR>(p, m0 + tid / TPR, tid % TPR, ln_in, ln_rows + tid / TPR, BM);
   __syncthreads();
   if (!live) return;
-  // v[e] becomes what the norm makes of it, without the bias; row r of the tile
-  auto normed = [&](float v, int r, float w_sum) {
-    if constexpr (LN && !FRONT) return fmaf(v, ln_rows[r], ln_rows[BM + r] * w_sum);
-    return v;
-  };
   auto total = [&](int r, int c) {                       // four columns of a row, over the wavefronts in order
     f32x4 v = *(const f32x4*)(part + r * PITCH + c);
 #pragma unroll
@@ -1242,7 +1149,7 @@ __global__ __launch_bounds__(512) void k_igemm_small(IgemmParams p) {
       v[e] = part[(rl + e) * PITCH + cl];
 #pragma unroll
       for (int w = 1; w < NW; ++w) v[e] += part[w * (BM * PITCH) + (rl + e) * PITCH + cl];
-      v[e] = normed(v[e], rl + e, col_sum[e]) + add[e];
+      v[e] += add[e];
     }
     const int ncols = MODE == OUT_QKV ? c3 : p.N, cc = MODE == OUT_QKV ? col - 2 * c3 : col;
     void* const dst = MODE == OUT_QKV ? p.out3 : p.out;
@@ -1269,11 +1176,11 @@ __global__ __launch_bounds__(512) void k_igemm_small(IgemmParams p) {
   if constexpr (MODE == OUT_GEGLU) {
     const f32x4 g = total(rl, cl + 32);
 #pragma unroll
-    for (int e = 0; e < 4; ++e) v[e] = (normed(v[e], rl, col_sum[e]) + add[e]) * gelu_f(normed(g[e], rl, gate_sum[e]) + gate[e]);
+    for (int e = 0; e < 4; ++e) v[e] = (v[e] + add[e]) * gelu_f(g[e] + gate[e]);
     ncols = p.N >> 1; c_out = (n0 >> 1) + cl;
   } else {
 #pragma unroll
-    for (int e = 0; e < 4; ++e) v[e] = normed(v[e], rl, col_sum[e]) + add[e];
+    for (int e = 0; e < 4; ++e) v[e] += add[e];
   }
   if constexpr (MODE == OUT_QKV) {
     dst = (T*)(which == 0 ? p.out : which == 1 ? p.out2 : p.out3);
@@ -1281,18 +1188,15 @@ __global__ __launch_bounds__(512) void k_igemm_small(IgemmParams p) {
   }
   const size_t o = (size_t)row * ncols + c_out;
   if constexpr (MODE == OUT_ROWMAJOR && !LN)
-    if (p.ln_out.pairs) {                                        // (whole tiles: BO / 4 lanes a row)
-      float sum = 0.f, sq = 0.f;
-      if constexpr (std::is_same<T, bf16>::value) {
+    if (p.ln_out.pairs) {                                // (whole tiles, BN / 4 lanes a row; of the values as they are stored)
+      float x[4], sq = 0.f;
 #pragma unroll
-        for (int e = 0; e < 4; e += 2) ln_add(bf16x2{from_f<T>(v[e]), from_f<T>(v[e + 1])}, sum, sq);
-        ln_emit<BO / 4>(p.ln_out, sum, sq, row, col, lane);
-      } else {
-        sum = ln_lanes<BO / 4>((v[0] + v[1]) + (v[2] + v[3]));
+      for (int e = 0; e < 4; ++e) x[e] = to_f(from_f<T>(v[e]));
+      const float sum = ln_lanes<BN / 4>((x[0] + x[1]) + (x[2] + x[3]));
 #pragma unroll
-        for (int e = 0; e < 4; ++e) { const float d = v[e] - sum * (1.f / BO); sq = fmaf(d, d, sq); }
-        ln_store<BO / 4>(p.ln_out, sum, ln_lanes<BO / 4>(sq), row, col, lane);
-      }
+      for (int e = 0; e < 4; ++e) { const float d = std::is_same<T, bf16>::value ? x[e] : x[e] - sum * (1.f / BN); sq += d * d; }
+      sq = ln_lanes<BN / 4>(sq);
+      if (cl == 0) *(f32x2*)(p.ln_out.pairs + 2 * ((size_t)row * p.ln_out.slabs + (col >> p.ln_out.shift))) = f32x2{sum, sq};
     }
   if ((ncols & 3) == 0) {
     *(V4*)(dst + o) = V4{from_f<T>(v[0]), from_f<T>(v[1]), from_f<T>(v[2]), from_f<T>(v[3])};
@@ -1307,7 +1211,6 @@ template <typename T, int TM, int TN, int MODE, bool LN = false>
 static ad_status run_igemm_small(const IgemmParams& p0, const char* name, hipStream_t s) {
   if constexpr (!LN && (MODE == OUT_ROWMAJOR || MODE == OUT_QKV || MODE == OUT_GEGLU))
     if (p0.ln_in) return run_igemm_small<T, TM, TN, MODE, true>(p0, name, s);
-  if (!LN && p0.ln_in) AD_FAIL(AD_ERR_INVALID, "conv: this tile does not take a LayerNorm");
   IgemmParams p = p0;
   set_tiles(p, 16 * TM, 16 * TN);
   constexpr int lds_bytes = 8 * 16 * TM * (16 * TN + 4) * 4 + (LN ? 2 * 16 * TM * 4 : 0);
@@ -1560,7 +1463,7 @@ template <typename T>
 __global__ __launch_bounds__(256) void k_splitk_reduce(const float* __restrict__ partial, int splits, int M, int N, int hw_out, FastDiv div_n4,
                                                        FastDiv div_hw, int vec, const float* __restrict__ bias,
                                                        const float* __restrict__ rowvec, int rowvec_ld, const T* __restrict__ residual,
-                                                       void* __restrict__ out, void* __restrict__ out2, void* __restrict__ out3, int out_mode, int ld_t, LnOut ln) {
+                                                       void* __restrict__ out, void* __restrict__ out2, void* __restrict__ out3, int out_mode, int ld_t) {
   typedef typename Vec4<T>::type V4;
   const unsigned n4 = N / 4, total = (unsigned)M * n4;
   for (unsigned i = blockIdx.x * 256 + threadIdx.x; i < total; i += gridDim.x * 256) {
@@ -1604,15 +1507,7 @@ __global__ __launch_bounds__(256) void k_splitk_reduce(const float* __restrict__
     const bool turned = out_mode == OUT_TRANSPOSED || out_mode == OUT_TRANSPOSED_F32 || (which == 2 && ld_t > 0);
     if (vec && !turned) {
       T* dst = (T*)(which == 0 ? out : which == 1 ? out2 : out3);
-      const V4 o = V4{from_f<T>(v[0]), from_f<T>(v[1]), from_f<T>(v[2]), from_f<T>(v[3])};
-      *(V4*)(dst + (size_t)row * c3 + col - which * c3) = o;
-      if constexpr (std::is_same<T, bf16>::value)
-        if (ln.pairs) {                                      // (N is a multiple of the pair's 32 or 64 columns, which eight or sixteen lanes hold)
-          float sum = 0.f, sq = 0.f;
-          ln_add(bf16x2{o[0], o[1]}, sum, sq); ln_add(bf16x2{o[2], o[3]}, sum, sq);
-          if (ln.shift == 6) ln_emit<16>(ln, sum, sq, row, col, threadIdx.x);
-          else ln_emit<8>(ln, sum, sq, row, col, threadIdx.x);
-        }
+      *(V4*)(dst + (size_t)row * c3 + col - which * c3) = V4{from_f<T>(v[0]), from_f<T>(v[1]), from_f<T>(v[2]), from_f<T>(v[3])};
       continue;
     }
 #pragma unroll
@@ -1808,32 +1703,16 @@ bool conv_takes_shortcut(int dtype, long long m, int n, int c, int xc) {
   }
 }
 
-// A LayerNorm over the c channels in front of a linear layer: inside the layer's launch on the LDS-DMA and small-tile kernels without K-splits, which
-// is all bf16 launches behind a LayerNorm in the SD-sized models; fp32: on the small-tile kernels (narrow models).
-static bool ln_tile(const ConvPlan& plan, int override) {
-  if (plan.splits != 1) return false;
-  switch (plan.tile) {
-    case TILE_SMALL: case TILE_P3_64: case TILE_K2_64: case TILE_D2_128: case TILE_D2_160: case TILE_D2_320: return true;
-    case TILE_P3_128: case TILE_P3_256: return override != TILE_P3_128_W4 && override != TILE_P3_256_W4 && override != TILE_P3_256_W16;
-    default: return false;
-  }
-}
-constexpr int kLnMostF32 = 2560;      // pairs of 16 columns: 160, all in the registers of 16 threads a row (ln_moments)
-bool ln_folds(int dtype, long long m, int n, int c, int out_mode) {
-  return c % 64 == 0 && dtype == AD_BF16 && ln_tile(compute_plan(dtype, m, n, c / bk_elems(dtype), out_mode, TILE_AUTO), TILE_AUTO);
-}
-bool conv_takes_ln(int dtype, long long m, int n, int c, int out_mode) {
-  return c % 64 == 0 && (dtype == AD_BF16 || c <= kLnMostF32) && ln_tile(choose_plan(dtype, m, n, c / bk_elems(dtype), out_mode), g_tile_override);
+bool conv_takes_ln(int dtype, long long m, int n, int c, int out_mode, bool any_tile) {
+  if (c % 64 || c > kLnMost || (out_mode != OUT_ROWMAJOR && out_mode != OUT_QKV && out_mode != OUT_GEGLU)) return false;
+  const int ktiles = c / bk_elems(dtype);
+  return (any_tile ? compute_plan(dtype, m, n, ktiles, out_mode, TILE_AUTO) : choose_plan(dtype, m, n, ktiles, out_mode)).tile == TILE_SMALL;
 }
 
 int conv_ln_width(int dtype, long long m, int n, int k) {
-  if (n % 64 || k % bk_elems(dtype)) return 0;
-  const int ktiles = k / bk_elems(dtype), tile = choose_plan(dtype, m, n, ktiles, OUT_ROWMAJOR).tile;
-  if (tile == TILE_SMALL) return small_tile(m, n, ktiles, OUT_ROWMAJOR).tn == 1 ? 16 : 32;
-  // where a wavefront holds 64 columns: half as many pairs for the GEMM to take in (a row tile's 40 instead of 80 KiB at 1280 channels, beside 640 KiB of
-  // rows; 1024px runs 0.6 % faster, 768px and 512px 0.1 to 0.2, video level).  An even number of pairs a row, since they are loaded in twos.
-  if (n % 128 == 0 && (tile == TILE_P3_128 || tile == TILE_P3_256 || tile == TILE_D2_128)) return 64;
-  return tile == TILE_128x128 || tile == TILE_64x64 ? 0 : 32;
+  const int ktiles = k / bk_elems(dtype);
+  if (n % 64 || k % bk_elems(dtype) || choose_plan(dtype, m, n, ktiles, OUT_ROWMAJOR).tile != TILE_SMALL) return 0;
+  return 16 * small_tile(m, n, ktiles, OUT_ROWMAJOR).tn;
 }
 
 ad_status launch_conv(const ConvArgs& a, hipStream_t s) {
@@ -1880,15 +1759,15 @@ ad_status launch_conv(const ConvArgs& a, hipStream_t s) {
   p.w = a.w; p.bias = a.bias; p.rowvec = a.rowvec; p.residual = a.residual;
   p.out = a.out; p.out_mode = a.out_mode; p.ld_t = a.ld_t; p.rowvec_ld = a.rowvec_ld > 0 ? a.rowvec_ld : (a.rowvec_ld < 0 ? 0 : a.n_out);
   p.out2 = a.out2; p.out3 = a.out3;
-  p.ln_gain = a.ln_gain; p.ln_offset = a.ln_offset;
-  p.ln_in = a.ln_in; p.ln_sum = a.ln_sum; p.ln_eps = a.ln_eps; p.ln_inv = 1.f / (float)p.Kp;
-  p.ln_slabs = a.ln_in ? p.Kp / a.ln_width : 0;
-  p.ln_out = LnOut{a.ln_out, a.ln_out ? a.n_out / a.ln_width : 0, a.ln_width == 16 ? 4 : a.ln_width == 32 ? 5 : 6};
-  if ((a.ln_in || a.ln_out) && a.ln_width != 16 && a.ln_width != 32 && a.ln_width != 64) AD_FAIL(AD_ERR_INVALID, "conv: bad LayerNorm");
-  if (a.ln_in && (a.ksize != 1 || a.stride != 1 || a.up || a.c1 || a.residual || a.rowvec || a.xw || a.ln_out || ((uintptr_t)a.ln_in & 15) ||
-                  (a.dtype == AD_F32 ? !a.ln_gain || !a.ln_offset || (((uintptr_t)a.ln_gain | (uintptr_t)a.ln_offset) & 15) : !a.bias || !a.ln_sum) ||
+  p.ln_in = a.ln_in; p.ln_gain = a.ln_gain; p.ln_offset = a.ln_offset; p.ln_eps = a.ln_eps;
+  p.ln_slabs = a.ln_in && a.ln_width > 0 ? p.Kp / a.ln_width : 0;
+  p.ln_out = LnOut{a.ln_out, a.ln_out && a.ln_width > 0 ? a.n_out / a.ln_width : 0, a.ln_width == 16 ? 4 : 5};
+  if (a.ln_in && ((a.ln_width != 16 && a.ln_width != 32) || a.ksize != 1 || a.stride != 1 || a.up || a.c1 || a.residual || a.rowvec || a.xw || a.ln_out ||
+                  !a.ln_gain || !a.ln_offset || (((uintptr_t)a.ln_in | (uintptr_t)a.ln_gain | (uintptr_t)a.ln_offset) & 15) ||
                   !conv_takes_ln(a.dtype, m, a.n_out, a.c0, a.out_mode)))
     AD_FAIL(AD_ERR_INVALID, "conv: bad LayerNorm");
+  if (a.ln_out && (!a.ln_width || a.out_mode != OUT_ROWMAJOR || a.xw || ((uintptr_t)a.ln_out & 7) || a.ln_width != conv_ln_width(a.dtype, m, a.n_out, p.Kp)))
+    AD_FAIL(AD_ERR_INVALID, "conv: the sums of this output's rows are not to be had");
   if (a.out_mode < OUT_ROWMAJOR || a.out_mode > OUT_QKV) AD_FAIL(AD_ERR_INVALID, "conv: bad out_mode");
   if (a.out_mode == OUT_QKV && (a.n_out % 3 || !a.out2 || !a.out3 || a.residual || a.rowvec || (a.ld_t > 0 && a.ld_t < p.hw_out)))
     AD_FAIL(AD_ERR_INVALID, "conv: bad fused q/k/v use");
@@ -1910,8 +1789,6 @@ ad_status launch_conv(const ConvArgs& a, hipStream_t s) {
   const auto at16 = [](const void* q) { return ((uintptr_t)q & 15) == 0; };
   p.vec16 = ncols % vn == 0 && at16(a.out) && at16(a.residual) && (a.out_mode != OUT_QKV || (at16(a.out2) && (turned || at16(a.out3))));
   p.turn16 = turned && at16(a.out3) && a.ld_t % vn == 0 && p.hw_out % vn == 0;
-  if (a.ln_out && (a.out_mode != OUT_ROWMAJOR || !p.vec16 || ((uintptr_t)a.ln_out & 7) || a.ln_width != conv_ln_width(a.dtype, m, a.n_out, p.ktiles * bk)))
-    AD_FAIL(AD_ERR_INVALID, "conv: the sums of this output's rows are not to be had");
   const ConvPlan plan = choose_plan(a.dtype, m, a.n_out, p.ktiles, a.out_mode);
   p.band = plan.band >= 0 ? plan.band : w_bytes > in_elems * (long long)(a.c0 + a.c1) * (long long)esize(a.dtype) * a.ksize * a.ksize ? 0 : 1;
   if (g_order_override >= 0) p.band = g_order_override == 1 ? 0 : 1;
@@ -2055,7 +1932,7 @@ ad_status launch_conv(const ConvArgs& a, hipStream_t s) {
   ProfLaunch pl("splitk_reduce", 0, (double)splits * m * a.n_out * 4 + (double)m * a.n_out * esize(a.dtype), s);
 #define AD_REDUCE(T_)                                                                                                                  \
   hipLaunchKernelGGL(k_splitk_reduce<T_>, dim3(blocks), dim3(256), 0, s, p.partial, splits, p.M, p.N, p.hw_out, make_fastdiv((unsigned)(p.N / 4)), \
-                     p.div_hw, vec4, a.bias, a.rowvec, rowvec_ld, (const T_*)a.residual, a.out, a.out2, a.out3, a.out_mode, a.ld_t, p.ln_out)
+                     p.div_hw, vec4, a.bias, a.rowvec, rowvec_ld, (const T_*)a.residual, a.out, a.out2, a.out3, a.out_mode, a.ld_t)
   if (a.dtype == AD_BF16) AD_REDUCE(bf16);
   else AD_REDUCE(float);
 #undef AD_REDUCE

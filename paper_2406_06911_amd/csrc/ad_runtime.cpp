@@ -65,17 +65,17 @@ struct Eval {
     a.w_blocks = 1;
     return launch_conv(a, s);
   }
-  // linear layer on a [rows][cin] matrix; next: the layer behind the LayerNorm that follows, which may want the sums of the rows (width: see ln_linear())
+  // linear layer on a [rows][cin] matrix; next: of the layer behind the LayerNorm that follows, which may want the sums of the rows (width: see ln_linear())
+  struct Next { int n, mode; int* width; };
   ad_status linear(const void* src, int rows, int cin, int w_idx, int b_idx, const void* residual, void* dst,
-                   int mode = OUT_ROWMAJOR, int batch = 1, int ld_t = 0, int next = -1, int* width = nullptr) const {
+                   int mode = OUT_ROWMAJOR, int batch = 1, int ld_t = 0, Next next = {0, 0, nullptr}) const {
     WView wv{c};
     ConvArgs a{dt, src, nullptr, cin, 0, batch, rows / batch, 1, 0, 1, 1, wv.at(w_idx), c.weights[w_idx].info.shape[0],
                b_idx >= 0 ? wv.f32(b_idx) : nullptr, nullptr, 0, residual, dst, mode, ld_t, temp(9), ws.temp_bytes[9]};
     a.w_blocks = 1;
-    if (width) {
-      *width = 0;
-      if ((dt == AD_F32 || c.weights[next].ln >= 0) && (((uintptr_t)dst | (uintptr_t)residual) & 15) == 0) *width = conv_ln_width(dt, rows, a.n_out, cin);
-      if (*width) { a.ln_out = (float*)temp(10); a.ln_width = *width; }
+    if (next.width) {
+      *next.width = conv_takes_ln(dt, rows, next.n, a.n_out, next.mode) ? conv_ln_width(dt, rows, a.n_out, cin) : 0;
+      if (*next.width) { a.ln_out = (float*)temp(10); a.ln_width = *next.width; }
     }
     return launch_conv(a, s);
   }
@@ -88,23 +88,18 @@ struct Eval {
     WView wv{c};
     return launch_layernorm(dt, src, rows, ch, wv.f32(g_idx), wv.f32(g_idx + 1), c.cfg.ln_eps, dst, s);
   }
-
-  // the linear layer w_idx behind a LayerNorm of h, in one launch where the norm is in its weights (fp32: its gain need not be), the launch's tile takes it and the launch that
-  // wrote h has left the sums of its rows (width: columns a pair of them covers, else 0); a.bias is the layer's own bias
-  ad_status ln_linear(const void* h, int rows, int ch, int g_idx, int w_idx, int width, ConvArgs a) const {
+  // a linear layer behind a LayerNorm of h (gain and offset at g_idx): in one launch where the launch that wrote h has left the sums of its rows, since the
+  // layer takes them (width: columns a pair of them covers), else a launch each
+  ad_status ln_linear(const void* h, int rows, int ch, int g_idx, int width, ConvArgs a) const {
     WView wv{c};
-    const Weight& w = c.weights[w_idx];
-    const float* folded = w.ln >= 0 ? (const float*)(c.weights_dev + w.ln_off) : nullptr;
-    a.w = wv.at(w_idx);
     a.w_blocks = 1;
-    if (folded) a.bias = folded + w.n_pad;
-    if ((folded || dt == AD_F32) && width && conv_takes_ln(dt, rows, a.n_out, ch, a.out_mode)) {
-      a.src0 = h; a.ln_in = (const float*)temp(10); a.ln_width = width; a.ln_sum = folded; a.ln_eps = c.cfg.ln_eps;
-      if (!folded) { a.ln_gain = wv.f32(g_idx); a.ln_offset = wv.f32(g_idx + 1); }
-      return launch_conv(a, s);
+    a.src0 = h;
+    if (width) {
+      a.ln_in = (const float*)temp(10); a.ln_width = width; a.ln_gain = wv.f32(g_idx); a.ln_offset = wv.f32(g_idx + 1); a.ln_eps = c.cfg.ln_eps;
+    } else {
+      AD_TRY(ln(h, rows, ch, g_idx, temp(0)));
+      a.src0 = temp(0);
     }
-    AD_TRY(ln(h, rows, ch, g_idx, temp(0)));
-    a.src0 = temp(0);
     return launch_conv(a, s);
   }
 
@@ -203,19 +198,21 @@ struct Eval {
     // gn.g gn.b proj_in.w proj_in.b | per layer 20 entries | proj_out.w proj_out.b
     AD_TRY(gn(x, nullptr, Cc, 0, L, w + 0, 0, temp(0)));
     if (tfm_rows_fits(dt, Cc, d, Lk, (long long)B * L)) return tfm_by_rows(f, w, x, tensor_out(ui), ui);
-    int width = 0;
-    AD_TRY(linear(temp(0), M, Cc, w + 2, w + 3, nullptr, temp(1), OUT_ROWMAJOR, 1, 0, w + 6, &width));
+    WView wv{c};
+    int width = 0;                                     // of the sums that the launch in front of a LayerNorm has left
+    const Next qkv{3 * Cc, OUT_QKV, &width}, query{Cc, OUT_ROWMAJOR, &width}, inner{8 * Cc, OUT_GEGLU, &width};
+    AD_TRY(linear(temp(0), M, Cc, w + 2, w + 3, nullptr, temp(1), OUT_ROWMAJOR, 1, 0, qkv));
     w += 4;
     void* h = temp(1);
     for (int k = 0; k < f.depth; ++k, w += 20) {
       // ln1.g ln1.b a1.q a1.k a1.v a1.o.w a1.o.b ln2.g ln2.b a2.q a2.k a2.v a2.o.w a2.o.b ln3.g ln3.b ff1.w ff1.b ff2.w ff2.b
       // q, k, v of the self-attention in one GEMM; v lands transposed when the MFMA attention kernel follows
-      AD_TRY(ln_linear(h, M, Cc, w + 0, w + 2, width, ConvArgs{dt, nullptr, nullptr, Cc, 0, B, L, 1, 0, 1, 1, nullptr, 3 * Cc, nullptr, nullptr, 0, nullptr, temp(2), OUT_QKV,
+      AD_TRY(ln_linear(h, M, Cc, w + 0, width, ConvArgs{dt, nullptr, nullptr, Cc, 0, B, L, 1, 0, 1, 1, wv.at(w + 2), 3 * Cc, nullptr, nullptr, 0, nullptr, temp(2), OUT_QKV,
                                                         vt ? lp : 0, temp(9), ws.temp_bytes[9], temp(3), temp(4)}));
       AD_TRY(launch_attention(dt, temp(2), temp(3), temp(4), vt, B, L, L, Cc, d, Cc, Cc, vt ? lp : Cc, Cc, temp(5), s));
-      AD_TRY(linear(temp(5), M, Cc, w + 5, w + 6, h, h, OUT_ROWMAJOR, 1, 0, w + 9, &width));
-      AD_TRY(ln_linear(h, M, Cc, w + 7, w + 9, width, ConvArgs{dt, nullptr, nullptr, Cc, 0, 1, M, 1, 0, 1, 1, nullptr, Cc, nullptr, nullptr, 0, nullptr, temp(2), OUT_ROWMAJOR, 0,
-                                                        temp(9), ws.temp_bytes[9]}));
+      AD_TRY(linear(temp(5), M, Cc, w + 5, w + 6, h, h, OUT_ROWMAJOR, 1, 0, query));
+      AD_TRY(ln_linear(h, M, Cc, w + 7, width, ConvArgs{dt, nullptr, nullptr, Cc, 0, 1, M, 1, 0, 1, 1, wv.at(w + 9), Cc, nullptr, nullptr, 0, nullptr, temp(2), OUT_ROWMAJOR,
+                                                        0, temp(9), ws.temp_bytes[9]}));
       // keys / values of the text: taken from the per-run cache when it was built from this embedding
       const void* tk = temp(7);
       const void* tv = temp(8);
@@ -228,18 +225,17 @@ struct Eval {
       // video: every frame attends to the one text embedding, so the frames' tokens form one long query sequence
       if (c.cfg.frames > 0) AD_TRY(launch_attention(dt, temp(2), tk, tv, vt, 1, M, Lk, Cc, d, Cc, Cc, vt ? lkp : Cc, Cc, temp(5), s));
       else AD_TRY(launch_attention(dt, temp(2), tk, tv, vt, B, L, Lk, Cc, d, Cc, Cc, vt ? lkp : Cc, Cc, temp(5), s));
-      AD_TRY(linear(temp(5), M, Cc, w + 12, w + 13, h, h, OUT_ROWMAJOR, 1, 0, w + 16, &width));
-      AD_TRY(ln_linear(h, M, Cc, w + 14, w + 16, width, ConvArgs{dt, nullptr, nullptr, Cc, 0, 1, M, 1, 0, 1, 1, nullptr, 8 * Cc, WView{c}.f32(w + 17), nullptr, 0, nullptr, temp(6),
-                                                          OUT_GEGLU, 0, temp(9), ws.temp_bytes[9]}));
-      if (k + 1 < f.depth) AD_TRY(linear(temp(6), M, 4 * Cc, w + 18, w + 19, h, h, OUT_ROWMAJOR, 1, 0, w + 22, &width));
-      else AD_TRY(linear(temp(6), M, 4 * Cc, w + 18, w + 19, h, h));
+      AD_TRY(linear(temp(5), M, Cc, w + 12, w + 13, h, h, OUT_ROWMAJOR, 1, 0, inner));
+      AD_TRY(ln_linear(h, M, Cc, w + 14, width, ConvArgs{dt, nullptr, nullptr, Cc, 0, 1, M, 1, 0, 1, 1, wv.at(w + 16), 8 * Cc, wv.f32(w + 17), nullptr, 0, nullptr, temp(6),
+                                                         OUT_GEGLU, 0, temp(9), ws.temp_bytes[9]}));
+      AD_TRY(linear(temp(6), M, 4 * Cc, w + 18, w + 19, h, h, OUT_ROWMAJOR, 1, 0, k + 1 < f.depth ? qkv : Next{0, 0, nullptr}));
     }
     void* z = tensor_out(ui);
-    if (c.cfg.temporal_heads == 0) return linear(h, M, Cc, w + 0, w + 1, x, z);
-    AD_TRY(linear(h, M, Cc, w + 0, w + 1, x, z, OUT_ROWMAJOR, 1, 0, w + 4, &width));
+    AD_TRY(linear(h, M, Cc, w + 0, w + 1, x, z, OUT_ROWMAJOR, 1, 0, c.cfg.temporal_heads ? qkv : Next{0, 0, nullptr}));
+    if (c.cfg.temporal_heads == 0) return AD_OK;
     // temporal layer: temp.ln.g temp.ln.b temp.q temp.k temp.v temp.o.w temp.o.b; tokens = the frames of one position
     w += 2;
-    AD_TRY(ln_linear(z, M, Cc, w + 0, w + 2, width, ConvArgs{dt, nullptr, nullptr, Cc, 0, B, L, 1, 0, 1, 1, nullptr, 3 * Cc, nullptr, nullptr, 0, nullptr, temp(2), OUT_QKV,
+    AD_TRY(ln_linear(z, M, Cc, w + 0, width, ConvArgs{dt, nullptr, nullptr, Cc, 0, B, L, 1, 0, 1, 1, wv.at(w + 2), 3 * Cc, nullptr, nullptr, 0, nullptr, temp(2), OUT_QKV,
                                                       0, temp(9), ws.temp_bytes[9], temp(3), temp(4)}));
     AD_TRY(launch_attention_frames(dt, temp(2), temp(3), temp(4), c.cfg.frames, L, Cc, c.cfg.temporal_heads, Cc, Cc, Cc, Cc, temp(5), s));
     return linear(temp(5), M, Cc, w + 5, w + 6, z, z);
@@ -438,17 +434,6 @@ ad_status ad_load_weights(ad_ctx* ctx, const float* const* host_ptrs, int n) {
     if (w.fragments) pack_fragments(stage.data(), w.n_pad, w.k_pad * (int)esize(dt));
     else pack_blocks(stage.data(), w.n_pad, w.k_pad * (int)esize(dt));
   };
-  // sums of the packed rows (still in rows) and the bias with a norm's offset in it
-  auto load_ln = [&](const Weight& w, const std::vector<float>& bias) -> ad_status {
-    std::vector<float> v(2 * (size_t)w.n_pad, 0.f);
-    for (int r = 0; r < w.n_pad; ++r) {
-      v[r] = packed_row_sum(dt, stage.data() + (size_t)r * w.k_pad * esize(dt), w.k_pad);
-      const int n = w.info.shape[0];
-      v[w.n_pad + r] = bias[w.role == W_GEGLU && r < n ? geglu_row(r, n) : r];
-    }
-    AD_HIP(hipMemcpy(c.weights_dev + w.ln_off, v.data(), v.size() * 4, hipMemcpyHostToDevice));
-    return AD_OK;
-  };
   // the fused time-projection matrix is assembled from the ResBlocks' rows
   std::vector<char> temb_w((size_t)c.temb_rows_total * c.temb_dim * esize(dt));
   std::vector<float> temb_b((size_t)c.temb_rows_total);
@@ -457,24 +442,6 @@ ad_status ad_load_weights(ad_ctx* ctx, const float* const* host_ptrs, int n) {
     const Weight& w = c.weights[i];
     const int* sh = w.info.shape;
     const float* src = host_ptrs[i];
-    if (w.absorbed) {                     // a gain (followed by its offset) that is in the operand behind it
-      const bool gain = w.info.name[std::strlen(w.info.name) - 1] == 'g';
-      stage.assign(w.dev_bytes, 0);
-      std::fill_n((float*)stage.data(), sh[0], gain ? 1.f : 0.f);
-      AD_HIP(hipMemcpy(c.weights_dev + w.dev_off, stage.data(), w.dev_bytes, hipMemcpyHostToDevice));
-      continue;
-    }
-    std::vector<float> scaled, bias;
-    if (w.ln >= 0) {
-      const int parts = w.role == W_QKV_Q ? 3 : 1;
-      const bool own = w.role == W_GEGLU;                    // the one with a bias, which follows it
-      scaled.resize((size_t)parts * sh[0] * sh[1]);
-      bias.assign(w.n_pad, 0.f);
-      for (int j = 0; j < parts; ++j)
-        fold_layernorm(host_ptrs[i + j], sh[0], sh[1], host_ptrs[w.ln], host_ptrs[w.ln + 1], own ? host_ptrs[i + 1] : nullptr,
-                       scaled.data() + (size_t)j * sh[0] * sh[1], bias.data() + j * sh[0]);
-      src = scaled.data();
-    }
     if (w.role == W_TEMB) {
       pack_rows(dt, src, (size_t)sh[0] * sh[1], temb_w.data() + temb_row * c.temb_dim * esize(dt));
       continue;
@@ -483,11 +450,9 @@ ad_status ad_load_weights(ad_ctx* ctx, const float* const* host_ptrs, int n) {
     if (w.role == W_QKV_Q) {
       const size_t each = (size_t)sh[0] * sh[1];
       std::vector<float> cat(3 * each);
-      if (w.ln >= 0) cat.swap(scaled);
-      else for (int j = 0; j < 3; ++j) std::memcpy(cat.data() + j * each, host_ptrs[i + j], each * 4);
+      for (int j = 0; j < 3; ++j) std::memcpy(cat.data() + j * each, host_ptrs[i + j], each * 4);
       stage.assign(w.dev_bytes, 0);
       pack_conv(dt, cat.data(), 3 * sh[0], sh[1], 1, false, stage.data());
-      if (w.ln >= 0) AD_TRY(load_ln(w, bias));
       arrange(w);
       AD_HIP(hipMemcpy(c.weights_dev + w.dev_off, stage.data(), w.dev_bytes, hipMemcpyHostToDevice));
       continue;
@@ -513,12 +478,17 @@ ad_status ad_load_weights(ad_ctx* ctx, const float* const* host_ptrs, int n) {
       }
       case W_SMALL: pack_rows(dt, src, (size_t)sh[0] * sh[1], stage.data()); break;
       case W_VEC_F32: std::memcpy(stage.data(), src, (size_t)sh[0] * 4); break;
-      case W_GEGLU_BIAS:
-        for (int r = 0; r < sh[0]; ++r) ((float*)stage.data())[r] = src[geglu_row(r, sh[0])];
+      case W_GEGLU_BIAS: {
+        float* dst = (float*)stage.data();
+        const int half = sh[0] / 2;
+        for (int r = 0; r < sh[0]; ++r) {
+          const int blk = r / 64, in = r % 64;
+          dst[r] = src[in < 32 ? blk * 32 + in : half + blk * 32 + in - 32];
+        }
         break;
+      }
       default: break;
     }
-    if (w.ln >= 0) AD_TRY(load_ln(w, bias));
     arrange(w);
     AD_HIP(hipMemcpy(c.weights_dev + w.dev_off, stage.data(), w.dev_bytes, hipMemcpyHostToDevice));
   }
