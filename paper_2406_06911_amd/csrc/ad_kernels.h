@@ -48,8 +48,8 @@ struct ConvArgs {
   const void* x0 = nullptr; const void* x1 = nullptr;
   int xc0 = 0, xc1 = 0;
   const void* xw = nullptr;             // packed [n_pad][xc0 + xc1]
-  // a LayerNorm over the channels in front of a linear layer, only where conv_takes_ln() says so: pairs (sum, squared deviations from their own mean;
-  // bf16: sum of squares) of every ln_width columns of a source row, gain and offset of the channels, epsilon
+  // a LayerNorm over the channels in front of a linear layer, only where conv_takes_ln() says so: pairs (sum, squared deviations from their own mean) of
+  // every ln_width columns of a source row, gain and offset of the channels, epsilon
   const float* ln_in = nullptr; const float* ln_gain = nullptr; const float* ln_offset = nullptr;
   float ln_eps = 0.f;
   float* ln_out = nullptr;              // leave those pairs of the output's rows here, [m][n_out / ln_width]; ln_width = conv_ln_width()

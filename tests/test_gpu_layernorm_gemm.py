@@ -131,3 +131,17 @@ def test_gains_are_not_rounded_into_the_weights(monkeypatch, tile, c):
     assert ("layernorm" in names) == (tile != AUTO), names
     # three roundings of at most 2^-9 (the block's input and output, the probabilities' sum)
     assert rel_l2(got, want) < 6e-3, rel_l2(got, want)
+
+
+@pytest.mark.parametrize("site", [1, 3])
+@pytest.mark.parametrize("tile,c,count", [(AUTO, 192, 11), (AUTO, 320, 13), (AUTO, 576, 11), (P3_64, 320, 13)])
+def test_bf16_rows_with_an_offset(monkeypatch, tile, c, count, site):
+    """Rows of 772 and a few 776, neighbours in bf16: a mean of 800 standard deviations or more.  The variance has to come from the deviations: the mean of
+    the squares less the square of the mean is off by 2 to 7 % of the deviation here, in fp32, where the mean is no short binary fraction."""
+    d, rng = config(c, 1, 5, 4, 2), np.random.default_rng(13)
+    row = np.full(c, 772.0)
+    row[rng.permutation(c)[:count]] = 776
+    got, want, names = block(monkeypatch, d, BF, tile, one_norm(d, row, 0, site, 2.0 ** 14, rng))
+    assert ("layernorm" in names) == (tile != AUTO), names
+    # seven roundings of 1.1e-3 (norm, value or inner row, probabilities, hidden row, result) and a mean off by two of its own, 9e-5 of a standard deviation
+    assert rel_l2(got, want) < 8e-3, rel_l2(got, want)
