@@ -936,12 +936,14 @@ static ad_status run_igemm_p3(const IgemmParams& p0, const char* name, hipStream
 // the row's mean nor the gain goes through the product: taken off the sum over K the mean costs relative precision by its ratio to the row's spread
 // (fp32, 256 channels, 100 standard deviations: 1.1e-5 instead of 3.6e-6; rows of one value 1e-2 instead of 1.8e-7), and a gain that is rounded into bf16
 // weights shows where the products cancel (3e-2 instead of 2e-3).  The statistics are combined in front of the k-loop from what the launch that wrote the
-// rows leaves beside them: for every 16 or 32 columns (its tile's) the sum and the squared deviations from their own mean, as exact as a second pass over the
-// row (the mean of the squares less the square of the mean, bf16 rows with a mean of 800 standard deviations: 2e-2 to 1.6e-1 behind the layer
-// instead of 3e-3 to 4e-3).
-// Whole runs, ms (a launch for the norm -> this): narrow model 37.7 -> 36.8, fp32 17.3 -> 17.0, with stride 2 27.1 -> 26.1, 576x320 px 64.1 -> 63.8, 512px
-// level.  The vector work is that of a k-tile or two a wavefront; the larger tiles, whose LDS is filled by the load unit and whose fragments every column
-// tile would normalise again, leave the norm to k_layernorm.
+// rows leaves beside them: for every 16 or 32 columns (its tile's) the sum and the squared deviations from their own mean, as exact as a second pass over
+// the row (the mean of the squares less the square of the mean, bf16 rows with a mean of 800 standard deviations: 2e-2 to 1.6e-1 behind the layer instead
+// of 3e-3 to 4e-3).
+// Measured inside the models, us (norm + GEMM -> GEMM; the launch in front takes 0.1 longer): bf16 72x768x256 3.7 + 4.1 -> 4.5, 72x2048x256 3.7 + 4.5 -> 5.7,
+// 128x2048x256 3.7 + 4.1 -> 5.4, 18x2048x256 3.3 + 4.6 -> 6.2, 180x1280x1280 3.9 + 8.1 -> 8.7, 45x1280x1280 3.9 + 5.6 -> 7; fp32 288x384x128 3.7 + 3.8 -> 4.7,
+// 288x1024x128 3.7 + 5.7 -> 6.9, 72x2048x256 3.7 + 5.6 -> 7.1.  Whole runs, ms: narrow model 37.7 -> 36.8, fp32 17.3 -> 17.0, with stride 2 27.1 -> 26.1,
+// 576x320 px 64.1 -> 63.8, 512px level.  The vector work is that of a k-tile or two a wavefront; the larger tiles, whose LDS is filled by the load unit and
+// whose fragments every column tile would normalise again, leave the norm to k_layernorm.
 // =================================================================================================
 constexpr int kLnLoads = 5;                              // pairs (two at a time) a thread takes in; 16 threads a row and pairs of 16 columns: 2560 columns
 constexpr int kLnMost = kLnLoads * 16 * 2 * 16;
@@ -2315,8 +2317,9 @@ __global__ __attribute__((amdgpu_waves_per_eu(OCC, OCC))) __launch_bounds__(64 *
       for (int ks = 1; ks < 4; ++ks) sc[s] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[ks], qf[s][ks], sc[s], 0, 0, 0);
     }
     // between its products a wavefront goes ahead of those that have matrix work to issue: its exponentials are what the next products wait for, theirs
-    // queue up anyway.  4096 tokens, 2 x 5 heads 65.9 -> 61.8 us, 2304, 2 x 10 40.1 -> 39.0, 2880, 5 22.0 -> 21.1, 9216 and 4096, 2 x 10 0.5 to 1.5 %
-    // slower alone; whole runs 512px 1.006, 768px 1.004, 1024px 1.004, video 1.003 (the products ahead instead: 1-2 % slower)
+    // queue up anyway.  Alone, us: 4096 tokens, 2 x 5 heads 65.9 -> 61.8, 2304, 2 x 10 40.1 -> 39.0, 2880, 5 22.0 -> 21.1, 9216, 2 x 5 227.6 -> 228.9, 4096,
+    // 2 x 10 100.9 -> 102.5 (inside the models on one stream 240.1 -> 240.8 and 107.6 -> 108.3, and all attention of a step 512px 458 -> 443, 768px 1485 -> 1481,
+    // 1024px 2459 -> 2428, video 2055 -> 2040); whole runs 512px 1.006, 768px 1.004, 1024px 1.004, video 1.003 (the products ahead instead: 1-2 % slower)
     __builtin_amdgcn_s_setprio(1);
     // the V^T fragments are requested before the exponentials so that they have arrived when the PV products start
     bf16x8 vf[2][2];
