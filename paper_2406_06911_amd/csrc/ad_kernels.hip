@@ -940,7 +940,7 @@ static ad_status run_igemm_p3(const IgemmParams& p0, const char* name, hipStream
 // the row (the mean of the squares less the square of the mean, bf16 rows with a mean of 800 standard deviations: 2e-2 to 1.6e-1 behind the layer instead
 // of 3e-3 to 4e-3).
 // Measured inside the models, us (norm + GEMM -> GEMM; the launch in front takes 0.1 longer): bf16 72x768x256 3.7 + 4.1 -> 4.5, 72x2048x256 3.7 + 4.5 -> 5.7,
-// 128x2048x256 3.7 + 4.1 -> 5.4, 18x2048x256 3.3 + 4.6 -> 6.2, 180x1280x1280 3.9 + 8.1 -> 8.7, 45x1280x1280 3.9 + 5.6 -> 7; fp32 288x384x128 3.7 + 3.8 -> 4.7,
+// 128x2048x256 3.7 + 4.1 -> 5.4, 18x2048x256 3.3 + 4.6 -> 6.2, 180x1280x1280 3.9 + 8.1 -> 9.5, 45x1280x1280 3.9 + 5.6 -> 8; fp32 288x384x128 3.7 + 3.8 -> 4.7,
 // 288x1024x128 3.7 + 5.7 -> 6.9, 72x2048x256 3.7 + 5.6 -> 7.1.  Whole runs, ms: narrow model 37.7 -> 36.8, fp32 17.3 -> 17.0, with stride 2 27.1 -> 26.1,
 // 576x320 px 64.1 -> 63.8, 512px level.  The vector work is that of a k-tile or two a wavefront; the larger tiles, whose LDS is filled by the load unit and
 // whose fragments every column tile would normalise again, leave the norm to k_layernorm.
@@ -1704,6 +1704,8 @@ bool conv_takes_shortcut(int dtype, long long m, int n, int c, int xc) {
   }
 }
 
+// Wherever the layer is a small-tile launch: every shape measured (above the kernel, 18 to 288 rows, 128 to 1280 channels) gains 1.5 to 3.3 us.  Not beyond
+// kLnMost channels, the pairs of sums a thread holds.
 bool conv_takes_ln(int dtype, long long m, int n, int c, int out_mode, bool any_tile) {
   if (c % 64 || c > kLnMost || (out_mode != OUT_ROWMAJOR && out_mode != OUT_QKV && out_mode != OUT_GEGLU)) return false;
   const int ktiles = c / bk_elems(dtype);
