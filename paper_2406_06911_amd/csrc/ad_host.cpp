@@ -495,9 +495,6 @@ static void plan_work(Ctx& c) {
           want(6, m_in * 4 * C * es);
           want(7, B * g.ctx_len * C * es);
           want(8, B * C * lkp * es);
-          // sums of the rows for a LayerNorm inside the layer behind it: two floats for 16 columns at the least
-          for (const auto& [n, md] : {std::pair<int, int>{3 * (int)C, OUT_QKV}, {(int)C, OUT_ROWMAJOR}, {8 * (int)C, OUT_GEGLU}})
-            if (!tfm_rows_fits(g.dtype, (int)C, g.head_dim, g.ctx_len, (long long)m_in) && conv_takes_ln(g.dtype, (long long)m_in, n, (int)C, md, true)) want(10, m_in * C / 16 * 8);
           gemm(m_in, (int)C, (int)C);
           gemm(m_in, (int)(3 * C), (int)C, OUT_QKV);
           gemm(m_in, (int)C, (int)(4 * C));

@@ -76,7 +76,7 @@ struct Component {
 };
 
 // Activation workspace of one (component, lane): offsets into the work arena.
-constexpr int kNumTemps = 11;
+constexpr int kNumTemps = 10;
 struct Workspace {
   std::vector<size_t> unit_off;        // per unit of the component (index unit - first); SIZE_MAX = external output
   size_t temp_off[kNumTemps] = {0};

@@ -48,12 +48,9 @@ struct ConvArgs {
   const void* x0 = nullptr; const void* x1 = nullptr;
   int xc0 = 0, xc1 = 0;
   const void* xw = nullptr;             // packed [n_pad][xc0 + xc1]
-  // a LayerNorm over the channels in front of a linear layer, only where conv_takes_ln() says so: pairs (sum, squared deviations from their own mean) of
-  // every ln_width columns of a source row, gain and offset of the channels, epsilon
-  const float* ln_in = nullptr; const float* ln_gain = nullptr; const float* ln_offset = nullptr;
+  // a LayerNorm over the channels in front of a linear layer, only where conv_takes_ln() says so: gain and offset of the channels, epsilon
+  const float* ln_gain = nullptr; const float* ln_offset = nullptr;
   float ln_eps = 0.f;
-  float* ln_out = nullptr;              // leave those pairs of the output's rows here, [m][n_out / ln_width]; ln_width = conv_ln_width()
-  int ln_width = 0;
   int w_blocks = 0;                     // w and xw are in blocks (pack_blocks()) instead of rows
 };
 // OUT_QKV: n_out = 3c; thirds go to out [m][c], out2 [m][c] and out3 ([batch][c][ld_t] when ld_t > 0, else [m][c])
@@ -66,10 +63,8 @@ void set_order_override(int order);   // -1 automatic, 0 row-tile-major, 1 colum
 // scratch a convolution of this shape wants for split-K (0 = it will not split); k = taps * channels
 size_t conv_workspace_bytes(int dtype, long long m, int n, int k, int out_mode);
 bool conv_takes_shortcut(int dtype, long long m, int n, int c, int xc);      // c, xc: channels of the 3x3 and of the 1x1 convolution
-// whether a LayerNorm over c channels goes into the launch of the linear layer behind it (any_tile: whatever tile is forced)
-bool conv_takes_ln(int dtype, long long m, int n, int c, int out_mode, bool any_tile = false);
-// columns a pair of row sums covers when a row-major launch of this shape leaves them (16 or 32; 0: it cannot)
-int conv_ln_width(int dtype, long long m, int n, int k);
+// whether a LayerNorm over c channels goes into the launch of the linear layer behind it
+bool conv_takes_ln(int dtype, long long m, int n, int c, int out_mode);
 
 ad_status launch_groupnorm(int dtype, const void* src0, const void* src1, int c0, int c1, int batch, int hw, int groups,
                            const float* gamma, const float* beta, float eps, int silu, void* out, void* scratch,

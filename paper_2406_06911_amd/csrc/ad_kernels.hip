@@ -43,7 +43,6 @@ ProfLaunch::~ProfLaunch() {
 // tiles.  One k-tile is 128 bytes of K per row (64 bf16 / 32 fp32), staged through LDS with a
 // 16-byte row pad; the next k-tile is fetched into registers while the current one is multiplied.
 // =================================================================================================
-struct LnOut { float* pairs; int slabs, shift; };   // where the sums of the output's rows go (null: nowhere), pairs a row, log2 of the columns of a pair
 struct IgemmParams {
   const void* src0; const void* src1;
   int c0, c1, ctot;
@@ -67,8 +66,7 @@ struct IgemmParams {
   const void* x0; const void* x1; const void* xw;       // XTRA (k_igemm_p3): sources and weights of the 1x1 convolution behind the taps
   int xc0, xc1, kt_main;                                // its channels; k-tiles of the taps
   unsigned xbytes0, xbytes1, xbytes_w;
-  const float* ln_in; const float* ln_gain; const float* ln_offset; int ln_slabs; float ln_eps;      // LN (k_igemm_small): pairs of the operand's rows
-  LnOut ln_out;
+  const float* ln_gain; const float* ln_offset; float ln_eps;      // LN (k_igemm_small)
 };
 
 // Byte offset of a row of a packed operand within a k-tile (k-tile kt is kt * p.w_kt further).  Two layouts: rows of k_bytes one after the other
@@ -934,51 +932,67 @@ static ad_status run_igemm_p3(const IgemmParams& p0, const char* name, hipStream
 // LN: a LayerNorm in front of the (linear) layer, without a launch and a pass through memory of its own: the fragments of the rows are normalised in
 // registers on their way into the matrix cores, with the arithmetic of k_layernorm (fp32 statistics, gain and offset, the result rounded to T).  Neither
 // the row's mean nor the gain goes through the product: taken off the sum over K the mean costs relative precision by its ratio to the row's spread
-// (fp32, 256 channels, 100 standard deviations: 1.1e-5 instead of 3.6e-6; rows of one value 1e-2 instead of 1.8e-7), and a gain that is rounded into bf16
-// weights shows where the products cancel (3e-2 instead of 2e-3).  The statistics are combined in front of the k-loop from what the launch that wrote the
-// rows leaves beside them: for every 16 or 32 columns (its tile's) the sum and the squared deviations from their own mean, as exact as a second pass over
-// the row (the mean of the squares less the square of the mean, bf16 rows with a mean of 800 standard deviations: 2e-2 to 1.6e-1 behind the layer instead
-// of 3e-3 to 4e-3).
-// Measured inside the models, us (norm + GEMM -> GEMM; the launch in front takes 0.1 longer): bf16 72x768x256 3.7 + 4.1 -> 4.5, 72x2048x256 3.7 + 4.5 -> 5.7,
-// 128x2048x256 3.7 + 4.1 -> 5.4, 18x2048x256 3.3 + 4.6 -> 6.2, 180x1280x1280 3.9 + 8.1 -> 9.5, 45x1280x1280 3.9 + 5.6 -> 8; fp32 288x384x128 3.7 + 3.8 -> 4.7,
-// 288x1024x128 3.7 + 5.7 -> 6.9, 72x2048x256 3.7 + 5.6 -> 7.1.  Whole runs, ms: narrow model 37.7 -> 36.8, fp32 17.3 -> 17.0, with stride 2 27.1 -> 26.1,
-// 576x320 px 64.1 -> 63.8, 512px level.  The vector work is that of a k-tile or two a wavefront; the larger tiles, whose LDS is filled by the load unit and
-// whose fragments every column tile would normalise again, leave the norm to k_layernorm.
+// (fp32, 256 channels, 100 standard deviations: 1.1e-5 instead of 3.5e-6; rows of one value 1e-2), and a gain that is rounded into bf16 weights shows where
+// the products cancel (3e-2 instead of 2e-3).  The statistics are those of k_layernorm to the bit: a workgroup reads its rows, 16 bytes a thread, ahead of
+// the fragments and adds them up in two passes in the order of 64 lanes a row.  (Sums and squared deviations that the launch in front leaves for every 16 or
+// 32 columns save that reading, level in time, but are another order of the sums: whole bf16 runs differed by 2e-3 to 6e-3 from those with a launch.)
+// Gain and offset go through LDS: in registers, two k-tiles ahead like the fragments, they take 64 of them.
+// Measured inside the models, us (norm + GEMM -> GEMM): bf16 72x768x256 3.6 + 3.8 -> 5.5, 72x2048x256 3.6 + 4.5 -> 6.0, 18x2048x256 3.3 + 4.2 -> 5.9, 45x3840x1280
+// 3.9 + 8.6 -> 11.0; fp32 288x384x128 3.6 + 4.0 -> 5.2, 288x1024x128 3.6 + 6.2 -> 7.6, 72x2048x256 3.6 + 6.0 -> 7.6; and the gap between two launches.  Whole runs
+// against a launch for every norm, ms: narrow model 37.28 -> 36.73, fp32 17.53 -> 17.21, with stride 2 27.04 -> 25.84, 576x320 px 64.39 -> 64.13, 512px level.
+// The larger tiles, whose LDS is filled by the load unit and whose fragments every column tile would normalise again, leave the norm to k_layernorm.
 // =================================================================================================
-constexpr int kLnLoads = 5;                              // pairs (two at a time) a thread takes in; 16 threads a row and pairs of 16 columns: 2560 columns
-constexpr int kLnMost = kLnLoads * 16 * 2 * 16;
-template <int LANES>                                     // sum over 4 or 8 neighbouring lanes
-__device__ __forceinline__ float ln_lanes(float v) {
-  v += dpp_f<0xB1>(v);                                   // quad_perm 1 0 3 2
-  v += dpp_f<0x4E>(v);                                   // quad_perm 2 3 0 1
-  return LANES == 8 ? v + dpp_f<0x141>(v) : v;           // row_half_mirror
-}
-template <int TPR>                                       // over the 16 or 32 threads of a row
+constexpr int small_ktiles(int bm, int bn) { return 200 * 1024 / ((bm + bn) * kRowBytes); }      // k-tiles that small_tile() takes at the most
+// Sum over the threads of a row, TPR = 16 or 32 neighbouring lanes, as k_layernorm's lanes add up: distances 32 / TPR .. 1, where a distance within 16 lanes is a
+// rotation, since the lanes that it brings together hold the same already.
+template <int TPR>
 __device__ __forceinline__ float ln_threads(float v) {
-  v = ln_lanes<8>(v);
-  v += dpp_f<0x140>(v);                                  // row_mirror
-  return TPR == 32 ? v + __shfl_xor(v, 16, 64) : v;
+  if (TPR == 32) v += __shfl_xor(v, 16, 64);
+  v += dpp_f<0x128>(v);                                  // row_ror 8
+  v += dpp_f<0x124>(v);                                  // row_ror 4
+  v += dpp_f<0x4E>(v);                                   // quad_perm 2 3 0 1
+  return v + dpp_f<0xB1>(v);                             // quad_perm 1 0 3 2
 }
-template <int TPR>
-__device__ __forceinline__ void ln_load(const IgemmParams& p, int row, int sub, f32x4 (&v)[kLnLoads]) {
-  const f32x4* src = (const f32x4*)(p.ln_in + (size_t)2 * p.ln_slabs * min(row, p.M - 1));
+// What k_layernorm and a linear layer with the norm inside have in common: the squared deviations of an access added to those of the lane's earlier ones
+// (first: there are none), and the norm of an element, with the products fused as written here and not as the compiler would choose for either of them.
+template <typename V>
+__device__ __forceinline__ float ln_squares(const V& x, float mean, float q, bool first) {
+  const float d0 = to_f(x[0]) - mean, d1 = to_f(x[1]) - mean;
+  q = first ? fmaf(d0, d0, d1 * d1) : fmaf(d1, d1, fmaf(d0, d0, q));
 #pragma unroll
-  for (int i = 0; i < kLnLoads; ++i) v[i] = 2 * (sub + i * TPR) < p.ln_slabs ? src[sub + i * TPR] : f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int e = 2; e < (int)(sizeof(V) / sizeof(x[0])); ++e) { const float d = to_f(x[e]) - mean; q = fmaf(d, d, q); }
+  return q;
 }
-template <int TPR>
-__device__ __forceinline__ void ln_fold(const IgemmParams& p, int sub, const f32x4 (&v)[kLnLoads], float* mean_out, float* rstd_out) {
-  float sum = 0.f, sq = 0.f;
+__device__ __forceinline__ float ln_value(float x, float mean, float rstd, float gain, float offset) { return fmaf((x - mean) * rstd, gain, offset); }
+// Thread `sub` of a row has its accesses sub, sub + TPR, ...: those of the lanes sub, sub + TPR, ... of 64, each of which k_layernorm sums for itself.  (Where it
+// gives a row fewer lanes, each has one access at the most in all launches that small_tile() takes, and the sums are the same.)
+template <typename T, int TPR, int LD>
+__device__ __forceinline__ void ln_load(const IgemmParams& p, int row, int sub, typename Vec<T>::type (&x)[LD]) {
+  typedef typename Vec<T>::type V;
+  const T* rp = (const T*)p.src0 + (size_t)min(row, p.M - 1) * p.ctot;
 #pragma unroll
-  for (int i = 0; i < kLnLoads; ++i) sum += v[i][0] + v[i][2];
-  const float mean = ln_threads<TPR>(sum) / p.ctot, width = (float)(p.ctot / p.ln_slabs), per = 1.f / width;       // (a power of two)
+  for (int i = 0; i < LD; ++i)
+    if ((sub + TPR * i) * Vec<T>::N < p.ctot) x[i] = *(const V*)(rp + (sub + TPR * i) * Vec<T>::N);
+}
+template <typename T, int TPR, int LD>
+__device__ __forceinline__ void ln_stats(const IgemmParams& p, int sub, const typename Vec<T>::type (&x)[LD], float* mean_out, float* rstd_out) {
+  constexpr int VN = Vec<T>::N, LANES = 64 / TPR;
+  auto row_sum = [&](const float (&v)[LANES]) {
+    if constexpr (LANES == 4) return ln_threads<TPR>((v[0] + v[2]) + (v[1] + v[3]));
+    else return ln_threads<TPR>(v[0] + v[1]);
+  };
+  float s[LANES] = {}, q[LANES] = {};
 #pragma unroll
-  for (int i = 0; i < kLnLoads; ++i)
-    if (2 * (sub + i * TPR) < p.ln_slabs) {
-      const float d0 = v[i][0] * per - mean, d1 = v[i][2] * per - mean;
-      sq += (v[i][1] + v[i][3]) + width * (d0 * d0 + d1 * d1);
-    }
-  sq = ln_threads<TPR>(sq);
-  if (sub == 0) { *mean_out = mean; *rstd_out = rsqrtf(sq / p.ctot + p.ln_eps); }
+  for (int i = 0; i < LD; ++i)
+    if ((sub + TPR * i) * VN < p.ctot)
+#pragma unroll
+      for (int e = 0; e < VN; ++e) s[i % LANES] += to_f(x[i][e]);
+  const float mean = row_sum(s) / p.ctot;
+#pragma unroll
+  for (int i = 0; i < LD; ++i)
+    if ((sub + TPR * i) * VN < p.ctot) q[i % LANES] = ln_squares(x[i], mean, q[i % LANES], i < LANES);
+  const float rstd = rsqrtf(row_sum(q) / p.ctot + p.ln_eps);
+  if (sub == 0) { *mean_out = mean; *rstd_out = rstd; }
 }
 
 template <typename T, int TM, int TN, int MODE, bool LN = false>
@@ -1030,19 +1044,7 @@ __global__ __launch_bounds__(512) void k_igemm_small(IgemmParams p) {
   int f_tap = wave * BK / p.ctot, f_cc = wave * BK - f_tap * p.ctot;
   unsigned f_w = (unsigned)wave * p.w_kt;
   V af[PF][TM][2], bf[PF][TN][2];
-  constexpr int GQ = VN / 4;                             // gains and offsets of a fragment, four at a time
-  f32x4 gain[LN ? PF : 1][2][GQ], offset[LN ? PF : 1][2][GQ];
   auto fetch = [&](int s) {
-    if constexpr (LN) {
-#pragma unroll
-      for (int h = 0; h < 2; ++h)
-#pragma unroll
-        for (int q = 0; q < GQ; ++q) {
-          const int at = f_cc + (h * 64 + kg * 16) / ES + 4 * q;
-          gain[s][h][q] = *(const f32x4*)(p.ln_gain + at);
-          offset[s][h][q] = *(const f32x4*)(p.ln_offset + at);
-        }
-    }
     const int u = p.ksize == 3 ? f_tap / 3 : 0, v = p.ksize == 3 ? f_tap - 3 * u : 0;
     const unsigned bit = 1u << (u * 3 + v), sb = f_w;
 #pragma unroll
@@ -1066,10 +1068,20 @@ __global__ __launch_bounds__(512) void k_igemm_small(IgemmParams p) {
     if constexpr (LN) return;                            // one tap, one source
     while (f_cc >= p.ctot) { f_cc -= p.ctot; ++f_tap; }
   };
-  constexpr int TPR = 64 * NW / BM;                      // LN: threads a row
+  // LN: threads a row, the accesses of 16 bytes a thread has to it and to gain and offset at the most, and what is asked for ahead of the fragments
+  constexpr int TPR = 64 * NW / BM, KT = LN ? small_ktiles(BM, BN) : 0, LD = LN ? (KT * (kRowBytes / 16) + TPR - 1) / TPR : 1, GL = LN ? (KT * BK / 2 + 511) / 512 : 1;
   float* const ln_rows = part + NW * BM * PITCH;         // [BM] mean, [BM] 1 / standard deviation
-  f32x4 ln_in[kLnLoads];
-  if constexpr (LN) ln_load<TPR>(p, m0 + tid / TPR, tid % TPR, ln_in);      // ahead of the fragments: the fold waits for these alone
+  float* const ln_chan = ln_rows + 2 * BM;               // [ctot] gain, [ctot] offset (in registers, two k-tiles ahead, they take 64 of them)
+  V x[LD];
+  f32x4 chan[GL];
+  if constexpr (LN) {
+    ln_load<T, TPR, LD>(p, m0 + tid / TPR, tid % TPR, x);
+#pragma unroll
+    for (int i = 0; i < GL; ++i) {
+      const int at = 4 * (tid + 512 * i);
+      if (at < 2 * p.ctot) chan[i] = *(const f32x4*)(at < p.ctot ? p.ln_gain + at : p.ln_offset + (at - p.ctot));
+    }
+  }
 #pragma unroll
   for (int s = 0; s < PF; ++s)
     if (s < mine) fetch(s);
@@ -1101,7 +1113,12 @@ __global__ __launch_bounds__(512) void k_igemm_small(IgemmParams p) {
 
   float mean[TM], rstd[TM];
   if constexpr (LN) {
-    ln_fold<TPR>(p, tid % TPR, ln_in, ln_rows + tid / TPR, ln_rows + BM + tid / TPR);
+    ln_stats<T, TPR, LD>(p, tid % TPR, x, ln_rows + tid / TPR, ln_rows + BM + tid / TPR);
+#pragma unroll
+    for (int i = 0; i < GL; ++i) {
+      const int at = 4 * (tid + 512 * i);
+      if (at < 2 * p.ctot) *(f32x4*)(ln_chan + at) = chan[i];
+    }
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < TM; ++i) { mean[i] = ln_rows[16 * i + r16]; rstd[i] = ln_rows[BM + 16 * i + r16]; }
@@ -1121,8 +1138,13 @@ __global__ __launch_bounds__(512) void k_igemm_small(IgemmParams p) {
         for (int i = 0; i < TM; ++i) {
           V a = af[s][i][h];
           if constexpr (LN) {
+            const float* ch = ln_chan + ((i0 + s) * NW + wave) * BK + (h * 64 + kg * 16) / ES;
 #pragma unroll
-            for (int e = 0; e < VN; ++e) a[e] = from_f<T>((to_f(a[e]) - mean[i]) * rstd[i] * gain[s][h][e / 4][e % 4] + offset[s][h][e / 4][e % 4]);
+            for (int q = 0; q < VN; q += 4) {
+              const f32x4 gain = *(const f32x4*)(ch + q), offset = *(const f32x4*)(ch + p.ctot + q);
+#pragma unroll
+              for (int e = 0; e < 4; ++e) a[q + e] = from_f<T>(ln_value(to_f(a[q + e]), mean[i], rstd[i], gain[e], offset[e]));
+            }
           }
 #pragma unroll
           for (int j = 0; j < TN; ++j) Mma16<T>::run(bf[s][j][h], a, acc[i][j]);
@@ -1188,17 +1210,6 @@ __global__ __launch_bounds__(512) void k_igemm_small(IgemmParams p) {
     ncols = c3; c_out = col - which * c3;
   }
   const size_t o = (size_t)row * ncols + c_out;
-  if constexpr (MODE == OUT_ROWMAJOR && !LN)
-    if (p.ln_out.pairs) {                                // (whole tiles, BN / 4 lanes a row; of the values as they are stored)
-      float x[4], sq = 0.f;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) x[e] = to_f(from_f<T>(v[e]));
-      const float sum = ln_lanes<BN / 4>((x[0] + x[1]) + (x[2] + x[3]));
-#pragma unroll
-      for (int e = 0; e < 4; ++e) { const float d = x[e] - sum * (1.f / BN); sq += d * d; }
-      sq = ln_lanes<BN / 4>(sq);
-      if (cl == 0) *(f32x2*)(p.ln_out.pairs + 2 * ((size_t)row * p.ln_out.slabs + (col >> p.ln_out.shift))) = f32x2{sum, sq};
-    }
   if ((ncols & 3) == 0) {
     *(V4*)(dst + o) = V4{from_f<T>(v[0]), from_f<T>(v[1]), from_f<T>(v[2]), from_f<T>(v[3])};
   } else {
@@ -1211,14 +1222,15 @@ __global__ __launch_bounds__(512) void k_igemm_small(IgemmParams p) {
 template <typename T, int TM, int TN, int MODE, bool LN = false>
 static ad_status run_igemm_small(const IgemmParams& p0, const char* name, hipStream_t s) {
   if constexpr (!LN && (MODE == OUT_ROWMAJOR || MODE == OUT_QKV || MODE == OUT_GEGLU))
-    if (p0.ln_in) return run_igemm_small<T, TM, TN, MODE, true>(p0, name, s);
+    if (p0.ln_gain) return run_igemm_small<T, TM, TN, MODE, true>(p0, name, s);
   IgemmParams p = p0;
   set_tiles(p, 16 * TM, 16 * TN);
-  constexpr int lds_bytes = 8 * 16 * TM * (16 * TN + 4) * 4 + (LN ? 2 * 16 * TM * 4 : 0);
-  if constexpr (lds_bytes > 65536) {
+  constexpr int lds_most = 8 * 16 * TM * (16 * TN + 4) * 4 + (LN ? 2 * 16 * TM * 4 + small_ktiles(16 * TM, 16 * TN) * kRowBytes / (int)sizeof(T) * 8 : 0);
+  const int lds_bytes = 8 * 16 * TM * (16 * TN + 4) * 4 + (LN ? 2 * 16 * TM * 4 + p.ctot * 8 : 0);
+  if constexpr (lds_most > 65536) {
     static std::atomic<bool> attr_set{false};
     if (!attr_set) {
-      AD_HIP(hipFuncSetAttribute((const void*)k_igemm_small<T, TM, TN, MODE, LN>, hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes));
+      AD_HIP(hipFuncSetAttribute((const void*)k_igemm_small<T, TM, TN, MODE, LN>, hipFuncAttributeMaxDynamicSharedMemorySize, lds_most));
       attr_set = true;
     }
   }
@@ -1615,7 +1627,7 @@ static SmallTile small_tile(long long m, int n, int ktiles, int out_mode) {
   for (int i = 0; i < (out_mode == OUT_GEGLU ? 2 : 3); ++i) {
     const SmallTile t = out_mode == OUT_GEGLU ? geglu[i] : plain[i];
     const long long wgs = ((m + 16 * t.tm - 1) / (16 * t.tm)) * ((n + 16 * t.tn - 1) / (16 * t.tn));
-    if (wgs <= 256 && (long long)(t.tm + t.tn) * 16 * kRowBytes * ktiles <= 200 * 1024) return t;
+    if (wgs <= 256 && ktiles <= small_ktiles(16 * t.tm, 16 * t.tn)) return t;
   }
   return SmallTile{0, 0};
 }
@@ -1704,18 +1716,10 @@ bool conv_takes_shortcut(int dtype, long long m, int n, int c, int xc) {
   }
 }
 
-// Wherever the layer is a small-tile launch: every shape measured (above the kernel, 18 to 288 rows, 128 to 1280 channels) gains 1.5 to 3.3 us.  Not beyond
-// kLnMost channels, the pairs of sums a thread holds.
-bool conv_takes_ln(int dtype, long long m, int n, int c, int out_mode, bool any_tile) {
-  if (c % 64 || c > kLnMost || (out_mode != OUT_ROWMAJOR && out_mode != OUT_QKV && out_mode != OUT_GEGLU)) return false;
-  const int ktiles = c / bk_elems(dtype);
-  return (any_tile ? compute_plan(dtype, m, n, ktiles, out_mode, TILE_AUTO) : choose_plan(dtype, m, n, ktiles, out_mode)).tile == TILE_SMALL;
-}
-
-int conv_ln_width(int dtype, long long m, int n, int k) {
-  const int ktiles = k / bk_elems(dtype);
-  if (n % 64 || k % bk_elems(dtype) || choose_plan(dtype, m, n, ktiles, OUT_ROWMAJOR).tile != TILE_SMALL) return 0;
-  return 16 * small_tile(m, n, ktiles, OUT_ROWMAJOR).tn;
+// Wherever the layer is a small-tile launch: every shape measured (above the kernel, 18 to 288 rows, 128 to 1280 channels) gains 1.5 to 2.4 us.
+bool conv_takes_ln(int dtype, long long m, int n, int c, int out_mode) {
+  const int bk = bk_elems(dtype);
+  return c % bk == 0 && (out_mode == OUT_ROWMAJOR || out_mode == OUT_QKV || out_mode == OUT_GEGLU) && choose_plan(dtype, m, n, c / bk, out_mode).tile == TILE_SMALL;
 }
 
 ad_status launch_conv(const ConvArgs& a, hipStream_t s) {
@@ -1762,15 +1766,10 @@ ad_status launch_conv(const ConvArgs& a, hipStream_t s) {
   p.w = a.w; p.bias = a.bias; p.rowvec = a.rowvec; p.residual = a.residual;
   p.out = a.out; p.out_mode = a.out_mode; p.ld_t = a.ld_t; p.rowvec_ld = a.rowvec_ld > 0 ? a.rowvec_ld : (a.rowvec_ld < 0 ? 0 : a.n_out);
   p.out2 = a.out2; p.out3 = a.out3;
-  p.ln_in = a.ln_in; p.ln_gain = a.ln_gain; p.ln_offset = a.ln_offset; p.ln_eps = a.ln_eps;
-  p.ln_slabs = a.ln_in && a.ln_width > 0 ? p.Kp / a.ln_width : 0;
-  p.ln_out = LnOut{a.ln_out, a.ln_out && a.ln_width > 0 ? a.n_out / a.ln_width : 0, a.ln_width == 16 ? 4 : 5};
-  if (a.ln_in && ((a.ln_width != 16 && a.ln_width != 32) || a.ksize != 1 || a.stride != 1 || a.up || a.c1 || a.residual || a.rowvec || a.xw || a.ln_out ||
-                  !a.ln_gain || !a.ln_offset || (((uintptr_t)a.ln_in | (uintptr_t)a.ln_gain | (uintptr_t)a.ln_offset) & 15) ||
-                  !conv_takes_ln(a.dtype, m, a.n_out, a.c0, a.out_mode)))
+  p.ln_gain = a.ln_gain; p.ln_offset = a.ln_offset; p.ln_eps = a.ln_eps;
+  if (a.ln_gain && (!a.ln_offset || a.ksize != 1 || a.stride != 1 || a.up || a.c1 || a.residual || a.rowvec || a.xw || (((uintptr_t)a.ln_gain | (uintptr_t)a.ln_offset) & 15) ||
+                    !conv_takes_ln(a.dtype, m, a.n_out, a.c0, a.out_mode)))
     AD_FAIL(AD_ERR_INVALID, "conv: bad LayerNorm");
-  if (a.ln_out && (!a.ln_width || a.out_mode != OUT_ROWMAJOR || a.xw || ((uintptr_t)a.ln_out & 7) || a.ln_width != conv_ln_width(a.dtype, m, a.n_out, p.Kp)))
-    AD_FAIL(AD_ERR_INVALID, "conv: the sums of this output's rows are not to be had");
   if (a.out_mode < OUT_ROWMAJOR || a.out_mode > OUT_QKV) AD_FAIL(AD_ERR_INVALID, "conv: bad out_mode");
   if (a.out_mode == OUT_QKV && (a.n_out % 3 || !a.out2 || !a.out3 || a.residual || a.rowvec || (a.ld_t > 0 && a.ld_t < p.hw_out)))
     AD_FAIL(AD_ERR_INVALID, "conv: bad fused q/k/v use");
@@ -3451,9 +3450,7 @@ __global__ __launch_bounds__(256) void k_layernorm(const T* __restrict__ src, in
   const float mean = row_sum(s) / c;
 #pragma unroll
   for (int i = 0; i < K; ++i)
-    if (FULL || l + lanes * i < nv)
-#pragma unroll
-      for (int e = 0; e < VN; ++e) { const float d = to_f(x[i][e]) - mean; q += d * d; }
+    if (FULL || l + lanes * i < nv) q = ln_squares(x[i], mean, q, i == 0);
   const float rstd = rsqrtf(row_sum(q) / c + eps);
   if (row >= rows) return;
 #pragma unroll
@@ -3462,7 +3459,7 @@ __global__ __launch_bounds__(256) void k_layernorm(const T* __restrict__ src, in
     if (FULL || v < nv) {
       V t;
 #pragma unroll
-      for (int e = 0; e < VN; ++e) t[e] = from_f<T>((to_f(x[i][e]) - mean) * rstd * ga[i][e] + be[i][e]);
+      for (int e = 0; e < VN; ++e) t[e] = from_f<T>(ln_value(to_f(x[i][e]), mean, rstd, ga[i][e], be[i][e]));
       *(V*)(out + (size_t)row * c + v * VN) = t;
     }
   }

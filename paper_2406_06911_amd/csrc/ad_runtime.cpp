@@ -65,18 +65,13 @@ struct Eval {
     a.w_blocks = 1;
     return launch_conv(a, s);
   }
-  // linear layer on a [rows][cin] matrix; next: of the layer behind the LayerNorm that follows, which may want the sums of the rows (width: see ln_linear())
-  struct Next { int n, mode; int* width; };
+  // linear layer on a [rows][cin] matrix
   ad_status linear(const void* src, int rows, int cin, int w_idx, int b_idx, const void* residual, void* dst,
-                   int mode = OUT_ROWMAJOR, int batch = 1, int ld_t = 0, Next next = {0, 0, nullptr}) const {
+                   int mode = OUT_ROWMAJOR, int batch = 1, int ld_t = 0) const {
     WView wv{c};
     ConvArgs a{dt, src, nullptr, cin, 0, batch, rows / batch, 1, 0, 1, 1, wv.at(w_idx), c.weights[w_idx].info.shape[0],
                b_idx >= 0 ? wv.f32(b_idx) : nullptr, nullptr, 0, residual, dst, mode, ld_t, temp(9), ws.temp_bytes[9]};
     a.w_blocks = 1;
-    if (next.width) {
-      *next.width = conv_takes_ln(dt, rows, next.n, a.n_out, next.mode) ? conv_ln_width(dt, rows, a.n_out, cin) : 0;
-      if (*next.width) { a.ln_out = (float*)temp(10); a.ln_width = *next.width; }
-    }
     return launch_conv(a, s);
   }
   ad_status gn(const void* src0, const void* src1, int c0, int c1, int hw, int g_idx, int silu, void* dst) const {
@@ -88,14 +83,13 @@ struct Eval {
     WView wv{c};
     return launch_layernorm(dt, src, rows, ch, wv.f32(g_idx), wv.f32(g_idx + 1), c.cfg.ln_eps, dst, s);
   }
-  // a linear layer behind a LayerNorm of h (gain and offset at g_idx): in one launch where the launch that wrote h has left the sums of its rows, since the
-  // layer takes them (width: columns a pair of them covers), else a launch each
-  ad_status ln_linear(const void* h, int rows, int ch, int g_idx, int width, ConvArgs a) const {
+  // a linear layer behind a LayerNorm of h (gain and offset at g_idx), in one launch where it takes the norm in
+  ad_status ln_linear(const void* h, int rows, int ch, int g_idx, ConvArgs a) const {
     WView wv{c};
     a.w_blocks = 1;
     a.src0 = h;
-    if (width) {
-      a.ln_in = (const float*)temp(10); a.ln_width = width; a.ln_gain = wv.f32(g_idx); a.ln_offset = wv.f32(g_idx + 1); a.ln_eps = c.cfg.ln_eps;
+    if (conv_takes_ln(dt, rows, a.n_out, ch, a.out_mode)) {
+      a.ln_gain = wv.f32(g_idx); a.ln_offset = wv.f32(g_idx + 1); a.ln_eps = c.cfg.ln_eps;
     } else {
       AD_TRY(ln(h, rows, ch, g_idx, temp(0)));
       a.src0 = temp(0);
@@ -199,19 +193,17 @@ struct Eval {
     AD_TRY(gn(x, nullptr, Cc, 0, L, w + 0, 0, temp(0)));
     if (tfm_rows_fits(dt, Cc, d, Lk, (long long)B * L)) return tfm_by_rows(f, w, x, tensor_out(ui), ui);
     WView wv{c};
-    int width = 0;                                     // of the sums that the launch in front of a LayerNorm has left
-    const Next qkv{3 * Cc, OUT_QKV, &width}, query{Cc, OUT_ROWMAJOR, &width}, inner{8 * Cc, OUT_GEGLU, &width};
-    AD_TRY(linear(temp(0), M, Cc, w + 2, w + 3, nullptr, temp(1), OUT_ROWMAJOR, 1, 0, qkv));
+    AD_TRY(linear(temp(0), M, Cc, w + 2, w + 3, nullptr, temp(1)));
     w += 4;
     void* h = temp(1);
     for (int k = 0; k < f.depth; ++k, w += 20) {
       // ln1.g ln1.b a1.q a1.k a1.v a1.o.w a1.o.b ln2.g ln2.b a2.q a2.k a2.v a2.o.w a2.o.b ln3.g ln3.b ff1.w ff1.b ff2.w ff2.b
       // q, k, v of the self-attention in one GEMM; v lands transposed when the MFMA attention kernel follows
-      AD_TRY(ln_linear(h, M, Cc, w + 0, width, ConvArgs{dt, nullptr, nullptr, Cc, 0, B, L, 1, 0, 1, 1, wv.at(w + 2), 3 * Cc, nullptr, nullptr, 0, nullptr, temp(2), OUT_QKV,
+      AD_TRY(ln_linear(h, M, Cc, w + 0, ConvArgs{dt, nullptr, nullptr, Cc, 0, B, L, 1, 0, 1, 1, wv.at(w + 2), 3 * Cc, nullptr, nullptr, 0, nullptr, temp(2), OUT_QKV,
                                                         vt ? lp : 0, temp(9), ws.temp_bytes[9], temp(3), temp(4)}));
       AD_TRY(launch_attention(dt, temp(2), temp(3), temp(4), vt, B, L, L, Cc, d, Cc, Cc, vt ? lp : Cc, Cc, temp(5), s));
-      AD_TRY(linear(temp(5), M, Cc, w + 5, w + 6, h, h, OUT_ROWMAJOR, 1, 0, query));
-      AD_TRY(ln_linear(h, M, Cc, w + 7, width, ConvArgs{dt, nullptr, nullptr, Cc, 0, 1, M, 1, 0, 1, 1, wv.at(w + 9), Cc, nullptr, nullptr, 0, nullptr, temp(2), OUT_ROWMAJOR,
+      AD_TRY(linear(temp(5), M, Cc, w + 5, w + 6, h, h));
+      AD_TRY(ln_linear(h, M, Cc, w + 7, ConvArgs{dt, nullptr, nullptr, Cc, 0, 1, M, 1, 0, 1, 1, wv.at(w + 9), Cc, nullptr, nullptr, 0, nullptr, temp(2), OUT_ROWMAJOR,
                                                         0, temp(9), ws.temp_bytes[9]}));
       // keys / values of the text: taken from the per-run cache when it was built from this embedding
       const void* tk = temp(7);
@@ -225,17 +217,17 @@ struct Eval {
       // video: every frame attends to the one text embedding, so the frames' tokens form one long query sequence
       if (c.cfg.frames > 0) AD_TRY(launch_attention(dt, temp(2), tk, tv, vt, 1, M, Lk, Cc, d, Cc, Cc, vt ? lkp : Cc, Cc, temp(5), s));
       else AD_TRY(launch_attention(dt, temp(2), tk, tv, vt, B, L, Lk, Cc, d, Cc, Cc, vt ? lkp : Cc, Cc, temp(5), s));
-      AD_TRY(linear(temp(5), M, Cc, w + 12, w + 13, h, h, OUT_ROWMAJOR, 1, 0, inner));
-      AD_TRY(ln_linear(h, M, Cc, w + 14, width, ConvArgs{dt, nullptr, nullptr, Cc, 0, 1, M, 1, 0, 1, 1, wv.at(w + 16), 8 * Cc, wv.f32(w + 17), nullptr, 0, nullptr, temp(6),
+      AD_TRY(linear(temp(5), M, Cc, w + 12, w + 13, h, h));
+      AD_TRY(ln_linear(h, M, Cc, w + 14, ConvArgs{dt, nullptr, nullptr, Cc, 0, 1, M, 1, 0, 1, 1, wv.at(w + 16), 8 * Cc, wv.f32(w + 17), nullptr, 0, nullptr, temp(6),
                                                          OUT_GEGLU, 0, temp(9), ws.temp_bytes[9]}));
-      AD_TRY(linear(temp(6), M, 4 * Cc, w + 18, w + 19, h, h, OUT_ROWMAJOR, 1, 0, k + 1 < f.depth ? qkv : Next{0, 0, nullptr}));
+      AD_TRY(linear(temp(6), M, 4 * Cc, w + 18, w + 19, h, h));
     }
     void* z = tensor_out(ui);
-    AD_TRY(linear(h, M, Cc, w + 0, w + 1, x, z, OUT_ROWMAJOR, 1, 0, c.cfg.temporal_heads ? qkv : Next{0, 0, nullptr}));
+    AD_TRY(linear(h, M, Cc, w + 0, w + 1, x, z));
     if (c.cfg.temporal_heads == 0) return AD_OK;
     // temporal layer: temp.ln.g temp.ln.b temp.q temp.k temp.v temp.o.w temp.o.b; tokens = the frames of one position
     w += 2;
-    AD_TRY(ln_linear(z, M, Cc, w + 0, width, ConvArgs{dt, nullptr, nullptr, Cc, 0, B, L, 1, 0, 1, 1, wv.at(w + 2), 3 * Cc, nullptr, nullptr, 0, nullptr, temp(2), OUT_QKV,
+    AD_TRY(ln_linear(z, M, Cc, w + 0, ConvArgs{dt, nullptr, nullptr, Cc, 0, B, L, 1, 0, 1, 1, wv.at(w + 2), 3 * Cc, nullptr, nullptr, 0, nullptr, temp(2), OUT_QKV,
                                                       0, temp(9), ws.temp_bytes[9], temp(3), temp(4)}));
     AD_TRY(launch_attention_frames(dt, temp(2), temp(3), temp(4), c.cfg.frames, L, Cc, c.cfg.temporal_heads, Cc, Cc, Cc, Cc, temp(5), s));
     return linear(temp(5), M, Cc, w + 5, w + 6, z, z);

@@ -1,12 +1,12 @@
-"""Transformer blocks whose LayerNorms go into the linear layers behind them (rows normalised on the way into the matrix cores, sums of the rows from the
-launch in front), against the oracle: small launches of either type, ragged rows, the larger tiles, which get the norm as a launch of its own."""
+"""Transformer blocks whose LayerNorms go into the linear layers behind them (rows normalised on the way into the matrix cores), against the oracle and, to the
+bit, against a launch for every norm: small launches of either type, ragged rows, the larger tiles, which get the norm as a launch of its own."""
 import numpy as np
 import pytest
 import torch
 
 import synthetic_inputs as SI
 from configs import CONFIGS
-from gpu_util import dev, host, nchw_to_nhwc, nhwc_to_nchw, rel_l2
+from gpu_util import DEV, dev, dev_bytes, dev_f32, host, nchw_to_nhwc, nhwc_to_nchw, p, quantize, rel_l2, stream_ptr, tdtype
 from oracle.unet import UNetConfig, weight_manifest
 from paper_2406_06911_amd import binding as B
 from test_gpu_pipeline import Case
@@ -42,6 +42,62 @@ def block(monkeypatch, d, dtype, tile, wts, spoil=None):
         return nhwc_to_nchw(host(out[case.m.component_io(2)[1].index(2)]) - host(x)), after - before, names
     finally:
         B.check(B.lib.ad_tune_conv_tile(-1))
+
+
+def by_launches(d, dtype, wts, x):
+    """The same block (no frames) from the single-kernel entry points, a launch for every norm; x on the GPU, [batch][h][w][c]."""
+    n, h, w, c = x.shape
+    m, l, lk, lp, lkp = n * h * w, h * w, d["ctx_len"], (h * w + 63) // 64 * 64, (d["ctx_len"] + 63) // 64 * 64
+    vt = dtype == BF                          # transposed values: the MFMA attention kernels
+    empty = lambda *shape: torch.zeros(shape, device=DEV, dtype=tdtype(dtype))
+
+    def linear(src, rows, cin, names, bias=None, residual=None, mode=B.OUT_ROWMAJOR, batch=1, ld_t=0):
+        wt = np.concatenate([wts[t] for t in names])
+        n_out = wt.shape[0]
+        wp = dev_bytes(B.pack_conv_weight(dtype, wt.reshape(n_out, cin, 1, 1), mode == B.OUT_GEGLU))
+        b = None
+        if bias:
+            b = np.zeros((n_out + 127) // 128 * 128, np.float32)
+            r = np.arange(n_out)
+            b[:n_out] = wts[bias][np.where(r % 64 < 32, r // 64 * 32 + r % 64, n_out // 2 + r // 64 * 32 + r % 64 - 32) if mode == B.OUT_GEGLU else r]
+            b = dev_f32(b)
+        third = empty(batch, n_out // 3, ld_t) if ld_t and mode == B.OUT_QKV else empty(rows, c)
+        out = [empty(batch, n_out, ld_t) if mode == B.OUT_TRANSPOSED else empty(rows, {B.OUT_QKV: c, B.OUT_GEGLU: n_out // 2}.get(mode, n_out)), empty(rows, c), third]
+        ws = B.lib.ad_conv_workspace_bytes(dtype, batch, rows // batch, 1, n_out, cin, 1, mode)
+        scratch = torch.zeros(max(ws, 16), dtype=torch.uint8, device=DEV)
+        B.check(B.lib.ad_conv_forward(dtype, p(src), None, cin, 0, batch, rows // batch, 1, 0, 1, 1, p(wp), n_out, p(b), None, p(residual), p(out[0]), p(out[1]), p(out[2]),
+                                      mode, ld_t, p(scratch) if ws else None, ws, stream_ptr()))
+        torch.cuda.synchronize()
+        return out if mode == B.OUT_QKV else out[0]
+
+    def norm(src, name):
+        out, g, b = empty(m, c), dev_f32(wts[name + ".g"]), dev_f32(wts[name + ".b"])
+        B.check(B.lib.ad_layernorm_forward(dtype, p(src), m, c, p(g), p(b), 1e-5, p(out), stream_ptr()))
+        torch.cuda.synchronize()
+        return out
+
+    def attention(q, k, v, keys, ld_v):
+        out = empty(m, c)
+        B.check(B.lib.ad_attention_forward(dtype, p(q), p(k), p(v), int(vt), n, l, keys, c, d["head_dim"], c, c, ld_v if vt else c, c, p(out), stream_ptr()))
+        torch.cuda.synchronize()
+        return out
+
+    t, text = "d0.0.tfm.", dev(quantize(SI.make_text(n, lk, d["ctx_dim"]), dtype), dtype)
+    y, g, b = empty(m, c), dev_f32(wts[t + "gn.g"]), dev_f32(wts[t + "gn.b"])
+    scratch = torch.zeros(B.lib.ad_groupnorm_scratch_bytes(n, l, c) // 4 + 4, device=DEV)
+    B.check(B.lib.ad_groupnorm_forward(dtype, p(x), None, c, 0, n, l, d["gn_groups"], p(g), p(b), 1e-5, 0, p(y), p(scratch), stream_ptr()))
+    rows = linear(y, m, c, [t + "proj_in.w"], t + "proj_in.b")
+    for k in range(d["transformer_depth"][0]):
+        s = "%s%d." % (t, k)
+        q, key, v = linear(norm(rows, s + "ln1"), m, c, [s + "attn1.%s.w" % i for i in "qkv"], mode=B.OUT_QKV, batch=n, ld_t=lp if vt else 0)
+        rows = linear(attention(q, key, v, l, lp), m, c, [s + "attn1.o.w"], s + "attn1.o.b", rows)
+        q = linear(norm(rows, s + "ln2"), m, c, [s + "attn2.q.w"])
+        key = linear(text, n * lk, d["ctx_dim"], [s + "attn2.k.w"])
+        v = linear(text, n * lk, d["ctx_dim"], [s + "attn2.v.w"], mode=B.OUT_TRANSPOSED if vt else B.OUT_ROWMAJOR, batch=n, ld_t=lkp if vt else 0)
+        rows = linear(attention(q, key, v, lk, lkp), m, c, [s + "attn2.o.w"], s + "attn2.o.b", rows)
+        inner = linear(norm(rows, s + "ln3"), m, c, [s + "ff1.w"], s + "ff1.b", mode=B.OUT_GEGLU)
+        rows = linear(inner, m, 4 * c, [s + "ff2.w"], s + "ff2.b", rows)
+    return linear(rows, m, c, [t + "proj_out.w"], t + "proj_out.b", x)
 
 
 def one_norm(d, row, spread, site, scale, rng):
@@ -85,19 +141,36 @@ def test_layernorm_inside_the_linear_layer_matches_oracle(monkeypatch, dtype, ti
     assert (names.count("layernorm") > 0) == separate, names
 
 
+# edges of the sums of a row: fewer accesses of 16 bytes than lanes (24, 32), 64 and more, no multiple of 64 (72, 80, 160), row tiles of 16 and 32, rows beyond the tensor
+@pytest.mark.parametrize("dtype,c,depth,height,width,batch", [(BF, *q) for q in [
+    (192, 2, 4, 4, 1), (256, 2, 5, 3, 2), (192, 1, 12, 12, 2), (320, 1, 9, 5, 1), (576, 1, 5, 4, 2), (640, 1, 9, 5, 1), (1280, 1, 3, 3, 1), (1280, 1, 10, 9, 2)]] + [
+    (F32, *q) for q in [(128, 1, 12, 12, 2), (192, 1, 12, 12, 2), (256, 2, 6, 6, 2), (320, 1, 3, 3, 1), (640, 1, 3, 3, 1)]])
+def test_same_bits_as_a_launch_for_every_norm(monkeypatch, dtype, c, depth, height, width, batch):
+    d = config(c, depth, height, width, batch)
+    wts = SI.make_weights(weight_manifest(UNetConfig(**d)), std=c ** -0.5, bf16_exact=dtype == BF)
+    rng = np.random.default_rng(17)
+    for name in wts:
+        if ".ln" in name:
+            wts[name] = (rng.standard_normal(wts[name].shape) * 0.3 + name.endswith(".g")).astype(np.float32)
+    kept = []
+    got, _, names = block(monkeypatch, d, dtype, AUTO, wts, spoil=kept.append)
+    x = kept[0]
+    want = nhwc_to_nchw(host(by_launches(d, dtype, wts, x).reshape(x.shape)) - host(x))
+    assert "layernorm" not in names or (dtype, c, batch) == (BF, 1280, 2), names       # there two of the three layers have too much of K for a small tile
+    assert np.isfinite(got).all() and np.array_equal(got, want), rel_l2(got, want)
+
+
 @pytest.mark.parametrize("site", [1, 3])
 @pytest.mark.parametrize("c,offset,spread", [(128, 10, 1), (256, 10, 1), (128, 100, 1), (256, 100, 1), (320, 100, 1), (256, 1000, 1), (256, 77.1, 0)])
 def test_fp32_rows_with_an_offset(monkeypatch, c, offset, spread, site):
-    """Rows whose mean is 10 to 1000 standard deviations, and rows of one value, which the norm turns into its own offset: the norm inside the linear layer
-    loses no more of them than as a launch of its own (which the register-staged kernels have in front of them)."""
-    d = config(c, 1, 5, 4, 2)
+    """Rows whose mean is 10 to 1000 standard deviations, and rows of one value, which the norm turns into its own offset: nothing is lost of them that a launch
+    for every norm keeps."""
+    d, kept = config(c, 1, 5, 4, 2), []
     wts = one_norm(d, offset, spread, site, 2.0 ** 14, np.random.default_rng(7))
-    got, want, names = block(monkeypatch, d, F32, AUTO, wts)
-    apart, _, names_apart = block(monkeypatch, d, F32, REGISTERS, wts)
-    assert "layernorm" not in names and names_apart.count("layernorm") == 3, (names, names_apart)
-    # half as much again for the luck of other roundings of the mean; 3e-7: the sums behind the norm
-    err, err_apart = rel_l2(got, want), rel_l2(apart, want)
-    assert err < 1.5 * err_apart + 3e-7, (err, err_apart)
+    got, _, names = block(monkeypatch, d, F32, AUTO, wts, spoil=kept.append)
+    x = kept[0]
+    want = nhwc_to_nchw(host(by_launches(d, F32, wts, x).reshape(x.shape)) - host(x))
+    assert "layernorm" not in names and np.abs(want).max() > 1 and np.array_equal(got, want), (names, rel_l2(got, want))
 
 
 @pytest.mark.parametrize("dtype,c", [(F32, 128), (F32, 256), (BF, 192), (BF, 256)])
