@@ -24,15 +24,15 @@ PEAK_HBM_GBS = 8000.0
 # `rocprofv3 --pmc` runs of this file (FETCH_SIZE, WRITE_SIZE; KiB per dispatch scaled by the factors 2.00 and 1.00 that the
 # same counters show for the 2^26-element sampler launch).  Commands and tables: profiles/bench_sd21_768_all_kernels.md.
 MEASURED_TRAFFIC = {"sd21_768": {
-    "igemm_bf16_256x128_p3": 62801715, "igemm_bf16_256x128_p3_splitk": 168029184, "igemm_bf16_128x128_p3": 41868493,
-    "igemm_bf16_128x128_p3_splitk": 60928307, "splitk_reduce": 19778150, "igemm_bf16_64x64_p3": 26217984,
-    "attn_mfma2_bf16": 33331405, "layernorm": 13100646, "gn_apply": 29586942, "gn_partial": 14604562,
-    "igemm_bf16_128x128_d2": 91216896, "gn_group": 6776218, "attn_mfma_bf16": 14640230, "igemm_bf16_128x160_d2": 39861862,
-    "igemm_bf16_64x64_splitk": 97678336, "igemm_bf16_256x320_d2": 57138176, "linear_rows": 5852911,
-    "igemm_bf16_64x64_k2": 11823718, "igemm_bf16_64x64_p3_splitk": 28575744, "igemm_bf16_small": 4584755}}
+    "igemm_bf16_256x128_p3": 62801587, "igemm_bf16_256x128_p3_splitk": 167921276, "igemm_bf16_128x128_p3": 41868338,
+    "igemm_bf16_128x128_p3_splitk": 60928377, "splitk_reduce": 19770033, "igemm_bf16_64x64_p3": 26215031,
+    "attn_mfma2_bf16": 33322500, "layernorm": 13099394, "gn_apply": 29595366, "gn_partial": 14604695,
+    "igemm_bf16_128x128_d2": 91206620, "gn_group": 6778736, "attn_mfma_bf16": 14639964, "igemm_bf16_128x160_d2": 39899220,
+    "igemm_bf16_64x64_splitk": 98368989, "igemm_bf16_256x320_d2": 57148519, "linear_rows": 5857998,
+    "igemm_bf16_64x64_k2": 11821670, "igemm_bf16_64x64_p3_splitk": 28567552, "igemm_bf16_small": 4581296}}
 
 
-TRAFFIC_SOURCE = "not measured in this run: FETCH_SIZE + WRITE_SIZE of two rocprofv3 --pmc runs of this file, profiles/bench_sd21_768_all_kernels.md (kernels of commit a38dddd)"
+TRAFFIC_SOURCE = "not measured in this run: FETCH_SIZE + WRITE_SIZE of two rocprofv3 --pmc runs of this file, profiles/bench_sd21_768_all_kernels.md (kernels of commit 695b0a0)"
 
 
 def log(*a):
