@@ -173,6 +173,21 @@ def test_fp32_rows_with_an_offset(monkeypatch, c, offset, spread, site):
     assert "layernorm" not in names and np.abs(want).max() > 1 and np.array_equal(got, want), (names, rel_l2(got, want))
 
 
+@pytest.mark.parametrize("dtype", [F32, BF])
+@pytest.mark.parametrize("value,finite", [(1e30, True), (float("inf"), False)])
+def test_rows_with_a_huge_value(monkeypatch, dtype, value, finite):
+    """1e30 in a channel: its square is beyond the type, the norm leaves its offset.  Infinity: no number in any row.  Both as with a launch for every norm."""
+    d, kept = config(192, 1, 5, 4, 2), []
+    row = np.zeros(192)
+    row[100] = value
+    wts = one_norm(d, row, 1, 1, 1, np.random.default_rng(19))
+    with np.errstate(all="ignore"):
+        got, _, names = block(monkeypatch, d, dtype, AUTO, wts, spoil=kept.append)
+    x = kept[0]
+    want = nhwc_to_nchw(host(by_launches(d, dtype, wts, x).reshape(x.shape)) - host(x))
+    assert "layernorm" not in names and np.isfinite(got).all() == finite and np.array_equal(got, want, equal_nan=True)
+
+
 @pytest.mark.parametrize("dtype,c", [(F32, 128), (F32, 256), (BF, 192), (BF, 256)])
 def test_a_sample_of_nan_stays_by_itself(monkeypatch, dtype, c):
     """Samples of 15 rows share row tiles: one that is not a number comes out as such, and the other to the same bits as without it."""
