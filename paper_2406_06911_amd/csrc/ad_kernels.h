@@ -51,6 +51,8 @@ struct ConvArgs {
   // a LayerNorm over the channels in front of a linear layer, only where conv_takes_ln() says so: gain and offset of the channels, epsilon
   const float* ln_gain = nullptr; const float* ln_offset = nullptr;
   float ln_eps = 0.f;
+  const void* ahead = nullptr;          // weights of a later launch, fetched from memory beside the product (a hint; the LDS-DMA kernels take it)
+  size_t ahead_bytes = 0;
   int w_blocks = 0;                     // w and xw are in blocks (pack_blocks()) instead of rows
 };
 // OUT_QKV: n_out = 3c; thirds go to out [m][c], out2 [m][c] and out3 ([batch][c][ld_t] when ld_t > 0, else [m][c])

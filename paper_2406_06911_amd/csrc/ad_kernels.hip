@@ -67,6 +67,7 @@ struct IgemmParams {
   int xc0, xc1, kt_main;                                // its channels; k-tiles of the taps
   unsigned xbytes0, xbytes1, xbytes_w;
   const float* ln_gain; const float* ln_offset; float ln_eps;      // LN (k_igemm_small)
+  const void* ahead; unsigned ahead_bytes, ahead_span;             // k_igemm_p3: weights of a later launch (0 bytes: none), and a wavefront's share of them
 };
 
 // Byte offset of a row of a packed operand within a k-tile (k-tile kt is kt * p.w_kt further).  Two layouts: rows of k_bytes one after the other
@@ -571,6 +572,10 @@ __device__ __forceinline__ void dma_load16(u32x4 rsrc, unsigned voffset, unsigne
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
                :: "s"(lds_addr), "v"(voffset), "s"(rsrc), "s"(soffset) : "memory");
 }
+// A load whose data nobody wants: 64 pieces of 128 bytes are on their way from memory to the caches, 4 bytes of each to LDS
+__device__ __forceinline__ void dma_touch(u32x4 rsrc, unsigned voffset, unsigned lds_addr) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, 0 offen lds" :: "s"(lds_addr), "v"(voffset), "s"(rsrc) : "memory");
+}
 __device__ __forceinline__ u32x4 make_rsrc_words(const void* base, unsigned bytes) {
   const unsigned long long a = (unsigned long long)base;
   return u32x4{(unsigned)a, (unsigned)(a >> 32) & 0xffffu, bytes, 0x00020000u};
@@ -607,6 +612,7 @@ __device__ __forceinline__ int lds_swizzle(int row) { return (row >> 1) & 7; }
 // (256x320), 3x3 16384x640x5760 139 -> 116 (128x160), 3x3 65536x320x2880 130 -> 121 (256x320), q/k/v 65536x960x320 79 -> 64 (256x320),
 // GEGLU 8192x5120x640 78 -> 66 (256x320), 2048x1280x1280 16.2 -> 13.7 (128x128 for 64x64).
 // =================================================================================================
+constexpr int kTouches = 2, kTouchLds = 256;      // weights ahead: loads of a wavefront, where they land
 // Wavefronts per SIMD that LDS allows: what the register budget is set for.
 constexpr int p3_waves_per_simd(int bm, int bn, int waves, int stages) { return (int)(kLdsLimit / (stages * (bm + bn) * kRowBytes)) * waves / 4; }
 template <typename T, int BM, int BN, int MODE, int WM = 2, int WN = 2, int NSTAGE = 3, int KG = 1, bool XTRA = false>
@@ -774,13 +780,27 @@ __global__ __launch_bounds__(64 * WM * WN * KG, p3_waves_per_simd(BM, BN, WM * W
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
 #pragma unroll
-  for (int t = 0; t < NSTAGE - 1; ++t)
+  for (int t = 0; t < NSTAGE - 1; ++t) {
     if (t < nkt) {
       begin_tile();
 #pragma unroll
       for (int i = 0; i < AG; ++i) issue_one(t, i);      // the B part of these tiles is already on its way
       end_tile();
     }
+    if (t == 0 && p.ahead_bytes) {
+      // Weights of a later launch, from memory into the memory-side cache (when that pays: kAheadRows): behind tile 0, ahead of tile 1, whose wait is the
+      // first that includes them.  All wavefronts take the same share: 3.3 MB by the first 25 of 240 workgroups made 2048x3840x1280 1.7 us slower, by all of
+      // them 0.5.  Workgroups of their own instead, in the launches of norms and attention in between, cost those 0.5 to 3 us each, and on other CUs they
+      // took from the other streams what they gave: 1024px 0.2 to 0.7 % slower than without.
+      const u32x4 rsn = make_rsrc_words(p.ahead, p.ahead_bytes);
+      const unsigned first = ((blockIdx.y * gridDim.x + blockIdx.x) * (NW * KG) + wave_all) * p.ahead_span;
+#pragma unroll
+      for (int i = 0; i < kTouches; ++i) {
+        const unsigned at = lane * 128 + i * 8192;
+        dma_touch(rsn, at < p.ahead_span ? first + at : kOob, (unsigned)(size_t)(__attribute__((address_space(3))) char*)lds_all + KG * NSTAGE * STAGE);
+      }
+    }
+  }
   // fragment reads: row * 128 + ((chunk ^ lds_swizzle(row)) * 16), chunk = 2 ks + half
   const int a_row = (wave_m * WTM + l32) * kRowBytes, b_row = (BM + wave_n * WTN + l32) * kRowBytes;
   const int x7 = lds_swizzle(l32);
@@ -837,8 +857,10 @@ __global__ __launch_bounds__(64 * WM * WN * KG, p3_waves_per_simd(BM, BN, WM * W
     if (PHASE == 2) end_tile();
     stage = next;
   };
-  // issue order so far: B(0), B(1), A(0), A(1): tile 0 is complete once only A(1) is outstanding
-  if (nkt >= NSTAGE - 1) wait_vmcnt<(NSTAGE - 2) * AG>(); else wait_vmcnt<0>();
+  // issue order so far: B(0), B(1), A(0), weights ahead, A(1): tile 0 is complete once only those and A(1) are outstanding
+  if (nkt < NSTAGE - 1) wait_vmcnt<0>();
+  else if (p.ahead_bytes) wait_vmcnt<(NSTAGE - 2) * AG + kTouches>();
+  else wait_vmcnt<(NSTAGE - 2) * AG>();
   __syncthreads();
   int kt = 0;
   if (idle) {
@@ -897,7 +919,7 @@ static ad_status run_igemm_p3(const IgemmParams& p0, const char* name, hipStream
   if (!XTRA && p0.xw) AD_FAIL(AD_ERR_INVALID, "conv: this tile does not take a shortcut");
   IgemmParams p = p0;
   set_tiles(p, BM, BN);
-  constexpr int lds_bytes = KG * NSTAGE * (BM + BN) * kRowBytes;
+  constexpr int lds_bytes = KG * NSTAGE * (BM + BN) * kRowBytes + kTouchLds;
   static_assert(lds_bytes / KG >= WM * WN * stage_bytes<T, BM / WM, BN / WN>(16) && lds_bytes <= (int)kLdsLimit, "epilogue staging fits");
   static_assert(MODE != OUT_GEGLU || BN / WN / 32 % 2 == 0 || lds_bytes >= WM * WN * stage_bytes<T, BM / WM, BN / WN>(32) + BM * 128, "so does the exchange");
   static std::atomic<bool> attr_set{false};
@@ -910,6 +932,8 @@ static ad_status run_igemm_p3(const IgemmParams& p0, const char* name, hipStream
   const double out_cols = p.out_mode == OUT_GEGLU ? p.N / 2 : p.N;
   ProfLaunch pl(name, 2.0 * p.M * p.N * (p.k_prof + xk), in_bytes + (double)p.N * (p.Kp + xk) * sizeof(T) + (double)p.M * out_cols * sizeof(T), s, p.M, p.N, p.Kp + xk);
   const int splits = (p.ktiles + p.kt_per_split - 1) / p.kt_per_split;
+  const unsigned waves = (unsigned)(p.tiles_n * p.tiles_m * splits * WM * WN * KG);
+  p.ahead_span = (p.ahead_bytes / 128 + waves - 1) / waves * 128;
   hipLaunchKernelGGL((k_igemm_p3<T, BM, BN, MODE, WM, WN, NSTAGE, KG, XTRA>), dim3(p.tiles_n * p.tiles_m, splits), dim3(64 * WM * WN * KG), lds_bytes, s, p);
   AD_HIP(hipGetLastError());
   return AD_OK;
@@ -1766,6 +1790,7 @@ ad_status launch_conv(const ConvArgs& a, hipStream_t s) {
   p.w = a.w; p.bias = a.bias; p.rowvec = a.rowvec; p.residual = a.residual;
   p.out = a.out; p.out_mode = a.out_mode; p.ld_t = a.ld_t; p.rowvec_ld = a.rowvec_ld > 0 ? a.rowvec_ld : (a.rowvec_ld < 0 ? 0 : a.n_out);
   p.out2 = a.out2; p.out3 = a.out3;
+  p.ahead = a.ahead; p.ahead_bytes = a.ahead ? (unsigned)std::min<size_t>(a.ahead_bytes, 0x7fffffff) : 0;
   p.ln_gain = a.ln_gain; p.ln_offset = a.ln_offset; p.ln_eps = a.ln_eps;
   if (a.ln_gain && (!a.ln_offset || a.ksize != 1 || a.stride != 1 || a.up || a.c1 || a.residual || a.rowvec || a.xw || (((uintptr_t)a.ln_gain | (uintptr_t)a.ln_offset) & 15) ||
                     !conv_takes_ln(a.dtype, m, a.n_out, a.c0, a.out_mode)))

@@ -25,6 +25,17 @@ struct WView {
   const float* f32(int idx) const { return (const float*)at(idx); }
 };
 
+// Weights ahead (ConvArgs::ahead).  A GEMM whose weights come from memory waits for them k-tile by k-tile: a CU holds some 64 KiB of requests, and memory answers
+// them in twice the time of the memory-side cache.  So a launch asks for the weights of the one behind it.  What that gives is a share of the k-tiles of the
+// launch behind it, what it costs is one round trip to memory in the launch that asks (0.3 to 0.5 us).  us without / with, inside the models on one stream: 2048x1280x5120
+// 46.5 / 38.1, 2048x1280x1280 15.2 / 13.1, 512x1280x1280 8.9 / 8.1, 720x640x2560 13.1 / 11.1, 2880x320x5760 26.2 / 21.6, 3x3 8192x320x8640 70.3 / 60.4; K = 320 and 640 level, so
+// with those too the 576x320 px run was 0.4 % slower than without any.  Not below 512 rows, where weights are most of what a launch takes in and asking for them
+// early moves the wait (180x1280x1280 8.4 / 8.1), nor beyond 16 MB, which the launch in front cannot take in on the side (GEGLU of 1280 channels, 3x3 of 1280: with them 768px
+// 0.7 % slower, 512px 0.9, 1024px 0.5 than without them), nor in models that the cache holds from one step to the next.
+// Whole runs, ms: 512px 192.4 -> 189.7, 576x320 px 64.9 -> 64.3, 768px component by component 32.2 -> 31.8, 1024px 527.8 -> 522.4, 768px and video level.
+constexpr size_t kAheadModel = 128 << 20, kAheadMost = 16000000;
+constexpr int kAheadRows = 512, kAheadK = 1280;
+
 struct Eval {
   Ctx& c;
   const Component& cp;
@@ -37,6 +48,19 @@ struct Eval {
   const float* proj = nullptr;   // fused time projection of the component's ResBlocks [batch][proj_ld]
   int proj_ld = 0;
 
+  // The launches of a unit in order; a weight of a unit: its index, or kFirst for the unit's first
+  static constexpr int kFirst = -1;
+  struct Next { int unit, weight; };
+  static constexpr Next kNone{INT32_MAX, 0};
+  // the launch behind the one of `a` is the one of `n` (an attention or a norm may lie between): its weights are asked for where that pays
+  void ask_ahead(ConvArgs& a, Next n) const {
+    if (n.unit > cp.last || c.weight_bytes < kAheadModel) return;
+    const ad_unit_info& f = c.units[n.unit].info;
+    if (n.weight == kFirst) n.weight = c.units[n.unit].w_first + (f.kind == AD_UNIT_DOWN || f.kind == AD_UNIT_UP ? 0 : 2);
+    const Weight& w = c.weights[n.weight];
+    if ((long long)c.cfg.batch * f.h_out * f.w_out < kAheadRows || w.k_pad < kAheadK || w.dev_bytes > kAheadMost || w.fragments) return;
+    a.ahead = c.weights_dev + w.dev_off; a.ahead_bytes = w.dev_bytes;
+  }
   char* work(size_t off) const { return c.work_dev + off; }
   void* temp(int t) const { return ws.temp_bytes[t] ? work(ws.temp_off[t]) : nullptr; }
   float* f32area() const { return (float*)work(ws.f32_off); }
@@ -58,20 +82,22 @@ struct Eval {
 
   ad_status conv(const void* src0, const void* src1, int c0, int c1, int hs, int wsz, int up, int ksize, int stride,
                  int w_idx, int b_idx, const float* rowvec, const void* residual, void* dst, int mode = OUT_ROWMAJOR,
-                 int ld_t = 0) const {
+                 int ld_t = 0, Next behind = kNone) const {
     WView wv{c};
     ConvArgs a{dt, src0, src1, c0, c1, c.cfg.batch, hs, wsz, up, ksize, stride, wv.at(w_idx), c.weights[w_idx].info.shape[0],
                b_idx >= 0 ? wv.f32(b_idx) : nullptr, rowvec, proj_ld, residual, dst, mode, ld_t, temp(9), ws.temp_bytes[9]};
     a.w_blocks = 1;
+    ask_ahead(a, behind);
     return launch_conv(a, s);
   }
   // linear layer on a [rows][cin] matrix
   ad_status linear(const void* src, int rows, int cin, int w_idx, int b_idx, const void* residual, void* dst,
-                   int mode = OUT_ROWMAJOR, int batch = 1, int ld_t = 0) const {
+                   int mode = OUT_ROWMAJOR, int batch = 1, int ld_t = 0, Next behind = kNone) const {
     WView wv{c};
     ConvArgs a{dt, src, nullptr, cin, 0, batch, rows / batch, 1, 0, 1, 1, wv.at(w_idx), c.weights[w_idx].info.shape[0],
                b_idx >= 0 ? wv.f32(b_idx) : nullptr, nullptr, 0, residual, dst, mode, ld_t, temp(9), ws.temp_bytes[9]};
     a.w_blocks = 1;
+    ask_ahead(a, behind);
     return launch_conv(a, s);
   }
   ad_status gn(const void* src0, const void* src1, int c0, int c1, int hw, int g_idx, int silu, void* dst) const {
@@ -84,9 +110,10 @@ struct Eval {
     return launch_layernorm(dt, src, rows, ch, wv.f32(g_idx), wv.f32(g_idx + 1), c.cfg.ln_eps, dst, s);
   }
   // a linear layer behind a LayerNorm of h (gain and offset at g_idx), in one launch where it takes the norm in
-  ad_status ln_linear(const void* h, int rows, int ch, int g_idx, ConvArgs a) const {
+  ad_status ln_linear(const void* h, int rows, int ch, int g_idx, ConvArgs a, Next behind) const {
     WView wv{c};
     a.w_blocks = 1;
+    ask_ahead(a, behind);
     a.src0 = h;
     if (conv_takes_ln(dt, rows, a.n_out, ch, a.out_mode)) {
       a.ln_gain = wv.f32(g_idx); a.ln_offset = wv.f32(g_idx + 1); a.ln_eps = c.cfg.ln_eps;
@@ -107,7 +134,7 @@ struct Eval {
     AD_TRY(gn(x0, x1, f.c_in, f.c_skip, hw, w0 + 0, 1, temp(0)));
     // conv1 adds this block's slice of the fused time projection per (sample, channel)
     const float* rowvec = proj + (u.temb_row - cp.temb_row0);
-    AD_TRY(conv(temp(0), nullptr, ci, 0, f.h_in, f.w_in, 0, 3, 1, w0 + 2, w0 + 3, rowvec, nullptr, temp(1)));
+    AD_TRY(conv(temp(0), nullptr, ci, 0, f.h_in, f.w_in, 0, 3, 1, w0 + 2, w0 + 3, rowvec, nullptr, temp(1), OUT_ROWMAJOR, 0, {ui, w0 + 8}));
     AD_TRY(gn(temp(1), nullptr, f.c_out, 0, hw, w0 + 6, 1, temp(0)));
     const void* shortcut = x0;
     if (ci != f.c_out && conv_takes_shortcut(dt, (long long)c.cfg.batch * hw, f.c_out, f.c_out, ci)) {
@@ -116,13 +143,14 @@ struct Eval {
                  nullptr, tensor_out(ui), OUT_ROWMAJOR, 0, temp(9), ws.temp_bytes[9]};
       a.x0 = x0; a.x1 = x1; a.xc0 = f.c_in; a.xc1 = f.c_skip; a.xw = wv.at(w0 + 10);
       a.w_blocks = 1;
+      ask_ahead(a, {ui + 1, kFirst});
       return launch_conv(a, s);
     }
     if (ci != f.c_out) {
       AD_TRY(conv(x0, x1, f.c_in, f.c_skip, f.h_in, f.w_in, 0, 1, 1, w0 + 10, w0 + 11, nullptr, nullptr, temp(2)));
       shortcut = temp(2);
     }
-    return conv(temp(0), nullptr, f.c_out, 0, f.h_in, f.w_in, 0, 3, 1, w0 + 8, w0 + 9, nullptr, shortcut, tensor_out(ui));
+    return conv(temp(0), nullptr, f.c_out, 0, f.h_in, f.w_in, 0, 3, 1, w0 + 8, w0 + 9, nullptr, shortcut, tensor_out(ui), OUT_ROWMAJOR, 0, {ui + 1, kFirst});
   }
   // cross-attention key / value projections of the text embedding for the layer whose weights start at w
   ad_status text_kv(int w, void* kdst, void* vdst) const {
@@ -193,18 +221,18 @@ struct Eval {
     AD_TRY(gn(x, nullptr, Cc, 0, L, w + 0, 0, temp(0)));
     if (tfm_rows_fits(dt, Cc, d, Lk, (long long)B * L)) return tfm_by_rows(f, w, x, tensor_out(ui), ui);
     WView wv{c};
-    AD_TRY(linear(temp(0), M, Cc, w + 2, w + 3, nullptr, temp(1)));
+    AD_TRY(linear(temp(0), M, Cc, w + 2, w + 3, nullptr, temp(1), OUT_ROWMAJOR, 1, 0, {ui, w + 6}));
     w += 4;
     void* h = temp(1);
     for (int k = 0; k < f.depth; ++k, w += 20) {
       // ln1.g ln1.b a1.q a1.k a1.v a1.o.w a1.o.b ln2.g ln2.b a2.q a2.k a2.v a2.o.w a2.o.b ln3.g ln3.b ff1.w ff1.b ff2.w ff2.b
       // q, k, v of the self-attention in one GEMM; v lands transposed when the MFMA attention kernel follows
       AD_TRY(ln_linear(h, M, Cc, w + 0, ConvArgs{dt, nullptr, nullptr, Cc, 0, B, L, 1, 0, 1, 1, wv.at(w + 2), 3 * Cc, nullptr, nullptr, 0, nullptr, temp(2), OUT_QKV,
-                                                        vt ? lp : 0, temp(9), ws.temp_bytes[9], temp(3), temp(4)}));
+                                                        vt ? lp : 0, temp(9), ws.temp_bytes[9], temp(3), temp(4)}, {ui, w + 5}));
       AD_TRY(launch_attention(dt, temp(2), temp(3), temp(4), vt, B, L, L, Cc, d, Cc, Cc, vt ? lp : Cc, Cc, temp(5), s));
-      AD_TRY(linear(temp(5), M, Cc, w + 5, w + 6, h, h));
+      AD_TRY(linear(temp(5), M, Cc, w + 5, w + 6, h, h, OUT_ROWMAJOR, 1, 0, {ui, w + 9}));
       AD_TRY(ln_linear(h, M, Cc, w + 7, ConvArgs{dt, nullptr, nullptr, Cc, 0, 1, M, 1, 0, 1, 1, wv.at(w + 9), Cc, nullptr, nullptr, 0, nullptr, temp(2), OUT_ROWMAJOR,
-                                                        0, temp(9), ws.temp_bytes[9]}));
+                                                        0, temp(9), ws.temp_bytes[9]}, {ui, w + 12}));
       // keys / values of the text: taken from the per-run cache when it was built from this embedding
       const void* tk = temp(7);
       const void* tv = temp(8);
@@ -217,20 +245,20 @@ struct Eval {
       // video: every frame attends to the one text embedding, so the frames' tokens form one long query sequence
       if (c.cfg.frames > 0) AD_TRY(launch_attention(dt, temp(2), tk, tv, vt, 1, M, Lk, Cc, d, Cc, Cc, vt ? lkp : Cc, Cc, temp(5), s));
       else AD_TRY(launch_attention(dt, temp(2), tk, tv, vt, B, L, Lk, Cc, d, Cc, Cc, vt ? lkp : Cc, Cc, temp(5), s));
-      AD_TRY(linear(temp(5), M, Cc, w + 12, w + 13, h, h));
+      AD_TRY(linear(temp(5), M, Cc, w + 12, w + 13, h, h, OUT_ROWMAJOR, 1, 0, {ui, w + 16}));
       AD_TRY(ln_linear(h, M, Cc, w + 14, ConvArgs{dt, nullptr, nullptr, Cc, 0, 1, M, 1, 0, 1, 1, wv.at(w + 16), 8 * Cc, wv.f32(w + 17), nullptr, 0, nullptr, temp(6),
-                                                         OUT_GEGLU, 0, temp(9), ws.temp_bytes[9]}));
-      AD_TRY(linear(temp(6), M, 4 * Cc, w + 18, w + 19, h, h));
+                                                         OUT_GEGLU, 0, temp(9), ws.temp_bytes[9]}, {ui, w + 18}));
+      AD_TRY(linear(temp(6), M, 4 * Cc, w + 18, w + 19, h, h, OUT_ROWMAJOR, 1, 0, {ui, k + 1 < f.depth ? w + 22 : w + 20}));
     }
     void* z = tensor_out(ui);
-    AD_TRY(linear(h, M, Cc, w + 0, w + 1, x, z));
+    AD_TRY(linear(h, M, Cc, w + 0, w + 1, x, z, OUT_ROWMAJOR, 1, 0, c.cfg.temporal_heads ? Next{ui, w + 4} : Next{ui + 1, kFirst}));
     if (c.cfg.temporal_heads == 0) return AD_OK;
     // temporal layer: temp.ln.g temp.ln.b temp.q temp.k temp.v temp.o.w temp.o.b; tokens = the frames of one position
     w += 2;
     AD_TRY(ln_linear(z, M, Cc, w + 0, ConvArgs{dt, nullptr, nullptr, Cc, 0, B, L, 1, 0, 1, 1, wv.at(w + 2), 3 * Cc, nullptr, nullptr, 0, nullptr, temp(2), OUT_QKV,
-                                                      0, temp(9), ws.temp_bytes[9], temp(3), temp(4)}));
+                                                      0, temp(9), ws.temp_bytes[9], temp(3), temp(4)}, {ui, w + 5}));
     AD_TRY(launch_attention_frames(dt, temp(2), temp(3), temp(4), c.cfg.frames, L, Cc, c.cfg.temporal_heads, Cc, Cc, Cc, Cc, temp(5), s));
-    return linear(temp(5), M, Cc, w + 5, w + 6, z, z);
+    return linear(temp(5), M, Cc, w + 5, w + 6, z, z, OUT_ROWMAJOR, 1, 0, {ui + 1, kFirst});
   }
 };
 
@@ -300,10 +328,10 @@ static ad_status run_component(Ctx& c, int comp, int lane, const void* const* in
       }
       case AD_UNIT_TFM: AD_TRY(e.tfm(u, ui)); break;
       case AD_UNIT_DOWN:
-        AD_TRY(e.conv(e.tensor_in(ui - 1), nullptr, f.c_in, 0, f.h_in, f.w_in, 0, 3, 2, u.w_first, u.w_first + 1, nullptr, nullptr, e.tensor_out(ui)));
+        AD_TRY(e.conv(e.tensor_in(ui - 1), nullptr, f.c_in, 0, f.h_in, f.w_in, 0, 3, 2, u.w_first, u.w_first + 1, nullptr, nullptr, e.tensor_out(ui), OUT_ROWMAJOR, 0, {ui + 1, Eval::kFirst}));
         break;
       case AD_UNIT_UP:
-        AD_TRY(e.conv(e.tensor_in(ui - 1), nullptr, f.c_in, 0, f.h_in, f.w_in, 1, 3, 1, u.w_first, u.w_first + 1, nullptr, nullptr, e.tensor_out(ui)));
+        AD_TRY(e.conv(e.tensor_in(ui - 1), nullptr, f.c_in, 0, f.h_in, f.w_in, 1, 3, 1, u.w_first, u.w_first + 1, nullptr, nullptr, e.tensor_out(ui), OUT_ROWMAJOR, 0, {ui + 1, Eval::kFirst}));
         break;
       case AD_UNIT_OUT:
         AD_TRY(e.gn(e.tensor_in(ui - 1), nullptr, f.c_in, 0, f.h_in * f.w_in, u.w_first, 1, e.temp(0)));
