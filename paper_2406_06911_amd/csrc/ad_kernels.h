@@ -51,6 +51,7 @@ struct ConvArgs {
   // a LayerNorm over the channels in front of a linear layer, only where conv_takes_ln() says so: gain and offset of the channels, epsilon
   const float* ln_gain = nullptr; const float* ln_offset = nullptr;
   float ln_eps = 0.f;
+  int gn_groups = 0, gn_silu = 0;       // > 0: not a LayerNorm but a GroupNorm of the input (and SiLU), only where conv_takes_gn() says so
   const void* ahead = nullptr;          // weights of a later launch, fetched from memory beside the product (a hint; the LDS-DMA kernels take it)
   size_t ahead_bytes = 0;
   int w_blocks = 0;                     // w and xw are in blocks (pack_blocks()) instead of rows
@@ -67,6 +68,8 @@ size_t conv_workspace_bytes(int dtype, long long m, int n, int k, int out_mode);
 bool conv_takes_shortcut(int dtype, long long m, int n, int c, int xc);      // c, xc: channels of the 3x3 and of the 1x1 convolution
 // whether a LayerNorm over c channels goes into the launch of the linear layer behind it
 bool conv_takes_ln(int dtype, long long m, int n, int c, int out_mode);
+// whether a GroupNorm over the c0 + c1 channels goes into the launch of the 3x3 convolution behind it (stride 1; out must not overlap the sources)
+bool conv_takes_gn(int dtype, int batch, int h, int w, int c0, int c1, int n, int groups, int out_mode);
 
 ad_status launch_groupnorm(int dtype, const void* src0, const void* src1, int c0, int c1, int batch, int hw, int groups,
                            const float* gamma, const float* beta, float eps, int silu, void* out, void* scratch,

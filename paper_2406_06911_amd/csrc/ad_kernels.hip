@@ -66,7 +66,8 @@ struct IgemmParams {
   const void* x0; const void* x1; const void* xw;       // XTRA (k_igemm_p3): sources and weights of the 1x1 convolution behind the taps
   int xc0, xc1, kt_main;                                // its channels; k-tiles of the taps
   unsigned xbytes0, xbytes1, xbytes_w;
-  const float* ln_gain; const float* ln_offset; float ln_eps;      // LN (k_igemm_small)
+  const float* ln_gain; const float* ln_offset; float ln_eps;      // LN, GN (k_igemm_small): of the channels
+  int gn_groups, gn_silu, gn_log_vps, gn_cpg; double gn_inv_n;                              // GN: groups (0: none), log2 of a wavefront's accesses to a pixel, see gn_stage()
   const void* ahead; unsigned ahead_bytes, ahead_span;             // k_igemm_p3: weights of a later launch (0 bytes: none), and a wavefront's share of them
 };
 
@@ -965,6 +966,15 @@ static ad_status run_igemm_p3(const IgemmParams& p0, const char* name, hipStream
 // 3.9 + 8.6 -> 11.0; fp32 288x384x128 3.6 + 4.0 -> 5.2, 288x1024x128 3.6 + 6.2 -> 7.6, 72x2048x256 3.6 + 6.0 -> 7.6; and the gap between two launches.  Whole runs
 // against a launch for every norm, ms: narrow model 37.28 -> 36.73, fp32 17.53 -> 17.21, with stride 2 27.04 -> 25.84, 576x320 px 64.39 -> 64.13, 512px level.
 // The larger tiles, whose LDS is filled by the load unit and whose fragments every column tile would normalise again, leave the norm to k_layernorm.
+//
+// GN: a GroupNorm (and SiLU) in front of a 3x3 convolution of a small map, likewise: the launch it saves takes 3.6 us, nearly all of it the launch itself and a
+// round trip to memory, in a chain of launches that wait for one another.  Every workgroup takes in the samples that its rows belong to (9 to 256 pixels), a
+// wavefront an eighth of the channels, so that the statistics of its groups need no other wavefront; the pixels that the taps read are normalised once, on
+// their way into LDS, and the fragments come from there.  Same statistics as k_gn_group (mean first, then deviations), other order of the sums.
+// Measured inside the models, us (norm + convolution -> convolution): bf16 18x256x2304 3.7 + 6.7 -> 8.2, 72x256x2304 3.7 + 7.1 -> 8.5, 128x256x2304 3.7 + 7.2 -> 7.8,
+// 288x128x1152 3.7 + 5.5 -> 7.3; fp32 64x64x576 3.4 + 5.5 -> 6.1, 256x32x288 3.6 + 4.8 -> 6.7; and the gap between two launches.
+// Whole runs, ms: tiny fp32 2.30 -> 1.73, narrow 36.9 -> 35.7, with stride 2 26.2 -> 25.4, narrow fp32 17.13 -> 17.04.
+// Taken back: statistics over all wavefronts through LDS, merged in double (4.3 us a launch), and 1x1 convolutions (72x256x256 3.7 + 3.9 -> 7.9).
 // =================================================================================================
 constexpr int small_ktiles(int bm, int bn) { return 200 * 1024 / ((bm + bn) * kRowBytes); }      // k-tiles that small_tile() takes at the most
 // Sum over the threads of a row, TPR = 16 or 32 neighbouring lanes, as k_layernorm's lanes add up: distances 32 / TPR .. 1, where a distance within 16 lanes is a
@@ -1019,8 +1029,108 @@ __device__ __forceinline__ void ln_stats(const IgemmParams& p, int sub, const ty
   if (sub == 0) { *mean_out = mean; *rstd_out = rstd; }
 }
 
-template <typename T, int TM, int TN, int MODE, bool LN = false>
+constexpr int gn_pitch(int row_bytes) { return row_bytes + 16; }      // of a pixel in LDS: 16 neighbouring pixels fall on different banks
+constexpr int gn_act_bytes(int bm, int ws, int row_bytes) { return 256 + (bm + 2 * (ws + 1)) * gn_pitch(row_bytes); }
+template <int CTRL> __device__ __forceinline__ float add_dpp(float v) { return v + dpp_f<CTRL>(v); }
+// A wavefront's eighth of the channels (whole groups) of all pixels of nb samples, in registers: access k of a lane is pixel px + k * step.  Normalises them
+// and leaves those that the tile reads, rows lo .. hi - 1, in LDS: 256 zero bytes, then a row after the other.  The statistics stay inside the wavefront: no barrier
+// before the last.  As in k_gn_group the mean comes first, to its 12 leading bits, then the sums of the deviations from it and of their squares.
+template <typename T, int N>
+__device__ __forceinline__ void gn_stage(const IgemmParams& p, const typename Vec<T>::type (&x)[N], const float (&gain)[Vec<T>::N], const float (&offset)[Vec<T>::N],
+                                         int first, int nb, int px, int channel, int lo, int hi, char* base) {
+  typedef typename Vec<T>::type V;
+  constexpr int VN = Vec<T>::N, PAIRS = VN / 2;
+  const int hw = p.hw_out, cpg = p.gn_cpg, lg = p.gn_log_vps, step = 64 >> lg;
+  const double inv_n = p.gn_inv_n;
+  auto again = [&](int e) { return (e & 1 && cpg >= 4) || (e == 2 && cpg >= 8); };      // the pair belongs to the group of the one before
+  // pair sums -> the sum of the pair's group, in every lane that holds a part of it
+  auto total = [&](float (&v)[PAIRS]) {
+    if (cpg >= 4)
+#pragma unroll
+      for (int e = 0; e < PAIRS; e += 2) v[e] += v[e + 1];
+    if (PAIRS == 4 && cpg >= 8) v[0] += v[2];
+#pragma unroll
+    for (int e = 0; e < PAIRS; ++e) {
+      if (again(e)) continue;
+      float t = v[e];
+      if (lg <= 0) t = add_dpp<0x121>(t);                // rotations within 16 lanes by 1, 2, 4, 8
+      if (lg <= 1) t = add_dpp<0x122>(t);
+      if (lg <= 2) t = add_dpp<0x124>(t);
+      if (lg <= 3) t = add_dpp<0x128>(t);
+      const unsigned u = __float_as_uint(t);
+      const auto h = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+      t = __uint_as_float(h[0]) + __uint_as_float(h[1]);
+      const unsigned w = __float_as_uint(t);
+      const auto o = __builtin_amdgcn_permlane32_swap(w, w, false, false);
+      t = __uint_as_float(o[0]) + __uint_as_float(o[1]);
+      if (cpg >= 2 * VN) t = add_dpp<0xB1>(t);           // the accesses of a group of 2 or 4: quad_perm 1 0 3 2, then 2 3 0 1
+      if (cpg >= 4 * VN) t = add_dpp<0x4E>(t);
+      v[e] = t;
+    }
+    if (cpg >= 4)
+#pragma unroll
+      for (int e = 0; e < PAIRS; e += 2) v[e + 1] = v[e];
+    if (PAIRS == 4 && cpg >= 8) { v[2] = v[0]; v[3] = v[0]; }
+  };
+  if (threadIdx.x < 16) *(f32x4*)(base + threadIdx.x * 16) = f32x4{0.f, 0.f, 0.f, 0.f};
+  const int pitch = gn_pitch(p.ctot * (int)sizeof(T));
+  char* const to = base + 256 + channel * (int)sizeof(T);
+  for (int z = 0; z < nb; ++z) {
+    auto mine = [&](int k) { return (unsigned)(px + k * step - z * hw) < (unsigned)hw; };
+    float s[PAIRS], q[PAIRS], about[PAIRS];
+#pragma unroll
+    for (int e = 0; e < PAIRS; ++e) s[e] = 0.f;
+#pragma unroll
+    for (int k = 0; k < N; ++k)
+      if (mine(k))
+#pragma unroll
+        for (int e = 0; e < VN; ++e) s[e / 2] += to_f(x[k][e]);
+    total(s);
+#pragma unroll
+    for (int e = 0; e < PAIRS; ++e) { about[e] = __uint_as_float(__float_as_uint(s[e] * (float)inv_n) & 0xfffff000u); s[e] = 0.f; q[e] = 0.f; }
+#pragma unroll
+    for (int k = 0; k < N; ++k)
+      if (mine(k))
+#pragma unroll
+        for (int e = 0; e < VN; ++e) { const float d = to_f(x[k][e]) - about[e / 2]; s[e / 2] += d; q[e / 2] += d * d; }
+    total(s); total(q);
+    float ga[VN], be[VN], rest = 0.f, rstd = 0.f;
+#pragma unroll
+    for (int e = 0; e < PAIRS; ++e) {
+      if (!again(e)) {
+        const double more = s[e] * inv_n;                // mean - about
+        double var = q[e] * inv_n - more * more;
+        var = (var < 0.0 ? 0.0 : var) + (double)p.ln_eps;
+        const float r0 = rsqrtf((float)var);
+        rstd = (float)(r0 * (1.5 - 0.5 * var * r0 * r0));
+        if (!(var > 1e-30 && var < 1e30)) rstd = (float)(1.0 / sqrt(var));
+        rest = (float)more;
+      }
+#pragma unroll
+      for (int c = 2 * e; c < 2 * e + 2; ++c) { ga[c] = gain[c] * rstd; be[c] = offset[c] - rest * ga[c]; }
+    }
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+      const int row = first + px + k * step;
+      if (!mine(k) || row < lo || row >= hi) continue;
+      V o;
+#pragma unroll
+      for (int e = 0; e < VN; ++e) {
+        float y = (to_f(x[k][e]) - about[e / 2]) * ga[e] + be[e];
+        if (p.gn_silu) y = silu_f(y);
+        o[e] = from_f<T>(y);
+      }
+      *(V*)(to + (row - lo) * pitch) = o;
+    }
+  }
+  __syncthreads();
+}
+
+enum { NORM_NONE = 0, NORM_LAYER = 1, NORM_GROUP = 2 };
+constexpr int gn_hold(int vn) { return 40 / vn; }        // GN: accesses of vn elements that a thread holds at the most
+template <typename T, int TM, int TN, int MODE, int NORM = NORM_NONE>
 __global__ __launch_bounds__(512) void k_igemm_small(IgemmParams p) {
+  constexpr bool LN = NORM == NORM_LAYER, GN = NORM == NORM_GROUP;
   typedef typename Vec<T>::type V;
   typedef typename Vec4<T>::type V4;
   constexpr int BM = 16 * TM, BN = 16 * TN, NW = 8, PF = 2, PITCH = BN + 4;
@@ -1067,7 +1177,32 @@ __global__ __launch_bounds__(512) void k_igemm_small(IgemmParams p) {
   const int mine = (p.ktiles - wave + NW - 1) / NW;      // k-tiles of this wavefront (0 when there are fewer k-tiles than wavefronts)
   int f_tap = wave * BK / p.ctot, f_cc = wave * BK - f_tap * p.ctot;
   unsigned f_w = (unsigned)wave * p.w_kt;
-  V af[PF][TM][2], bf[PF][TN][2];
+  V af[GN ? 1 : PF][TM][2], bf[PF][TN][2];
+  // GN: a wavefront's eighth of the channels of the samples that the tile's rows belong to, asked for ahead of everything else
+  constexpr int HOLD = GN ? gn_hold(VN) : 1;
+  V held[HOLD];
+  float g_gain[GN ? VN : 1], g_offset[GN ? VN : 1];
+  int g_px = 0, g_channel = 0, g_first = 0, g_nb = 0, g_lo = 0, g_hi = 0;
+  if constexpr (GN) {
+    const int m_last = min(m0 + BM, p.M) - 1, z0 = (int)fast_div((unsigned)m0, p.div_hw), reach = p.ws + 1;
+    g_first = z0 * p.hw_out;
+    g_nb = (int)fast_div((unsigned)m_last, p.div_hw) - z0 + 1;
+    g_lo = max(m0 - reach, g_first); g_hi = min(m_last + reach + 1, g_first + g_nb * p.hw_out);
+    g_px = lane >> p.gn_log_vps;
+    g_channel = (((wave << p.gn_log_vps) + (lane & ((1 << p.gn_log_vps) - 1)))) * VN;
+    const bool second = g_channel >= p.c0;
+    const T* src = second ? (const T*)p.src1 + (g_channel - p.c0) : (const T*)p.src0 + g_channel;
+    const int ld = second ? p.c1 : p.c0, step = 64 >> p.gn_log_vps;
+#pragma unroll
+    for (int k = 0; k < HOLD; ++k)
+      if (g_px + k * step < g_nb * p.hw_out) held[k] = *(const V*)(src + (size_t)(g_first + g_px + k * step) * ld);
+#pragma unroll
+    for (int e = 0; e < VN; e += 4) {
+      const f32x4 g = *(const f32x4*)(p.ln_gain + g_channel + e), o = *(const f32x4*)(p.ln_offset + g_channel + e);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) { g_gain[e + i] = g[i]; g_offset[e + i] = o[i]; }
+    }
+  }
   auto fetch = [&](int s) {
     const int u = p.ksize == 3 ? f_tap / 3 : 0, v = p.ksize == 3 ? f_tap - 3 * u : 0;
     const unsigned bit = 1u << (u * 3 + v), sb = f_w;
@@ -1075,6 +1210,7 @@ __global__ __launch_bounds__(512) void k_igemm_small(IgemmParams p) {
     for (int j = 0; j < TN; ++j)
 #pragma unroll
       for (int h = 0; h < 2; ++h) bf[s][j][h] = buffer_load16<V>(rsw, b_off[j] + h * 64, sb);
+    if constexpr (GN) { f_w += NW * p.w_kt; return; }
     const bool second = f_cc >= p.c0;
     const unsigned cs = (unsigned)(second ? p.c1 : p.c0) * ES, sc = (unsigned)(second ? f_cc - p.c0 : f_cc) * ES;
     // the tap goes into the lane's offset: the range check compares that offset with the tensor's size less the scalar one, which
@@ -1147,6 +1283,18 @@ __global__ __launch_bounds__(512) void k_igemm_small(IgemmParams p) {
 #pragma unroll
     for (int i = 0; i < TM; ++i) { mean[i] = ln_rows[16 * i + r16]; rstd[i] = ln_rows[BM + 16 * i + r16]; }
   }
+  // GN: the normalised pixels in LDS, behind the partial sums
+  const int g_pitch = gn_pitch(p.ctot * ES);
+  char* const act = lds + NW * BM * PITCH * 4;
+  unsigned g_at[TM];
+  if constexpr (GN) {
+    gn_stage<T, HOLD>(p, held, g_gain, g_offset, g_first, g_nb, g_px, g_channel, g_lo, g_hi, act);
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {                       // pixel of tap (0, 0), modulo 2^32 where it lies before the staged ones (the tap is masked then)
+      const int m = m0 + 16 * i + r16;
+      g_at[i] = 256u + (unsigned)(m - (p.ws + 1) - g_lo) * (unsigned)g_pitch + kg * 16;
+    }
+  }
   f32x4 acc[TM][TN];
 #pragma unroll
   for (int i = 0; i < TM; ++i)
@@ -1156,11 +1304,23 @@ __global__ __launch_bounds__(512) void k_igemm_small(IgemmParams p) {
 #pragma unroll
     for (int s = 0; s < PF; ++s) {
       if (i0 + s >= mine) break;
+      if constexpr (GN) {
+        const int u = f_tap / 3, v = f_tap - 3 * u;
+        const unsigned bit = 1u << f_tap, tap = (unsigned)(u * p.ws + v) * (unsigned)g_pitch + (unsigned)(f_cc * ES);
+#pragma unroll
+        for (int i = 0; i < TM; ++i) {
+          const unsigned o = (a_taps[i] & bit) ? g_at[i] + tap : 0u;
+#pragma unroll
+          for (int h = 0; h < 2; ++h) af[0][i][h] = *(const V*)(act + o + h * 64);
+        }
+        f_cc += BK * NW;
+        while (f_cc >= p.ctot) { f_cc -= p.ctot; ++f_tap; }
+      }
 #pragma unroll
       for (int h = 0; h < 2; ++h)
 #pragma unroll
         for (int i = 0; i < TM; ++i) {
-          V a = af[s][i][h];
+          V a = af[GN ? 0 : s][i][h];
           if constexpr (LN) {
             const float* ch = ln_chan + ((i0 + s) * NW + wave) * BK + (h * 64 + kg * 16) / ES;
 #pragma unroll
@@ -1243,25 +1403,31 @@ __global__ __launch_bounds__(512) void k_igemm_small(IgemmParams p) {
   }
 }
 
-template <typename T, int TM, int TN, int MODE, bool LN = false>
+// samples that the rows of a tile belong to at the most
+static int gn_samples(int bm, int batch, int hw) { return std::min(batch, hw % bm == 0 ? 1 : (bm - 2) / hw + 2); }
+template <typename T, int TM, int TN, int MODE, int NORM = NORM_NONE>
 static ad_status run_igemm_small(const IgemmParams& p0, const char* name, hipStream_t s) {
-  if constexpr (!LN && (MODE == OUT_ROWMAJOR || MODE == OUT_QKV || MODE == OUT_GEGLU))
-    if (p0.ln_gain) return run_igemm_small<T, TM, TN, MODE, true>(p0, name, s);
+  constexpr bool LN = NORM == NORM_LAYER;
+  if constexpr (NORM == NORM_NONE && (MODE == OUT_ROWMAJOR || MODE == OUT_TRANSPOSED_F32))
+    if (p0.gn_groups) return run_igemm_small<T, TM, TN, MODE, NORM_GROUP>(p0, name, s);
+  if constexpr (NORM == NORM_NONE && (MODE == OUT_ROWMAJOR || MODE == OUT_QKV || MODE == OUT_GEGLU))
+    if (p0.ln_gain) return run_igemm_small<T, TM, TN, MODE, NORM_LAYER>(p0, name, s);
   IgemmParams p = p0;
   set_tiles(p, 16 * TM, 16 * TN);
-  constexpr int lds_most = 8 * 16 * TM * (16 * TN + 4) * 4 + (LN ? 2 * 16 * TM * 4 + small_ktiles(16 * TM, 16 * TN) * kRowBytes / (int)sizeof(T) * 8 : 0);
-  const int lds_bytes = 8 * 16 * TM * (16 * TN + 4) * 4 + (LN ? 2 * 16 * TM * 4 + p.ctot * 8 : 0);
+  constexpr int lds_sums = 8 * 16 * TM * (16 * TN + 4) * 4;
+  constexpr int lds_most = NORM == NORM_GROUP ? (int)kLdsLimit : lds_sums + (LN ? 2 * 16 * TM * 4 + small_ktiles(16 * TM, 16 * TN) * kRowBytes / (int)sizeof(T) * 8 : 0);
+  const int lds_bytes = lds_sums + (LN ? 2 * 16 * TM * 4 + p.ctot * 8 : NORM == NORM_GROUP ? gn_act_bytes(16 * TM, p.ws, p.ctot * (int)sizeof(T)) : 0);
   if constexpr (lds_most > 65536) {
     static std::atomic<bool> attr_set{false};
     if (!attr_set) {
-      AD_HIP(hipFuncSetAttribute((const void*)k_igemm_small<T, TM, TN, MODE, LN>, hipFuncAttributeMaxDynamicSharedMemorySize, lds_most));
+      AD_HIP(hipFuncSetAttribute((const void*)k_igemm_small<T, TM, TN, MODE, NORM>, hipFuncAttributeMaxDynamicSharedMemorySize, lds_most));
       attr_set = true;
     }
   }
   const double in_bytes = (double)p.M * p.ctot * sizeof(T) * (p.stride == 2 ? 4 : 1) / (p.up ? 4 : 1);
   const double out_cols = p.out_mode == OUT_GEGLU ? p.N / 2 : p.N;
   ProfLaunch pl(name, 2.0 * p.M * p.N * p.k_prof, in_bytes + (double)p.N * p.Kp * sizeof(T) + (double)p.M * out_cols * sizeof(T), s, p.M, p.N, p.Kp);
-  hipLaunchKernelGGL((k_igemm_small<T, TM, TN, MODE, LN>), dim3(p.tiles_n * p.tiles_m), dim3(512), lds_bytes, s, p);
+  hipLaunchKernelGGL((k_igemm_small<T, TM, TN, MODE, NORM>), dim3(p.tiles_n * p.tiles_m), dim3(512), lds_bytes, s, p);
   AD_HIP(hipGetLastError());
   return AD_OK;
 }
@@ -1746,6 +1912,22 @@ bool conv_takes_ln(int dtype, long long m, int n, int c, int out_mode) {
   return c % bk == 0 && (out_mode == OUT_ROWMAJOR || out_mode == OUT_QKV || out_mode == OUT_GEGLU) && choose_plan(dtype, m, n, c / bk, out_mode).tile == TILE_SMALL;
 }
 
+// A small-tile launch whose threads hold at most 40 elements each: what a workgroup does for the norm grows with the samples it takes in, the launch that it
+// saves does not.  us (norm + convolution / one launch): two samples of 24x24 of 64 bf16 channels (72 elements) 3.9 + 4.3 / 10.4, 16x16 of 128 (64) 3.7 + 5.0 / 8.8,
+// 12x12 of 128 (36) 3.7 + 5.5 / 7.3, 16x16 of 64 (32) 3.8 + 4.0 / 8.2 in a chain that is one gap shorter.  Channels that a power of two of accesses covers (not 192 or 384).
+bool conv_takes_gn(int dtype, int batch, int h, int w, int c0, int c1, int n, int groups, int out_mode) {
+  const int c = c0 + c1, bk = bk_elems(dtype), es = (int)esize(dtype), vn = 16 / es, hw = h * w;
+  if ((out_mode != OUT_ROWMAJOR && out_mode != OUT_TRANSPOSED_F32) || c0 % bk || c1 % bk || groups < 8 || groups % 8 || c % (2 * groups)) return false;
+  const int cpg = c / groups, vps = c / (8 * vn);         // a wavefront takes an eighth of the channels: whole groups, whole accesses, powers of two
+  if (c % (8 * vn) || (vps & (vps - 1)) || vps > 16 || (cpg & (cpg - 1)) || cpg > 4 * vn) return false;
+  const long long m = (long long)batch * hw;
+  if (choose_plan(dtype, m, n, 9 * c / bk, out_mode).tile != TILE_SMALL) return false;
+  const SmallTile t = small_tile(m, n, 9 * c / bk, out_mode);
+  const int bm = 16 * t.tm;
+  return (long long)gn_samples(bm, batch, hw) * hw <= gn_hold(vn) * (64 / vps) &&
+         8 * bm * (16 * t.tn + 4) * 4 + gn_act_bytes(bm, w, c * es) <= (int)kLdsLimit;
+}
+
 ad_status launch_conv(const ConvArgs& a, hipStream_t s) {
   if (a.dtype != AD_F32 && a.dtype != AD_BF16) AD_FAIL(AD_ERR_INVALID, "conv: bad dtype");
   const int bk = bk_elems(a.dtype);
@@ -1792,7 +1974,20 @@ ad_status launch_conv(const ConvArgs& a, hipStream_t s) {
   p.out2 = a.out2; p.out3 = a.out3;
   p.ahead = a.ahead; p.ahead_bytes = a.ahead ? (unsigned)std::min<size_t>(a.ahead_bytes, 0x7fffffff) : 0;
   p.ln_gain = a.ln_gain; p.ln_offset = a.ln_offset; p.ln_eps = a.ln_eps;
-  if (a.ln_gain && (!a.ln_offset || a.ksize != 1 || a.stride != 1 || a.up || a.c1 || a.residual || a.rowvec || a.xw || (((uintptr_t)a.ln_gain | (uintptr_t)a.ln_offset) & 15) ||
+  p.gn_groups = a.gn_groups; p.gn_silu = a.gn_silu;
+  if (a.gn_groups) {
+    const char *o = (const char*)a.out, *s0 = (const char*)a.src0, *s1 = (const char*)a.src1;
+    const size_t es = esize(a.dtype), out_bytes = (size_t)m * a.n_out * (a.out_mode == OUT_TRANSPOSED_F32 ? 4 : es), px = (size_t)a.batch * a.hs * a.ws;
+    const bool apart = (s0 + px * a.c0 * es <= o || o + out_bytes <= s0) && (a.c1 == 0 || s1 + px * a.c1 * es <= o || o + out_bytes <= s1);
+    if (!a.ln_gain || !a.ln_offset || a.ksize != 3 || a.stride != 1 || a.up || a.xw || !apart || ((uintptr_t)s0 & 15) || (a.c1 && ((uintptr_t)s1 & 15)) ||
+        !conv_takes_gn(a.dtype, a.batch, a.hs, a.ws, a.c0, a.c1, a.n_out, a.gn_groups, a.out_mode))
+      AD_FAIL(AD_ERR_INVALID, "conv: bad GroupNorm");
+    p.gn_log_vps = 0;
+    p.gn_cpg = p.ctot / a.gn_groups;
+    p.gn_inv_n = 1.0 / ((double)p.hw_out * p.gn_cpg);
+    while ((8 * (16 / (int)es)) << p.gn_log_vps < p.ctot) ++p.gn_log_vps;
+  }
+  if (!a.gn_groups && a.ln_gain && (!a.ln_offset || a.ksize != 1 || a.stride != 1 || a.up || a.c1 || a.residual || a.rowvec || a.xw || (((uintptr_t)a.ln_gain | (uintptr_t)a.ln_offset) & 15) ||
                     !conv_takes_ln(a.dtype, m, a.n_out, a.c0, a.out_mode)))
     AD_FAIL(AD_ERR_INVALID, "conv: bad LayerNorm");
   if (a.out_mode < OUT_ROWMAJOR || a.out_mode > OUT_QKV) AD_FAIL(AD_ERR_INVALID, "conv: bad out_mode");

@@ -105,6 +105,20 @@ struct Eval {
     return launch_groupnorm(dt, src0, src1, c0, c1, c.cfg.batch, hw, c.cfg.gn_groups, wv.f32(g_idx), wv.f32(g_idx + 1),
                             c.cfg.gn_eps, silu, dst, work(ws.gn_off), c.gn_bytes, s);
   }
+  // a convolution (stride 1) behind a GroupNorm of its input (gain and offset at g_idx), in one launch where it takes the norm in
+  ad_status gn_conv(const void* src0, const void* src1, int c0, int c1, int h, int w, int g_idx, int silu, int w_idx, const float* rowvec, const void* residual,
+                    void* dst, int mode, int ld_t, Next behind) const {
+    WView wv{c};
+    if (!conv_takes_gn(dt, c.cfg.batch, h, w, c0, c1, c.weights[w_idx].info.shape[0], c.cfg.gn_groups, mode)) {
+      AD_TRY(gn(src0, src1, c0, c1, h * w, g_idx, silu, temp(0)));
+      return conv(temp(0), nullptr, c0 + c1, 0, h, w, 0, 3, 1, w_idx, w_idx + 1, rowvec, residual, dst, mode, ld_t, behind);
+    }
+    ConvArgs a{dt, src0, src1, c0, c1, c.cfg.batch, h, w, 0, 3, 1, wv.at(w_idx), c.weights[w_idx].info.shape[0], wv.f32(w_idx + 1), rowvec, proj_ld, residual, dst, mode, ld_t};
+    a.ln_gain = wv.f32(g_idx); a.ln_offset = wv.f32(g_idx + 1); a.ln_eps = c.cfg.gn_eps;
+    a.gn_groups = c.cfg.gn_groups; a.gn_silu = silu;
+    a.w_blocks = 1;
+    return launch_conv(a, s);
+  }
   ad_status ln(const void* src, int rows, int ch, int g_idx, void* dst) const {
     WView wv{c};
     return launch_layernorm(dt, src, rows, ch, wv.f32(g_idx), wv.f32(g_idx + 1), c.cfg.ln_eps, dst, s);
@@ -131,14 +145,13 @@ struct Eval {
     const void* x1 = f.skip_from >= 0 ? tensor_in(f.skip_from) : nullptr;
     if (!x0 || (f.skip_from >= 0 && !x1)) AD_FAIL(AD_ERR_STATE, "unit %s: missing input", f.name);
     // manifest order: gn1.g gn1.b conv1.w conv1.b temb.w temb.b gn2.g gn2.b conv2.w conv2.b [short.w short.b]
-    AD_TRY(gn(x0, x1, f.c_in, f.c_skip, hw, w0 + 0, 1, temp(0)));
     // conv1 adds this block's slice of the fused time projection per (sample, channel)
     const float* rowvec = proj + (u.temb_row - cp.temb_row0);
-    AD_TRY(conv(temp(0), nullptr, ci, 0, f.h_in, f.w_in, 0, 3, 1, w0 + 2, w0 + 3, rowvec, nullptr, temp(1), OUT_ROWMAJOR, 0, {ui, w0 + 8}));
-    AD_TRY(gn(temp(1), nullptr, f.c_out, 0, hw, w0 + 6, 1, temp(0)));
+    AD_TRY(gn_conv(x0, x1, f.c_in, f.c_skip, f.h_in, f.w_in, w0 + 0, 1, w0 + 2, rowvec, nullptr, temp(1), OUT_ROWMAJOR, 0, {ui, w0 + 8}));
     const void* shortcut = x0;
     if (ci != f.c_out && conv_takes_shortcut(dt, (long long)c.cfg.batch * hw, f.c_out, f.c_out, ci)) {
       WView wv{c};                      // the shortcut's bias goes in as a row vector that all samples share
+      AD_TRY(gn(temp(1), nullptr, f.c_out, 0, hw, w0 + 6, 1, temp(0)));
       ConvArgs a{dt, temp(0), nullptr, f.c_out, 0, c.cfg.batch, f.h_in, f.w_in, 0, 3, 1, wv.at(w0 + 8), f.c_out, wv.f32(w0 + 9), wv.f32(w0 + 11), -1,
                  nullptr, tensor_out(ui), OUT_ROWMAJOR, 0, temp(9), ws.temp_bytes[9]};
       a.x0 = x0; a.x1 = x1; a.xc0 = f.c_in; a.xc1 = f.c_skip; a.xw = wv.at(w0 + 10);
@@ -150,7 +163,7 @@ struct Eval {
       AD_TRY(conv(x0, x1, f.c_in, f.c_skip, f.h_in, f.w_in, 0, 1, 1, w0 + 10, w0 + 11, nullptr, nullptr, temp(2)));
       shortcut = temp(2);
     }
-    return conv(temp(0), nullptr, f.c_out, 0, f.h_in, f.w_in, 0, 3, 1, w0 + 8, w0 + 9, nullptr, shortcut, tensor_out(ui), OUT_ROWMAJOR, 0, {ui + 1, kFirst});
+    return gn_conv(temp(1), nullptr, f.c_out, 0, f.h_in, f.w_in, w0 + 6, 1, w0 + 8, nullptr, shortcut, tensor_out(ui), OUT_ROWMAJOR, 0, {ui + 1, kFirst});
   }
   // cross-attention key / value projections of the text embedding for the layer whose weights start at w
   ad_status text_kv(int w, void* kdst, void* vdst) const {
@@ -334,9 +347,8 @@ static ad_status run_component(Ctx& c, int comp, int lane, const void* const* in
         AD_TRY(e.conv(e.tensor_in(ui - 1), nullptr, f.c_in, 0, f.h_in, f.w_in, 1, 3, 1, u.w_first, u.w_first + 1, nullptr, nullptr, e.tensor_out(ui), OUT_ROWMAJOR, 0, {ui + 1, Eval::kFirst}));
         break;
       case AD_UNIT_OUT:
-        AD_TRY(e.gn(e.tensor_in(ui - 1), nullptr, f.c_in, 0, f.h_in * f.w_in, u.w_first, 1, e.temp(0)));
-        AD_TRY(e.conv(e.temp(0), nullptr, f.c_in, 0, f.h_in, f.w_in, 0, 3, 1, u.w_first + 2, u.w_first + 3, nullptr, nullptr,
-                      e.tensor_out(ui), OUT_TRANSPOSED_F32, f.h_out * f.w_out));
+        AD_TRY(e.gn_conv(e.tensor_in(ui - 1), nullptr, f.c_in, 0, f.h_in, f.w_in, u.w_first, 1, u.w_first + 2, nullptr, nullptr, e.tensor_out(ui), OUT_TRANSPOSED_F32,
+                         f.h_out * f.w_out, Eval::kNone));
         break;
     }
   }

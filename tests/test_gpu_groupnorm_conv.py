@@ -1,0 +1,82 @@
+"""GroupNorm inside the 3x3 convolution behind it (small maps): the output head against 64 bits on inputs of all kinds, ResBlocks against the oracle.  Tiles that
+begin and end in the middle of samples and image rows, one and two sources, a group in a quarter of an access to four of them, both types."""
+import numpy as np
+import pytest
+import torch
+import torch.nn.functional as F
+
+from gpu_util import DEV, dev, quantize, rel_l2
+from paper_2406_06911_amd import binding as B
+from test_gpu_resblocks import check_blocks
+
+pytestmark = pytest.mark.gpu
+
+
+def config(channels, height, width, batch, groups):
+    return dict(latent_channels=4, height=height, width=width, batch=batch, channels=channels, layers_per_block=1, transformer_depth=[0] * len(channels), mid_depth=0,
+                head_dim=64, gn_groups=groups, ctx_len=8, ctx_dim=64, pooled_dim=0)
+
+
+def head(d, dtype, x, gain, offset, w, bias):
+    """The output head alone (second component of two) on x [batch][h][w][c]; result, names of the launches of the component."""
+    probe = B.AsyncDiff(d, 1, 0, 1, dtype)
+    last = len(probe.units()) - 1
+    probe.close()
+    m = B.AsyncDiff(d, 2, 1, 1, dtype, cuts=[last])
+    m.allocate(DEV)
+    mine = {"out.gn.g": gain, "out.gn.b": offset, "out.conv.w": w, "out.conv.b": bias}
+    m.load_weights({n: mine.get(n, np.zeros(s, np.float32)) for n, s in m.weight_manifest()})
+    m.reset(2)
+    text = torch.zeros(d["batch"], d["ctx_len"], d["ctx_dim"], device=DEV, dtype=x.dtype)
+    out = torch.full((d["batch"], 4, d["height"], d["width"]), float("nan"), device=DEV)
+    m.profile(True)
+    m.component_forward(2, [x], 0, text, [out], torch.cuda.current_stream())
+    torch.cuda.synchronize()
+    names = [r[0] for r in m.profile_records()]
+    m.profile(False)
+    m.close()
+    return out.cpu().numpy().astype(np.float64), names
+
+
+SHAPES = [  # dtype, channels, height, width, batch, groups, in one launch
+    (B.AD_BF16, 256, 3, 3, 2, 32, True), (B.AD_BF16, 256, 6, 6, 2, 32, True), (B.AD_BF16, 128, 12, 12, 2, 32, True), (B.AD_BF16, 64, 10, 14, 1, 32, True),
+    (B.AD_BF16, 64, 16, 20, 1, 8, True), (B.AD_BF16, 64, 17, 19, 1, 8, False), (B.AD_BF16, 512, 2, 4, 2, 16, False), (B.AD_BF16, 128, 1, 1, 1, 8, True),
+    (B.AD_BF16, 192, 6, 6, 2, 32, False), (B.AD_BF16, 128, 5, 7, 2, 64, True), (B.AD_BF16, 64, 24, 24, 2, 32, False),
+    (B.AD_F32, 32, 16, 16, 1, 8, True), (B.AD_F32, 64, 12, 12, 2, 32, True), (B.AD_F32, 128, 12, 12, 2, 32, True), (B.AD_F32, 256, 6, 6, 2, 32, False),
+    (B.AD_F32, 128, 5, 7, 1, 64, True), (B.AD_F32, 32, 3, 7, 2, 8, True), (B.AD_F32, 96, 6, 6, 1, 8, False)]
+
+
+@pytest.mark.parametrize("kind", ["plain", "offset", "outlier", "constant"])
+@pytest.mark.parametrize("dtype,c,height,width,batch,groups,fused", SHAPES)
+def test_head(dtype, c, height, width, batch, groups, fused, kind):
+    d = config([c], height, width, batch, groups)
+    rng = np.random.default_rng(c + height)
+    x = rng.standard_normal((batch, height, width, c)).astype(np.float32)
+    if kind == "offset":
+        x += 100.0 * rng.standard_normal(c).astype(np.float32)[None, None, None, :]
+    if kind == "outlier":
+        x[:, -1, -1, ::3] = 30.0
+    if kind == "constant":
+        x[-1] = 7.0                                                   # a sample without variance: eps alone
+    x = quantize(x, dtype)
+    gain, offset = (1 + 0.3 * rng.standard_normal(c)).astype(np.float32), (0.3 * rng.standard_normal(c)).astype(np.float32)
+    w, bias = quantize(rng.standard_normal((4, c, 3, 3)) * (9 * c) ** -0.5, dtype), rng.standard_normal(4).astype(np.float32)
+    got, names = head(d, dtype, dev(x, dtype), gain, offset, w, bias)
+    assert ("gn_group" not in names and "gn_apply" not in names) == fused, names
+    t = torch.from_numpy(x).double().permute(0, 3, 1, 2)
+    y = F.silu(F.group_norm(t, groups, torch.from_numpy(gain).double(), torch.from_numpy(offset).double(), 1e-5))
+    if dtype == B.AD_BF16:
+        y = y.float().bfloat16().double()                             # the operand of the matrix cores
+    ref = F.conv2d(y, torch.from_numpy(np.asarray(w)).double(), torch.from_numpy(bias).double(), padding=1).numpy()
+    # fp32: sums of 9 c terms and a dozen roundings on the way, 6e-8 each.  bf16: the same operands but for the few that fp32 rounds to the other neighbour
+    # (1e-6 of a value moves one in some thousand by 2^-8, less than 2e-4 in all)
+    assert rel_l2(got, ref) < (5e-4 if dtype == B.AD_BF16 else 3e-6), rel_l2(got, ref)
+    assert np.abs(got - ref).max() < (1e-2 if dtype == B.AD_BF16 else 3e-5) * np.sqrt(np.mean(ref ** 2))
+
+
+@pytest.mark.parametrize("dtype,channels,height,width,batch,groups", [
+    (B.AD_BF16, [256, 256], 6, 6, 2, 32), (B.AD_BF16, [128, 128], 12, 12, 2, 32), (B.AD_BF16, [64, 64], 4, 12, 2, 8), (B.AD_F32, [32, 32], 12, 4, 1, 8),
+    (B.AD_F32, [64, 64], 6, 10, 2, 16)])
+def test_blocks(monkeypatch, dtype, channels, height, width, batch, groups):
+    """Two sources, the time projection of each sample, residuals, shortcuts."""
+    check_blocks(monkeypatch, dtype, -1, channels, height, width, batch, lambda u: True, groups)
