@@ -317,9 +317,6 @@ static void build_manifest(Ctx& c) {
             auto ends = [&](const char* t) { const size_t l = std::strlen(t); return nm.size() >= l && nm.compare(nm.size() - l, l, t) == 0; };
             w.fragments = (w.role == W_CONV1 || w.role == W_GEGLU || w.role == W_QKV_Q) && !ends(".attn2.k.w") && !ends(".attn2.v.w") && !ends(".temp.o.w");
           }
-        else if (tfm_text_fits(g.dtype, C, g.head_dim, g.ctx_len, (long long)g.batch * f.h_in * f.w_in))
-          for (int k = 0; k < f.depth; ++k)      // layer k: 20 entries behind the block's first four; attn1.o.w, attn2.q.w, attn2.o.w
-            for (int i : {5, 9, 12}) c.weights[first + 4 + 20 * k + i].fragments = true;
         break;
       }
     }

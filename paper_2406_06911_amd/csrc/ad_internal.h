@@ -180,8 +180,6 @@ void pack_blocks(void* packed, int rows, int row_bytes);
 
 // whether a transformer block of this width and number of tokens (of all samples) runs in the row-local kernel (its weights are packed for that)
 bool tfm_rows_fits(int dtype, int c, int head_dim, int ctx_len, long long tokens);
-// whether, where it does not, the steps around its attention to the text do: from the self-attention's output projection to that of the text
-bool tfm_text_fits(int dtype, int c, int head_dim, int ctx_len, long long tokens);
 uint16_t f32_to_bf16(float f);
 
 }  // namespace ad

@@ -83,7 +83,7 @@ ad_status launch_attention(int dtype, const void* q, const void* k, const void* 
                            int head_dim, int ldq, int ldk, int ldv, int ldo, void* out, hipStream_t s);
 // The row-local part of a transformer block (see k_tfm_rows): the input projection (w_in) or what follows an attention over the image
 // (w_o .. b_ff2), then, where asked for, the block's output projection with its residual x (w_out, into z), then LayerNorm and q/k/v
-// (w_qkv).  Without w_out the rows go to h.  Without w_ff1 (only where tfm_text_fits() says so) it ends behind the text's output projection w_o2.  text_k [text samples][lk][c]; text_v the same, or, in bf16, [text samples][c][text_ldv].
+// (w_qkv).  Without w_out the rows go to h.  text_k [text samples][lk][c]; text_v the same, or, in bf16, [text samples][c][text_ldv].
 struct TfmRows {
   int dtype, batch, l, c, head_dim;
   float eps;

@@ -28,11 +28,10 @@ namespace ad {
 // Measured, bf16, us (the separate launches at 3.7 each inside a replayed graph -> this): behind an attention 1152 tokens of 64 channels
 // 33 -> 13.1, 288 of 128 33 -> 18.1; input projection, LayerNorm and q/k/v 11 -> 7.2 and 8.4.  Weights in rows instead of fragment order (16
 // rows of 64 bytes an access, half the rate from beyond the L2): 19 and 23.  At 256 channels the weights decide: 34.5 and 12.8, and whole runs
-// with it are 1 % slower than with the separate launches, which use the whole chip; hence kRowsMaxBytes.  A part of the list goes further, see tfm_text_fits().
+// with it are 1 % slower than with the separate launches, which use the whole chip; hence kRowsMaxBytes.
 // =================================================================================================
 enum { ROW_SYNC = 1, ROW_GEGLU = 2, ROW_HALVES = 4, ROW_SHORT = 8, ROW_TEXT = 16, ROW_PUT = 32, ROW_PUT_QKV = 64, ROW_NORM = 128 };
 constexpr int kRowsMaxBytes = 256;      // of a row of C channels
-constexpr int kTextMaxBytes = 512;      // where only the steps around the text are asked for
 constexpr int kRowOps = 9, kRowVecs = 24, kRowWaves = 8, kRowRing = 4;
 struct RowOp {
   const void* w;
@@ -181,9 +180,9 @@ __global__ __launch_bounds__(64 * kRowWaves, 4) void k_tfm_rows(RowParams p) {
     const RowOp next = read_op(o + 1);
     if (op.flags & ROW_SYNC) __syncthreads();
     if (op.flags & ROW_NORM) {
-      // 32 lanes a row, at most two accesses of four channels a lane; the row stays in registers between the two passes over it
+      // 32 lanes a row, four channels an access; the row stays in registers between the two passes over it
       const int l = lane & 31, nv = C / 4;
-      static_assert(kRowsMaxBytes <= kTextMaxBytes && kTextMaxBytes / ES <= 256, "two accesses a lane");
+      static_assert(kRowsMaxBytes / ES <= 128, "one access a lane");
       auto row_sum = [&](float v) {
         v += dpp_f<0xB1>(v);
         v += dpp_f<0x4E>(v);
@@ -193,33 +192,23 @@ __global__ __launch_bounds__(64 * kRowWaves, 4) void k_tfm_rows(RowParams p) {
       };
 #pragma unroll 1
       for (int r = 2 * wave + (lane >> 5); r < R; r += 2 * NW) {
-        f32x4 x[2], ga[2], be[2];
+        f32x4 x = {0.f, 0.f, 0.f, 0.f}, ga = x, be = x;
+        if (l < nv) {
+          const V4 t = *(const V4*)(lds + op.norm + r * p.pitch + l * 4 * ES);
+          ga = *(const f32x4*)(vec + op.gain + l * 4);
+          be = *(const f32x4*)(vec + op.offset + l * 4);
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
-          x[j] = ga[j] = be[j] = f32x4{0.f, 0.f, 0.f, 0.f};
-          const int at = l + 32 * j;
-          if (at < nv) {
-            const V4 t = *(const V4*)(lds + op.norm + r * p.pitch + at * 4 * ES);
-            ga[j] = *(const f32x4*)(vec + op.gain + at * 4);
-            be[j] = *(const f32x4*)(vec + op.offset + at * 4);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) x[j][e] = to_f(t[e]);
-          }
+          for (int e = 0; e < 4; ++e) x[e] = to_f(t[e]);
         }
-        auto four = [&](const f32x4& v) { return (v[0] + v[1]) + (v[2] + v[3]); };
-        const float mean = row_sum(four(x[0]) + four(x[1])) / C;
+        const float mean = row_sum((x[0] + x[1]) + (x[2] + x[3])) / C;
+        if (l < nv) x -= mean;
+        const float rstd = rsqrtf(row_sum((x[0] * x[0] + x[1] * x[1]) + (x[2] * x[2] + x[3] * x[3])) / C + p.eps);
+        if (l < nv) {
+          V4 t;
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
-          if (l + 32 * j < nv) x[j] -= mean;
-        const float rstd = rsqrtf(row_sum(four(x[0] * x[0]) + four(x[1] * x[1])) / C + p.eps);
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-          if (l + 32 * j < nv) {
-            V4 t;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) t[e] = from_f<T>(x[j][e] * rstd * ga[j][e] + be[j][e]);
-            *(V4*)(lds + op.src + r * op.src_pitch + (l + 32 * j) * 4 * ES) = t;
-          }
+          for (int e = 0; e < 4; ++e) t[e] = from_f<T>(x[e] * rstd * ga[e] + be[e]);
+          *(V4*)(lds + op.src + r * op.src_pitch + l * 4 * ES) = t;
+        }
       }
       __syncthreads();
     }
@@ -482,14 +471,14 @@ __global__ __launch_bounds__(64 * kRowWaves, 4) void k_tfm_rows(RowParams p) {
 // Buffers in LDS: A, H, X of C channels a row and G of 4 C (the feed-forward's inner rows; q of the attention to the text; q, k, v), the
 // attention's partial results and the vectors.  Keys are shared out so that there is work for eight wavefronts.
 struct RowPlan { int tm, splits, split_keys, part, bytes; };
-static RowPlan plan_rows(int dtype, int c, int head_dim, int batch, int l, int lk, int inner) {      // inner: channels of G
+static RowPlan plan_rows(int dtype, int c, int head_dim, int batch, int l, int lk) {
   const int es = (int)esize(dtype), block = dtype == AD_BF16 ? 32 : 16;
   auto plan = [&](int tm) {
     RowPlan r{tm};
     const int heads = c / head_dim, blocks = (lk + block - 1) / block, want = std::max(1, kRowWaves / (heads * tm));
     r.split_keys = (blocks + want - 1) / want * block;
     r.splits = (lk + r.split_keys - 1) / r.split_keys;
-    r.part = 16 * tm * (3 * (c * es + 16) + (inner * es + 16));
+    r.part = 16 * tm * (3 * (c * es + 16) + (4 * c * es + 16));
     r.bytes = r.part + heads * tm * r.splits * 16 * (head_dim + 4) * 4 + kRowVecs * c * 4;
     return r;
   };
@@ -515,19 +504,6 @@ bool tfm_rows_fits(int dtype, int c, int head_dim, int lk, long long tokens) {
   return dtype == AD_BF16 ? head_dim == 64 : (head_dim == 16 || head_dim == 32 || head_dim == 64);
 }
 
-// Wider rows, up to kTextMaxBytes: not the whole list, whose 15 C^2 weights a workgroup would wait for, but the steps around the text (output projection,
-// LayerNorm, query, attention to the text, its output projection: 3 C^2 weights), four launches that wait for one another.  15.3 us at 72 and at 128 tokens of 256 bf16
-// channels, for 3.9 + 4.4 + 4.3 + 3.9 and three gaps; 288 of 128 fp32 channels 15.5 for 3.8 + 4.4 + 5.8 + 3.8.  Whole runs, ms (separate launches -> this): narrow 35.9 ->
-// 35.6, with stride 2 25.5 -> 24.5; the same models at 48x48 20.0 -> 19.0 and 11.9 -> 11.1, 64x64 24.3 -> 23.0 and 12.7 -> 11.9, 128x128 (up to 2048 tokens) 29.1 -> 28.7 and
-// 12.2 -> 11.5, 16 frames of 32x32 16.3 -> 15.3; fp32 24x24 17.0 -> 16.9, 64x64 (2048 tokens) 19.6 -> 19.4, 96x96 (4608) 44.7 -> 44.9.
-constexpr long long kTextTokens = 2048;
-bool tfm_text_fits(int dtype, int c, int head_dim, int lk, long long tokens) {
-  if (dtype != AD_BF16 && dtype != AD_F32) return false;
-  if ((long long)(lk + 64) * c * (int)esize(dtype) >= 1LL << 31) return false;
-  if (c * (int)esize(dtype) > kTextMaxBytes || c % bk_elems(dtype) || c % head_dim || tokens > kTextTokens || tfm_rows_fits(dtype, c, head_dim, lk, tokens)) return false;
-  return dtype == AD_BF16 ? head_dim == 64 : (head_dim == 16 || head_dim == 32 || head_dim == 64);
-}
-
 template <typename T, int TM, int DT>
 static ad_status run_tfm_rows(const RowParams& p, int grid, int lds_bytes, hipStream_t s) {
   static std::atomic<bool> attr_set{false};
@@ -541,13 +517,11 @@ static ad_status run_tfm_rows(const RowParams& p, int grid, int lds_bytes, hipSt
 }
 
 ad_status launch_tfm_rows(const TfmRows& a, hipStream_t s) {
-  const long long tokens = (long long)a.batch * a.l;
-  const bool text_only = a.w_o && !a.w_ff1;                  // the steps around the text alone
-  if (a.batch < 1 || a.l < 1 || !a.in || !(text_only ? tfm_text_fits(a.dtype, a.c, a.head_dim, a.lk, tokens) : tfm_rows_fits(a.dtype, a.c, a.head_dim, a.lk, tokens))) AD_FAIL(AD_ERR_INVALID, "tfm_rows: unsupported shape");
+  if (a.batch < 1 || a.l < 1 || !a.in || !tfm_rows_fits(a.dtype, a.c, a.head_dim, a.lk, (long long)a.batch * a.l)) AD_FAIL(AD_ERR_INVALID, "tfm_rows: unsupported shape");
   if ((a.w_in != nullptr) == (a.w_o != nullptr)) AD_FAIL(AD_ERR_INVALID, "tfm_rows: either the input projection or the layer behind an attention");
   const int c = a.c, es = (int)esize(a.dtype);
-  const RowPlan plan = plan_rows(a.dtype, c, a.head_dim, a.batch, a.l, a.w_o ? a.lk : 1, text_only ? c : 4 * c);
-  const int r = 16 * plan.tm, pitch = c * es + 16, gpitch = (text_only ? c : 4 * c) * es + 16;
+  const RowPlan plan = plan_rows(a.dtype, c, a.head_dim, a.batch, a.l, a.w_o ? a.lk : 1);
+  const int r = 16 * plan.tm, pitch = c * es + 16, gpitch = 4 * c * es + 16;
   const int lds_a = 0, lds_h = r * pitch, lds_x = 2 * r * pitch, lds_g = 3 * r * pitch;
   RowParams p = {};
   p.lds_part = plan.part;
@@ -596,12 +570,9 @@ ad_status launch_tfm_rows(const TfmRows& a, hipStream_t s) {
     q.flags |= ROW_TEXT;
     flops += 4.0 * a.batch * a.l * a.lk * c;
     gemm(lds_a, a.w_o2, a.b_o2, c, c, lds_h, lds_h);
-    if (!text_only) {
-      with_norm(gemm(lds_a, a.w_ff1, a.b_ff1, 8 * c, c, lds_g, -1, ROW_GEGLU), lds_h, a.ln3_g, a.ln3_b);
-      gemm(lds_g, a.w_ff2, a.b_ff2, c, 4 * c, lds_h, lds_h);
-    }
+    with_norm(gemm(lds_a, a.w_ff1, a.b_ff1, 8 * c, c, lds_g, -1, ROW_GEGLU), lds_h, a.ln3_g, a.ln3_b);
+    gemm(lds_g, a.w_ff2, a.b_ff2, c, 4 * c, lds_h, lds_h);
   }
-  if (text_only && (a.w_out || a.w_qkv)) AD_FAIL(AD_ERR_INVALID, "tfm_rows: nothing behind the steps around the text");
   if (a.w_out) {
     if (!a.x || !a.z) AD_FAIL(AD_ERR_INVALID, "tfm_rows: null pointer");
     p.x = a.x;
@@ -624,7 +595,7 @@ ad_status launch_tfm_rows(const TfmRows& a, hipStream_t s) {
   p.div_per = make_fastdiv((unsigned)(c * es / 16));
   const int lds_bytes = plan.bytes, grid = a.batch * p.tiles;
   if (p.n_ops >= kRowOps || p.n_vecs >= kRowVecs || lds_bytes > 160 * 1024) AD_FAIL(AD_ERR_INVALID, "tfm_rows: does not fit");
-  ProfLaunch pl(a.dtype == AD_BF16 ? "tfm_rows_bf16" : "tfm_rows_f32", flops, 0, s, a.batch * a.l, c, text_only ? 3 * c : a.w_o ? 15 * c : 4 * c);
+  ProfLaunch pl(a.dtype == AD_BF16 ? "tfm_rows_bf16" : "tfm_rows_f32", flops, 0, s, a.batch * a.l, c, a.w_o ? 15 * c : 4 * c);
 #define AD_ROWS(T_, DT_) return plan.tm == 2 ? run_tfm_rows<T_, 2, DT_>(p, grid, lds_bytes, s) : run_tfm_rows<T_, 1, DT_>(p, grid, lds_bytes, s)
   if (a.dtype == AD_BF16) AD_ROWS(bf16, 4);
   if (a.head_dim == 16) AD_ROWS(float, 1);

@@ -237,13 +237,15 @@ struct Eval {
     AD_TRY(linear(temp(0), M, Cc, w + 2, w + 3, nullptr, temp(1), OUT_ROWMAJOR, 1, 0, {ui, w + 6}));
     w += 4;
     void* h = temp(1);
-    const bool text_rows = tfm_text_fits(dt, Cc, d, Lk, (long long)B * L);
     for (int k = 0; k < f.depth; ++k, w += 20) {
       // ln1.g ln1.b a1.q a1.k a1.v a1.o.w a1.o.b ln2.g ln2.b a2.q a2.k a2.v a2.o.w a2.o.b ln3.g ln3.b ff1.w ff1.b ff2.w ff2.b
       // q, k, v of the self-attention in one GEMM; v lands transposed when the MFMA attention kernel follows
       AD_TRY(ln_linear(h, M, Cc, w + 0, ConvArgs{dt, nullptr, nullptr, Cc, 0, B, L, 1, 0, 1, 1, wv.at(w + 2), 3 * Cc, nullptr, nullptr, 0, nullptr, temp(2), OUT_QKV,
                                                         vt ? lp : 0, temp(9), ws.temp_bytes[9], temp(3), temp(4)}, {ui, w + 5}));
       AD_TRY(launch_attention(dt, temp(2), temp(3), temp(4), vt, B, L, L, Cc, d, Cc, Cc, vt ? lp : Cc, Cc, temp(5), s));
+      AD_TRY(linear(temp(5), M, Cc, w + 5, w + 6, h, h, OUT_ROWMAJOR, 1, 0, {ui, w + 9}));
+      AD_TRY(ln_linear(h, M, Cc, w + 7, ConvArgs{dt, nullptr, nullptr, Cc, 0, 1, M, 1, 0, 1, 1, wv.at(w + 9), Cc, nullptr, nullptr, 0, nullptr, temp(2), OUT_ROWMAJOR,
+                                                        0, temp(9), ws.temp_bytes[9]}, {ui, w + 12}));
       // keys / values of the text: taken from the per-run cache when it was built from this embedding
       const void* tk = temp(7);
       const void* tv = temp(8);
@@ -253,23 +255,10 @@ struct Eval {
       } else {
         AD_TRY(text_kv(w, temp(7), temp(8)));
       }
-      if (text_rows) {       // narrow models: from here to the text's output projection a token at a time, in one launch
-        TfmRows a{dt, B, L, Cc, d, c.cfg.ln_eps, temp(5), h};
-        a.text_k = tk; a.text_v = tv; a.lk = Lk; a.text_ldv = lkp; a.text_shared = c.cfg.frames > 0;
-        a.w_o = wv.at(w + 5); a.b_o = wv.f32(w + 6);
-        a.ln2_g = wv.f32(w + 7); a.ln2_b = wv.f32(w + 8);
-        a.w_q2 = wv.at(w + 9);
-        a.w_o2 = wv.at(w + 12); a.b_o2 = wv.f32(w + 13);
-        AD_TRY(launch_tfm_rows(a, s));
-      } else {
-        AD_TRY(linear(temp(5), M, Cc, w + 5, w + 6, h, h, OUT_ROWMAJOR, 1, 0, {ui, w + 9}));
-        AD_TRY(ln_linear(h, M, Cc, w + 7, ConvArgs{dt, nullptr, nullptr, Cc, 0, 1, M, 1, 0, 1, 1, wv.at(w + 9), Cc, nullptr, nullptr, 0, nullptr, temp(2), OUT_ROWMAJOR,
-                                                          0, temp(9), ws.temp_bytes[9]}, {ui, w + 12}));
-        // video: every frame attends to the one text embedding, so the frames' tokens form one long query sequence
-        if (c.cfg.frames > 0) AD_TRY(launch_attention(dt, temp(2), tk, tv, vt, 1, M, Lk, Cc, d, Cc, Cc, vt ? lkp : Cc, Cc, temp(5), s));
-        else AD_TRY(launch_attention(dt, temp(2), tk, tv, vt, B, L, Lk, Cc, d, Cc, Cc, vt ? lkp : Cc, Cc, temp(5), s));
-        AD_TRY(linear(temp(5), M, Cc, w + 12, w + 13, h, h, OUT_ROWMAJOR, 1, 0, {ui, w + 16}));
-      }
+      // video: every frame attends to the one text embedding, so the frames' tokens form one long query sequence
+      if (c.cfg.frames > 0) AD_TRY(launch_attention(dt, temp(2), tk, tv, vt, 1, M, Lk, Cc, d, Cc, Cc, vt ? lkp : Cc, Cc, temp(5), s));
+      else AD_TRY(launch_attention(dt, temp(2), tk, tv, vt, B, L, Lk, Cc, d, Cc, Cc, vt ? lkp : Cc, Cc, temp(5), s));
+      AD_TRY(linear(temp(5), M, Cc, w + 12, w + 13, h, h, OUT_ROWMAJOR, 1, 0, {ui, w + 16}));
       AD_TRY(ln_linear(h, M, Cc, w + 14, ConvArgs{dt, nullptr, nullptr, Cc, 0, 1, M, 1, 0, 1, 1, wv.at(w + 16), 8 * Cc, wv.f32(w + 17), nullptr, 0, nullptr, temp(6),
                                                          OUT_GEGLU, 0, temp(9), ws.temp_bytes[9]}, {ui, w + 18}));
       AD_TRY(linear(temp(6), M, 4 * Cc, w + 18, w + 19, h, h, OUT_ROWMAJOR, 1, 0, {ui, k + 1 < f.depth ? w + 22 : w + 20}));

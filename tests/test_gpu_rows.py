@@ -46,38 +46,6 @@ def test_transformer_of_a_narrow_model_matches_oracle(monkeypatch, dtype, c, hea
         case.m.precompute_text(case.d_text, torch.cuda.current_stream())
 
 
-@pytest.mark.parametrize("dtype,c,head_dim,depth,height,width,batch,ctx_len,frames", [
-    (BF, 256, 64, 1, 3, 3, 2, 77, 0), (BF, 256, 64, 2, 6, 6, 2, 77, 0), (BF, 256, 64, 1, 1, 17, 1, 1, 0), (BF, 192, 64, 2, 5, 7, 2, 154, 0), (BF, 256, 64, 1, 4, 4, 3, 33, 3),
-    (BF, 256, 64, 1, 32, 32, 2, 77, 0), (F32, 128, 64, 1, 12, 12, 2, 77, 0), (F32, 128, 32, 2, 3, 5, 2, 17, 0), (F32, 96, 16, 1, 7, 7, 1, 120, 0), (F32, 128, 64, 1, 5, 5, 5, 16, 5)])
-def test_steps_around_the_text_match_oracle(monkeypatch, dtype, c, head_dim, depth, height, width, batch, ctx_len, frames):
-    """Wider rows, where these steps alone run in one launch."""
-    names = profile_names(monkeypatch)
-    test_transformer_of_a_narrow_model_matches_oracle(monkeypatch, dtype, c, head_dim, depth, height, width, batch, ctx_len, frames)
-    assert sum("tfm_rows" in n for n in names) == 2 * depth, names       # two evaluations
-
-
-@pytest.mark.parametrize("dtype,c,height,width", [(BF, 256, 32, 33), (F32, 128, 32, 33), (BF, 320, 5, 5), (F32, 160, 5, 5)])
-def test_beyond_the_steps_around_the_text(monkeypatch, dtype, c, height, width):
-    """More than 2048 tokens, or rows of more than 512 bytes: the separate launches."""
-    names = profile_names(monkeypatch)
-    test_transformer_of_a_narrow_model_matches_oracle(monkeypatch, dtype, c, 64 if dtype == BF else 32, 1, height, width, 2, 77, 0)
-    assert not any("tfm_rows" in n for n in names), names
-
-
-def profile_names(monkeypatch):
-    """Names of the launches of every component_forward from here on."""
-    names = []
-    forward = B.AsyncDiff.component_forward
-
-    def profiled(self, *args, **more):
-        self.profile(True)
-        forward(self, *args, **more)
-        names.extend(r[0] for r in self.profile_records())
-
-    monkeypatch.setattr(B.AsyncDiff, "component_forward", profiled)
-    return names
-
-
 @pytest.mark.parametrize("dtype,c,frames,height,width,by_rows", [(BF, 128, 16, 32, 32, True), (BF, 128, 15, 33, 34, False), (BF, 64, 15, 33, 34, True), (F32, 64, 15, 33, 34, True)])
 def test_transformer_of_many_tokens(monkeypatch, dtype, c, frames, height, width, by_rows):
     """Beyond 16384 tokens 128 bf16 channels go through the separate launches (their weights are packed for those): which way is taken, and the result."""
