@@ -976,7 +976,7 @@ static ad_status run_igemm_p3(const IgemmParams& p0, const char* name, hipStream
 // Whole runs, ms: tiny fp32 2.30 -> 1.73, narrow 36.9 -> 35.7, with stride 2 26.2 -> 25.4, narrow fp32 17.13 -> 17.04.
 // Taken back: statistics over all wavefronts through LDS, merged in double (4.3 us a launch), and 1x1 convolutions (72x256x256 3.7 + 3.9 -> 7.9).
 // =================================================================================================
-constexpr int small_ktiles(int bm, int bn) { return 200 * 1024 / ((bm + bn) * kRowBytes); }      // k-tiles that small_tile() takes at the most
+constexpr int small_ktiles(int bm, int bn) { return 200 * 1024 / ((bm + bn) * kRowBytes); }      // k-tiles that small_tile() takes at the most (bf16), and of a LayerNorm in front
 // Sum over the threads of a row, TPR = 16 or 32 neighbouring lanes, as k_layernorm's lanes add up: distances 32 / TPR .. 1, where a distance within 16 lanes is a
 // rotation, since the lanes that it brings together hold the same already.
 template <int TPR>
@@ -1811,13 +1811,19 @@ static int best_band(long long m, int n, const DmaTile& t, int splits) {
 // Tile of k_igemm_small (16-row and 16-column units), or {0, 0} where another kernel is the better choice: the smallest tile that
 // makes at most a workgroup per CU, as long as a workgroup takes in at most 200 KiB (beyond that the 60 GB/s a CU gets from memory
 // decide, and K split over workgroups wins: 3x3 72x192x5760 13 us against 11).  GEGLU pairs 32 value with 32 gate columns.
+// fp32: at most 600 KiB, since what is left to split K over workgroups are register-staged tiles of 64 or 128 rows on matrix cores of a sixteenth of the rate, which
+// multiply mostly padding.  3x3, us (those and their second pass / this): 18x256x2304 27.1 / 10.1, 72x256x2304 27.6 / 11.4, 18x256x4608 29.5 / 16.6, 288x256x2304 28.2 / 15.6,
+// 512x128x3456 30.4 / 15.4, 1152x128x3456 21.8 / 21.4; linear: 180x1280x1280 18.8 / 14.6.  1200 KiB: 288x256x4608 31.3 / 26.6, but 1152x128x3456
+// in tiles of 32x32 21.8 / 27.4.
+constexpr int kSmallF32 = 600 * 1024;
 struct SmallTile { int tm, tn; };
-static SmallTile small_tile(long long m, int n, int ktiles, int out_mode) {
+static SmallTile small_tile(int dtype, long long m, int n, int ktiles, int out_mode) {
   const SmallTile plain[] = {{1, 1}, {1, 2}, {2, 2}}, geglu[] = {{1, 4}, {2, 4}};
   for (int i = 0; i < (out_mode == OUT_GEGLU ? 2 : 3); ++i) {
     const SmallTile t = out_mode == OUT_GEGLU ? geglu[i] : plain[i];
     const long long wgs = ((m + 16 * t.tm - 1) / (16 * t.tm)) * ((n + 16 * t.tn - 1) / (16 * t.tn));
-    if (wgs <= 256 && ktiles <= small_ktiles(16 * t.tm, 16 * t.tn)) return t;
+    const int most = dtype == AD_F32 ? kSmallF32 / ((16 * t.tm + 16 * t.tn) * kRowBytes) : small_ktiles(16 * t.tm, 16 * t.tn);
+    if (wgs <= 256 && ktiles <= most) return t;
   }
   return SmallTile{0, 0};
 }
@@ -1845,7 +1851,7 @@ static ConvPlan compute_plan(int dtype, long long m, int n, int ktiles, int out_
   }
   else if (forced != TILE_AUTO && geglu) forced = TILE_AUTO;
   if (forced == TILE_128x128 || forced == TILE_64x64) return ConvPlan{forced, splits_by_tiles(m, n, ktiles, out_mode, forced == TILE_64x64 ? 64 : 128), -1};
-  if (forced == TILE_AUTO && small_tile(m, n, ktiles, out_mode).tm) return ConvPlan{TILE_SMALL, 1, -1};
+  if (forced == TILE_AUTO && small_tile(dtype, m, n, ktiles, out_mode).tm) return ConvPlan{TILE_SMALL, 1, -1};
   if (!dma) {
     // measured on the GEMM shapes of the SD-sized models: 128x128 register-staged tiles pay off once there is
     // more than one of them per CU, or with very few rows and a long K (the weights are re-read less often)
@@ -1909,7 +1915,9 @@ bool conv_takes_shortcut(int dtype, long long m, int n, int c, int xc) {
 // Wherever the layer is a small-tile launch: every shape measured (above the kernel, 18 to 288 rows, 128 to 1280 channels) gains 1.5 to 2.4 us.
 bool conv_takes_ln(int dtype, long long m, int n, int c, int out_mode) {
   const int bk = bk_elems(dtype);
-  return c % bk == 0 && (out_mode == OUT_ROWMAJOR || out_mode == OUT_QKV || out_mode == OUT_GEGLU) && choose_plan(dtype, m, n, c / bk, out_mode).tile == TILE_SMALL;
+  if (c % bk || (out_mode != OUT_ROWMAJOR && out_mode != OUT_QKV && out_mode != OUT_GEGLU) || choose_plan(dtype, m, n, c / bk, out_mode).tile != TILE_SMALL) return false;
+  const SmallTile t = small_tile(dtype, m, n, c / bk, out_mode);
+  return c / bk <= small_ktiles(16 * t.tm, 16 * t.tn);
 }
 
 // A small-tile launch whose threads hold at most 40 elements each: what a workgroup does for the norm grows with the samples it takes in, the launch that it
@@ -1922,7 +1930,7 @@ bool conv_takes_gn(int dtype, int batch, int h, int w, int c0, int c1, int n, in
   if (c % (8 * vn) || (vps & (vps - 1)) || vps > 16 || (cpg & (cpg - 1)) || cpg > 4 * vn) return false;
   const long long m = (long long)batch * hw;
   if (choose_plan(dtype, m, n, 9 * c / bk, out_mode).tile != TILE_SMALL) return false;
-  const SmallTile t = small_tile(m, n, 9 * c / bk, out_mode);
+  const SmallTile t = small_tile(dtype, m, n, 9 * c / bk, out_mode);
   const int bm = 16 * t.tm;
   return (long long)gn_samples(bm, batch, hw) * hw <= gn_hold(vn) * (64 / vps) &&
          8 * bm * (16 * t.tn + 4) * 4 + gn_act_bytes(bm, w, c * es) <= (int)kLdsLimit;
@@ -2081,7 +2089,7 @@ ad_status launch_conv(const ConvArgs& a, hipStream_t s) {
     }
 #undef AD_P3W
   } else if (tile == TILE_SMALL) {
-    const SmallTile t = small_tile(m, a.n_out, p.ktiles, a.out_mode);
+    const SmallTile t = small_tile(a.dtype, m, a.n_out, p.ktiles, a.out_mode);
     name = h16 ? "igemm_bf16_small" : "igemm_f32_small";
 #define AD_SMALL(TM_, TN_, MODE_) st = h16 ? run_igemm_small<bf16, TM_, TN_, MODE_>(p, name, s) : run_igemm_small<float, TM_, TN_, MODE_>(p, name, s)
 #define AD_SMALL_MODE(MODE_)                                  \

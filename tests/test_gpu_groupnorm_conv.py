@@ -42,7 +42,7 @@ SHAPES = [  # dtype, channels, height, width, batch, groups, in one launch
     (B.AD_BF16, 256, 3, 3, 2, 32, True), (B.AD_BF16, 256, 6, 6, 2, 32, True), (B.AD_BF16, 128, 12, 12, 2, 32, True), (B.AD_BF16, 64, 10, 14, 1, 32, True),
     (B.AD_BF16, 64, 16, 20, 1, 8, True), (B.AD_BF16, 64, 17, 19, 1, 8, False), (B.AD_BF16, 512, 2, 4, 2, 16, False), (B.AD_BF16, 128, 1, 1, 1, 8, True),
     (B.AD_BF16, 192, 6, 6, 2, 32, False), (B.AD_BF16, 128, 5, 7, 2, 64, True), (B.AD_BF16, 64, 24, 24, 2, 32, False),
-    (B.AD_F32, 32, 16, 16, 1, 8, True), (B.AD_F32, 64, 12, 12, 2, 32, True), (B.AD_F32, 128, 12, 12, 2, 32, True), (B.AD_F32, 256, 6, 6, 2, 32, False),
+    (B.AD_F32, 32, 16, 16, 1, 8, True), (B.AD_F32, 64, 12, 12, 2, 32, True), (B.AD_F32, 128, 12, 12, 2, 32, True), (B.AD_F32, 256, 6, 6, 2, 32, True), (B.AD_F32, 512, 3, 3, 1, 32, True), (B.AD_F32, 1024, 2, 2, 1, 64, False),
     (B.AD_F32, 128, 5, 7, 1, 64, True), (B.AD_F32, 32, 3, 7, 2, 8, True), (B.AD_F32, 96, 6, 6, 1, 8, False)]
 
 

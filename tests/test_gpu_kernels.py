@@ -820,3 +820,19 @@ def test_attention_over_frames(dtype, frames, positions, c, heads):
     got = host(out)
     assert np.isnan(got[:, c:]).all()                        # nothing written past the row
     assert_kernel_close(got[:, :c], ref, dtype)
+
+
+@pytest.mark.parametrize("rows,n_out,k,small", [
+    (45, 64, 4800, True), (45, 64, 4832, False),          # tiles of 16x16: 150 k-tiles of 32 at the most
+    (288, 256, 3200, True), (288, 256, 3232, False),      # 16x32: 100
+    (512, 320, 2400, True), (512, 320, 2432, False),      # 32x32: 75
+    (18, 260, 2304, True)])
+def test_fp32_long_k_in_small_tiles(rows, n_out, k, small):
+    """fp32 layers of few rows and a long K: small tiles up to 600 KiB a workgroup, K shared out over workgroups (which needs scratch) beyond."""
+    x = SI.make_array((1, k, rows, 1), 321)
+    w = SI.make_array((n_out, k, 1, 1), 322, k ** -0.5)
+    bias, res = SI.make_array((n_out,), 323, 0.1), SI.make_array((1, rows, 1, n_out), 324)
+    ref = P.conv2d(x, w, bias)
+    got, _ = run_conv(B.AD_F32, x, None, w, bias, residual=res, splitk=True)
+    assert (run_conv.last_ws_bytes == 0) == small
+    assert_kernel_close(nhwc_to_nchw(got), ref + nhwc_to_nchw(res), B.AD_F32)
