@@ -68,8 +68,9 @@ size_t conv_workspace_bytes(int dtype, long long m, int n, int k, int out_mode);
 bool conv_takes_shortcut(int dtype, long long m, int n, int c, int xc);      // c, xc: channels of the 3x3 and of the 1x1 convolution
 // whether a LayerNorm over c channels goes into the launch of the linear layer behind it
 bool conv_takes_ln(int dtype, long long m, int n, int c, int out_mode);
-// whether a GroupNorm over the c0 + c1 channels goes into the launch of the 3x3 convolution behind it (stride 1; out must not overlap the sources)
-bool conv_takes_gn(int dtype, int batch, int h, int w, int c0, int c1, int n, int groups, int out_mode);
+// whether a GroupNorm over the c0 + c1 channels goes into the launch of the 3x3 convolution behind it (stride 1; out must not overlap the sources; xc: channels of the shortcut that
+// goes into the same launch)
+bool conv_takes_gn(int dtype, int batch, int h, int w, int c0, int c1, int n, int groups, int out_mode, int xc = 0);
 
 ad_status launch_groupnorm(int dtype, const void* src0, const void* src1, int c0, int c1, int batch, int hw, int groups,
                            const float* gamma, const float* beta, float eps, int silu, void* out, void* scratch,

@@ -974,6 +974,10 @@ static ad_status run_igemm_p3(const IgemmParams& p0, const char* name, hipStream
 // Measured inside the models, us (norm + convolution -> convolution): bf16 18x256x2304 3.7 + 6.7 -> 8.2, 72x256x2304 3.7 + 7.1 -> 8.5, 128x256x2304 3.7 + 7.2 -> 7.8,
 // 288x128x1152 3.7 + 5.5 -> 7.3; fp32 64x64x576 3.4 + 5.5 -> 6.1, 256x32x288 3.6 + 4.8 -> 6.7; and the gap between two launches.
 // Whole runs, ms: tiny fp32 2.30 -> 1.73, narrow 36.9 -> 35.7, with stride 2 26.2 -> 25.4, narrow fp32 17.13 -> 17.04.
+// XTRA: the 1x1 shortcut of a ResBlock as k-tiles behind the taps, as in k_igemm_p3: a launch of 3.7 to 4.3 us for 0.7 to 2 us. fp32 too. us (shortcut + second convolution ->
+// one): bf16 18x256 of 2304 + 512 4.2 + 8.1 -> 9.6, 72x256 4.2 + 7.7 -> 9.8, 288x128 of 1152 + 256 4.0 + 6.9 -> 7.6; fp32 256x32 of 288 + 96 3.7 + 6.7 -> 7.4, 18x256 of 2304 + 512
+// 4.8 + 10.2 -> 12.1. Launches of a step: tiny fp32 34 -> 29, narrow 204 -> 190, narrow fp32 223 -> 213. Whole runs, ms: tiny 1.89 -> 1.74, narrow 35.8 -> 34.0, with stride 2
+// 25.5 -> 24.7, narrow fp32 12.10 -> 11.84.
 // Taken back: statistics over all wavefronts through LDS, merged in double (4.3 us a launch), and 1x1 convolutions (72x256x256 3.7 + 3.9 -> 7.9).
 // =================================================================================================
 constexpr int small_ktiles(int bm, int bn) { return 200 * 1024 / ((bm + bn) * kRowBytes); }      // k-tiles that small_tile() takes at the most (bf16), and of a LayerNorm in front
@@ -1128,7 +1132,7 @@ __device__ __forceinline__ void gn_stage(const IgemmParams& p, const typename Ve
 
 enum { NORM_NONE = 0, NORM_LAYER = 1, NORM_GROUP = 2 };
 constexpr int gn_hold(int vn) { return 40 / vn; }        // GN: accesses of vn elements that a thread holds at the most
-template <typename T, int TM, int TN, int MODE, int NORM = NORM_NONE>
+template <typename T, int TM, int TN, int MODE, int NORM = NORM_NONE, bool XTRA = false>
 __global__ __launch_bounds__(512) void k_igemm_small(IgemmParams p) {
   constexpr bool LN = NORM == NORM_LAYER, GN = NORM == NORM_GROUP;
   typedef typename Vec<T>::type V;
@@ -1174,7 +1178,7 @@ __global__ __launch_bounds__(512) void k_igemm_small(IgemmParams p) {
   const __amdgpu_buffer_rsrc_t rs1 = make_rsrc(p.src1, p.bytes1);
   const __amdgpu_buffer_rsrc_t rsw = make_rsrc(p.w, p.bytes_w);
 
-  const int mine = (p.ktiles - wave + NW - 1) / NW;      // k-tiles of this wavefront (0 when there are fewer k-tiles than wavefronts)
+  const int kt_taps = XTRA ? p.kt_main : p.ktiles, mine = (kt_taps - wave + NW - 1) / NW;      // k-tiles of this wavefront (0 when there are fewer k-tiles than wavefronts)
   int f_tap = wave * BK / p.ctot, f_cc = wave * BK - f_tap * p.ctot;
   unsigned f_w = (unsigned)wave * p.w_kt;
   V af[GN ? 1 : PF][TM][2], bf[PF][TN][2];
@@ -1245,6 +1249,30 @@ __global__ __launch_bounds__(512) void k_igemm_small(IgemmParams p) {
 #pragma unroll
   for (int s = 0; s < PF; ++s)
     if (s < mine) fetch(s);
+
+  // XTRA: behind the taps the k-tiles of a 1x1 convolution of other sources, taken in turn as well; a wavefront's first one is asked for ahead of the loop
+  V xa[XTRA ? TM : 1][2], xb[XTRA ? TN : 1][2];
+  const int x_tiles = p.ktiles - kt_taps, x_first = (wave + NW - kt_taps % NW) % NW;
+  auto fetch_extra = [&](int e) {
+    const int xk = p.xc0 + p.xc1, cc = e * BK;
+    const bool second = cc >= p.xc0;
+    const __amdgpu_buffer_rsrc_t rx = second ? make_rsrc(p.x1, p.xbytes1) : make_rsrc(p.x0, p.xbytes0), rw = make_rsrc(p.xw, p.xbytes_w);
+    const unsigned row = (unsigned)(second ? p.xc1 : p.xc0) * ES, sc = (unsigned)(second ? cc - p.xc0 : cc) * ES;
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+        xb[j][h] = buffer_load16<V>(rw, weight_at(n0 + 16 * j + r16, (unsigned)xk * ES, p.xw_row) + kg * 16 + h * 64, (unsigned)e * p.w_kt);
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+      const int m = m0 + 16 * i + r16;
+      const unsigned o = m < p.M ? (unsigned)m * row + kg * 16 : kOob;
+#pragma unroll
+      for (int h = 0; h < 2; ++h) xa[i][h] = buffer_load16<V>(rx, o + h * 64, sc);
+    }
+  };
+  if constexpr (XTRA)
+    if (x_first < x_tiles) fetch_extra(x_first);
 
   // what the epilogue adds.  A thread of it finishes four consecutive columns of a row, or, for transposed outputs, four
   // consecutive rows of a column
@@ -1336,6 +1364,16 @@ __global__ __launch_bounds__(512) void k_igemm_small(IgemmParams p) {
       if (i0 + s + PF < mine) fetch(s);
     }
   }
+  if constexpr (XTRA)
+    for (int e = x_first; e < x_tiles; e += NW) {
+      if (e > x_first) fetch_extra(e);
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+          for (int j = 0; j < TN; ++j) Mma16<T>::run(xb[j][h], xa[i][h], acc[i][j]);
+    }
   // lane: row r16 of row tile i, columns 4 kg .. 4 kg + 3 of column tile j
 #pragma unroll
   for (int i = 0; i < TM; ++i)
@@ -1405,13 +1443,15 @@ __global__ __launch_bounds__(512) void k_igemm_small(IgemmParams p) {
 
 // samples that the rows of a tile belong to at the most
 static int gn_samples(int bm, int batch, int hw) { return std::min(batch, hw % bm == 0 ? 1 : (bm - 2) / hw + 2); }
-template <typename T, int TM, int TN, int MODE, int NORM = NORM_NONE>
+template <typename T, int TM, int TN, int MODE, int NORM = NORM_NONE, bool XTRA = false>
 static ad_status run_igemm_small(const IgemmParams& p0, const char* name, hipStream_t s) {
   constexpr bool LN = NORM == NORM_LAYER;
+  if constexpr (!XTRA && MODE == OUT_ROWMAJOR && !LN)
+    if (p0.xw) return run_igemm_small<T, TM, TN, MODE, NORM, true>(p0, name, s);
   if constexpr (NORM == NORM_NONE && (MODE == OUT_ROWMAJOR || MODE == OUT_TRANSPOSED_F32))
-    if (p0.gn_groups) return run_igemm_small<T, TM, TN, MODE, NORM_GROUP>(p0, name, s);
-  if constexpr (NORM == NORM_NONE && (MODE == OUT_ROWMAJOR || MODE == OUT_QKV || MODE == OUT_GEGLU))
-    if (p0.ln_gain) return run_igemm_small<T, TM, TN, MODE, NORM_LAYER>(p0, name, s);
+    if (p0.gn_groups) return run_igemm_small<T, TM, TN, MODE, NORM_GROUP, XTRA>(p0, name, s);
+  if constexpr (NORM == NORM_NONE && !XTRA && (MODE == OUT_ROWMAJOR || MODE == OUT_QKV || MODE == OUT_GEGLU))
+    if (p0.ln_gain && !p0.gn_groups) return run_igemm_small<T, TM, TN, MODE, NORM_LAYER>(p0, name, s);
   IgemmParams p = p0;
   set_tiles(p, 16 * TM, 16 * TN);
   constexpr int lds_sums = 8 * 16 * TM * (16 * TN + 4) * 4;
@@ -1420,14 +1460,15 @@ static ad_status run_igemm_small(const IgemmParams& p0, const char* name, hipStr
   if constexpr (lds_most > 65536) {
     static std::atomic<bool> attr_set{false};
     if (!attr_set) {
-      AD_HIP(hipFuncSetAttribute((const void*)k_igemm_small<T, TM, TN, MODE, NORM>, hipFuncAttributeMaxDynamicSharedMemorySize, lds_most));
+      AD_HIP(hipFuncSetAttribute((const void*)k_igemm_small<T, TM, TN, MODE, NORM, XTRA>, hipFuncAttributeMaxDynamicSharedMemorySize, lds_most));
       attr_set = true;
     }
   }
   const double in_bytes = (double)p.M * p.ctot * sizeof(T) * (p.stride == 2 ? 4 : 1) / (p.up ? 4 : 1);
   const double out_cols = p.out_mode == OUT_GEGLU ? p.N / 2 : p.N;
-  ProfLaunch pl(name, 2.0 * p.M * p.N * p.k_prof, in_bytes + (double)p.N * p.Kp * sizeof(T) + (double)p.M * out_cols * sizeof(T), s, p.M, p.N, p.Kp);
-  hipLaunchKernelGGL((k_igemm_small<T, TM, TN, MODE, NORM>), dim3(p.tiles_n * p.tiles_m), dim3(512), lds_bytes, s, p);
+  const int xk = p.xc0 + p.xc1;
+  ProfLaunch pl(name, 2.0 * p.M * p.N * (p.k_prof + xk), in_bytes + ((double)p.N * (p.Kp + xk) + (double)p.M * xk) * sizeof(T) + (double)p.M * out_cols * sizeof(T), s, p.M, p.N, p.Kp + xk);
+  hipLaunchKernelGGL((k_igemm_small<T, TM, TN, MODE, NORM, XTRA>), dim3(p.tiles_n * p.tiles_m), dim3(512), lds_bytes, s, p);
   AD_HIP(hipGetLastError());
   return AD_OK;
 }
@@ -1899,14 +1940,16 @@ size_t conv_workspace_bytes(int dtype, long long m, int n, int k, int out_mode) 
   return splits > 1 ? (size_t)splits * m * n * 4 : 0;
 }
 
-// A 1x1 convolution of the block's input (the shortcut) added to the 3x3 one: as further k-tiles of the same launch on the LDS-DMA kernels, a
+// A 1x1 convolution of the block's input (the shortcut) added to the 3x3 one: as further k-tiles of the same launch on the LDS-DMA and the small-tile kernels, a
 // launch of its own, whose sum goes through memory as the residual, on the others.  Saves a launch of 7 to 25 us per such block (14 of 22
-// blocks of the SD-sized models) for as many k-tiles at the rate of a long launch: whole runs at 576x320 px 67.5 -> 66.2 ms, 512px 191.4 -> 188.3,
+// blocks of the SD-sized models) for as many k-tiles at the rate of a long launch (figures of the small tiles at k_igemm_small): whole runs at 576x320 px 67.5 -> 66.2 ms, 512px 191.4 -> 188.3,
 // 768px 299.1 -> 297.5, 1024px level.
 bool conv_takes_shortcut(int dtype, long long m, int n, int c, int xc) {
-  if (dtype != AD_BF16 || c % bk_elems(dtype) || xc % bk_elems(dtype)) return false;
-  switch (choose_plan(dtype, m, n, (9 * c + xc) / bk_elems(dtype), OUT_ROWMAJOR).tile) {
-    case TILE_P3_64: case TILE_K2_64: case TILE_D2_128: case TILE_D2_160: case TILE_D2_320: return true;
+  if (c % bk_elems(dtype) || xc % bk_elems(dtype)) return false;
+  const int tile = choose_plan(dtype, m, n, (9 * c + xc) / bk_elems(dtype), OUT_ROWMAJOR).tile;
+  if (dtype != AD_BF16) return tile == TILE_SMALL;
+  switch (tile) {
+    case TILE_SMALL: case TILE_P3_64: case TILE_K2_64: case TILE_D2_128: case TILE_D2_160: case TILE_D2_320: return true;
     case TILE_P3_128: case TILE_P3_256: return g_tile_override == TILE_AUTO || g_tile_override == TILE_P3_128 || g_tile_override == TILE_P3_256;
     default: return false;
   }
@@ -1923,14 +1966,14 @@ bool conv_takes_ln(int dtype, long long m, int n, int c, int out_mode) {
 // A small-tile launch whose threads hold at most 40 elements each: what a workgroup does for the norm grows with the samples it takes in, the launch that it
 // saves does not.  us (norm + convolution / one launch): two samples of 24x24 of 64 bf16 channels (72 elements) 3.9 + 4.3 / 10.4, 16x16 of 128 (64) 3.7 + 5.0 / 8.8,
 // 12x12 of 128 (36) 3.7 + 5.5 / 7.3, 16x16 of 64 (32) 3.8 + 4.0 / 8.2 in a chain that is one gap shorter.  Channels that a power of two of accesses covers (not 192 or 384).
-bool conv_takes_gn(int dtype, int batch, int h, int w, int c0, int c1, int n, int groups, int out_mode) {
+bool conv_takes_gn(int dtype, int batch, int h, int w, int c0, int c1, int n, int groups, int out_mode, int xc) {
   const int c = c0 + c1, bk = bk_elems(dtype), es = (int)esize(dtype), vn = 16 / es, hw = h * w;
   if ((out_mode != OUT_ROWMAJOR && out_mode != OUT_TRANSPOSED_F32) || c0 % bk || c1 % bk || groups < 8 || groups % 8 || c % (2 * groups)) return false;
   const int cpg = c / groups, vps = c / (8 * vn);         // a wavefront takes an eighth of the channels: whole groups, whole accesses, powers of two
   if (c % (8 * vn) || (vps & (vps - 1)) || vps > 16 || (cpg & (cpg - 1)) || cpg > 4 * vn) return false;
   const long long m = (long long)batch * hw;
-  if (choose_plan(dtype, m, n, 9 * c / bk, out_mode).tile != TILE_SMALL) return false;
-  const SmallTile t = small_tile(dtype, m, n, 9 * c / bk, out_mode);
+  if (choose_plan(dtype, m, n, (9 * c + xc) / bk, out_mode).tile != TILE_SMALL) return false;
+  const SmallTile t = small_tile(dtype, m, n, (9 * c + xc) / bk, out_mode);
   const int bm = 16 * t.tm;
   return (long long)gn_samples(bm, batch, hw) * hw <= gn_hold(vn) * (64 / vps) &&
          8 * bm * (16 * t.tn + 4) * 4 + gn_act_bytes(bm, w, c * es) <= (int)kLdsLimit;
@@ -1987,8 +2030,8 @@ ad_status launch_conv(const ConvArgs& a, hipStream_t s) {
     const char *o = (const char*)a.out, *s0 = (const char*)a.src0, *s1 = (const char*)a.src1;
     const size_t es = esize(a.dtype), out_bytes = (size_t)m * a.n_out * (a.out_mode == OUT_TRANSPOSED_F32 ? 4 : es), px = (size_t)a.batch * a.hs * a.ws;
     const bool apart = (s0 + px * a.c0 * es <= o || o + out_bytes <= s0) && (a.c1 == 0 || s1 + px * a.c1 * es <= o || o + out_bytes <= s1);
-    if (!a.ln_gain || !a.ln_offset || a.ksize != 3 || a.stride != 1 || a.up || a.xw || !apart || ((uintptr_t)s0 & 15) || (a.c1 && ((uintptr_t)s1 & 15)) ||
-        !conv_takes_gn(a.dtype, a.batch, a.hs, a.ws, a.c0, a.c1, a.n_out, a.gn_groups, a.out_mode))
+    if (!a.ln_gain || !a.ln_offset || a.ksize != 3 || a.stride != 1 || a.up || !apart || ((uintptr_t)s0 & 15) || (a.c1 && ((uintptr_t)s1 & 15)) ||
+        !conv_takes_gn(a.dtype, a.batch, a.hs, a.ws, a.c0, a.c1, a.n_out, a.gn_groups, a.out_mode, p.xc0 + p.xc1))
       AD_FAIL(AD_ERR_INVALID, "conv: bad GroupNorm");
     p.gn_log_vps = 0;
     p.gn_cpg = p.ctot / a.gn_groups;

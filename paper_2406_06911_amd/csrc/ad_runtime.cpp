@@ -151,11 +151,13 @@ struct Eval {
     const void* shortcut = x0;
     if (ci != f.c_out && conv_takes_shortcut(dt, (long long)c.cfg.batch * hw, f.c_out, f.c_out, ci)) {
       WView wv{c};                      // the shortcut's bias goes in as a row vector that all samples share
-      AD_TRY(gn(temp(1), nullptr, f.c_out, 0, hw, w0 + 6, 1, temp(0)));
-      ConvArgs a{dt, temp(0), nullptr, f.c_out, 0, c.cfg.batch, f.h_in, f.w_in, 0, 3, 1, wv.at(w0 + 8), f.c_out, wv.f32(w0 + 9), wv.f32(w0 + 11), -1,
+      const bool norm_in = conv_takes_gn(dt, c.cfg.batch, f.h_in, f.w_in, f.c_out, 0, f.c_out, c.cfg.gn_groups, OUT_ROWMAJOR, ci);
+      if (!norm_in) AD_TRY(gn(temp(1), nullptr, f.c_out, 0, hw, w0 + 6, 1, temp(0)));
+      ConvArgs a{dt, norm_in ? temp(1) : temp(0), nullptr, f.c_out, 0, c.cfg.batch, f.h_in, f.w_in, 0, 3, 1, wv.at(w0 + 8), f.c_out, wv.f32(w0 + 9), wv.f32(w0 + 11), -1,
                  nullptr, tensor_out(ui), OUT_ROWMAJOR, 0, temp(9), ws.temp_bytes[9]};
       a.x0 = x0; a.x1 = x1; a.xc0 = f.c_in; a.xc1 = f.c_skip; a.xw = wv.at(w0 + 10);
       a.w_blocks = 1;
+      if (norm_in) { a.ln_gain = wv.f32(w0 + 6); a.ln_offset = wv.f32(w0 + 7); a.ln_eps = c.cfg.gn_eps; a.gn_groups = c.cfg.gn_groups; a.gn_silu = 1; }
       ask_ahead(a, {ui + 1, kFirst});
       return launch_conv(a, s);
     }

@@ -76,7 +76,34 @@ def test_head(dtype, c, height, width, batch, groups, fused, kind):
 
 @pytest.mark.parametrize("dtype,channels,height,width,batch,groups", [
     (B.AD_BF16, [256, 256], 6, 6, 2, 32), (B.AD_BF16, [128, 128], 12, 12, 2, 32), (B.AD_BF16, [64, 64], 4, 12, 2, 8), (B.AD_F32, [32, 32], 12, 4, 1, 8),
-    (B.AD_F32, [64, 64], 6, 10, 2, 16)])
+    (B.AD_F32, [64, 64], 6, 10, 2, 16), (B.AD_BF16, [64, 64], 24, 26, 2, 32), (B.AD_F32, [128, 256], 6, 6, 2, 32), (B.AD_BF16, [64, 256], 2, 2, 1, 32), (B.AD_BF16, [192, 128], 6, 6, 2, 32)])
 def test_blocks(monkeypatch, dtype, channels, height, width, batch, groups):
     """Two sources, the time projection of each sample, residuals, shortcuts."""
     check_blocks(monkeypatch, dtype, -1, channels, height, width, batch, lambda u: True, groups)
+
+
+@pytest.mark.parametrize("dtype,channels,height,width,batch,groups,launches", [
+    (B.AD_BF16, [128, 256], 6, 6, 2, 32, 2), (B.AD_F32, [64, 128], 6, 6, 2, 32, 2),              # both norms and the shortcut inside the convolutions
+    (B.AD_BF16, [64, 128], 48, 48, 2, 32, 4), (B.AD_BF16, [192, 128], 6, 6, 2, 32, 3)])          # the norms of larger maps, and of 192 channels, are launches
+def test_launches_of_a_block_that_changes_its_width(dtype, channels, height, width, batch, groups, launches):
+    d = config(channels, height, width, batch, groups)
+    probe = B.AsyncDiff(d, 1, 0, 1, dtype)
+    units = [u.name.decode() for u in probe.units()]
+    probe.close()
+    i = units.index("d1.0.res")                                       # channels[0] -> channels[1] on a quarter of the pixels
+    m = B.AsyncDiff(d, 3, 1, 1, dtype, cuts=[i, i + 1])
+    m.allocate(DEV)
+    m.load_weights({n: np.full(s, 0.01, np.float32) for n, s in m.weight_manifest()})
+    m.reset(2)
+    ins, outs = m.component_io(2)
+    store = {}
+    for u in ins + outs:
+        b, h, w, c = m.tensor_shape(u)[0]
+        store[u] = torch.ones(b, h, w, c, device=DEV, dtype=torch.bfloat16 if dtype == B.AD_BF16 else torch.float32)
+    text = torch.zeros(batch, 8, 64, device=DEV, dtype=store[ins[0]].dtype)
+    m.profile(True)
+    m.component_forward(2, [store[u] for u in ins], 0, text, [store[u] for u in outs], torch.cuda.current_stream())
+    torch.cuda.synchronize()
+    names = [r[0] for r in m.profile_records() if not r[0].startswith(("time", "linear_rows"))]
+    m.close()
+    assert len(names) == launches, names
