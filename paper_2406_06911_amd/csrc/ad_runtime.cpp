@@ -105,11 +105,15 @@ struct Eval {
     return launch_groupnorm(dt, src0, src1, c0, c1, c.cfg.batch, hw, c.cfg.gn_groups, wv.f32(g_idx), wv.f32(g_idx + 1),
                             c.cfg.gn_eps, silu, dst, work(ws.gn_off), c.gn_bytes, s);
   }
+  // whether a caller's tensors share no memory: a launch whose workgroups read what others do not write needs that
+  static bool apart(const void* a, size_t a_bytes, const void* b, size_t b_bytes) { return !a || (const char*)a + a_bytes <= (const char*)b || (const char*)b + b_bytes <= (const char*)a; }
   // a convolution (stride 1) behind a GroupNorm of its input (gain and offset at g_idx), in one launch where it takes the norm in
   ad_status gn_conv(const void* src0, const void* src1, int c0, int c1, int h, int w, int g_idx, int silu, int w_idx, const float* rowvec, const void* residual,
                     void* dst, int mode, int ld_t, Next behind) const {
     WView wv{c};
-    if (!conv_takes_gn(dt, c.cfg.batch, h, w, c0, c1, c.weights[w_idx].info.shape[0], c.cfg.gn_groups, mode)) {
+    const size_t px = (size_t)c.cfg.batch * h * w, es = esize(dt), out_bytes = px * c.weights[w_idx].info.shape[0] * (mode == OUT_TRANSPOSED_F32 ? 4 : es);
+    if (!conv_takes_gn(dt, c.cfg.batch, h, w, c0, c1, c.weights[w_idx].info.shape[0], c.cfg.gn_groups, mode) || !apart(src0, px * c0 * es, dst, out_bytes) ||
+        !apart(src1, px * c1 * es, dst, out_bytes)) {
       AD_TRY(gn(src0, src1, c0, c1, h * w, g_idx, silu, temp(0)));
       return conv(temp(0), nullptr, c0 + c1, 0, h, w, 0, 3, 1, w_idx, w_idx + 1, rowvec, residual, dst, mode, ld_t, behind);
     }
@@ -149,7 +153,9 @@ struct Eval {
     const float* rowvec = proj + (u.temb_row - cp.temb_row0);
     AD_TRY(gn_conv(x0, x1, f.c_in, f.c_skip, f.h_in, f.w_in, w0 + 0, 1, w0 + 2, rowvec, nullptr, temp(1), OUT_ROWMAJOR, 0, {ui, w0 + 8}));
     const void* shortcut = x0;
-    if (ci != f.c_out && conv_takes_shortcut(dt, (long long)c.cfg.batch * hw, f.c_out, f.c_out, ci)) {
+    const size_t px = (size_t)c.cfg.batch * hw * esize(dt);
+    if (ci != f.c_out && conv_takes_shortcut(dt, (long long)c.cfg.batch * hw, f.c_out, f.c_out, ci) && apart(x0, px * f.c_in, tensor_out(ui), px * f.c_out) &&
+        apart(x1, px * f.c_skip, tensor_out(ui), px * f.c_out)) {
       WView wv{c};                      // the shortcut's bias goes in as a row vector that all samples share
       const bool norm_in = conv_takes_gn(dt, c.cfg.batch, f.h_in, f.w_in, f.c_out, 0, f.c_out, c.cfg.gn_groups, OUT_ROWMAJOR, ci);
       if (!norm_in) AD_TRY(gn(temp(1), nullptr, f.c_out, 0, hw, w0 + 6, 1, temp(0)));
