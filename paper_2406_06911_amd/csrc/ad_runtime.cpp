@@ -112,7 +112,8 @@ struct Eval {
                     void* dst, int mode, int ld_t, Next behind) const {
     WView wv{c};
     const size_t px = (size_t)c.cfg.batch * h * w, es = esize(dt), out_bytes = px * c.weights[w_idx].info.shape[0] * (mode == OUT_TRANSPOSED_F32 ? 4 : es);
-    if (!conv_takes_gn(dt, c.cfg.batch, h, w, c0, c1, c.weights[w_idx].info.shape[0], c.cfg.gn_groups, mode) || !apart(src0, px * c0 * es, dst, out_bytes) ||
+    const bool at16 = (((uintptr_t)src0 | (uintptr_t)src1) & 15) == 0;      // a caller's tensors may begin anywhere
+    if (!at16 || !conv_takes_gn(dt, c.cfg.batch, h, w, c0, c1, c.weights[w_idx].info.shape[0], c.cfg.gn_groups, mode) || !apart(src0, px * c0 * es, dst, out_bytes) ||
         !apart(src1, px * c1 * es, dst, out_bytes)) {
       AD_TRY(gn(src0, src1, c0, c1, h * w, g_idx, silu, temp(0)));
       return conv(temp(0), nullptr, c0 + c1, 0, h, w, 0, 3, 1, w_idx, w_idx + 1, rowvec, residual, dst, mode, ld_t, behind);

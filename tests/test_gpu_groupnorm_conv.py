@@ -142,3 +142,42 @@ def test_a_block_whose_result_overwrites_its_input(dtype, channels, height, widt
     m.close()
     # the shortcut's sum passes through the storage type in the separate launches: one rounding (2^-9 of a value) and what follows from it
     assert rel_l2(same.numpy(), apart.numpy()) < (4e-3 if dtype == B.AD_BF16 else 1e-6)
+
+
+@pytest.mark.parametrize("dtype", [B.AD_BF16, B.AD_F32])
+def test_an_input_between_two_accesses(dtype):
+    """hidden_in 8 bytes behind a multiple of 16: the norm is a launch of its own."""
+    c, size = 64, 12
+    d = config([c], size, size, 2, 32)
+    rng = np.random.default_rng(4)
+    x = quantize(rng.standard_normal((2, size, size, c)), dtype)
+    gain, offset = (1 + 0.3 * rng.standard_normal(c)).astype(np.float32), (0.3 * rng.standard_normal(c)).astype(np.float32)
+    w, bias = quantize(rng.standard_normal((4, c, 3, 3)) * (9 * c) ** -0.5, dtype), rng.standard_normal(4).astype(np.float32)
+    at16 = dev(x, dtype)
+    skip = 8 // at16.element_size()
+    moved = torch.empty(at16.numel() + 16, device=DEV, dtype=at16.dtype)[skip:skip + at16.numel()].view(at16.shape)
+    moved.copy_(at16)
+    want, _ = head(d, dtype, at16, gain, offset, w, bias)
+    got, names = head(d, dtype, moved, gain, offset, w, bias)
+    assert any(n.startswith("gn_") for n in names), names
+    # other order of the sums of the statistics: fp32 roundings, and the few bf16 operands that these move
+    assert rel_l2(got, want) < (5e-4 if dtype == B.AD_BF16 else 3e-6)
+
+
+@pytest.mark.parametrize("value", [float("inf"), float("nan")])
+@pytest.mark.parametrize("dtype,c,size", [(B.AD_BF16, 256, 3), (B.AD_F32, 64, 6)])
+def test_a_sample_that_is_not_finite(dtype, c, size, value):
+    """Rows of both samples meet in a tile: the finite one keeps its bits, the other has no value anywhere, as with a launch for the norm."""
+    d = config([c], size, size, 2, 32)
+    rng = np.random.default_rng(6)
+    x = quantize(rng.standard_normal((2, size, size, c)), dtype)
+    gain, offset = np.ones(c, np.float32), np.zeros(c, np.float32)
+    w, bias = quantize(rng.standard_normal((4, c, 3, 3)) * (9 * c) ** -0.5, dtype), np.zeros(4, np.float32)
+    want, names = head(d, dtype, dev(x, dtype), gain, offset, w, bias)
+    assert not any(n.startswith("gn_") for n in names), names
+    for z in range(2):
+        broken = x.copy()
+        broken[z, size // 2, size // 2, 5] = value
+        got, _ = head(d, dtype, dev(broken, dtype), gain, offset, w, bias)
+        assert np.array_equal(got[1 - z], want[1 - z])
+        assert np.isnan(got[z]).all()
