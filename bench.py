@@ -24,15 +24,15 @@ PEAK_HBM_GBS = 8000.0
 # `rocprofv3 --pmc` runs of this file (FETCH_SIZE, WRITE_SIZE; KiB per dispatch scaled by the factors 2.00 and 1.00 that the
 # same counters show for the 2^26-element sampler launch).  Commands and tables: profiles/bench_sd21_768_all_kernels.md.
 MEASURED_TRAFFIC = {"sd21_768": {
-    "igemm_bf16_256x128_p3": 62801587, "igemm_bf16_256x128_p3_splitk": 167921276, "igemm_bf16_128x128_p3": 41868338,
-    "igemm_bf16_128x128_p3_splitk": 60928377, "splitk_reduce": 19770033, "igemm_bf16_64x64_p3": 26215031,
-    "attn_mfma2_bf16": 33322500, "layernorm": 13099394, "gn_apply": 29595366, "gn_partial": 14604695,
-    "igemm_bf16_128x128_d2": 91206620, "gn_group": 6778736, "attn_mfma_bf16": 14639964, "igemm_bf16_128x160_d2": 39899220,
-    "igemm_bf16_64x64_splitk": 98368989, "igemm_bf16_256x320_d2": 57148519, "linear_rows": 5857998,
-    "igemm_bf16_64x64_k2": 11821670, "igemm_bf16_64x64_p3_splitk": 28567552, "igemm_bf16_small": 4581296}}
+    "igemm_bf16_256x128_p3": 66942122, "igemm_bf16_256x128_p3_splitk": 170711505, "igemm_bf16_128x128_p3": 43485990,
+    "igemm_bf16_128x128_p3_splitk": 62350919, "splitk_reduce": 19782286, "igemm_bf16_64x64_p3": 29391829,
+    "attn_mfma2_bf16": 33324244, "layernorm": 13100547, "gn_apply": 29580146, "gn_partial": 14604206,
+    "igemm_bf16_128x128_d2": 92416823, "gn_group": 6774979, "attn_mfma_bf16": 14628862, "igemm_bf16_128x160_d2": 39866587,
+    "igemm_bf16_64x64_splitk": 96710086, "igemm_bf16_256x320_d2": 57041137, "linear_rows": 5847423,
+    "igemm_bf16_64x64_k2": 11824742, "igemm_bf16_64x64_p3_splitk": 28567552, "igemm_bf16_small": 4579658}}
 
 
-TRAFFIC_SOURCE = "not measured in this run: FETCH_SIZE + WRITE_SIZE of two rocprofv3 --pmc runs of this file, profiles/bench_sd21_768_all_kernels.md (kernels of commit 695b0a0)"
+TRAFFIC_SOURCE = "not measured in this run: FETCH_SIZE + WRITE_SIZE of two rocprofv3 --pmc runs of this file, profiles/bench_sd21_768_all_kernels.md (kernels of commit 5eed711)"
 
 
 def log(*a):
