@@ -979,6 +979,8 @@ static ad_status run_igemm_p3(const IgemmParams& p0, const char* name, hipStream
 // 4.8 + 10.2 -> 12.1. Launches of a step: tiny fp32 34 -> 29, narrow 204 -> 190, narrow fp32 223 -> 213. Whole runs, ms: tiny 1.89 -> 1.74, narrow 35.8 -> 34.0, with stride 2
 // 25.5 -> 24.7, narrow fp32 12.10 -> 11.84.
 // Taken back: statistics over all wavefronts through LDS, merged in double (4.3 us a launch), and 1x1 convolutions (72x256x256 3.7 + 3.9 -> 7.9).
+// Four k-tiles of fragments on their way instead of two are level (18x256x2304 8.5 / 8.7 us, fp32 10.4 / 10.7, fp32 72x2048x256 8.1 / 7.9; whole runs 0.993 to 1.003): what a CU
+// takes in at a time decides, not how early a wavefront asks.
 // =================================================================================================
 constexpr int small_ktiles(int bm, int bn) { return 200 * 1024 / ((bm + bn) * kRowBytes); }      // k-tiles that small_tile() takes at the most (bf16), and of a LayerNorm in front
 // Sum over the threads of a row, TPR = 16 or 32 neighbouring lanes, as k_layernorm's lanes add up: distances 32 / TPR .. 1, where a distance within 16 lanes is a
