@@ -1330,7 +1330,27 @@ __global__ __launch_bounds__(512) void k_igemm_small(IgemmParams p) {
   for (int i = 0; i < TM; ++i)
 #pragma unroll
     for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  // fp32: every SUM_TILES k-tiles the sum goes to another one, so that no chain of additions is longer than 32 * SUM_TILES.  Error against 64 bits, 2-norm
+  // (register-staged tiles with K split / one chain a wavefront / this): 18x256x2304 2.96e-7 / 3.13e-7 / 2.10e-7, 18x256x4608 3.17e-7 / 4.35e-7 / 2.12e-7,
+  // 45x64x4800 3.36e-7 / 4.42e-7 / 2.12e-7; narrow fp32 runs level (11.88 ms, 11.91 without).
+  constexpr bool BY_PARTS = sizeof(T) == 4;
+  constexpr int SUM_TILES = 4;
+  static_assert(SUM_TILES % PF == 0, "a part ends between two rounds of the loop");
+  f32x4 parts[BY_PARTS ? TM : 1][BY_PARTS ? TN : 1];
+  auto end_part = [&]() {
+    if constexpr (BY_PARTS)
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) { parts[i][j] += acc[i][j]; acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f}; }
+  };
+  if constexpr (BY_PARTS)
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j) parts[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
   for (int i0 = 0; i0 < mine; i0 += PF) {
+    if (BY_PARTS && i0 % SUM_TILES == 0) end_part();
 #pragma unroll
     for (int s = 0; s < PF; ++s) {
       if (i0 + s >= mine) break;
@@ -1369,6 +1389,7 @@ __global__ __launch_bounds__(512) void k_igemm_small(IgemmParams p) {
   if constexpr (XTRA)
     for (int e = x_first; e < x_tiles; e += NW) {
       if (e > x_first) fetch_extra(e);
+      end_part();
 #pragma unroll
       for (int h = 0; h < 2; ++h)
 #pragma unroll
@@ -1376,6 +1397,11 @@ __global__ __launch_bounds__(512) void k_igemm_small(IgemmParams p) {
 #pragma unroll
           for (int j = 0; j < TN; ++j) Mma16<T>::run(xb[j][h], xa[i][h], acc[i][j]);
     }
+  if constexpr (BY_PARTS)
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j) acc[i][j] += parts[i][j];
   // lane: row r16 of row tile i, columns 4 kg .. 4 kg + 3 of column tile j
 #pragma unroll
   for (int i = 0; i < TM; ++i)
