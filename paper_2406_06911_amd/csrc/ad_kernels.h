@@ -51,7 +51,7 @@ struct ConvArgs {
   // a LayerNorm over the channels in front of a linear layer, only where conv_takes_ln() says so: gain and offset of the channels, epsilon
   const float* ln_gain = nullptr; const float* ln_offset = nullptr;
   float ln_eps = 0.f;
-  int gn_groups = 0, gn_silu = 0;       // > 0: not a LayerNorm but a GroupNorm of the input (and SiLU), only where conv_takes_gn() says so
+  int gn_groups = 0;                    // > 0: not a LayerNorm but a GroupNorm of the input and SiLU, only where conv_takes_gn() says so
   const void* ahead = nullptr;          // weights of a later launch, fetched from memory beside the product (a hint; the LDS-DMA kernels take it)
   size_t ahead_bytes = 0;
   int w_blocks = 0;                     // w and xw are in blocks (pack_blocks()) instead of rows

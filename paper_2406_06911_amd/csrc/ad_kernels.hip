@@ -43,6 +43,16 @@ ProfLaunch::~ProfLaunch() {
 // tiles.  One k-tile is 128 bytes of K per row (64 bf16 / 32 fp32), staged through LDS with a
 // 16-byte row pad; the next k-tile is fetched into registers while the current one is multiplied.
 // =================================================================================================
+// GN: how the wavefronts of a small-tile convolution hold the samples that they normalise, see gn_stats()
+struct GnLayout {
+  int log_vps;                                           // log2 of a wavefront's accesses to a pixel
+  int vpp, per_access;                                   // accesses that a group has to a pixel, groups in an access: one of the two is 1
+  int run;                                               // accesses of a lane that make up a wavefront of k_gn_group
+  int pixels, slots;                                     // pixels that begin in lane 0, accesses of a lane to them at the most (0: no layout)
+  int bits;                                              // of a sample's pixels in an access
+  int chained;                                           // threads of k_gn_group have several accesses
+};
+
 struct IgemmParams {
   const void* src0; const void* src1;
   int c0, c1, ctot;
@@ -67,7 +77,7 @@ struct IgemmParams {
   int xc0, xc1, kt_main;                                // its channels; k-tiles of the taps
   unsigned xbytes0, xbytes1, xbytes_w;
   const float* ln_gain; const float* ln_offset; float ln_eps;      // LN, GN (k_igemm_small): of the channels
-  int gn_groups, gn_silu, gn_log_vps, gn_cpg; double gn_inv_n;                              // GN: groups (0: none), log2 of a wavefront's accesses to a pixel, see gn_stage()
+  int gn_groups; GnLayout gn; double gn_inv_n;            // GN: groups (0: none)
   const void* ahead; unsigned ahead_bytes, ahead_span;             // k_igemm_p3: weights of a later launch (0 bytes: none), and a wavefront's share of them
 };
 
@@ -970,10 +980,13 @@ static ad_status run_igemm_p3(const IgemmParams& p0, const char* name, hipStream
 // GN: a GroupNorm (and SiLU) in front of a 3x3 convolution of a small map, likewise: the launch it saves takes 3.6 us, nearly all of it the launch itself and a
 // round trip to memory, in a chain of launches that wait for one another.  Every workgroup takes in the samples that its rows belong to (9 to 256 pixels), a
 // wavefront an eighth of the channels, so that the statistics of its groups need no other wavefront; the pixels that the taps read are normalised once, on
-// their way into LDS, and the fragments come from there.  Same statistics as k_gn_group (mean first, then deviations), other order of the sums.
-// Measured inside the models, us (norm + convolution -> convolution): bf16 18x256x2304 3.7 + 6.7 -> 8.2, 72x256x2304 3.7 + 7.1 -> 8.5, 128x256x2304 3.7 + 7.2 -> 7.8,
-// 288x128x1152 3.7 + 5.5 -> 7.3; fp32 64x64x576 3.4 + 5.5 -> 6.1, 256x32x288 3.6 + 4.8 -> 6.7; and the gap between two launches.
-// Whole runs, ms: tiny fp32 2.30 -> 1.73, narrow 36.9 -> 35.7, with stride 2 26.2 -> 25.4, narrow fp32 17.13 -> 17.04.
+// their way into LDS, and the fragments come from there.  Statistics and norm are k_gn_group's to the bit (gn_stats()): its order of the sums, one number taken off all values
+// of a group, the last sums in double.  Bound by vector instructions: two wavefronts a SIMD, 680 to 1120 each with the product's 160.
+// Measured inside the models, us (norm + convolution -> convolution): bf16 18x256x2304 3.8 + 5.9 -> 9.3, 72x256x2304 3.7 + 6.3 -> 9.5, 128x256x2304 3.7 + 7.4 -> 9.6,
+// 288x128x1152 3.7 + 4.8 -> 8.9; fp32 288x128x1152 3.7 + 7.9 -> 9.9, 64x64x576 3.7 + 4.8 -> 7.1, 256x32x288 3.6 + 3.9 -> 8.3: what it saves is the gap between two launches.
+// Whole runs, a launch for every norm / this, ms, the same bits: tiny fp32 2.16 / 1.74, narrow 35.2 / 34.5, with stride 2 25.35 / 25.11, narrow fp32 12.93 / 12.28.  (With every
+// lane's sums over its own accesses, rotated within the row and folded in fp32, a launch took 1 to 1.5 us less, but lanes took different numbers off the values of a group
+// where their sums met a boundary of 12 bits (fp32 values up to 2e-2 off), and sums of squares beyond fp32 left the offset alone.)
 // XTRA: the 1x1 shortcut of a ResBlock as k-tiles behind the taps, as in k_igemm_p3: a launch of 3.7 to 4.3 us for 0.7 to 2 us. fp32 too. us (shortcut + second convolution ->
 // one): bf16 18x256 of 2304 + 512 4.2 + 8.1 -> 9.6, 72x256 4.2 + 7.7 -> 9.8, 288x128 of 1152 + 256 4.0 + 6.9 -> 7.6; fp32 256x32 of 288 + 96 3.7 + 6.7 -> 7.4, 18x256 of 2304 + 512
 // 4.8 + 10.2 -> 12.1. Launches of a step: tiny fp32 34 -> 29, narrow 204 -> 190, narrow fp32 223 -> 213. Whole runs, ms: tiny 1.89 -> 1.74, narrow 35.8 -> 34.0, with stride 2
@@ -1037,103 +1050,230 @@ __device__ __forceinline__ void ln_stats(const IgemmParams& p, int sub, const ty
 
 constexpr int gn_pitch(int row_bytes) { return row_bytes + 16; }      // of a pixel in LDS: 16 neighbouring pixels fall on different banks
 constexpr int gn_act_bytes(int bm, int ws, int row_bytes) { return 256 + (bm + 2 * (ws + 1)) * gn_pitch(row_bytes); }
-template <int CTRL> __device__ __forceinline__ float add_dpp(float v) { return v + dpp_f<CTRL>(v); }
-// A wavefront's eighth of the channels (whole groups) of all pixels of nb samples, in registers: access k of a lane is pixel px + k * step.  Normalises them
-// and leaves those that the tile reads, rows lo .. hi - 1, in LDS: 256 zero bytes, then a row after the other.  The statistics stay inside the wavefront: no barrier
-// before the last.  As in k_gn_group the mean comes first, to its 12 leading bits, then the sums of the deviations from it and of their squares.
-template <typename T, int N>
-__device__ __forceinline__ void gn_stage(const IgemmParams& p, const typename Vec<T>::type (&x)[N], const float (&gain)[Vec<T>::N], const float (&offset)[Vec<T>::N],
-                                         int first, int nb, int px, int channel, int lo, int hi, char* base) {
-  typedef typename Vec<T>::type V;
-  constexpr int VN = Vec<T>::N, PAIRS = VN / 2;
-  const int hw = p.hw_out, cpg = p.gn_cpg, lg = p.gn_log_vps, step = 64 >> lg;
-  const double inv_n = p.gn_inv_n;
-  auto again = [&](int e) { return (e & 1 && cpg >= 4) || (e == 2 && cpg >= 8); };      // the pair belongs to the group of the one before
-  // pair sums -> the sum of the pair's group, in every lane that holds a part of it
-  auto total = [&](float (&v)[PAIRS]) {
-    if (cpg >= 4)
+// What k_gn_group and a convolution with the norm inside have in common, with the products fused as written: an element's deviation added to the sums, what
+// the sums make of a group, and the norm of an element.  sum: of the deviations from `about`; rest: what the mean is beyond that.
+__device__ __forceinline__ void gn_add(float x, float about, float& s, float& q) { const float d = x - about; s += d; q = fmaf(d, d, q); }
+__device__ __forceinline__ void gn_moments(double sum, double squares, double inv_n, float eps, float& rstd, float& rest) {
+  const double mean = sum * inv_n;
+  double var = fma(inv_n, squares, -(mean * mean));
+  var = (var < 0.0 ? 0.0 : var) + (double)eps;
+  // 1 / sqrt(var): one Newton step on the fp32 value, a fifth of the instructions of the double division and root
+  const double r0 = rsqrtf((float)var);
+  rstd = (float)(var > 1e-30 && var < 1e30 ? fma(-0.5 * var * r0, r0, 1.5) * r0 : 1.0 / sqrt(var));
+  rest = (float)mean;
+}
+__device__ __forceinline__ float gn_about(float sum, double inv_n) { return __uint_as_float(__float_as_uint(sum * (float)inv_n) & 0xfffff000u); }
+__device__ __forceinline__ float gn_value(float x, float about, float gain, float offset) { return fmaf(x - about, gain, offset); }
+
+// Pixel of a lane in an access: pixel bit 0 is the highest of the row's bits behind the accesses, and so on downwards, so that the pixels to be added up first lie 8
+// lanes apart, the next 4, ...; then the rows of 16 lanes
+__device__ __forceinline__ int gn_pixel(int lane, int log_vps) {
+  const int r = (lane & 15) >> log_vps, bits = 4 - log_vps;
+  return (int)(__brev((unsigned)r) >> 1 >> (31 - bits)) + (lane >> 4 << bits);
+}
+// Sums over the lanes of a group, in every one of them: first over its accesses to a pixel, then over pixels 1, 2, 4, ... apart, as the 64 threads of a wavefront
+// of k_gn_group add up.  Both lanes of a pair add the same two numbers, so all lanes hold the same; a distance of 4 lanes is a rotation by 4 where lanes
+// 8 apart hold the same already.
+template <int GP, int S>
+__device__ __forceinline__ void gn_lanes(const GnLayout& g, float (&sums)[GP][S]) {
+  constexpr int N = GP * S;
+  float v[(N + 3) / 4 * 4];
 #pragma unroll
-      for (int e = 0; e < PAIRS; e += 2) v[e] += v[e + 1];
-    if (PAIRS == 4 && cpg >= 8) v[0] += v[2];
+  for (int i = 0; i < (N + 3) / 4 * 4; ++i) v[i] = i < N ? sums[i < N ? i / S : 0][i % S] : 0.f;
+  const int in_row = 4 - g.log_vps;                      // pixel bits within a row
+  if (g.vpp >= 2)
 #pragma unroll
-    for (int e = 0; e < PAIRS; ++e) {
-      if (again(e)) continue;
-      float t = v[e];
-      if (lg <= 0) t = add_dpp<0x121>(t);                // rotations within 16 lanes by 1, 2, 4, 8
-      if (lg <= 1) t = add_dpp<0x122>(t);
-      if (lg <= 2) t = add_dpp<0x124>(t);
-      if (lg <= 3) t = add_dpp<0x128>(t);
-      const unsigned u = __float_as_uint(t);
-      const auto h = __builtin_amdgcn_permlane16_swap(u, u, false, false);
-      t = __uint_as_float(h[0]) + __uint_as_float(h[1]);
-      const unsigned w = __float_as_uint(t);
-      const auto o = __builtin_amdgcn_permlane32_swap(w, w, false, false);
-      t = __uint_as_float(o[0]) + __uint_as_float(o[1]);
-      if (cpg >= 2 * VN) t = add_dpp<0xB1>(t);           // the accesses of a group of 2 or 4: quad_perm 1 0 3 2, then 2 3 0 1
-      if (cpg >= 4 * VN) t = add_dpp<0x4E>(t);
-      v[e] = t;
-    }
-    if (cpg >= 4)
+    for (int i = 0; i < N; ++i) v[i] += dpp_f<0xB1>(v[i]);                   // quad_perm 1 0 3 2
+  if (g.vpp >= 4)
 #pragma unroll
-      for (int e = 0; e < PAIRS; e += 2) v[e + 1] = v[e];
-    if (PAIRS == 4 && cpg >= 8) { v[2] = v[0]; v[3] = v[0]; }
+    for (int i = 0; i < N; ++i) v[i] += dpp_f<0x4E>(v[i]);                   // quad_perm 2 3 0 1
+  if (g.bits > 0 && in_row > 0)
+#pragma unroll
+    for (int i = 0; i < N; ++i) v[i] += dpp_f<0x128>(v[i]);                  // row_ror 8
+  if (g.bits > 1 && in_row > 1)
+#pragma unroll
+    for (int i = 0; i < N; ++i) v[i] += dpp_f<0x124>(v[i]);                  // row_ror 4
+  if (g.bits > 2 && in_row > 2)
+#pragma unroll
+    for (int i = 0; i < N; ++i) v[i] += dpp_f<0x122>(v[i]);                  // row_ror 2
+  if (g.bits > 3 && in_row > 3)
+#pragma unroll
+    for (int i = 0; i < N; ++i) v[i] += dpp_f<0x121>(v[i]);                  // row_ror 1
+  auto swap16 = [](float& x, float& y) {                 // odd rows of x and even rows of y change places
+    const auto h = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+    x = __uint_as_float(h[0]); y = __uint_as_float(h[1]);
   };
+  auto swap32 = [](float& x, float& y) {                 // upper half of x and lower half of y
+    const auto h = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+    x = __uint_as_float(h[0]); y = __uint_as_float(h[1]);
+  };
+  if (g.bits > in_row + 1) {
+    // four sums at a time, a row of the result each, and back to all rows
+#pragma unroll
+    for (int i = 0; i < N; i += 4) {
+      float a = v[i], b = v[i + 1], c = v[i + 2], d = v[i + 3];
+      swap16(a, b); a += b;
+      swap16(c, d); c += d;
+      swap32(a, c); a += c;
+      b = a;
+      swap16(a, b);
+      c = a; d = b;
+      swap32(a, c); swap32(b, d);
+      v[i] = a; v[i + 1] = b; v[i + 2] = c; v[i + 3] = d;
+    }
+  } else if (g.bits > in_row) {
+#pragma unroll
+    for (int i = 0; i < N; ++i) { float o = v[i]; swap16(v[i], o); v[i] += o; }
+  }
+#pragma unroll
+  for (int i = 0; i < N; ++i) sums[i / S][i % S] = v[i];
+}
+// Sum over the accesses of a group as k_gn_group's wavefronts add up: `run` accesses are one of them, pairwise, the wavefronts follow one another (ACC)
+template <typename ACC, int S>
+__device__ __forceinline__ ACC gn_waves(int run, const float (&r)[S]) {
+  ACC sum = 0;
+  auto add = [&](auto size) {
+    constexpr int R = decltype(size)::value;
+#pragma unroll
+    for (int k = 0; k < S; k += R) {
+      float w[R];
+#pragma unroll
+      for (int i = 0; i < R; ++i) w[i] = k + i < S ? r[k + i < S ? k + i : 0] : 0.f;
+#pragma unroll
+      for (int n = 1; n < R; n *= 2)
+#pragma unroll
+        for (int i = 0; i + n < R; i += 2 * n)
+          if (k + i + n < S) w[i] += w[i + n];
+      sum += w[0];
+    }
+  };
+  if (run == 1) add(std::integral_constant<int, 1>{});
+  else if (S <= 2 || run == 2) add(std::integral_constant<int, 2>{});
+  else if (S <= 4 || run == 4) add(std::integral_constant<int, 4>{});
+  else add(std::integral_constant<int, 8>{});
+  return sum;
+}
+// A wavefront's eighth of the channels (whole groups; of those of an access the first GP, PER channels each) of the pixels that begin in its lane 0, in registers: access
+// k < S of a lane is pixel px + k * step, nothing from `left` on.  `about`, gain and offset of the lane's channels, for gn_value().  The statistics are k_gn_group's to the bit: there 256 threads
+// hold a group, thread t the access t % vpp of pixels t / vpp, + 256 / vpp, ...; every thread adds up its own elements, the lanes of a wavefront
+// pairwise, the wavefronts in order, in double the deviations.  Here 4 * run accesses of the lanes are those threads.
+template <typename T, int S, int GP, int PER, bool CHAINED, int N>
+__device__ __forceinline__ void gn_stats(const IgemmParams& p, const GnLayout& gn, const u32x4 (&x)[N], int px, int left, float (&about)[Vec<T>::N], float (&gain)[Vec<T>::N],
+                                         float (&offset)[Vec<T>::N]) {
+  typedef typename Vec<T>::type V;
+  constexpr int CN = GP * PER;
+  const int step = 64 >> gn.log_vps, threads = 4 * gn.run;
+  float s[GP][S], q[GP][S];
+  // what thread `k` of the group adds up: access k and (CHAINED) those a multiple of `threads` behind it
+  auto each = [&](int k, auto visit) {
+    if (!CHAINED) return visit(k);
+    if (k >= threads) return;
+#pragma unroll
+    for (int j = k; j < S; j += 4)
+      if (j == k || ((j - k) & (threads - 1)) == 0) visit(j);
+  };
+  auto clear = [&](float (&v)[GP][S]) {
+#pragma unroll
+    for (int g = 0; g < GP; ++g)
+#pragma unroll
+      for (int k = 0; k < S; ++k) v[g][k] = 0.f;
+  };
+  clear(s);
+#pragma unroll
+  for (int k = 0; k < S; ++k)
+    each(k, [&](int j) {
+      if (px + j * step < left)
+#pragma unroll
+        for (int e = 0; e < CN; ++e) s[e / PER][k] += to_f(__builtin_bit_cast(V, x[j])[e]);
+    });
+  gn_lanes(gn, s);
+#pragma unroll
+  for (int g = 0; g < GP; ++g) {
+    const float a = gn_about(gn_waves<float>(gn.run, s[g]), p.gn_inv_n);
+#pragma unroll
+    for (int e = g * PER; e < (g + 1) * PER; ++e) about[e] = a;
+  }
+  clear(s); clear(q);
+#pragma unroll
+  for (int k = 0; k < S; ++k)
+    each(k, [&](int j) {
+      if (px + j * step < left)
+#pragma unroll
+        for (int e = 0; e < CN; ++e) gn_add(to_f(__builtin_bit_cast(V, x[j])[e]), about[e], s[e / PER][k], q[e / PER][k]);
+    });
+  gn_lanes(gn, s);
+  gn_lanes(gn, q);
+#pragma unroll
+  for (int g = 0; g < GP; ++g) {
+    float rstd, rest;
+    gn_moments(gn_waves<double>(gn.run, s[g]), gn_waves<double>(gn.run, q[g]), p.gn_inv_n, p.ln_eps, rstd, rest);
+#pragma unroll
+    for (int e = g * PER; e < (g + 1) * PER; ++e) { gain[e] *= rstd; offset[e] = fmaf(-rest, gain[e], offset[e]); }
+  }
+}
+// Normalises the samples of a tile, one after the other, and leaves the pixels that the tile reads, rows lo .. hi - 1, in LDS behind 256 zero bytes.  One barrier.
+template <typename T, int N>
+__device__ __forceinline__ void gn_stage(const IgemmParams& p, u32x4 (&x)[N], const float (&gain)[Vec<T>::N], const float (&offset)[Vec<T>::N],
+                                         int first, int pixels, int px, int channel, int lo, int hi, char* base) {
+  typedef typename Vec<T>::type V;
+  constexpr int VN = Vec<T>::N;
   if (threadIdx.x < 16) *(f32x4*)(base + threadIdx.x * 16) = f32x4{0.f, 0.f, 0.f, 0.f};
-  const int pitch = gn_pitch(p.ctot * (int)sizeof(T));
+  const int pitch = gn_pitch(p.ctot * (int)sizeof(T)), step = 64 >> p.gn.log_vps;
   char* const to = base + 256 + channel * (int)sizeof(T);
-  for (int z = 0; z < nb; ++z) {
-    auto mine = [&](int k) { return (unsigned)(px + k * step - z * hw) < (unsigned)hw; };
-    float s[PAIRS], q[PAIRS], about[PAIRS];
+  for (int at = 0; at < pixels; at += p.gn.pixels) {
+    GnLayout gn = p.gn;
+    // not known to be the same for every sample: the compiler would make a copy of the loop for each of their values
+    asm volatile("" : "+s"(gn.vpp), "+s"(gn.per_access), "+s"(gn.run), "+s"(gn.slots), "+s"(gn.bits), "+s"(gn.chained), "+s"(gn.log_vps));
+    const int left = min(gn.pixels, pixels - at);
+    float about[VN], ga[VN], be[VN];
 #pragma unroll
-    for (int e = 0; e < PAIRS; ++e) s[e] = 0.f;
+    for (int e = 0; e < VN; ++e) { ga[e] = gain[e]; be[e] = offset[e]; }
+    auto by_slots = [&](auto groups, auto channels) {
+      constexpr int GP = decltype(groups)::value, PER = decltype(channels)::value;
+      constexpr bool WHOLE = PER == VN;
+      if (WHOLE && gn.chained && gn.slots == N) gn_stats<T, N, GP, PER, WHOLE>(p, gn, x, px, left, about, ga, be);
+      else if (WHOLE && gn.chained) gn_stats<T, N / 2, GP, PER, WHOLE>(p, gn, x, px, left, about, ga, be);
+      else if (gn.slots == N) gn_stats<T, N, GP, PER, false>(p, gn, x, px, left, about, ga, be);
+      else if (gn.slots == N / 2) gn_stats<T, N / 2, GP, PER, false>(p, gn, x, px, left, about, ga, be);
+      else gn_stats<T, N / 5, GP, PER, false>(p, gn, x, px, left, about, ga, be);
+    };
+    if (gn.per_access == 1) by_slots(std::integral_constant<int, 1>{}, std::integral_constant<int, VN>{});
+    else if (VN == 8 && gn.per_access == 2) by_slots(std::integral_constant<int, 2>{}, std::integral_constant<int, VN / 2>{});
+    else {
+      // groups of two channels: half of an access at a time, for want of registers
+      auto turn = [](float& y, float& z) { const float w = y; y = z; z = w; };
+#pragma nounroll
+      for (int half = 0; half < 2; ++half) {
+        by_slots(std::integral_constant<int, VN / 4>{}, std::integral_constant<int, 2>{});
 #pragma unroll
-    for (int k = 0; k < N; ++k)
-      if (mine(k))
+        for (int e = 0; e < VN / 2; ++e) { turn(about[e], about[e + VN / 2]); turn(ga[e], ga[e + VN / 2]); turn(be[e], be[e + VN / 2]); }
 #pragma unroll
-        for (int e = 0; e < VN; ++e) s[e / 2] += to_f(x[k][e]);
-    total(s);
-#pragma unroll
-    for (int e = 0; e < PAIRS; ++e) { about[e] = __uint_as_float(__float_as_uint(s[e] * (float)inv_n) & 0xfffff000u); s[e] = 0.f; q[e] = 0.f; }
-#pragma unroll
-    for (int k = 0; k < N; ++k)
-      if (mine(k))
-#pragma unroll
-        for (int e = 0; e < VN; ++e) { const float d = to_f(x[k][e]) - about[e / 2]; s[e / 2] += d; q[e / 2] += d * d; }
-    total(s); total(q);
-    float ga[VN], be[VN], rest = 0.f, rstd = 0.f;
-#pragma unroll
-    for (int e = 0; e < PAIRS; ++e) {
-      if (!again(e)) {
-        const double more = s[e] * inv_n;                // mean - about
-        double var = q[e] * inv_n - more * more;
-        var = (var < 0.0 ? 0.0 : var) + (double)p.ln_eps;
-        const float r0 = rsqrtf((float)var);
-        rstd = (float)(r0 * (1.5 - 0.5 * var * r0 * r0));
-        if (!(var > 1e-30 && var < 1e30)) rstd = (float)(1.0 / sqrt(var));
-        rest = (float)more;
+        for (int k = 0; k < N; ++k) x[k] = __builtin_shufflevector(x[k], x[k], 2, 3, 0, 1);
       }
-#pragma unroll
-      for (int c = 2 * e; c < 2 * e + 2; ++c) { ga[c] = gain[c] * rstd; be[c] = offset[c] - rest * ga[c]; }
     }
 #pragma unroll
     for (int k = 0; k < N; ++k) {
-      const int row = first + px + k * step;
-      if (!mine(k) || row < lo || row >= hi) continue;
+      const int row = first + at + px + k * step;
+      if (k >= gn.slots || px + k * step >= left || row < lo || row >= hi) continue;
       V o;
 #pragma unroll
-      for (int e = 0; e < VN; ++e) {
-        float y = (to_f(x[k][e]) - about[e / 2]) * ga[e] + be[e];
-        if (p.gn_silu) y = silu_f(y);
-        o[e] = from_f<T>(y);
-      }
+      for (int e = 0; e < VN; ++e) o[e] = from_f<T>(silu_f(gn_value(to_f(__builtin_bit_cast(V, x[k])[e]), about[e], ga[e], be[e])));
       *(V*)(to + (row - lo) * pitch) = o;
     }
+    // the next sample's accesses to the front
+    auto shift = [&](auto by) {
+#pragma unroll
+      for (int k = 0; k + decltype(by)::value < N; ++k) x[k] = x[k + decltype(by)::value];
+    };
+    if (at + gn.pixels >= pixels) break;
+    if (gn.slots == N / 2) shift(std::integral_constant<int, N / 2>{});
+    else shift(std::integral_constant<int, N / 5>{});
   }
   __syncthreads();
 }
 
 enum { NORM_NONE = 0, NORM_LAYER = 1, NORM_GROUP = 2 };
-constexpr int gn_hold(int vn) { return 40 / vn; }        // GN: accesses of vn elements that a thread holds at the most
+constexpr int gn_hold(int vn) { return vn == 8 ? 6 : 10; }      // GN: accesses of vn elements that a thread holds at the most
 template <typename T, int TM, int TN, int MODE, int NORM = NORM_NONE, bool XTRA = false>
 __global__ __launch_bounds__(512) void k_igemm_small(IgemmParams p) {
   constexpr bool LN = NORM == NORM_LAYER, GN = NORM == NORM_GROUP;
@@ -1186,22 +1326,27 @@ __global__ __launch_bounds__(512) void k_igemm_small(IgemmParams p) {
   V af[GN ? 1 : PF][TM][2], bf[PF][TN][2];
   // GN: a wavefront's eighth of the channels of the samples that the tile's rows belong to, asked for ahead of everything else
   constexpr int HOLD = GN ? gn_hold(VN) : 1;
-  V held[HOLD];
+  u32x4 held[HOLD];
   float g_gain[GN ? VN : 1], g_offset[GN ? VN : 1];
-  int g_px = 0, g_channel = 0, g_first = 0, g_nb = 0, g_lo = 0, g_hi = 0;
+  int g_px = 0, g_channel = 0, g_first = 0, g_pixels = 0, g_lo = 0, g_hi = 0;
   if constexpr (GN) {
     const int m_last = min(m0 + BM, p.M) - 1, z0 = (int)fast_div((unsigned)m0, p.div_hw), reach = p.ws + 1;
     g_first = z0 * p.hw_out;
-    g_nb = (int)fast_div((unsigned)m_last, p.div_hw) - z0 + 1;
-    g_lo = max(m0 - reach, g_first); g_hi = min(m_last + reach + 1, g_first + g_nb * p.hw_out);
-    g_px = lane >> p.gn_log_vps;
-    g_channel = (((wave << p.gn_log_vps) + (lane & ((1 << p.gn_log_vps) - 1)))) * VN;
+    g_pixels = ((int)fast_div((unsigned)m_last, p.div_hw) - z0 + 1) * p.hw_out;
+    g_lo = max(m0 - reach, g_first); g_hi = min(m_last + reach + 1, g_first + g_pixels);
+    g_px = gn_pixel(lane, p.gn.log_vps);
+    g_channel = (((wave << p.gn.log_vps) + (lane & ((1 << p.gn.log_vps) - 1)))) * VN;
     const bool second = g_channel >= p.c0;
     const T* src = second ? (const T*)p.src1 + (g_channel - p.c0) : (const T*)p.src0 + g_channel;
-    const int ld = second ? p.c1 : p.c0, step = 64 >> p.gn_log_vps;
+    const int ld = second ? p.c1 : p.c0, step = 64 >> p.gn.log_vps;
+    int at = 0, slot = 0;                                // the samples one after the other, each from lane 0 on
 #pragma unroll
-    for (int k = 0; k < HOLD; ++k)
-      if (g_px + k * step < g_nb * p.hw_out) held[k] = *(const V*)(src + (size_t)(g_first + g_px + k * step) * ld);
+    for (int k = 0; k < HOLD; ++k) {
+      const int in_sample = g_px + slot * step;
+      // a lane without a pixel loads the first one: without branches all loads go out one after the other
+      if (at < g_pixels) held[k] = *(const u32x4*)(src + (size_t)(g_first + (in_sample < p.gn.pixels && at + in_sample < g_pixels ? at + in_sample : 0)) * ld);
+      if (++slot == p.gn.slots) { slot = 0; at += p.gn.pixels; }
+    }
 #pragma unroll
     for (int e = 0; e < VN; e += 4) {
       const f32x4 g = *(const f32x4*)(p.ln_gain + g_channel + e), o = *(const f32x4*)(p.ln_offset + g_channel + e);
@@ -1273,7 +1418,7 @@ __global__ __launch_bounds__(512) void k_igemm_small(IgemmParams p) {
       for (int h = 0; h < 2; ++h) xa[i][h] = buffer_load16<V>(rx, o + h * 64, sc);
     }
   };
-  if constexpr (XTRA)
+  if constexpr (XTRA && !GN)
     if (x_first < x_tiles) fetch_extra(x_first);
 
   // what the epilogue adds.  A thread of it finishes four consecutive columns of a row, or, for transposed outputs, four
@@ -1318,7 +1463,9 @@ __global__ __launch_bounds__(512) void k_igemm_small(IgemmParams p) {
   char* const act = lds + NW * BM * PITCH * 4;
   unsigned g_at[TM];
   if constexpr (GN) {
-    gn_stage<T, HOLD>(p, held, g_gain, g_offset, g_first, g_nb, g_px, g_channel, g_lo, g_hi, act);
+    gn_stage<T, HOLD>(p, held, g_gain, g_offset, g_first, g_pixels, g_px, g_channel, g_lo, g_hi, act);
+    if constexpr (XTRA)
+      if (x_first < x_tiles) fetch_extra(x_first);
 #pragma unroll
     for (int i = 0; i < TM; ++i) {                       // pixel of tap (0, 0), modulo 2^32 where it lies before the staged ones (the tap is masked then)
       const int m = m0 + 16 * i + r16;
@@ -1471,6 +1618,28 @@ __global__ __launch_bounds__(512) void k_igemm_small(IgemmParams p) {
 
 // samples that the rows of a tile belong to at the most
 static int gn_samples(int bm, int batch, int hw) { return std::min(batch, hw % bm == 0 ? 1 : (bm - 2) / hw + 2); }
+// How a workgroup of bm rows holds them: every sample from lane 0 on, since k_gn_group adds its pixels up by their place in it, or several samples of a power of two of
+// pixels in an access; slots 0 where that does not fit.  A wavefront takes an eighth of the channels: whole groups, whole accesses, powers of two.
+static GnLayout gn_layout(int vn, int bm, int batch, int hw, int c, int groups) {
+  GnLayout g{};
+  if (groups < 8 || groups % 8 || c % (2 * groups) || c % (8 * vn)) return g;
+  const int cpg = c / groups, vps = c / (8 * vn), hold = gn_hold(vn);
+  if ((vps & (vps - 1)) || vps > 16 || (cpg & (cpg - 1)) || cpg > 4 * vn) return g;
+  while (1 << g.log_vps < vps) ++g.log_vps;
+  g.vpp = std::max(1, cpg / vn);
+  g.per_access = std::max(1, vn / cpg);
+  g.run = vps / g.vpp;
+  if (g.run > 8) return g;
+  const int step = 64 / vps, all = gn_samples(bm, batch, hw) * hw;
+  g.pixels = hw < step && (hw & (hw - 1)) == 0 ? step : hw;
+  while (1 << g.bits < std::min(hw, step)) ++g.bits;
+  const int accesses = (g.pixels + step - 1) / step, blocks = (all + g.pixels - 1) / g.pixels;
+  g.chained = accesses > 4 * g.run;
+  if (g.chained && g.per_access > 1) return g;
+  for (int slots : {hold / 5, hold / 2, hold})
+    if (accesses <= slots && blocks * slots <= hold) { g.slots = slots; break; }
+  return g;
+}
 template <typename T, int TM, int TN, int MODE, int NORM = NORM_NONE, bool XTRA = false>
 static ad_status run_igemm_small(const IgemmParams& p0, const char* name, hipStream_t s) {
   constexpr bool LN = NORM == NORM_LAYER;
@@ -1991,19 +2160,18 @@ bool conv_takes_ln(int dtype, long long m, int n, int c, int out_mode) {
   return c / bk <= small_ktiles(16 * t.tm, 16 * t.tn);
 }
 
-// A small-tile launch whose threads hold at most 40 elements each: what a workgroup does for the norm grows with the samples it takes in, the launch that it
-// saves does not.  us (norm + convolution / one launch): two samples of 24x24 of 64 bf16 channels (72 elements) 3.9 + 4.3 / 10.4, 16x16 of 128 (64) 3.7 + 5.0 / 8.8,
-// 12x12 of 128 (36) 3.7 + 5.5 / 7.3, 16x16 of 64 (32) 3.8 + 4.0 / 8.2 in a chain that is one gap shorter.  Channels that a power of two of accesses covers (not 192 or 384).
+// A small-tile launch that takes in at most 40 elements a thread: what a workgroup does for the norm grows with the samples it takes in, the launch that it
+// saves does not.  us (norm + convolution / one launch): 12x12 of 128 bf16 channels (36 elements) 3.7 + 4.8 / 8.9 in a chain that is one gap shorter; beyond the line, with the
+// cheaper sums named above the kernel: two samples of 24x24 of 64 (72) 3.9 + 4.3 / 10.4, 16x16 of 128 (64) 3.7 + 5.0 / 8.8.  Channels that a power of two of accesses covers (not 192
+// or 384), and samples that gn_layout() can arrange: 257 to 320 pixels of groups of two or four channels it cannot, nor more than six samples of 3, 5, ... pixels.
 bool conv_takes_gn(int dtype, int batch, int h, int w, int c0, int c1, int n, int groups, int out_mode, int xc) {
   const int c = c0 + c1, bk = bk_elems(dtype), es = (int)esize(dtype), vn = 16 / es, hw = h * w;
-  if ((out_mode != OUT_ROWMAJOR && out_mode != OUT_TRANSPOSED_F32) || c0 % bk || c1 % bk || groups < 8 || groups % 8 || c % (2 * groups)) return false;
-  const int cpg = c / groups, vps = c / (8 * vn);         // a wavefront takes an eighth of the channels: whole groups, whole accesses, powers of two
-  if (c % (8 * vn) || (vps & (vps - 1)) || vps > 16 || (cpg & (cpg - 1)) || cpg > 4 * vn) return false;
+  if ((out_mode != OUT_ROWMAJOR && out_mode != OUT_TRANSPOSED_F32) || c0 % bk || c1 % bk) return false;
   const long long m = (long long)batch * hw;
   if (choose_plan(dtype, m, n, (9 * c + xc) / bk, out_mode).tile != TILE_SMALL) return false;
   const SmallTile t = small_tile(dtype, m, n, (9 * c + xc) / bk, out_mode);
   const int bm = 16 * t.tm;
-  return (long long)gn_samples(bm, batch, hw) * hw <= gn_hold(vn) * (64 / vps) &&
+  return gn_layout(vn, bm, batch, hw, c, groups).slots > 0 && (long long)gn_samples(bm, batch, hw) * hw * c <= 8 * 64 * 40 &&
          8 * bm * (16 * t.tn + 4) * 4 + gn_act_bytes(bm, w, c * es) <= (int)kLdsLimit;
 }
 
@@ -2053,7 +2221,7 @@ ad_status launch_conv(const ConvArgs& a, hipStream_t s) {
   p.out2 = a.out2; p.out3 = a.out3;
   p.ahead = a.ahead; p.ahead_bytes = a.ahead ? (unsigned)std::min<size_t>(a.ahead_bytes, 0x7fffffff) : 0;
   p.ln_gain = a.ln_gain; p.ln_offset = a.ln_offset; p.ln_eps = a.ln_eps;
-  p.gn_groups = a.gn_groups; p.gn_silu = a.gn_silu;
+  p.gn_groups = a.gn_groups;
   if (a.gn_groups) {
     const char *o = (const char*)a.out, *s0 = (const char*)a.src0, *s1 = (const char*)a.src1;
     const size_t es = esize(a.dtype), out_bytes = (size_t)m * a.n_out * (a.out_mode == OUT_TRANSPOSED_F32 ? 4 : es), px = (size_t)a.batch * a.hs * a.ws;
@@ -2061,10 +2229,8 @@ ad_status launch_conv(const ConvArgs& a, hipStream_t s) {
     if (!a.ln_gain || !a.ln_offset || a.ksize != 3 || a.stride != 1 || a.up || !apart || ((uintptr_t)s0 & 15) || (a.c1 && ((uintptr_t)s1 & 15)) ||
         !conv_takes_gn(a.dtype, a.batch, a.hs, a.ws, a.c0, a.c1, a.n_out, a.gn_groups, a.out_mode, p.xc0 + p.xc1))
       AD_FAIL(AD_ERR_INVALID, "conv: bad GroupNorm");
-    p.gn_log_vps = 0;
-    p.gn_cpg = p.ctot / a.gn_groups;
-    p.gn_inv_n = 1.0 / ((double)p.hw_out * p.gn_cpg);
-    while ((8 * (16 / (int)es)) << p.gn_log_vps < p.ctot) ++p.gn_log_vps;
+    p.gn = gn_layout(16 / (int)es, 16 * small_tile(a.dtype, m, a.n_out, p.ktiles, a.out_mode).tm, a.batch, p.hw_out, p.ctot, a.gn_groups);
+    p.gn_inv_n = 1.0 / ((double)p.hw_out * (p.ctot / a.gn_groups));
   }
   if (!a.gn_groups && a.ln_gain && (!a.ln_offset || a.ksize != 1 || a.stride != 1 || a.up || a.c1 || a.residual || a.rowvec || a.xw || (((uintptr_t)a.ln_gain | (uintptr_t)a.ln_offset) & 15) ||
                     !conv_takes_ln(a.dtype, m, a.n_out, a.c0, a.out_mode)))
@@ -3516,27 +3682,23 @@ __global__ __launch_bounds__(NT) void k_gn_group(const T* __restrict__ src0, con
   s = 0.f;
 #pragma unroll
   for (int w = 0; w < NT / 64; ++w) s += red[0][w];
-  float about = __uint_as_float(__float_as_uint(s * (float)inv_n) & 0xfffff000u);
+  float about = gn_about(s, inv_n);
   s = 0.f;
 #pragma unroll
   for (int k = 0; k < NV; ++k)
     if (lanep + k * pl < p_end)
 #pragma unroll
-      for (int e = 0; e < G; ++e) { const float d = to_f(x[k][e]) - about; s += d; q += d * d; }
+      for (int e = 0; e < G; ++e) gn_add(to_f(x[k][e]), about, s, q);
   s = wave_sum_rows(s); q = wave_sum_rows(q);
   if (lane == 0) { red[1][wave] = s; red[2][wave] = q; }
   __syncthreads();
   double ds = 0.0, dq = 0.0;
 #pragma unroll 4
   for (int w = 0; w < NT / 64; ++w) { ds += red[1][w]; dq += red[2][w]; }
-  const double rest = ds * inv_n;                        // mean - about
-  double var = dq * inv_n - rest * rest;
-  var = (var < 0.0 ? 0.0 : var) + (double)eps;
-  // 1 / sqrt(var): one Newton step on the fp32 value, a fifth of the instructions of the double division and root
-  const float r0 = rsqrtf((float)var);
-  const float rstd = (float)(var > 1e-30 && var < 1e30 ? r0 * (1.5 - 0.5 * var * r0 * r0) : 1.0 / sqrt(var)), shift = (float)rest;
+  float rstd, rest;
+  gn_moments(ds, dq, inv_n, eps, rstd, rest);
 #pragma unroll
-  for (int e = 0; e < G; ++e) { ga[e] *= rstd; be[e] -= shift * ga[e]; }
+  for (int e = 0; e < G; ++e) { ga[e] *= rstd; be[e] = fmaf(-rest, ga[e], be[e]); }
   asm volatile("" : "+v"(about));                        // x - about is formed anew: kept from the sums on, 48 elements would not fit
 #pragma unroll
   for (int k = 0; k < NV; ++k) {
@@ -3545,7 +3707,7 @@ __global__ __launch_bounds__(NT) void k_gn_group(const T* __restrict__ src0, con
       V o;
 #pragma unroll
       for (int e = 0; e < G; ++e) {
-        float y = (to_f(x[k][e]) - about) * ga[e] + be[e];
+        float y = gn_value(to_f(x[k][e]), about, ga[e], be[e]);
         if (silu) y = silu_f(y);
         o[e] = from_f<T>(y);
       }

@@ -107,20 +107,20 @@ struct Eval {
   }
   // whether a caller's tensors share no memory: a launch whose workgroups read what others do not write needs that
   static bool apart(const void* a, size_t a_bytes, const void* b, size_t b_bytes) { return !a || (const char*)a + a_bytes <= (const char*)b || (const char*)b + b_bytes <= (const char*)a; }
-  // a convolution (stride 1) behind a GroupNorm of its input (gain and offset at g_idx), in one launch where it takes the norm in
-  ad_status gn_conv(const void* src0, const void* src1, int c0, int c1, int h, int w, int g_idx, int silu, int w_idx, const float* rowvec, const void* residual,
+  // a convolution (stride 1) behind a GroupNorm and SiLU of its input (gain and offset at g_idx), in one launch where it takes them in
+  ad_status gn_conv(const void* src0, const void* src1, int c0, int c1, int h, int w, int g_idx, int w_idx, const float* rowvec, const void* residual,
                     void* dst, int mode, int ld_t, Next behind) const {
     WView wv{c};
     const size_t px = (size_t)c.cfg.batch * h * w, es = esize(dt), out_bytes = px * c.weights[w_idx].info.shape[0] * (mode == OUT_TRANSPOSED_F32 ? 4 : es);
     const bool at16 = (((uintptr_t)src0 | (uintptr_t)src1) & 15) == 0;      // a caller's tensors may begin anywhere
     if (!at16 || !conv_takes_gn(dt, c.cfg.batch, h, w, c0, c1, c.weights[w_idx].info.shape[0], c.cfg.gn_groups, mode) || !apart(src0, px * c0 * es, dst, out_bytes) ||
         !apart(src1, px * c1 * es, dst, out_bytes)) {
-      AD_TRY(gn(src0, src1, c0, c1, h * w, g_idx, silu, temp(0)));
+      AD_TRY(gn(src0, src1, c0, c1, h * w, g_idx, 1, temp(0)));
       return conv(temp(0), nullptr, c0 + c1, 0, h, w, 0, 3, 1, w_idx, w_idx + 1, rowvec, residual, dst, mode, ld_t, behind);
     }
     ConvArgs a{dt, src0, src1, c0, c1, c.cfg.batch, h, w, 0, 3, 1, wv.at(w_idx), c.weights[w_idx].info.shape[0], wv.f32(w_idx + 1), rowvec, proj_ld, residual, dst, mode, ld_t};
     a.ln_gain = wv.f32(g_idx); a.ln_offset = wv.f32(g_idx + 1); a.ln_eps = c.cfg.gn_eps;
-    a.gn_groups = c.cfg.gn_groups; a.gn_silu = silu;
+    a.gn_groups = c.cfg.gn_groups;
     a.w_blocks = 1;
     return launch_conv(a, s);
   }
@@ -152,7 +152,7 @@ struct Eval {
     // manifest order: gn1.g gn1.b conv1.w conv1.b temb.w temb.b gn2.g gn2.b conv2.w conv2.b [short.w short.b]
     // conv1 adds this block's slice of the fused time projection per (sample, channel)
     const float* rowvec = proj + (u.temb_row - cp.temb_row0);
-    AD_TRY(gn_conv(x0, x1, f.c_in, f.c_skip, f.h_in, f.w_in, w0 + 0, 1, w0 + 2, rowvec, nullptr, temp(1), OUT_ROWMAJOR, 0, {ui, w0 + 8}));
+    AD_TRY(gn_conv(x0, x1, f.c_in, f.c_skip, f.h_in, f.w_in, w0 + 0, w0 + 2, rowvec, nullptr, temp(1), OUT_ROWMAJOR, 0, {ui, w0 + 8}));
     const void* shortcut = x0;
     const size_t px = (size_t)c.cfg.batch * hw * esize(dt);
     if (ci != f.c_out && conv_takes_shortcut(dt, (long long)c.cfg.batch * hw, f.c_out, f.c_out, ci) && apart(x0, px * f.c_in, tensor_out(ui), px * f.c_out) &&
@@ -164,7 +164,7 @@ struct Eval {
                  nullptr, tensor_out(ui), OUT_ROWMAJOR, 0, temp(9), ws.temp_bytes[9]};
       a.x0 = x0; a.x1 = x1; a.xc0 = f.c_in; a.xc1 = f.c_skip; a.xw = wv.at(w0 + 10);
       a.w_blocks = 1;
-      if (norm_in) { a.ln_gain = wv.f32(w0 + 6); a.ln_offset = wv.f32(w0 + 7); a.ln_eps = c.cfg.gn_eps; a.gn_groups = c.cfg.gn_groups; a.gn_silu = 1; }
+      if (norm_in) { a.ln_gain = wv.f32(w0 + 6); a.ln_offset = wv.f32(w0 + 7); a.ln_eps = c.cfg.gn_eps; a.gn_groups = c.cfg.gn_groups; }
       ask_ahead(a, {ui + 1, kFirst});
       return launch_conv(a, s);
     }
@@ -172,7 +172,7 @@ struct Eval {
       AD_TRY(conv(x0, x1, f.c_in, f.c_skip, f.h_in, f.w_in, 0, 1, 1, w0 + 10, w0 + 11, nullptr, nullptr, temp(2)));
       shortcut = temp(2);
     }
-    return gn_conv(temp(1), nullptr, f.c_out, 0, f.h_in, f.w_in, w0 + 6, 1, w0 + 8, nullptr, shortcut, tensor_out(ui), OUT_ROWMAJOR, 0, {ui + 1, kFirst});
+    return gn_conv(temp(1), nullptr, f.c_out, 0, f.h_in, f.w_in, w0 + 6, w0 + 8, nullptr, shortcut, tensor_out(ui), OUT_ROWMAJOR, 0, {ui + 1, kFirst});
   }
   // cross-attention key / value projections of the text embedding for the layer whose weights start at w
   ad_status text_kv(int w, void* kdst, void* vdst) const {
@@ -356,7 +356,7 @@ static ad_status run_component(Ctx& c, int comp, int lane, const void* const* in
         AD_TRY(e.conv(e.tensor_in(ui - 1), nullptr, f.c_in, 0, f.h_in, f.w_in, 1, 3, 1, u.w_first, u.w_first + 1, nullptr, nullptr, e.tensor_out(ui), OUT_ROWMAJOR, 0, {ui + 1, Eval::kFirst}));
         break;
       case AD_UNIT_OUT:
-        AD_TRY(e.gn_conv(e.tensor_in(ui - 1), nullptr, f.c_in, 0, f.h_in, f.w_in, u.w_first, 1, u.w_first + 2, nullptr, nullptr, e.tensor_out(ui), OUT_TRANSPOSED_F32,
+        AD_TRY(e.gn_conv(e.tensor_in(ui - 1), nullptr, f.c_in, 0, f.h_in, f.w_in, u.w_first, u.w_first + 2, nullptr, nullptr, e.tensor_out(ui), OUT_TRANSPOSED_F32,
                          f.h_out * f.w_out, Eval::kNone));
         break;
     }

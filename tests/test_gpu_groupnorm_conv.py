@@ -5,7 +5,7 @@ import pytest
 import torch
 import torch.nn.functional as F
 
-from gpu_util import DEV, dev, quantize, rel_l2
+from gpu_util import DEV, dev, dev_bytes, dev_f32, p, quantize, rel_l2, stream_ptr
 from paper_2406_06911_amd import binding as B
 from test_gpu_resblocks import check_blocks
 
@@ -14,7 +14,7 @@ pytestmark = pytest.mark.gpu
 
 def config(channels, height, width, batch, groups):
     return dict(latent_channels=4, height=height, width=width, batch=batch, channels=channels, layers_per_block=1, transformer_depth=[0] * len(channels), mid_depth=0,
-                head_dim=64, gn_groups=groups, ctx_len=8, ctx_dim=64, pooled_dim=0)
+                head_dim=64, gn_groups=groups, ctx_len=8, ctx_dim=64, pooled_dim=0, frames=batch if batch > 2 else 0, temporal_heads=8 if batch > 2 else 0)
 
 
 def head(d, dtype, x, gain, offset, w, bias):
@@ -181,3 +181,88 @@ def test_a_sample_that_is_not_finite(dtype, c, size, value):
         got, _ = head(d, dtype, dev(broken, dtype), gain, offset, w, bias)
         assert np.array_equal(got[1 - z], want[1 - z])
         assert np.isnan(got[z]).all()
+
+
+def by_launches(d, dtype, x, gain, offset, w, bias):
+    """The head from the single-kernel entry points, a launch for the norm."""
+    n, h, wd, c = x.shape
+    y = torch.empty_like(x)
+    scratch = torch.zeros(B.lib.ad_groupnorm_scratch_bytes(n, h * wd, c) // 4 + 4, device=DEV)
+    g, o, b = dev_f32(gain), dev_f32(offset), dev_f32(np.concatenate([bias, np.zeros(124, np.float32)]))
+    B.check(B.lib.ad_groupnorm_forward(dtype, p(x), None, c, 0, n, h * wd, d["gn_groups"], p(g), p(o), 1e-5, 1, p(y), p(scratch), stream_ptr()))
+    wp, out = dev_bytes(B.pack_conv_weight(dtype, w)), torch.full((n, 4, h, wd), float("nan"), device=DEV)
+    B.check(B.lib.ad_conv_forward(dtype, p(y), None, c, 0, n, h, wd, 0, 3, 1, p(wp), 4, p(b), None, None, p(out), None, None, B.OUT_TRANSPOSED_F32, h * wd, None, 0, stream_ptr()))
+    torch.cuda.synchronize()
+    return out.cpu().numpy().astype(np.float64)
+
+
+def on_a_boundary(rng, shape, groups, mean):
+    """Groups whose mean is a number of few bits: sums of it that differ in their last bit are cut off to different 12 bits."""
+    n, h, w, c = shape
+    x = rng.standard_normal((n, h * w, groups, c // groups))
+    return (x - x.mean(axis=(1, 3), keepdims=True) + mean).reshape(shape).astype(np.float32)
+
+
+# every arrangement of samples in the lanes: one sample, two, three; sizes of a power of two side by side; more than 256 accesses of a group (16x20, 24x24, 17x18)
+SAME_BITS = [s[:6] for s in SHAPES if s[6]] + [
+    (B.AD_BF16, 64, 16, 16, 1, 32), (B.AD_BF16, 128, 8, 8, 2, 32), (B.AD_BF16, 256, 3, 3, 4, 32), (B.AD_BF16, 256, 2, 2, 16, 32), (B.AD_BF16, 256, 1, 1, 16, 32), (B.AD_BF16, 128, 2, 4, 5, 32),
+    (B.AD_BF16, 256, 5, 8, 2, 32), (B.AD_BF16, 256, 4, 4, 3, 8), (B.AD_BF16, 256, 6, 6, 2, 16), (B.AD_BF16, 128, 12, 13, 1, 8), (B.AD_BF16, 256, 6, 6, 1, 64),
+    (B.AD_F32, 32, 24, 24, 1, 8), (B.AD_F32, 64, 17, 18, 1, 8), (B.AD_F32, 32, 17, 17, 2, 8), (B.AD_F32, 64, 8, 8, 2, 16), (B.AD_F32, 256, 3, 3, 3, 32), (B.AD_F32, 256, 2, 1, 8, 32), (B.AD_F32, 128, 6, 7, 2, 8),
+    (B.AD_F32, 256, 6, 6, 2, 64), (B.AD_F32, 32, 1, 1, 7, 8)]
+
+
+@pytest.mark.parametrize("kind", ["plain", "boundary", "offset", "huge"])
+@pytest.mark.parametrize("dtype,c,height,width,batch,groups", SAME_BITS)
+def test_same_bits_as_a_launch_for_the_norm(dtype, c, height, width, batch, groups, kind):
+    d = config([c], height, width, batch, groups)
+    rng = np.random.default_rng(29 + c + height)
+    shape = (batch, height, width, c)
+    x = on_a_boundary(rng, shape, groups, 8.0) if kind == "boundary" else rng.standard_normal(shape)
+    if kind == "offset":
+        x = x + 100.0 * rng.standard_normal(c)
+    if kind == "huge":
+        x = 7e17 * x
+    x = dev(quantize(x, dtype), dtype)
+    gain, offset = (1 + 0.3 * rng.standard_normal(c)).astype(np.float32), (0.3 * rng.standard_normal(c)).astype(np.float32)
+    w, bias = quantize(rng.standard_normal((4, c, 3, 3)) * (9 * c) ** -0.5, dtype), rng.standard_normal(4).astype(np.float32)
+    got, names = head(d, dtype, x, gain, offset, w, bias)
+    assert not any(n.startswith("gn_") for n in names), names
+    want = by_launches(d, dtype, x, gain, offset, w, bias)
+    assert np.isfinite(got).all() and np.array_equal(got, want), rel_l2(got, want)
+
+
+def picked(d, dtype, x, gain, offset, channels):
+    """The normalised values of four channels, as they are: the head's weights take a channel each, at the middle tap."""
+    w = np.zeros((4, x.shape[3], 3, 3), np.float32)
+    w[np.arange(4), channels, 1, 1] = 1
+    got, names = head(d, dtype, dev(x, dtype), gain, offset, w, np.zeros(4, np.float32))
+    assert not any(n.startswith("gn_") for n in names), names
+    t = torch.from_numpy(x).double().permute(0, 3, 1, 2)
+    ref = F.silu(F.group_norm(t, d["gn_groups"], torch.from_numpy(gain).double(), torch.from_numpy(offset).double(), 1e-5))
+    return got, ref[:, list(channels)].numpy()
+
+
+@pytest.mark.parametrize("mean", [1.0, 8.0, 100.0])
+@pytest.mark.parametrize("c,size,groups", [(32, 16, 8), (64, 12, 8), (128, 12, 32)])
+def test_fp32_means_on_a_boundary_of_twelve_bits(c, size, groups, mean):
+    """Every lane has to take the same number off the values of a group before their squares are summed."""
+    d, rng = config([c], size, size, 1, groups), np.random.default_rng(31)
+    ones, zeros = np.ones(c, np.float32), np.zeros(c, np.float32)
+    for i in range(8):
+        x = on_a_boundary(rng, (1, size, size, c), groups, mean)
+        channels = rng.permutation(groups)[:4] * (c // groups)
+        got, ref = picked(d, B.AD_F32, x, ones, zeros, channels)
+        # a value of up to 5: ten roundings, 6e-8 each; the mean of up to 1024 deviations, each exact but for one rounding
+        assert np.abs(got - ref).max() < 5e-6, (i, np.abs(got - ref).max())
+
+
+@pytest.mark.parametrize("dtype,c,size,groups", [(B.AD_F32, 32, 16, 8), (B.AD_BF16, 64, 16, 8)])
+def test_squares_whose_sum_is_beyond_fp32(dtype, c, size, groups):
+    """7e17 squared 1024 or 2048 times: beyond fp32 in all, not in a quarter of them.  The norm has a value, not its offset."""
+    d, rng = config([c], size, size, 1, groups), np.random.default_rng(37)
+    scale = 7e17 if dtype == B.AD_F32 else 5e17
+    x = quantize(scale * rng.choice([-1.0, 1.0], (1, size, size, c)), dtype)
+    ones, zeros = np.ones(c, np.float32), np.zeros(c, np.float32)
+    got, ref = picked(d, dtype, x, ones, zeros, rng.permutation(groups)[:4] * (c // groups))
+    # fp32: as above.  bf16: one rounding of the operand, 2^-9
+    assert np.abs(got - ref).max() < (4e-3 if dtype == B.AD_BF16 else 5e-6), np.abs(got - ref).max()
