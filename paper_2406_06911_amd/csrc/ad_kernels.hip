@@ -1050,9 +1050,21 @@ __device__ __forceinline__ void ln_stats(const IgemmParams& p, int sub, const ty
 
 constexpr int gn_pitch(int row_bytes) { return row_bytes + 16; }      // of a pixel in LDS: 16 neighbouring pixels fall on different banks
 constexpr int gn_act_bytes(int bm, int ws, int row_bytes) { return 256 + (bm + 2 * (ws + 1)) * gn_pitch(row_bytes); }
-// What k_gn_group and a convolution with the norm inside have in common, with the products fused as written: an element's deviation added to the sums, what
-// the sums make of a group, and the norm of an element.  sum: of the deviations from `about`; rest: what the mean is beyond that.
-__device__ __forceinline__ void gn_add(float x, float about, float& s, float& q) { const float d = x - about; s += d; q = fmaf(d, d, q); }
+// What k_gn_group and a convolution with the norm inside have in common, with the products fused as written: the deviations of a group's channels in an access, FROM and
+// the PER - 1 behind it, added to a thread's sums (first: there are none yet), what the sums make of a group, and the norm of an element.  sum: of the deviations
+// from `about`; rest: what the mean is beyond that.
+template <int FROM, int PER, typename V>
+__device__ __forceinline__ void gn_add(const V& x, float about, float& s, float& q, bool first) {
+  float d[PER];
+#pragma unroll
+  for (int e = 0; e < PER; ++e) { d[e] = to_f(x[FROM + e]) - about; s += d[e]; }
+  constexpr int NEXT = PER > 1 ? 1 : 0;
+  if (PER > 1 && first) q = fmaf(d[0], d[0], d[NEXT] * d[NEXT]);
+  else q = fmaf(d[0], d[0], q);
+#pragma unroll
+  for (int e = 1; e < PER; ++e)
+    if (e > 1 || !first) q = fmaf(d[e], d[e], q);
+}
 __device__ __forceinline__ void gn_moments(double sum, double squares, double inv_n, float eps, float& rstd, float& rest) {
   const double mean = sum * inv_n;
   double var = fma(inv_n, squares, -(mean * mean));
@@ -1178,6 +1190,11 @@ __device__ __forceinline__ void gn_stats(const IgemmParams& p, const GnLayout& g
 #pragma unroll
       for (int k = 0; k < S; ++k) v[g][k] = 0.f;
   };
+  static_assert(GP <= 2, "groups that all_groups() visits");
+  auto all_groups = [&](auto visit) {
+    visit(std::integral_constant<int, 0>{});
+    if constexpr (GP > 1) visit(std::integral_constant<int, 1>{});
+  };
   clear(s);
 #pragma unroll
   for (int k = 0; k < S; ++k)
@@ -1198,8 +1215,7 @@ __device__ __forceinline__ void gn_stats(const IgemmParams& p, const GnLayout& g
   for (int k = 0; k < S; ++k)
     each(k, [&](int j) {
       if (px + j * step < left)
-#pragma unroll
-        for (int e = 0; e < CN; ++e) gn_add(to_f(__builtin_bit_cast(V, x[j])[e]), about[e], s[e / PER][k], q[e / PER][k]);
+        all_groups([&](auto g) { gn_add<decltype(g)::value * PER, PER>(__builtin_bit_cast(V, x[j]), about[decltype(g)::value * PER], s[decltype(g)::value][k], q[decltype(g)::value][k], j == k); });
     });
   gn_lanes(gn, s);
   gn_lanes(gn, q);
@@ -3686,9 +3702,7 @@ __global__ __launch_bounds__(NT) void k_gn_group(const T* __restrict__ src0, con
   s = 0.f;
 #pragma unroll
   for (int k = 0; k < NV; ++k)
-    if (lanep + k * pl < p_end)
-#pragma unroll
-      for (int e = 0; e < G; ++e) gn_add(to_f(x[k][e]), about, s, q);
+    if (lanep + k * pl < p_end) gn_add<0, G>(x[k], about, s, q, k == 0);
   s = wave_sum_rows(s); q = wave_sum_rows(q);
   if (lane == 0) { red[1][wave] = s; red[2][wave] = q; }
   __syncthreads();

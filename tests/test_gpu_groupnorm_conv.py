@@ -266,3 +266,64 @@ def test_squares_whose_sum_is_beyond_fp32(dtype, c, size, groups):
     got, ref = picked(d, dtype, x, ones, zeros, rng.permutation(groups)[:4] * (c // groups))
     # fp32: as above.  bf16: one rounding of the operand, 2^-9
     assert np.abs(got - ref).max() < (4e-3 if dtype == B.AD_BF16 else 5e-6), np.abs(got - ref).max()
+
+
+def replay(x, gain, offset, per):
+    """One group of one sample, x [pixels][channels] fp32, as k_gn_group adds it up: thread t of 256 takes the access of `per` channels t % vpp of pixels t // vpp, + 256 // vpp, ...,
+    the first two squares fused as a0 a0 + (a1 a1), the lanes of a wavefront pairwise, the wavefronts in order, in double for the deviations."""
+    f32, f64 = np.float32, np.float64
+    hw, c = x.shape
+    vpp = c // per
+    fma = lambda a, b, z: (f64(a) * f64(b) + f64(z)).astype(f32)      # the product is exact in 64 bits
+    rounds = -(-hw * vpp // 256)
+    held = np.zeros((rounds * 256, per), f32)
+    held[:hw * vpp] = x.reshape(hw * vpp, per)
+    live = (np.arange(rounds * 256) < hw * vpp).reshape(rounds, 256)
+    held = held.reshape(rounds, 256, per)
+
+    def lanes(v):
+        v = v.reshape(4, 64)
+        while v.shape[1] > 1:
+            v = v[:, ::2] + v[:, 1::2]
+        return v[:, 0]
+
+    s = np.zeros(256, f32)
+    for r in range(rounds):
+        for e in range(per):
+            s = s + held[r, :, e]
+    total = f32(0)
+    for v in lanes(s):
+        total = total + v
+    about = (np.array([total * f32(1.0 / (hw * c))], f32).view(np.uint32) & np.uint32(0xfffff000)).view(f32)[0]
+    s, q = np.zeros(256, f32), np.zeros(256, f32)
+    for r in range(rounds):
+        d = np.where(live[r][:, None], held[r] - about, f32(0))
+        for e in range(per):
+            s = s + d[:, e]
+        q = fma(d[:, 0], d[:, 0], d[:, 1] * d[:, 1] if r == 0 else q)
+        for e in range(2 if r == 0 else 1, per):
+            q = fma(d[:, e], d[:, e], q)
+    more = np.sum(lanes(s).astype(f64)) * (1.0 / (hw * c))
+    var = np.sum(lanes(q).astype(f64)) * (1.0 / (hw * c)) - more * more + f64(f32(1e-5))
+    ga = gain * f32(1 / np.sqrt(var))
+    return fma(x - about, ga, fma(-f32(more), ga, offset))
+
+
+@pytest.mark.parametrize("c,hw,groups", [(64, 36, 16), (64, 144, 32), (128, 300, 16), (32, 256, 8), (256, 90, 16)])
+def test_order_of_the_sums_of_the_norm_by_itself(c, hw, groups):
+    """The norm's own kernel keeps its bits: what is compared with it elsewhere would not show that it changed."""
+    rng = np.random.default_rng(43)
+    x = (rng.standard_normal((2, hw, c)) + 3).astype(np.float32)
+    gain, offset = (1 + 0.3 * rng.standard_normal(c)).astype(np.float32), (0.3 * rng.standard_normal(c)).astype(np.float32)
+    d, g, o = dev_f32(x), dev_f32(gain), dev_f32(offset)
+    out, scratch = torch.empty_like(d), torch.zeros(B.lib.ad_groupnorm_scratch_bytes(2, hw, c) // 4 + 4, device=DEV)
+    B.check(B.lib.ad_groupnorm_forward(B.AD_F32, p(d), None, c, 0, 2, hw, groups, p(g), p(o), 1e-5, 0, p(out), p(scratch), stream_ptr()))
+    torch.cuda.synchronize()
+    got, cpg = out.cpu().numpy(), c // groups
+    differ = 0
+    for z in range(2):
+        for k in range(groups):
+            at = slice(k * cpg, (k + 1) * cpg)
+            differ += np.count_nonzero(replay(x[z][:, at], gain[at], offset[at], min(cpg, 4)) != got[z][:, at])
+    # the replay rounds twice where a kernel's fused product rounds once (one in 2^29), and takes 1 / sqrt exactly; another order of the sums is 1 to 10 %
+    assert differ <= 1e-3 * got.size, differ / got.size
