@@ -44,7 +44,7 @@ struct ConvArgs {
   void* out2 = nullptr; void* out3 = nullptr;   // OUT_QKV: columns [n/3, 2n/3) and [2n/3, n)
   int k_real = 0;                       // > 0: K without zero padding, for the profiler's FLOP count (the im2col'ed first convolution)
   // a 1x1 convolution of x0 (and x1, concatenated on channels) added to a 3x3 one at stride 1, as further k-tiles of the same launch; only
-  // where conv_takes_shortcut() says so
+  // where conv_takes_shortcut() says so.  rowvec is its bias (the small tiles add it before the sum takes the storage type, the others in fp32)
   const void* x0 = nullptr; const void* x1 = nullptr;
   int xc0 = 0, xc1 = 0;
   const void* xw = nullptr;             // packed [n_pad][xc0 + xc1]

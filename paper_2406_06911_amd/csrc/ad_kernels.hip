@@ -987,10 +987,10 @@ static ad_status run_igemm_p3(const IgemmParams& p0, const char* name, hipStream
 // Whole runs, a launch for every norm / this, ms, the same bits: tiny fp32 2.16 / 1.74, narrow 35.2 / 34.5, with stride 2 25.35 / 25.11, narrow fp32 12.93 / 12.28.  (With every
 // lane's sums over its own accesses, rotated within the row and folded in fp32, a launch took 1 to 1.5 us less, but lanes took different numbers off the values of a group
 // where their sums met a boundary of 12 bits (fp32 values up to 2e-2 off), and sums of squares beyond fp32 left the offset alone.)
-// XTRA: the 1x1 shortcut of a ResBlock as k-tiles behind the taps, as in k_igemm_p3: a launch of 3.7 to 4.3 us for 0.7 to 2 us. fp32 too. us (shortcut + second convolution ->
-// one): bf16 18x256 of 2304 + 512 4.2 + 8.1 -> 9.6, 72x256 4.2 + 7.7 -> 9.8, 288x128 of 1152 + 256 4.0 + 6.9 -> 7.6; fp32 256x32 of 288 + 96 3.7 + 6.7 -> 7.4, 18x256 of 2304 + 512
-// 4.8 + 10.2 -> 12.1. Launches of a step: tiny fp32 34 -> 29, narrow 204 -> 190, narrow fp32 223 -> 213. Whole runs, ms: tiny 1.89 -> 1.74, narrow 35.8 -> 34.0, with stride 2
-// 25.5 -> 24.7, narrow fp32 12.10 -> 11.84.
+// XTRA: the 1x1 shortcut of a ResBlock as k-tiles behind the taps, in sums of their own, which take the storage type before they are added: the bits of a launch for the
+// shortcut, whose sum is the residual.  (In one sum with the taps, as in k_igemm_p3, it saves 0.1 us, but bf16 runs differed by 4e-3 to 7e-3 from those with a launch.)  fp32 too.
+// us (norm + shortcut + second convolution -> one): bf16 18x256 of 2304 + 512 3.8 + 4.2 + 6.3 -> 10.3, 72x256 3.7 + 4.1 + 6.7 -> 11.7, 288x128 of 1152 + 256 3.7 + 3.8 + 4.9 ->
+// 9.1; fp32 256x32 of 288 + 96 3.6 + 3.6 + 4.3 -> 7.6.  Launches of a step: tiny fp32 34 -> 29, narrow 204 -> 190, narrow fp32 223 -> 213.
 // Taken back: statistics over all wavefronts through LDS, merged in double (4.3 us a launch), and 1x1 convolutions (72x256x256 3.7 + 3.9 -> 7.9).
 // Four k-tiles of fragments on their way instead of two are level (18x256x2304 8.5 / 8.7 us, fp32 10.4 / 10.7, fp32 72x2048x256 8.1 / 7.9; whole runs 0.993 to 1.003): what a CU
 // takes in at a time decides, not how early a wavefront asks.
@@ -1048,6 +1048,7 @@ __device__ __forceinline__ void ln_stats(const IgemmParams& p, int sub, const ty
   if (sub == 0) { *mean_out = mean; *rstd_out = rstd; }
 }
 
+constexpr int small_sum_bytes(int bm, int bn) { return 8 * bm * (bn + 4) * 4; }      // partial sums of the wavefronts of a small tile
 constexpr int gn_pitch(int row_bytes) { return row_bytes + 16; }      // of a pixel in LDS: 16 neighbouring pixels fall on different banks
 constexpr int gn_act_bytes(int bm, int ws, int row_bytes) { return 256 + (bm + 2 * (ws + 1)) * gn_pitch(row_bytes); }
 // What k_gn_group and a convolution with the norm inside have in common, with the products fused as written: the deviations of a group's channels in an access, FROM and
@@ -1413,7 +1414,7 @@ __global__ __launch_bounds__(512) void k_igemm_small(IgemmParams p) {
   for (int s = 0; s < PF; ++s)
     if (s < mine) fetch(s);
 
-  // XTRA: behind the taps the k-tiles of a 1x1 convolution of other sources, taken in turn as well; a wavefront's first one is asked for ahead of the loop
+  // XTRA: behind the taps the k-tiles of a 1x1 convolution of other sources, taken in turn as well; a wavefront's first one, x_first, is asked for ahead of the loop
   V xa[XTRA ? TM : 1][2], xb[XTRA ? TN : 1][2];
   const int x_tiles = p.ktiles - kt_taps, x_first = (wave + NW - kt_taps % NW) % NW;
   auto fetch_extra = [&](int e) {
@@ -1448,7 +1449,7 @@ __global__ __launch_bounds__(512) void k_igemm_small(IgemmParams p) {
   const int rl = by_column ? (tid % (BM / 4)) * 4 : tid / (BO / 4), cl = by_column ? tid / (BM / 4) : (tid % (BO / 4)) * 4;
   const int row = m0 + rl, col = n0 + cl;
   const bool live = tid < QUADS && row < p.M && (MODE == OUT_GEGLU || col < p.N);
-  float add[4] = {0.f, 0.f, 0.f, 0.f}, gate[4] = {0.f, 0.f, 0.f, 0.f};
+  float add[4] = {0.f, 0.f, 0.f, 0.f}, gate[4] = {0.f, 0.f, 0.f, 0.f}, shortcut[4] = {0.f, 0.f, 0.f, 0.f};
   if (live) {
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
@@ -1456,7 +1457,7 @@ __global__ __launch_bounds__(512) void k_igemm_small(IgemmParams p) {
       if (c >= p.N) continue;
       if (p.bias) { add[e] = p.bias[c]; if constexpr (MODE == OUT_GEGLU) gate[e] = p.bias[c + 32]; }
       if constexpr (MODE == OUT_ROWMAJOR || TRANSPOSED)
-        if (p.rowvec) add[e] += p.rowvec[(size_t)fast_div((unsigned)r, p.div_hw) * p.rowvec_ld + c];
+        if (p.rowvec) (XTRA ? shortcut : add)[e] += p.rowvec[(size_t)fast_div((unsigned)r, p.div_hw) * p.rowvec_ld + c];
       if constexpr (MODE == OUT_ROWMAJOR)
         if (p.residual) add[e] += to_f(((const T*)p.residual)[(size_t)row * p.N + c]);
     }
@@ -1476,7 +1477,7 @@ __global__ __launch_bounds__(512) void k_igemm_small(IgemmParams p) {
   }
   // GN: the normalised pixels in LDS, behind the partial sums
   const int g_pitch = gn_pitch(p.ctot * ES);
-  char* const act = lds + NW * BM * PITCH * 4;
+  char* const act = lds + (XTRA ? 2 : 1) * NW * BM * PITCH * 4;
   unsigned g_at[TM];
   if constexpr (GN) {
     gn_stage<T, HOLD>(p, held, g_gain, g_offset, g_first, g_pixels, g_px, g_channel, g_lo, g_hi, act);
@@ -1549,10 +1550,30 @@ __global__ __launch_bounds__(512) void k_igemm_small(IgemmParams p) {
       if (i0 + s + PF < mine) fetch(s);
     }
   }
-  if constexpr (XTRA)
+  // the sum of these k-tiles, to LDS as wavefront w's; lane: row r16 of row tile i, columns 4 kg .. 4 kg + 3 of column tile j
+  auto hand_over = [&](float* sums, int w) {
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j) {
+        if constexpr (BY_PARTS) acc[i][j] += parts[i][j];
+        *(f32x4*)(sums + w * (BM * PITCH) + (16 * i + r16) * PITCH + 16 * j + 4 * kg) = acc[i][j];
+      }
+  };
+  hand_over(part, wave);
+  float* const part_x = part + NW * BM * PITCH;
+  if constexpr (XTRA) {
+    // the shortcut's sum by itself, as by a launch of its own: k-tiles x, x + NW, ... are wavefront x's there
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j) {
+        acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        if constexpr (BY_PARTS) parts[i][j] = acc[i][j];
+      }
     for (int e = x_first; e < x_tiles; e += NW) {
       if (e > x_first) fetch_extra(e);
-      end_part();
+      if (BY_PARTS && (e / NW) % SUM_TILES == 0) end_part();
 #pragma unroll
       for (int h = 0; h < 2; ++h)
 #pragma unroll
@@ -1560,22 +1581,14 @@ __global__ __launch_bounds__(512) void k_igemm_small(IgemmParams p) {
 #pragma unroll
           for (int j = 0; j < TN; ++j) Mma16<T>::run(xb[j][h], xa[i][h], acc[i][j]);
     }
-  if constexpr (BY_PARTS)
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-      for (int j = 0; j < TN; ++j) acc[i][j] += parts[i][j];
-  // lane: row r16 of row tile i, columns 4 kg .. 4 kg + 3 of column tile j
-#pragma unroll
-  for (int i = 0; i < TM; ++i)
-#pragma unroll
-    for (int j = 0; j < TN; ++j) *(f32x4*)(part + wave * (BM * PITCH) + (16 * i + r16) * PITCH + 16 * j + 4 * kg) = acc[i][j];
+    hand_over(part_x, x_first);
+  }
   __syncthreads();
   if (!live) return;
-  auto total = [&](int r, int c) {                       // four columns of a row, over the wavefronts in order
-    f32x4 v = *(const f32x4*)(part + r * PITCH + c);
+  auto total = [&](const float* sums, int r, int c) {    // four columns of a row, over the wavefronts in order
+    f32x4 v = *(const f32x4*)(sums + r * PITCH + c);
 #pragma unroll
-    for (int w = 1; w < NW; ++w) v += *(const f32x4*)(part + w * (BM * PITCH) + r * PITCH + c);
+    for (int w = 1; w < NW; ++w) v += *(const f32x4*)(sums + w * (BM * PITCH) + r * PITCH + c);
     return v;
   };
   if (by_column) {
@@ -1606,15 +1619,20 @@ __global__ __launch_bounds__(512) void k_igemm_small(IgemmParams p) {
     }
     return;
   }
-  f32x4 v = total(rl, cl);
+  f32x4 v = total(part, rl, cl);
   int ncols = p.N, c_out = col;
   T* dst = (T*)p.out;
   if constexpr (MODE == OUT_GEGLU) {
-    const f32x4 g = total(rl, cl + 32);
+    const f32x4 g = total(part, rl, cl + 32);
 #pragma unroll
     for (int e = 0; e < 4; ++e) v[e] = (v[e] + add[e]) * gelu_f(g[e] + gate[e]);
     ncols = p.N >> 1; c_out = (n0 >> 1) + cl;
   } else {
+    if constexpr (XTRA) {
+      const f32x4 x = total(part_x, rl, cl);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) add[e] += to_f(from_f<T>(x[e] + shortcut[e]));
+    }
 #pragma unroll
     for (int e = 0; e < 4; ++e) v[e] += add[e];
   }
@@ -1667,7 +1685,7 @@ static ad_status run_igemm_small(const IgemmParams& p0, const char* name, hipStr
     if (p0.ln_gain && !p0.gn_groups) return run_igemm_small<T, TM, TN, MODE, NORM_LAYER>(p0, name, s);
   IgemmParams p = p0;
   set_tiles(p, 16 * TM, 16 * TN);
-  constexpr int lds_sums = 8 * 16 * TM * (16 * TN + 4) * 4;
+  constexpr int lds_sums = small_sum_bytes(16 * TM, 16 * TN) * (XTRA ? 2 : 1);
   constexpr int lds_most = NORM == NORM_GROUP ? (int)kLdsLimit : lds_sums + (LN ? 2 * 16 * TM * 4 + small_ktiles(16 * TM, 16 * TN) * kRowBytes / (int)sizeof(T) * 8 : 0);
   const int lds_bytes = lds_sums + (LN ? 2 * 16 * TM * 4 + p.ctot * 8 : NORM == NORM_GROUP ? gn_act_bytes(16 * TM, p.ws, p.ctot * (int)sizeof(T)) : 0);
   if constexpr (lds_most > 65536) {
@@ -2188,7 +2206,7 @@ bool conv_takes_gn(int dtype, int batch, int h, int w, int c0, int c1, int n, in
   const SmallTile t = small_tile(dtype, m, n, (9 * c + xc) / bk, out_mode);
   const int bm = 16 * t.tm;
   return gn_layout(vn, bm, batch, hw, c, groups).slots > 0 && (long long)gn_samples(bm, batch, hw) * hw * c <= 8 * 64 * 40 &&
-         8 * bm * (16 * t.tn + 4) * 4 + gn_act_bytes(bm, w, c * es) <= (int)kLdsLimit;
+         small_sum_bytes(bm, 16 * t.tn) * (xc ? 2 : 1) + gn_act_bytes(bm, w, c * es) <= (int)kLdsLimit;
 }
 
 ad_status launch_conv(const ConvArgs& a, hipStream_t s) {

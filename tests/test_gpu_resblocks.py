@@ -4,8 +4,9 @@ import numpy as np
 import pytest
 import torch
 
+import synthetic_inputs as SI
 from configs import CONFIGS
-from gpu_util import dev, host, nchw_to_nhwc, nhwc_to_nchw, rel_l2
+from gpu_util import DEV, dev, dev_bytes, dev_f32, host, nchw_to_nhwc, nhwc_to_nchw, p, rel_l2, stream_ptr, tdtype
 from paper_2406_06911_amd import binding as B
 from test_gpu_pipeline import Case
 
@@ -57,3 +58,78 @@ def test_shortcut_inside_the_second_convolution(monkeypatch, tile, channels, hei
 def test_weights_in_blocks_in_every_kernel(monkeypatch, dtype, tile, channels, height, width, batch):
     """The kernel families that the test above leaves out read a model's weights in blocks of 32 rows; tiles that end beyond the padded rows."""
     check_blocks(monkeypatch, dtype, tile, channels, height, width, batch, lambda u: True)
+
+
+def from_single_kernels(d, dtype, wts, name, x0, x1, c_out):
+    """A ResBlock from the single-kernel entry points, a launch for every norm and for the shortcut (whose sum passes through the storage type)."""
+    n, h, w, c0 = x0.shape
+    c1 = 0 if x1 is None else x1.shape[3]
+
+    def norm(a, b, part):
+        c = a.shape[3] + (0 if b is None else b.shape[3])
+        out, g, o = torch.empty(n, h, w, c, device=DEV, dtype=tdtype(dtype)), dev_f32(wts[name + part + ".g"]), dev_f32(wts[name + part + ".b"])
+        scratch = torch.zeros(B.lib.ad_groupnorm_scratch_bytes(n, h * w, c) // 4 + 4, device=DEV)
+        B.check(B.lib.ad_groupnorm_forward(dtype, p(a), p(b), a.shape[3], c - a.shape[3], n, h * w, d["gn_groups"], p(g), p(o), 1e-5, 1, p(out), p(scratch), stream_ptr()))
+        torch.cuda.synchronize()
+        return out
+
+    def conv(a, b, part, k, rowvec=None, residual=None):
+        wt = wts[name + part + ".w"]
+        wp, bias = dev_bytes(B.pack_conv_weight(dtype, wt)), np.zeros((c_out + 127) // 128 * 128, np.float32)
+        bias[:c_out] = wts[name + part + ".b"]
+        bias, out = dev_f32(bias), torch.empty(n, h, w, c_out, device=DEV, dtype=tdtype(dtype))
+        cb = 0 if b is None else b.shape[3]
+        ws = B.lib.ad_conv_workspace_bytes(dtype, n, h, w, c_out, a.shape[3] + cb, k, B.OUT_ROWMAJOR)
+        scratch = torch.zeros(max(ws, 16), dtype=torch.uint8, device=DEV)
+        B.check(B.lib.ad_conv_forward(dtype, p(a), p(b), a.shape[3], cb, n, h, w, 0, k, 1, p(wp), c_out, p(bias), p(rowvec), p(residual), p(out), None, None, B.OUT_ROWMAJOR, 0,
+                                      p(scratch) if ws else None, ws, stream_ptr()))
+        torch.cuda.synchronize()
+        return out
+
+    rowvec = dev_f32(np.tile(wts[name + "temb.b"], (n, 1)))           # the time projection's weights are 0
+    y = norm(conv(norm(x0, x1, "gn1"), None, "conv1", 3, rowvec), None, "gn2")
+    short = x0 if c0 + c1 == c_out else conv(x0, x1, "short", 1)
+    return conv(y, None, "conv2", 3, residual=short)
+
+
+# tiles of 16x16, 16x32 and 32x32; the shortcut's k-tiles fewer than, as many as and more than the wavefronts, beginning with each of them; one and two sources
+@pytest.mark.parametrize("dtype,channels,groups,height,width,batch", [
+    (B.AD_BF16, [128, 256], 32, 6, 6, 2), (B.AD_BF16, [64, 128], 32, 24, 24, 2), (B.AD_BF16, [256, 256], 32, 6, 6, 2), (B.AD_BF16, [64, 128], 8, 34, 18, 1), (B.AD_BF16, [192, 128], 32, 6, 6, 2),
+    (B.AD_BF16, [64, 64], 32, 48, 46, 2), (B.AD_BF16, [64, 256], 32, 32, 32, 2), (B.AD_F32, [32, 64], 8, 16, 16, 1), (B.AD_F32, [64, 128], 32, 24, 24, 2), (B.AD_F32, [128, 256], 32, 12, 12, 2),
+    (B.AD_F32, [256, 256], 32, 6, 6, 2), (B.AD_F32, [96, 32], 8, 10, 6, 2), (B.AD_F32, [32, 64], 8, 34, 30, 1)])
+def test_small_tiles_have_the_bits_of_separate_launches(dtype, channels, groups, height, width, batch):
+    d = dict(latent_channels=4, height=height, width=width, batch=batch, channels=channels, layers_per_block=1, transformer_depth=[0, 0], mid_depth=0,
+             head_dim=64, gn_groups=groups, ctx_len=8, ctx_dim=64, pooled_dim=0)
+    probe = B.AsyncDiff(d, 1, 0, 1, dtype)
+    units = probe.units()
+    wts = SI.make_weights(probe.weight_manifest(), std=(9 * channels[0]) ** -0.5, bf16_exact=dtype == B.AD_BF16)
+    probe.close()
+    rng = np.random.default_rng(41)
+    for name in wts:
+        if ".gn" in name:
+            wts[name] = (rng.standard_normal(wts[name].shape) * 0.3 + name.endswith(".g")).astype(np.float32)
+        if name.endswith("temb.w"):
+            wts[name] *= np.float32(0)
+    small = 0
+    for i, u in enumerate(units):
+        if ".res" not in u.name.decode():
+            continue
+        m = B.AsyncDiff(d, 3, 1, 1, dtype, cuts=[i, i + 1])
+        m.allocate(DEV)
+        m.load_weights(wts)
+        m.reset(2)
+        ins, outs = m.component_io(2)
+        text = torch.zeros(batch, 8, 64, device=DEV, dtype=tdtype(dtype))
+        store = {v: dev(rng.standard_normal(m.tensor_shape(v)[0]), dtype) for v in ins}
+        out = {v: torch.full(m.tensor_shape(v)[0], float("nan"), device=DEV, dtype=tdtype(dtype)) for v in outs}
+        m.profile(True)
+        m.component_forward(2, [store[v] for v in ins], 0, text, [out[v] for v in outs], torch.cuda.current_stream())
+        torch.cuda.synchronize()
+        names = [r[0] for r in m.profile_records() if not r[0].startswith(("time", "linear_rows"))]
+        m.close()
+        if any("igemm" in n and not n.endswith("small") for n in names):       # other tiles keep the shortcut's sum in fp32
+            continue
+        small += 1
+        want = from_single_kernels(d, dtype, wts, u.name.decode() + ".", store[i - 1], store[u.skip_from] if u.c_skip else None, u.c_out)
+        assert torch.equal(out[i], want), (u.name, rel_l2(host(out[i]), host(want)), names)
+    assert small >= 2
