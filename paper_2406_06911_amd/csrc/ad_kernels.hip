@@ -2235,9 +2235,15 @@ ad_status launch_conv(const ConvArgs& a, hipStream_t s) {
   p.kt_main = p.Kp / bk;
   p.xw = a.xw; p.x0 = a.x0; p.x1 = a.xc1 ? a.x1 : a.x0; p.xc0 = a.xw ? a.xc0 : 0; p.xc1 = a.xw ? a.xc1 : 0;
   p.xbytes0 = p.xbytes1 = p.xbytes_w = 0;
+  // whether a source of c channels shares no memory with the result: other workgroups may read all of it behind one that has written
+  auto apart = [&](const void* src, int c) {
+    const size_t es = esize(a.dtype), px = (size_t)a.batch * a.hs * a.ws;
+    const char *o = (const char*)a.out, *s0 = (const char*)src;
+    return c == 0 || s0 + px * c * es <= o || o + (size_t)m * a.n_out * (a.out_mode == OUT_TRANSPOSED_F32 ? 4 : es) <= s0;
+  };
   if (a.xw) {
     if (a.ksize != 3 || a.stride != 1 || a.up || a.c1 || a.residual || a.out_mode != OUT_ROWMAJOR || !a.x0 || a.xc0 < bk || a.xc0 % bk || a.xc1 < 0 ||
-        a.xc1 % bk || (a.xc1 > 0 && !a.x1) || !conv_takes_shortcut(a.dtype, m, a.n_out, a.c0, a.xc0 + a.xc1))
+        a.xc1 % bk || (a.xc1 > 0 && !a.x1) || !apart(a.x0, a.xc0) || !apart(a.x1, a.xc1) || !conv_takes_shortcut(a.dtype, m, a.n_out, a.c0, a.xc0 + a.xc1))
       AD_FAIL(AD_ERR_INVALID, "conv: bad shortcut");
     const long long pixels = (long long)a.batch * a.hs * a.ws, es = (long long)esize(a.dtype), wb = (long long)round_up(a.n_out, kNPad) * (a.xc0 + a.xc1) * es;
     if (pixels * std::max(a.xc0, a.xc1) * es >= 0x7fffffffLL || wb >= 0x7fffffffLL) AD_FAIL(AD_ERR_INVALID, "conv: operands of 2 GiB or more are not supported");
@@ -2257,13 +2263,11 @@ ad_status launch_conv(const ConvArgs& a, hipStream_t s) {
   p.ln_gain = a.ln_gain; p.ln_offset = a.ln_offset; p.ln_eps = a.ln_eps;
   p.gn_groups = a.gn_groups;
   if (a.gn_groups) {
-    const char *o = (const char*)a.out, *s0 = (const char*)a.src0, *s1 = (const char*)a.src1;
-    const size_t es = esize(a.dtype), out_bytes = (size_t)m * a.n_out * (a.out_mode == OUT_TRANSPOSED_F32 ? 4 : es), px = (size_t)a.batch * a.hs * a.ws;
-    const bool apart = (s0 + px * a.c0 * es <= o || o + out_bytes <= s0) && (a.c1 == 0 || s1 + px * a.c1 * es <= o || o + out_bytes <= s1);
-    if (!a.ln_gain || !a.ln_offset || a.ksize != 3 || a.stride != 1 || a.up || !apart || ((uintptr_t)s0 & 15) || (a.c1 && ((uintptr_t)s1 & 15)) ||
+    if (!a.ln_gain || !a.ln_offset || a.ksize != 3 || a.stride != 1 || a.up || !apart(a.src0, a.c0) || !apart(a.src1, a.c1) ||
+        (((uintptr_t)a.ln_gain | (uintptr_t)a.ln_offset | (uintptr_t)a.src0 | (a.c1 ? (uintptr_t)a.src1 : 0)) & 15) ||
         !conv_takes_gn(a.dtype, a.batch, a.hs, a.ws, a.c0, a.c1, a.n_out, a.gn_groups, a.out_mode, p.xc0 + p.xc1))
       AD_FAIL(AD_ERR_INVALID, "conv: bad GroupNorm");
-    p.gn = gn_layout(16 / (int)es, 16 * small_tile(a.dtype, m, a.n_out, p.ktiles, a.out_mode).tm, a.batch, p.hw_out, p.ctot, a.gn_groups);
+    p.gn = gn_layout(16 / (int)esize(a.dtype), 16 * small_tile(a.dtype, m, a.n_out, p.ktiles, a.out_mode).tm, a.batch, p.hw_out, p.ctot, a.gn_groups);
     p.gn_inv_n = 1.0 / ((double)p.hw_out * (p.ctot / a.gn_groups));
   }
   if (!a.gn_groups && a.ln_gain && (!a.ln_offset || a.ksize != 1 || a.stride != 1 || a.up || a.c1 || a.residual || a.rowvec || a.xw || (((uintptr_t)a.ln_gain | (uintptr_t)a.ln_offset) & 15) ||

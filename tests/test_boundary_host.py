@@ -4,9 +4,11 @@ import concurrent.futures
 import ctypes
 import os
 import re
+import subprocess
 
 import numpy as np
 import pytest
+import torch
 
 import paper_2406_06911_amd as ad
 from paper_2406_06911_amd import binding as B
@@ -219,6 +221,38 @@ def test_kernel_entry_points_reject_bad_shapes_before_touching_the_gpu():
     ]
     assert all(st == B.AD_ERR_INVALID for st in bad), bad
     assert b"frame attention" in L.ad_last_error() or b"attention" in L.ad_last_error()
+
+
+@pytest.mark.skipif(torch.cuda.is_available(), reason="addresses of nothing: with a GPU a call that is not refused would use them")
+def test_convolution_refuses_what_its_kernels_cannot_do(tmp_path):
+    """Gain and offset of a GroupNorm off a 16-byte boundary, and a result on a source that other workgroups still read: refused by the launcher itself."""
+    program = tmp_path / "refuse.cpp"
+    program.write_text(r"""
+#include "ad_kernels.h"
+#include <cstdio>
+int main() {
+  char* const at = (char*)0x10000000;                    // never dereferenced
+  auto say = [](const char* what, const ad::ConvArgs& a) { std::printf("%s %d\n", what, (int)ad::launch_conv(a, nullptr)); };
+  ad::ConvArgs norm{AD_F32, at, nullptr, 64, 0, 1, 8, 8, 0, 3, 1, at + (1 << 20), 64, nullptr, nullptr, 0, nullptr, at + (2 << 20), ad::OUT_ROWMAJOR, 0};
+  norm.ln_gain = (const float*)(at + (3 << 20)); norm.ln_offset = norm.ln_gain + 64; norm.ln_eps = 1e-5f; norm.gn_groups = 8;
+  ad::ConvArgs block = norm;
+  block.gn_groups = 0; block.ln_gain = block.ln_offset = nullptr;
+  block.x0 = at + (4 << 20); block.xc0 = 64; block.x1 = at + (5 << 20); block.xc1 = 32; block.xw = at + (6 << 20);
+  std::printf("takes %d\n", (int)ad::conv_takes_gn(AD_F32, 1, 8, 8, 64, 0, 64, 8, ad::OUT_ROWMAJOR));
+  std::printf("takes %d\n", (int)ad::conv_takes_shortcut(AD_F32, 64, 64, 64, 96));
+  ad::ConvArgs a = norm; a.ln_gain += 1; say("refused", a);
+  a = norm; a.ln_offset += 2; say("refused", a);
+  a = norm; a.out = at + 64; say("refused", a);
+  a = block; a.x0 = (char*)a.out - 64 * 64 * 4 + 4; say("refused", a);
+  a = block; a.x1 = (char*)a.out + 64 * 64 * 4 - 4; say("refused", a);
+  a = block; a.x1 = a.out; say("refused", a);
+}
+""")
+    exe = str(tmp_path / "refuse")
+    subprocess.run(["g++", "-std=c++17", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", "-I" + os.path.join(ROOT, "include"), "-I" + os.path.join(os.path.dirname(B.lib_path), "csrc"),
+                    str(program), "-o", exe, B.lib_path, "-Wl,-rpath," + os.path.dirname(B.lib_path), "-L/opt/rocm/lib", "-lamdhip64"], check=True)
+    lines = subprocess.run([exe], check=True, capture_output=True, text=True, timeout=60).stdout.split("\n")[:-1]
+    assert lines == ["takes 1"] * 2 + ["refused %d" % B.AD_ERR_INVALID] * 6, lines
 
 
 def test_split_k_scratch_does_not_depend_on_earlier_queries():
