@@ -930,9 +930,10 @@ static ad_status run_igemm_p3(const IgemmParams& p0, const char* name, hipStream
   if (!XTRA && p0.xw) AD_FAIL(AD_ERR_INVALID, "conv: this tile does not take a shortcut");
   IgemmParams p = p0;
   set_tiles(p, BM, BN);
-  constexpr int lds_bytes = KG * NSTAGE * (BM + BN) * kRowBytes + kTouchLds;
-  static_assert(lds_bytes / KG >= WM * WN * stage_bytes<T, BM / WM, BN / WN>(16) && lds_bytes <= (int)kLdsLimit, "epilogue staging fits");
-  static_assert(MODE != OUT_GEGLU || BN / WN / 32 % 2 == 0 || lds_bytes >= WM * WN * stage_bytes<T, BM / WM, BN / WN>(32) + BM * 128, "so does the exchange");
+  // what the epilogue uses ends where the loads of weights ahead land: with two stages and a single k-tile those may still be on their way
+  constexpr int tile_bytes = KG * NSTAGE * (BM + BN) * kRowBytes, lds_bytes = tile_bytes + kTouchLds;
+  static_assert(tile_bytes / KG >= WM * WN * stage_bytes<T, BM / WM, BN / WN>(16) && lds_bytes <= (int)kLdsLimit, "epilogue staging fits");
+  static_assert(MODE != OUT_GEGLU || BN / WN / 32 % 2 == 0 || tile_bytes >= WM * WN * stage_bytes<T, BM / WM, BN / WN>(32) + BM * 128, "so does the exchange");
   static std::atomic<bool> attr_set{false};
   if (!attr_set) {
     AD_HIP(hipFuncSetAttribute((const void*)k_igemm_p3<T, BM, BN, MODE, WM, WN, NSTAGE, KG, XTRA>, hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes));
