@@ -273,6 +273,8 @@ ad_status ad_profile_enable(ad_ctx* ctx, int on);
 ad_status ad_profile_clear(ad_ctx* ctx);
 int ad_profile_count(const ad_ctx* ctx);
 ad_status ad_profile_get(const ad_ctx* ctx, int index, ad_profile_rec* out); /* HOST out */
+/* Manifest index of the weight that the launch of record `index` fetched ahead of the launch behind it, -1: none. */
+int ad_profile_ahead(const ad_ctx* ctx, int index);
 
 /* ---- single kernels (entry points for kernel-level parity tests and measurements) -------------- *
  * All pointers DEVICE; element type `dtype` (ad_dtype) unless stated.  Tensors NHWC. */

@@ -14,6 +14,7 @@ struct ProfRec {
   double bytes;      // algorithmic HBM bytes of the launch
   hipEvent_t start, stop;
   int m = 0, n = 0, k = 0;   // GEMM view of the launch (attention: queries, keys, channels), else 0
+  const void* ahead = nullptr;   // weights of a later launch that it fetched
 };
 struct Profiler {
   bool on = false;
@@ -23,6 +24,7 @@ void set_profiler(Profiler* p);   // per host thread; nullptr removes it
 struct ProfLaunch {
   ProfLaunch(const char* name, double flops, double bytes, hipStream_t s, int m = 0, int n = 0, int k = 0);
   ~ProfLaunch();
+  void fetches(const void* ahead);
   hipEvent_t stop_ = nullptr;
   hipStream_t s_ = nullptr;
 };

@@ -36,6 +36,9 @@ ProfLaunch::ProfLaunch(const char* name, double flops, double bytes, hipStream_t
 ProfLaunch::~ProfLaunch() {
   if (stop_) (void)hipEventRecord(stop_, s_);
 }
+void ProfLaunch::fetches(const void* ahead) {
+  if (stop_) g_prof->recs.back().ahead = ahead;
+}
 
 // =================================================================================================
 // Implicit GEMM:  out[m][n] = sum_k A[m][k] * W[n][k],  m = (batch, oy, ox), k = (tap, channel).
@@ -943,6 +946,7 @@ static ad_status run_igemm_p3(const IgemmParams& p0, const char* name, hipStream
   const double in_bytes = (double)p.M * (p.ctot + xk) * sizeof(T) * (p.stride == 2 ? 4 : 1) / (p.up ? 4 : 1);
   const double out_cols = p.out_mode == OUT_GEGLU ? p.N / 2 : p.N;
   ProfLaunch pl(name, 2.0 * p.M * p.N * (p.k_prof + xk), in_bytes + (double)p.N * (p.Kp + xk) * sizeof(T) + (double)p.M * out_cols * sizeof(T), s, p.M, p.N, p.Kp + xk);
+  if (p.ahead_bytes) pl.fetches(p.ahead);
   const int splits = (p.ktiles + p.kt_per_split - 1) / p.kt_per_split;
   const unsigned waves = (unsigned)(p.tiles_n * p.tiles_m * splits * WM * WN * KG);
   p.ahead_span = (p.ahead_bytes / 128 + waves - 1) / waves * 128;

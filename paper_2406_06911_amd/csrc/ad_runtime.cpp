@@ -424,6 +424,15 @@ ad_status ad_profile_get(const ad_ctx* ctx, int index, ad_profile_rec* out) {
   return AD_OK;
 }
 
+int ad_profile_ahead(const ad_ctx* ctx, int index) {
+  if (!ctx || index < 0 || index >= ad_profile_count(ctx)) return -1;
+  const Ctx& c = *C(ctx);
+  const void* ahead = prof_of(c)->recs[index].ahead;
+  for (size_t i = 0; ahead && i < c.weights.size(); ++i)
+    if (c.weights[i].dev_bytes && c.weights_dev + c.weights[i].dev_off == ahead) return (int)i;
+  return -1;
+}
+
 void ad_destroy(ad_ctx* ctx) {
   if (!ctx) return;
   Ctx* c = C(ctx);
