@@ -40,12 +40,6 @@ void ProfLaunch::fetches(const void* ahead) {
   if (stop_) g_prof->recs.back().ahead = ahead;
 }
 
-// =================================================================================================
-// Implicit GEMM:  out[m][n] = sum_k A[m][k] * W[n][k],  m = (batch, oy, ox), k = (tap, channel).
-// Block tile BM x BN, 4 wavefronts in a 2 x 2 grid, each computing (BM/2) x (BN/2) with 32x32 MFMA
-// tiles.  One k-tile is 128 bytes of K per row (64 bf16 / 32 fp32), staged through LDS with a
-// 16-byte row pad; the next k-tile is fetched into registers while the current one is multiplied.
-// =================================================================================================
 // GN: how the wavefronts of a small-tile convolution hold the samples that they normalise, see gn_stats()
 struct GnLayout {
   int log_vps;                                           // log2 of a wavefront's accesses to a pixel
@@ -56,6 +50,12 @@ struct GnLayout {
   int chained;                                           // threads of k_gn_group have several accesses
 };
 
+// =================================================================================================
+// Implicit GEMM:  out[m][n] = sum_k A[m][k] * W[n][k],  m = (batch, oy, ox), k = (tap, channel).
+// Block tile BM x BN, 4 wavefronts in a 2 x 2 grid, each computing (BM/2) x (BN/2) with 32x32 MFMA
+// tiles.  One k-tile is 128 bytes of K per row (64 bf16 / 32 fp32), staged through LDS with a
+// 16-byte row pad; the next k-tile is fetched into registers while the current one is multiplied.
+// =================================================================================================
 struct IgemmParams {
   const void* src0; const void* src1;
   int c0, c1, ctot;
@@ -2089,7 +2089,7 @@ static int best_band(long long m, int n, const DmaTile& t, int splits) {
 // makes at most a workgroup per CU, as long as a workgroup takes in at most 200 KiB (beyond that the 60 GB/s a CU gets from memory
 // decide, and K split over workgroups wins: 3x3 72x192x5760 13 us against 11).  GEGLU pairs 32 value with 32 gate columns.
 // fp32: at most 600 KiB, since what is left to split K over workgroups are register-staged tiles of 64 or 128 rows on matrix cores of a sixteenth of the rate, which
-// multiply mostly padding.  3x3, us (those and their second pass / this): 18x256x2304 27.1 / 10.1, 72x256x2304 27.6 / 11.4, 18x256x4608 29.5 / 16.6, 288x256x2304 28.2 / 15.6,
+// multiply mostly padding.  3x3, us (those and their second pass / this): 18x256x2304 27.1 / 11.1, 72x256x2304 27.6 / 11.7 and 18x256x4608 29.5 / 16.6 with the norm inside, 288x256x2304 28.2 / 15.6,
 // 512x128x3456 30.4 / 15.4, 1152x128x3456 21.8 / 21.4; linear: 180x1280x1280 18.8 / 14.6.  1200 KiB: 288x256x4608 31.3 / 26.6, but 1152x128x3456
 // in tiles of 32x32 21.8 / 27.4.
 constexpr int kSmallF32 = 600 * 1024;
@@ -3712,7 +3712,7 @@ __global__ __launch_bounds__(NT) void k_gn_group(const T* __restrict__ src0, con
   for (int e = 0; e < G; ++e) { ga[e] = p_end ? gamma[c + e] : 0.f; be[e] = p_end ? beta[c + e] : 0.f; }
   // The mean first, to the 12 leading bits (x less it is then exact but for a few elements), then the sums of the deviations from it and of
   // their squares: nothing cancels whatever the offset and the outliers.  The wavefronts' sums are folded in double, as in the two
-  // launches.
+  // launches.  gn_stats() keeps to this order of the sums.
   float s = 0.f, q = 0.f;
 #pragma unroll
   for (int k = 0; k < NV; ++k)

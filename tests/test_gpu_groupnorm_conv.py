@@ -140,7 +140,7 @@ def test_a_block_whose_result_overwrites_its_input(dtype, channels, height, widt
     both[:x.numel()] = x
     same = run(both, both)
     m.close()
-    # the shortcut's sum passes through the storage type in the separate launches: one rounding (2^-9 of a value) and what follows from it
+    # one rounding of the shortcut's sum to the storage type (2^-9 of a value) and what follows from it; the small tiles round it as the separate launches do
     assert rel_l2(same.numpy(), apart.numpy()) < (4e-3 if dtype == B.AD_BF16 else 1e-6)
 
 
@@ -160,7 +160,7 @@ def test_an_input_between_two_accesses(dtype):
     want, _ = head(d, dtype, at16, gain, offset, w, bias)
     got, names = head(d, dtype, moved, gain, offset, w, bias)
     assert any(n.startswith("gn_") for n in names), names
-    # other order of the sums of the statistics: fp32 roundings, and the few bf16 operands that these move
+    # fp32 roundings, and the few bf16 operands that these move, were the sums of the statistics taken in another order
     assert rel_l2(got, want) < (5e-4 if dtype == B.AD_BF16 else 3e-6)
 
 
